@@ -15,6 +15,7 @@
 // to the instructions its sum needs, reads operands that all threads have laid side by side in LDS,
 // and leaves products, divisions, comparisons and counting to all threads or to wavefront ballots.
 //
+// gather_columns_kernel  the columns of every codebook side by side, rows aligned
 // Per level t = 1..4 of all C trees at once:
 //   order_rows_kernel    the rows of every bucket listed in row order, the bucket sizes
 //   bucket_loss_kernel   L(j, B) (Section 4.2) for every column j of every bucket, two passes
@@ -23,11 +24,11 @@
 //   key_kernel, sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column (bitonic sort of
 //                        (value, row) keys: equal values stay in row order, as a stable sort
 //                        of a bucket's rows leaves them)
-//   split_ordered_kernel (split_kernel for the widest subspaces)  Algorithm 3 for every bucket of
-//                        the level in one forward and one backward sweep over that order
-//                        (Algorithm 4's running sums kept per bucket), the best threshold and
-//                        loss per bucket
-//   choose_kernel        Algorithm 2's choice among the candidates
+//   split_chains_kernel, judge_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
+//                        running sums at every 32nd row in both directions, then the loss of
+//                        every split, a wavefront per 256 rows
+//   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
+//                        candidates
 //   apply_kernel         apply_split: the next level's buckets
 // Prototypes: cooccurrence_kernel (G^T G), gta_kernel (G^T A~), cholesky_panel_kernel,
 // factor by rows, substitution_kernel; or means_kernel.
@@ -38,17 +39,7 @@ namespace {
 
 constexpr int kSplitBuckets = 8;   // buckets of the deepest level that is split (level 4 splits 8)
 constexpr int kCand = 4;           // candidate columns per level (Section 4.2: n = 4)
-constexpr int kMaxTile = 256;      // most sorted positions a workgroup of split_ordered_kernel takes at a time (a thread each)
-constexpr int kSplitTile = 64;     // sorted positions a workgroup of split_kernel takes at a time
 constexpr int kSortChunk = 8192;   // keys sorted in LDS at a time (64 KiB)
-
-// LDS of split_kernel for subspaces of d columns and tiles of T positions (a multiple of 8 bytes)
-__host__ __device__ constexpr size_t split_lds_bytes_base(int d, int T)
-{
-    return sizeof(double) * ((size_t)T * d + 2 * (size_t)kSplitBuckets * d + T) + sizeof(float) * (size_t)T * (d + 2) +
-           sizeof(int32_t) * 3 * T + kSplitBuckets * (3 * sizeof(double) + 3 * sizeof(float) + 3 * sizeof(int32_t)) +
-           T * (sizeof(double) + sizeof(float)) + sizeof(int32_t) * ((size_t)T + 6 * kSplitBuckets);
-}
 
 struct Bounds {
     int32_t v[2 * MADDNESS_MAX_C];
@@ -59,6 +50,8 @@ struct LearnArgs {
     int64_t lda, N, Npad;
     int32_t C, dmax;
     int32_t *bounds;      // [C][2] first and one-past-last column of every codebook
+    int32_t pitch;        // values of a row of X: dmax rounded up to whole groups of columns
+    float *X;             // [C][N + 1][pitch] the codebook's columns of A, then zeros; row N is zeros
     uint8_t *node;        // [C][N] bucket (0-based) of every row in the current level
     double *col_loss;     // [C][8][dmax] L(j, B_i)
     double *bucket_loss;  // [C][8] L(B_i)
@@ -68,9 +61,12 @@ struct LearnArgs {
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
     uint64_t *keys;       // [C][4][Npad] sorted (value, row) keys
-    double *head;         // [C][4][N] Algorithm 4, forward, by sorted position
-    double *res_loss;     // [C][4][8] loss of the best split of bucket i along candidate q
-    float *res_v;         // [C][4][8] its threshold
+    int64_t tile_slots;   // tiles of kJudgeRows sorted rows of all buckets of a level, at most
+    double *sums;         // [C][4][2][tile_slots][2][dmax] Algorithm 4's running sums before every tile, up and down
+    int64_t group_slots;  // groups of kGroupTiles tiles of all buckets of a level, at most
+    double *group_loss;   // [C][4][group_slots] loss of the group's best split
+    int32_t *group_at;    // [C][4][group_slots][2] the bucket's row it comes after (-1: none); the group's first split
+                          // if its loss is not a number (else -1)
     int32_t *chosen;      // [C] the level's column (within the subspace)
     int32_t *split_dims;  // out [C][4]
     float *thresholds;    // out [C][16]
@@ -86,6 +82,22 @@ __global__ void fill_bytes_kernel(uint8_t *p, int64_t n, uint8_t v)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
+}
+
+// The columns of every codebook side by side, each row on a 32-byte (or 64-byte) boundary.  The levels read the rows of a
+// bucket in many orders, a codebook's columns at a time: from here they take whole 16-byte pieces, and the rows of a
+// codebook fit in an XCD's L2 where A does not.  A thread per 16-byte piece.
+__global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
+{
+    const int c = blockIdx.y, pieces = a.pitch / 4;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t row = i / pieces;
+    if (row > a.N) return;
+    const int col = 4 * (int)(i - row * pieces), lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = row < a.N && col + e < d ? a.A[row * a.lda + lo + col + e] : 0.0f;
+    reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch)[i] = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // The rows of every bucket, in row order (a stable counting sort of the rows by bucket): rows_by_bucket[c]
@@ -143,150 +155,153 @@ __global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int 
     }
 }
 
-// L(j, B_i): a thread per column of the subspace - a chain - takes the bucket's rows in row order, twice (the
-// sum, then the squared distances from the mean); one workgroup per (codebook, bucket).  The chains are the
-// serial part and a wavefront issues a vector instruction in four cycles, so they are kept short: all threads
-// of the workgroup gather the next rows' values into LDS, a column's values side by side, while the chains
-// walk the rows gathered before, four rows to an LDS read.  (The list of rows is fetched two tiles ahead, the
-// values one tile ahead.)
-constexpr int kLossTileFloats = 8192;      // values of a tile (32 KiB), two tiles in LDS
-constexpr int kLossTileRows = 512;         // most rows of a tile
-constexpr int kLossPer = kLossTileFloats / 256;
-constexpr int kLossMaxWidth = 128;         // widest subspace its LDS tiles are laid out for
-__host__ __device__ constexpr int loss_tile_rows(int d)
-{
-    return kLossTileFloats / d >= kLossTileRows ? kLossTileRows : (kLossTileFloats / d) & ~15;
-}
-constexpr size_t kLossTileStride = kLossTileFloats + 4 * kLossMaxWidth + 8;     // floats between the two tiles
-constexpr size_t kLossLdsBytes = sizeof(float) * 2 * kLossTileStride + sizeof(int32_t) * 2 * kLossTileRows;
+// The serial sums.  A sum in a given order is one dependent addition per row, and what else is done per row decides how
+// near the kernel comes to the adder's latency (5.2 cycles).  A chain sits in a row of 16 lanes of a wavefront: each lane
+// holds one of 16 consecutive terms, and v_fmac_f64 with a row broadcast adds them one after the other (times 1.0, which
+// rounds as an addition does) without any data movement between the additions; four chains to a wavefront.  (A lane per
+// chain that reads its terms from LDS takes twice as long, 12.4 against 6.5 cycles per term for one wavefront.)
+// The other wavefronts of the workgroup (helpers) fetch the rows several tiles ahead, NC columns of each, 16 bytes per
+// lane, and lay the values out by column in LDS.
+constexpr int kChainRows = 256;                              // rows staged at a time (a tile)
+constexpr int kChainHelpers = 256;                           // threads that fetch them: one lists a row of a tile
+constexpr int kDepth = 4;                                    // tiles whose values are on their way at a time
+constexpr int kLists = 8;                                    // lists of row numbers in LDS (a power of two > kDepth + 1)
+constexpr int kChainPitch = kChainRows + 4;                  // (a wavefront's writes, 16 rows of every fourth column, meet in no bank)
+constexpr int kMaxWidth = 128;                               // widest subspace
+static_assert(kChainHelpers == kChainRows, "a helper lists one row of every tile");
 
-__global__ __launch_bounds__(256) void bucket_loss_kernel(const LearnArgs a)
+#define MADDNESS_ADD_TERM(k) "v_fmac_f64_dpp %0, %1, %2 row_newbcast:" #k " row_mask:0xf bank_mask:0xf\n\t"
+// acc += the 16 terms of the lane's row of 16 lanes, first lane's first
+__device__ __forceinline__ void add_16_in_order(double &acc, double term, double one)
 {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    float *xt = reinterpret_cast<float *>(lds_raw);                                   // [2][kLossTileStride]
-    int32_t *listed = reinterpret_cast<int32_t *>(xt + 2 * kLossTileStride);          // [2][kLossTileRows]
-    const int c = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
-    const int lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
-    const int R = loss_tile_rows(d), Rp = R + 4;       // (columns R + 4 floats apart: 16-byte reads, and the banks spread)
-    const int64_t count = a.bucket_count[c * kSplitBuckets + b];
-    const int32_t *list = a.rows_by_bucket + (size_t)c * a.N + a.bucket_start[c * kSplitBuckets + b];
-    const float *cols = a.A + lo;
-    const int64_t n_tiles = (count + R - 1) / R;
-    const int jj = tid < d ? tid : 0;
-    // what this thread gathers of a tile: elements tid + 256 u of its R x d values; (row, column) of the first,
-    // and the step from one to the next
-    const int row_first = tid / d, col_first = tid - row_first * d, row_step = 256 / d, col_step = 256 - row_step * d;
-    float pre[kLossPer];
-    int32_t pre_rows[kLossTileRows / 256];
-    auto fetch_list = [&](int64_t tile) __attribute__((always_inline)) {
+    // (a register that a vector instruction has written may be broadcast two cycles later)
+    asm("s_nop 1\n\t" MADDNESS_ADD_TERM(0) MADDNESS_ADD_TERM(1) MADDNESS_ADD_TERM(2) MADDNESS_ADD_TERM(3)
+        MADDNESS_ADD_TERM(4) MADDNESS_ADD_TERM(5) MADDNESS_ADD_TERM(6) MADDNESS_ADD_TERM(7) MADDNESS_ADD_TERM(8)
+        MADDNESS_ADD_TERM(9) MADDNESS_ADD_TERM(10) MADDNESS_ADD_TERM(11) MADDNESS_ADD_TERM(12) MADDNESS_ADD_TERM(13)
+        MADDNESS_ADD_TERM(14) MADDNESS_ADD_TERM(15)
+        : "+v"(acc)
+        : "v"(term), "v"(one));
+}
+#undef MADDNESS_ADD_TERM
+
+// The chains' part of a tile: `at` is the lane's first value (its 16th of the column's), term(x, i) the term of value x in
+// row i of the lane's; before(k) runs before every 32nd row.
+template <typename Term, typename Before>
+__device__ __forceinline__ void add_tile_in_order(double &acc, const float *at, Term term, Before before)
+{
+    double one = 1.0;
+    asm("" : "+v"(one));
+    float x[kChainRows / 16];
 #pragma unroll
-        for (int u = 0; u < kLossTileRows / 256; ++u) {
-            const int64_t at = tile * R + tid + 256 * u;
-            pre_rows[u] = (tid + 256 * u < R && at < count) ? list[at] : 0;
+    for (int i = 0; i < kChainRows / 16; ++i) x[i] = at[16 * i];
+#pragma unroll
+    for (int i = 0; i < kChainRows / 16; ++i) {
+        if (i % 2 == 0) before(i / 2);
+        add_16_in_order(acc, term(x[i], 16 * i), one);
+    }
+}
+
+// The workgroup's loop: n_steps tiles of kChainRows rows.  walk(values of tile s, s) runs on the first kWalkers
+// wavefronts; meanwhile the helpers lay out tile s + 1, fetch the values of tile s + kDepth + 1 and list the rows of the
+// tile after that (row_at(s, i): the number of row i of tile s, `N` where there is none), whose numbers they asked for
+// kDepth steps before.  X: the codebook's values, from the workgroup's first column on.
+template <int NC>
+constexpr size_t stream_lds_bytes() { return sizeof(float) * 2 * NC * kChainPitch + sizeof(int32_t) * kLists * kChainRows; }
+
+template <int NC, int kWalkers, typename RowAt, typename Walk>
+__device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, int pitch, int n_steps, RowAt row_at, Walk walk)
+{
+    constexpr int kPieces = NC / 4, kStride = kChainHelpers / kPieces, kPer = kChainRows / kStride, kBuffer = NC * kChainPitch;
+    float *values = reinterpret_cast<float *>(lds);                        // [2][NC][kChainPitch]
+    int32_t *listed = reinterpret_cast<int32_t *>(values + 2 * kBuffer);   // [kLists][kChainRows]
+    const int helper = (int)threadIdx.x - 64 * kWalkers, at = helper < 0 ? 0 : helper;
+    const int rsub = at / kPieces, piece = at % kPieces;
+    const float *src = X + 4 * piece;
+    float4 x[kDepth][kPer];
+    int32_t next[kDepth];
+    auto fetch = [&](int s, int set) __attribute__((always_inline)) {
+        const int32_t *rows = listed + (s % kLists) * kChainRows;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            x[set][u] = *reinterpret_cast<const float4 *>(src + (uint64_t)(uint32_t)rows[rsub + u * kStride] * (uint32_t)pitch);
+    };
+    auto stash = [&](int s, int set) __attribute__((always_inline)) {
+        float *dst = values + (s & 1) * kBuffer + 4 * piece * kChainPitch + rsub;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            dst[u * kStride] = x[set][u].x;
+            dst[u * kStride + kChainPitch] = x[set][u].y;
+            dst[u * kStride + 2 * kChainPitch] = x[set][u].z;
+            dst[u * kStride + 3 * kChainPitch] = x[set][u].w;
         }
     };
-    auto stash_list = [&](int64_t tile) __attribute__((always_inline)) {
+    if (helper >= 0)
 #pragma unroll
-        for (int u = 0; u < kLossTileRows / 256; ++u)
-            if (tid + 256 * u < R) listed[(tile & 1) * kLossTileRows + tid + 256 * u] = pre_rows[u];
-    };
-    auto fetch = [&](int64_t tile) __attribute__((always_inline)) {
-        const int32_t *rows = listed + (tile & 1) * kLossTileRows;
-        const int64_t left = count - tile * R;
-        int row = row_first, col = col_first;
+        for (int s = 0; s < kDepth + 2; ++s) listed[(s % kLists) * kChainRows + helper] = row_at(s, helper);
+    __syncthreads();
+    if (helper >= 0) {
+        fetch(0, 0);
+        stash(0, 0);
 #pragma unroll
-        for (int u = 0; u < kLossPer; ++u) {
-            pre[u] = (row < R && row < left) ? cols[(int64_t)rows[row] * a.lda + col] : 0.0f;
-            row += row_step;
-            col += col_step;
-            if (col >= d) {
-                col -= d;
-                ++row;
-            }
+        for (int s = 1; s <= kDepth; ++s) {
+            fetch(s, s % kDepth);
+            next[s - 1] = row_at(s + kDepth + 1, helper);
         }
-    };
-    auto stash = [&](int64_t tile) __attribute__((always_inline)) {
-        float *dst = xt + (tile & 1) * kLossTileStride;
-        int row = row_first, col = col_first;
+    }
+    __syncthreads();
+    for (int s0 = 0; s0 < n_steps; s0 += kDepth) {
 #pragma unroll
-        for (int u = 0; u < kLossPer; ++u) {
-            if (row < R) dst[col * Rp + row] = pre[u];
-            row += row_step;
-            col += col_step;
-            if (col >= d) {
-                col -= d;
-                ++row;
+        for (int i = 0; i < kDepth; ++i) {
+            const int s = s0 + i;
+            if (s >= n_steps) break;
+            if (helper < 0) {
+                walk(values + (s & 1) * kBuffer, s);
+            } else {
+                stash(s + 1, (i + 1) % kDepth);
+                fetch(s + 1 + kDepth, (i + 1) % kDepth);
+                listed[((s + kDepth + 2) % kLists) * kChainRows + helper] = next[i];
+                next[i] = row_at(s + 2 * kDepth + 2, helper);
             }
-        }
-    };
-    double sum = 0.0, mean = 0.0, loss = 0.0;
-    auto walk = [&](auto second) __attribute__((always_inline)) {
-        constexpr bool kSecond = decltype(second)::value;
-        __syncthreads();
-        fetch_list(0);
-        stash_list(0);
-        fetch_list(1);
-        __syncthreads();
-        fetch(0);
-        stash(0);
-        stash_list(1);
-        __syncthreads();
-        for (int64_t tile = 0; tile < n_tiles; ++tile) {
-            if (tile + 2 < n_tiles) fetch_list(tile + 2);
-            if (tile + 1 < n_tiles) fetch(tile + 1);
-            if (tid < d) {
-                const float *xs = xt + (tile & 1) * kLossTileStride + jj * Rp;
-                const int64_t left = count - tile * R;
-                const int rows_here = (int)(left < R ? left : R);
-                // eight rows at a time, the eight after them read from LDS meanwhile (the fences keep the compiler
-                // from moving the reads back to where their values are used)
-                float x0[8], x1[8];
-                auto read = [&](int row, float *x) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) x[u] = xs[row + u];
-                };
-                auto add = [&](const float *x) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        if constexpr (!kSecond) {
-                            sum += (double)x[u];
-                        } else {
-                            const double e = (double)x[u] - mean;
-                            loss += e * e;
-                        }
-                    }
-                };
-                const int full = rows_here & ~15;
-                read(0, x0);
-                for (int row = 0; row < full; row += 16) {
-                    read(row + 8, x1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    add(x0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    read(row + 16, x0);            // (past the tile's last row at the end: read, not used)
-                    __builtin_amdgcn_sched_barrier(0);
-                    add(x1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                for (int row = full; row < rows_here; ++row) {
-                    const double x = (double)xs[row];
-                    if constexpr (!kSecond) {
-                        sum += x;
-                    } else {
-                        const double e = x - mean;
-                        loss += e * e;
-                    }
-                }
-            }
-            if (tile + 1 < n_tiles) stash(tile + 1);
-            if (tile + 2 < n_tiles) stash_list(tile + 2);
             __syncthreads();
         }
+    }
+}
+
+// L(j, B_i): the sum, then the squared distances from the mean, over the bucket's rows in row order, a chain per
+// column, up to NC columns of a bucket to a workgroup.  (Measured, level 1 of 260100 x 27 with 4 codebooks, two sums of
+// 260100 rows: 1.6 ms, 3 ns a row; 7.1 ms with a lane per chain that read and converted its values itself.  The four
+// levels: 3.3 against 14.6 ms, and 0.39 against 1.75 ms for 20000 x 512 with 32 codebooks.)
+template <int NC>
+__global__ __launch_bounds__(16 * NC + kChainHelpers) void bucket_loss_kernel(const LearnArgs a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int c = blockIdx.x, b = blockIdx.y, col0 = blockIdx.z * NC;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (col0 >= d) return;
+    const int count = (int)a.bucket_count[c * kSplitBuckets + b];
+    const int32_t *list = a.rows_by_bucket + (size_t)c * a.N + a.bucket_start[c * kSplitBuckets + b];
+    const int n_steps = (count + kChainRows - 1) / kChainRows;
+    const int tid = threadIdx.x, cols = min(NC, d - col0);
+    const int chain = (tid / 16) % NC, l = tid & 15;
+    const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
+    auto row_at = [&](int s, int i) __attribute__((always_inline)) {
+        const int p = s * kChainRows + i;
+        return p < count ? list[p] : (int32_t)a.N;
     };
-    walk(std::false_type{});
-    mean = count > 0 ? sum / (double)count : 0.0;
-    walk(std::true_type{});
-    if (tid < d) a.col_loss[((size_t)c * kSplitBuckets + b) * a.dmax + jj] = count > 0 ? loss : 0.0;
+    double sum = 0.0, loss = 0.0;
+    stream_rows<NC, NC / 4>(lds_raw, X, a.pitch, n_steps, row_at, [&](const float *values, int) __attribute__((always_inline)) {
+        add_tile_in_order(sum, values + chain * kChainPitch + l, [](float x, int) { return (double)x; }, [](int) {});
+    });
+    const double mean = count > 0 ? sum / (double)count : 0.0;
+    stream_rows<NC, NC / 4>(lds_raw, X, a.pitch, n_steps, row_at, [&](const float *values, int s) __attribute__((always_inline)) {
+        const int left = count - s * kChainRows - l;
+        add_tile_in_order(loss, values + chain * kChainPitch + l, [&](float x, int row) __attribute__((always_inline)) {
+            const double e = (double)x - mean;
+            return row < left ? e * e : 0.0;          // (adding 0 leaves a sum as it is)
+        }, [](int) {});
+    });
+    if (tid < 16 * NC && l == 0 && chain < cols)
+        a.col_loss[((size_t)c * kSplitBuckets + b) * a.dmax + col0 + chain] = count > 0 ? loss : 0.0;
 }
 
 // heuristic_select_idxs, and L(B_i) = sum over the columns of L(j, B_i).
@@ -339,15 +354,15 @@ __device__ __forceinline__ float key_value(uint64_t key)
 }
 __device__ __forceinline__ int32_t key_row(uint64_t key) { return (int32_t)(key & ((1u << kKeyRowBits) - 1u)); }
 
-__global__ __launch_bounds__(256) void key_kernel(const LearnArgs a, int by_bucket)
+__global__ __launch_bounds__(256) void key_kernel(const LearnArgs a)
 {
     const int c = blockIdx.z, q = blockIdx.y;
     if (q >= a.n_cand[c]) return;
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= a.Npad) return;
-    const int j = a.bounds[2 * c] + a.cand[c * kCand + q];
+    const int j = a.cand[c * kCand + q];
     a.keys[((size_t)c * kCand + q) * a.Npad + p] =
-        p < a.N ? make_key(by_bucket ? a.node[(size_t)c * a.N + p] : 0, a.A[p * a.lda + j], (uint32_t)p) : ~0ull;
+        p < a.N ? make_key(a.node[(size_t)c * a.N + p], a.X[((size_t)c * (a.N + 1) + p) * a.pitch + j], (uint32_t)p) : ~0ull;
 }
 
 // Bitonic sort of Npad keys (a power of two) per (codebook, candidate).  The exchanges at distances below
@@ -402,485 +417,287 @@ __global__ __launch_bounds__(256) void sort_exchange_kernel(const LearnArgs a, i
     }
 }
 
-// Algorithm 3 for all buckets of the level along candidate q of codebook c.
-// Forward sweep over the sorted rows: Algorithm 4's running sums per bucket and column, the
-// SSE of the bucket's rows so far (head) stored by position.  Backward sweep: the same from
-// the other end (tail); at a row of bucket i the split between it and the bucket's next row
-// up is judged by head + tail, if their values differ.  Going down, a loss that is not larger
-// replaces the best: the first minimum in ascending order wins.
-// kSplitTile positions at a time (a tile): a thread per position fetches its row's bucket and values into LDS, the
-// running sums are carried through the tile in order by a thread per column, then summed over the columns (in
-// column order) by one thread per position.  This kernel takes the subspaces too wide for split_ordered_kernel.
-__global__ __launch_bounds__(256) void split_kernel(const LearnArgs a, int n_buckets)
+// Algorithm 3 in two parts.  Algorithm 4's running sums are the one serial thing in it, and a serial sum costs a
+// few cycles per row whatever else is done with it, so split_chains_kernel does nothing but add: a chain per
+// (candidate, bucket, direction, column, which of the two sums) walks the bucket's rows in sorted order and leaves its
+// value at every kJudgeRows-th of them.  judge_kernel takes it up from there, tile by tile of kJudgeRows rows: it
+// repeats the few additions in between (the same operations on the same operands), and does the products, divisions,
+// differences and comparisons of its rows, all tiles of all buckets at once.  (Measured, the four levels of
+// 20000 x 512 with 32 codebooks and of 260100 x 27 with 4: 0.67 + 0.45 and 2.36 + 0.42 ms for the two kernels; 4.8 and
+// 34.8 ms as one kernel that did all of it tile after tile.)
+constexpr int kJudgeRows = 32;
+constexpr int kGroupTiles = 8, kGroupRows = kGroupTiles * kJudgeRows;     // tiles that a wavefront of judge_kernel takes
+
+// the first of the tile slots of a bucket (count rows beginning at `start` take up to count / kJudgeRows + 1 of them)
+__device__ __forceinline__ int64_t first_slot(int32_t start, int bucket) { return start / kJudgeRows + bucket; }
+__device__ __forceinline__ int64_t first_group(int32_t start, int bucket) { return start / kGroupRows + bucket; }
+
+// The chains are those of bucket_loss_kernel, both sums of up to NC columns to a workgroup.  Going down (direction 1)
+// the tiles are taken last to first, each from its end; what lies past the bucket's last row counts as zeros, which
+// leave a sum as it is.
+template <int NC>
+__global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(const LearnArgs a)
 {
-    constexpr int T = kSplitTile;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int c = blockIdx.y, q = blockIdx.x;
+    // (the codebook changes fastest from workgroup to workgroup: those of one codebook meet on few XCDs)
+    const int c = blockIdx.x, b = blockIdx.z, dir = blockIdx.y & 1, q = (blockIdx.y >> 1) & 3, col0 = (blockIdx.y >> 3) * NC;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (q >= a.n_cand[c] || col0 >= d) return;
+    const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
+    const int n_tiles = (count + kJudgeRows - 1) / kJudgeRows;
+    if (n_tiles == 0) return;
+    constexpr int kTiles = kChainRows / kJudgeRows;
+    const int n_steps = (n_tiles + kTiles - 1) / kTiles;
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+    const int tid = threadIdx.x, cols = min(NC, d - col0);
+    const int chain = (tid / 16) % (2 * NC), l = tid & 15;
+    const bool squares = chain >= NC;
+    // where the chain's values go: the sums before tile i (of all rows before it, in the direction's order)
+    double *out = a.sums + (((size_t)c * kCand + q) * 2 + dir) * a.tile_slots * (2 * a.dmax) +
+                  (size_t)first_slot(start, b) * (2 * a.dmax) + (chain / NC) * a.dmax + col0 + chain % NC;
+    const bool stored = l == 0 && chain % NC < cols;
+    double acc = 0.0;
+    stream_rows<NC, NC / 2>(
+        lds_raw, a.X + (size_t)c * (a.N + 1) * a.pitch + col0, a.pitch, n_steps,
+        [&](int s, int i) __attribute__((always_inline)) {
+            const int tile = kTiles * s + i / kJudgeRows, in_tile = i % kJudgeRows;
+            const int p = dir ? (n_tiles - 1 - tile) * kJudgeRows + kJudgeRows - 1 - in_tile : tile * kJudgeRows + in_tile;
+            if (tile >= n_tiles || p >= count) return (int32_t)a.N;
+            return (int32_t)(static_cast<uint32_t>(keys[p]) & ((1u << kKeyRowBits) - 1u));
+        },
+        [&](const float *values, int s) __attribute__((always_inline)) {
+            add_tile_in_order(acc, values + (chain % NC) * kChainPitch + l,
+                              [&](float x, int) __attribute__((always_inline)) {
+                                  const double v = (double)x;
+                                  return squares ? v * v : v;
+                              },
+                              [&](int t) __attribute__((always_inline)) {
+                                  const int tile = kTiles * s + t;
+                                  if (stored && tile < n_tiles) out[(size_t)(dir ? n_tiles - 1 - tile : tile) * (2 * a.dmax)] = acc;
+                              });
+        });
+}
+
+// A wavefront per kGroupTiles tiles of kJudgeRows sorted rows of a bucket, one tile after the other with the next one's
+// rows on their way: both running sums of every column and both directions from the values that split_chains_kernel
+// left at the tile's ends, a lane per (direction, sum, column); then Algorithm 4's term of every column, summed over the
+// columns in column order, a lane per (direction, row); then the loss of the split between every row and the next one
+// up, and the best of them (the first of equal ones).
+// Bound by the vector ALUs: cx cx / n takes one division per row for all its columns, y = 1 / n, and per column a product
+// q = t y and one correction q + (t - n q) y by fused multiply-adds.  That is the correctly rounded quotient, as a
+// division gives it: q is off by less than 1.5 ulp and n < 2^29 is whole, so the remainder is exact; what remains
+// is off by less than 2^-52 ulp before the last rounding, and t / n is either a double or at least ulp / 2^30 from
+// the middle between two (n times such a middle has 54 significant bits or more, t has 53 at most).
+// (A loss that is not a number, from data with infinities, gives way to one that is.)
+__device__ __forceinline__ bool better(double l2, int at2, double loss, int at)
+{
+    return at2 >= 0 && (at < 0 || l2 < loss || (loss != loss && l2 == l2) || ((l2 == loss || (l2 != l2 && loss != loss)) && at2 < at));
+}
+
+template <int NC>
+__global__ __launch_bounds__(64) void judge_kernel(const LearnArgs a, int n_buckets)
+{
+    constexpr int T = kJudgeRows, kPitch = T + 4, kSumPitch = T + 1, kChains = 4 * NC;
+    constexpr int kPieces = NC / 4, kRows = 64 / kPieces, kPer = T / kRows;
+    __shared__ __align__(16) double sums[kChains][kSumPitch];
+    __shared__ __align__(16) float xs[2][NC][kPitch];       // the tile's values, first to last and last to first
+    const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x;
     if (q >= a.n_cand[c]) return;
-    const int lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
-    const int jsplit = a.cand[c * kCand + q];
-    const int tid = threadIdx.x;
-    const int64_t N = a.N;
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
-    const uint8_t *node = a.node + (size_t)c * N;
-    double *head = a.head + ((size_t)c * kCand + q) * N;
-
-    double *term = reinterpret_cast<double *>(lds_raw);            // [T][d]
-    double *cumX = term + (size_t)T * d;                       // [8][d]
-    double *cumX2 = cumX + (size_t)kSplitBuckets * d;              // [8][d]
-    double *sse = cumX2 + (size_t)kSplitBuckets * d;               // [T]
-    float *xt = reinterpret_cast<float *>(sse + T);            // [T][d]
-    // (rows of xt are xld = d | 1 floats apart: an odd pitch, so that the threads of a wavefront, a slot each,
-    // write their rows without meeting in the same LDS banks; the area holds T (d + 2) floats, a whole number
-    // of 8 bytes)
-    const int xld = d | 1;
-    int32_t *rows = reinterpret_cast<int32_t *>(xt + (size_t)T * (d + 2));   // [T]
-    int32_t *bkt = rows + T;                                   // [T]
-    int32_t *cnt_at = bkt + T;                                 // [T] rows of the bucket up to this one
-    // per bucket: rows seen in this sweep; the best split so far; the bucket's row above the current one
-    int64_t *count = reinterpret_cast<int64_t *>(cnt_at + T);
-    double *best_loss = reinterpret_cast<double *>(count + kSplitBuckets), *up_tail = best_loss + kSplitBuckets;
-    float *best_lo = reinterpret_cast<float *>(up_tail + kSplitBuckets), *best_hi = best_lo + kSplitBuckets;
-    float *up_value = best_hi + kSplitBuckets;
-    int32_t *have_best = reinterpret_cast<int32_t *>(up_value + kSplitBuckets), *have_up = have_best + kSplitBuckets;
-    int32_t *first_row = have_up + kSplitBuckets;
-    // the backward sweep's copies of a tile's forward sums and values
-    double *head_l = reinterpret_cast<double *>(first_row + kSplitBuckets);   // [T]
-    float *value_l = reinterpret_cast<float *>(head_l + T);               // [T]
-
-    auto sweep = [&](bool backward, auto per_tile) {
-        for (int i = tid; i < kSplitBuckets * d; i += 256) cumX[i] = cumX2[i] = 0.0;
-        if (tid < kSplitBuckets) count[tid] = 0;
-        __syncthreads();
-        const int64_t n_tiles = (N + T - 1) / T;
-        for (int64_t tile = 0; tile < n_tiles; ++tile) {
-            const int64_t p0 = (backward ? n_tiles - 1 - tile : tile) * T;
-            const int len = (int)(N - p0 < T ? N - p0 : T);
-            // slot s of the tile: position p0 + s going up, p0 + len - 1 - s going down
-            // (a thread per slot fetches its row's bucket and its row's d values: both need only the row number)
-            if (tid < len) {
-                const int64_t p = backward ? p0 + len - 1 - tid : p0 + tid;
-                const int32_t r = key_row(keys[p]);
-                rows[tid] = r;
-                bkt[tid] = node[r];
-                const float *src = a.A + (int64_t)r * a.lda + lo;
-                float *dst = xt + tid * xld;
-                int jj = 0;
-                for (; jj + 8 <= d; jj += 8) {
-                    float v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = src[jj + u];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) dst[jj + u] = v[u];
-                }
-                for (; jj < d; ++jj) dst[jj] = src[jj];
-            }
-            __syncthreads();
-            // rows of each bucket up to every slot
-            if (tid == 0)
-                for (int s = 0; s < len; ++s) cnt_at[s] = (int32_t)++count[bkt[s]];
-            __syncthreads();
-            {
-                for (int jj = tid; jj < d; jj += 256)
-                    for (int s = 0; s < len; ++s) {
-                        const int b = bkt[s];
-                        const double x = (double)xt[s * xld + jj];
-                        const double cx = cumX[b * d + jj] + x;
-                        const double cx2 = cumX2[b * d + jj] + x * x;
-                        cumX[b * d + jj] = cx;
-                        cumX2[b * d + jj] = cx2;
-                        term[s * d + jj] = cx2 - (cx * cx / (double)cnt_at[s]);
-                    }
-            }
-            __syncthreads();
-            if (tid < len) {
-                double o = 0.0;
-                for (int jj = 0; jj < d; ++jj) o = o + term[tid * d + jj];
-                sse[tid] = o;
-            }
-            __syncthreads();
-            per_tile(p0, len);
-            __syncthreads();
+    const int64_t group = blockIdx.x / a.C;
+    int b = -1, start = 0, count = 0;
+    for (int k = 0; k < n_buckets; ++k) {
+        const int s = a.bucket_start[c * kSplitBuckets + k], n = (int)a.bucket_count[c * kSplitBuckets + k];
+        const int64_t first = first_group(s, k);
+        if (group >= first && group < first + (n + kGroupRows - 1) / kGroupRows) {
+            b = k;
+            start = s;
+            count = n;
         }
+    }
+    if (b < 0) return;
+    const int tile0 = (int)(group - first_group(start, b)) * kGroupTiles;                   // of the bucket's tiles
+    const int n_tiles = min(kGroupTiles, (count + T - 1) / T - tile0);
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+    const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + 4 * (lane % kPieces);
+    // as the sums are taken: a lane per chain
+    const int chain_dir = (lane / (2 * NC)) & 1, which = (lane / NC) & 1, chain_col = lane % NC;
+    const double *ends = a.sums + ((((size_t)c * kCand + q) * 2 + chain_dir) * a.tile_slots + first_slot(start, b) + tile0) * (2 * a.dmax) +
+                         (size_t)which * a.dmax;
+    // as the terms are taken: going up the sums with row k, going down those of the rows after it (what the split after
+    // row k leaves above)
+    const int k = lane & (T - 1), dir = lane / T, entry = dir ? T - 1 - k : k + 1;
+
+    auto key_of = [&](int t) __attribute__((always_inline)) {       // (one more than the tile's, where there is one)
+        const int p = (tile0 + t) * T + lane;
+        return t < n_tiles && lane <= T && p < count ? keys[p] : 0;
     };
+    auto row_of = [&](int t, uint64_t key) __attribute__((always_inline)) {
+        return (tile0 + t) * T + lane < count ? key_row(key) : (int32_t)a.N;
+    };
+    float4 v[kPer];
+    double end;
+    auto fetch = [&](int t, int32_t my_row, int col0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            v[u] = *reinterpret_cast<const float4 *>(X + col0 + (int64_t)__shfl(my_row, lane / kPieces + u * kRows) * a.pitch);
+        end = ends[(size_t)t * (2 * a.dmax) + min(col0 + chain_col, d - 1)];
+    };
+    uint64_t key = key_of(0), next_key = key_of(1);
+    int32_t my_row = row_of(0, key);
+    fetch(0, my_row, 0);
+    double best = 0.0;
+    int at = -1, first_nan = -1;
+    bool have_cand = false;
+    for (int t = 0; t < n_tiles; ++t) {
+        const int left = count - (tile0 + t) * T;                         // rows from the tile's first to the bucket's last
+        const double n = (double)max(dir ? left - (k + 1) : (tile0 + t) * T + k + 1, 1), y = 1.0 / n;
+        const uint64_t key_after = key_of(t + 2);
+        double sse = 0.0;
+        for (int col0 = 0; col0 < d; col0 += NC) {
+            if (col0 > 0) fetch(t, my_row, col0);
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int p = lane / kPieces + u * kRows;
+                const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    xs[0][4 * (lane % kPieces) + e][p] = x[e];
+                    xs[1][4 * (lane % kPieces) + e][T - 1 - p] = x[e];
+                }
+            }
+            double acc = end;
+            __syncthreads();
+            if (col0 + NC >= d) {
+                my_row = row_of(t + 1, next_key);
+                if (t + 1 < n_tiles) fetch(t + 1, my_row, 0);
+            }
+            if (lane < kChains) {
+                const float *x = xs[chain_dir][chain_col];
+                double *dst = sums[lane];          // the sums before the first row, after it, after the second, ...
+                *dst = acc;
+#pragma unroll
+                for (int s = 0; s < T; s += 4) {
+                    const float4 f = *reinterpret_cast<const float4 *>(x + s);
+                    const float e[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const double w = (double)e[u];
+                        acc = acc + w * (which ? w : 1.0);
+                        dst[s + u + 1] = acc;
+                    }
+                }
+            }
+            __syncthreads();
+            const int cols = min(NC, d - col0);
+#pragma unroll 4
+            for (int col = 0; col < cols; ++col) {
+                const double cx = sums[dir * 2 * NC + col][entry], cx2 = sums[dir * 2 * NC + NC + col][entry];
+                const double square = cx * cx;
+                const double quotient = square * y;
+                sse = sse + (cx2 - __builtin_fma(__builtin_fma(-n, quotient, square), y, quotient));
+            }
+            __syncthreads();
+        }
+        // a split between row k and the next one: in the same bucket, and their values differ
+        const double loss = sse + __shfl_down(sse, T);
+        const float value = key_value(key), next_value = __shfl_down(value, 1);
+        const bool cand = dir == 0 && k + 1 < left && value < next_value;
+        const unsigned long long cands = __ballot(cand);
+        if (!have_cand && cands) {
+            const int first = __ffsll(cands) - 1;
+            const double l = __shfl(loss, first);
+            first_nan = l != l ? (tile0 + t) * T + first : -1;
+            have_cand = true;
+        }
+        if (cand && better(loss, (tile0 + t) * T + k, best, at)) {
+            best = loss;
+            at = (tile0 + t) * T + k;
+        }
+        key = next_key;
+        next_key = key_after;
+    }
+#pragma unroll
+    for (int off = 1; off < T; off <<= 1) {
+        const double l2 = __shfl_xor(best, off);
+        const int at2 = __shfl_xor(at, off);
+        const bool take = better(l2, at2, best, at);
+        best = take ? l2 : best;
+        at = take ? at2 : at;
+    }
+    if (lane == 0) {
+        const size_t o = ((size_t)c * kCand + q) * a.group_slots + group;
+        a.group_loss[o] = best;
+        a.group_at[2 * o] = at;
+        a.group_at[2 * o + 1] = first_nan;
+    }
+}
 
-    sweep(false, [&](int64_t p0, int len) {
-        if (tid < len) head[p0 + tid] = sse[tid];
-    });
+// The best split of every (candidate, bucket) from its groups of tiles, a wavefront each; then Algorithm 2's choice: the
+// candidate with the smallest loss summed over the buckets (the first of equal ones), its thresholds into the tree.
+// A comparison with a loss that is not a number (data with infinities) is false, as in Algorithm 3: it stays the best
+// where it is the bucket's first.
+__global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int level, int n_buckets)
+{
+    __shared__ double res_loss[kCand][kSplitBuckets];
+    __shared__ float res_v[kCand][kSplitBuckets];
+    const int c = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n_cand = a.n_cand[c];
+    for (int pair = wave; pair < n_cand * n_buckets; pair += 8) {
+        const int q = pair / n_buckets, b = pair - q * n_buckets;
+        const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
+        const int n_groups = (count + kGroupRows - 1) / kGroupRows;
+        const size_t o = ((size_t)c * kCand + q) * a.group_slots + first_group(start, b);
+        double loss = 0.0;
+        int at = -1, first = 0x7fffffff;           // (the first group that has a split at all)
+        for (int i = lane; i < n_groups; i += 64) {
+            const int at2 = a.group_at[2 * (o + i)];
+            const double l2 = a.group_loss[o + i];
+            if (at2 >= 0 && first == 0x7fffffff) first = i;
+            if (better(l2, at2, loss, at)) {
+                loss = l2;
+                at = at2;
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double l2 = __shfl_xor(loss, off);
+            const int at2 = __shfl_xor(at, off);
+            first = min(first, __shfl_xor(first, off));
+            const bool take = better(l2, at2, loss, at);
+            loss = take ? l2 : loss;
+            at = take ? at2 : at;
+        }
+        if (lane == 0) {
+            if (at >= 0) {
+                const int not_a_number = a.group_at[2 * (o + first) + 1];
+                if (not_a_number >= 0) {
+                    at = not_a_number;
+                    loss = __builtin_nan("");
+                }
+            }
+            const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+            float v = 0.0f;
+            if (at >= 0) {
+                const float l = key_value(keys[at]), h = key_value(keys[at + 1]);
+                v = (float)(((double)l + (double)h) / 2.0);
+                if (!(v > l)) v = h;
+            } else if (count > 0) {
+                // cannot be split: the value of the bucket's first row in sorted order, the loss L(B)
+                v = a.X[((size_t)c * (a.N + 1) + key_row(keys[0])) * a.pitch + a.cand[c * kCand + q]];
+                loss = a.bucket_loss[c * kSplitBuckets + b];
+            }
+            res_v[q][b] = v;
+            res_loss[q][b] = loss;
+        }
+    }
     __syncthreads();
-
-    // Going down: the candidates of a bucket are judged in order, the buckets independently of one another - a
-    // thread per bucket walks the tile's slots, its bucket's state in registers, and takes the slots of its bucket
-    // (selects, no branches).  The values and the forward sums of the tile's positions are fetched by all threads
-    // first, so that the walk reads LDS only, eight slots at a time.
-    bool r_have_best = false, r_have_up = false;
-    double r_best_loss = 0.0, r_up_tail = 0.0;
-    float r_best_lo = 0.0f, r_best_hi = 0.0f, r_up_value = 0.0f;
-    int32_t r_first_row = 0;
-    sweep(true, [&](int64_t p0, int len) {
-        if (tid < len) {
-            const int64_t p = p0 + len - 1 - tid;
-            head_l[tid] = head[p];
-            value_l[tid] = key_value(keys[p]);
-        }
-        __syncthreads();
-        if (tid >= n_buckets) return;
-        const int b = tid;
-        for (int s0 = 0; s0 < len; s0 += 8) {
-            int bk[8], rw[8];
-            float val[8];
-            double hd[8], ss[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool in_tile = s0 + u < len;
-                const int s = in_tile ? s0 + u : 0;
-                bk[u] = in_tile ? bkt[s] : -1;
-                val[u] = value_l[s];
-                hd[u] = head_l[s];
-                ss[u] = sse[s];
-                rw[u] = rows[s];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool mine = bk[u] == b;
-                const bool cand = mine && r_have_up && val[u] < r_up_value;
-                const double loss = hd[u] + r_up_tail;
-                const bool better = cand && (!r_have_best || loss <= r_best_loss);
-                r_have_best = r_have_best || better;
-                r_best_loss = better ? loss : r_best_loss;
-                r_best_lo = better ? val[u] : r_best_lo;
-                r_best_hi = better ? r_up_value : r_best_hi;
-                r_have_up = r_have_up || mine;
-                r_up_value = mine ? val[u] : r_up_value;
-                r_up_tail = mine ? ss[u] : r_up_tail;
-                r_first_row = mine ? rw[u] : r_first_row;
-            }
-        }
-    });
-    if (tid < n_buckets) {
-        const int b = tid;
-        float v = 0.0f;
-        double loss = 0.0;
-        if (r_have_best) {
-            const float l = r_best_lo, h = r_best_hi;
-            v = (float)(((double)l + (double)h) / 2.0);
-            if (!(v > l)) v = h;
-            loss = r_best_loss;
-        } else if (r_have_up) {
-            // cannot be split: the value of the bucket's first row in sorted order, the loss L(B)
-            v = a.A[(int64_t)r_first_row * a.lda + lo + jsplit];
-            loss = a.bucket_loss[c * kSplitBuckets + b];
-        }
-        a.res_v[(c * kCand + q) * kSplitBuckets + b] = v;
-        a.res_loss[(c * kCand + q) * kSplitBuckets + b] = loss;
-    }
-}
-
-// LDS of split_ordered_kernel for subspaces of d columns and tiles of T positions: two [d][T + kOrderedPad]
-// arrays of doubles (the two running sums of every (column, place)), the sums carried from tile to tile, and a
-// handful of values per place and per bucket
-constexpr int kOrderedPad = 17;    // the batches of 8 read up to 16 places past the last; an odd pitch spreads the columns over the banks
-__host__ __device__ constexpr size_t split_ordered_lds_bytes(int d, int T)
-{
-    return sizeof(double) * (2 * (size_t)d * (T + kOrderedPad) + 2 * (size_t)kSplitBuckets * d + 2 * (size_t)T + 7 * kSplitBuckets) +
-           sizeof(int32_t) * (5 * (size_t)T + 16 * kSplitBuckets);
-}
-
-// Algorithm 3 as split_kernel does it, for subspaces narrow enough that LDS holds both running sums of a whole
-// tile; a workgroup per (candidate, codebook) takes all sorted positions, or (by_bucket) a workgroup per
-// (candidate, bucket, codebook) the bucket's stretch of them.  The
-// positions of a tile are put in the order of their buckets first (a place each: the places of a
-// bucket side by side, in the order of the sweep; wavefront ballots give a position's rank among those of its
-// bucket), and their values go to LDS by column, as doubles, beside their squares.  Then
-//   - a running sum is a walk over neighbouring doubles, in place: a thread per (bucket, column, which of the two
-//     sums) reads a value, adds, writes the sum back (a wavefront issues a vector instruction in four cycles and
-//     these chains are the one serial part, so they are kept to those three instructions per position);
-//   - the product, the division, the difference and the sum over the columns (in column order) go to a thread
-//     per place: the same operations on the same operands as in Algorithm 4;
-//   - going down, a place's candidate split (between it and the bucket's place before it) needs no chain at all:
-//     its loss is head + the tail of the place before, and "a loss that is not larger replaces the best" is the
-//     minimum over the candidates, the last of equal ones - a reduction (comparisons only), by wavefront and
-//     then across the four wavefronts and the tiles before.
-__global__ __launch_bounds__(256) void split_ordered_kernel(const LearnArgs a, int n_buckets, int T, int by_bucket)
-{
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int c = blockIdx.z, q = blockIdx.x, bucket = blockIdx.y;
-    if (q >= a.n_cand[c]) return;
-    const int lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
-    const int jsplit = a.cand[c * kCand + q];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t N = a.N;
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
-    const uint8_t *node = a.node + (size_t)c * N;
-    double *head = a.head + ((size_t)c * kCand + q) * N;
-
-    const int Tp = T + kOrderedPad;
-    double *sumX = reinterpret_cast<double *>(lds_raw);      // [d][Tp] x, then its running sum, then Algorithm 4's term
-    double *sumX2 = sumX + (size_t)d * Tp;                   // [d][Tp] x^2, then its running sum
-    double *cumX = sumX2 + (size_t)d * Tp;                   // [8][d] the sums at the end of the tile before
-    double *cumX2 = cumX + (size_t)kSplitBuckets * d;        // [8][d]
-    double *sse = cumX2 + (size_t)kSplitBuckets * d;         // [T] by place
-    double *head_l = sse + T;                                // [T] by place (going down)
-    double *best_loss = head_l + T;                          // [8]
-    double *up_tail = best_loss + kSplitBuckets;             // [8]
-    double *wave_loss = up_tail + kSplitBuckets;             // [8][4]
-    int64_t *count = reinterpret_cast<int64_t *>(wave_loss + 4 * kSplitBuckets);   // [8] rows seen in this sweep
-    float *value_l = reinterpret_cast<float *>(count + kSplitBuckets);             // [T] by place
-    int32_t *rows_l = reinterpret_cast<int32_t *>(value_l + T);                    // [T] by place
-    int32_t *bucket_l = rows_l + T;                                                // [T] by place
-    int32_t *cnt_at = bucket_l + T;                                                // [T] by place: rows of the bucket up to it
-    int32_t *slot_of = cnt_at + T;                                                 // [T] by place: its slot in the tile
-    int32_t *wave_count = slot_of + T;                                             // [8][4]
-    int32_t *wave_place = wave_count + 4 * kSplitBuckets;                          // [8][4]
-    int32_t *start = wave_place + 4 * kSplitBuckets;                               // [8]
-    int32_t *in_tile = start + kSplitBuckets;                                      // [8]
-    int32_t *have_best = in_tile + kSplitBuckets, *have_up = have_best + kSplitBuckets;
-    int32_t *first_row = have_up + kSplitBuckets;
-    float *best_lo = reinterpret_cast<float *>(first_row + kSplitBuckets), *best_hi = best_lo + kSplitBuckets;
-    float *up_value = best_hi + kSplitBuckets;
-
-    if (tid < kSplitBuckets) {
-        have_best[tid] = have_up[tid] = 0;
-        best_loss[tid] = up_tail[tid] = 0.0;
-        best_lo[tid] = best_hi[tid] = up_value[tid] = 0.0f;
-        first_row[tid] = 0;
-    }
-    // the positions this workgroup takes: all of them, or (by_bucket: the keys sort by bucket first) its bucket's
-    const int64_t first = by_bucket ? a.bucket_start[c * kSplitBuckets + bucket] : 0;
-    const int64_t S = by_bucket ? a.bucket_count[c * kSplitBuckets + bucket] : N;
-    const int64_t n_tiles = (S + T - 1) / T;
-    for (int sweep = 0; sweep < 2; ++sweep) {
-        const bool backward = sweep == 1;
-        __syncthreads();
-        for (int i = tid; i < kSplitBuckets * d; i += 256) cumX[i] = cumX2[i] = 0.0;
-        if (tid < kSplitBuckets) count[tid] = 0;
-        __syncthreads();
-        for (int64_t tile = 0; tile < n_tiles; ++tile) {
-            const int64_t p0 = (backward ? n_tiles - 1 - tile : tile) * T;
-            const int len = (int)(S - p0 < T ? S - p0 : T);
-            // slot s of the tile: the bucket's position p0 + s going up, p0 + len - 1 - s going down; a thread per slot
-            int64_t p = 0;
-            int32_t r = 0;
-            int my_b = -1;
-            float my_value = 0.0f;
-            if (tid < len) {
-                p = first + (backward ? p0 + len - 1 - tid : p0 + tid);
-                const uint64_t key = keys[p];
-                r = key_row(key);
-                my_value = key_value(key);
-                my_b = node[r];
-            }
-            // the slot's rank among the slots of its bucket: within its wavefront from a ballot, the wavefronts
-            // before it from their counts
-            int rank = 0;
-            for (int b = 0; b < n_buckets; ++b) {
-                const unsigned long long mask = __ballot(my_b == b);
-                if (my_b == b) rank = __popcll(mask & ((1ull << lane) - 1ull));
-                if (lane == 0) wave_count[4 * b + wave] = __popcll(mask);
-            }
-            __syncthreads();
-            if (tid < n_buckets) {
-                int before = 0;
-                for (int b = 0; b < tid; ++b)
-                    before += wave_count[4 * b] + wave_count[4 * b + 1] + wave_count[4 * b + 2] + wave_count[4 * b + 3];
-                start[tid] = before;
-                in_tile[tid] = wave_count[4 * tid] + wave_count[4 * tid + 1] + wave_count[4 * tid + 2] + wave_count[4 * tid + 3];
-            }
-            int32_t my_cnt = 0;
-            if (my_b >= 0) {
-                for (int w = 0; w < wave; ++w) rank += wave_count[4 * my_b + w];
-                my_cnt = (int32_t)(count[my_b] + rank + 1);
-            }
-            __syncthreads();
-            if (tid < n_buckets) count[tid] += in_tile[tid];       // (read above, before the barrier)
-            if (my_b >= 0) {
-                const int place = start[my_b] + rank;
-                cnt_at[place] = my_cnt;
-                bucket_l[place] = my_b;
-                rows_l[place] = r;
-                slot_of[place] = tid;
-                value_l[place] = my_value;
-                if (backward) head_l[place] = head[p];
-                const float *src = a.A + (int64_t)r * a.lda + lo;
-                double *dx = sumX + place, *dx2 = sumX2 + place;
-                int jj = 0;
-                for (; jj + 8 <= d; jj += 8) {
-                    float v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = src[jj + u];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double x = (double)v[u];
-                        dx[(size_t)(jj + u) * Tp] = x;
-                        dx2[(size_t)(jj + u) * Tp] = x * x;
-                    }
-                }
-                for (; jj < d; ++jj) {
-                    const double x = (double)src[jj];
-                    dx[(size_t)jj * Tp] = x;
-                    dx2[(size_t)jj * Tp] = x * x;
-                }
-            }
-            __syncthreads();
-            // the running sums, in place
-            const int n_chains = n_buckets * d;
-            for (int i = tid; i < 2 * n_chains; i += 256) {
-                const int which = i >= n_chains ? 1 : 0;
-                const int rem = i - which * n_chains;
-                const int b = rem / d, jj = rem - b * d;
-                double *cum = (which ? cumX2 : cumX) + rem;
-                double *at = (which ? sumX2 : sumX) + (size_t)jj * Tp + start[b];
-                const int n_here = in_tile[b];
-                double acc = *cum;
-                // eight places at a time, the eight after them read from LDS meanwhile (the fences keep the compiler
-                // from moving the reads back to where their values are used); a batch past the bucket's last place is
-                // read (the arrays end in kOrderedPad spare places) and not used
-                double v0[8], v1[8];
-                auto read = [&](int k, double *v) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = at[k + u];
-                };
-                auto add = [&](int k, const double *v) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        acc = acc + v[u];
-                        at[k + u] = acc;
-                    }
-                };
-                const int full = n_here & ~15;
-                read(0, v0);
-                int k = 0;
-                for (; k < full; k += 16) {
-                    read(k + 8, v1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    add(k, v0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    read(k + 16, v0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    add(k + 8, v1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (k < n_here) {
-                    read(k + 8, v1);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (k + u < n_here) {
-                            acc = acc + v0[u];
-                            at[k + u] = acc;
-                        }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (k + 8 + u < n_here) {
-                            acc = acc + v1[u];
-                            at[k + 8 + u] = acc;
-                        }
-                }
-                *cum = acc;
-            }
-            __syncthreads();
-            // Algorithm 4's term of every column and their sum, a thread per place
-            double my_sse = 0.0;
-            if (tid < len) {
-                const double n_rows = (double)cnt_at[tid];
-                for (int jj = 0; jj < d; ++jj) {
-                    const double cx = sumX[(size_t)jj * Tp + tid];
-                    my_sse = my_sse + (sumX2[(size_t)jj * Tp + tid] - (cx * cx / n_rows));
-                }
-                sse[tid] = my_sse;
-                if (!backward) head[first + p0 + slot_of[tid]] = my_sse;
-            }
-            if (backward) {
-                __syncthreads();
-                // the candidate of every place, and the best of each bucket's candidates in this wavefront
-                bool cand = false;
-                double loss = 0.0;
-                int b_here = -1;
-                if (tid < len) {
-                    b_here = bucket_l[tid];
-                    const bool first_here = tid == start[b_here];
-                    const bool have = first_here ? have_up[b_here] != 0 : true;
-                    const float before_value = first_here ? up_value[b_here] : value_l[tid - 1];
-                    const double before_tail = first_here ? up_tail[b_here] : sse[tid - 1];
-                    cand = have && value_l[tid] < before_value;
-                    loss = head_l[tid] + before_tail;
-                }
-                const int wave_first = 64 * wave, wave_end = min(len, 64 * wave + 64);
-                for (int b = 0; b < n_buckets; ++b) {
-                    if (lane == 0) wave_place[4 * b + wave] = -1;
-                    if (in_tile[b] == 0 || start[b] >= wave_end || start[b] + in_tile[b] <= wave_first) continue;
-                    double l = loss;
-                    int pl = (cand && b_here == b) ? tid : -1;
-#pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const double l2 = __shfl_xor(l, off);
-                        const int pl2 = __shfl_xor(pl, off);
-                        const bool take = pl2 >= 0 && (pl < 0 || l2 < l || (l2 == l && pl2 > pl));
-                        l = take ? l2 : l;
-                        pl = take ? pl2 : pl;
-                    }
-                    if (lane == 0) {
-                        wave_place[4 * b + wave] = pl;
-                        wave_loss[4 * b + wave] = l;
-                    }
-                }
-                __syncthreads();
-                if (tid < n_buckets && in_tile[tid] > 0) {
-                    const int b = tid;
-                    int pl = -1;
-                    double l = 0.0;
-                    for (int w = 0; w < 4; ++w) {
-                        const int pl2 = wave_place[4 * b + w];
-                        if (pl2 >= 0 && (pl < 0 || wave_loss[4 * b + w] <= l)) {
-                            pl = pl2;
-                            l = wave_loss[4 * b + w];
-                        }
-                    }
-                    if (pl >= 0 && (!have_best[b] || l <= best_loss[b])) {
-                        have_best[b] = 1;
-                        best_loss[b] = l;
-                        best_lo[b] = value_l[pl];
-                        best_hi[b] = pl == start[b] ? up_value[b] : value_l[pl - 1];
-                    }
-                    const int last = start[b] + in_tile[b] - 1;
-                    have_up[b] = 1;
-                    up_value[b] = value_l[last];
-                    up_tail[b] = sse[last];
-                    first_row[b] = rows_l[last];
-                }
-            }
-            __syncthreads();
-        }
-    }
-    if (by_bucket ? tid == bucket : tid < n_buckets) {
-        const int b = tid;
-        float v = 0.0f;
-        double loss = 0.0;
-        if (have_best[b]) {
-            const float l = best_lo[b], h = best_hi[b];
-            v = (float)(((double)l + (double)h) / 2.0);
-            if (!(v > l)) v = h;
-            loss = best_loss[b];
-        } else if (have_up[b]) {
-            // cannot be split: the value of the bucket's first row in sorted order, the loss L(B)
-            v = a.A[(int64_t)first_row[b] * a.lda + lo + jsplit];
-            loss = a.bucket_loss[c * kSplitBuckets + b];
-        }
-        a.res_v[(c * kCand + q) * kSplitBuckets + b] = v;
-        a.res_loss[(c * kCand + q) * kSplitBuckets + b] = loss;
-    }
-}
-
-// Algorithm 2's choice: the candidate with the smallest loss summed over the buckets (the
-// first of equal ones), its thresholds into the tree.
-__global__ void choose_kernel(const LearnArgs a, int level, int n_buckets)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= a.C) return;
+    if (threadIdx.x != 0) return;
     int best_q = 0;
     double l_min = 0.0;
-    for (int q = 0; q < a.n_cand[c]; ++q) {
+    for (int q = 0; q < n_cand; ++q) {
         double l = 0.0;
-        for (int b = 0; b < n_buckets; ++b) l += a.res_loss[(c * kCand + q) * kSplitBuckets + b];
+        for (int b = 0; b < n_buckets; ++b) l += res_loss[q][b];
         if (q == 0 || l < l_min) {
             l_min = l;
             best_q = q;
@@ -889,8 +706,7 @@ __global__ void choose_kernel(const LearnArgs a, int level, int n_buckets)
     const int jj = a.cand[c * kCand + best_q];
     a.chosen[c] = jj;
     a.split_dims[4 * c + level] = a.bounds[2 * c] + jj;
-    for (int b = 0; b < n_buckets; ++b)
-        a.thresholds[16 * c + n_buckets - 1 + b] = a.res_v[(c * kCand + best_q) * kSplitBuckets + b];
+    for (int b = 0; b < n_buckets; ++b) a.thresholds[16 * c + n_buckets - 1 + b] = res_v[best_q][b];
     if (level == 3) a.thresholds[16 * c + 15] = 0.0f;
 }
 
@@ -900,10 +716,10 @@ __global__ __launch_bounds__(256) void apply_kernel(const LearnArgs a, int level
     const int c = blockIdx.y;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (n >= a.N) return;
-    const int j = a.bounds[2 * c] + a.chosen[c];
+    const int j = a.chosen[c];
     const int b = a.node[(size_t)c * a.N + n];
     const float v = a.thresholds[16 * c + n_buckets - 1 + b];
-    const int child = 2 * b + (a.A[n * a.lda + j] >= v ? 1 : 0);
+    const int child = 2 * b + (a.X[((size_t)c * (a.N + 1) + n) * a.pitch + j] >= v ? 1 : 0);
     a.node[(size_t)c * a.N + n] = (uint8_t)child;
     if (level == 3 && a.codes) a.codes[n * a.C + c] = (uint8_t)child;
 }
@@ -1439,15 +1255,12 @@ struct Carver {
     }
 };
 
-size_t split_lds_bytes(int d)
-{
-    return split_lds_bytes_base(d, kSplitTile);
-}
-
 void carve_trees(Carver &w, LearnArgs &a)
 {
     const size_t C = a.C;
     a.bounds = w.take<int32_t>(2 * C);
+    a.pitch = a.dmax <= 8 ? 8 : (a.dmax + 15) / 16 * 16;
+    a.X = w.take<float>(C * (a.N + 1) * a.pitch);
     a.node = w.take<uint8_t>(C * a.N);
     a.col_loss = w.take<double>(C * kSplitBuckets * a.dmax);
     a.bucket_loss = w.take<double>(C * kSplitBuckets);
@@ -1457,9 +1270,11 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.cand = w.take<int32_t>(C * kCand);
     a.n_cand = w.take<int32_t>(C);
     a.keys = w.take<uint64_t>(C * kCand * a.Npad);
-    a.head = w.take<double>(C * kCand * a.N);
-    a.res_loss = w.take<double>(C * kCand * kSplitBuckets);
-    a.res_v = w.take<float>(C * kCand * kSplitBuckets);
+    a.tile_slots = a.N / kJudgeRows + kSplitBuckets + 1;
+    a.sums = w.take<double>(C * kCand * 2 * a.tile_slots * 2 * a.dmax);
+    a.group_slots = a.N / kGroupRows + kSplitBuckets + 1;
+    a.group_loss = w.take<double>(C * kCand * a.group_slots);
+    a.group_at = w.take<int32_t>(C * kCand * a.group_slots * 2);
     a.chosen = w.take<int32_t>(C);
 }
 
@@ -1493,13 +1308,7 @@ size_t learn_prototypes_workspace_bytes(int32_t D, int32_t C)
     return w.used;
 }
 
-int learn_max_subspace_width()
-{
-    // the running sums of split_kernel (one column per thread slot) must fit in LDS
-    int d = 1;
-    while (2 * d <= kLossMaxWidth && split_lds_bytes(2 * d) + 1024 <= (size_t)device_info().lds_per_block) d *= 2;
-    return d;
-}
+int learn_max_subspace_width() { return kMaxWidth; }
 
 #define LAUNCH_OK(what)                                                       \
     if (int rc_ = check_hip(hipGetLastError(), what); rc_ != MADDNESS_OK) return rc_
@@ -1512,7 +1321,7 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
     a.split_dims = split_dims; a.thresholds = thresholds; a.codes = codes;
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
-    note_kernel("order_rows_kernel + bucket_loss_kernel + select_kernel + key_kernel + sort_chunks_kernel + sort_exchange_kernel + split_ordered_kernel + choose_kernel + apply_kernel", nullptr);
+    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + key_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_kernel + judge_kernel + choose_kernel + apply_kernel", nullptr);
 
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
@@ -1523,32 +1332,28 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
                        (uint8_t)0);
     LAUNCH_OK("launch fill_bytes_kernel");
 
+    const int64_t pieces = (N + 1) * (a.pitch / 4);
+    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)((pieces + 255) / 256), C), dim3(256), 0, stream, a);
+    LAUNCH_OK("launch gather_columns_kernel");
+
     const size_t sort_lds = sizeof(uint64_t) * (size_t)(a.Npad < kSortChunk ? a.Npad : kSortChunk);
-    // subspaces narrow enough for split_ordered_kernel take it, with the largest tile that fits (a tile costs a
-    // fixed chain of barriers and memory latencies, whatever its size); wider ones take split_kernel
-    const size_t lds_max = (size_t)device_info().lds_per_block - 1024;
-    const bool ordered = split_ordered_lds_bytes(dmax, 64) <= lds_max;
-    int tile = 64;
-    if (ordered)
-        while (2 * tile <= kMaxTile && split_ordered_lds_bytes(dmax, 2 * tile) <= lds_max) tile *= 2;
-    const size_t split_lds = ordered ? split_ordered_lds_bytes(dmax, tile) : split_lds_bytes(dmax);
-    if (int rc = allow_full_lds<split_ordered_kernel>(); rc != MADDNESS_OK) return rc;
-    // With few (candidate, codebook) pairs a workgroup per bucket as well fills more of the chip: the keys then
-    // sort by bucket first and every workgroup takes its bucket's stretch.  With many pairs the chip is full
-    // anyway, and a tile that mixes the buckets has its running sums on more lanes, each over fewer positions.
-    const int by_bucket = ordered && 4 * kCand * C <= device_info().cus ? 1 : 0;
-    if (int rc = allow_full_lds<bucket_loss_kernel>(); rc != MADDNESS_OK) return rc;
     if (int rc = allow_full_lds<sort_chunks_kernel>(); rc != MADDNESS_OK) return rc;
-    if (int rc = allow_full_lds<split_kernel>(); rc != MADDNESS_OK) return rc;
+    const bool narrow = dmax <= 8;
     for (int level = 0; level < 4; ++level) {
         const int n_buckets = 1 << level;
         hipLaunchKernelGGL(order_rows_kernel, dim3(C), dim3(256), 0, stream, a, n_buckets);
         LAUNCH_OK("launch order_rows_kernel");
-        hipLaunchKernelGGL(bucket_loss_kernel, dim3(n_buckets, C), dim3(256), kLossLdsBytes, stream, a);
+        // (columns eight or sixteen at a time: a wavefront carries them all)
+        const int groups = narrow ? 1 : a.pitch / 16;
+        const dim3 loss_groups(C, n_buckets, groups);
+        if (narrow)
+            hipLaunchKernelGGL(bucket_loss_kernel<8>, loss_groups, dim3(16 * 8 + kChainHelpers), stream_lds_bytes<8>(), stream, a);
+        else
+            hipLaunchKernelGGL(bucket_loss_kernel<16>, loss_groups, dim3(16 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a);
         LAUNCH_OK("launch bucket_loss_kernel");
         hipLaunchKernelGGL(select_kernel, dim3(C), dim3(64), sizeof(double) * dmax, stream, a, n_buckets);
         LAUNCH_OK("launch select_kernel");
-        hipLaunchKernelGGL(key_kernel, dim3((unsigned)((a.Npad + 255) / 256), kCand, C), dim3(256), 0, stream, a, by_bucket);
+        hipLaunchKernelGGL(key_kernel, dim3((unsigned)((a.Npad + 255) / 256), kCand, C), dim3(256), 0, stream, a);
         LAUNCH_OK("launch key_kernel");
         const int64_t chunk_len = a.Npad < kSortChunk ? a.Npad : kSortChunk;
         const dim3 chunks((unsigned)(a.Npad / chunk_len), kCand, C), pairs((unsigned)((a.Npad / 2 + 255) / 256), kCand, C);
@@ -1562,13 +1367,19 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
             hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(1024), sort_lds, stream, a, k, k, chunk_len >> 1);
             LAUNCH_OK("launch sort_chunks_kernel");
         }
-        if (ordered)
-            hipLaunchKernelGGL(split_ordered_kernel, dim3(kCand, by_bucket ? n_buckets : 1, C), dim3(256), split_lds, stream, a,
-                               n_buckets, tile, by_bucket);
-        else
-            hipLaunchKernelGGL(split_kernel, dim3(kCand, C), dim3(256), split_lds, stream, a, n_buckets);
-        LAUNCH_OK("launch split_kernel");
-        hipLaunchKernelGGL(choose_kernel, dim3((C + 63) / 64), dim3(64), 0, stream, a, level, n_buckets);
+        const dim3 chain_groups(C, 8 * groups, n_buckets);
+        const dim3 judges((unsigned)(a.group_slots * C), kCand);
+        if (narrow) {
+            hipLaunchKernelGGL(split_chains_kernel<8>, chain_groups, dim3(32 * 8 + kChainHelpers), stream_lds_bytes<8>(), stream, a);
+            LAUNCH_OK("launch split_chains_kernel");
+            hipLaunchKernelGGL(judge_kernel<8>, judges, dim3(64), 0, stream, a, n_buckets);
+        } else {
+            hipLaunchKernelGGL(split_chains_kernel<16>, chain_groups, dim3(32 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a);
+            LAUNCH_OK("launch split_chains_kernel");
+            hipLaunchKernelGGL(judge_kernel<16>, judges, dim3(64), 0, stream, a, n_buckets);
+        }
+        LAUNCH_OK("launch judge_kernel");
+        hipLaunchKernelGGL(choose_kernel, dim3(C), dim3(512), 0, stream, a, level, n_buckets);
         LAUNCH_OK("launch choose_kernel");
         hipLaunchKernelGGL(apply_kernel, dim3((unsigned)((N + 255) / 256), C), dim3(256), 0, stream, a, level, n_buckets);
         LAUNCH_OK("launch apply_kernel");
