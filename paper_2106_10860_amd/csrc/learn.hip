@@ -30,7 +30,7 @@
 //   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
 //                        candidates
 //   apply_kernel         apply_split: the next level's buckets
-// Prototypes: cooccurrence_kernel (G^T G), gta_kernel (G^T A~), cholesky_panel_kernel,
+// Prototypes: cooccurrence_kernel (G^T G), count_codes_kernel, list_codes_kernel and gta_kernel (G^T A~), cholesky_panel_kernel,
 // factor by rows, substitution_kernel; or means_kernel.
 #include "common.h"
 
@@ -57,6 +57,7 @@ struct LearnArgs {
     double *bucket_loss;  // [C][8] L(B_i)
     int64_t *bucket_count;  // [C][8]
     int32_t *bucket_start;  // [C][8] where the bucket's rows begin in rows_by_bucket[c]
+    int32_t *chunk_count;   // [4][C][kMaxChunks][8] rows of every bucket in every chunk of rows, by level
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
@@ -78,10 +79,10 @@ __global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst)
     for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = b.v[i];
 }
 
-__global__ void fill_bytes_kernel(uint8_t *p, int64_t n, uint8_t v)
+__global__ void clear_kernel(int32_t *p, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < n) p[i] = 0;
 }
 
 // The columns of every codebook side by side, each row on a 32-byte (or 64-byte) boundary.  The levels read the rows of a
@@ -101,43 +102,56 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
 }
 
 // The rows of every bucket, in row order (a stable counting sort of the rows by bucket): rows_by_bucket[c]
-// holds the rows of bucket 0, then those of bucket 1, ...; bucket_start and bucket_count say where.  One
-// workgroup per codebook: the counts first, then the rows 256 at a time, a row's place among the rows of its
-// bucket from wavefront ballots.
-__global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int n_buckets)
+// holds the rows of bucket 0, then those of bucket 1, ...; bucket_start and bucket_count say where.  A workgroup
+// per codebook and chunk of chunk_rows rows; how many rows of each bucket the chunks hold is known (apply_kernel counts
+// them as it deals them out), and a row's place among its chunk's comes from wavefront ballots.  (260100 rows, 4
+// codebooks: 5.0 ms for the four levels with one workgroup per codebook.)
+constexpr int kMaxChunks = 256;
+__host__ __device__ constexpr int64_t order_chunk_rows(int64_t N)
 {
-    __shared__ int32_t total[kSplitBuckets], first[kSplitBuckets], seen[kSplitBuckets];
+    const int64_t r = (N + kMaxChunks - 1) / kMaxChunks;
+    return r <= 2048 ? 2048 : (r + 255) / 256 * 256;
+}
+
+__global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int level, int n_buckets)
+{
+    __shared__ int32_t total[kSplitBuckets], before[kSplitBuckets], seen[kSplitBuckets];
     __shared__ int32_t wave_count[2][kSplitBuckets][4];
-    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t N = a.N;
+    const int c = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t N = a.N, chunk_rows = order_chunk_rows(N);
+    const int chunk = blockIdx.x, n_chunks = gridDim.x;
     const uint8_t *node = a.node + (size_t)c * N;
     int32_t *out = a.rows_by_bucket + (size_t)c * N;
-    if (tid < kSplitBuckets) total[tid] = 0;
+    if (tid < kSplitBuckets) total[tid] = before[tid] = 0;
     __syncthreads();
-    for (int64_t n0 = 0; n0 < N; n0 += 256) {
-        const int my_b = n0 + tid < N ? node[n0 + tid] : -1;
+    if (tid < n_chunks)
         for (int k = 0; k < n_buckets; ++k) {
-            const unsigned long long mask = __ballot(my_b == k);
-            if (lane == 0 && mask != 0) atomicAdd(&total[k], __popcll(mask));
+            const int64_t rows = N - tid * chunk_rows;
+            const int32_t here = level == 0 ? (int32_t)(rows < chunk_rows ? rows : chunk_rows)
+                                            : a.chunk_count[(((size_t)level * a.C + c) * kMaxChunks + tid) * kSplitBuckets + k];
+            if (here) atomicAdd(&total[k], here);
+            if (here && tid < chunk) atomicAdd(&before[k], here);
         }
-    }
     __syncthreads();
     if (tid == 0) {
         int32_t at = 0;
         for (int k = 0; k < kSplitBuckets; ++k) {
-            first[k] = at;
-            seen[k] = 0;
-            a.bucket_start[c * kSplitBuckets + k] = at;
-            a.bucket_count[c * kSplitBuckets + k] = k < n_buckets ? total[k] : 0;
-            at += k < n_buckets ? total[k] : 0;
+            const int32_t here = k < n_buckets ? total[k] : 0;
+            seen[k] = at + before[k];
+            if (chunk == 0) {
+                a.bucket_start[c * kSplitBuckets + k] = at;
+                a.bucket_count[c * kSplitBuckets + k] = here;
+            }
+            at += here;
         }
     }
-    int next_b = tid < N ? node[tid] : -1;
+    const int64_t first = chunk * chunk_rows, end = first + chunk_rows < N ? first + chunk_rows : N;
+    int next_b = first + tid < end ? node[first + tid] : -1;
     __syncthreads();
     int parity = 0;
-    for (int64_t n0 = 0; n0 < N; n0 += 256, parity ^= 1) {
+    for (int64_t n0 = first; n0 < end; n0 += 256, parity ^= 1) {
         const int my_b = next_b;
-        next_b = n0 + 256 + tid < N ? node[n0 + 256 + tid] : -1;
+        next_b = n0 + 256 + tid < end ? node[n0 + 256 + tid] : -1;
         int rank = 0;
         for (int k = 0; k < n_buckets; ++k) {
             const unsigned long long mask = __ballot(my_b == k);
@@ -147,7 +161,7 @@ __global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int 
         __syncthreads();
         if (my_b >= 0) {
             for (int w = 0; w < wave; ++w) rank += wave_count[parity][my_b][w];
-            out[first[my_b] + seen[my_b] + rank] = (int32_t)(n0 + tid);
+            out[seen[my_b] + rank] = (int32_t)(n0 + tid);
         }
         __syncthreads();
         if (tid < n_buckets)
@@ -710,18 +724,30 @@ __global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int leve
     if (level == 3) a.thresholds[16 * c + 15] = 0.0f;
 }
 
-// apply_split: below the threshold stays left (2 i), the rest goes right (2 i + 1).
+// apply_split: below the threshold stays left (2 i), the rest goes right (2 i + 1); the rows that every bucket of the next
+// level gets are counted by chunk.
 __global__ __launch_bounds__(256) void apply_kernel(const LearnArgs a, int level, int n_buckets)
 {
-    const int c = blockIdx.y;
+    const int c = blockIdx.y, lane = threadIdx.x & 63;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= a.N) return;
-    const int j = a.chosen[c];
-    const int b = a.node[(size_t)c * a.N + n];
-    const float v = a.thresholds[16 * c + n_buckets - 1 + b];
-    const int child = 2 * b + (a.X[((size_t)c * (a.N + 1) + n) * a.pitch + j] >= v ? 1 : 0);
-    a.node[(size_t)c * a.N + n] = (uint8_t)child;
-    if (level == 3 && a.codes) a.codes[n * a.C + c] = (uint8_t)child;
+    int child = -1;
+    if (n < a.N) {
+        const int j = a.chosen[c];
+        const int b = a.node[(size_t)c * a.N + n];
+        const float v = a.thresholds[16 * c + n_buckets - 1 + b];
+        child = 2 * b + (a.X[((size_t)c * (a.N + 1) + n) * a.pitch + j] >= v ? 1 : 0);
+        a.node[(size_t)c * a.N + n] = (uint8_t)child;
+        if (level == 3 && a.codes) a.codes[n * a.C + c] = (uint8_t)child;
+    }
+    if (level == 3) return;
+    // (a chunk is a whole number of workgroups' rows)
+    const int chunk = (int)(((int64_t)blockIdx.x * 256) / order_chunk_rows(a.N));
+    int mine = 0;
+    for (int k = 0; k < 2 * n_buckets; ++k) {
+        const int here = __popcll(__ballot(child == k));
+        if (lane == k) mine = here;
+    }
+    if (mine) atomicAdd(&a.chunk_count[(((size_t)(level + 1) * a.C + c) * kMaxChunks + chunk) * kSplitBuckets + lane], mine);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -737,13 +763,18 @@ struct ProtoArgs {
     int32_t *counts;        // [Q][Q] G^T G
     double *M;              // [Q][Q]: G^T G + lambda I, then M[k][i] = L[i][k]
     double *Lr;             // [Q][Q]: L by rows
-    double *R;              // [Q][D]: G^T A~, then y, then P
+    double *R;              // [Q][D]: G^T A~
+    int64_t stretch;        // rows of a stretch
+    uint32_t *list;         // [C][kListRows + kListSpare] distances in bytes of the stretch's rows, by code
+    int32_t *list_count;    // [C][kListChunks][16] how many each of its chunks has of every code
+    int32_t *list_start;    // [C][17] where those of a code begin
     float *P;               // out [C][16][D]
 };
 
 // G^T G: entry (q, q') counts the training rows whose one-hot row has ones at q and q'.  A workgroup takes
-// codebook c against kCoGroup codebooks c2 and counts in LDS (16 x 16 counters a pair), then stores its
-// 16 x (16 kCoGroup) block of the matrix: no two workgroups share an entry.
+// codebook c against kCoGroup codebooks c2 and a stretch of the rows, counts in LDS (16 x 16 counters a pair), and adds
+// its 16 x (16 kCoGroup) block to the matrix (whole numbers: in any order).  (One workgroup for all rows of a block left
+// the chip empty: 260100 rows, 4 codebooks 0.60 ms.)
 constexpr int kCoGroup = 8;
 __global__ __launch_bounds__(256) void cooccurrence_kernel(const ProtoArgs a)
 {
@@ -752,7 +783,7 @@ __global__ __launch_bounds__(256) void cooccurrence_kernel(const ProtoArgs a)
     const int n_c2 = min(kCoGroup, a.C - c2_first);
     for (int i = tid; i < kCoGroup * 256; i += 256) (&hist[0][0])[i] = 0;
     __syncthreads();
-    for (int64_t n = tid; n < a.N; n += 256) {
+    for (int64_t n = (int64_t)blockIdx.z * 256 + tid; n < a.N; n += (int64_t)gridDim.z * 256) {
         const uint8_t *row = a.codes + n * a.C;
         const int k = row[c] & 15;
         uint8_t k2[kCoGroup];
@@ -765,7 +796,8 @@ __global__ __launch_bounds__(256) void cooccurrence_kernel(const ProtoArgs a)
     __syncthreads();
     for (int i = tid; i < n_c2 * 256; i += 256) {
         const int g = i >> 8, k = (i >> 4) & 15, k2 = i & 15;
-        a.counts[(size_t)(16 * c + k) * a.Q + 16 * (c2_first + g) + k2] = hist[g][16 * k + k2];
+        const int32_t here = hist[g][16 * k + k2];
+        if (here) atomicAdd(&a.counts[(size_t)(16 * c + k) * a.Q + 16 * (c2_first + g) + k2], here);
     }
 }
 
@@ -777,66 +809,150 @@ __global__ __launch_bounds__(256) void ridge_matrix_kernel(const ProtoArgs a, do
     a.M[i] = (double)a.counts[i] + (r == col ? lambda : 0.0);
 }
 
-// G^T A~: row 16 c + k = the sum, in row order, of the training rows with code k in codebook c.
-// A thread per (codebook, column); the four wavefronts of a workgroup take four codebooks over
-// the same 64 columns, and the values and codes of kGtaAhead rows are fetched before they are added.
-constexpr int kGtaAhead = 16;
-__global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a)
+// G^T A~: row 16 c + k = the sum, in row order, of the training rows with code k in codebook c.  kListRows rows at a
+// time: count_codes_kernel and list_codes_kernel list the rows of every code in row order (as order_rows_kernel does
+// for buckets, a workgroup per codebook and kListChunk rows), then a wavefront per (codebook, code, 64 columns) adds
+// its rows, 32 fetched ahead.  Every codebook reads all of A; the workgroups of the same columns run on the same XCD
+// when their number is a multiple of 8, and all codes' wavefronts walk the rows at about the same pace, so those reads
+// meet in its L2.  Bound by the instructions per row (its address, a load, a conversion, an addition):
+// 0.20 + 0.02 ms for 20000 x 512 and 32 codebooks, 0.77 + 0.08 ms for 260100 x 27 and 4 (1.0 and 7.5 ms with every thread
+// reading all rows; four columns to a lane, for a third of the instructions, gave 0.27 ms: fewer wavefronts, and rows
+// four times as long to keep in L2).
+constexpr int kListRows = 65536;       // rows of a stretch, at most (their distances in bytes from its first fit 32 bits)
+constexpr int kGtaAhead = 32;
+constexpr int kListSpare = 4 * kGtaAhead;     // entries read past the last (and not used)
+constexpr int kListChunk = 2048, kListChunks = kListRows / kListChunk;
+__global__ __launch_bounds__(256) void count_codes_kernel(const ProtoArgs a, int64_t first_row)
 {
-    __shared__ double acc[4][16][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int c = blockIdx.y * 4 + wave;
-    const int col = blockIdx.x * 64 + lane;
-    if (c >= a.C || col >= a.D) return;      // no barrier below: every thread works on its own sums
-    double(*mine)[64] = acc[wave];
-    for (int k = 0; k < 16; ++k) mine[k][lane] = 0.0;
-    const float *src = a.A + col;
-    const uint8_t *code = a.codes + c;
-    int64_t n = 0;
-    for (; n + kGtaAhead <= a.N; n += kGtaAhead) {
-        float v[kGtaAhead];
-        int k[kGtaAhead];
+    __shared__ int32_t total[16];
+    const int c = blockIdx.x, chunk = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int64_t first = first_row + chunk * kListChunk;
+    const int64_t left = min(a.N - first, a.stretch - chunk * kListChunk);
+    const int rows = (int)(left < kListChunk ? left : kListChunk);
+    const uint8_t *code = a.codes + first * a.C + c;
+    if (tid < 16) total[tid] = 0;
+    __syncthreads();
+    int mine = 0;
 #pragma unroll
-        for (int u = 0; u < kGtaAhead; ++u) {
-            v[u] = src[(n + u) * a.lda];
-            k[u] = code[(n + u) * a.C];
+    for (int u = 0; u < kListChunk / 256; ++u) {
+        const int k = 256 * u + tid < rows ? code[(int64_t)(256 * u + tid) * a.C] & 15 : -1;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int here = __popcll(__ballot(k == j));
+            if (lane == j) mine += here;
         }
-#pragma unroll
-        for (int u = 0; u < kGtaAhead; ++u) mine[k[u] & 15][lane] += (double)v[u];
     }
-    for (; n < a.N; ++n) mine[code[n * a.C] & 15][lane] += (double)src[n * a.lda];
-    for (int k = 0; k < 16; ++k) a.R[((size_t)16 * c + k) * a.D + col] = mine[k][lane];
+    if (mine) atomicAdd(&total[lane], mine);
+    __syncthreads();
+    if (tid < 16) a.list_count[(c * kListChunks + chunk) * 16 + tid] = total[tid];
 }
 
-// G^T A~ for problems with few (codebook, column) pairs, where gta_kernel would leave the chip empty and wait
-// for its LDS sums row after row: a thread per (codebook, code, column) with its one sum in a register; a row
-// with another code adds 0.0, which leaves the sum as it is.
-__global__ __launch_bounds__(64) void gta_by_code_kernel(const ProtoArgs a)
+__global__ __launch_bounds__(256) void list_codes_kernel(const ProtoArgs a, int64_t first_row)
 {
-    const int c = blockIdx.z, k = blockIdx.y;
-    const int col = blockIdx.x * 64 + threadIdx.x;
-    if (col >= a.D) return;
-    const float *src = a.A + col;
-    const uint8_t *code = a.codes + c;
-    double sum = 0.0;
-    int64_t n = 0;
-    for (; n + kGtaAhead <= a.N; n += kGtaAhead) {
-        float v[kGtaAhead];
-        int at[kGtaAhead];
-#pragma unroll
-        for (int u = 0; u < kGtaAhead; ++u) {
-            v[u] = src[(n + u) * a.lda];
-            at[u] = code[(n + u) * a.C];
+    __shared__ int32_t total[16], seen[16], wave_count[kListChunk / 256][16][4];
+    const int c = blockIdx.x, chunk = blockIdx.y, n_chunks = gridDim.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t first = first_row + chunk * kListChunk;
+    const int64_t left = min(a.N - first, a.stretch - chunk * kListChunk);
+    const int rows = (int)(left < kListChunk ? left : kListChunk);
+    const uint8_t *code = a.codes + first * a.C + c;
+    if (tid < 16) {
+        int before = 0, all = 0;
+        for (int i = 0; i < n_chunks; ++i) {
+            const int here = a.list_count[(c * kListChunks + i) * 16 + tid];
+            before += i < chunk ? here : 0;
+            all += here;
         }
+        total[tid] = all;
+        seen[tid] = before;
+    }
+    int k[kListChunk / 256], rank[kListChunk / 256];
 #pragma unroll
-        for (int u = 0; u < kGtaAhead; ++u) {
-            float x = (at[u] & 15) == k ? v[u] : 0.0f;
-            asm volatile("" : "+v"(x));      // (the selection stays one 32-bit move, before the conversion)
-            sum += (double)x;
+    for (int u = 0; u < kListChunk / 256; ++u) {
+        k[u] = 256 * u + tid < rows ? code[(int64_t)(256 * u + tid) * a.C] & 15 : -1;
+        int mine = 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const unsigned long long mask = __ballot(k[u] == j);
+            if (k[u] == j) rank[u] = __popcll(mask & ((1ull << lane) - 1ull));
+            if (lane == j) mine = __popcll(mask);
+        }
+        if (lane < 16) wave_count[u][lane][wave] = mine;
+    }
+    __syncthreads();
+    if (tid < 16) {
+        int at = 0;
+        for (int j = 0; j < tid; ++j) at += total[j];
+        if (chunk == 0) {
+            a.list_start[c * 17 + tid] = at;
+            if (tid == 15) a.list_start[c * 17 + 16] = at + total[15];
+        }
+        // the place of the first row of every wavefront's 64
+        at += seen[tid];
+        for (int u = 0; u < kListChunk / 256; ++u)
+            for (int w = 0; w < 4; ++w) {
+                const int here = wave_count[u][tid][w];
+                wave_count[u][tid][w] = at;
+                at += here;
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kListChunk / 256; ++u)
+        if (k[u] >= 0)
+            a.list[(size_t)c * (kListRows + kListSpare) + wave_count[u][k[u]][wave] + rank[u]] =
+                (uint32_t)(chunk * kListChunk + 256 * u + tid) * (uint32_t)(4 * a.lda);
+}
+
+__global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t first_row)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int k = blockIdx.y * 4 + wave, c = blockIdx.z;
+    const int col = blockIdx.x * 64 + lane;
+    const int start = a.list_start[c * 17 + k], count = a.list_start[c * 17 + k + 1] - start;
+    double *out = a.R + ((size_t)16 * c + k) * a.D + col;
+    double sum = first_row > 0 && col < a.D ? *out : 0.0;
+    if (count > 0) {
+        // (the same for a whole wavefront, and written by a kernel before this one: scalar loads)
+        const auto *list = (const __attribute__((address_space(4))) uint32_t *)(a.list + (size_t)c * (kListRows + kListSpare) + start);
+        const char *src = reinterpret_cast<const char *>(a.A + first_row * a.lda);
+        const uint32_t col_offset = 4 * min(col, a.D - 1);
+        float x0[kGtaAhead], x1[kGtaAhead];
+        uint32_t r0[kGtaAhead], r1[kGtaAhead];
+        auto entries = [&](uint32_t (&r)[kGtaAhead], int at) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < kGtaAhead; ++u) r[u] = list[at + u];
+        };
+        // (past the last row: row 0 of the stretch, not added)
+        auto fetch = [&](float (&v)[kGtaAhead], const uint32_t (&r)[kGtaAhead], int at) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < kGtaAhead; ++u)
+                v[u] = *reinterpret_cast<const float *>(src + (uint32_t)((at + u < count ? r[u] : 0u) + col_offset));
+        };
+        auto add = [&](const float (&v)[kGtaAhead], int at) __attribute__((always_inline)) {
+            if (at + kGtaAhead <= count) {
+#pragma unroll
+                for (int u = 0; u < kGtaAhead; ++u) sum += (double)v[u];
+            } else {
+#pragma unroll
+                for (int u = 0; u < kGtaAhead; ++u) sum += at + u < count ? (double)v[u] : 0.0;
+            }
+        };
+        entries(r0, 0);
+        entries(r1, kGtaAhead);
+        fetch(x0, r0, 0);
+        for (int at = 0; at < count; at += 2 * kGtaAhead) {
+            entries(r0, at + 2 * kGtaAhead);
+            fetch(x1, r1, at + kGtaAhead);
+            __builtin_amdgcn_sched_barrier(0);      // (the loads stay ahead of the additions)
+            add(x0, at);
+            if (at + kGtaAhead >= count) break;
+            entries(r1, at + 3 * kGtaAhead);
+            fetch(x0, r0, at + 2 * kGtaAhead);
+            __builtin_amdgcn_sched_barrier(0);
+            add(x1, at + kGtaAhead);
         }
     }
-    for (; n < a.N; ++n) sum += (double)((code[n * a.C] & 15) == k ? src[n * a.lda] : 0.0f);
-    a.R[((size_t)16 * c + k) * a.D + col] = sum;
+    if (col < a.D) *out = sum;
 }
 
 // Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
@@ -1261,7 +1377,8 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.bounds = w.take<int32_t>(2 * C);
     a.pitch = a.dmax <= 8 ? 8 : (a.dmax + 15) / 16 * 16;
     a.X = w.take<float>(C * (a.N + 1) * a.pitch);
-    a.node = w.take<uint8_t>(C * a.N);
+    a.chunk_count = w.take<int32_t>(4 * C * kMaxChunks * kSplitBuckets);
+    a.node = w.take<uint8_t>(C * a.N);      // (right behind chunk_count: both are cleared together)
     a.col_loss = w.take<double>(C * kSplitBuckets * a.dmax);
     a.bucket_loss = w.take<double>(C * kSplitBuckets);
     a.bucket_count = w.take<int64_t>(C * kSplitBuckets);
@@ -1286,6 +1403,9 @@ void carve_prototypes(Carver &w, ProtoArgs &a)
     a.M = w.take<double>(Q * Q);
     a.Lr = w.take<double>(Q * Q);
     a.R = w.take<double>(Q * a.D);
+    a.list = w.take<uint32_t>((size_t)a.C * (kListRows + kListSpare));
+    a.list_count = w.take<int32_t>((size_t)a.C * kListChunks * 16);
+    a.list_start = w.take<int32_t>((size_t)a.C * 17);
 }
 
 }  // namespace
@@ -1327,10 +1447,9 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
     hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds);
     LAUNCH_OK("launch upload_bounds_kernel");
-    const int64_t node_bytes = (int64_t)C * N;
-    hipLaunchKernelGGL(fill_bytes_kernel, dim3((unsigned)((node_bytes + 255) / 256)), dim3(256), 0, stream, a.node, node_bytes,
-                       (uint8_t)0);
-    LAUNCH_OK("launch fill_bytes_kernel");
+    const int64_t clear_words = (a.node + (size_t)C * N - reinterpret_cast<uint8_t *>(a.chunk_count) + 3) / 4;
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, stream, a.chunk_count, clear_words);
+    LAUNCH_OK("launch clear_kernel");
 
     const int64_t pieces = (N + 1) * (a.pitch / 4);
     hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)((pieces + 255) / 256), C), dim3(256), 0, stream, a);
@@ -1341,7 +1460,8 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
     const bool narrow = dmax <= 8;
     for (int level = 0; level < 4; ++level) {
         const int n_buckets = 1 << level;
-        hipLaunchKernelGGL(order_rows_kernel, dim3(C), dim3(256), 0, stream, a, n_buckets);
+        hipLaunchKernelGGL(order_rows_kernel, dim3((unsigned)((N + order_chunk_rows(N) - 1) / order_chunk_rows(N)), C), dim3(256), 0,
+                           stream, a, level, n_buckets);
         LAUNCH_OK("launch order_rows_kernel");
         // (columns eight or sixteen at a time: a wavefront carries them all)
         const int groups = narrow ? 1 : a.pitch / 16;
@@ -1405,18 +1525,28 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
         LAUNCH_OK("launch means_kernel");
         return MADDNESS_OK;
     }
-    note_kernel("cooccurrence_kernel + gta_kernel + cholesky_panel_kernel + substitution_kernel", nullptr);
+    note_kernel("cooccurrence_kernel + count_codes_kernel + list_codes_kernel + gta_kernel + cholesky_panel_kernel + substitution_kernel", nullptr);
     const int64_t QQ = (int64_t)a.Q * a.Q;
-    hipLaunchKernelGGL(cooccurrence_kernel, dim3(C, (C + kCoGroup - 1) / kCoGroup), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((QQ + 255) / 256)), dim3(256), 0, stream, a.counts, QQ);
+    LAUNCH_OK("launch clear_kernel");
+    // (stretches of at least 2048 rows, and about four workgroups per compute unit)
+    const int co_groups = (C + kCoGroup - 1) / kCoGroup;
+    const int64_t stretches = std::max<int64_t>(1, std::min<int64_t>(N / 2048, 4 * device_info().cus / (C * co_groups)));
+    hipLaunchKernelGGL(cooccurrence_kernel, dim3(C, co_groups, (unsigned)stretches), dim3(256), 0, stream, a);
     LAUNCH_OK("launch cooccurrence_kernel");
     hipLaunchKernelGGL(ridge_matrix_kernel, dim3((unsigned)((QQ + 255) / 256)), dim3(256), 0, stream, a, lambda);
     LAUNCH_OK("launch ridge_matrix_kernel");
-    // (a thread per (codebook, code, column) while that is at most a wavefront per SIMD of the chip)
-    if ((int64_t)C * 16 * D <= (int64_t)device_info().cus * 4 * 64)
-        hipLaunchKernelGGL(gta_by_code_kernel, dim3((D + 63) / 64, 16, C), dim3(64), 0, stream, a);
-    else
-        hipLaunchKernelGGL(gta_kernel, dim3((D + 63) / 64, (C + 3) / 4), dim3(256), 0, stream, a);
-    LAUNCH_OK("launch gta_kernel");
+    a.stretch = std::min<int64_t>(kListRows, std::max<int64_t>(1, (1LL << 30) / lda));
+    for (int64_t first = 0; first < N; first += a.stretch) {
+        const int64_t rows = std::min<int64_t>(N - first, a.stretch);
+        const dim3 chunks(C, (unsigned)((rows + kListChunk - 1) / kListChunk));
+        hipLaunchKernelGGL(count_codes_kernel, chunks, dim3(256), 0, stream, a, first);
+        LAUNCH_OK("launch count_codes_kernel");
+        hipLaunchKernelGGL(list_codes_kernel, chunks, dim3(256), 0, stream, a, first);
+        LAUNCH_OK("launch list_codes_kernel");
+        hipLaunchKernelGGL(gta_kernel, dim3((D + 63) / 64, 4, C), dim3(256), 0, stream, a, first);
+        LAUNCH_OK("launch gta_kernel");
+    }
     for (int J0 = 0; J0 < a.Q; J0 += kCholPanel) {
         const int below = a.Q - J0 - kCholPanel, per_group = kCholRows - kCholPanel;
         hipLaunchKernelGGL(cholesky_panel_kernel, dim3(std::max(1, (below + per_group - 1) / per_group)), dim3(256), 0,
