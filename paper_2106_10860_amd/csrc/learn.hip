@@ -956,376 +956,276 @@ __global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t fir
 }
 
 // Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
-// every sum over k ascending.  M is symmetric, and L_ik is kept at M[k][i] (rows of a column side by side).
-// One launch per panel of 16 columns J0 .. J0 + 15; a workgroup takes the 16 rows of the panel's
-// diagonal block (every workgroup works them out for itself, the first one stores them) and 48 rows
-// below it, four entries of a row per thread.  First the terms of the columns before the panel, in
-// chunks of kCholChunk columns staged in LDS, then the panel's own columns one after the other.
-constexpr int kCholPanel = 16, kCholRows = 64, kCholChunk = 32;
+// every sum over k ascending.  M is symmetric, and entry (i, j), i >= j, is kept at M[j][i] (a column side by side).
+// One launch per panel of 16 columns J0 .. J0 + 15, which takes the panel's terms off everything to its right: a
+// workgroup per 64 x 64 tile of what is left, which works out the panel's rows of L that it needs for itself (the 16 of
+// the diagonal block, those of its rows and those of its columns) and then subtracts their 16 products from its
+// entries, k ascending as panels and columns go.  The tiles of the first column store L, by rows; what they read stays
+// as it is.  Bound by the chain of 16 roots and divisions per panel, 12 us a launch.  (Subtracting all columns
+// before the panel at once, when the panel's turn comes, takes few workgroups and up to 31 us a launch: 0.65 against
+// 0.38 ms for Q = 512.)
+constexpr int kCholPanel = 16, kCholTile = 64, kCholPitch = kCholPanel + 1;
 __global__ __launch_bounds__(256) void cholesky_panel_kernel(const ProtoArgs a, int J0)
 {
-    __shared__ __align__(16) double Lc[kCholRows][kCholChunk + 2];     // (rows 4 banks apart: 16-byte reads of 16 rows at once)
-    __shared__ double T[kCholRows][kCholPanel + 1];
-    const int Q = a.Q;
+    __shared__ double T[kCholPanel + 2 * kCholTile][kCholPitch];     // rows of L: the panel's, the tile's rows, its columns
+    if (blockIdx.y > blockIdx.x) return;                             // (the other triangle)
+    const int Q = a.Q, tid = threadIdx.x;
     double *M = a.M;
-    const int tid = threadIdx.x;
-    auto global_row = [&](int r) {
-        return r < kCholPanel ? J0 + r : J0 + kCholPanel + (int)blockIdx.x * (kCholRows - kCholPanel) + (r - kCholPanel);
-    };
-    const int r = tid >> 2, cg = tid & 3;
-    const int gi = global_row(r);
-    double s[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] = gi < Q ? M[(size_t)(J0 + 4 * cg + e) * Q + gi] : 0.0;
-
-    // staging: thread -> row (tid & 63) of the chunk, columns (tid >> 6) + 4 u
-    const int srow = tid & 63, sk = tid >> 6;
-    const int sgi = global_row(srow);
-    constexpr int kPer = kCholChunk / 4;
-    double pre[kPer];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int k = k0 + sk + 4 * u;
-            pre[u] = (sgi < Q && k < J0) ? M[(size_t)k * Q + sgi] : 0.0;
-        }
-    };
-    if (J0 > 0) fetch(0);
-    for (int k0 = 0; k0 < J0; k0 += kCholChunk) {
-        __syncthreads();                      // the chunk before this one has been used
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) Lc[srow][sk + 4 * u] = pre[u];
-        __syncthreads();
-        if (k0 + kCholChunk < J0) fetch(k0 + kCholChunk);
-        const int kc = min(kCholChunk, J0 - k0);
-        for (int kk = 0; kk < kc; kk += 2) {          // (two columns to an LDS read; kc is a multiple of 16)
-            const double2 li = *reinterpret_cast<const double2 *>(&Lc[r][kk]);
-            double2 lj[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) lj[e] = *reinterpret_cast<const double2 *>(&Lc[4 * cg + e][kk]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] -= li.x * lj[e].x;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] -= li.y * lj[e].y;
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) T[r][4 * cg + e] = s[e];
-    __syncthreads();
-
-    // the panel's own columns: a thread per row (the first wavefront), the row's entries in registers
+    const int row0 = J0 + kCholPanel + blockIdx.x * kCholTile, col0 = J0 + kCholPanel + blockIdx.y * kCholTile;
+    const int own = tid < kCholPanel + 2 * kCholTile ? tid : 0;
+    const int grow = own < kCholPanel ? J0 + own : own < kCholPanel + kCholTile ? row0 + own - kCholPanel
+                                                                                : col0 + own - kCholPanel - kCholTile;
     double t[kCholPanel];
-    const int row = tid, grow = global_row(tid < kCholRows ? tid : 0);
-    if (tid < kCholRows)
 #pragma unroll
-        for (int j = 0; j < kCholPanel; ++j) t[j] = T[row][j];
+    for (int j = 0; j < kCholPanel; ++j) t[j] = grow < Q && grow >= J0 + j ? M[(size_t)(J0 + j) * Q + grow] : 0.0;
+    // a tile's entries: four rows of four columns to a thread
+    const int tr = 4 * (tid & 15), tc = 4 * (tid >> 4);
+    double s[4][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const int r = row0 + tr + f, c = col0 + tc + e;
+            s[e][f] = r < Q && c <= r ? M[(size_t)c * Q + r] : 0.0;
+        }
 #pragma unroll
     for (int j = 0; j < kCholPanel; ++j) {
-        if (tid < kCholRows) {
+        if (tid == j) {
+            t[j] = sqrt(t[j]);
+            T[j][j] = t[j];
+        }
+        __syncthreads();
+        if (tid != j) t[j] = t[j] / T[j][j];
+        if (tid > j && tid < kCholPanel) T[tid][j] = t[j];
+        __syncthreads();
 #pragma unroll
-            for (int k = 0; k < j; ++k) t[j] -= t[k] * T[j][k];
-            if (row == j) {
-                t[j] = sqrt(t[j]);
-                T[j][j] = t[j];
-            }
-        }
-        __syncthreads();
-        if (tid < kCholRows && row != j) {
-            t[j] = t[j] / T[j][j];
-            if (row < kCholPanel) T[row][j] = t[j];     // a row of the diagonal block: read by the rows below
-        }
-        __syncthreads();
+        for (int j2 = j + 1; j2 < kCholPanel; ++j2) t[j2] -= t[j] * T[j2][j];
     }
-    if (tid < kCholRows && grow < Q && (row >= kCholPanel || blockIdx.x == 0))
+    if (tid >= kCholPanel && tid < kCholPanel + 2 * kCholTile)
+#pragma unroll
+        for (int j = 0; j < kCholPanel; ++j) T[tid][j] = t[j];
+    if (blockIdx.y == 0 && tid < kCholPanel + kCholTile && grow < Q && (tid >= kCholPanel || blockIdx.x == 0))
 #pragma unroll
         for (int j = 0; j < kCholPanel; ++j)
-            if (row >= kCholPanel || j <= row) M[(size_t)(J0 + j) * Q + grow] = t[j];
+            if (tid >= kCholPanel || j <= tid) a.Lr[(size_t)grow * Q + J0 + j] = t[j];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kCholPanel; ++k) {
+        double li[4], lj[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            li[e] = T[kCholPanel + tr + e][k];
+            lj[e] = T[kCholPanel + kCholTile + tc + e][k];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int f = 0; f < 4; ++f) s[e][f] -= li[f] * lj[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const int r = row0 + tr + f, c = col0 + tc + e;
+            if (r < Q && c <= r) M[(size_t)c * Q + r] = s[e][f];
+        }
 }
 
 __global__ __launch_bounds__(256) void transpose_factor_kernel(const ProtoArgs a)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= (int64_t)a.Q * a.Q) return;
-    const int r = (int)(i / a.Q), k = (int)(i - (int64_t)r * a.Q);
-    a.Lr[i] = k <= r ? a.M[(size_t)k * a.Q + r] : 0.0;
+    const int k = (int)(i / a.Q), r = (int)(i - (int64_t)k * a.Q);
+    if (k <= r) a.M[i] = a.Lr[(size_t)r * a.Q + k];
 }
 
 // L y = G^T A~ and L^T P = y, sums over k ascending: y_i = (b_i - sum_{k<i} L_ik y_k) / L_ii, then
-// P_i = (y_i - sum_{k>i} L_ki P_k) / L_ii.  A workgroup takes NC columns of A~ and keeps them in LDS
-// for both sweeps; the first NC threads carry a column each through the sums (in the second sweep the
-// sum of a row begins with the value found just before, so a column's subtractions are one chain),
-// while all threads fetch the next row of L (first sweep) or of L^T (second sweep, kept at M) through
-// registers into the other of two LDS buffers.  A wavefront issues one vector instruction in four
-// cycles, so the chain's loop is kept to the two LDS reads, the product and the subtraction of a term:
-// NC is a constant (the reads take immediate offsets) and terms go in batches of kSubBatch without a
-// bound check.  A batch may run past the row's last term: there the buffer's entry of L is 0 (buffers
-// start as zeros, a row's diagonal entry is kept apart, and kSubPad entries and rows follow the last),
-// the term is 0 times a finite value, and subtracting 0 changes nothing.
-constexpr int kSubMaxPer = MADDNESS_MAX_C * 16 / 256;     // most values of a row a thread fetches
-constexpr int kSubBatch = 8;
-constexpr int kSubPad = 5 * kSubBatch;                    // the reads run up to five batches past a row's last term
-size_t substitution_lds_bytes(int Q, int nc) { return sizeof(double) * ((size_t)(Q + kSubPad) * nc + 2 * (size_t)(Q + kSubPad + 1)); }
+// P_i = (y_i - sum_{k>i} L_ki P_k) / L_ii.  A workgroup takes NC columns of A~ and keeps them in LDS for both.
+// Forward, a sum ends with the value found last, so 16 rows at a time are solved (by every wavefront for itself, a row of
+// 16 lanes per column) and their products taken off all rows below, which the wavefronts share out.  Backward, a sum
+// BEGINS with the value found just before, and a column's subtractions are one chain of Q^2 / 2 steps: one wavefront
+// subtracts the products, 16 at a time in the lanes of a row, by row broadcasts (as in add_16_in_order), while the other
+// three form those of the next row, all but the one with the value that is just being found; the factor's rows come
+// kSubDepth ahead.  Bound by that chain, 5.2 cycles a step: 0.64 ms for
+// 512 columns of A~ and Q = 512 (2.24 ms with a lane per column that read its products from LDS).  Four columns to a workgroup where LDS holds them and two
+// rows' products (up to 104 codebooks), else one.
+constexpr int kSubDepth = 4, kSubHelpers = 192, kSubSpare = 128;
+constexpr size_t substitution_lds_bytes(int Q, int nc) { return sizeof(double) * (3 * (size_t)nc * (Q + 16) + kSubSpare + 4); }
 
-template <int NC>
+template <int K>
+__device__ __forceinline__ double row_broadcast(double x)
+{
+    const int64_t bits = __builtin_bit_cast(int64_t, x);
+    const int low = __builtin_amdgcn_update_dpp(0, (int)bits, 0x150 + K, 0xf, 0xf, true);
+    const int high = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), 0x150 + K, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (int64_t)high << 32 | (uint32_t)low);
+}
+
+template <int NC, int kPer>
 __global__ __launch_bounds__(256) void substitution_kernel(const ProtoArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int Q = a.Q, D = a.D, tid = threadIdx.x;
-    const int Qp = Q + kSubPad;
-    double *X = reinterpret_cast<double *>(lds_raw);      // [Qp][NC]
-    double *rows = X + (size_t)Qp * NC;                   // [2][Qp + 1]: a row of the factor, its diagonal entry last
+    double *X = reinterpret_cast<double *>(lds_raw);      // [NC][Q + 16]
+    const int Q = a.Q, D = a.D, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = lane & 15;
+    const int blocks = Q / 16;
     const int col0 = blockIdx.x * NC;
-    const int ncols = min(NC, D - col0);
-    for (int idx = tid; idx < Qp * NC; idx += 256) {
+    for (int idx = tid; idx < Q * NC; idx += 256) {
         const int i = idx / NC, cc = idx % NC;
-        X[idx] = (i < Q && cc < ncols) ? a.R[(size_t)i * D + col0 + cc] : 0.0;
+        X[cc * (Q + 16) + i] = col0 + cc < D ? a.R[(size_t)i * D + col0 + cc] : 0.0;
     }
-    for (int idx = tid; idx < 2 * (Qp + 1); idx += 256) rows[idx] = 0.0;
+    double *x = X + min(lane >> 4, NC - 1) * (Q + 16);      // (NC = 1: the other rows of lanes do the same)
     __syncthreads();
-    // step s < Q: row i = s of L, entries 0..i; step s >= Q: row i = 2Q - 1 - s of L^T, entries i..Q-1
-    const int n_steps = 2 * Q;
-    const int per = (Q + 255) / 256;
-    double ahead[kSubMaxPer];
-    auto fetch = [&](int s) {
-        if (s >= n_steps) return;
-        const bool fwd = s < Q;
-        const int i = fwd ? s : 2 * Q - 1 - s;
-        const double *src = (fwd ? a.Lr : a.M) + (size_t)i * Q;
-        const int lo = fwd ? 0 : i, hi = fwd ? i + 1 : Q;
+    // forward
+    for (int J = 0; J < blocks; ++J) {
+        double y[16];
+        {
+            const double *Li = a.Lr + (size_t)(16 * J + l) * Q + 16 * J;
+            double L[16];
 #pragma unroll
-        for (int u = 0; u < kSubMaxPer; ++u) {
-            const int k = lo + tid + 256 * u;
-            if (u < per && k < hi) ahead[u] = src[k];
-        }
-    };
-    auto stash = [&](int s) {
-        if (s >= n_steps) return;
-        const bool fwd = s < Q;
-        const int i = fwd ? s : 2 * Q - 1 - s;
-        const int lo = fwd ? 0 : i, hi = fwd ? i + 1 : Q;
-        double *dst = rows + (size_t)(s & 1) * (Qp + 1);
-#pragma unroll
-        for (int u = 0; u < kSubMaxPer; ++u) {
-            const int k = lo + tid + 256 * u;
-            if (u < per && k < hi) {
-                dst[k] = k == i ? 0.0 : ahead[u];
-                if (k == i) dst[Qp] = ahead[u];
-            }
-        }
-    };
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int s = 0; s < n_steps; ++s) {
-        fetch(s + 1);
-        if (tid < NC) {
-            const bool fwd = s < Q;
-            const int i = fwd ? s : 2 * Q - 1 - s;
-            const double *Li = rows + (size_t)(s & 1) * (Qp + 1);
-            const int lo = fwd ? 0 : i + 1, hi = fwd ? i : Q;
-            double v = X[(size_t)i * NC + tid];
-            const double *pl = Li + lo, *px = X + (size_t)lo * NC + tid;
-            double l0[kSubBatch], x0[kSubBatch], l1[kSubBatch], x1[kSubBatch], l2[kSubBatch], x2[kSubBatch];
-            auto read = [&](int at, double *l, double *x) {
-#pragma unroll
-                for (int u = 0; u < kSubBatch; ++u) {
-                    l[u] = pl[at + u];
-                    x[u] = px[(at + u) * NC];
-                }
+            for (int k = 0; k < 16; ++k) L[k] = Li[k];
+            const double diagonal = Li[l];
+            double acc = x[16 * J + l];
+            auto step = [&](auto index) __attribute__((always_inline)) {
+                constexpr int k = decltype(index)::value;
+                const double quotient = acc / diagonal;
+                y[k] = row_broadcast<k>(quotient);
+                acc = l > k ? acc - L[k] * y[k] : l == k ? quotient : acc;
             };
-            auto subtract = [&](const double *l, const double *x) {
-#pragma unroll
-                for (int u = 0; u < kSubBatch; ++u) v -= l[u] * x[u];
-            };
-            read(0, l0, x0);
-            read(kSubBatch, l1, x1);
-            for (int k = lo; k < hi; k += 3 * kSubBatch) {
-                // (the fences keep the compiler from gathering the reads of several batches in one place)
-                read(2 * kSubBatch, l2, x2);
-                __builtin_amdgcn_sched_barrier(0);
-                subtract(l0, x0);
-                __builtin_amdgcn_sched_barrier(0);
-                read(3 * kSubBatch, l0, x0);
-                __builtin_amdgcn_sched_barrier(0);
-                subtract(l1, x1);
-                __builtin_amdgcn_sched_barrier(0);
-                read(4 * kSubBatch, l1, x1);
-                __builtin_amdgcn_sched_barrier(0);
-                subtract(l2, x2);
-                __builtin_amdgcn_sched_barrier(0);
-                pl += 3 * kSubBatch;
-                px += 3 * kSubBatch * NC;
-            }
-            X[(size_t)i * NC + tid] = v / Li[Qp];
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
+            step(std::integral_constant<int, 4>{});
+            step(std::integral_constant<int, 5>{});
+            step(std::integral_constant<int, 6>{});
+            step(std::integral_constant<int, 7>{});
+            step(std::integral_constant<int, 8>{});
+            step(std::integral_constant<int, 9>{});
+            step(std::integral_constant<int, 10>{});
+            step(std::integral_constant<int, 11>{});
+            step(std::integral_constant<int, 12>{});
+            step(std::integral_constant<int, 13>{});
+            step(std::integral_constant<int, 14>{});
+            step(std::integral_constant<int, 15>{});
+            __syncthreads();                          // (every wavefront has read the panel's rows)
+            if (wave == 0) x[16 * J + l] = acc;
         }
-        stash(s + 1);
+        double2 L0[8], L1[8];
+        auto fetch = [&](double2 (&L)[8], int m) __attribute__((always_inline)) {
+            const double2 *src = reinterpret_cast<const double2 *>(a.Lr + (size_t)(16 * min(m, blocks - 1) + l) * Q + 16 * J);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) L[u] = src[u];
+        };
+        auto take_off = [&](const double2 (&L)[8], int m) __attribute__((always_inline)) {
+            double v = x[16 * m + l];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                v -= L[u].x * y[2 * u];
+                v -= L[u].y * y[2 * u + 1];
+            }
+            x[16 * m + l] = v;
+        };
+        int m = J + 1 + wave;
+        fetch(L0, m);
+        for (; m < blocks; m += 8) {
+            fetch(L1, m + 4);
+            __builtin_amdgcn_sched_barrier(0);
+            take_off(L0, m);
+            if (m + 4 >= blocks) break;
+            fetch(L0, m + 8);
+            __builtin_amdgcn_sched_barrier(0);
+            take_off(L1, m + 4);
+        }
         __syncthreads();
+    }
+    // backward
+    double *products = X + NC * (Q + 16);                          // [2][NC][Q + 16] of row i in products[i & 1]
+    double *ends = products + 2 * NC * (Q + 16) + kSubSpare;       // [2][2] row i's diagonal entry and the one beside it
+    const int ht = tid - 64;
+    double ring[kSubDepth][kPer];
+    // helpers: entries i + ht + kSubHelpers u of row i of L^T
+    auto fetch_row = [&](int i, double (&L)[kPer]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int k = i + ht + kSubHelpers * u;
+            if (i >= 0 && k < Q) L[u] = a.M[(size_t)i * Q + k];
+        }
+    };
+    auto lay_out = [&](int i, const double (&L)[kPer]) __attribute__((always_inline)) {
+        double *dst = products + (i & 1) * NC * (Q + 16);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int k = i + ht + kSubHelpers * u;
+            if (i < 0 || k >= Q) continue;
+            if (u == 0 && ht < 2) {
+                ends[2 * (i & 1) + ht] = L[u];
+                continue;
+            }
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) dst[cc * (Q + 16) + k] = L[u] * X[cc * (Q + 16) + k];
+        }
+    };
+    if (ht >= 0) {
+#pragma unroll
+        for (int u = 0; u < kSubDepth; ++u) fetch_row(Q - 1 - u, ring[u]);
+        lay_out(Q - 1, ring[0]);
+        fetch_row(Q - 1 - kSubDepth, ring[0]);
+    }
+    __syncthreads();
+    double value = 0.0, minus_one = -1.0;
+    asm("" : "+v"(minus_one));
+    auto solve_row = [&](int i) __attribute__((always_inline)) {
+        const int first = (i + 1) >> 4, k0 = 16 * first + l;
+        const double *row = products + ((i & 1) * NC + min(lane >> 4, NC - 1)) * (Q + 16) + l;
+        const double diagonal = ends[2 * (i & 1)], beside = ends[2 * (i & 1) + 1];
+        double acc = x[i];
+        if (first < blocks) {
+            double p[4], p2[4];
+            const double t = row[16 * first];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) p[u] = row[16 * (first + 1 + u)];        // (past the last block: read, not used)
+            add_16_in_order(acc, k0 > i + 1 ? t : k0 == i + 1 ? beside * value : 0.0, minus_one);
+            int m = first + 1;
+            for (; m + 4 <= blocks; m += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p2[u] = row[16 * (m + 4 + u)];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) add_16_in_order(acc, p[u], minus_one);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p[u] = p2[u];
+            }
+            if (m < blocks) add_16_in_order(acc, p[0], minus_one);
+            if (m + 1 < blocks) add_16_in_order(acc, p[1], minus_one);
+            if (m + 2 < blocks) add_16_in_order(acc, p[2], minus_one);
+        }
+        value = acc / diagonal;
+        if (l == 0) x[i] = value;
+    };
+    for (int i0 = Q - 1; i0 >= 0; i0 -= kSubDepth) {            // (Q is a multiple of kSubDepth)
+#pragma unroll
+        for (int u = 0; u < kSubDepth; ++u) {
+            const int i = i0 - u;
+            if (ht < 0) {
+                solve_row(i);
+            } else {
+                lay_out(i - 1, ring[(u + 1) % kSubDepth]);
+                fetch_row(i - 1 - kSubDepth, ring[(u + 1) % kSubDepth]);
+            }
+            __syncthreads();
+        }
     }
     for (int idx = tid; idx < Q * NC; idx += 256) {
         const int i = idx / NC, cc = idx % NC;
-        if (cc < ncols) a.P[(size_t)i * D + col0 + cc] = (float)X[idx];
+        if (col0 + cc < D) a.P[(size_t)i * D + col0 + cc] = (float)X[cc * (Q + 16) + i];
     }
 }
 
-template <int NC>
+template <int NC, int kPer>
 int launch_substitution(const ProtoArgs &a, hipStream_t stream)
 {
-    if (int rc = allow_full_lds<substitution_kernel<NC>>(); rc != MADDNESS_OK) return rc;
-    hipLaunchKernelGGL(substitution_kernel<NC>, dim3((a.D + NC - 1) / NC), dim3(256), substitution_lds_bytes(a.Q, NC), stream, a);
-    return MADDNESS_OK;
-}
-
-// The substitutions with the products taken out of the chain.  While the first wavefront carries its columns
-// through the sum of row i, the other three form the products L_i'k x_k of the NEXT row i' for every k whose x_k
-// is known by then (all but the one the chain is just working out) and leave them in LDS; the chain of row i'
-// then only reads a product and subtracts it, and forms the one missing product itself - the last term going
-// forward, the first going back, so that the terms keep their order.  Same products, same subtractions, a chain
-// of half the instructions.  LDS holds the columns, two sets of products and three rows of the factor, so a
-// workgroup takes fewer columns than substitution_kernel does; factors too large for that stay with it.
-constexpr int kSubHelpers = 192;
-constexpr int kSubMaxPerHelper = (MADDNESS_MAX_C * 16 + kSubHelpers - 1) / kSubHelpers;
-size_t substitution_products_lds_bytes(int Q, int nc)
-{
-    return sizeof(double) * (3 * (size_t)(Q + kSubPad) * nc + 3 * (size_t)(Q + kSubPad + 1));
-}
-
-template <int NC>
-__global__ __launch_bounds__(256) void substitution_products_kernel(const ProtoArgs a)
-{
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int Q = a.Q, D = a.D, tid = threadIdx.x;
-    const int Qp = Q + kSubPad;
-    double *X = reinterpret_cast<double *>(lds_raw);      // [Qp][NC]
-    double *P = X + (size_t)Qp * NC;                      // [2][Qp][NC] products of the row of step s in P[s & 1]
-    double *rows = P + 2 * (size_t)Qp * NC;               // [3][Qp + 1] the row of step s in rows[s % 3], its diagonal entry last
-    const int col0 = blockIdx.x * NC;
-    const int ncols = min(NC, D - col0);
-    for (int idx = tid; idx < Qp * NC; idx += 256) {
-        const int i = idx / NC, cc = idx % NC;
-        X[idx] = (i < Q && cc < ncols) ? a.R[(size_t)i * D + col0 + cc] : 0.0;
-    }
-    for (int idx = tid; idx < 2 * Qp * NC + 3 * (Qp + 1); idx += 256) P[idx] = 0.0;     // (products and rows)
-    __syncthreads();
-    // step s < Q: row i = s of L, entries 0..i; step s >= Q: row i = 2Q - 1 - s of L^T, entries i..Q-1
-    const int n_steps = 2 * Q;
-    const int ht = tid - 64;                              // helper number (the threads of the other three wavefronts)
-    const int per = (Q + kSubHelpers - 1) / kSubHelpers;
-    double ahead[kSubMaxPerHelper];
-    auto fetch = [&](int s) __attribute__((always_inline)) {
-        if (s >= n_steps || ht < 0) return;
-        const bool fwd = s < Q;
-        const int i = fwd ? s : 2 * Q - 1 - s;
-        const double *src = (fwd ? a.Lr : a.M) + (size_t)i * Q;
-        const int lo = fwd ? 0 : i, hi = fwd ? i + 1 : Q;
-#pragma unroll
-        for (int u = 0; u < kSubMaxPerHelper; ++u) {
-            const int k = lo + ht + kSubHelpers * u;
-            if (u < per && k < hi) ahead[u] = src[k];
-        }
-    };
-    auto stash = [&](int s) __attribute__((always_inline)) {
-        if (s >= n_steps || ht < 0) return;
-        const bool fwd = s < Q;
-        const int i = fwd ? s : 2 * Q - 1 - s;
-        const int lo = fwd ? 0 : i, hi = fwd ? i + 1 : Q;
-        double *dst = rows + (size_t)(s % 3) * (Qp + 1);
-#pragma unroll
-        for (int u = 0; u < kSubMaxPerHelper; ++u) {
-            const int k = lo + ht + kSubHelpers * u;
-            if (u < per && k < hi) {
-                dst[k] = ahead[u];
-                if (k == i) dst[Qp] = ahead[u];
-            }
-        }
-    };
-    // the products of the row of step s, for every k but the one next to the diagonal; zeros after the last
-    // (going forward; going back the places after Q - 1 are never written and stay zero)
-    auto products = [&](int s) __attribute__((always_inline)) {
-        if (s >= n_steps || ht < 0) return;
-        const bool fwd = s < Q;
-        const int i = fwd ? s : 2 * Q - 1 - s;
-        const double *Li = rows + (size_t)(s % 3) * (Qp + 1);
-        double *dst = P + (size_t)(s & 1) * Qp * NC;
-        const int k_first = fwd ? 0 : i + 2, k_end = fwd ? max(i - 1, 0) : Q;      // [k_first, k_end)
-        int idx = k_first * NC + ht;
-        const int idx_end = k_end * NC;
-        for (; idx + 3 * kSubHelpers < idx_end; idx += 4 * kSubHelpers) {
-            double l[4], x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                l[u] = Li[(idx + u * kSubHelpers) / NC];
-                x[u] = X[idx + u * kSubHelpers];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) dst[idx + u * kSubHelpers] = l[u] * x[u];
-        }
-        for (; idx < idx_end; idx += kSubHelpers) dst[idx] = Li[idx / NC] * X[idx];
-        if (fwd)
-            for (int z = k_end * NC + ht; z < (k_end + 2 * kSubBatch) * NC; z += kSubHelpers) dst[z] = 0.0;
-    };
-    fetch(0);
-    stash(0);
-    fetch(1);
-    stash(1);
-    __syncthreads();
-    for (int s = 0; s < n_steps; ++s) {
-        fetch(s + 2);
-        if (tid < NC) {
-            const bool fwd = s < Q;
-            const int i = fwd ? s : 2 * Q - 1 - s;
-            const double *Li = rows + (size_t)(s % 3) * (Qp + 1);
-            const int lo = fwd ? 0 : i + 2, hi = fwd ? i - 1 : Q;       // the terms whose products are in P
-            double v = X[(size_t)i * NC + tid];
-            if (!fwd && i + 1 < Q) v -= Li[i + 1] * X[(size_t)(i + 1) * NC + tid];
-            const double *pp = P + (size_t)(s & 1) * Qp * NC + (size_t)lo * NC + tid;
-            double p0[kSubBatch], p1[kSubBatch], p2[kSubBatch];
-            auto read = [&](int at, double *t) __attribute__((always_inline)) {
-#pragma unroll
-                for (int u = 0; u < kSubBatch; ++u) t[u] = pp[(at + u) * NC];
-            };
-            auto subtract = [&](const double *t) __attribute__((always_inline)) {
-#pragma unroll
-                for (int u = 0; u < kSubBatch; ++u) v -= t[u];
-            };
-            read(0, p0);
-            read(kSubBatch, p1);
-            for (int k = lo; k < hi; k += 3 * kSubBatch) {
-                // (the fences keep the compiler from gathering the reads of several batches in one place; a batch
-                // past the last term subtracts zeros, or is read and not used)
-                read(2 * kSubBatch, p2);
-                __builtin_amdgcn_sched_barrier(0);
-                subtract(p0);
-                __builtin_amdgcn_sched_barrier(0);
-                read(3 * kSubBatch, p0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (k + kSubBatch < hi) subtract(p1);
-                __builtin_amdgcn_sched_barrier(0);
-                read(4 * kSubBatch, p1);
-                __builtin_amdgcn_sched_barrier(0);
-                if (k + 2 * kSubBatch < hi) subtract(p2);
-                __builtin_amdgcn_sched_barrier(0);
-                pp += 3 * kSubBatch * NC;
-            }
-            if (fwd && i >= 1) v -= Li[i - 1] * X[(size_t)(i - 1) * NC + tid];
-            X[(size_t)i * NC + tid] = v / Li[Qp];
-        } else {
-            products(s + 1);
-        }
-        stash(s + 2);
-        __syncthreads();
-    }
-    for (int idx = tid; idx < Q * NC; idx += 256) {
-        const int i = idx / NC, cc = idx % NC;
-        if (cc < ncols) a.P[(size_t)i * D + col0 + cc] = (float)X[idx];
-    }
-}
-
-template <int NC>
-int launch_substitution_products(const ProtoArgs &a, hipStream_t stream)
-{
-    if (int rc = allow_full_lds<substitution_products_kernel<NC>>(); rc != MADDNESS_OK) return rc;
-    hipLaunchKernelGGL(substitution_products_kernel<NC>, dim3((a.D + NC - 1) / NC), dim3(256),
-                       substitution_products_lds_bytes(a.Q, NC), stream, a);
+    if (int rc = allow_full_lds<substitution_kernel<NC, kPer>>(); rc != MADDNESS_OK) return rc;
+    hipLaunchKernelGGL((substitution_kernel<NC, kPer>), dim3((a.D + NC - 1) / NC), dim3(256), substitution_lds_bytes(a.Q, NC), stream, a);
     return MADDNESS_OK;
 }
 
@@ -1548,43 +1448,21 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
         LAUNCH_OK("launch gta_kernel");
     }
     for (int J0 = 0; J0 < a.Q; J0 += kCholPanel) {
-        const int below = a.Q - J0 - kCholPanel, per_group = kCholRows - kCholPanel;
-        hipLaunchKernelGGL(cholesky_panel_kernel, dim3(std::max(1, (below + per_group - 1) / per_group)), dim3(256), 0,
-                           stream, a, J0);
+        const unsigned tiles = std::max(1, (a.Q - J0 - kCholPanel + kCholTile - 1) / kCholTile);
+        hipLaunchKernelGGL(cholesky_panel_kernel, dim3(tiles, tiles), dim3(256), 0, stream, a, J0);
         LAUNCH_OK("launch cholesky_panel_kernel");
     }
     hipLaunchKernelGGL(transpose_factor_kernel, dim3((unsigned)((QQ + 255) / 256)), dim3(256), 0, stream, a);
     LAUNCH_OK("launch transpose_factor_kernel");
-    // the kernel that takes the products out of the chain where its LDS layout fits (as many columns of A~ per
-    // workgroup as fit, a power of two up to 16); else substitution_kernel (as many columns as LDS holds beside two
-    // rows of the factor: a power of two, a wavefront's worth at most)
     const size_t lds_limit = (size_t)device_info().lds_per_block;
+    if (substitution_lds_bytes(a.Q, 1) > lds_limit)
+        return fail(MADDNESS_E_UNSUPPORTED, "maddness_learn_prototypes: a column of 16 C values does not fit in LDS");
+    // (a helper's registers hold its entries of a row: Q / kSubHelpers of them)
     int rc = MADDNESS_OK;
-    int npc = 16;
-    while (npc > 1 && substitution_products_lds_bytes(a.Q, npc) > lds_limit) npc >>= 1;
-    if (substitution_products_lds_bytes(a.Q, npc) <= lds_limit) {
-        switch (npc) {
-        case 16: rc = launch_substitution_products<16>(a, stream); break;
-        case 8: rc = launch_substitution_products<8>(a, stream); break;
-        case 4: rc = launch_substitution_products<4>(a, stream); break;
-        case 2: rc = launch_substitution_products<2>(a, stream); break;
-        default: rc = launch_substitution_products<1>(a, stream); break;
-        }
-    } else {
-        int nc = 64;
-        while (nc > 1 && substitution_lds_bytes(a.Q, nc) > lds_limit) nc >>= 1;
-        if (substitution_lds_bytes(a.Q, nc) > lds_limit)
-            return fail(MADDNESS_E_UNSUPPORTED, "maddness_learn_prototypes: a column of 16 C values does not fit in LDS");
-        switch (nc) {
-        case 64: rc = launch_substitution<64>(a, stream); break;
-        case 32: rc = launch_substitution<32>(a, stream); break;
-        case 16: rc = launch_substitution<16>(a, stream); break;
-        case 8: rc = launch_substitution<8>(a, stream); break;
-        case 4: rc = launch_substitution<4>(a, stream); break;
-        case 2: rc = launch_substitution<2>(a, stream); break;
-        default: rc = launch_substitution<1>(a, stream); break;
-        }
-    }
+    if (a.Q <= 3 * kSubHelpers) rc = launch_substitution<4, 3>(a, stream);
+    else if (a.Q <= 6 * kSubHelpers) rc = launch_substitution<4, 6>(a, stream);
+    else if (substitution_lds_bytes(a.Q, 4) <= lds_limit && a.Q <= 9 * kSubHelpers) rc = launch_substitution<4, 9>(a, stream);
+    else rc = launch_substitution<1, 22>(a, stream);
     if (rc != MADDNESS_OK) return rc;
     LAUNCH_OK("launch substitution_kernel");
     return MADDNESS_OK;
