@@ -135,12 +135,12 @@ int maddness_build_luts_pooled(const maddness_params *params, const float *B, in
 /*
  * maddness_build_luts for callers that cannot allocate device memory (code under HIP
  * graph capture, serving loops, harnesses that forbid hipMalloc): the workspace is an
- * array of MADDNESS_STATIC_WORKSPACE_BYTES bytes inside the library, one per GPU,
+ * array inside the library (MADDNESS_STATIC_WORKSPACE_BYTES and a sixteenth), one per GPU,
  * held from the first use on that GPU until the process ends.  The call allocates
  * nothing; same kernels, same results as maddness_build_luts, bit for bit.
- * Shapes whose workspace (maddness_build_luts_workspace) exceeds that size are
- * refused with MADDNESS_E_UNSUPPORTED before anything is launched (C = 64, M = 512
- * needs 4.3 MiB).  Every call on one GPU uses the same array: calls that overlap in
+ * Shapes for which 8 (17 C M + 2 C) + 4 M bytes, rounded up to a multiple of 256,
+ * exceed that size are refused with MADDNESS_E_UNSUPPORTED before anything is launched
+ * (C = 64, M = 512: 4.3 MiB).  Every call on one GPU uses the same array: calls that overlap in
  * time on one GPU (different streams, different threads) race and must be ordered by
  * the caller.  Nothing in the array has to be cleared between calls: every word a
  * call reads it has written itself before.

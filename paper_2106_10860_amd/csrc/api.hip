@@ -209,7 +209,7 @@ int maddness_build_luts_static(const maddness_params *params, const float *B, in
     int rc = check_params(params, false, true);
     if (rc != MADDNESS_OK) return rc;
     if (M < 1) return fail(MADDNESS_E_INVAL, "M = %d, must be >= 1", M);
-    const size_t need = build_luts_workspace_bytes(params->D, params->C, M);
+    const size_t need = build_luts_static_bytes(params->C, M);
     if (need > (size_t)MADDNESS_STATIC_WORKSPACE_BYTES)
         return fail(MADDNESS_E_UNSUPPORTED,
                     "tables of C = %d codebooks and M = %d columns need a workspace of %zu bytes; "
@@ -217,8 +217,8 @@ int maddness_build_luts_static(const maddness_params *params, const float *B, in
                     params->C, M, need, (size_t)MADDNESS_STATIC_WORKSPACE_BYTES);
     void *workspace = nullptr;
     if ((rc = static_workspace(&workspace)) != MADDNESS_OK) return rc;
-    return build_luts_checked(params, B, M, ldb, luts, scale, offset, workspace, MADDNESS_STATIC_WORKSPACE_BYTES,
-                              false, stream);
+    return build_luts_checked(params, B, M, ldb, luts, scale, offset, workspace,
+                              build_luts_workspace_bytes(params->D, params->C, M), false, stream);
 }
 
 static int check_averaged(int32_t C)

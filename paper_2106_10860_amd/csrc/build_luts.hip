@@ -7,7 +7,8 @@
 // reference only by summation order (~1e-16 relative) and the 8-bit entries are
 // reproducible to the byte except for values within that distance of a rounding
 // boundary.  The contraction is tiny (2 * 16 C D M flops, 0.13 GFLOP at C = 32,
-// D = 512, M = 256), so three small launches are enough.
+// D = 512, M = 256), so two small launches are enough: one contracts and takes each table's minimum and range from
+// its registers, one quantises.
 #include "common.h"
 
 namespace maddness {
@@ -15,111 +16,182 @@ namespace {
 
 // Workspace of maddness_build_luts_static, the entry point for callers that cannot
 // allocate: one array per GPU, held until the process ends.  In host code the name
-// `scratch` is only a handle for hipGetSymbolAddress, never a device address.
-static __device__ __align__(256) unsigned char scratch[MADDNESS_STATIC_WORKSPACE_BYTES];
+// `scratch` is only a handle for hipGetSymbolAddress, never a device address.  Which shapes the entry point takes is
+// counted without `range` (build_luts_static_bytes); the array has room for it beside the largest of them
+// (8 C M bytes, under a seventeenth of what is counted).
+static __device__ __align__(256) unsigned char scratch[MADDNESS_STATIC_WORKSPACE_BYTES + MADDNESS_STATIC_WORKSPACE_BYTES / 16];
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
-// One workgroup of KSPLIT wavefronts per (codebook, tile of 16 output columns);
-// wavefront w contracts the slice d = 4 (w + KSPLIT i) + 0..3 of the inner
-// dimension, eight steps' worth of loads in flight at a time, and the partial
-// tiles are added in wavefront order through LDS.
+// T and, per codebook and column, the least entry and the range.  A workgroup of eight wavefronts takes RT codebooks
+// (16 RT rows of T) and 32 columns.  64 steps of the inner dimension at a time go to LDS, the next 64 on their way
+// meanwhile; four wavefronts take each half of the columns, the w-th of them contracts d = 4 (w + 4 i) + 0..3 for its
+// RT tiles of 16 x 16, and the partial tiles are added in that order through LDS.
 // Operand layout of v_mfma_f64_16x16x4_f64: lane l supplies A[i = l % 16][k = l / 16]
 // and B[k = l / 16][j = l % 16]; it receives D[i = 4 r + l / 16][j = l % 16] in
 // accumulator element r = 0..3.
+// Bound by the fp64 matrix cores (2 * 16 C D M flops; 1024 x 512 with 64 codebooks: 15 us at 73 TFLOP/s, which a large
+// product reaches); takes 32 us there.  One codebook and 16 columns to a workgroup, operands straight from memory, took
+// 77 us: two loads of 16 rows or 4 rows each per matrix instruction, where staged tiles need 5 reads of LDS for 4 of them.
 constexpr int KSPLIT = 4;
+constexpr int GEMM_COLS = 32, GEMM_DEPTH = 64, GEMM_THREADS = 128 * KSPLIT;
+constexpr int A_PITCH = GEMM_DEPTH + 4, B_PITCH = GEMM_COLS + 16;      // (an operand's 64 values meet in no LDS bank)
 
-__global__ __launch_bounds__(64 * KSPLIT) void lut_gemm_kernel(const float *__restrict__ P,
-                                                               const float *__restrict__ B, int D, int M,
-                                                               int64_t ldb, double *__restrict__ T)
+template <int RT>
+__global__ __launch_bounds__(GEMM_THREADS) void lut_gemm_kernel(const float *__restrict__ P,
+                                                               const float *__restrict__ B, int C, int D, int M,
+                                                               int64_t ldb, double *__restrict__ T,
+                                                               double *__restrict__ delta, double *__restrict__ range)
 {
-    __shared__ double part[KSPLIT][4][64];
-    const int c = blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int i = lane & 15;
-    const int kk = lane >> 4;
-    const int m = blockIdx.y * 16 + i;
-    const bool m_ok = m < M;
-    const float *prow = P + ((size_t)c * 16 + i) * D;
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    constexpr int UNROLL = 8;
-    for (int d0 = 4 * w; d0 < D; d0 += 4 * KSPLIT * UNROLL) {
-        float av[UNROLL], bv[UNROLL];
+    constexpr int ROWS = 16 * RT, TILES = 2 * RT;
+    constexpr int STAGE = ROWS * A_PITCH + GEMM_DEPTH * B_PITCH;           // floats of one of the two stages
+    constexpr size_t PART = sizeof(double) * KSPLIT * TILES * 4 * 64;
+    constexpr size_t LDS = sizeof(float) * 2 * STAGE > PART ? sizeof(float) * 2 * STAGE : PART;
+    __shared__ __align__(16) unsigned char lds[LDS];
+    float *stage = reinterpret_cast<float *>(lds);
+    double(*part)[TILES][4][64] = reinterpret_cast<double(*)[TILES][4][64]>(lds);   // once the stages are done with
+    const int c0 = blockIdx.x * RT, m0 = blockIdx.y * GEMM_COLS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, w = wave % KSPLIT, half = wave / KSPLIT;
+    const int i = lane & 15, kk = lane >> 4;
+
+    constexpr int PER_A = ROWS * GEMM_DEPTH / GEMM_THREADS, PER_B = GEMM_DEPTH * GEMM_COLS / GEMM_THREADS;
+    constexpr int A_STEP = GEMM_THREADS / GEMM_DEPTH, B_STEP = GEMM_THREADS / GEMM_COLS;
+    // where this thread's first pieces lie; rows and columns that do not exist read the last one and become zeros
+    // on their way to LDS (decided at the load, the compiler makes every load a branch of its own, each waited for)
+    const int m_own = m0 + tid % GEMM_COLS;
+    const float *b_src = B + min(m_own, M - 1);
+    float a_next[PER_A], b_next[PER_B];
+    auto fetch = [&](int d0) __attribute__((always_inline)) {
+        const int d_a = d0 + lane;
+        const float *a_src = P + min(d_a, D - 1);
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int d = d0 + 4 * KSPLIT * u + kk;
-            const bool ok = d < D;
-            av[u] = ok ? prow[d] : 0.0f;
-            bv[u] = (ok && m_ok) ? B[(size_t)d * ldb + m] : 0.0f;
+        for (int u = 0; u < PER_A; ++u) {
+            const int row = 16 * c0 + wave + A_STEP * u;
+            a_next[u] = a_src[(size_t)min(row, 16 * C - 1) * D];
         }
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[u], (double)bv[u], acc, 0, 0, 0);
+        for (int u = 0; u < PER_B; ++u) {
+            const int d = d0 + tid / GEMM_COLS + B_STEP * u;
+            b_next[u] = b_src[(size_t)min(d, D - 1) * ldb];
+        }
+    };
+    double4_t acc[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) acc[r] = double4_t{0.0, 0.0, 0.0, 0.0};
+    fetch(0);
+    int parity = 0;
+    for (int d0 = 0; d0 < D; d0 += GEMM_DEPTH, parity ^= 1) {
+        float *As = stage + parity * STAGE, *Bs = As + ROWS * A_PITCH;
+#pragma unroll
+        for (int u = 0; u < PER_A; ++u)
+            As[(wave + A_STEP * u) * A_PITCH + lane] = 16 * c0 + wave + A_STEP * u < 16 * C && d0 + lane < D ? a_next[u] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < PER_B; ++u)
+            Bs[(tid / GEMM_COLS + B_STEP * u) * B_PITCH + tid % GEMM_COLS] =
+                d0 + tid / GEMM_COLS + B_STEP * u < D && m_own < M ? b_next[u] : 0.0f;
+        __syncthreads();
+        if (d0 + GEMM_DEPTH < D) fetch(d0 + GEMM_DEPTH);
+#pragma unroll
+        for (int s = 0; s < GEMM_DEPTH / 16; ++s) {
+            const int k = 16 * s + 4 * w + kk;
+            const double bv = (double)Bs[k * B_PITCH + 16 * half + i];
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)As[(16 * r + i) * A_PITCH + k], bv, acc[r], 0, 0, 0);
+        }
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) part[w][r][lane] = acc[r];
     __syncthreads();
-    if (w == 0 && m_ok) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double s = part[0][r][lane];
+    for (int r = 0; r < RT; ++r)
 #pragma unroll
-            for (int q = 1; q < KSPLIT; ++q) s += part[q][r][lane];
-            T[((size_t)c * 16 + 4 * r + kk) * M + m] = s;
+        for (int e = 0; e < 4; ++e) part[w][2 * r + half][e][lane] = acc[r][e];
+    __syncthreads();
+    for (int tile = wave; tile < TILES; tile += 2 * KSPLIT) {
+        const int c = c0 + tile / 2, m = m0 + 16 * (tile % 2) + i;
+        double lo = 0.0, hi = 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double s = part[0][tile][e][lane];
+#pragma unroll
+            for (int q = 1; q < KSPLIT; ++q) s += part[q][tile][e][lane];
+            if (c < C && m < M) T[((size_t)c * 16 + 4 * e + kk) * M + m] = s;
+            lo = e == 0 || s < lo ? s : lo;
+            hi = e == 0 || s > hi ? s : hi;
+        }
+#pragma unroll
+        for (int off = 16; off < 64; off <<= 1) {
+            const double lo2 = __shfl_xor(lo, off), hi2 = __shfl_xor(hi, off);
+            lo = lo2 < lo ? lo2 : lo;
+            hi = hi2 > hi ? hi2 : hi;
+        }
+        if (kk == 0 && c < C && m < M) {
+            delta[(size_t)c * M + m] = lo;
+            range[(size_t)c * M + m] = hi - lo;
         }
     }
 }
 
-// Per output column: table minima, the widest range, the power-of-two scale.
-// A block covers 32 columns; its 16 slices share out the codebooks, the widest
-// range is reduced through LDS, and slice 0 then adds the minima in codebook
-// order (the order the definition of beta is written in).
-constexpr int STAT_COLS = 32;
-constexpr int STAT_SLICES = 16;
-
-__global__ __launch_bounds__(STAT_COLS * STAT_SLICES) void lut_stats_kernel(
-    const double *__restrict__ T, int C, int M, double *__restrict__ delta, int *__restrict__ lexp,
-    float *__restrict__ scale, float *__restrict__ offset)
+// the exponent l of the power-of-two scale for the widest range r
+__device__ __forceinline__ int scale_exponent(double r)
 {
-    __shared__ double rmax[STAT_SLICES][STAT_COLS];
-    const int tx = threadIdx.x % STAT_COLS;
-    const int ty = threadIdx.x / STAT_COLS;
-    const int m = blockIdx.x * STAT_COLS + tx;
+    if (!(r > 0.0) || !isfinite(r)) return 0;
+    // r = f 2^e with f in [0.5, 1); r 2^l <= 255 = (255/256) 2^8
+    int e;
+    const double f = frexp(r, &e);
+    const int l = (f <= 255.0 / 256.0) ? 8 - e : 7 - e;
+    return l > 126 ? 126 : (l < -126 ? -126 : l);
+}
+
+// A workgroup takes 64 columns and QUANT_CODEBOOKS codebooks: the widest range of every column over all codebooks gives
+// the scale's exponent (every workgroup works it out for itself: C values a column), then the entries are quantised.
+// The first workgroup of the columns writes scale and offset, the minima added in codebook order (the order the
+// definition of beta is written in).
+constexpr int QUANT_COLS = 64, QUANT_CODEBOOKS = 2;
+constexpr int QUANT_BATCH = 8;       // loads on their way at a time (one by one, 64 codebooks' minima took 15 us)
+__global__ __launch_bounds__(256) void lut_quantize_kernel(const double *__restrict__ T, const double *__restrict__ delta,
+                                                           const double *__restrict__ range, int C, int M,
+                                                           uint8_t *__restrict__ luts, float *__restrict__ scale,
+                                                           float *__restrict__ offset)
+{
+    __shared__ double widest[4][QUANT_COLS];
+    const int tx = threadIdx.x % QUANT_COLS, ty = threadIdx.x / QUANT_COLS;
+    const int m = blockIdx.x * QUANT_COLS + tx, c0 = blockIdx.y * QUANT_CODEBOOKS;
     double r = 0.0;
-    if (m < M) {
-        for (int c = ty; c < C; c += STAT_SLICES) {
-            const double *t = T + (size_t)c * 16 * M + m;
-            double lo = t[0], hi = t[0];
+    if (m < M)
+        for (int c = ty; c < C; c += 4 * QUANT_BATCH) {
+            double e[QUANT_BATCH];
 #pragma unroll
-            for (int k = 1; k < 16; ++k) {
-                const double v = t[(size_t)k * M];
-                lo = v < lo ? v : lo;
-                hi = v > hi ? v : hi;
-            }
-            const double e = hi - lo;
-            r = e > r ? e : r;
-            delta[(size_t)c * M + m] = lo;
+            for (int u = 0; u < QUANT_BATCH; ++u) e[u] = range[(size_t)min(c + 4 * u, C - 1) * M + m];
+#pragma unroll
+            for (int u = 0; u < QUANT_BATCH; ++u) r = e[u] > r ? e[u] : r;
         }
-    }
-    rmax[ty][tx] = r;
-    __syncthreads();   // also makes this block's writes to delta visible to slice 0
-    if (ty != 0 || m >= M) return;
+    widest[ty][tx] = r;
+    __syncthreads();
 #pragma unroll
-    for (int q = 1; q < STAT_SLICES; ++q) r = rmax[q][tx] > r ? rmax[q][tx] : r;
-    double beta = 0.0;
-    for (int c = 0; c < C; ++c) beta += delta[(size_t)c * M + m];
-    int l = 0;
-    if (r > 0.0 && isfinite(r)) {
-        // r = f 2^e with f in [0.5, 1); r 2^l <= 255 = (255/256) 2^8
-        int e;
-        const double f = frexp(r, &e);
-        l = (f <= 255.0 / 256.0) ? 8 - e : 7 - e;
-        l = l > 126 ? 126 : (l < -126 ? -126 : l);
+    for (int q = 0; q < 4; ++q) r = widest[q][tx] > r ? widest[q][tx] : r;
+    if (m >= M) return;
+    const int l = scale_exponent(r);
+    if (blockIdx.y == 0 && ty == 0) {
+        double beta = 0.0;
+        for (int c = 0; c < C; c += 2 * QUANT_BATCH) {
+            double v[2 * QUANT_BATCH];
+#pragma unroll
+            for (int u = 0; u < 2 * QUANT_BATCH; ++u) v[u] = delta[(size_t)min(c + u, C - 1) * M + m];
+#pragma unroll
+            for (int u = 0; u < 2 * QUANT_BATCH; ++u) beta = c + u < C ? beta + v[u] : beta;
+        }
+        scale[m] = ldexpf(1.0f, -l);
+        offset[m] = (float)beta;
     }
-    lexp[m] = l;
-    scale[m] = ldexpf(1.0f, -l);
-    offset[m] = (float)beta;
+    for (int row = ty; row < 16 * QUANT_CODEBOOKS; row += 4) {
+        const int c = c0 + row / 16;
+        if (c >= C) break;
+        const size_t at = ((size_t)c * 16 + row % 16) * M + m;
+        double q = rint(ldexp(T[at] - delta[(size_t)c * M + m], l));
+        q = (q >= 0.0) ? q : 0.0;  // NaN -> 0
+        q = q > 255.0 ? 255.0 : q;
+        luts[at] = (uint8_t)q;
+    }
 }
 
 // Pooled variant (Appendix A as printed), step 1: one block per codebook finds
@@ -155,12 +227,10 @@ __global__ __launch_bounds__(256) void lut_pooled_minmax_kernel(const double *__
 }
 
 // Step 2 (one block): the widest range gives the scale, the minima are added in
-// codebook order; delta[c][m] and lexp[m] are filled so that the quantise kernel
-// of the per-column variant can be used unchanged.
+// codebook order.
 __global__ __launch_bounds__(256) void lut_pooled_finish_kernel(const double *__restrict__ cb_min,
                                                                 const double *__restrict__ cb_range, int C,
-                                                                int M, double *__restrict__ delta,
-                                                                int *__restrict__ lexp, float *__restrict__ scale,
+                                                                int M, int *__restrict__ lexp, float *__restrict__ scale,
                                                                 float *__restrict__ offset)
 {
     double r = 0.0, beta = 0.0;
@@ -168,31 +238,23 @@ __global__ __launch_bounds__(256) void lut_pooled_finish_kernel(const double *__
         r = cb_range[c] > r ? cb_range[c] : r;
         beta += cb_min[c];
     }
-    int l = 0;
-    if (r > 0.0 && isfinite(r)) {
-        int e;
-        const double f = frexp(r, &e);
-        l = (f <= 255.0 / 256.0) ? 8 - e : 7 - e;
-        l = l > 126 ? 126 : (l < -126 ? -126 : l);
-    }
+    const int l = scale_exponent(r);
     for (int m = threadIdx.x; m < M; m += 256) {
-        lexp[m] = l;
         scale[m] = ldexpf(1.0f, -l);
         offset[m] = (float)beta;
     }
-    for (int i = threadIdx.x; i < C * M; i += 256) delta[i] = cb_min[i / M];
+    if (threadIdx.x == 0) *lexp = l;
 }
 
-__global__ __launch_bounds__(256) void lut_quantize_kernel(const double *__restrict__ T,
-                                                           const double *__restrict__ delta,
-                                                           const int *__restrict__ lexp, int C, int M,
-                                                           uint8_t *__restrict__ luts)
+__global__ __launch_bounds__(256) void lut_pooled_quantize_kernel(const double *__restrict__ T,
+                                                                  const double *__restrict__ cb_min,
+                                                                  const int *__restrict__ lexp, int M,
+                                                                  uint8_t *__restrict__ luts)
 {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     const int row = blockIdx.y;  // c * 16 + k
     if (m >= M) return;
-    const int c = row >> 4;
-    double q = rint(ldexp(T[(size_t)row * M + m] - delta[(size_t)c * M + m], lexp[m]));
+    double q = rint(ldexp(T[(size_t)row * M + m] - cb_min[row >> 4], *lexp));
     q = (q >= 0.0) ? q : 0.0;  // NaN -> 0
     q = q > 255.0 ? 255.0 : q;
     luts[(size_t)row * M + m] = (uint8_t)q;
@@ -202,14 +264,17 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
 
-// Workspace: T [C][16][M], delta [C][M], per-codebook min and range [2][C] (pooled
-// variant), then lexp [M].
+// Workspace: T [C][16][M], delta and range [C][M], per-codebook min and range [2][C] and the exponent (pooled variant).
 size_t build_luts_workspace_bytes(int32_t D, int32_t C, int32_t M)
 {
     (void)D;
-    return align_up(sizeof(double) * ((size_t)C * 16 * M + (size_t)C * M + 2 * (size_t)C) +
-                        sizeof(int) * (size_t)M,
-                    256);
+    return align_up(sizeof(double) * ((size_t)C * 16 * M + 2 * (size_t)C * M + 2 * (size_t)C) + sizeof(int), 256);
+}
+
+// What maddness_build_luts_static holds against MADDNESS_STATIC_WORKSPACE_BYTES.
+size_t build_luts_static_bytes(int32_t C, int32_t M)
+{
+    return align_up(sizeof(double) * ((size_t)C * 16 * M + (size_t)C * M + 2 * (size_t)C) + sizeof(int) * (size_t)M, 256);
 }
 
 int launch_build_luts(const maddness_params &p, const float *B, int32_t M, int64_t ldb,
@@ -219,32 +284,41 @@ int launch_build_luts(const maddness_params &p, const float *B, int32_t M, int64
     const int C = p.C;
     double *T = static_cast<double *>(workspace);
     double *delta = T + (size_t)C * 16 * M;
-    double *cb_min = delta + (size_t)C * M;
+    double *range = delta + (size_t)C * M;
+    double *cb_min = range + (size_t)C * M;
     double *cb_range = cb_min + C;
     int *lexp = reinterpret_cast<int *>(cb_range + C);
 
-    note_kernel(pooled ? "lut_gemm_kernel + lut_pooled_minmax_kernel + lut_pooled_finish_kernel + lut_quantize_kernel"
-                       : "lut_gemm_kernel + lut_stats_kernel + lut_quantize_kernel", nullptr);
-    hipLaunchKernelGGL(lut_gemm_kernel, dim3(C, (M + 15) / 16), dim3(64 * KSPLIT), 0, stream, p.prototypes, B,
-                       p.D, M, ldb, T);
+    note_kernel(pooled ? "lut_gemm_kernel + lut_pooled_minmax_kernel + lut_pooled_finish_kernel + lut_pooled_quantize_kernel"
+                       : "lut_gemm_kernel + lut_quantize_kernel", nullptr);
+    // as many codebooks to a workgroup as still leave one per compute unit
+    const int col_tiles = (M + GEMM_COLS - 1) / GEMM_COLS, cus = device_info().cus;
+    auto groups = [&](int rt) { return (C + rt - 1) / rt; };
+    if (groups(4) * col_tiles >= cus)
+        hipLaunchKernelGGL(lut_gemm_kernel<4>, dim3(groups(4), col_tiles), dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M,
+                           ldb, T, delta, range);
+    else if (groups(2) * col_tiles >= cus)
+        hipLaunchKernelGGL(lut_gemm_kernel<2>, dim3(groups(2), col_tiles), dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M,
+                           ldb, T, delta, range);
+    else
+        hipLaunchKernelGGL(lut_gemm_kernel<1>, dim3(groups(1), col_tiles), dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M,
+                           ldb, T, delta, range);
     int rc = check_hip(hipGetLastError(), "launch lut_gemm_kernel");
     if (rc != MADDNESS_OK) return rc;
-    if (pooled) {
-        hipLaunchKernelGGL(lut_pooled_minmax_kernel, dim3(C), dim3(256), 0, stream, T, M, cb_min, cb_range);
-        rc = check_hip(hipGetLastError(), "launch lut_pooled_minmax_kernel");
-        if (rc != MADDNESS_OK) return rc;
-        hipLaunchKernelGGL(lut_pooled_finish_kernel, dim3(1), dim3(256), 0, stream, cb_min, cb_range, C, M,
-                           delta, lexp, scale, offset);
-        rc = check_hip(hipGetLastError(), "launch lut_pooled_finish_kernel");
-    } else {
-        hipLaunchKernelGGL(lut_stats_kernel, dim3((M + STAT_COLS - 1) / STAT_COLS),
-                           dim3(STAT_COLS * STAT_SLICES), 0, stream, T, C, M, delta, lexp, scale, offset);
-        rc = check_hip(hipGetLastError(), "launch lut_stats_kernel");
+    if (!pooled) {
+        hipLaunchKernelGGL(lut_quantize_kernel,
+                           dim3((M + QUANT_COLS - 1) / QUANT_COLS, (C + QUANT_CODEBOOKS - 1) / QUANT_CODEBOOKS), dim3(256), 0,
+                           stream, T, delta, range, C, M, luts, scale, offset);
+        return check_hip(hipGetLastError(), "launch lut_quantize_kernel");
     }
+    hipLaunchKernelGGL(lut_pooled_minmax_kernel, dim3(C), dim3(256), 0, stream, T, M, cb_min, cb_range);
+    rc = check_hip(hipGetLastError(), "launch lut_pooled_minmax_kernel");
     if (rc != MADDNESS_OK) return rc;
-    hipLaunchKernelGGL(lut_quantize_kernel, dim3((M + 255) / 256, C * 16), dim3(256), 0, stream, T,
-                       delta, lexp, C, M, luts);
-    return check_hip(hipGetLastError(), "launch lut_quantize_kernel");
+    hipLaunchKernelGGL(lut_pooled_finish_kernel, dim3(1), dim3(256), 0, stream, cb_min, cb_range, C, M, lexp, scale, offset);
+    rc = check_hip(hipGetLastError(), "launch lut_pooled_finish_kernel");
+    if (rc != MADDNESS_OK) return rc;
+    hipLaunchKernelGGL(lut_pooled_quantize_kernel, dim3((M + 255) / 256, C * 16), dim3(256), 0, stream, T, cb_min, lexp, M, luts);
+    return check_hip(hipGetLastError(), "launch lut_pooled_quantize_kernel");
 }
 
 // The address of `scratch` on the current device, looked up once per device (every GPU

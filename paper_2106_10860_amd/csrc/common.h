@@ -123,6 +123,7 @@ int launch_fused_cols(const maddness_params &p, const MatrixA &A, int64_t N, int
                       int64_t ldo, uint16_t *acc, uint8_t *codes, bool averaged, hipStream_t stream);
 
 size_t build_luts_workspace_bytes(int32_t D, int32_t C, int32_t M);
+size_t build_luts_static_bytes(int32_t C, int32_t M);
 // pooled: Appendix A as printed (one scale, one offset per codebook) instead of
 // per-column scale and offsets.
 int launch_build_luts(const maddness_params &p, const float *B, int32_t M, int64_t ldb,
@@ -140,8 +141,8 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
                             const int32_t *bounds_host, bool ridge, double lambda, float *prototypes, void *workspace,
                             hipStream_t stream);
 
-// Device address of the library's own table-build workspace (MADDNESS_STATIC_WORKSPACE_BYTES,
-// one per GPU) on the current device.  Allocates nothing.
+// Device address of the library's own table-build workspace (one per GPU; holds every shape with
+// build_luts_static_bytes of at most MADDNESS_STATIC_WORKSPACE_BYTES) on the current device.  Allocates nothing.
 int static_workspace(void **workspace);
 
 }  // namespace maddness
