@@ -65,14 +65,16 @@ __device__ __forceinline__ int opaque(int x)
 enum EncodeMode { kRowMajor = 0, kByColumns = 1 };
 
 // Bytes at the start of LDS that the phases use in turn: E stages RPI rows of DV KiB per wavefront there
-// (row-major A); S keeps the one-hot table there (256 bytes) and, when it writes whole rows, two tiles
-// of one step's results each (16 rows, or 32 with NT = 2, of 8 blocks of 16 NT columns + 4 floats of padding).
+// (row-major A); S first passes the tables of its columns through it, then keeps the one-hot table there (256 bytes)
+// and, when it writes whole rows, two tiles of one step's results each (16 rows, or 32 with NT = 2, of 8 blocks of
+// 16 NT columns + 4 floats of padding).
 constexpr int tile_bytes(int NT) { return (NT == 2 ? 32 : 16) * (kWaves * 16 * NT + 4) * 4; }
-constexpr int shared_bytes(int emode, int RPI, int DV, int NT, bool gather)
+constexpr int shared_bytes(int emode, int RPI, int DV, int NT, bool scan, bool gather)
 {
     const int stage = emode == kRowMajor ? kWaves * RPI * DV * 1024 : 256;
+    const int tables = scan ? kWaves * kTableStage : 256;
     const int tiles = gather ? 256 + 2 * tile_bytes(NT) : 256;
-    return stage > tiles ? stage : tiles;
+    return std::max(stage, std::max(tables, tiles));
 }
 
 // DV: 16-byte pieces per lane and row (row-major); unused for columns.
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
 #endif
     constexpr int E_PF = DT == kF32 ? 1 : (DT == kU8 ? 2 * MADDNESS_NARROW_PREFETCH : MADDNESS_NARROW_PREFETCH);
     // row-major: staging of RPI rows per wavefront; by columns: room for the one-hot table only
-    constexpr int STAGE_BYTES = shared_bytes(EMODE, RPI, DV, NT, GATHER);
+    constexpr int STAGE_BYTES = shared_bytes(EMODE, RPI, DV, NT, SCAN, GATHER);
     typedef unsigned cvec __attribute__((ext_vector_type(CW)));
 
     extern __shared__ __align__(16) unsigned char smem[];
@@ -132,10 +134,18 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
     float sc[NT], of[NT];
     int col = 0, j = 0, g = 0, lane_in_s = 0;
     bool col_on = false;
-    auto take_columns = [&](int block) INLINE_LAMBDA {
-        col = block * SPAN + NT * j;
+    // the tables of the pass whose first block of columns is block0, `blocks` of them, into the registers of the
+    // wavefronts; this one has block0 + my_block
+    auto take_columns = [&](int block0, int blocks, int my_block) INLINE_LAMBDA {
+        col = (block0 + my_block) * SPAN + NT * j;
         col_on = col < a.M;
-        load_tables<KG, NT, PAD, ODD>(B, a.luts, a.M, col, col_on, g, a.codebooks);
+        const int tid_s = 64 * wave + lane_in_s;
+        __syncthreads();      // (the staging area: E, or the pass before, is done with it)
+        load_tables<KG, NT, kWaves * 64, PAD>(B, a.luts, a.M, block0 * SPAN, blocks * SPAN, my_block * SPAN, g, j, smem, tid_s,
+                                              a.codebooks);
+        __syncthreads();
+        fill_one_hot_table(one_hot, tid_s);
+        __syncthreads();
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const bool on = ODD ? col + t < a.M : col_on;    // (else M is a multiple of NT)
@@ -156,8 +166,9 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
                 else store16<NT>(o, acc, [&](int k) INLINE_LAMBDA { return row_of(16 * rg + k); }, a.N, g, col, sc, of);
             }
         };
-        for (int block = my_block; block < col_blocks; block += blocks_per_pass) {
-            take_columns(block);   // re-read every time: the registers are free for E meanwhile
+        for (int block0 = 0; block0 < col_blocks; block0 += blocks_per_pass) {
+            take_columns(block0, blocks_per_pass, my_block);   // re-read every time: the registers are free for E meanwhile
+            if (block0 + my_block >= col_blocks) continue;
             if constexpr (NT == 2) {
                 // two groups per step: four independent accumulation chains for the matrix pipe
 #pragma unroll 1
@@ -208,9 +219,8 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
         const int n_writers = kWaves - first_writer;
         int it = 0;
         for (int pass = 0; pass < n_passes; ++pass) {
-            const int block = pass * kWaves + wave;
-            const bool active = block < col_blocks;
-            if (active) take_columns(block);
+            const bool active = pass * kWaves + wave < col_blocks;
+            take_columns(pass * kWaves, kWaves, wave);
             const int col0 = pass * kWaves * SPAN;
             const int n_cols = a.M - col0 < kWaves * SPAN ? a.M - col0 : kWaves * SPAN;
 #pragma unroll 1
@@ -335,11 +345,6 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
             }
             encode_rows_to_lds<C, DV, DT, false, PAD, ODD, E_PF>(a, tr, stage, codes_l + wave * CB, region0 + 8 * (int64_t)blockIdx.x + wave,
                                           rw, lane_e, 8 * G, 8);
-            // the one-hot table takes the place of the first wavefront's staging area until the next E
-            if (SCAN && wave == 0) {
-                wave_lds_fence();
-                fill_one_hot_table(one_hot, tid);
-            }
             __syncthreads();
             const int64_t units_left = (a.N - region0 + 7) / 8 - (int64_t)blockIdx.x;   // units of this region from ours on
             const int64_t my_units = units_left <= 0 ? 0 : (units_left + G - 1) / G;
@@ -384,7 +389,6 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
     } else {
         // A workgroup takes blocks of 8 rw consecutive rows (rw a multiple of 256), wavefront
         // w the rows [w rw, (w + 1) rw) of the block in groups of 256.  N is a multiple of 4.
-        fill_one_hot_table(one_hot, tid);
         const int64_t block_rows = 8 * (int64_t)rw;
         for (int64_t R0 = blockIdx.x * block_rows; R0 < a.N; R0 += G * block_rows) {
             // ---- E ----
@@ -420,7 +424,7 @@ int launch_rows(const RowsArgs &a, hipStream_t stream)
     constexpr int RPI = 64 / C;
     const DeviceInfo &dev = device_info();
     // (the staging area of E; with GATHER, S puts its two tiles of results there)
-    constexpr int stage_bytes = shared_bytes(kRowMajor, RPI, DV, NT, GATHER);
+    constexpr int stage_bytes = shared_bytes(kRowMajor, RPI, DV, NT, SCAN, GATHER);
     // rows per wavefront and region: as many as LDS holds codes for (the tables are re-read
     // once per region and pass)
     int rw = (dev.lds_per_block - stage_bytes) / (kWaves * (C / 2));
@@ -450,16 +454,17 @@ int launch_cols(const RowsArgs &a, hipStream_t stream)
     const DeviceInfo &dev = device_info();
     // rows per wavefront and block: a multiple of 256; as few blocks per workgroup as LDS
     // allows, all of the same size
-    int rw_max = (dev.lds_per_block - 256) / (kWaves * (C / 2)) / 256 * 256;
+    int rw_max = (dev.lds_per_block - shared_bytes(kByColumns, 1, 1, NT, true, false)) / (kWaves * (C / 2)) / 256 * 256;
     // MADDNESS_OPT_PHASED_ROWS lowers that (testing aid: several blocks per workgroup with few rows)
     if (const int v = option(MADDNESS_OPT_PHASED_ROWS); v >= 2 && (v + 255) / 256 * 256 < rw_max) rw_max = (v + 255) / 256 * 256;
     if (rw_max < 256) return 1;
     const int wgs = max_workgroups();
+    constexpr int stage_bytes = shared_bytes(kByColumns, 1, 1, NT, true, false);
     const int64_t per_wave = (a.N + (int64_t)kWaves * wgs - 1) / ((int64_t)kWaves * wgs);   // rows per wavefront in all
     const int64_t turns = (per_wave + rw_max - 1) / rw_max;
     int rw = (int)(((per_wave + turns - 1) / turns + 255) / 256 * 256);
     if (rw > rw_max) rw = rw_max;
-    const size_t lds = 256 + (size_t)kWaves * rw * (C / 2);
+    const size_t lds = stage_bytes + (size_t)kWaves * rw * (C / 2);
     if (int rc = allow_full_lds<fused_mfma_kernel<C, 1, NT, kByColumns, DT>>(); rc != MADDNESS_OK) return rc;
     const int64_t blocks = (a.N + (int64_t)kWaves * rw - 1) / ((int64_t)kWaves * rw);
     const int grid = (int)(blocks < wgs ? blocks : wgs);

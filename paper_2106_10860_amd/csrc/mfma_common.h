@@ -75,54 +75,83 @@ struct ScanOut {
     int M;
 };
 
-// The table entries of columns col .. col + NT - 1 (col = c0 + NT j) for all codebooks
-// into B; lane (j, g) holds codebook 4 G + g of tile t in B[t][G].  Lanes with
-// col_on == false get arbitrary finite contents (their results are never stored).
-// PAD: only `codebooks` (< 4 KG) codebooks exist; the others get zero entries, which together
-// with their code 0 add nothing to the sums.
-// BYTES: M need not be a multiple of NT and the tables need no alignment: entries are read
-// byte by byte, those of columns >= M as zero.
-template <int KG, int NT, bool PAD = false, bool BYTES = false>
-__device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *luts, int M, int col, bool col_on, int g,
-                                            int codebooks = 0)
+// The table entries of a workgroup's columns, col0 .. col0 + cols - 1 (a multiple of SPAN = 16 NT, at most SPAN per
+// wavefront), into the registers of its wavefronts: lane (j, g) of the wavefront with columns first .. first + SPAN - 1
+// (counted from col0) ends up with the 16 entries of codebook 4 G + g and column first + NT j + t in B[t][G].  The tables
+// lie in memory by code; the operand wants a column's 16 codes side by side.  The whole workgroup reads CHUNK codebooks
+// at a time, four columns of the 16 codes of one to a thread, neighbouring threads neighbouring columns, turns them
+// round (transpose4x4) and passes them on through LDS (kTableStage bytes per 64 threads at `stage`), 16 bytes
+// to an access; four chunks are on their way at a time.  Read by each lane for itself, two or four bytes of a
+// code at a time, the same tables cost 8 to 16 times the requests, of which all compute units sent the same at the same
+// time: D = 1024, M = 512, C = 64, N = 65536 took 223 us that way, 82 so (bfloat16 rows: 202 and 65), the scan alone 109
+// and 38; D = 512, M = 256, C = 32, N = 2^18 145 and 139.
+// Entries of columns >= M and (PAD) of codebooks >= `codebooks` are zeros, which add nothing to a sum together with the
+// code 0; entries need no alignment.  Every wavefront takes part (barriers); the stage is free again after one more.
+constexpr int kTableStage = 4096;
+template <int KG, int NT, int THREADS, bool PAD>
+__device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *luts, int M, int col0, int cols, int first, int g,
+                                            int j, unsigned char *stage, int tid, int codebooks)
 {
-    // entry (codebook 4 G + g, code b) of column col sits at offset (64 G + 16 g + b) M + col.
-    // The offset is carried along (and hidden from the optimiser once per group): computed
-    // afresh for each of the 16 KG loads, the addresses get hoisted out of the caller's loops
-    // and spill.
-    size_t off = (size_t)(16 * g) * M + col;
-#pragma unroll
-    for (int G = 0; G < KG; ++G) {
-        asm volatile("" : "+v"(off));
-        uint32_t w[16];   // w[b]: entries of code b for the lane's NT columns
+    constexpr int SPAN = 16 * NT, P = THREADS / 64 * SPAN, QUADS = P / 4, CHUNK = THREADS / QUADS;
+    constexpr int CHUNKS = 4 * KG / CHUNK, AHEAD = CHUNKS < 4 ? CHUNKS : 4;
+    static_assert(CHUNK * P * 16 == kTableStage * (THREADS / 64) && CHUNK % 4 == 0 && (4 * KG) % CHUNK == 0, "stage of the tables");
+    v4i *entries = reinterpret_cast<v4i *>(stage);          // [CHUNK][P], a block's columns ordered by (t, j)
+    const int quad = tid % QUADS, cb = tid / QUADS, col = col0 + 4 * quad;
+    const bool mine = 4 * quad < cols && col < M, whole = mine && col + 4 <= M;
+    uint32_t raw[AHEAD][16];
+    auto fetch = [&](int n, uint32_t(&w)[16]) INLINE_LAMBDA {
+        const bool there = !PAD || CHUNK * n + cb < codebooks;
+        const bool read = whole && there;
+        // (a thread with nothing to read reads the first entries again and again)
+        const uint8_t *src = read ? luts + (size_t)(16 * (CHUNK * n + cb)) * M + col : luts;
+        const size_t step = read ? (size_t)M : 0;
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
-            const uint8_t *src = luts + off + (size_t)b * M;
-            uint32_t v = 0;
-            if (col_on && (!PAD || 4 * G + g < codebooks)) {
-                if constexpr (BYTES) {
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        if (col + t < M) v |= (uint32_t)src[t] << (8 * t);
-                } else if constexpr (NT == 4) {
-                    v = *reinterpret_cast<const uint32_t *>(src);
-                } else {
-                    v = *reinterpret_cast<const uint16_t *>(src);
-                }
-            }
-            w[b] = v ^ 0x80808080u;   // t - 128 as a signed byte
+            uint32_t v;
+            __builtin_memcpy(&v, src, 4);
+            w[b] = v;
+            src += step;
         }
-        off += (size_t)64 * M;
+    };
+#pragma unroll
+    for (int n = 0; n < AHEAD; ++n) fetch(n, raw[n]);
+#pragma unroll
+    for (int n = 0; n < CHUNKS; ++n) {
+        uint32_t(&w)[16] = raw[n % AHEAD];
+        // (decided here and not at the load, which the compiler would make a branch of its own, waited for)
+        const bool there = !PAD || CHUNK * n + cb < codebooks;
+        if (!whole || !there) {
+#pragma unroll
+            for (int b = 0; b < 16; ++b) w[b] = 0;
+            if (mine && there) {
+                const uint8_t *src = luts + (size_t)(16 * (CHUNK * n + cb)) * M + col;
+                for (int t = 0; t < M - col; ++t)
+#pragma unroll
+                    for (int b = 0; b < 16; ++b) w[b] |= (uint32_t)src[(size_t)b * M + t] << (8 * t);
+            }
+        }
+        v4i column[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            uint32_t m[4] = {w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+            uint32_t m[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) m[t] = w[4 * q + t] ^ 0x80808080u;   // t - 128 as a signed byte
             transpose4x4(m);          // m[t]: bytes of column t for codes 4q .. 4q + 3
 #pragma unroll
-            for (int t = 0; t < NT; ++t) B[t][G][q] = (int)m[t];
+            for (int t = 0; t < 4; ++t) column[t][q] = (int)m[t];
         }
-        // two codebook groups at a time (32 loads in flight): without this the compiler
-        // issues the loads of all groups at once and runs out of registers
-        if (G % 2 == 1) asm volatile("" ::: "memory");
+        if (n > 0) __syncthreads();   // (the chunk before has been read)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int r = (4 * quad + t) % SPAN;
+            entries[cb * P + (4 * quad + t - r) + (r % NT) * 16 + r / NT] = column[t];
+        }
+        if (n + AHEAD < CHUNKS) fetch(n + AHEAD, w);
+        __syncthreads();
+#pragma unroll
+        for (int G = 0; G < CHUNK / 4; ++G)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) B[t][n * (CHUNK / 4) + G] = entries[(4 * G + g) * P + first + 16 * t + j];
     }
 }
 

@@ -47,7 +47,9 @@ __device__ __forceinline__ void scan_gathered(const MfmaScanArgs &a, const v4i *
 
     v4i B[NT][KG];
     float sc[NT], of[NT];
-    if (active) load_tables<KG, NT, ODD, ODD>(B, a.luts, a.o.M, col, col_on, g, a.codebooks);
+    load_tables<KG, NT, 256, ODD>(B, a.luts, a.o.M, col0, 4 * SPAN, wave * SPAN, g, j, reinterpret_cast<unsigned char *>(tile),
+                                  threadIdx.x, a.codebooks);
+    __syncthreads();
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const bool on = ODD ? col + t < a.o.M : col_on;
@@ -165,6 +167,7 @@ __global__ __launch_bounds__(256, 2) void mfma_scan_kernel(const MfmaScanArgs a)
     __syncthreads();
     if constexpr (GATHER) {
         __shared__ __align__(16) float tile[(NT == 2 ? 32 : 16) * (4 * SPAN + 4)];
+        static_assert(sizeof(tile) >= 4 * kTableStage, "the tables pass through it");
         scan_gathered<KG, NT, ODD>(a, one_hot, tile, lane, wave);
         return;
     }
@@ -174,12 +177,16 @@ __global__ __launch_bounds__(256, 2) void mfma_scan_kernel(const MfmaScanArgs a)
     const int share = col_blocks >= 3 ? 1 : (col_blocks == 2 ? 2 : 4);
     const int blocks_here = 4 / share;
     const int c0 = (blockIdx.y * blocks_here + wave % blocks_here) * SPAN;   // first column of this wavefront
-    if (c0 >= a.o.M) return;                        // no barriers below
     const int col = c0 + NT * j;                    // first of this lane's NT columns
     const bool col_on = col < a.o.M;                // M is a multiple of NT
 
     v4i B[NT][KG];
-    load_tables<KG, NT>(B, a.luts, a.o.M, col, col_on, g);
+    {
+        __shared__ __align__(16) unsigned char stage[4 * kTableStage];
+        load_tables<KG, NT, 256, false>(B, a.luts, a.o.M, blockIdx.y * blocks_here * SPAN, blocks_here * SPAN,
+                                        wave % blocks_here * SPAN, g, j, stage, threadIdx.x, a.codebooks);
+    }
+    if (c0 >= a.o.M) return;                        // no barriers below
     float sc[NT], of[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
