@@ -584,7 +584,6 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
 {
     const int D = p.D;
     const int es = A.elem_bytes();
-    if (N < 16384) return 1;
     RowsArgs a{};
     a.A = A.data; a.lda = A.ld; a.D = D; a.N = N;
     a.split_dims = p.split_dims; a.thresholds = p.thresholds;
@@ -601,6 +600,7 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
                          (!acc || aligned_to(acc, 2 * NT)) &&
                          (A.col_major || ((D * es) % 16 == 0 && (A.ld * es) % 16 == 0 && aligned_to(A.data, 16) &&
                                           (!codes || aligned_to(codes, C != p.C ? 4 : (C == 16 ? 8 : 16)))));
+    if (N < matrix_cores_min_rows(p.C, M, regular && (p.C == 16 || p.C == 32))) return 1;
     if (!regular) {
         if (!A.plain() || p.C > 64) return 1;
         return launch_odd<true>(a, p.C, 4 * D, stream);

@@ -75,6 +75,17 @@ struct ScanOut {
     int M;
 };
 
+// From how many rows on the scan runs on the matrix cores.  Tables that fit in LDS whole are read there faster for few
+// rows (`in_lds`: 16 or 32 codebooks, up to 128 KiB; M = 256, C = 32: 11 us for 4096 rows of bfloat16, 16 for 16384
+// here), and the general kernels take up to 64 KiB at once.  Larger tables these and tiled_rows_kernel walk tile by
+// tile, whatever the rows: M = 512, C = 64 in 46 us for one row, 239 for 500 or 8192 against 17, 19 and 25 here;
+// M = 1000, C = 32 in 54, 253 and 308 against 19, 20 and 27; the scan alone of M = 512, C = 64 in 17, 201 and 346
+// against 9, 10 and 12; M = 200, C = 24 (75 KiB) in 12, 13 and 16 against the same 12, 13 and 16.
+inline int64_t matrix_cores_min_rows(int C, int M, bool in_lds)
+{
+    return 16 * (int64_t)C * M > (in_lds ? 128 : 64) * 1024 ? 1 : 16384;
+}
+
 // The table entries of a workgroup's columns, col0 .. col0 + cols - 1 (a multiple of SPAN = 16 NT, at most SPAN per
 // wavefront), into the registers of its wavefronts: lane (j, g) of the wavefront with columns first .. first + SPAN - 1
 // (counted from col0) ends up with the 16 entries of codebook 4 G + g and column first + NT j + t in B[t][G].  The tables
@@ -88,6 +99,7 @@ struct ScanOut {
 // Entries of columns >= M and (PAD) of codebooks >= `codebooks` are zeros, which add nothing to a sum together with the
 // code 0; entries need no alignment.  Every wavefront takes part (barriers); the stage is free again after one more.
 constexpr int kTableStage = 4096;
+
 template <int KG, int NT, int THREADS, bool PAD>
 __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *luts, int M, int col0, int cols, int first, int g,
                                             int j, unsigned char *stage, int tid, int codebooks)
@@ -97,13 +109,16 @@ __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *lut
     static_assert(CHUNK * P * 16 == kTableStage * (THREADS / 64) && CHUNK % 4 == 0 && (4 * KG) % CHUNK == 0, "stage of the tables");
     v4i *entries = reinterpret_cast<v4i *>(stage);          // [CHUNK][P], a block's columns ordered by (t, j)
     const int quad = tid % QUADS, cb = tid / QUADS, col = col0 + 4 * quad;
-    const bool mine = 4 * quad < cols && col < M, whole = mine && col + 4 <= M;
+    // the columns' last four bytes where fewer than four are left: moved down when they are used (tables of less
+    // than four columns are read byte by byte)
+    const bool mine = 4 * quad < cols && col < M, whole = mine && M >= 4;
+    const int back = col + 4 > M ? col + 4 - M : 0;
     uint32_t raw[AHEAD][16];
     auto fetch = [&](int n, uint32_t(&w)[16]) INLINE_LAMBDA {
         const bool there = !PAD || CHUNK * n + cb < codebooks;
         const bool read = whole && there;
         // (a thread with nothing to read reads the first entries again and again)
-        const uint8_t *src = read ? luts + (size_t)(16 * (CHUNK * n + cb)) * M + col : luts;
+        const uint8_t *src = read ? luts + (size_t)(16 * (CHUNK * n + cb)) * M + (col - back) : luts;
         const size_t step = read ? (size_t)M : 0;
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
@@ -131,11 +146,12 @@ __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *lut
             }
         }
         v4i column[4];
+        const int shift = whole ? 8 * back : 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             uint32_t m[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) m[t] = w[4 * q + t] ^ 0x80808080u;   // t - 128 as a signed byte
+            for (int t = 0; t < 4; ++t) m[t] = (w[4 * q + t] >> shift) ^ 0x80808080u;   // t - 128 as a signed byte
             transpose4x4(m);          // m[t]: bytes of column t for codes 4q .. 4q + 3
 #pragma unroll
             for (int t = 0; t < 4; ++t) column[t][q] = (int)m[t];

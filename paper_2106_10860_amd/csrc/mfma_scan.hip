@@ -288,7 +288,7 @@ int launch_scan_mfma(int32_t C, int32_t M, const uint8_t *codes, int64_t N, cons
 {
     // whole words of packed codes per row; the tables are read once per workgroup, which
     // only pays with many rows
-    if (C > 64 || N < 16384) return 1;
+    if (C > 64 || N < matrix_cores_min_rows(C, M, C == 16 || C == 32)) return 1;
     const int NT = C <= 32 ? 4 : 2;
     MfmaScanArgs a{codes, luts, scale, offset, ScanOut{out, ldo, acc, M}, N, C};
     if (C % 8 != 0 || !aligned_to(codes, 16) || M % NT != 0 || !aligned_to(luts, NT) ||
