@@ -58,6 +58,7 @@ class _Params(C.Structure):
 
 
 _lib = None
+_torch = None
 
 
 def lib() -> C.CDLL:
@@ -103,37 +104,52 @@ def _check(status: int) -> None:
         raise MaddnessError(status, lib().maddness_last_error().decode())
 
 
+# A call spends its time on the host in this marshalling (an empty call took 7 us of it, the launch 3), so the checks
+# below look at a tensor once, take the module from a global and the stream from torch without the object around it.
+
+def _torch_module():
+    global _torch
+    import torch
+    _torch = torch
+    return torch
+
+
 def _ptr(t, dtype, name: str) -> Optional[int]:
     if t is None:
         return None
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise TypeError(f"{name} must be a device tensor")
-    if dtype == torch.uint16 and t.dtype == torch.int16:
-        return t.data_ptr()      # same bytes; int16 tensors have wider operator support
-    if t.dtype != dtype:
+    torch = _torch or _torch_module()
+    if isinstance(t, torch.Tensor) and t.is_cuda:
+        if t.dtype is dtype or (dtype is torch.uint16 and t.dtype is torch.int16):
+            return t.data_ptr()      # (int16: same bytes, wider operator support)
         raise TypeError(f"{name} must have dtype {dtype}, has {t.dtype}")
-    return t.data_ptr()
+    raise TypeError(f"{name} must be a device tensor")
 
 
 def _rows(t, name: str):
-    """(pointer, row stride in elements) of a 2-D tensor whose rows are contiguous."""
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
-        raise ValueError(f"{name} must be 2-D with unit column stride")
-    return t.shape[0], t.shape[1], (t.stride(0) if t.shape[0] > 1 else max(t.shape[1], t.stride(0)))
+    """(rows, columns, row stride in elements) of a 2-D tensor whose rows are contiguous."""
+    shape = t.shape
+    if len(shape) == 2:
+        rows, cols = shape
+        stride = t.stride()
+        if cols <= 1 or stride[1] == 1:
+            return rows, cols, (stride[0] if rows > 1 else max(cols, stride[0]))
+    raise ValueError(f"{name} must be 2-D with unit column stride")
 
 
 def _stream(stream) -> Optional[int]:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    if stream is not None:
+        return stream.cuda_stream or None
+    c = (_torch or _torch_module())._C
+    try:
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice()) or None      # the current device's current stream
+    except AttributeError:
+        return _torch.cuda.current_stream().cuda_stream or None
 
 
 class Params:
     """Learned parameters resident on the device (see ``maddness_params``)."""
 
     def __init__(self, split_dims, thresholds, prototypes=None):
-        import torch
         self.C = int(split_dims.shape[0])
         if tuple(split_dims.shape) != (self.C, 4) or tuple(thresholds.shape) != (self.C, 16):
             raise ValueError("split_dims must be [C][4] and thresholds [C][16]")
@@ -144,8 +160,6 @@ class Params:
             if prototypes.dim() != 3 or prototypes.shape[0] != self.C or prototypes.shape[1] != 16:
                 raise ValueError("prototypes must be [C][16][D]")
         self.D: Optional[int] = None if prototypes is None else int(prototypes.shape[2])
-        self._c = None
-        self._torch = torch
 
     @classmethod
     def from_model(cls, model, device="cuda"):
@@ -156,7 +170,7 @@ class Params:
                    torch.from_numpy(model.prototypes).to(device))
 
     def c_struct(self, D: int) -> _Params:
-        t = self._torch
+        t = _torch or _torch_module()
         return _Params(D, self.C, _ptr(self.split_dims, t.int32, "split_dims"),
                        _ptr(self.thresholds, t.float32, "thresholds"),
                        _ptr(self.prototypes, t.float32, "prototypes"))
@@ -164,7 +178,7 @@ class Params:
 
 def maddness_encode(params: Params, A, codes=None, stream=None):
     """g(A): packed 4-bit codes, uint8 [N][(C+1)/2]."""
-    import torch
+    torch = _torch or _torch_module()
     N, D, lda = _rows(A, "A")
     if params.D is not None and params.D != D:
         raise ValueError("A has a different D than the prototypes")
@@ -183,22 +197,23 @@ MADDNESS_ROW_MAJOR, MADDNESS_COL_MAJOR = 0, 1
 def _typed(A, col_major: bool):
     """(pointer, dtype code, layout code, N, D, lda) of an input of any supported type.
     With col_major the tensor holds the columns of A: shape [D][N]."""
-    import torch
-    codes = {torch.float32: MADDNESS_F32, torch.float16: MADDNESS_F16, torch.bfloat16: MADDNESS_BF16,
-             torch.uint8: MADDNESS_U8}
+    torch = _torch or _torch_module()
     if not isinstance(A, torch.Tensor) or not A.is_cuda:
         raise TypeError("A must be a device tensor")
-    if A.dtype not in codes:
+    dtype = A.dtype
+    code = (MADDNESS_F32 if dtype is torch.float32 else MADDNESS_F16 if dtype is torch.float16 else
+            MADDNESS_BF16 if dtype is torch.bfloat16 else MADDNESS_U8 if dtype is torch.uint8 else None)
+    if code is None:
         raise TypeError(f"A has dtype {A.dtype}; supported: float32, float16, bfloat16, uint8")
     r, c, ld = _rows(A, "A")
     N, D = (c, r) if col_major else (r, c)
-    return A.data_ptr(), codes[A.dtype], (MADDNESS_COL_MAJOR if col_major else MADDNESS_ROW_MAJOR), N, D, ld
+    return A.data_ptr(), code, (MADDNESS_COL_MAJOR if col_major else MADDNESS_ROW_MAJOR), N, D, ld
 
 
 def maddness_encode_typed(params: Params, A, col_major=False, codes=None, stream=None):
     """g(A) for A of dtype float32 / float16 / bfloat16 / uint8, stored by rows ([N][D]) or,
     with col_major, by columns ([D][N])."""
-    import torch
+    torch = _torch or _torch_module()
     ptr, dt, layout, N, D, lda = _typed(A, col_major)
     if params.D is not None and params.D != D:
         raise ValueError("A has a different D than the prototypes")
@@ -213,7 +228,7 @@ def maddness_encode_typed(params: Params, A, col_major=False, codes=None, stream
 def maddness_encode_scan_typed(params: Params, A, luts, scale, offset, col_major=False, out=None, acc=None,
                                codes=None, want_out=True, stream=None):
     """Fused g, f and alpha f + beta for A of any supported type and storage order."""
-    import torch
+    torch = _torch or _torch_module()
     ptr, dt, layout, N, D, lda = _typed(A, col_major)
     M = luts.shape[2]
     if want_out and out is None:
@@ -239,7 +254,7 @@ def maddness_build_luts_pooled(params: Params, B, luts=None, scale=None, offset=
 def maddness_build_luts(params: Params, B, luts=None, scale=None, offset=None, workspace=None,
                         stream=None, _pooled=False):
     """h(B): uint8 tables [C][16][M] with per-column scale and offset."""
-    import torch
+    torch = _torch or _torch_module()
     D, M, ldb = _rows(B, "B")
     if params.D != D:
         raise ValueError("B has a different D than the prototypes")
@@ -265,7 +280,7 @@ STATIC_WORKSPACE_BYTES = 8388608
 def maddness_build_luts_static(params: Params, B, luts, scale, offset, stream=None):
     """h(B) with the library's own per-GPU workspace: the call allocates nothing, so every
     output is passed in.  Shapes beyond STATIC_WORKSPACE_BYTES raise MADDNESS_E_UNSUPPORTED."""
-    import torch
+    torch = _torch or _torch_module()
     D, M, ldb = _rows(B, "B")
     if params.D != D:
         raise ValueError("B has a different D than the prototypes")
@@ -279,7 +294,7 @@ def maddness_build_luts_static(params: Params, B, luts, scale, offset, stream=No
 
 
 def _scan(entry, n_codebooks: int, codes, luts, scale, offset, out, acc, want_out, stream):
-    import torch
+    torch = _torch or _torch_module()
     N = codes.shape[0]
     M = luts.shape[2]
     if want_out and out is None:
@@ -307,7 +322,7 @@ def maddness_scan_averaged(n_codebooks: int, codes, luts, scale, offset, out=Non
 
 
 def _encode_scan(entry, params: Params, A, luts, scale, offset, out, acc, codes, want_out, stream):
-    import torch
+    torch = _torch or _torch_module()
     N, D, lda = _rows(A, "A")
     M = luts.shape[2]
     if want_out and out is None:
@@ -350,7 +365,7 @@ def maddness_learn_trees(A_train, subspaces, split_dims=None, thresholds=None, t
                          stream=None):
     """The C hashing trees from a training matrix on the device (Section 4.2; Appendix C).
     Returns device tensors (split_dims int32 [C][4], thresholds fp32 [C][16], train_codes uint8 [N][C])."""
-    import torch
+    torch = _torch or _torch_module()
     N, D, lda = _rows(A_train, "A_train")
     bounds, n_cb = _bounds(subspaces)
     dev = A_train.device
@@ -372,7 +387,7 @@ def maddness_learn_prototypes(train_codes, A_train, subspaces, ridge=True, lam=1
                               stream=None):
     """The prototypes [C][16][D] from the training codes: ridge regression (Section 4.3) or, with
     ridge=False, the bucket means."""
-    import torch
+    torch = _torch or _torch_module()
     N, D, lda = _rows(A_train, "A_train")
     bounds, n_cb = _bounds(subspaces)
     if tuple(train_codes.shape) != (N, n_cb):
