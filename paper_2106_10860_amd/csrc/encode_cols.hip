@@ -280,7 +280,13 @@ int launch_fused_cols(const maddness_params &p, const MatrixA &A, int64_t N, int
                       int64_t ldo, uint16_t *acc, uint8_t *codes, bool averaged, hipStream_t stream)
 {
     const int C = p.C;
-    if (!A.col_major || N < kMinRows) return 1;
+    if (!A.col_major) return 1;
+    if (!averaged && !vector_scan_only() && !option(MADDNESS_OPT_COLS_RUN)) {
+        // (few rows: any number of them)
+        const int rc = launch_fused_mfma(p, A, N, M, luts, scale, offset, out, ldo, acc, codes, stream);
+        if (rc != 1) return rc;
+    }
+    if (N < kMinRows) return 1;
     // whole runs of four rows (whatever run length is chosen); the rest goes to the general kernel
     const int64_t Nq = N & ~(int64_t)3;
     // the exact sum on the matrix cores where that kernel takes the shape (bound by HBM, where

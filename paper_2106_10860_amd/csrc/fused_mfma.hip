@@ -56,13 +56,18 @@ int max_workgroups()
 #define MADDNESS_PHASED_MAX_ROWS 1024
 #endif
 
+// A stored by columns: up to this many rows are encoded a row to a lane (EncodeMode kByColumnsFew).  Four rows to a lane
+// read longer pieces of a column, but a workgroup takes 2048 rows then: C = 32, M = 256, binary16, N = 65536 40 us a
+// row to a lane and 98 four, N = 2^18 132 and 104.
+constexpr int64_t kColsFewRows = 1 << 17;
+
 // the value of x, as far as the compiler knows a new one each time
 __device__ __forceinline__ int opaque(int x)
 {
     asm volatile("" : "+v"(x));
     return x;
 }
-enum EncodeMode { kRowMajor = 0, kByColumns = 1 };
+enum EncodeMode { kRowMajor = 0, kByColumns = 1, kByColumnsFew = 2 };
 
 // Bytes at the start of LDS that the phases use in turn: E stages RPI rows of DV KiB per wavefront there
 // (row-major A); S first passes the tables of its columns through it, then keeps the one-hot table there (256 bytes)
@@ -387,12 +392,43 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
             __syncthreads();   // the codes area is overwritten by the next region's E
         }
     } else {
-        // A workgroup takes blocks of 8 rw consecutive rows (rw a multiple of 256), wavefront
-        // w the rows [w rw, (w + 1) rw) of the block in groups of 256.  N is a multiple of 4.
+        // A workgroup takes blocks of 8 rw consecutive rows; kByColumns: rw a multiple of 256, wavefront
+        // w the rows [w rw, (w + 1) rw) of the block in groups of 256, N a multiple of 4.
         const int64_t block_rows = 8 * (int64_t)rw;
         for (int64_t R0 = blockIdx.x * block_rows; R0 < a.N; R0 += G * block_rows) {
             // ---- E ----
-            {
+            if constexpr (EMODE == kByColumnsFew) {
+                // Few rows: the wavefronts share out the codebooks as well, eight (a word of codes) of 64 rows to one,
+                // a row to a lane, all 32 loads of a lane on their way at once.  (In runs of four rows, two codebooks
+                // at a time, a wavefront takes 256 rows in C / 2 turns of one memory latency each: N = 65536 keeps 32
+                // compute units busy, for 98 us with C = 32 and M = 256 and 234 us with C = 64 and M = 512.)
+                constexpr int TOGETHER = kWaves / CW;                  // wavefront groups of 64 rows
+                const int q = wave % CW;
+                const auto split_dims = cols::as_constant(a.split_dims);
+                const auto thresholds = cols::as_constant(a.thresholds);
+                const int64_t block_end = block_rows < a.N - R0 ? block_rows : a.N - R0;
+                for (int local = 64 * (wave / CW); local < block_end; local += 64 * TOGETHER) {
+                    const int64_t row = R0 + local + lane, from = row < a.N ? row : a.N - 1;
+                    float x[8][4];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const int col_t = min(max(split_dims[4 * (8 * q + u) + t], 0), a.D - 1);
+                            x[u][t] = widen_at<DT>(a.A, (int64_t)col_t * a.lda + from);
+                        }
+                    unsigned word = 0;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        Tree tr;
+#pragma unroll
+                        for (int i = 0; i < 15; ++i) tr.t[i] = thresholds[16 * (8 * q + u) + i];
+                        word |= hash_regs(tr, x[u][0], x[u][1], x[u][2], x[u][3]) << (4 * u);
+                    }
+                    *reinterpret_cast<uint32_t *>(codes_l + (size_t)(local + lane) * CB + 4 * q) = word;
+                    if (a.codes_out && row < a.N) *reinterpret_cast<uint32_t *>(a.codes_out + row * CB + 4 * q) = word;
+                }
+            } else {
                 cols::ColsEncoder<C, DT, 2, 4> enc(a);
                 for (int grp = 0; grp < rw / 256; ++grp) {
                     const int local = wave * rw + grp * 256;
@@ -408,7 +444,6 @@ __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs 
                     }
                 }
             }
-            __syncthreads();
             // ---- S ----
             const int64_t left = a.N - R0;
             const int groups = (int)(((left < block_rows ? left : block_rows) + 15) >> 4);
@@ -471,6 +506,40 @@ int launch_cols(const RowsArgs &a, hipStream_t stream)
     note_kernel("fused_mfma_kernel, A by columns", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_mfma_kernel<C, 1, NT, kByColumns, DT>), dim3(grid), dim3(kWaves * 64), lds, stream, a, rw);
     return check_hip(hipGetLastError(), "launch fused_mfma_kernel");
+}
+
+// A stored by columns, few rows: any number of them, any stride.
+template <int C, int NT, int DT>
+int launch_cols_few(const RowsArgs &a, hipStream_t stream)
+{
+    const DeviceInfo &dev = device_info();
+    constexpr int stage_bytes = shared_bytes(kByColumnsFew, 1, 1, NT, true, false);
+    constexpr int STEP = 64 * kWaves / (C / 8);      // rows that the workgroup encodes at a time
+    // an even share of the rows for every workgroup, in as many turns as LDS takes codes for
+    const int cap = (dev.lds_per_block - stage_bytes) / (C / 2) / STEP * STEP, wgs = max_workgroups();
+    int64_t rows = (a.N + wgs - 1) / wgs;
+    if (rows > cap) rows = (rows + (rows + cap - 1) / cap - 1) / ((rows + cap - 1) / cap);
+    // MADDNESS_OPT_PHASED_ROWS lowers that (testing aid: several blocks per workgroup with few rows)
+    if (const int v = option(MADDNESS_OPT_PHASED_ROWS); v >= 2 && kWaves * (int64_t)v < rows) rows = kWaves * v;
+    rows = (rows + STEP - 1) / STEP * STEP;
+    const size_t lds = stage_bytes + (size_t)rows * (C / 2);
+    if (int rc = allow_full_lds<fused_mfma_kernel<C, 1, NT, kByColumnsFew, DT>>(); rc != MADDNESS_OK) return rc;
+    const int64_t blocks = (a.N + rows - 1) / rows;
+    note_kernel("fused_mfma_kernel, A by columns, few rows", __PRETTY_FUNCTION__);
+    hipLaunchKernelGGL((fused_mfma_kernel<C, 1, NT, kByColumnsFew, DT>), dim3((unsigned)(blocks < wgs ? blocks : wgs)), dim3(kWaves * 64),
+                       lds, stream, a, (int)(rows / kWaves));
+    return check_hip(hipGetLastError(), "launch fused_mfma_kernel");
+}
+
+template <int C, int NT>
+int launch_cols_few_typed(const RowsArgs &a, int dtype, hipStream_t stream)
+{
+    switch (dtype) {
+    case MADDNESS_F32: return launch_cols_few<C, NT, kF32>(a, stream);
+    case MADDNESS_F16: return launch_cols_few<C, NT, kF16>(a, stream);
+    case MADDNESS_BF16: return launch_cols_few<C, NT, kBF16>(a, stream);
+    default: return launch_cols_few<C, NT, kU8>(a, stream);
+    }
 }
 
 template <int C, int DV, int NT>
@@ -600,6 +669,18 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
                          (!acc || aligned_to(acc, 2 * NT)) &&
                          (A.col_major || ((D * es) % 16 == 0 && (A.ld * es) % 16 == 0 && aligned_to(A.data, 16) &&
                                           (!codes || aligned_to(codes, C != p.C ? 4 : (C == 16 ? 8 : 16)))));
+    if (regular && A.col_major && C == p.C && N <= kColsFewRows) {
+        // (tables and trees cost this kernel 13 to 19 us before the first row, and the general one single elements and
+        // tiles of the tables: binary16, M = 256, C = 32 19 against 19 us for 1000 rows, 20 against 22 for 8192, 21
+        // against 30 for 16384; bfloat16, M = 64, C = 32 16 against 12 for 2048 and 16 against 16 for 8192; fp32, M = 512,
+        // C = 64 25 against 180 for 500)
+        const int64_t tables = 16 * (int64_t)C * M;
+        if (N < (tables <= 64 * 1024 ? 16384 : tables <= 128 * 1024 ? 4096 : 1)) return 1;
+        if (codes && !aligned_to(codes, 4)) return 1;
+        return C == 16   ? launch_cols_few_typed<16, 4>(a, A.dtype, stream)
+               : C == 32 ? launch_cols_few_typed<32, 4>(a, A.dtype, stream)
+                         : launch_cols_few_typed<64, 2>(a, A.dtype, stream);
+    }
     if (N < matrix_cores_min_rows(p.C, M, regular && (p.C == 16 || p.C == 32))) return 1;
     if (!regular) {
         if (!A.plain() || p.C > 64) return 1;

@@ -1,0 +1,149 @@
+"""GPU parity at the edges of three pieces: the tables' way into the registers of the matrix-core scan (any M, any
+alignment, few rows), A stored by columns encoded a row to a lane, and the staged product of the table build; and the
+learner's ridge solve at the sizes where its launch changes, and its trees on data with infinities.  Codes,
+accumulators, outputs, trees and prototypes equal the oracle's to the bit; table bytes as in compare_luts."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import compare_luts, oracle_pipeline, random_trees
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mad():
+    import torch
+    import paper_2106_10860_amd as m
+    assert torch.cuda.is_available()
+    m.lib()
+    return m
+
+
+def dev(x):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def problem(seed, N, D, M, C):
+    rng = np.random.default_rng(seed)
+    A = np.maximum(rng.standard_normal((N, D)), 0).astype(np.float32)
+    sd, th = random_trees(rng, A, C)
+    luts = rng.integers(0, 256, size=(C, 16, M)).astype(np.uint8)
+    scale = np.exp2(-rng.integers(0, 6, size=M)).astype(np.float32)
+    offset = rng.standard_normal(M).astype(np.float32)
+    return A, sd, th, luts, scale, offset
+
+
+# (N, D, M, C, bytes the tables start after a 16-byte boundary): tables of more than 64 KiB take the matrix cores from
+# the first row on; one row, whole and broken units of 8 and groups of 16, one to three columns after the last four,
+# padding codebooks, several passes of columns
+FEW = [
+    (1, 256, 512, 64, 0), (7, 256, 260, 64, 0), (17, 1024, 1032, 32, 0), (33, 128, 1001, 16, 0), (9, 300, 333, 24, 0),
+    (65, 300, 342, 24, 1), (255, 512, 255, 30, 3), (300, 512, 1022, 32, 2), (40, 200, 97, 50, 1), (129, 160, 128, 40, 0),
+    (16390, 200, 3, 20, 1), (16390, 200, 1, 33, 0),
+]
+
+
+@pytest.mark.parametrize("shape", FEW, ids=lambda s: "N%d_D%d_M%d_C%d_at%d" % s)
+def test_tables_in_registers(mad, shape):
+    import torch
+    N, D, M, C, at = shape
+    print("case", shape, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D + M, N, D, M, C)
+    want_out, want_acc, want_codes = oracle.encode_scan(A, sd, th, luts, scale, offset)
+    params = mad.Params(dev(sd), dev(th))
+    raw = torch.zeros(luts.size + at, dtype=torch.uint8, device="cuda")
+    raw[at:] = dev(luts).reshape(-1)
+    luts_d = raw[at:].reshape(C, 16, M)
+    acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+    codes = torch.zeros((N, (C + 1) // 2), dtype=torch.uint8, device="cuda")
+    out = mad.maddness_encode_scan(params, dev(A), luts_d, dev(scale), dev(offset), acc=acc, codes=codes)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("fused_mfma_kernel"), kernel
+    assert (codes.cpu().numpy() == want_codes).all()
+    assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+    assert (out.cpu().numpy() == want_out).all()
+    out2, _ = mad.maddness_scan(C, codes, luts_d, dev(scale), dev(offset))
+    torch.cuda.synchronize()
+    assert (out2.cpu().numpy() == want_out).all(), mad.maddness_last_kernel()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "u8"])
+@pytest.mark.parametrize("shape", [(1, 40, 512, 64, 0), (63, 40, 516, 64, 1), (16385, 64, 68, 16, 3), (4099, 48, 256, 32, 0),
+                                   (4097, 40, 512, 64, 5), (40000, 32, 64, 32, 2)], ids=lambda s: "N%d_D%d_M%d_C%d_p%d" % s)
+def test_by_columns_few_rows(mad, shape, dtype):
+    import torch
+    N, D, M, C, pad = shape
+    print("case", shape, dtype, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D, N, D, M, C)
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    full = torch.zeros((D, N + pad), dtype=kind, device="cuda")
+    full[:, :N] = (dev(A.T) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind)
+    A_d = full[:, :N]
+    values = A_d.float().cpu().numpy().T.copy()
+    want_out, want_acc, want_codes = oracle.encode_scan(values, sd, th, luts, scale, offset)
+    params = mad.Params(dev(sd), dev(th))
+    acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+    codes = torch.zeros((N, C // 2), dtype=torch.uint8, device="cuda")
+    out = mad.maddness_encode_scan_typed(params, A_d, dev(luts), dev(scale), dev(offset), col_major=True, acc=acc, codes=codes)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("fused_mfma_kernel, A by columns, few rows"), kernel
+    assert (codes.cpu().numpy() == want_codes).all()
+    assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+    assert (out.cpu().numpy() == want_out).all()
+
+
+# (D, M, C): one tile and parts of tiles of the inner dimension (64), the columns (32 a workgroup, 64 a workgroup of the
+# quantisation) and the codebooks (1, 2 or 4 a workgroup, whichever leaves one for every compute unit; 8 minima at a time)
+@pytest.mark.parametrize("shape", [(1, 1, 1), (63, 31, 3), (64, 32, 4), (65, 33, 5), (130, 65, 17), (200, 520, 33), (129, 520, 63),
+                                   (70, 1030, 255)], ids=lambda s: "D%d_M%d_C%d" % s)
+def test_table_build_at_tile_edges(mad, shape):
+    import torch
+    D, M, C = shape
+    print("case", shape, flush=True)
+    rng = np.random.default_rng(D + M + C)
+    P = rng.standard_normal((C, 16, D)).astype(np.float32)
+    B = rng.standard_normal((D, M + 3)).astype(np.float32)
+    A = rng.standard_normal((5, D)).astype(np.float32)
+    sd, th = random_trees(rng, A, C)
+    ref = oracle_pipeline(A, sd, th, P, B[:, :M].copy())
+    params = mad.Params(dev(sd), dev(th), dev(P))
+    luts, scale, offset = mad.maddness_build_luts(params, dev(B)[:, :M])
+    torch.cuda.synchronize()
+    compare_luts(luts.cpu().numpy(), scale.cpu().numpy(), offset.cpu().numpy(), ref, P, B[:, :M])
+
+
+@pytest.mark.parametrize("C", [1, 4, 36, 37, 73, 110])
+def test_ridge_solve_where_its_launch_changes(mad, C):
+    """One and four panels of 16, and either side of the sizes at which a helper takes more entries of a row (576,
+    1152 rows of the factor) or a workgroup fewer columns (1700)."""
+    import torch
+    rng = np.random.default_rng(C)
+    N, D = 300, C + 2
+    A = rng.standard_normal((N, D)).astype(np.float32)
+    subspaces = [(c, c + 1) for c in range(C)]
+    codes = rng.integers(0, 16, size=(N, C)).astype(np.uint8)
+    P = mad.maddness_learn_prototypes(dev(codes), dev(A), subspaces, ridge=True, lam=0.5)
+    torch.cuda.synchronize()
+    assert (P.cpu().numpy() == oracle.ridge_prototypes(codes, A, 0.5).astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("where", [(0, 5), (3, 5), (700, 700)], ids=["first", "both_signs", "last"])
+def test_trees_on_data_with_infinities(mad, where):
+    """An infinite value makes the losses of the splits around it not a number; a comparison with one is false, so such a
+    split is the best only where it is its bucket's first."""
+    import torch
+    rng = np.random.default_rng(sum(where))
+    A = rng.standard_normal((701, 12)).astype(np.float32)
+    A[where[0], 2] = np.inf
+    A[where[1], 9] = -np.inf
+    subspaces = [(0, 6), (6, 12)]
+    sd, th, codes = mad.maddness_learn_trees(dev(A), subspaces)
+    torch.cuda.synchronize()
+    want_sd, want_th, want_codes, _ = oracle.learn_trees(A, subspaces)
+    assert (sd.cpu().numpy() == want_sd).all()
+    assert (th.cpu().numpy().view(np.uint32) == want_th.view(np.uint32)).all()
+    assert (codes.cpu().numpy() == want_codes).all()
