@@ -217,13 +217,15 @@ __device__ __forceinline__ void add_tile_in_order(double &acc, const float *at, 
 
 // The workgroup's loop: n_steps tiles of kChainRows rows.  walk(values of tile s, s) runs on the first kWalkers
 // wavefronts; meanwhile the helpers lay out tile s + 1, fetch the values of tile s + kDepth + 1 and list the rows of the
-// tile after that (row_at(s, i): the number of row i of tile s, `N` where there is none), whose numbers they asked for
-// kDepth steps before.  X: the codebook's values, from the workgroup's first column on.
+// tile after that, whose numbers they asked for kDepth steps before: ask(s, i) reads what tells the number of row i of
+// tile s, anything where there is none, and row(read, s, i) is the number, `N` where there is none.  (ask has to read in
+// any case: a read under a condition becomes a branch, after which every wait is one for all that is on its way, 600 ns
+// a tile.)  X: the codebook's values, from the workgroup's first column on.
 template <int NC>
 constexpr size_t stream_lds_bytes() { return sizeof(float) * 2 * NC * kChainPitch + sizeof(int32_t) * kLists * kChainRows; }
 
-template <int NC, int kWalkers, typename RowAt, typename Walk>
-__device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, int pitch, int n_steps, RowAt row_at, Walk walk)
+template <int NC, int kWalkers, typename Ask, typename Row, typename Walk>
+__device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, int pitch, int n_steps, Ask ask, Row row, Walk walk)
 {
     constexpr int kPieces = NC / 4, kStride = kChainHelpers / kPieces, kPer = kChainRows / kStride, kBuffer = NC * kChainPitch;
     float *values = reinterpret_cast<float *>(lds);                        // [2][NC][kChainPitch]
@@ -232,7 +234,7 @@ __device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, 
     const int rsub = at / kPieces, piece = at % kPieces;
     const float *src = X + 4 * piece;
     float4 x[kDepth][kPer];
-    int32_t next[kDepth];
+    decltype(ask(0, 0)) next[kDepth];
     auto fetch = [&](int s, int set) __attribute__((always_inline)) {
         const int32_t *rows = listed + (s % kLists) * kChainRows;
 #pragma unroll
@@ -249,73 +251,205 @@ __device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, 
             dst[u * kStride + 3 * kChainPitch] = x[set][u].w;
         }
     };
-    if (helper >= 0)
-#pragma unroll
-        for (int s = 0; s < kDepth + 2; ++s) listed[(s % kLists) * kChainRows + helper] = row_at(s, helper);
-    __syncthreads();
-    if (helper >= 0) {
-        fetch(0, 0);
-        stash(0, 0);
-#pragma unroll
-        for (int s = 1; s <= kDepth; ++s) {
-            fetch(s, s % kDepth);
-            next[s - 1] = row_at(s + kDepth + 1, helper);
+    // (Two loops with a barrier a tile in each: in one loop the compiler takes a load for the newest wherever the walkers'
+    // side may have come between, and waits for all of them.)
+    if (__builtin_amdgcn_readfirstlane(helper) < 0) {
+        __syncthreads();
+        __syncthreads();
+        for (int s = 0; s < n_steps; ++s) {
+            walk(values + (s & 1) * kBuffer, s);
+            __syncthreads();
         }
+        return;
+    }
+#pragma unroll
+    for (int s = 0; s < kDepth + 2; ++s) listed[(s % kLists) * kChainRows + helper] = row(ask(s, helper), s, helper);
+    __syncthreads();
+    fetch(0, 0);
+    stash(0, 0);
+#pragma unroll
+    for (int s = 1; s <= kDepth; ++s) {
+        fetch(s, s % kDepth);
+        next[s - 1] = ask(s + kDepth + 1, helper);
     }
     __syncthreads();
     for (int s0 = 0; s0 < n_steps; s0 += kDepth) {
 #pragma unroll
         for (int i = 0; i < kDepth; ++i) {
             const int s = s0 + i;
-            if (s >= n_steps) break;
-            if (helper < 0) {
-                walk(values + (s & 1) * kBuffer, s);
-            } else {
-                stash(s + 1, (i + 1) % kDepth);
-                fetch(s + 1 + kDepth, (i + 1) % kDepth);
-                listed[((s + kDepth + 2) % kLists) * kChainRows + helper] = next[i];
-                next[i] = row_at(s + 2 * kDepth + 2, helper);
-            }
+            if (s >= n_steps) return;
+            stash(s + 1, (i + 1) % kDepth);
+            fetch(s + 1 + kDepth, (i + 1) % kDepth);
+            listed[((s + kDepth + 2) % kLists) * kChainRows + helper] = row(next[i], s + kDepth + 2, helper);
+            next[i] = ask(s + 2 * kDepth + 2, helper);
             __syncthreads();
         }
     }
 }
 
-// L(j, B_i): the sum, then the squared distances from the mean, over the bucket's rows in row order, a chain per
-// column, up to NC columns of a bucket to a workgroup.  (Measured, level 1 of 260100 x 27 with 4 codebooks, two sums of
-// 260100 rows: 1.6 ms, 3 ns a row; 7.1 ms with a lane per chain that read and converted its values itself.  The four
-// levels: 3.3 against 14.6 ms, and 0.39 against 1.75 ms for 20000 x 512 with 32 codebooks.)
-template <int NC>
-__global__ __launch_bounds__(16 * NC + kChainHelpers) void bucket_loss_kernel(const LearnArgs a)
+// A sum in a given order without its chain of roundings: 256 terms at once, 4 to a lane (term 64 k + lane is t[k]), on
+// two grounds that are checked for every 256, after which any order gives the same bits.
+//   - While a sum s stays in one binade, its ulp u does not change, and adding t rounds s + t to a multiple of u: the
+//     step is t rounded to a multiple of u (which adding and subtracting 1.5 times the binade's power of two does), halves
+//     going to whichever side makes the sum an even multiple.  Steps are whole multiples of u, so their sum is
+//     exact.  A half's side depends on the parity of the sum before it, which the parities of the steps since the last
+//     half give (after a half the sum is even): ballots.
+//   - If all terms and s are multiples of 2^(E-52) and no partial sum reaches 2^(E+1), every sum is exact.
+// Where neither holds (a sum that leaves its binade, some 30 times in a sum of 2^18 squares; data with infinities) the
+// 256 terms go through the chain.  (A tile of 256 whole values, both sums: 370 ns each, of which 215 are the rows' way
+// into LDS; the chain of either takes 560.)
+__device__ __forceinline__ double power_of_two(int field) { return __builtin_bit_cast(double, (uint64_t)field << 52); }
+
+__device__ __forceinline__ double read_lane(double x, int lane)
+{
+    const uint64_t bits = __builtin_bit_cast(uint64_t, x);
+    const uint32_t low = __builtin_amdgcn_readlane((int)(uint32_t)bits, lane), high = __builtin_amdgcn_readlane((int)(bits >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)high << 32 | low);
+}
+
+// the sum over the wavefront's lanes, in any order
+__device__ __forceinline__ double wave_sum(double x)
+{
+    auto rotated = [](double v, auto by) __attribute__((always_inline)) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, v);
+        const int low = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)bits, 0x120 + decltype(by)::value, 0xf, 0xf, true);
+        const int high = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), 0x120 + decltype(by)::value, 0xf, 0xf, true);
+        return __builtin_bit_cast(double, (uint64_t)(uint32_t)high << 32 | (uint32_t)low);
+    };
+    x += rotated(x, std::integral_constant<int, 8>{});
+    x += rotated(x, std::integral_constant<int, 4>{});
+    x += rotated(x, std::integral_constant<int, 2>{});
+    x += rotated(x, std::integral_constant<int, 1>{});
+    return (read_lane(x, 0) + read_lane(x, 16)) + (read_lane(x, 32) + read_lane(x, 48));
+}
+
+__device__ __forceinline__ bool add_in_binade(double &s, const double (&t)[4])      // terms >= 0
+{
+    const uint64_t bits = __builtin_bit_cast(uint64_t, s);
+    const int e = __builtin_amdgcn_readfirstlane((int)(bits >> 52));
+    // (zero, or next to the ends of the range: the sum stays only if all terms are 0, as a column of equal values has them)
+    if (e < 64 || e > 2000) return !__ballot(t[0] != 0.0 || t[1] != 0.0 || t[2] != 0.0 || t[3] != 0.0);
+    const double c = __builtin_bit_cast(double, (uint64_t)e << 52 | 1ull << 51);
+    const double ulp = power_of_two(e - 52), half = power_of_two(e - 53), most = power_of_two(e - 1);
+    double y[4], steps = 0.0;
+    bool fits = true, halves = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        y[k] = t[k] + c;
+        const double step = y[k] - c;
+        fits &= t[k] < most;
+        halves |= fabs(t[k] - step) == half;
+        steps += step;
+    }
+    if (__ballot(!fits)) return false;
+    double end = s + wave_sum(steps);
+    const double limit = power_of_two(e + 1);
+    if (__ballot(halves)) {
+        if (!(end + 256.0 * ulp < limit)) return false;
+        const int lane = threadIdx.x & 63;
+        const unsigned long long below = (1ull << lane) - 1ull;
+        int parity = (int)(bits & 1), moved = 0;               // of the sum in units of u; units that halves went the other way
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double left = t[k] - (y[k] - c);
+            const bool is_half = fabs(left) == half;
+            const unsigned long long odd = __ballot((__builtin_bit_cast(uint64_t, y[k]) & 1) != 0), half_at = __ballot(is_half);
+            // the parity before this lane's term: of the steps since the last half, or since the lanes' first
+            const unsigned long long before = half_at & below;
+            const unsigned long long since = before ? ~((2ull << (63 - __clzll(before))) - 1ull) : ~0ull;
+            const bool is_odd = ((__popcll(odd & below & since) + (before ? 0 : parity)) & 1) != 0;
+            // (the step as computed is the even one of the two; an odd sum takes the other)
+            moved += __popcll(__ballot(is_half && is_odd && left > 0.0)) - __popcll(__ballot(is_half && is_odd && left < 0.0));
+            parity = half_at ? __popcll(odd & ~((2ull << (63 - __clzll(half_at))) - 1ull)) & 1 : (parity + __popcll(odd)) & 1;
+        }
+        end += (double)moved * ulp;
+    }
+    if (!(end < limit)) return false;
+    s = end;
+    return true;
+}
+
+// room: the least E (as an exponent field) that the terms so far have asked for
+__device__ __forceinline__ bool add_exactly(double &s, const double (&t)[4], int &room)
+{
+    const double m = fmax(fmax(fabs(t[0]), fabs(t[1])), fmax(fabs(t[2]), fabs(t[3])));
+    int E = __builtin_amdgcn_readfirstlane(max((int)(__builtin_bit_cast(uint64_t, s) >> 52 & 2047) + 1, room));
+    // (256 terms of at most 2^(E-9) each: half a binade)
+    while (__ballot(m > power_of_two(E - 9))) {
+        room = E = E + 4;
+        if (E > 2000) return false;
+    }
+    if (E > 2000) return false;
+    const double scale = power_of_two(2098 - E);               // 2^(52 - E)
+    bool whole = s * scale == rint(s * scale);
+    double steps = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        whole &= t[k] * scale == rint(t[k] * scale);
+        steps += t[k];
+    }
+    if (__ballot(!whole)) return false;
+    s += wave_sum(steps);
+    return true;
+}
+
+__device__ __forceinline__ void add_chained(double &s, const double (&t)[4])
+{
+    double one = 1.0;
+    asm("" : "+v"(one));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int row = 0; row < 4; ++row) {
+            double acc = s;
+            add_16_in_order(acc, t[k], one);
+            s = read_lane(acc, 16 * row);
+        }
+}
+
+// L(j, B_i): the sum, then the squared distances from the mean, over the bucket's rows in row order, a wavefront per
+// column, four columns of a bucket to a workgroup.  (Measured, the four levels of 260100 x 27 with 4 codebooks, whole
+// values: 1.65 ms; 3.3 ms with four chains to a wavefront and 14.6 ms with a lane per chain that read and converted its
+// values itself.  20000 x 512 with 32, of both signs, whose first sum takes the chain: 0.31, 0.39 and 1.75 ms.)
+__global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(const LearnArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int c = blockIdx.x, b = blockIdx.y, col0 = blockIdx.z * NC;
+    const int c = blockIdx.x, b = blockIdx.y, col0 = blockIdx.z * 4;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b];
     const int32_t *list = a.rows_by_bucket + (size_t)c * a.N + a.bucket_start[c * kSplitBuckets + b];
     const int n_steps = (count + kChainRows - 1) / kChainRows;
-    const int tid = threadIdx.x, cols = min(NC, d - col0);
-    const int chain = (tid / 16) % NC, l = tid & 15;
+    double *out = a.col_loss + ((size_t)c * kSplitBuckets + b) * a.dmax + col0;
+    if (count == 0) {
+        if (threadIdx.x < 4 && (int)threadIdx.x < d - col0) out[threadIdx.x] = 0.0;
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), cols = min(4, d - col0);
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
-    auto row_at = [&](int s, int i) __attribute__((always_inline)) {
-        const int p = s * kChainRows + i;
-        return p < count ? list[p] : (int32_t)a.N;
+    auto ask = [&](int s, int i) __attribute__((always_inline)) { return list[min(s * kChainRows + i, count - 1)]; };
+    auto row = [&](int32_t read, int s, int i) __attribute__((always_inline)) {
+        return s * kChainRows + i < count ? read : (int32_t)a.N;
     };
     double sum = 0.0, loss = 0.0;
-    stream_rows<NC, NC / 4>(lds_raw, X, a.pitch, n_steps, row_at, [&](const float *values, int) __attribute__((always_inline)) {
-        add_tile_in_order(sum, values + chain * kChainPitch + l, [](float x, int) { return (double)x; }, [](int) {});
+    int room = 1023;
+    stream_rows<4, 4>(lds_raw, X, a.pitch, n_steps, ask, row, [&](const float *values, int) __attribute__((always_inline)) {
+        double t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = (double)values[wave * kChainPitch + 64 * k + lane];
+        if (!add_exactly(sum, t, room)) add_chained(sum, t);
     });
-    const double mean = count > 0 ? sum / (double)count : 0.0;
-    stream_rows<NC, NC / 4>(lds_raw, X, a.pitch, n_steps, row_at, [&](const float *values, int s) __attribute__((always_inline)) {
-        const int left = count - s * kChainRows - l;
-        add_tile_in_order(loss, values + chain * kChainPitch + l, [&](float x, int row) __attribute__((always_inline)) {
-            const double e = (double)x - mean;
-            return row < left ? e * e : 0.0;          // (adding 0 leaves a sum as it is)
-        }, [](int) {});
+    const double mean = sum / (double)count;
+    stream_rows<4, 4>(lds_raw, X, a.pitch, n_steps, ask, row, [&](const float *values, int s) __attribute__((always_inline)) {
+        double t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double e = (double)values[wave * kChainPitch + 64 * k + lane] - mean;
+            t[k] = s * kChainRows + 64 * k + lane < count ? e * e : 0.0;          // (adding 0 leaves a sum as it is)
+        }
+        if (!add_in_binade(loss, t)) add_chained(loss, t);
     });
-    if (tid < 16 * NC && l == 0 && chain < cols)
-        a.col_loss[((size_t)c * kSplitBuckets + b) * a.dmax + col0 + chain] = count > 0 ? loss : 0.0;
+    if (wave < cols && lane == 0) out[wave] = loss;
 }
 
 // heuristic_select_idxs, and L(B_i) = sum over the columns of L(j, B_i).
@@ -507,7 +641,7 @@ constexpr int kGroupTiles = 8, kGroupRows = kGroupTiles * kJudgeRows;     // til
 __device__ __forceinline__ int64_t first_slot(int32_t start, int bucket) { return start / kJudgeRows + bucket; }
 __device__ __forceinline__ int64_t first_group(int32_t start, int bucket) { return start / kGroupRows + bucket; }
 
-// The chains are those of bucket_loss_kernel, both sums of up to NC columns to a workgroup.  Going down (direction 1)
+// Both sums of up to NC columns to a workgroup, four chains to a wavefront.  Going down (direction 1)
 // the tiles are taken last to first, each from its end; what lies past the bucket's last row counts as zeros, which
 // leave a sum as it is.
 template <int NC>
@@ -531,14 +665,20 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     double *out = a.sums + (((size_t)c * kCand + q) * 2 + dir) * a.tile_slots * (2 * a.dmax) +
                   (size_t)first_slot(start, b) * (2 * a.dmax) + (chain / NC) * a.dmax + col0 + chain % NC;
     const bool stored = l == 0 && chain % NC < cols;
+    // the place in the sorted order of row i of step s (before the first or after the last: none)
+    auto place = [&](int s, int i) __attribute__((always_inline)) {
+        const int at = s * kChainRows + i;
+        return dir ? n_tiles * kJudgeRows - 1 - at : at;
+    };
     double acc = 0.0;
     stream_rows<NC, NC / 2>(
         lds_raw, a.X + (size_t)c * (a.N + 1) * a.pitch + col0, a.pitch, n_steps,
         [&](int s, int i) __attribute__((always_inline)) {
-            const int tile = kTiles * s + i / kJudgeRows, in_tile = i % kJudgeRows;
-            const int p = dir ? (n_tiles - 1 - tile) * kJudgeRows + kJudgeRows - 1 - in_tile : tile * kJudgeRows + in_tile;
-            if (tile >= n_tiles || p >= count) return (int32_t)a.N;
-            return (int32_t)(static_cast<uint32_t>(keys[p]) & ((1u << kKeyRowBits) - 1u));
+            return static_cast<uint32_t>(keys[max(0, min(place(s, i), count - 1))]);
+        },
+        [&](uint32_t read, int s, int i) __attribute__((always_inline)) {
+            const int p = place(s, i);
+            return p >= 0 && p < count ? (int32_t)(read & ((1u << kKeyRowBits) - 1u)) : (int32_t)a.N;
         },
         [&](const float *values, int s) __attribute__((always_inline)) {
             add_tile_in_order(acc, values + (chain % NC) * kChainPitch + l,
@@ -1423,13 +1563,7 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
         hipLaunchKernelGGL(order_rows_kernel, dim3((unsigned)((N + order_chunk_rows(N) - 1) / order_chunk_rows(N)), C), dim3(256), 0,
                            stream, a, level, n_buckets);
         LAUNCH_OK("launch order_rows_kernel");
-        // (columns eight or sixteen at a time: a wavefront carries them all)
-        const int groups = narrow ? 1 : a.pitch / 16;
-        const dim3 loss_groups(C, n_buckets, groups);
-        if (narrow)
-            hipLaunchKernelGGL(bucket_loss_kernel<8>, loss_groups, dim3(16 * 8 + kChainHelpers), stream_lds_bytes<8>(), stream, a);
-        else
-            hipLaunchKernelGGL(bucket_loss_kernel<16>, loss_groups, dim3(16 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a);
+        hipLaunchKernelGGL(bucket_loss_kernel, dim3(C, n_buckets, a.pitch / 4), dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a);
         LAUNCH_OK("launch bucket_loss_kernel");
         hipLaunchKernelGGL(select_kernel, dim3(C), dim3(64), sizeof(double) * dmax, stream, a, n_buckets);
         LAUNCH_OK("launch select_kernel");
@@ -1451,6 +1585,8 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
             hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, k, chunk_len >> 1);
             LAUNCH_OK("launch sort_chunks_kernel");
         }
+        // (columns eight or sixteen at a time)
+        const int groups = narrow ? 1 : a.pitch / 16;
         const dim3 chain_groups(C, 8 * groups, n_buckets);
         const dim3 judges((unsigned)(a.group_slots * C), kCand);
         if (narrow) {

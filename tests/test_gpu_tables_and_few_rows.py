@@ -147,3 +147,31 @@ def test_trees_on_data_with_infinities(mad, where):
     assert (sd.cpu().numpy() == want_sd).all()
     assert (th.cpu().numpy().view(np.uint32) == want_th.view(np.uint32)).all()
     assert (codes.cpu().numpy() == want_codes).all()
+
+
+@pytest.mark.parametrize("kind", ["whole", "halves", "leaps", "signed", "tiny", "equal"])
+def test_losses_in_row_order(mad, kind):
+    """Which columns a level may split rests on the last bits of their losses here: each codebook's columns hold the same
+    values in orders of their own.  The kinds take the ways in which the sums are made: exact; half-way cases of the
+    rounding in every tile; sums that leave their binade; sums of both signs; the smallest; sums that stay zero."""
+    import torch
+    rng = np.random.default_rng(len(kind) + ord(kind[0]))
+    N, d = 2999, 8
+    half = rng.integers(1, 1 << 23, size=N // 2) * 2 + 1                      # odd, 24 bits: squares of 48 bits
+    half = np.concatenate([half, -half, [0]]) * 2.0 ** -20                    # of mean exactly 0
+    values = {"whole": rng.integers(0, 256, size=N),
+              "halves": half,
+              "leaps": half * np.exp2(20 * (rng.random(N) < 0.003)),
+              "signed": rng.standard_normal(N),
+              "tiny": rng.standard_normal(N) * 2.0 ** -140,
+              "equal": np.zeros(N)}[kind].astype(np.float32)
+    A = np.stack([rng.permutation(values) for _ in range(2 * d)], axis=1)
+    if kind == "equal":
+        A[:, 3] = rng.permutation(half)
+    subspaces = [(0, d), (d, 2 * d)]
+    sd, th, codes = mad.maddness_learn_trees(dev(A), subspaces)
+    torch.cuda.synchronize()
+    want_sd, want_th, want_codes, _ = oracle.learn_trees(A, subspaces)
+    assert (sd.cpu().numpy() == want_sd).all()
+    assert (th.cpu().numpy().view(np.uint32) == want_th.view(np.uint32)).all()
+    assert (codes.cpu().numpy() == want_codes).all()
