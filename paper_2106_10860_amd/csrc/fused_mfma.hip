@@ -89,8 +89,8 @@ constexpr int shared_bytes(int emode, int RPI, int DV, int NT, bool scan, bool g
 // on 128-byte lines.
 // PAD = true: a.codebooks < C codebooks exist (a multiple of 8); the kernel runs as for C with
 // the others' codes and table entries zero, and writes rows of a.codebooks / 2 bytes to a.codes_out.
-// ODD = true (fp32 row-major A, with GATHER and PAD): any shape the tile sizes cover - rows of A that
-// start on any 4-byte boundary and end anywhere, any number of codebooks up to C, any M, any pitch
+// ODD = true (row-major A, with PAD): any shape the tile sizes cover - rows of A that start on any
+// element and end anywhere, any number of codebooks up to C, any M, any pitch
 // and alignment of the outputs.  The E phase reads the aligned 16-byte pieces that cover a row,
 // the tables are read byte by byte, and the S phase writes through LDS (GATHER) - rows without padding
 // between them as ranges of floats in aligned 16-byte pieces, other rows each as a range of its own
@@ -100,7 +100,7 @@ constexpr int shared_bytes(int emode, int RPI, int DV, int NT, bool scan, bool g
 template <int C, int DV, int NT, int EMODE, int DT, bool SCAN = true, bool GATHER = false, bool PAD = false, bool ODD = false>
 __global__ __launch_bounds__(kWaves * 64) void fused_mfma_kernel(const RowsArgs a, const int rw)
 {
-    static_assert(!ODD || (PAD && EMODE == kRowMajor && DT == kF32), "ODD: fp32 rows, padding codebooks");
+    static_assert(!ODD || (PAD && EMODE == kRowMajor), "ODD: rows, padding codebooks");
     constexpr int KG = C / 4;
     constexpr int RPI = 64 / C;
     constexpr int CB = C / 2;
@@ -554,7 +554,7 @@ int launch_rows_typed(const RowsArgs &a, int dtype, hipStream_t stream)
 
 // fp32 row-major A of any shape the tiles cover (up to 64 codebooks, rows of up to 8 KiB; up to 16
 // codebooks: 2 KiB, up to 32: 4 KiB), any M, any pitch and alignment: the ODD form of the kernel.
-// Not for short rows: the E phase spends a fixed time per row, and below 512 bytes the general
+// Not for short rows to encode: the E phase spends a fixed time per row, and below 512 bytes the general
 // kernels, which only fetch the 4 C split values of a row, are faster (D = 27, C = 4, N = 2^20:
 // 0.03 against 0.47 ms).
 template <bool SCAN, bool GATHER>
@@ -569,20 +569,61 @@ int launch_odd_sized(const RowsArgs &a, int codebooks, int need, hipStream_t str
     return 1;
 }
 
-template <bool SCAN>
-int launch_odd(const RowsArgs &a, int codebooks, int row_bytes, hipStream_t stream)
+// The same for a narrow type: rows of up to 4 KiB (up to 16 codebooks: 1 KiB, up to 32: 2 KiB).
+template <int DT, bool GATHER>
+int launch_odd_narrow(const RowsArgs &a, int codebooks, int need, hipStream_t stream)
 {
-    if (row_bytes < 512) return 1;
-    // a row is staged from the 16-byte boundary at or before its start: row n begins (a0 + n s4) mod 16
+    if (codebooks <= 16 && need <= 1024) return launch_rows<16, 1, 4, DT, true, GATHER, true, true>(a, stream);
+    if (codebooks <= 32 && need <= 1024) return launch_rows<32, 1, 4, DT, true, GATHER, true, true>(a, stream);
+    if (codebooks <= 32 && need <= 2048) return launch_rows<32, 2, 4, DT, true, GATHER, true, true>(a, stream);
+    if (codebooks <= 64 && need <= 1024) return launch_rows<64, 1, 2, DT, true, GATHER, true, true>(a, stream);
+    if (codebooks <= 64 && need <= 2048) return launch_rows<64, 2, 2, DT, true, GATHER, true, true>(a, stream);
+    if (codebooks <= 64 && need <= 4096) return launch_rows<64, 4, 2, DT, true, GATHER, true, true>(a, stream);
+    return 1;
+}
+
+template <bool GATHER>
+int launch_odd_typed(const RowsArgs &a, int dtype, int codebooks, int need, hipStream_t stream)
+{
+    switch (dtype) {
+    case MADDNESS_F16: return launch_odd_narrow<kF16, GATHER>(a, codebooks, need, stream);
+    case MADDNESS_BF16: return launch_odd_narrow<kBF16, GATHER>(a, codebooks, need, stream);
+    default: return launch_odd_narrow<kU8, GATHER>(a, codebooks, need, stream);
+    }
+}
+
+template <bool SCAN>
+int launch_odd(const RowsArgs &a, int codebooks, const MatrixA &A, hipStream_t stream)
+{
+    const int es = A.elem_bytes(), row_bytes = a.D * es;
+    if constexpr (SCAN) {
+        // Where the general kernels are as fast, having few table entries to add for the time a row takes here: fp32 rows
+        // below 512 bytes and tables they read in one piece (C = 15, M = 100 43 us there and 44 here for 2^17 rows; C = 30,
+        // M = 300, 140 KiB, 189 and 89); narrow ones with next to none (binary16, C = 4, M = 10, rows of 64 bytes 39 and
+        // 72 for 2^19; bytes, C = 8, M = 34 172 and 102); and few rows of those (the same 10 and 14 for 16384, 17.5 and 16.7
+        // for 32768; bfloat16, C = 24, M = 200, 75 KiB, 13 and 14 for 1410, but M = 250, 94 KiB, 30 and 15).
+        const int64_t entries = (int64_t)codebooks * a.M;
+        if (A.dtype == MADDNESS_F32 && row_bytes < 512 && 16 * entries <= 64 * 1024) return 1;
+        if (A.dtype != MADDNESS_F32 && row_bytes < 512 && entries < 256) return 1;
+        if (A.dtype != MADDNESS_F32 && 16 * entries <= 80 * 1024 && a.N < 32768) return 1;
+    } else if (row_bytes < 512 || A.dtype != MADDNESS_F32) {
+        return 1;
+    }
+    if (!aligned_to(a.A, es)) return 1;
+    // a row is staged from the 16-byte boundary at or before its start: row n begins (a0 + n s) mod 16
     // bytes after one
-    const unsigned a0 = (unsigned)reinterpret_cast<uintptr_t>(a.A) & 15u, s4 = (unsigned)(a.lda * 4) & 15u;
+    const unsigned a0 = (unsigned)reinterpret_cast<uintptr_t>(a.A) & 15u, s = (unsigned)(a.lda * es) & 15u;
     unsigned max_shift = 0;
-    for (unsigned n = 0; n < 4; ++n) max_shift = std::max(max_shift, (a0 + n * s4) & 15u);
+    for (unsigned n = 0; n < 16; ++n) max_shift = std::max(max_shift, (a0 + n * s) & 15u);
     const int need = row_bytes + (int)max_shift;
     if constexpr (SCAN) {
         // more than two blocks of columns: whole rows through LDS; else straight from the registers
         const int span = codebooks <= 32 ? 64 : 32;
-        if ((a.M + span - 1) / span > 2) return launch_odd_sized<true, true>(a, codebooks, need, stream);
+        const bool gather = (a.M + span - 1) / span > 2;
+        if (A.dtype != MADDNESS_F32)
+            return gather ? launch_odd_typed<true>(a, A.dtype, codebooks, need, stream)
+                          : launch_odd_typed<false>(a, A.dtype, codebooks, need, stream);
+        if (gather) return launch_odd_sized<true, true>(a, codebooks, need, stream);
     }
     return launch_odd_sized<SCAN, false>(a, codebooks, need, stream);
 }
@@ -634,7 +675,8 @@ int launch_row_major(const RowsArgs &a, int C, int D, const MatrixA &A, hipStrea
         return 1;
     }
     if constexpr (!SCAN) return 1;
-    if (row_bytes > 4096 || C == 16) return 1;
+    if (row_bytes > 4096) return 1;
+    if (C == 16) return launch_odd<SCAN>(a, C, A, stream);
     if (C == 32)
         return row_bytes <= 1024   ? launch_rows_typed<32, 1, 4>(a, A.dtype, stream)
                : row_bytes <= 2048 ? launch_rows_typed<32, 2, 4>(a, A.dtype, stream)
@@ -683,8 +725,8 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
     }
     if (N < matrix_cores_min_rows(p.C, M, regular && (p.C == 16 || p.C == 32))) return 1;
     if (!regular) {
-        if (!A.plain() || p.C > 64) return 1;
-        return launch_odd<true>(a, p.C, 4 * D, stream);
+        if (A.col_major || p.C > 64) return 1;
+        return launch_odd<true>(a, p.C, A, stream);
     }
     if (A.col_major) {
         if (C == 16) return 1;
@@ -726,7 +768,7 @@ int launch_encode_phased(const maddness_params &p, const MatrixA &A, int64_t N, 
         const int rc = launch_row_major<false>(a, C, p.D, A, stream);
         if (rc != 1) return rc;
     }
-    return launch_odd<false>(a, p.C, 4 * p.D, stream);
+    return launch_odd<false>(a, p.C, A, stream);
 }
 
 }  // namespace maddness

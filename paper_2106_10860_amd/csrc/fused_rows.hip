@@ -427,9 +427,8 @@ int launch_fused_rows(const maddness_params &p, const MatrixA &A, int64_t N, int
 {
     const int C = p.C, D = p.D;
     if (!rows_ok(D, A) || (codes && !aligned_to(codes, 4))) {
-        // rows that are not whole aligned 16-byte pieces: many fp32 rows go to the phased kernel's form
-        // for any shape
-        if (A.plain() && !averaged && !vector_scan_only())
+        // rows that are not whole aligned 16-byte pieces: many go to the phased kernel's form for any shape
+        if (!A.col_major && !averaged && !vector_scan_only())
             return launch_fused_mfma(p, A, N, M, luts, scale, offset, out, ldo, acc, codes, stream);
         return 1;
     }

@@ -131,8 +131,8 @@ __device__ __forceinline__ void store_row(const RowsArgs &a, int64_t row, int la
 // the matrix read as zeros.
 // STORE: also to a.codes_out when that is set (else the caller copies them from LDS).
 // PAD: codebooks a.codebooks .. C - 1 do not exist; their codes are 0 (the caller gives their lanes any tree).
-// UNALIGNED (fp32): rows start on any 4-byte boundary and end anywhere; the aligned pieces that cover
-// a row are read (DV KiB of staging must hold the row plus 12 bytes).
+// UNALIGNED: rows start on any element and end anywhere; the aligned pieces that cover a row are read
+// (DV KiB of staging must hold the row and what precedes it in its first piece).
 template <int C, int DV, int DT = kF32, bool STORE = true, bool PAD = false, bool UNALIGNED = false, int PF = 1>
 __device__ __forceinline__ void encode_rows_to_lds(const RowsArgs &a, const Tree &tr, unsigned char *stage,
                                                    unsigned char *my_codes, int64_t row0, int n_rows, int lane,
@@ -147,9 +147,8 @@ __device__ __forceinline__ void encode_rows_to_lds(const RowsArgs &a, const Tree
     const unsigned char *st = stage + rsub * ROWB;
     const unsigned char *A_bytes = static_cast<const unsigned char *>(a.A);
     const int row_bytes = a.D * ES;
-    // UNALIGNED: row n begins (a0 + n s4) mod 16 bytes after a 16-byte boundary; s4 is a multiple of 4,
-    // so that only n mod 4 matters
-    const unsigned a0 = (unsigned)reinterpret_cast<uintptr_t>(A_bytes) & 15u, s4 = (unsigned)(a.lda * ES) & 15u;
+    // UNALIGNED: row n begins (a0 + n step) mod 16 bytes after a 16-byte boundary
+    const unsigned a0 = (unsigned)reinterpret_cast<uintptr_t>(A_bytes) & 15u, step = (unsigned)(a.lda * ES) & 15u;
     f4 pre[PF][RPI][DV];
     auto issue_loads = [&](int gi, int slot) INLINE_LAMBDA {
 #pragma unroll
@@ -163,10 +162,10 @@ __device__ __forceinline__ void encode_rows_to_lds(const RowsArgs &a, const Tree
                     if (row < a.N && 16 * col4 < row_bytes)
                         v = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(A_bytes + row * a.lda * ES) + col4);
                 } else {
-                    // the aligned 16-byte pieces that cover the row: the first may begin up to 12 bytes before
-                    // it and the last end up to 12 bytes after it, inside the 16 bytes that hold the row's
+                    // the aligned 16-byte pieces that cover the row: the first may begin up to 15 bytes before
+                    // it and the last end up to 15 bytes after it, inside the 16 bytes that hold the row's
                     // first / last element (such a piece never leaves the page its valid bytes are on)
-                    const int shift = (int)((a0 + ((unsigned)row & 3u) * s4) & 15u);
+                    const int shift = (int)((a0 + (unsigned)row * step) & 15u);
                     if (row < a.N && 16 * col4 < shift + row_bytes)
                         v = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(A_bytes + row * a.lda * ES - shift) + col4);
                 }
@@ -195,7 +194,7 @@ __device__ __forceinline__ void encode_rows_to_lds(const RowsArgs &a, const Tree
             if constexpr (UNALIGNED) {
                 // the row begins `shift` bytes into its first piece
                 const int64_t row = row0 + (gi * RPI + rsub) * row_stride;
-                rowp = st + ((a0 + ((unsigned)row & 3u) * s4) & 15u);
+                rowp = st + ((a0 + (unsigned)row * step) & 15u);
             }
             const float x0 = widen_at<DT>(rowp, tr.j0), x1 = widen_at<DT>(rowp, tr.j1), x2 = widen_at<DT>(rowp, tr.j2),
                         x3 = widen_at<DT>(rowp, tr.j3);

@@ -96,6 +96,36 @@ def test_by_columns_few_rows(mad, shape, dtype):
     assert (out.cpu().numpy() == want_out).all()
 
 
+# (N, D, M, C, elements between rows, elements before the first): C of 16 and what is padded to 16, 32 and 64; rows of whole
+# pieces and rows that start on any element; results by lane and through LDS; full staging
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "u8"])
+@pytest.mark.parametrize("shape", [(32768, 256, 64, 16, 0, 0), (32771, 250, 33, 15, 3, 1), (1411, 360, 512, 30, 0, 0),
+                                   (999, 505, 257, 31, 7, 5), (4097, 768, 250, 48, 0, 0), (32769, 97, 40, 7, 0, 3),
+                                   (777, 1009, 193, 57, 0, 7), (70, 1993, 130, 63, 2, 0)],
+                         ids=lambda s: "N%d_D%d_M%d_C%d_p%d_o%d" % s)
+def test_narrow_rows_of_any_shape(mad, shape, dtype):
+    import torch
+    N, D, M, C, pad, before = shape
+    print("case", shape, dtype, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D, N, D, M, C)
+    kind = {"f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    full = torch.full((before + N * (D + pad),), 1, dtype=kind, device="cuda")
+    A_d = full[before:].view(N, D + pad)[:, :D]
+    A_d.copy_((dev(A) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind))
+    values = A_d.float().cpu().numpy().copy()
+    want_out, want_acc, want_codes = oracle.encode_scan(values, sd, th, luts, scale, offset)
+    params = mad.Params(dev(sd), dev(th))
+    acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+    codes = torch.zeros((N, (C + 1) // 2), dtype=torch.uint8, device="cuda")
+    out = mad.maddness_encode_scan_typed(params, A_d, dev(luts), dev(scale), dev(offset), acc=acc, codes=codes)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("fused_mfma_kernel, A by rows"), kernel
+    assert (codes.cpu().numpy() == want_codes).all()
+    assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+    assert (out.cpu().numpy() == want_out).all()
+
+
 # (D, M, C): one tile and parts of tiles of the inner dimension (64), the columns (32 a workgroup, 64 a workgroup of the
 # quantisation) and the codebooks (1, 2 or 4 a workgroup, whichever leaves one for every compute unit; 8 minima at a time)
 @pytest.mark.parametrize("shape", [(1, 1, 1), (63, 31, 3), (64, 32, 4), (65, 33, 5), (130, 65, 17), (200, 520, 33), (129, 520, 63),
