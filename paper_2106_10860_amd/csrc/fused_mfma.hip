@@ -14,8 +14,8 @@
 //       exceeds 8 SPAN columns the phase is repeated with the next 8 SPAN columns;
 //       if it has at most 4 SPAN, several wavefronts hold the same columns and
 //       share out the rows.
-//       The tables are re-read from L2 at the start of every S phase (a few hundred
-//       bytes per row of the block), which leaves the registers to E meanwhile.
+//       The tables are re-read from L2 at the start of every S phase, by the whole
+//       workgroup through LDS, which leaves the registers to E meanwhile.
 // E is bound by HBM reads, S by HBM writes; they do not overlap within a
 // workgroup, and the larger a region, the longer the chip as a whole only reads or
 // only writes, which HBM serves faster than a mixture (N = 2^20, D = 512, M = 256,
@@ -26,9 +26,9 @@
 // (6.0 ms; 7.3 ms when started half a period apart), and 4 encoding + 4 scanning
 // wavefronts with double-buffered codes (6.2 ms, whatever the encoders' prefetch
 // depth; only the by-columns input gained, 0.295 against 0.324 ms at N = 2^20,
-// M = 256).  Used for many rows with C = 16, 32 or 64: the metric's shape, tables larger
-// than LDS, narrow element types, A stored by columns; and, as its E phase alone, to
-// encode fp32 rows.
+// M = 256).  Used for many rows of any type by up to 64 codebooks, for any number of them
+// where the tables are larger than the other kernels take at once, for A stored by columns;
+// and, as its E phase alone, to encode fp32 rows.
 #include <algorithm>
 
 #include "cols_common.h"

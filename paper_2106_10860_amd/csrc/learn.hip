@@ -10,10 +10,10 @@
 // on the launch shape.  The parallelism is ACROSS the independent pieces: codebooks, candidate
 // columns, buckets and columns.  This file is compiled without floating-point contraction.
 //
-// The serial parts are chains of a few instructions per row on a few lanes, and a wavefront issues
-// one vector instruction in four cycles whatever the number of its active lanes: each chain is kept
-// to the instructions its sum needs, reads operands that all threads have laid side by side in LDS,
-// and leaves products, divisions, comparisons and counting to all threads or to wavefront ballots.
+// The serial parts are sums in a given order: chains of additions at the adder's latency over
+// operands that other wavefronts have laid side by side in LDS (or no chain, where a sum's bits
+// allow any order); products, divisions, comparisons and counting are left to all threads or to
+// wavefront ballots.
 //
 // gather_columns_kernel  the columns of every codebook side by side, rows aligned
 // Per level t = 1..4 of all C trees at once:
@@ -30,8 +30,8 @@
 //   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
 //                        candidates
 //   apply_kernel         apply_split: the next level's buckets
-// Prototypes: cooccurrence_kernel (G^T G), count_codes_kernel, list_codes_kernel and gta_kernel (G^T A~), cholesky_panel_kernel,
-// factor by rows, substitution_kernel; or means_kernel.
+// Prototypes: cooccurrence_kernel (G^T G), count_codes_kernel, list_codes_kernel and gta_kernel (G^T A~),
+// cholesky_panel_kernel, transpose_factor_kernel (the factor by rows), substitution_kernel; or means_kernel.
 #include "common.h"
 
 namespace maddness {
