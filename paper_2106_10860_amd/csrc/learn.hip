@@ -24,7 +24,7 @@
 //   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column (bitonic sort of
 //                        (value, row) keys: equal values stay in row order, as a stable sort
 //                        of a bucket's rows leaves them)
-//   split_chains_kernel, judge_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
+//   split_chains_kernel, split_losses_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
 //                        running sums at every 32nd row in both directions, then the loss of
 //                        every split, a wavefront per 256 rows
 //   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
@@ -62,7 +62,7 @@ struct LearnArgs {
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
     uint64_t *keys;       // [C][4][Npad] sorted (value, row) keys
-    int64_t tile_slots;   // tiles of kJudgeRows sorted rows of all buckets of a level, at most
+    int64_t tile_slots;   // tiles of kSplitRows sorted rows of all buckets of a level, at most
     double *sums;         // [C][4][2][tile_slots][2][dmax] Algorithm 4's running sums before every tile, up and down
     int64_t group_slots;  // groups of kGroupTiles tiles of all buckets of a level, at most
     double *group_loss;   // [C][4][group_slots] loss of the group's best split
@@ -629,16 +629,16 @@ __global__ __launch_bounds__(256) void sort_exchange_kernel(const LearnArgs a, i
 // Algorithm 3 in two parts.  Algorithm 4's running sums are the one serial thing in it, and a serial sum costs a
 // few cycles per row whatever else is done with it, so split_chains_kernel does nothing but add: a chain per
 // (candidate, bucket, direction, column, which of the two sums) walks the bucket's rows in sorted order and leaves its
-// value at every kJudgeRows-th of them.  judge_kernel takes it up from there, tile by tile of kJudgeRows rows: it
+// value at every kSplitRows-th of them.  split_losses_kernel takes it up from there, tile by tile of kSplitRows rows: it
 // repeats the few additions in between (the same operations on the same operands), and does the products, divisions,
 // differences and comparisons of its rows, all tiles of all buckets at once.  (Measured, the four levels of
 // 20000 x 512 with 32 codebooks and of 260100 x 27 with 4: 0.67 + 0.45 and 2.36 + 0.42 ms for the two kernels; 4.8 and
 // 34.8 ms as one kernel that did all of it tile after tile.)
-constexpr int kJudgeRows = 32;
-constexpr int kGroupTiles = 8, kGroupRows = kGroupTiles * kJudgeRows;     // tiles that a wavefront of judge_kernel takes
+constexpr int kSplitRows = 32;
+constexpr int kGroupTiles = 8, kGroupRows = kGroupTiles * kSplitRows;     // tiles that a wavefront of split_losses_kernel takes
 
-// the first of the tile slots of a bucket (count rows beginning at `start` take up to count / kJudgeRows + 1 of them)
-__device__ __forceinline__ int64_t first_slot(int32_t start, int bucket) { return start / kJudgeRows + bucket; }
+// the first of the tile slots of a bucket (count rows beginning at `start` take up to count / kSplitRows + 1 of them)
+__device__ __forceinline__ int64_t first_slot(int32_t start, int bucket) { return start / kSplitRows + bucket; }
 __device__ __forceinline__ int64_t first_group(int32_t start, int bucket) { return start / kGroupRows + bucket; }
 
 // Both sums of up to NC columns to a workgroup, four chains to a wavefront.  Going down (direction 1)
@@ -653,9 +653,9 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
-    const int n_tiles = (count + kJudgeRows - 1) / kJudgeRows;
+    const int n_tiles = (count + kSplitRows - 1) / kSplitRows;
     if (n_tiles == 0) return;
-    constexpr int kTiles = kChainRows / kJudgeRows;
+    constexpr int kTiles = kChainRows / kSplitRows;
     const int n_steps = (n_tiles + kTiles - 1) / kTiles;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
     const int tid = threadIdx.x, cols = min(NC, d - col0);
@@ -668,7 +668,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     // the place in the sorted order of row i of step s (before the first or after the last: none)
     auto place = [&](int s, int i) __attribute__((always_inline)) {
         const int at = s * kChainRows + i;
-        return dir ? n_tiles * kJudgeRows - 1 - at : at;
+        return dir ? n_tiles * kSplitRows - 1 - at : at;
     };
     double acc = 0.0;
     stream_rows<NC, NC / 2>(
@@ -693,7 +693,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
         });
 }
 
-// A wavefront per kGroupTiles tiles of kJudgeRows sorted rows of a bucket, one tile after the other with the next one's
+// A wavefront per kGroupTiles tiles of kSplitRows sorted rows of a bucket, one tile after the other with the next one's
 // rows on their way: both running sums of every column and both directions from the values that split_chains_kernel
 // left at the tile's ends, a lane per (direction, sum, column); then Algorithm 4's term of every column, summed over the
 // columns in column order, a lane per (direction, row); then the loss of the split between every row and the next one
@@ -710,9 +710,9 @@ __device__ __forceinline__ bool better(double l2, int at2, double loss, int at)
 }
 
 template <int NC>
-__global__ __launch_bounds__(64) void judge_kernel(const LearnArgs a, int n_buckets)
+__global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int n_buckets)
 {
-    constexpr int T = kJudgeRows, kPitch = T + 4, kSumPitch = T + 1, kChains = 4 * NC;
+    constexpr int T = kSplitRows, kPitch = T + 4, kSumPitch = T + 1, kChains = 4 * NC;
     constexpr int kPieces = NC / 4, kRows = 64 / kPieces, kPer = T / kRows;
     __shared__ __align__(16) double sums[kChains][kSumPitch];
     __shared__ __align__(16) float xs[2][NC][kPitch];       // the tile's values, first to last and last to first
@@ -1488,7 +1488,7 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.cand = w.take<int32_t>(C * kCand);
     a.n_cand = w.take<int32_t>(C);
     a.keys = w.take<uint64_t>(C * kCand * a.Npad);
-    a.tile_slots = a.N / kJudgeRows + kSplitBuckets + 1;
+    a.tile_slots = a.N / kSplitRows + kSplitBuckets + 1;
     a.sums = w.take<double>(C * kCand * 2 * a.tile_slots * 2 * a.dmax);
     a.group_slots = a.N / kGroupRows + kSplitBuckets + 1;
     a.group_loss = w.take<double>(C * kCand * a.group_slots);
@@ -1542,7 +1542,7 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
     a.split_dims = split_dims; a.thresholds = thresholds; a.codes = codes;
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
-    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_kernel + judge_kernel + choose_kernel + apply_kernel", nullptr);
+    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
 
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
@@ -1588,17 +1588,17 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
         // (columns eight or sixteen at a time)
         const int groups = narrow ? 1 : a.pitch / 16;
         const dim3 chain_groups(C, 8 * groups, n_buckets);
-        const dim3 judges((unsigned)(a.group_slots * C), kCand);
+        const dim3 grid_losses((unsigned)(a.group_slots * C), kCand);
         if (narrow) {
             hipLaunchKernelGGL(split_chains_kernel<8>, chain_groups, dim3(32 * 8 + kChainHelpers), stream_lds_bytes<8>(), stream, a);
             LAUNCH_OK("launch split_chains_kernel");
-            hipLaunchKernelGGL(judge_kernel<8>, judges, dim3(64), 0, stream, a, n_buckets);
+            hipLaunchKernelGGL(split_losses_kernel<8>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         } else {
             hipLaunchKernelGGL(split_chains_kernel<16>, chain_groups, dim3(32 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a);
             LAUNCH_OK("launch split_chains_kernel");
-            hipLaunchKernelGGL(judge_kernel<16>, judges, dim3(64), 0, stream, a, n_buckets);
+            hipLaunchKernelGGL(split_losses_kernel<16>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         }
-        LAUNCH_OK("launch judge_kernel");
+        LAUNCH_OK("launch split_losses_kernel");
         hipLaunchKernelGGL(choose_kernel, dim3(C), dim3(512), 0, stream, a, level, n_buckets);
         LAUNCH_OK("launch choose_kernel");
         hipLaunchKernelGGL(apply_kernel, dim3((unsigned)((N + 255) / 256), C), dim3(256), 0, stream, a, level, n_buckets);
