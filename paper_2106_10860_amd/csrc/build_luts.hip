@@ -108,15 +108,18 @@ __global__ __launch_bounds__(GEMM_THREADS) void lut_gemm_kernel(const float *__r
     __syncthreads();
     for (int tile = wave; tile < TILES; tile += 2 * KSPLIT) {
         const int c = c0 + tile / 2, m = m0 + 16 * (tile % 2) + i;
-        double lo = 0.0, hi = 0.0;
+        // (an entry that is not a number counts neither way, unless it is the table's first: then minimum and range are
+        // none either, as a walk over the sixteen that begins with the first has it)
+        double lo = __builtin_inf(), hi = -__builtin_inf(), first = 0.0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             double s = part[0][tile][e][lane];
 #pragma unroll
             for (int q = 1; q < KSPLIT; ++q) s += part[q][tile][e][lane];
             if (c < C && m < M) T[((size_t)c * 16 + 4 * e + kk) * M + m] = s;
-            lo = e == 0 || s < lo ? s : lo;
-            hi = e == 0 || s > hi ? s : hi;
+            if (e == 0) first = s;
+            lo = s < lo ? s : lo;
+            hi = s > hi ? s : hi;
         }
 #pragma unroll
         for (int off = 16; off < 64; off <<= 1) {
@@ -125,6 +128,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void lut_gemm_kernel(const float *__r
             hi = hi2 > hi ? hi2 : hi;
         }
         if (kk == 0 && c < C && m < M) {
+            lo = first == first ? lo : first;
             delta[(size_t)c * M + m] = lo;
             range[(size_t)c * M + m] = hi - lo;
         }

@@ -146,6 +146,32 @@ def test_table_build_at_tile_edges(mad, shape):
     compare_luts(luts.cpu().numpy(), scale.cpu().numpy(), offset.cpu().numpy(), ref, P, B[:, :M])
 
 
+@pytest.mark.parametrize("kind", ["nan", "inf", "mixed"])
+def test_table_build_on_prototypes_that_are_not_numbers(mad, kind):
+    """One entry after the other of a table is not a number or infinite: the finite ones keep minimum, range and bytes,
+    and only a table whose first entry is not a number has none.  Whole values, so that the tables are exact."""
+    import torch
+    rng = np.random.default_rng(len(kind))
+    C, D, M = 19, 5, 33
+    P = rng.integers(-9, 10, size=(C, 16, D)).astype(np.float32)
+    B = rng.integers(1, 5, size=(D, M)).astype(np.float32)
+    for c in range(16):
+        P[c, c, c % D] = {"nan": np.nan, "inf": np.inf, "mixed": np.nan if c % 2 else -np.inf}[kind]
+    P[16, 1:] = np.nan
+    P[17, [2, 7, 9]] = [[np.nan], [np.inf], [-np.inf]]
+    P[18] = np.inf if kind == "inf" else np.nan
+    # (a codebook at a time too: a column's scale is that of its widest table)
+    for first, last in [(0, C)] + [(c, c + 1) for c in range(C)]:
+        Pc = np.ascontiguousarray(P[first:last])
+        want_luts, want_scale, want_offset, _, _ = oracle.quantize_luts(oracle.build_luts_f64(Pc, B))
+        sd, th = np.zeros((last - first, 4), np.int32), np.zeros((last - first, 16), np.float32)
+        luts, scale, offset = mad.maddness_build_luts(mad.Params(dev(sd), dev(th), dev(Pc)), dev(B))
+        torch.cuda.synchronize()
+        assert (scale.cpu().numpy() == want_scale).all(), (first, last)
+        assert np.array_equal(offset.cpu().numpy(), want_offset, equal_nan=True), (first, last)
+        assert (luts.cpu().numpy() == want_luts).all(), (first, last)
+
+
 @pytest.mark.parametrize("C", [1, 4, 36, 37, 73, 110])
 def test_ridge_solve_where_its_launch_changes(mad, C):
     """One and four panels of 16, and either side of the sizes at which a helper takes more entries of a row (576,
