@@ -695,6 +695,7 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
 {
     const int D = p.D;
     const int es = A.elem_bytes();
+    if (!A.col_major && (int64_t)D * es > kMaxRowBytes) return 1;
     RowsArgs a{};
     a.A = A.data; a.lda = A.ld; a.D = D; a.N = N;
     a.split_dims = p.split_dims; a.thresholds = p.thresholds;
@@ -757,7 +758,7 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
 // whole chip.
 int launch_encode_phased(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes, hipStream_t stream)
 {
-    if (p.C > 64 || !A.plain() || N < 16384) return 1;
+    if (p.C > 64 || !A.plain() || N < 16384 || (int64_t)p.D * A.elem_bytes() > kMaxRowBytes) return 1;
     const int C = p.C <= 16 ? 16 : (p.C <= 32 ? 32 : 64);   // the kernel's C; the rest is padding
     RowsArgs a{};
     a.A = A.data; a.lda = A.ld; a.D = p.D; a.N = N;

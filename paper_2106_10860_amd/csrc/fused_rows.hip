@@ -412,7 +412,7 @@ int encode_narrow(const RowsArgs &a, int C, int dtype, bool one_piece, hipStream
 bool rows_ok(int D, const MatrixA &A)
 {
     const int es = A.elem_bytes();
-    return !A.col_major && (D * es) % 16 == 0 && (A.ld * es) % 16 == 0 && aligned_to(A.data, 16);
+    return !A.col_major && (int64_t)D * es <= kMaxRowBytes && (D * es) % 16 == 0 && (A.ld * es) % 16 == 0 && aligned_to(A.data, 16);
 }
 
 }  // namespace

@@ -216,6 +216,9 @@ __device__ __forceinline__ void encode_rows_to_lds(const RowsArgs &a, const Tree
 }
 
 // Host-side shape checks shared by the launchers.
+// No kernel that takes whole rows takes longer ones.  Checked in 64 bits before anything else: what follows counts a
+// row's bytes in an int.
+constexpr int64_t kMaxRowBytes = 8192;
 inline bool aligned_to(const void *p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; }
 
 inline bool tables_ok(int C, int M, const uint8_t *luts, const float *scale, const float *offset,

@@ -126,6 +126,30 @@ def test_narrow_rows_of_any_shape(mad, shape, dtype):
     assert (out.cpu().numpy() == want_out).all()
 
 
+@pytest.mark.parametrize("dtype,D,C,M", [("f32", (1 << 29) + 4, 30, 300), ("f32", (1 << 29) + 4, 32, 260),
+                                         ("bf16", (1 << 30) + 16, 32, 260), ("bf16", (1 << 30) + 16, 32, 128),
+                                         ("u8", (1 << 31) - 9, 24, 400)])
+def test_rows_of_more_than_2_gib(mad, dtype, D, C, M):
+    """The bytes of such a row do not fit 32 bits (or end just below): no kernel may take it for a short one."""
+    import torch
+    print("case", dtype, D, C, M, flush=True)
+    rng = np.random.default_rng(C + M)
+    used = np.unique(np.concatenate([[0, D - 1], rng.integers(0, D, size=60)]))
+    values = rng.integers(0, 200, size=(1, len(used))).astype(np.float32)
+    sd, th = random_trees(rng, values, C)
+    luts = rng.integers(0, 256, size=(C, 16, M)).astype(np.uint8)
+    scale, offset = np.ones(M, np.float32), np.zeros(M, np.float32)
+    want_out, _, want_codes = oracle.encode_scan(values, sd, th, luts, scale, offset)
+    A = torch.zeros((1, D), dtype={"f32": torch.float32, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype], device="cuda")
+    A[0, dev(used)] = dev(values)[0].to(A.dtype)
+    codes = torch.zeros((1, (C + 1) // 2), dtype=torch.uint8, device="cuda")
+    out = mad.maddness_encode_scan_typed(mad.Params(dev(used[sd].astype(np.int32)), dev(th)), A, dev(luts), dev(scale), dev(offset),
+                                         codes=codes)
+    torch.cuda.synchronize()
+    assert (codes.cpu().numpy() == want_codes).all()
+    assert (out.cpu().numpy() == want_out).all()
+
+
 # (D, M, C): one tile and parts of tiles of the inner dimension (64), the columns (32 a workgroup, 64 a workgroup of the
 # quantisation) and the codebooks (1, 2 or 4 a workgroup, whichever leaves one for every compute unit; 8 minima at a time)
 @pytest.mark.parametrize("shape", [(1, 1, 1), (63, 31, 3), (64, 32, 4), (65, 33, 5), (130, 65, 17), (200, 520, 33), (129, 520, 63),
