@@ -96,8 +96,9 @@ inline int64_t matrix_cores_min_rows(int C, int M, bool in_lds)
 // code at a time, the same tables cost 8 to 16 times the requests, of which all compute units sent the same at the same
 // time: D = 1024, M = 512, C = 64, N = 65536 took 223 us that way, 82 so (bfloat16 rows: 202 and 65), the scan alone 109
 // and 38; D = 512, M = 256, C = 32, N = 2^18 145 and 139.
-// Entries of columns >= M and (PAD) of codebooks >= `codebooks` are zeros, which add nothing to a sum together with the
-// code 0; entries need no alignment.  Every wavefront takes part (barriers); the stage is free again after one more.
+// Entries of (PAD) codebooks >= `codebooks` are zeros, which add nothing to a sum together with the code 0; those of columns
+// >= M are anything (their sums are never stored); entries need no alignment.  Every wavefront takes part (barriers); the
+// stage is free again after one more.
 constexpr int kTableStage = 4096;
 
 template <int KG, int NT, int THREADS, bool PAD>
@@ -109,14 +110,16 @@ __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *lut
     static_assert(CHUNK * P * 16 == kTableStage * (THREADS / 64) && CHUNK % 4 == 0 && (4 * KG) % CHUNK == 0, "stage of the tables");
     v4i *entries = reinterpret_cast<v4i *>(stage);          // [CHUNK][P], a block's columns ordered by (t, j)
     const int quad = tid % QUADS, cb = tid / QUADS, col = col0 + 4 * quad;
-    // the columns' last four bytes where fewer than four are left: moved down when they are used (tables of less
-    // than four columns are read byte by byte)
-    const bool mine = 4 * quad < cols && col < M, whole = mine && M >= 4;
-    const int back = col + 4 > M ? col + 4 - M : 0;
+    // the columns' last four bytes where fewer than four are left: moved down when they are used.  In tables of less than
+    // four columns the four bytes run on into the next code's, which stand for columns that do not exist; the last
+    // codebook of such tables (without PAD, all of them) is read byte by byte
+    const bool mine = 4 * quad < cols && col < M;
+    const int back = M >= 4 && col + 4 > M ? col + 4 - M : 0;
+    const int whole_end = M >= 4 ? codebooks : codebooks - 1;
+    auto is_whole = [&](int n) INLINE_LAMBDA { return mine && (PAD ? CHUNK * n + cb < whole_end : M >= 4); };
     uint32_t raw[AHEAD][16];
     auto fetch = [&](int n, uint32_t(&w)[16]) INLINE_LAMBDA {
-        const bool there = !PAD || CHUNK * n + cb < codebooks;
-        const bool read = whole && there;
+        const bool read = is_whole(n);
         // (a thread with nothing to read reads the first entries again and again)
         const uint8_t *src = read ? luts + (size_t)(16 * (CHUNK * n + cb)) * M + (col - back) : luts;
         const size_t step = read ? (size_t)M : 0;
@@ -134,11 +137,11 @@ __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *lut
     for (int n = 0; n < CHUNKS; ++n) {
         uint32_t(&w)[16] = raw[n % AHEAD];
         // (decided here and not at the load, which the compiler would make a branch of its own, waited for)
-        const bool there = !PAD || CHUNK * n + cb < codebooks;
-        if (!whole || !there) {
+        const bool whole = is_whole(n);
+        if (!whole) {
 #pragma unroll
             for (int b = 0; b < 16; ++b) w[b] = 0;
-            if (mine && there) {
+            if (mine && (!PAD || CHUNK * n + cb < codebooks)) {
                 const uint8_t *src = luts + (size_t)(16 * (CHUNK * n + cb)) * M + col;
                 for (int t = 0; t < M - col; ++t)
 #pragma unroll

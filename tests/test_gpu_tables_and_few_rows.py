@@ -37,11 +37,12 @@ def problem(seed, N, D, M, C):
 
 # (N, D, M, C, bytes the tables start after a 16-byte boundary): tables of more than 64 KiB take the matrix cores from
 # the first row on; one row, whole and broken units of 8 and groups of 16, one to three columns after the last four,
-# padding codebooks, several passes of columns
+# less than four columns in all, padding codebooks, several passes of columns
 FEW = [
     (1, 256, 512, 64, 0), (7, 256, 260, 64, 0), (17, 1024, 1032, 32, 0), (33, 128, 1001, 16, 0), (9, 300, 333, 24, 0),
     (65, 300, 342, 24, 1), (255, 512, 255, 30, 3), (300, 512, 1022, 32, 2), (40, 200, 97, 50, 1), (129, 160, 128, 40, 0),
-    (16390, 200, 3, 20, 1), (16390, 200, 1, 33, 0),
+    (16390, 200, 3, 20, 1), (16390, 200, 1, 33, 0), (16385, 256, 2, 64, 0), (16390, 200, 2, 40, 2), (16387, 130, 1, 16, 3),
+    (16384, 300, 3, 48, 1), (16384, 140, 2, 5, 0),
 ]
 
 
