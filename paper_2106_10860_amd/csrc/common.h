@@ -73,6 +73,8 @@ int launch_scan(const maddness_params *p, const MatrixA *A, const uint8_t *codes
                 int32_t C, int32_t M, int64_t N, const uint8_t *luts, const float *scale,
                 const float *offset, float *out, int64_t ldo, uint16_t *acc, uint8_t *codes_out,
                 bool averaged, hipStream_t stream);
+// Whether that kernel holds the tables in LDS at once (else it walks tiles of their columns, for every block of rows).
+bool scan_in_one_piece(int32_t C, int32_t M, bool fused);
 
 // Row-streaming kernels specialised for C in {16, 32, 64}, rows of 16-byte pieces
 // and (fused, scan) one tile of <= 256 output columns whose tables fit in LDS, or

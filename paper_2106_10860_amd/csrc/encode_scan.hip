@@ -396,6 +396,19 @@ int launch_encode(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t
     return check_hip(hipGetLastError(), "launch encode_kernel");
 }
 
+// LDS bytes that launch_scan's plan has for tables
+static int table_budget(int32_t C, bool fused)
+{
+    const int offs_row_bytes = 4 * ((C + 3) & ~3);
+    const int min_offs_bytes = 8 * 1024 > 4 * offs_row_bytes ? 8 * 1024 : 4 * offs_row_bytes;
+    return device_info().lds_per_block - (fused ? C * 80 : 0) - min_offs_bytes - 64;
+}
+
+bool scan_in_one_piece(int32_t C, int32_t M, bool fused)
+{
+    return (int64_t)16 * C * (((int64_t)M + 3) & ~3) <= table_budget(C, fused);
+}
+
 int launch_scan(const maddness_params *p, const MatrixA *A, const uint8_t *codes_in,
                 int32_t C, int32_t M, int64_t N, const uint8_t *luts, const float *scale,
                 const float *offset, float *out, int64_t ldo, uint16_t *acc, uint8_t *codes_out,
@@ -418,8 +431,7 @@ int launch_scan(const maddness_params *p, const MatrixA *A, const uint8_t *codes
     // takes what it needs (all of M if that fits), the offsets get the rest.
     const int params_bytes = fused ? C * 80 : 0;
     const int offs_row_bytes = 4 * a.Cp;
-    const int min_offs_bytes = 8 * 1024 > 4 * offs_row_bytes ? 8 * 1024 : 4 * offs_row_bytes;
-    int lut_budget = dev.lds_per_block - params_bytes - min_offs_bytes - 64;
+    int lut_budget = table_budget(C, fused);
     // tables that do not fit are tiled over columns and the tile is re-loaded for
     // every block of rows: a smaller tile leaves room for the offsets of more rows
     if ((int64_t)16 * C * ((M + 3) & ~3) > lut_budget && lut_budget > MADDNESS_TILE_BYTES) lut_budget = MADDNESS_TILE_BYTES;

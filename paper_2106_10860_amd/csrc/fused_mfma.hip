@@ -592,23 +592,38 @@ int launch_odd_typed(const RowsArgs &a, int dtype, int codebooks, int need, hipS
     }
 }
 
+// The codebooks of the kernel that takes rows of `need` bytes in that form (0: none does).
+int odd_codebooks(int es, int codebooks, int need)
+{
+    const int per_row = es == 4 ? 1 : 2;      // (narrow rows: half the bytes)
+    return codebooks <= 16 && need * per_row <= 2048 ? 16 : codebooks <= 32 && need * per_row <= 4096 ? 32
+           : codebooks <= 64 && need * per_row <= 8192 ? 64 : 0;
+}
+
+// Few rows: the general kernel has to bring the tables into LDS, 11 to 20 us for what it holds at once (up to some
+// 148 KiB; 25 to 45 us where it reads single bytes), and this one tables of `kernel_codebooks` codebooks and whole passes
+// of columns into registers, 12 us for one pass and some 8 for each further one.  So it depends on how much of these is
+// padding.  Measured, general and here: words, fp32 rows, 1.5 times the tables 19 and 13 us, 2.5 times 15 and 13, 3.3 times
+// 11.7 and 12.5, 3.9 times 12.4 and 14.1, 5.3 times 18 and 30 (C = 12, M = 592, rows of 6000 bytes, which the kernel for 64
+// codebooks takes); narrow rows 3.1 times 15.3 and 14.5, 4.1 times 19 and 22, 6.2 times 19 and 29; up to 8 rows, for which
+// the general kernel takes 11 to 13 us, 2.0 times 12.7 and 12.3, 2.4 times 11.3 and 12.3; single bytes 5.2 times 28 and 21,
+// 7.8 times 24 and 23, 10.2 times 28 and 31.  64 codebooks with whole 16-byte pieces have tiles walked instead (30 to 100 us).
+bool few_rows_in_lds(const RowsArgs &a, int kernel_codebooks, int es, bool any_shape)
+{
+    if (a.N >= 16384 || !scan_in_one_piece(a.codebooks, a.M, true)) return false;
+    if (a.codebooks == 64 && (a.N > 8 || a.M % 16 == 0)) return false;
+    const int pass = kernel_codebooks == 64 ? 256 : 512;                      // columns
+    const int64_t padded = (int64_t)kernel_codebooks * ((a.M + pass - 1) / pass * pass), tables = (int64_t)a.codebooks * a.M;
+    const bool words = a.M % 4 == 0 && aligned_to(a.luts, 4);
+    const int tenths = !words ? 90 : a.N <= 8 ? 23 : es != 4 ? 35 : any_shape ? 30 : 33;
+    return 10 * padded > tenths * tables;
+}
+
 template <bool SCAN>
 int launch_odd(const RowsArgs &a, int codebooks, const MatrixA &A, hipStream_t stream)
 {
     const int es = A.elem_bytes(), row_bytes = a.D * es;
-    if constexpr (SCAN) {
-        // Where the general kernels are as fast, having few table entries to add for the time a row takes here: fp32 rows
-        // below 512 bytes and tables they read in one piece (C = 15, M = 100 43 us there and 44 here for 2^17 rows; C = 30,
-        // M = 300, 140 KiB, 189 and 89); narrow ones with next to none (binary16, C = 4, M = 10, rows of 64 bytes 39 and
-        // 72 for 2^19; bytes, C = 8, M = 34 172 and 102); and few rows of those (the same 10 and 14 for 16384, 17.5 and 16.7
-        // for 32768; bfloat16, C = 24, M = 200, 75 KiB, 13 and 14 for 1410, but M = 250, 94 KiB, 30 and 15).
-        const int64_t entries = (int64_t)codebooks * a.M;
-        if (A.dtype == MADDNESS_F32 && row_bytes < 512 && 16 * entries <= 64 * 1024) return 1;
-        if (A.dtype != MADDNESS_F32 && row_bytes < 512 && entries < 256) return 1;
-        if (A.dtype != MADDNESS_F32 && 16 * entries <= 80 * 1024 && a.N < 32768) return 1;
-    } else if (row_bytes < 512 || A.dtype != MADDNESS_F32) {
-        return 1;
-    }
+    if (!SCAN && (row_bytes < 512 || A.dtype != MADDNESS_F32)) return 1;
     if (!aligned_to(a.A, es)) return 1;
     // a row is staged from the 16-byte boundary at or before its start: row n begins (a0 + n s) mod 16
     // bytes after one
@@ -617,6 +632,18 @@ int launch_odd(const RowsArgs &a, int codebooks, const MatrixA &A, hipStream_t s
     for (unsigned n = 0; n < 16; ++n) max_shift = std::max(max_shift, (a0 + n * s) & 15u);
     const int need = row_bytes + (int)max_shift;
     if constexpr (SCAN) {
+        // Where the general kernels are as fast, having few table entries to add for the time a row takes here: fp32 rows
+        // below 512 bytes and tables they read in one piece (C = 15, M = 100 43 us there and 44 here for 2^17 rows; C = 30,
+        // M = 300, 140 KiB, 189 and 89); narrow ones with next to none (binary16, C = 4, M = 10, rows of 64 bytes 39 and
+        // 72 for 2^19; bytes, C = 8, M = 34 172 and 102); and few rows of those (the same 10 and 14 for 16384, 17.5 and 16.7
+        // for 32768; bfloat16, C = 24, M = 200, 75 KiB, 13 and 14 for 1410, but M = 250, 94 KiB, 30 and 15); and few rows as above.
+        const int64_t table_bytes = 16 * (int64_t)codebooks * a.M;
+        if (A.dtype == MADDNESS_F32 && row_bytes < 512 && table_bytes <= 64 * 1024) return 1;
+        const int kernel_codebooks = odd_codebooks(es, codebooks, need);
+        if (kernel_codebooks == 0) return 1;
+        if (A.dtype != MADDNESS_F32 && row_bytes < 512 && table_bytes < 16 * 256) return 1;
+        if (A.dtype != MADDNESS_F32 && table_bytes <= 80 * 1024 && a.N < 32768) return 1;
+        if (few_rows_in_lds(a, kernel_codebooks, es, true)) return 1;
         // more than two blocks of columns: whole rows through LDS; else straight from the registers
         const int span = codebooks <= 32 ? 64 : 32;
         const bool gather = (a.M + span - 1) / span > 2;
@@ -750,6 +777,7 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
         default: return launch_cols<64, 2, kU8>(a, stream);
         }
     }
+    if (few_rows_in_lds(a, C, es, false)) return 1;
     return launch_row_major<true>(a, C, D, A, stream);
 }
 

@@ -75,12 +75,14 @@ struct ScanOut {
     int M;
 };
 
-// From how many rows on the scan runs on the matrix cores.  Tables that fit in LDS whole are read there faster for few
-// rows (`in_lds`: 16 or 32 codebooks, up to 128 KiB; M = 256, C = 32: 11 us for 4096 rows of bfloat16, 16 for 16384
-// here), and the general kernels take up to 64 KiB at once.  Larger tables these and tiled_rows_kernel walk tile by
+// From how many rows on the scan runs on the matrix cores.  `in_lds`: 16 or 32 codebooks, up to 128 KiB: kernels that hold
+// the tables in LDS are faster for few rows where they take the shape (M = 256, C = 32: 11 us for 4096 rows of bfloat16, 16
+// for 16384 here), and the general kernel, which does the same for any shape (launch_scan), is taken elsewhere.  It is also
+// for tables of up to 64 KiB.  What neither holds at once it and tiled_rows_kernel walk tile by
 // tile, whatever the rows: M = 512, C = 64 in 46 us for one row, 239 for 500 or 8192 against 17, 19 and 25 here;
 // M = 1000, C = 32 in 54, 253 and 308 against 19, 20 and 27; the scan alone of M = 512, C = 64 in 17, 201 and 346
-// against 9, 10 and 12; M = 200, C = 24 (75 KiB) in 12, 13 and 16 against the same 12, 13 and 16.
+// against 9, 10 and 12.  In between it depends on the shape (few_rows_in_lds in the fused kernel); the scan alone is level or
+// better here (M = 200, C = 24, 75 KiB 12, 13 and 16 us for 1, 500 and 8192 rows either way; M = 92, C = 50 10.5 and 10.2).
 inline int64_t matrix_cores_min_rows(int C, int M, bool in_lds)
 {
     return 16 * (int64_t)C * M > (in_lds ? 128 : 64) * 1024 ? 1 : 16384;

@@ -151,6 +151,39 @@ def test_rows_of_more_than_2_gib(mad, dtype, D, C, M):
     assert (out.cpu().numpy() == want_out).all()
 
 
+# (N, D, M, C, dtype, by columns) -> the kernel that measured faster: either side of the rules of the dispatch
+FASTER = [
+    # tables between 64 KiB and what the general kernel holds at once: padding of codebooks and columns decides, and rows
+    ((1, 1500, 656, 12, "f32", False), "scan_kernel"), ((239, 1500, 592, 12, "f32", False), "scan_kernel"),
+    ((5257, 510, 300, 16, "f32", False), "fused_mfma"), ((120, 2001, 340, 16, "f32", False), "scan_kernel"),
+    ((2000, 300, 250, 30, "f32", False), "fused_mfma"), ((6, 333, 96, 50, "f32", False), "scan_kernel"),
+    ((125, 1000, 288, 20, "f32", False), "fused_mfma"), ((430, 1500, 780, 12, "bf16", False), "scan_kernel"),
+    ((378, 333, 224, 30, "bf16", False), "fused_mfma"), ((1, 256, 172, 40, "u8", False), "scan_kernel"),
+    ((16384, 1500, 592, 12, "f32", False), "fused_mfma"), ((1787, 512, 112, 40, "f32", False), "scan_kernel"),
+    ((1000, 256, 92, 64, "f32", False), "fused_mfma"), ((1, 256, 72, 64, "f32", False), "scan_kernel"),
+]
+
+
+@pytest.mark.parametrize("case", FASTER, ids=lambda c: "N%d_D%d_M%d_C%d_%s_%d" % c[0])
+def test_dispatch_either_side(mad, case):
+    import torch
+    (N, D, M, C, dtype, col_major), family = case
+    print("case", case, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D, N, D, M, C)
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    A_d = (dev(A.T if col_major else A) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind)
+    values = A_d.float().cpu().numpy()
+    want_out, _, want_codes = oracle.encode_scan(values.T.copy() if col_major else values, sd, th, luts, scale, offset)
+    codes = torch.zeros((N, (C + 1) // 2), dtype=torch.uint8, device="cuda")
+    out = mad.maddness_encode_scan_typed(mad.Params(dev(sd), dev(th)), A_d, dev(luts), dev(scale), dev(offset), col_major=col_major,
+                                         codes=codes)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith(family), kernel
+    assert (codes.cpu().numpy() == want_codes).all()
+    assert (out.cpu().numpy() == want_out).all()
+
+
 # (D, M, C): one tile and parts of tiles of the inner dimension (64), the columns (32 a workgroup, 64 a workgroup of the
 # quantisation) and the codebooks (1, 2 or 4 a workgroup, whichever leaves one for every compute unit; 8 minima at a time)
 @pytest.mark.parametrize("shape", [(1, 1, 1), (63, 31, 3), (64, 32, 4), (65, 33, 5), (130, 65, 17), (200, 520, 33), (129, 520, 63),
