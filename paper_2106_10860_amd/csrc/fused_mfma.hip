@@ -619,6 +619,38 @@ bool few_rows_in_lds(const RowsArgs &a, int kernel_codebooks, int es, bool any_s
     return 10 * padded > tenths * tables;
 }
 
+// Narrow rows of any shape, tables of up to 80 KiB: the general kernel reads the 4 C split values of a row and adds C table
+// entries for every column, this one reads whole rows and pays for the codebooks and columns it is built for.  Below 32768
+// rows the general kernel wins or is level (C = 24, M = 200, 75 KiB 13 and 14 us for 1410), and for short rows with next to no
+// entries (C = 22, M = 8, rows of 348 bytes, 124440 of them 24 and 33).  From there on both times are
+// estimated, in us, with costs fitted to 624 drawn shapes of 32768 to 300000 rows: this kernel's within a tenth, the general
+// one's, which depends on what of the rows the caches hold, within a third, which is why this kernel has to be faster by
+// more than a little; with 16 lanes to a row the general one is dearer than that.  Measured, general and here: C = 1, M = 13,
+// bytes, rows of 562, 152670 of them 16 and 35; C = 16, M = 20, rows of 85, 53325 12 and 20; C = 12, M = 216, rows of 160,
+// 252134 86 and 102; C = 2, M = 92, binary16, rows of 3116, 55727 24 and 45; C = 16, M = 64, rows of 512, 32768 25 and 15;
+// C = 16, M = 17, rows of 1536, 51491 48 and 25; C = 53, M = 42, bytes, rows of 426, 85913 67 and 33.
+bool narrow_rows_split_only(const RowsArgs &a, int kernel_codebooks, int es)
+{
+    if (a.N < 32768 || (a.D * es < 512 && a.codebooks * (int64_t)a.M < 256)) return true;
+    const int words = (a.M + 3) / 4, span = kernel_codebooks == 64 ? 32 : 64, blocks = (a.M + span - 1) / span;
+    int lanes = 1;                                         // of a wavefront to a row, as launch_scan has it
+    while (lanes < words && lanes < 64) lanes *= 2;
+    const int rows_at_once = std::max(64 / lanes, 4), row_passes = rows_at_once * lanes / 64 * ((words + lanes - 1) / lanes);
+    const int code_passes = (rows_at_once * ((a.codebooks + 1) / 2) + 63) / 64;
+    const double rows = 1e-3 * (double)a.N, C = a.codebooks, KC = kernel_codebooks, row_bytes = (double)a.D * es;
+    const bool odd = a.M % 4 != 0;
+    // a wavefront's turn: codes, table entries (reads that start a power of two apart meet in LDS banks), stores; then what
+    // grows with the rows' bytes
+    const double turn = 0.64 * code_passes + 0.008 * C * row_passes + (a.M == 4 * lanes ? 0.32 : 0.0) + (odd ? 0.29 : 0.0) +
+                        (lanes >= 16 ? 0.19 : 0.0);
+    const double general = 5.0 + 0.003 * C * a.M + (a.M <= 8 ? 0.26 * C : 0.0) + rows / rows_at_once * turn +
+                           rows * ((odd ? 0.95e-3 * a.M : 0.0) + 1.1e-4 * std::min(row_bytes, 256.0 * C) +
+                                   7e-3 * C * std::min(1.0, row_bytes / 2048));
+    const double here = 10.5 + (es == 1 ? 2.5 : 0.0) +
+                        rows * (0.056 + KC * (1.8e-3 + 3.1e-4 * blocks) + 8e-5 * row_bytes + 1.15e-3 * a.M);
+    return general < (lanes == 16 ? 0.75 : 1.15) * here;
+}
+
 template <bool SCAN>
 int launch_odd(const RowsArgs &a, int codebooks, const MatrixA &A, hipStream_t stream)
 {
@@ -634,15 +666,12 @@ int launch_odd(const RowsArgs &a, int codebooks, const MatrixA &A, hipStream_t s
     if constexpr (SCAN) {
         // Where the general kernels are as fast, having few table entries to add for the time a row takes here: fp32 rows
         // below 512 bytes and tables they read in one piece (C = 15, M = 100 43 us there and 44 here for 2^17 rows; C = 30,
-        // M = 300, 140 KiB, 189 and 89); narrow ones with next to none (binary16, C = 4, M = 10, rows of 64 bytes 39 and
-        // 72 for 2^19; bytes, C = 8, M = 34 172 and 102); and few rows of those (the same 10 and 14 for 16384, 17.5 and 16.7
-        // for 32768; bfloat16, C = 24, M = 200, 75 KiB, 13 and 14 for 1410, but M = 250, 94 KiB, 30 and 15); and few rows as above.
+        // M = 300, 140 KiB, 189 and 89); narrow rows and few rows as above.
         const int64_t table_bytes = 16 * (int64_t)codebooks * a.M;
         if (A.dtype == MADDNESS_F32 && row_bytes < 512 && table_bytes <= 64 * 1024) return 1;
         const int kernel_codebooks = odd_codebooks(es, codebooks, need);
         if (kernel_codebooks == 0) return 1;
-        if (A.dtype != MADDNESS_F32 && row_bytes < 512 && table_bytes < 16 * 256) return 1;
-        if (A.dtype != MADDNESS_F32 && table_bytes <= 80 * 1024 && a.N < 32768) return 1;
+        if (A.dtype != MADDNESS_F32 && table_bytes <= 80 * 1024 && narrow_rows_split_only(a, kernel_codebooks, es)) return 1;
         if (few_rows_in_lds(a, kernel_codebooks, es, true)) return 1;
         // more than two blocks of columns: whole rows through LDS; else straight from the registers
         const int span = codebooks <= 32 ? 64 : 32;

@@ -161,6 +161,11 @@ FASTER = [
     ((378, 333, 224, 30, "bf16", False), "fused_mfma"), ((1, 256, 172, 40, "u8", False), "scan_kernel"),
     ((16384, 1500, 592, 12, "f32", False), "fused_mfma"), ((1787, 512, 112, 40, "f32", False), "scan_kernel"),
     ((1000, 256, 92, 64, "f32", False), "fused_mfma"), ((1, 256, 72, 64, "f32", False), "scan_kernel"),
+    # narrow rows, small tables: the split values alone or whole rows
+    ((32767, 250, 33, 15, "f16", False), "scan_kernel"), ((32768, 250, 33, 15, "f16", False), "fused_mfma"),
+    ((53325, 85, 20, 16, "u8", False), "scan_kernel"), ((40000, 716, 5, 4, "u8", False), "scan_kernel"),
+    ((33000, 1558, 92, 2, "f16", False), "scan_kernel"), ((40001, 174, 8, 22, "bf16", False), "scan_kernel"),
+    ((35000, 426, 42, 53, "u8", False), "fused_mfma"), ((36000, 472, 66, 16, "bf16", False), "fused_mfma"),
 ]
 
 
