@@ -742,6 +742,33 @@ int launch_row_major(const RowsArgs &a, int C, int D, const MatrixA &A, hipStrea
                                : launch_rows_typed<64, 4, 2>(a, A.dtype, stream);
 }
 
+// A stored by columns, few rows: tables and trees cost this kernel 12 to 19 us before the first row; the general one brings
+// the tables it can hold at once into LDS in 9 to 22 us, and then takes 8192 rows of large tables, or more the fewer words
+// a row of them has, in 2 us; reads of rows of 16, 32 or 64 words meet in LDS banks there.  Measured, general and here: C = 16,
+// M = 264, 66 KiB, 15.2 and 18.3 us for 4200 rows, 22.5 and 18.1 (M = 320) for 8500; C = 32, M = 192 15.2 and 17.3 for 6000, 22.1
+// and 19.1 for 8500; M = 256 20 and 19 for 5000; C = 64, M = 96 18.5 and 17.3 for 6000; C = 16, M = 584, 146 KiB, 21.3 and
+// 19.0 for 100, 22.7 and 28.1 for 1000, 33.1 and 28.7 for 8500; small tables, time there over time here for 16384, 25000,
+// 45000 and 80000 rows: C = 16, M = 16 1.04, 1.01, 1.01, 0.79 (100000: 1.12), M = 28 0.97, 0.97, 0.92, 1.15, M = 48 0.94, 1.15,
+// 1.87, 2.46, M = 64 1.07, 1.87, 2.52, 2.27; C = 32, M = 20 0.69, 0.75, 0.76, 1.95, M = 48 0.79, 1.02, 1.30, 1.46, M = 100 0.95,
+// 1.19, 1.23, 2.48.
+bool few_columns_in_lds(int C, int M, int64_t N)
+{
+    const int64_t tables = 16 * (int64_t)C * M;
+    if (tables > 128 * 1024) return C == 16 && N > 256 && N <= 8192 && scan_in_one_piece(C, M, true);
+    if (tables > 64 * 1024) return N < (C == 64 || tables == 128 * 1024 ? 4096 : 8193);
+    if (C == 64) return N < 16384;
+    int lanes = 1;                                         // of a wavefront to a row, as launch_scan has it
+    while (4 * lanes < M && lanes < 64) lanes *= 2;
+    const bool banks = M == 4 * lanes;
+    switch (lanes) {
+    case 1: return N < 16384;
+    case 2: return C == 16 || N < 16384;
+    case 4: return N < (C == 16 ? 98304 : 65536);
+    case 8: return N < (C == 32 && banks ? 24576 : 57344);
+    default: return N < (banks || (C == 16 && lanes == 32) ? 16384 : 24576);
+    }
+}
+
 }  // namespace
 
 // Returns MADDNESS_OK after a launch, 1 if the shape is not covered.
@@ -769,12 +796,7 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
                          (A.col_major || ((D * es) % 16 == 0 && (A.ld * es) % 16 == 0 && aligned_to(A.data, 16) &&
                                           (!codes || aligned_to(codes, C != p.C ? 4 : (C == 16 ? 8 : 16)))));
     if (regular && A.col_major && C == p.C && N <= kColsFewRows) {
-        // (tables and trees cost this kernel 13 to 19 us before the first row, and the general one single elements and
-        // tiles of the tables: binary16, M = 256, C = 32 19 against 19 us for 1000 rows, 20 against 22 for 8192, 21
-        // against 30 for 16384; bfloat16, M = 64, C = 32 16 against 12 for 2048 and 16 against 16 for 8192; fp32, M = 512,
-        // C = 64 25 against 180 for 500)
-        const int64_t tables = 16 * (int64_t)C * M;
-        if (N < (tables <= 64 * 1024 ? 16384 : tables <= 128 * 1024 ? 4096 : 1)) return 1;
+        if (few_columns_in_lds(C, M, N)) return 1;
         if (codes && !aligned_to(codes, 4)) return 1;
         return C == 16   ? launch_cols_few_typed<16, 4>(a, A.dtype, stream)
                : C == 32 ? launch_cols_few_typed<32, 4>(a, A.dtype, stream)

@@ -166,6 +166,13 @@ FASTER = [
     ((53325, 85, 20, 16, "u8", False), "scan_kernel"), ((40000, 716, 5, 4, "u8", False), "scan_kernel"),
     ((33000, 1558, 92, 2, "f16", False), "scan_kernel"), ((40001, 174, 8, 22, "bf16", False), "scan_kernel"),
     ((35000, 426, 42, 53, "u8", False), "fused_mfma"), ((36000, 472, 66, 16, "bf16", False), "fused_mfma"),
+    # A by columns: small tables by the words of their rows, larger ones up to 8192 rows
+    ((80000, 40, 8, 16, "f32", True), "scan_kernel"), ((97000, 20, 16, 16, "f16", True), "scan_kernel"),
+    ((98304, 20, 16, 16, "f16", True), "fused_mfma"), ((57000, 24, 28, 32, "u8", True), "scan_kernel"),
+    ((24576, 24, 32, 32, "f32", True), "fused_mfma"), ((24575, 24, 48, 16, "f32", True), "scan_kernel"),
+    ((8192, 50, 192, 32, "f32", True), "scan_kernel"), ((8193, 50, 192, 32, "bf16", True), "fused_mfma"),
+    ((300, 50, 584, 16, "f32", True), "scan_kernel"), ((256, 50, 584, 16, "f32", True), "fused_mfma"),
+    ((4096, 50, 96, 64, "u8", True), "fused_mfma"),
 ]
 
 
