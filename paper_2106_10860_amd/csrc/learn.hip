@@ -24,7 +24,7 @@
 //   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column (bitonic sort of
 //                        (value, row) keys: equal values stay in row order, as a stable sort
 //                        of a bucket's rows leaves them)
-//   split_chains_kernel, split_losses_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
+//   split_chains_kernel (split_chains_small_kernel), split_losses_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
 //                        running sums at every 32nd row in both directions, then the loss of
 //                        every split, a wavefront per 256 rows
 //   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
@@ -199,9 +199,9 @@ __device__ __forceinline__ void add_16_in_order(double &acc, double term, double
 #undef MADDNESS_ADD_TERM
 
 // The chains' part of a tile: `at` is the lane's first value (its 16th of the column's), term(x, i) the term of value x in
-// row i of the lane's; before(k) runs before every 32nd row.
+// row i of the lane's; before(k) runs before every 32nd row.  Rows from `rows` on (a multiple of 32) are left out.
 template <typename Term, typename Before>
-__device__ __forceinline__ void add_tile_in_order(double &acc, const float *at, Term term, Before before)
+__device__ __forceinline__ void add_tile_in_order(double &acc, const float *at, int rows, Term term, Before before)
 {
     double one = 1.0;
     asm("" : "+v"(one));
@@ -210,22 +210,24 @@ __device__ __forceinline__ void add_tile_in_order(double &acc, const float *at, 
     for (int i = 0; i < kChainRows / 16; ++i) x[i] = at[16 * i];
 #pragma unroll
     for (int i = 0; i < kChainRows / 16; ++i) {
+        if (i % 2 == 0 && 16 * i >= rows) break;
         if (i % 2 == 0) before(i / 2);
         add_16_in_order(acc, term(x[i], 16 * i), one);
     }
 }
 
-// The workgroup's loop: n_steps tiles of kChainRows rows.  walk(values of tile s, s) runs on the first kWalkers
+// The workgroup's loop: n_steps tiles of kChainRows rows.  walk(values of tile s, s, rows) runs on the first kWalkers
 // wavefronts; meanwhile the helpers lay out tile s + 1, fetch the values of tile s + kDepth + 1 and list the rows of the
 // tile after that, whose numbers they asked for kDepth steps before: ask(s, i) reads what tells the number of row i of
 // tile s, anything where there is none, and row(read, s, i) is the number, `N` where there is none.  (ask has to read in
 // any case: a read under a condition becomes a branch, after which every wait is one for all that is on its way, 600 ns
-// a tile.)  X: the codebook's values, from the workgroup's first column on.
+// a tile.)  X: the codebook's values, from the workgroup's first column on.  n_rows: how many rows there are in all,
+// rounded up to a multiple of 32 at most; `rows` is kChainRows, or n_rows where there is one tile alone.
 template <int NC>
 constexpr size_t stream_lds_bytes() { return sizeof(float) * 2 * NC * kChainPitch + sizeof(int32_t) * kLists * kChainRows; }
 
 template <int NC, int kWalkers, typename Ask, typename Row, typename Walk>
-__device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, int pitch, int n_steps, Ask ask, Row row, Walk walk)
+__device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, int pitch, int n_steps, int n_rows, Ask ask, Row row, Walk walk)
 {
     constexpr int kPieces = NC / 4, kStride = kChainHelpers / kPieces, kPer = kChainRows / kStride, kBuffer = NC * kChainPitch;
     float *values = reinterpret_cast<float *>(lds);                        // [2][NC][kChainPitch]
@@ -251,13 +253,38 @@ __device__ __forceinline__ void stream_rows(unsigned char *lds, const float *X, 
             dst[u * kStride + 3 * kChainPitch] = x[set][u].w;
         }
     };
+    if (n_steps == 1) {
+        // a bucket of one tile (many codebooks, few rows): nothing to fetch ahead, and no more rows than there are (the trees
+        // of 64 codebooks of 9 columns, 50 rows: 275 us with all that the loop below reads, 227 so)
+        const bool walks = __builtin_amdgcn_readfirstlane(helper) < 0;
+        if (!walks && helper < n_rows) listed[helper] = row(ask(0, helper), 0, helper);
+        __syncthreads();
+        if (!walks) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (u * kStride < n_rows) {
+                    const int r = rsub + u * kStride;
+                    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (r < n_rows) v = *reinterpret_cast<const float4 *>(src + (uint64_t)(uint32_t)listed[r] * (uint32_t)pitch);
+                    float *dst = values + 4 * piece * kChainPitch + r;
+                    dst[0] = v.x;
+                    dst[kChainPitch] = v.y;
+                    dst[2 * kChainPitch] = v.z;
+                    dst[3 * kChainPitch] = v.w;
+                }
+        }
+        __syncthreads();
+        if (walks) walk(values, 0, n_rows);
+        __syncthreads();
+        return;
+    }
     // (Two loops with a barrier a tile in each: in one loop the compiler takes a load for the newest wherever the walkers'
     // side may have come between, and waits for all of them.)
     if (__builtin_amdgcn_readfirstlane(helper) < 0) {
         __syncthreads();
         __syncthreads();
         for (int s = 0; s < n_steps; ++s) {
-            walk(values + (s & 1) * kBuffer, s);
+            walk(values + (s & 1) * kBuffer, s, kChainRows);
             __syncthreads();
         }
         return;
@@ -433,14 +460,14 @@ __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(con
     };
     double sum = 0.0, loss = 0.0;
     int room = 1023;
-    stream_rows<4, 4>(lds_raw, X, a.pitch, n_steps, ask, row, [&](const float *values, int) __attribute__((always_inline)) {
+    stream_rows<4, 4>(lds_raw, X, a.pitch, n_steps, count, ask, row, [&](const float *values, int, int) __attribute__((always_inline)) {
         double t[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) t[k] = (double)values[wave * kChainPitch + 64 * k + lane];
         if (!add_exactly(sum, t, room)) add_chained(sum, t);
     });
     const double mean = sum / (double)count;
-    stream_rows<4, 4>(lds_raw, X, a.pitch, n_steps, ask, row, [&](const float *values, int s) __attribute__((always_inline)) {
+    stream_rows<4, 4>(lds_raw, X, a.pitch, n_steps, count, ask, row, [&](const float *values, int s, int) __attribute__((always_inline)) {
         double t[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -643,9 +670,9 @@ __device__ __forceinline__ int64_t first_group(int32_t start, int bucket) { retu
 
 // Both sums of up to NC columns to a workgroup, four chains to a wavefront.  Going down (direction 1)
 // the tiles are taken last to first, each from its end; what lies past the bucket's last row counts as zeros, which
-// leave a sum as it is.
+// leave a sum as it is.  small_too: split_chains_small_kernel takes the buckets of up to kChainRows rows.
 template <int NC>
-__global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(const LearnArgs a)
+__global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(const LearnArgs a, int small_too)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     // (the codebook changes fastest from workgroup to workgroup: those of one codebook meet on few XCDs)
@@ -654,7 +681,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows;
-    if (n_tiles == 0) return;
+    if (count <= (small_too ? kChainRows : 1)) return;
     constexpr int kTiles = kChainRows / kSplitRows;
     const int n_steps = (n_tiles + kTiles - 1) / kTiles;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
@@ -672,7 +699,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     };
     double acc = 0.0;
     stream_rows<NC, NC / 2>(
-        lds_raw, a.X + (size_t)c * (a.N + 1) * a.pitch + col0, a.pitch, n_steps,
+        lds_raw, a.X + (size_t)c * (a.N + 1) * a.pitch + col0, a.pitch, n_steps, n_tiles * kSplitRows,
         [&](int s, int i) __attribute__((always_inline)) {
             return static_cast<uint32_t>(keys[max(0, min(place(s, i), count - 1))]);
         },
@@ -680,8 +707,8 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
             const int p = place(s, i);
             return p >= 0 && p < count ? (int32_t)(read & ((1u << kKeyRowBits) - 1u)) : (int32_t)a.N;
         },
-        [&](const float *values, int s) __attribute__((always_inline)) {
-            add_tile_in_order(acc, values + (chain % NC) * kChainPitch + l,
+        [&](const float *values, int s, int rows) __attribute__((always_inline)) {
+            add_tile_in_order(acc, values + (chain % NC) * kChainPitch + l, rows,
                               [&](float x, int) __attribute__((always_inline)) {
                                   const double v = (double)x;
                                   return squares ? v * v : v;
@@ -691,6 +718,59 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
                                   if (stored && tile < n_tiles) out[(size_t)(dir ? n_tiles - 1 - tile : tile) * (2 * a.dmax)] = acc;
                               });
         });
+}
+
+// The same for buckets of at most one tile of kChainRows rows, where the other kernel would spend its time on the way in
+// and out (a workgroup of 12 wavefronts to a compute unit): both directions and all columns of a group from one reading of
+// the rows, a row of 16 lanes per column.  (164 codebooks of 40 columns, 8 rows: a level's chains 8.5 us, 88 there; the trees of
+// 64 of 9 columns, 50 rows 185 and 227.)  A bucket of one row has no split.
+template <int NC>
+__global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const LearnArgs a)
+{
+    __shared__ __align__(16) float values[NC][kChainPitch];
+    __shared__ int32_t rows[kChainRows];
+    const int c = blockIdx.x, b = blockIdx.z, q = blockIdx.y & 3, col0 = (blockIdx.y >> 2) * NC;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (q >= a.n_cand[c] || col0 >= d) return;
+    const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
+    if (count < 2 || count > kChainRows) return;
+    const int n_tiles = (count + kSplitRows - 1) / kSplitRows, n_rows = n_tiles * kSplitRows, tid = threadIdx.x;
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+    const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
+    for (int i = tid; i < n_rows; i += 16 * NC) rows[i] = i < count ? key_row(keys[i]) : (int32_t)a.N;
+    __syncthreads();
+    for (int i = tid; i < n_rows * (NC / 4); i += 16 * NC) {
+        const int r = i / (NC / 4), piece = i % (NC / 4);
+        const float4 v = *reinterpret_cast<const float4 *>(X + (int64_t)rows[r] * a.pitch + 4 * piece);
+        values[4 * piece][r] = v.x;
+        values[4 * piece + 1][r] = v.y;
+        values[4 * piece + 2][r] = v.z;
+        values[4 * piece + 3][r] = v.w;
+    }
+    __syncthreads();
+    const int col = tid / 16, l = tid & 15;
+    const size_t row_size = 2 * (size_t)a.dmax, down = (size_t)a.tile_slots * row_size;
+    double *out = a.sums + ((size_t)c * kCand + q) * 2 * down + (size_t)first_slot(start, b) * row_size + col0 + col;
+    double sum[2] = {0.0, 0.0}, squares[2] = {0.0, 0.0}, one = 1.0;
+    asm("" : "+v"(one));
+    for (int t = 0; t < n_tiles; ++t) {
+        if (l == 0 && col0 + col < d)
+#pragma unroll
+            for (int dir = 0; dir < 2; ++dir) {
+                double *at = out + dir * down + (dir ? n_tiles - 1 - t : t) * row_size;
+                at[0] = sum[dir];
+                at[a.dmax] = squares[dir];
+            }
+#pragma unroll
+        for (int i = 0; i < kSplitRows; i += 16)
+#pragma unroll
+            for (int dir = 0; dir < 2; ++dir) {
+                const int at = t * kSplitRows + i + l;
+                const double v = (double)values[col][dir ? n_rows - 1 - at : at];
+                add_16_in_order(sum[dir], v, one);
+                add_16_in_order(squares[dir], v * v, one);
+            }
+    }
 }
 
 // A wavefront per kGroupTiles tiles of kSplitRows sorted rows of a bucket, one tile after the other with the next one's
@@ -1542,7 +1622,7 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
     a.split_dims = split_dims; a.thresholds = thresholds; a.codes = codes;
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
-    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
+    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
 
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
@@ -1589,15 +1669,21 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
         const int groups = narrow ? 1 : a.pitch / 16;
         const dim3 chain_groups(C, 8 * groups, n_buckets);
         const dim3 grid_losses((unsigned)(a.group_slots * C), kCand);
-        if (narrow) {
-            hipLaunchKernelGGL(split_chains_kernel<8>, chain_groups, dim3(32 * 8 + kChainHelpers), stream_lds_bytes<8>(), stream, a);
-            LAUNCH_OK("launch split_chains_kernel");
-            hipLaunchKernelGGL(split_losses_kernel<8>, grid_losses, dim3(64), 0, stream, a, n_buckets);
-        } else {
-            hipLaunchKernelGGL(split_chains_kernel<16>, chain_groups, dim3(32 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a);
-            LAUNCH_OK("launch split_chains_kernel");
-            hipLaunchKernelGGL(split_losses_kernel<16>, grid_losses, dim3(64), 0, stream, a, n_buckets);
+        // (where buckets of one tile can be the rule: even shares of the rows are)
+        const int small_too = N <= (int64_t)kChainRows * n_buckets;
+        const dim3 small_groups(C, 4 * groups, n_buckets);
+        if (small_too) {
+            if (narrow) hipLaunchKernelGGL(split_chains_small_kernel<8>, small_groups, dim3(16 * 8), 0, stream, a);
+            else hipLaunchKernelGGL(split_chains_small_kernel<16>, small_groups, dim3(16 * 16), 0, stream, a);
+            LAUNCH_OK("launch split_chains_small_kernel");
         }
+        if (N > (small_too ? kChainRows : 1)) {
+            if (narrow) hipLaunchKernelGGL(split_chains_kernel<8>, chain_groups, dim3(32 * 8 + kChainHelpers), stream_lds_bytes<8>(), stream, a, small_too);
+            else hipLaunchKernelGGL(split_chains_kernel<16>, chain_groups, dim3(32 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a, small_too);
+            LAUNCH_OK("launch split_chains_kernel");
+        }
+        if (narrow) hipLaunchKernelGGL(split_losses_kernel<8>, grid_losses, dim3(64), 0, stream, a, n_buckets);
+        else hipLaunchKernelGGL(split_losses_kernel<16>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         LAUNCH_OK("launch split_losses_kernel");
         hipLaunchKernelGGL(choose_kernel, dim3(C), dim3(512), 0, stream, a, level, n_buckets);
         LAUNCH_OK("launch choose_kernel");

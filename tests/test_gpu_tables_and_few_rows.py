@@ -301,3 +301,22 @@ def test_losses_in_row_order(mad, kind):
     assert (sd.cpu().numpy() == want_sd).all()
     assert (th.cpu().numpy().view(np.uint32) == want_th.view(np.uint32)).all()
     assert (codes.cpu().numpy() == want_codes).all()
+
+
+@pytest.mark.parametrize("width", [5, 20])
+@pytest.mark.parametrize("N", [1, 2, 3, 9, 33, 255, 256, 257, 300, 511, 513, 2048, 2049])
+def test_trees_of_few_rows(mad, N, width):
+    """Buckets of no row, one row and either side of the 256 rows up to which a bucket's sums have a kernel of their own,
+    where that kernel is taken and where it is not; skewed, so that a level has both."""
+    import torch
+    rng = np.random.default_rng(N + width)
+    A = np.exp(rng.standard_normal((N, 3 * width))).astype(np.float32)
+    A[:, 1] = np.round(A[:, 1])
+    A[: N // 2, width] = 1.0
+    subspaces = [(0, width), (width, 2 * width), (2 * width, 3 * width)]
+    sd, th, codes = mad.maddness_learn_trees(dev(A), subspaces)
+    torch.cuda.synchronize()
+    want_sd, want_th, want_codes, _ = oracle.learn_trees(A, subspaces)
+    assert (sd.cpu().numpy() == want_sd).all()
+    assert (th.cpu().numpy().view(np.uint32) == want_th.view(np.uint32)).all()
+    assert (codes.cpu().numpy() == want_codes).all()
