@@ -265,7 +265,11 @@ int maddness_encode_scan_typed(const maddness_params *params, const void *A, int
  *                  training row in every tree; may be NULL.
  * workspace        device scratch of at least maddness_learn_trees_workspace(...) bytes,
  *                  256-byte aligned (maddness_learn_trees_workspace returns 0 for arguments
- *                  it cannot size).
+ *                  it cannot size).  A codebook of w columns takes about N (8 w + 5) + 32 N'
+ *                  bytes (w rounded up to 8 or a multiple of 16, N' = N rounded up to a
+ *                  power of two); trees are learned as many at a time as stay within the
+ *                  larger of 4 GiB and 2 C (37 N + 32 N'), one at least, and the result does
+ *                  not depend on how many.
  *
  * maddness_learn_prototypes computes the prototype matrix P from the training codes:
  *   ridge != 0   P = (G^T G + lambda I)^-1 G^T A_train (Section 4.3), G the one-hot matrix of
@@ -274,7 +278,8 @@ int maddness_encode_scan_typed(const maddness_params *params, const void *A, int
  *                own columns and 0 elsewhere (an empty bucket: 0) - the prototypes before the
  *                ridge step, the variant Section 5.1 calls MADDNESS-PQ.
  * prototypes       out [C][16][D] fp32, as maddness_params takes them.
- * workspace        at least maddness_learn_prototypes_workspace(D, C) bytes, 256-byte aligned.
+ * workspace        at least maddness_learn_prototypes_workspace(D, C) bytes, 256-byte aligned
+ *                  (about 20 Q^2 + 8 Q D + 264000 C bytes, Q = 16 C).
  *
  * Both calls are enqueued on `stream` and return without synchronising; errors as everywhere.
  */

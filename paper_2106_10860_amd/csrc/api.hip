@@ -337,14 +337,10 @@ static int check_learn(const float *A, int64_t N, int64_t lda, int32_t D, int32_
 
 size_t maddness_learn_trees_workspace(int64_t N, int32_t D, int32_t C, const int32_t *subspace_bounds)
 {
-    int32_t dmax = 0;
     if (N < 1 || D < 1 || C < 1 || C > MADDNESS_MAX_C || !subspace_bounds) return 0;
-    for (int c = 0; c < C; ++c) {
-        const int w = subspace_bounds[2 * c + 1] - subspace_bounds[2 * c];
-        if (w < 1) return 0;
-        if (w > dmax) dmax = w;
-    }
-    return learn_trees_workspace_bytes(N, C, dmax);
+    for (int c = 0; c < C; ++c)
+        if (subspace_bounds[2 * c + 1] - subspace_bounds[2 * c] < 1) return 0;
+    return learn_trees_workspace_bytes(N, C, subspace_bounds);
 }
 
 int maddness_learn_trees(const float *A_train, int64_t N, int64_t lda, int32_t D, int32_t C,
@@ -360,11 +356,11 @@ int maddness_learn_trees(const float *A_train, int64_t N, int64_t lda, int32_t D
     if (dmax > learn_max_subspace_width())
         return fail(MADDNESS_E_UNSUPPORTED, "a subspace of %d columns: the GPU learner takes at most %d", dmax,
                     learn_max_subspace_width());
-    const size_t need = learn_trees_workspace_bytes(N, C, dmax);
+    const size_t need = learn_trees_workspace_bytes(N, C, subspace_bounds);
     if (!workspace || workspace_bytes < need)
         return fail(MADDNESS_E_UNSUPPORTED, "workspace of %zu bytes given, %zu needed", workspace_bytes, need);
     if (!aligned(workspace, 256)) return fail(MADDNESS_E_ALIGN, "workspace not 256-byte aligned");
-    return launch_learn_trees(A_train, N, lda, C, subspace_bounds, dmax, split_dims, thresholds, train_codes, workspace,
+    return launch_learn_trees(A_train, N, lda, C, subspace_bounds, split_dims, thresholds, train_codes, workspace,
                               static_cast<hipStream_t>(stream));
 }
 

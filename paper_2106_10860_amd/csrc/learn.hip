@@ -71,7 +71,8 @@ struct LearnArgs {
     int32_t *chosen;      // [C] the level's column (within the subspace)
     int32_t *split_dims;  // out [C][4]
     float *thresholds;    // out [C][16]
-    uint8_t *codes;       // out [N][C] or null
+    uint8_t *codes;       // out [N][codes_pitch] or null
+    int32_t codes_pitch;
 };
 
 __global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst)
@@ -1018,7 +1019,7 @@ __global__ __launch_bounds__(256) void apply_kernel(const LearnArgs a, int level
         const float v = a.thresholds[16 * c + n_buckets - 1 + b];
         child = 2 * b + (a.X[((size_t)c * (a.N + 1) + n) * a.pitch + j] >= v ? 1 : 0);
         a.node[(size_t)c * a.N + n] = (uint8_t)child;
-        if (level == 3 && a.codes) a.codes[n * a.C + c] = (uint8_t)child;
+        if (level == 3 && a.codes) a.codes[n * a.codes_pitch + c] = (uint8_t)child;
     }
     if (level == 3) return;
     // (a chunk is a whole number of workgroups' rows)
@@ -1591,13 +1592,48 @@ void carve_prototypes(Carver &w, ProtoArgs &a)
 
 }  // namespace
 
-size_t learn_trees_workspace_bytes(int64_t N, int32_t C, int32_t dmax)
+namespace {
+
+size_t batch_bytes(int64_t N, int32_t C, int32_t dmax)
 {
     LearnArgs a{};
     a.N = N; a.Npad = pow2_at_least(N); a.C = C; a.dmax = dmax;
     Carver w{nullptr};
     carve_trees(w, a);
     return w.used;
+}
+
+// Trees do not depend on each other, so the codebooks are taken in batches, one after the other in the same workspace: as
+// many as stay within `limit`, one at least.  The codebooks' columns (X) and running sums (sums) take 8 bytes per row and
+// column, everything else 69 per row and codebook or less; without a limit 2^20 rows of 16 subspaces of 128 columns take 16.6
+// GiB, and one wide subspace makes all others of its batch as wide.  Returns one past the batch's last codebook, its
+// widest subspace in *dmax.
+int32_t batch_end(int64_t N, int32_t C, const int32_t *bounds, int32_t first, int32_t *dmax)
+{
+    const size_t rows = (size_t)N, padded = (size_t)pow2_at_least(N);
+    const size_t limit = std::max<size_t>((size_t)4 << 30, 2 * (size_t)C * (37 * rows + 32 * padded));
+    *dmax = 0;
+    int32_t end = first;
+    for (; end < C; ++end) {
+        const int32_t widest = std::max(*dmax, bounds[2 * end + 1] - bounds[2 * end]);
+        if (end > first && batch_bytes(N, end + 1 - first, widest) > limit) break;
+        *dmax = widest;
+    }
+    return end;
+}
+
+}  // namespace
+
+size_t learn_trees_workspace_bytes(int64_t N, int32_t C, const int32_t *bounds)
+{
+    size_t bytes = 0;
+    for (int32_t c = 0; c < C;) {
+        int32_t dmax = 0;
+        const int32_t end = batch_end(N, C, bounds, c, &dmax);
+        bytes = std::max(bytes, batch_bytes(N, end - c, dmax));
+        c = end;
+    }
+    return bytes;
 }
 
 size_t learn_prototypes_workspace_bytes(int32_t D, int32_t C)
@@ -1614,16 +1650,12 @@ int learn_max_subspace_width() { return kMaxWidth; }
 #define LAUNCH_OK(what)                                                       \
     if (int rc_ = check_hip(hipGetLastError(), what); rc_ != MADDNESS_OK) return rc_
 
-int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const int32_t *bounds_host, int32_t dmax,
-                       int32_t *split_dims, float *thresholds, uint8_t *codes, void *workspace, hipStream_t stream)
+static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *workspace, hipStream_t stream)
 {
-    LearnArgs a{};
-    a.A = A; a.lda = lda; a.N = N; a.Npad = pow2_at_least(N); a.C = C; a.dmax = dmax;
-    a.split_dims = split_dims; a.thresholds = thresholds; a.codes = codes;
+    const int64_t N = a.N;
+    const int32_t C = a.C, dmax = a.dmax;
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
-    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
-
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
     hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds);
@@ -1636,7 +1668,6 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
     hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)((pieces + 255) / 256), C), dim3(256), 0, stream, a);
     LAUNCH_OK("launch gather_columns_kernel");
 
-    if (int rc = allow_full_lds<sort_chunks_kernel>(); rc != MADDNESS_OK) return rc;
     const bool narrow = dmax <= 8;
     for (int level = 0; level < 4; ++level) {
         const int n_buckets = 1 << level;
@@ -1689,6 +1720,23 @@ int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const 
         LAUNCH_OK("launch choose_kernel");
         hipLaunchKernelGGL(apply_kernel, dim3((unsigned)((N + 255) / 256), C), dim3(256), 0, stream, a, level, n_buckets);
         LAUNCH_OK("launch apply_kernel");
+    }
+    return MADDNESS_OK;
+}
+
+int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const int32_t *bounds_host, int32_t *split_dims,
+                       float *thresholds, uint8_t *codes, void *workspace, hipStream_t stream)
+{
+    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
+    if (int rc = allow_full_lds<sort_chunks_kernel>(); rc != MADDNESS_OK) return rc;
+    for (int32_t c = 0; c < C;) {
+        LearnArgs a{};
+        const int32_t end = batch_end(N, C, bounds_host, c, &a.dmax);
+        a.A = A; a.lda = lda; a.N = N; a.Npad = pow2_at_least(N); a.C = end - c;
+        a.split_dims = split_dims + 4 * c; a.thresholds = thresholds + 16 * c;
+        a.codes = codes ? codes + c : nullptr; a.codes_pitch = C;
+        if (int rc = launch_learn_batch(a, bounds_host + 2 * c, workspace, stream); rc != MADDNESS_OK) return rc;
+        c = end;
     }
     return MADDNESS_OK;
 }

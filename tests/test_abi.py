@@ -148,3 +148,24 @@ def test_learning_calls_reject_on_the_host(mad):
     assert L.maddness_learn_prototypes(fake, fake, 10, 16, 16, 2, ok, 1, -1.0, fake, fake, 1 << 30, None) == mad.MADDNESS_E_INVAL
     assert L.maddness_learn_prototypes(fake, fake, 10, 16, 16, 2, ok, 1, 1.0, None, fake, 1 << 30, None) == mad.MADDNESS_E_INVAL
     assert L.maddness_learn_prototypes(fake, fake, 10, 16, 16, 2, ok, 0, 0.0, fake, fake, 16, None) == mad.MADDNESS_E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("N,widths", [(1 << 20, [128] * 16), (1 << 20, [8] * 60 + [128] + [8] * 3), (260100, [7, 7, 7, 6]),
+                                      (20000, [16] * 32), (1 << 25, [9] * 8), (3, [128] * 256), (1 << 27, [128])])
+def test_learn_trees_workspace_is_bounded(mad, N, widths):
+    """Beyond 4 GiB it is at most twice what keys, lists and places of all codebooks take, or what the widest codebook takes
+    alone; up to there it is that of all codebooks at once."""
+    L = mad.lib()
+
+    def workspace(ws):
+        ends = [sum(ws[:i + 1]) for i in range(len(ws))]
+        bounds = (C.c_int32 * (2 * len(ws)))(*[v for w, e in zip(ws, ends) for v in (e - w, e)])
+        return L.maddness_learn_trees_workspace(N, ends[-1], len(ws), bounds)
+
+    padded = 1 << (N - 1).bit_length()
+    got = workspace(widths)
+    alone = workspace([max(widths)])
+    assert got <= max(4 << 30, 2 * len(widths) * (37 * N + 32 * padded), alone)
+    assert alone <= N * (8 * (max(widths) + 15) + 5) + 32 * padded + (1 << 20)
+    if len(widths) * alone <= 4 << 30:
+        assert got >= len(widths) * 8 * max(widths) * N

@@ -320,3 +320,20 @@ def test_trees_of_few_rows(mad, N, width):
     assert (sd.cpu().numpy() == want_sd).all()
     assert (th.cpu().numpy().view(np.uint32) == want_th.view(np.uint32)).all()
     assert (codes.cpu().numpy() == want_codes).all()
+
+
+def test_trees_in_batches(mad):
+    """More codebooks than the workspace takes at a time, one of them narrow: the same trees and codes as each alone."""
+    import torch
+    N, D = 1 << 20, 132
+    g = torch.Generator(device="cuda").manual_seed(7)
+    A = torch.randn((N, D), device="cuda", generator=g)
+    subspaces = [(0, 128), (4, 132), (2, 130), (1, 6), (3, 129), (0, 120), (5, 132)]
+    sd, th, codes = mad.maddness_learn_trees(A, subspaces)
+    torch.cuda.synchronize()
+    for c, subspace in enumerate(subspaces):
+        print("codebook", c, flush=True)
+        sd1, th1, codes1 = mad.maddness_learn_trees(A, [subspace])
+        torch.cuda.synchronize()
+        assert torch.equal(sd[c], sd1[0]) and torch.equal(th[c], th1[0]), c
+        assert torch.equal(codes[:, c], codes1[:, 0]), c
