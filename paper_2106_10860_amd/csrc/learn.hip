@@ -88,18 +88,20 @@ __global__ void clear_kernel(int32_t *p, int64_t n)
 
 // The columns of every codebook side by side, each row on a 32-byte (or 64-byte) boundary.  The levels read the rows of a
 // bucket in many orders, a codebook's columns at a time: from here they take whole 16-byte pieces, and the rows of a
-// codebook fit in an XCD's L2 where A does not.  A thread per 16-byte piece.
+// codebook fit in an XCD's L2 where A does not.  A 16-byte piece to a thread and turn.
 __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
 {
-    const int c = blockIdx.y, pieces = a.pitch / 4;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t row = i / pieces;
-    if (row > a.N) return;
-    const int col = 4 * (int)(i - row * pieces), lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
-    float v[4];
+    const int c = blockIdx.y, pieces = a.pitch / 4, lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
+    float4 *X = reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch);
+    // (a grid of as many threads as pieces would have more than 2^32 from 2^34 values on)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (a.N + 1) * pieces; i += (int64_t)gridDim.x * 256) {
+        const int64_t row = i / pieces;
+        const int col = 4 * (int)(i - row * pieces);
+        float v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = row < a.N && col + e < d ? a.A[row * a.lda + lo + col + e] : 0.0f;
-    reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch)[i] = make_float4(v[0], v[1], v[2], v[3]);
+        for (int e = 0; e < 4; ++e) v[e] = row < a.N && col + e < d ? a.A[row * a.lda + lo + col + e] : 0.0f;
+        X[i] = make_float4(v[0], v[1], v[2], v[3]);
+    }
 }
 
 // The rows of every bucket, in row order (a stable counting sort of the rows by bucket): rows_by_bucket[c]
@@ -1665,7 +1667,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     LAUNCH_OK("launch clear_kernel");
 
     const int64_t pieces = (N + 1) * (a.pitch / 4);
-    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)((pieces + 255) / 256), C), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, 1 << 16), C), dim3(256), 0, stream, a);
     LAUNCH_OK("launch gather_columns_kernel");
 
     const bool narrow = dmax <= 8;
