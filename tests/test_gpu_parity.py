@@ -869,9 +869,9 @@ def test_parity_typed_and_column_major(mad, shape, dtype, run, options):
                          ids=lambda s: "N%d_D%d_M%d_C%d_p%d" % s)
 @pytest.mark.parametrize("dtype", ["f32", "f16", "u8"])
 def test_parity_typed_phased_kernel_many_blocks(mad, shape, dtype, options):
-    """The phased kernel on narrow rows and on A stored by columns with three workgroups and the
-    fewest rows per region: every workgroup takes many blocks in turn (codes area reused, the
-    barrier after the scan), the last block is ragged and some wavefronts get no rows in it."""
+    """The phased kernel on rows of any type and on A stored by columns (its form for up to 131072 rows) with
+    three workgroups and the fewest rows per region: every workgroup takes many blocks in turn (codes area reused,
+    the barrier after the scan), the last block is ragged and some wavefronts get no rows in it."""
     import torch
     N, D, M, C, pad = shape
     print("case typed blocks", shape, dtype, flush=True)

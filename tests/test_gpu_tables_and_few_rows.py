@@ -337,3 +337,94 @@ def test_trees_in_batches(mad):
         torch.cuda.synchronize()
         assert torch.equal(sd[c], sd1[0]) and torch.equal(th[c], th1[0]), c
         assert torch.equal(codes[:, c], codes1[:, 0]), c
+
+
+@pytest.fixture
+def options(mad):
+    """set_option(option, value) for one test; every switch is back at 0 afterwards."""
+    yield mad.maddness_set_option
+    for opt in range(4):
+        mad.maddness_set_option(opt, 0)
+
+
+# (N, D, M, C): four rows to a lane from 131073 rows on - whole blocks and a last one in which wavefronts have no rows, and
+# rows beyond the last four, which the general kernel takes; a row to a lane below
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "u8"])
+@pytest.mark.parametrize("shape", [(131076, 20, 128, 32), (133124, 24, 130, 64), (131079, 17, 72, 32), (30001, 20, 128, 32),
+                                   (30001, 24, 130, 64), (30001, 24, 132, 16)], ids=lambda s: "N%d_D%d_M%d_C%d" % s)
+def test_by_columns_many_blocks(mad, shape, dtype, options):
+    """Three workgroups and the fewest rows per block: every workgroup takes many blocks in turn (the area of the codes and
+    the one the tables pass through used again, the barrier after the scan)."""
+    import torch
+    N, D, M, C = shape
+    print("case", shape, dtype, flush=True)
+    options(mad.MADDNESS_OPT_MAX_WORKGROUPS, 3)
+    options(mad.MADDNESS_OPT_PHASED_ROWS, 256)
+    A, sd, th, luts, scale, offset = problem(N + D, N, D, M, C)
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    full = torch.zeros((D, (N + 3) // 4 * 4), dtype=kind, device="cuda")
+    full[:, :N] = (dev(A.T) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind)
+    A_d = full[:, :N]
+    values = A_d.float().cpu().numpy().T.copy()
+    want_out, want_acc, want_codes = oracle.encode_scan(values, sd, th, luts, scale, offset)
+    acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+    codes = torch.zeros((N, C // 2), dtype=torch.uint8, device="cuda")
+    out = mad.maddness_encode_scan_typed(mad.Params(dev(sd), dev(th)), A_d, dev(luts), dev(scale), dev(offset), col_major=True,
+                                         acc=acc, codes=codes)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("fused_mfma_kernel, A by columns"), kernel
+    assert ("few rows" in kernel) == (N < 131073), kernel
+    assert (codes.cpu().numpy() == want_codes).all()
+    assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+    assert (out.cpu().numpy() == want_out).all()
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_selected_kernels_against_general_kernels_at_their_lines(mad, seed, options):
+    """Random shapes with rows on either side of every line of the dispatch, odd widths, columns or rows that start on any
+    element: whatever kernel the library selects gives the bits of its general kernels."""
+    import torch
+    rng = np.random.default_rng(100 + seed)
+    rows = [1, 7, 8, 9, 63, 256, 257, 500, 4095, 4096, 8192, 8193, 16383, 16384, 24576, 32767, 32768, 57344, 65536, 98304, 131072, 131073,
+            131076]
+    kinds = [torch.float32, torch.float32, torch.float16, torch.bfloat16, torch.uint8]
+    for case in range(90):
+        N, C = int(rng.choice(rows)), int(rng.choice([16, 32, 64, 64, 8, 24, 40, 1, 15, 30, 50]))
+        D = int(rng.choice([33, 64, 97, 250, 256, 333, 1021]))
+        M = int(rng.choice([1, 2, 3, 8, 16, 20, 33, 64, 68, 128, 132, 255, 256, 260, 300, 333, 512, 584, 1022]))
+        if N > 60000: D = int(rng.choice([33, 64, 97]))
+        if N > 30000: M = min(M, 300)
+        col, kind = bool(rng.random() < 0.45), kinds[int(rng.integers(len(kinds)))]
+        pad, before = int(rng.choice([0, 0, 1, 2, 3, 5, 7, 8])), int(rng.choice([0, 0, 0, 1, 2, 3, 5]))
+        want_acc, want_codes = bool(rng.random() < 0.4), bool(rng.random() < 0.5)
+        print("case", seed, case, N, D, M, C, kind, col, pad, before, want_acc, want_codes, flush=True)
+        g = torch.Generator(device="cuda").manual_seed(int(rng.integers(1 << 30)))
+        r, c = (D, N) if col else (N, D)
+        flat = torch.zeros(before + r * (c + pad), dtype=kind, device="cuda")
+        A = flat[before:].view(r, c + pad)[:, :c]
+        A.copy_((torch.randn((r, c), device="cuda", generator=g) * (40 if kind == torch.uint8 else 1) +
+                 (128 if kind == torch.uint8 else 0)).clamp(-200, 255).to(kind))
+        sd = torch.randint(0, D, (C, 4), dtype=torch.int32, device="cuda", generator=g)
+        th = torch.randn((C, 16), device="cuda", generator=g) * (30 if kind == torch.uint8 else 0.7) + (128 if kind == torch.uint8 else 0)
+        luts = torch.randint(0, 256, (C, 16, M), dtype=torch.uint8, device="cuda", generator=g)
+        scale, offset = 2.0 ** torch.randint(-5, 3, (M,), device="cuda", generator=g).float(), torch.randn(M, device="cuda", generator=g)
+        params = mad.Params(sd, th)
+
+        def run():
+            acc = torch.zeros((N, M), dtype=torch.int16, device="cuda") if want_acc else None
+            codes = torch.zeros((N, (C + 1) // 2), dtype=torch.uint8, device="cuda") if want_codes else None
+            out = mad.maddness_encode_scan_typed(params, A, luts, scale, offset, col_major=col, acc=acc, codes=codes)
+            kernel = mad.maddness_last_kernel()
+            enc = mad.maddness_encode_typed(params, A, col_major=col)
+            scan, _ = mad.maddness_scan(C, enc, luts, scale, offset)
+            torch.cuda.synchronize()
+            return [out.view(torch.int32), acc, codes, enc, scan.view(torch.int32)], kernel
+
+        options(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_AUTO)
+        got, kernel = run()
+        options(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+        want, _ = run()
+        for name, x, y in zip(("fused out", "acc", "fused codes", "codes", "scan out"), got, want):
+            assert x is None or torch.equal(x, y), f"{name} differs ({kernel})"
+        assert torch.equal(got[0], got[4])
