@@ -237,10 +237,21 @@ __global__ __launch_bounds__(256) void lut_pooled_finish_kernel(const double *__
                                                                 int M, int *__restrict__ lexp, float *__restrict__ scale,
                                                                 float *__restrict__ offset)
 {
+    // every thread computes the same two numbers, from loads on their way a batch at a time (one by one, 194 codebooks
+    // took 25 us, 22 while the compiler still ran ahead; 17 so)
     double r = 0.0, beta = 0.0;
-    for (int c = 0; c < C; ++c) {   // every thread computes the same two numbers
-        r = cb_range[c] > r ? cb_range[c] : r;
-        beta += cb_min[c];
+    for (int c = 0; c < C; c += 2 * QUANT_BATCH) {
+        double e[2 * QUANT_BATCH], v[2 * QUANT_BATCH];
+#pragma unroll
+        for (int u = 0; u < 2 * QUANT_BATCH; ++u) {
+            e[u] = cb_range[min(c + u, C - 1)];
+            v[u] = cb_min[min(c + u, C - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 2 * QUANT_BATCH; ++u) {
+            r = e[u] > r ? e[u] : r;
+            beta = c + u < C ? beta + v[u] : beta;
+        }
     }
     const int l = scale_exponent(r);
     for (int m = threadIdx.x; m < M; m += 256) {

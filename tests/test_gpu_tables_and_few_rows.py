@@ -216,6 +216,21 @@ def test_table_build_at_tile_edges(mad, shape):
     compare_luts(luts.cpu().numpy(), scale.cpu().numpy(), offset.cpu().numpy(), ref, P, B[:, :M])
 
 
+@pytest.mark.parametrize("C", [1, 15, 16, 17, 33, 255])
+def test_pooled_table_build_around_a_batch_of_codebooks(mad, C):
+    """Whole values, so that the tables are exact; one entry is not a number."""
+    import torch
+    rng = np.random.default_rng(C)
+    P, B = rng.integers(-9, 10, size=(C, 16, 7)).astype(np.float32), rng.integers(-5, 6, size=(7, 11)).astype(np.float32)
+    P[C - 1, 3, 2] = np.nan
+    want_luts, want_scale, want_offset, _, _ = oracle.quantize_luts_pooled(oracle.build_luts_f64(P, B))
+    sd, th = np.zeros((C, 4), np.int32), np.zeros((C, 16), np.float32)
+    luts, scale, offset = mad.maddness_build_luts_pooled(mad.Params(dev(sd), dev(th), dev(P)), dev(B))
+    torch.cuda.synchronize()
+    assert (scale.cpu().numpy() == want_scale).all() and (offset.cpu().numpy() == want_offset).all()
+    assert (luts.cpu().numpy() == want_luts).all()
+
+
 @pytest.mark.parametrize("kind", ["nan", "inf", "mixed"])
 def test_table_build_on_prototypes_that_are_not_numbers(mad, kind):
     """One entry after the other of a table is not a number or infinite: the finite ones keep minimum, range and bytes,
