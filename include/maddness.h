@@ -19,6 +19,10 @@
  *     state between calls (apart from one-time per-process kernel attributes
  *     and the switches of maddness_set_option) and never modifies an input.
  *     Outputs must not alias inputs.
+ *   - Rows of A that are not whole aligned 16-byte pieces may be read in the
+ *     aligned 16-byte pieces that hold an element of them, that is up to 15
+ *     bytes before a row and after it (never on another page than that
+ *     element's).  What those bytes hold does not matter.
  *   - Work is enqueued on the HIP stream given as `stream` (a hipStream_t cast
  *     to void*; NULL is the null stream) and the call returns without
  *     synchronising.
@@ -257,8 +261,7 @@ int maddness_encode_scan_typed(const maddness_params *params, const void *A, int
  *                  holds bucket, value and row number in 64 bits).
  * subspace_bounds  HOST array [C][2]: first and one-past-last column of every codebook,
  *                  0 <= first < last <= D.  A subspace may be at most 128 columns wide
- *                  (MADDNESS_E_UNSUPPORTED beyond; the running sums of a bucket live in
- *                  on-chip memory).
+ *                  (MADDNESS_E_UNSUPPORTED beyond).
  * split_dims       out [C][4], thresholds out [C][16] (slot 15 = 0): as maddness_params
  *                  takes them.
  * train_codes      out [N][C], ONE BYTE per code (not packed): the leaf minus 1 of every
@@ -308,9 +311,10 @@ int maddness_learn_prototypes(const uint8_t *train_codes, const float *A_train, 
  *                              product of the one-hot code matrix of Section 4.3 with
  *                              the tables on the int8 matrix cores).
  *                           2  only the general kernels (any shape, no specialisation).
- * MADDNESS_OPT_PHASED_ROWS  n >= 2: at most n rows per wavefront and region (rounded up to
- *                           a multiple of 256 for A stored by columns) in the kernels that
- *                           work in phases, so that few rows already make many regions;
+ * MADDNESS_OPT_PHASED_ROWS  n >= 2: at most n rows per wavefront and region in the kernels that
+ *                           work in phases, so that few rows already make many regions (A
+ *                           stored by columns: rounded up to a multiple of 256, or, up to
+ *                           131072 rows, 8 n rows per workgroup to one of 64, 128 or 256);
  *                           0: as many as on-chip memory holds.
  * MADDNESS_OPT_COLS_RUN     1, 2 or 4 rows per lane in the by-columns kernels; 0: automatic.
  * MADDNESS_OPT_MAX_WORKGROUPS  n >= 1: the phased kernels launch at most n workgroups, so

@@ -97,22 +97,23 @@ int32_t option(int which);
 // stay testable and comparable).
 bool vector_scan_only();
 
-// The exact scan on the matrix cores (one-hot codes x tables, int8 MFMA): C a multiple
-// of 8 up to 64, many rows.  Same return convention as the row kernels.
+// The exact scan on the matrix cores (one-hot codes x tables, int8 MFMA): up to 64 codebooks,
+// many rows, or any number of them beside large tables.  Same return convention as the row kernels.
 int launch_scan_mfma(int32_t C, int32_t M, const uint8_t *codes, int64_t N, const uint8_t *luts,
                      const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
                      hipStream_t stream);
 
-// Fused encode + exact scan in phases with the scan on the matrix cores (C = 32 or 64,
-// many rows; A row-major of any element type, or stored by columns with N a multiple
-// of 4; C = 16 with row-major fp32 A).  The callers use it for many rows: where the one-kernel-per-wavefront designs
-// are bound by the vector ALUs (tables larger than LDS, narrow element types, A stored by
-// columns), and for C = 16 and 32 in general, because whole-chip read and write phases suit HBM.
+// Fused encode + exact scan in phases with the scan on the matrix cores: row-major A of any
+// element type, alignment and pitch (rows of up to 8 KiB, narrow types 4 KiB, up to 64
+// codebooks), or stored by columns (C = 16, 32 or 64; above 131072 rows C = 32 or 64 and N a multiple
+// of 4).  Taken where the one-kernel-per-wavefront designs are bound by the vector ALUs (narrow element types, A by
+// columns) or walk tables larger than LDS tile by tile (any number of rows), and for many rows of C = 16
+// and 32 in general, because whole-chip read and write phases suit HBM.
 int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
                       const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
                       uint8_t *codes, hipStream_t stream);
 
-// Encode only with the first phase of that kernel (row-major fp32 A, C = 16, 32 or 64, many rows).
+// Encode only with the first phase of that kernel (row-major fp32 A, up to 64 codebooks, many rows).
 int launch_encode_phased(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes,
                          hipStream_t stream);
 

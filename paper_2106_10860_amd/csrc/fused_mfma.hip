@@ -27,8 +27,9 @@
 // wavefronts with double-buffered codes (6.2 ms, whatever the encoders' prefetch
 // depth; only the by-columns input gained, 0.295 against 0.324 ms at N = 2^20,
 // M = 256).  Used for many rows of any type by up to 64 codebooks, for any number of them
-// where the tables are larger than the other kernels take at once, for A stored by columns;
-// and, as its E phase alone, to encode fp32 rows.
+// where the tables are larger than the other kernels take at once (and for many shapes whose
+// tables these still hold: few_rows_in_lds), for A stored by columns (few_columns_in_lds); and,
+// as its E phase alone, to encode fp32 rows.
 #include <algorithm>
 
 #include "cols_common.h"
@@ -92,7 +93,7 @@ constexpr int shared_bytes(int emode, int RPI, int DV, int NT, bool scan, bool g
 // ODD = true (row-major A, with PAD): any shape the tile sizes cover - rows of A that start on any
 // element and end anywhere, any number of codebooks up to C, any M, any pitch
 // and alignment of the outputs.  The E phase reads the aligned 16-byte pieces that cover a row,
-// the tables are read byte by byte, and the S phase writes through LDS (GATHER) - rows without padding
+// the tables are read from any byte on, and the S phase writes through LDS (GATHER) - rows without padding
 // between them as ranges of floats in aligned 16-byte pieces, other rows each as a range of its own
 // (store_dense_rows) - or, for one or two blocks of columns, with 4-byte stores straight from the registers,
 // the wavefronts sharing out the rows (gathered, such narrow outputs would leave the matrix work to one or

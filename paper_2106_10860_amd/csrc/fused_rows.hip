@@ -463,8 +463,8 @@ int launch_fused_rows(const maddness_params &p, const MatrixA &A, int64_t N, int
                        : launch_variant<kFused, 32, 2, 16, 1, false, kU8>(a, 1, stream);
         }
     }
-    // tables larger than LDS: the exact scan runs on the matrix cores; the averaged one,
-    // and few rows, over column tiles in LDS
+    // tables larger than LDS: the exact scan runs on the matrix cores, from the first row on; the averaged one over
+    // column tiles in LDS (the exact one too where the matrix cores are switched off)
     const bool big = (C == 64 && M > 64) || (C == 32 && M > 256);
     if (big && !averaged && !vector_scan_only()) {
         const int rc = launch_fused_mfma(p, A, N, M, luts, scale, offset, out, ldo, acc, codes, stream);

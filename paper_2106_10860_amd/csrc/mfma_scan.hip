@@ -25,7 +25,7 @@ struct MfmaScanArgs {
 // whose rows do not start on 128-byte lines, where the direct stores end inside lines and run
 // at a third to a half of their rate.  All 4 wavefronts take part in every step (barriers).
 // ODD: any number of codebooks up to C (the others padded with zero codes and entries), any M,
-// any pitch and alignment of codes, tables and outputs: codes and tables are read byte by byte,
+// any pitch and alignment of codes, tables and outputs: codes and tables are read from any byte on,
 // rows are written as ranges of floats in aligned 16-byte pieces (store_dense_rows): the 16 or 32
 // consecutive rows of a step as one range when there is no padding between them, else row by row.
 template <int KG, int NT, bool ODD = false>
@@ -286,8 +286,7 @@ int launch_scan_mfma(int32_t C, int32_t M, const uint8_t *codes, int64_t N, cons
                      const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
                      hipStream_t stream)
 {
-    // whole words of packed codes per row; the tables are read once per workgroup, which
-    // only pays with many rows
+    // (the tables are read once per workgroup: from which number of rows on that pays depends on what else holds them)
     if (C > 64 || N < matrix_cores_min_rows(C, M, C == 16 || C == 32)) return 1;
     const int NT = C <= 32 ? 4 : 2;
     MfmaScanArgs a{codes, luts, scale, offset, ScanOut{out, ldo, acc, M}, N, C};

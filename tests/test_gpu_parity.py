@@ -963,8 +963,8 @@ MFMA_SHAPES = [
     (16384, 4, 8), (20001, 100, 16), (16400, 256, 24), (30000, 256, 32), (17000, 300, 32), (16385, 64, 32),
     (16500, 130, 40), (18000, 512, 48), (16390, 34, 56), (20000, 512, 64), (16384, 1000, 64), (70000, 16, 16),
     (16400, 200, 64),   # an odd number of 16-row groups where two are taken per step
-    # any other shape of many rows: the same kernel padded to 16 / 32 / 64 codebooks, codes and tables read byte by
-    # byte, rows written with 4-byte stores
+    # any other shape of many rows: the same kernel padded to 16 / 32 / 64 codebooks, codes and tables from any byte
+    # on, rows written as ranges of floats
     (20000, 250, 30), (16400, 257, 31), (16390, 130, 5), (17000, 18, 33), (16500, 1030, 17), (16385, 66, 63),
     (262144 + 3, 100, 12),
 ]
