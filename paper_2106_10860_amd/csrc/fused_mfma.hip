@@ -767,12 +767,12 @@ bool few_columns_in_lds(int C, int M, int64_t N)
     case 2: return C == 16 || N < 16384;
     case 4: return N < (C == 16 ? 98304 : 65536);
     case 8: return N < (C == 32 && banks ? 24576 : 57344);
+    case 64: return N <= (M < 192 ? 24576 : 16384);
     default: return N < (banks || (C == 16 && lanes == 32) ? 16384 : 24576);
     }
 }
 
 }  // namespace
-    case 64: return N <= (M < 192 ? 24576 : 16384);
 
 // Returns MADDNESS_OK after a launch, 1 if the shape is not covered.
 int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,

@@ -170,9 +170,9 @@ FASTER = [
     ((80000, 40, 8, 16, "f32", True), "scan_kernel"), ((97000, 20, 16, 16, "f16", True), "scan_kernel"),
     ((98304, 20, 16, 16, "f16", True), "fused_mfma"), ((57000, 24, 28, 32, "u8", True), "scan_kernel"),
     ((24576, 24, 32, 32, "f32", True), "fused_mfma"), ((24575, 24, 48, 16, "f32", True), "scan_kernel"),
-    ((8192, 50, 192, 32, "f32", True), "scan_kernel"), ((8193, 50, 192, 32, "bf16", True), "fused_mfma"),
     ((24576, 24, 188, 16, "f32", True), "scan_kernel"), ((24577, 24, 188, 16, "f32", True), "fused_mfma"),
     ((16385, 24, 192, 16, "u8", True), "fused_mfma"), ((16384, 24, 192, 16, "u8", True), "scan_kernel"),
+    ((8192, 50, 192, 32, "f32", True), "scan_kernel"), ((8193, 50, 192, 32, "bf16", True), "fused_mfma"),
     ((300, 50, 584, 16, "f32", True), "scan_kernel"), ((256, 50, 584, 16, "f32", True), "fused_mfma"),
     ((4096, 50, 96, 64, "u8", True), "fused_mfma"),
 ]
