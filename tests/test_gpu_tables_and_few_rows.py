@@ -166,6 +166,7 @@ FASTER = [
     ((53325, 85, 20, 16, "u8", False), "scan_kernel"), ((40000, 716, 5, 4, "u8", False), "scan_kernel"),
     ((33000, 1558, 92, 2, "f16", False), "scan_kernel"), ((40001, 174, 8, 22, "bf16", False), "scan_kernel"),
     ((35000, 426, 42, 53, "u8", False), "fused_mfma"), ((36000, 472, 66, 16, "bf16", False), "fused_mfma"),
+    ((35550, 107, 72, 16, "f16", False), "fused_mfma"), ((34561, 901, 23, 32, "u8", False), "fused_mfma"),
     # A by columns: small tables by the words of their rows, larger ones up to 8192 rows
     ((80000, 40, 8, 16, "f32", True), "scan_kernel"), ((97000, 20, 16, 16, "f16", True), "scan_kernel"),
     ((98304, 20, 16, 16, "f16", True), "fused_mfma"), ((57000, 24, 28, 32, "u8", True), "scan_kernel"),
