@@ -30,12 +30,13 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 // Operand layout of v_mfma_f64_16x16x4_f64: lane l supplies A[i = l % 16][k = l / 16]
 // and B[k = l / 16][j = l % 16]; it receives D[i = 4 r + l / 16][j = l % 16] in
 // accumulator element r = 0..3.
-// Bound by the fp64 matrix cores (2 * 16 C D M flops; 1024 x 512 with 64 codebooks: 15 us at 73 TFLOP/s, which a large
-// product reaches); takes 32 us there.  One codebook and 16 columns to a workgroup, operands straight from memory, took
+// 2 * 16 C D M flops; 1024 x 512 with 64 codebooks: 15 us at the 73 TFLOP/s that a large product reaches; takes 29 us
+// there: two wavefronts to a SIMD, each waiting for its operands from LDS, leave the matrix cores busy 38 % of the time (LDS
+// 16 %, by the counters; 30 % of that conflicts, of writes).  One codebook and 16 columns to a workgroup, operands straight from memory, took
 // 77 us: two loads of 16 rows or 4 rows each per matrix instruction, where staged tiles need 5 reads of LDS for 4 of them.
 constexpr int KSPLIT = 4;
 constexpr int GEMM_COLS = 32, GEMM_DEPTH = 64, GEMM_THREADS = 128 * KSPLIT;
-constexpr int A_PITCH = GEMM_DEPTH + 4, B_PITCH = GEMM_COLS + 16;      // (an operand's 64 values meet in no LDS bank)
+constexpr int A_PITCH = GEMM_DEPTH + 4, B_PITCH = GEMM_COLS + 16;      // (the reads of an operand's 64 values meet in no LDS bank)
 
 template <int RT>
 __global__ __launch_bounds__(GEMM_THREADS) void lut_gemm_kernel(const float *__restrict__ P,
