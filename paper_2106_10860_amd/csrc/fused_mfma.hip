@@ -625,13 +625,14 @@ bool few_rows_in_lds(const RowsArgs &a, int kernel_codebooks, int es, bool any_s
 // rows the general kernel wins or is level (C = 24, M = 200, 75 KiB 13 and 14 us for 1410), and for short rows with next to no
 // entries (C = 22, M = 8, rows of 348 bytes, 124440 of them 24 and 33).  From there on both times are estimated, in us, with
 // costs fitted to 638 drawn shapes of 32768 to 300000 rows: this kernel's within a tenth, the general one's, which depends on
-// what of the rows the caches hold, within a third (with 16 lanes to a row it is the dearer one).  By this rule 861 shapes
-// take 1.02 times as long as with the faster kernel every time, 24 of them over a tenth longer than in the general kernel, 27
-// than here; always the general one 1.34 times, always this one 1.06 times.  Measured, general and here: C = 1, M = 13,
+// what of the rows the caches hold, within a third (with 16 lanes to a row it is the dearer one).  By this rule 917 shapes
+// take 1.02 times as long as with the faster kernel every time, 25 of them over a tenth longer than in the general kernel, 27
+// than here; always the general one 1.36 times, always this one 1.06 times.  Measured, general and here: C = 1, M = 13,
 // bytes, rows of 562, 152670 of them 16 and 35; C = 16, M = 20, rows of 85, 53325 12 and 20; C = 12, M = 216, rows of 160,
 // 252134 86 and 102; C = 2, M = 92, binary16, rows of 3116, 55727 24 and 45; C = 16, M = 64, rows of 512, 32768 25 and 15;
 // C = 16, M = 16, bytes, rows of 1943, 106122 90 and 47; C = 16, M = 17, rows of 1536, 51491 48 and 25; C = 53, M = 42,
-// bytes, rows of 426, 85913 67 and 33; C = 9, M = 240, bytes, rows of 702, 205940 150 and 88.
+// bytes, rows of 426, 85913 67 and 33; C = 9, M = 240, bytes, rows of 702, 205940 150 and 88; C = 4, M = 512, binary16,
+// rows of 128, 131072 111 and 71.
 bool narrow_rows_split_only(const RowsArgs &a, int kernel_codebooks, int es)
 {
     if (a.N < 32768 || (a.D * es < 512 && a.codebooks * (int64_t)a.M < 256)) return true;
@@ -646,7 +647,8 @@ bool narrow_rows_split_only(const RowsArgs &a, int kernel_codebooks, int es)
     // grows with the rows' bytes
     const double turn = 0.64 * code_passes + 0.008 * C * row_passes + (a.M == 4 * lanes ? 0.32 : 0.0) + (odd ? 0.29 : 0.0) +
                         (lanes >= 16 ? 0.19 : 0.0);
-    // rows of the tables that start a multiple of 64 bytes apart; input and results beyond the 256 MB of the last cache
+    // rows of the tables that start a multiple of 64 bytes apart; input and results beyond the 256 MB of the last cache; and it
+    // writes no more than some 2.2 TB/s
     const double slower = (lanes == 1 ? 1.09 : 1.0) * (a.M % 64 == 0 ? 1.17 : 1.0) *
                           (rows * (row_bytes + 4.0 * a.M) > 256e3 ? 1.25 : 1.0);
     const double general = 5.0 + 0.003 * C * a.M + (a.M <= 8 ? 0.26 * C : 0.0) + rows / rows_at_once * turn +
@@ -654,7 +656,7 @@ bool narrow_rows_split_only(const RowsArgs &a, int kernel_codebooks, int es)
                                    7e-3 * C * std::min(1.0, row_bytes / 2048));
     const double here = 10.5 + (es == 1 ? 2.5 : 0.0) +
                         rows * (0.056 + KC * (1.8e-3 + 3.1e-4 * blocks) + 8e-5 * row_bytes + 1.15e-3 * a.M);
-    return slower * general < (lanes == 16 ? 0.75 : 1.05) * here;
+    return std::max(slower * general, 1.82e-3 * rows * a.M) < (lanes == 16 ? 0.75 : 1.05) * here;
 }
 
 template <bool SCAN>
