@@ -759,7 +759,8 @@ int launch_row_major(const RowsArgs &a, int C, int D, const MatrixA &A, hipStrea
 // 45000 and 80000 rows: C = 16, M = 16 1.04, 1.01, 1.01, 0.79 (100000: 1.12), M = 28 0.97, 0.97, 0.92, 1.15, M = 48 0.94, 1.15,
 // 1.87, 2.46, M = 64 1.07, 1.87, 2.52, 2.27; C = 32, M = 20 0.69, 0.75, 0.76, 1.95, M = 48 0.79, 1.02, 1.30, 1.46, M = 100 0.95,
 // 1.19, 1.23, 2.48.  C = 16, M = 140, general and here, 15.2 and 17.3 for 24576, 19.9 and 17.4 for 25000; M = 188 13.3 and 17.1 for
-// 16384, 17.0 and 17.4 for 24576; M = 200 13.9 and 17.5 for 16384, 21.0 and 17.6 for 19000; M = 252 15.3 and 17.6, 18.4 and 17.6.
+// 16384, 17.0 and 17.4 for 24576; M = 200 13.9 and 17.5 for 16384, 21.0 and 17.6 for 19000; M = 252 15.3 and 17.6, 18.4 and 17.6;
+// M = 256 20.1 and 17.0 for 16384.
 bool few_columns_in_lds(int C, int M, int64_t N)
 {
     const int64_t tables = 16 * (int64_t)C * M;
@@ -774,7 +775,7 @@ bool few_columns_in_lds(int C, int M, int64_t N)
     case 2: return C == 16 || N < 16384;
     case 4: return N < (C == 16 ? 98304 : 65536);
     case 8: return N < (C == 32 && banks ? 24576 : 57344);
-    case 64: return N <= (M < 192 ? 24576 : 16384);
+    case 64: return N < (banks ? 16384 : M < 192 ? 24577 : 16385);
     default: return N < (banks || (C == 16 && lanes == 32) ? 16384 : 24576);
     }
 }

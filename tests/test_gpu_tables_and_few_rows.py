@@ -173,6 +173,7 @@ FASTER = [
     ((24576, 24, 32, 32, "f32", True), "fused_mfma"), ((24575, 24, 48, 16, "f32", True), "scan_kernel"),
     ((24576, 24, 188, 16, "f32", True), "scan_kernel"), ((24577, 24, 188, 16, "f32", True), "fused_mfma"),
     ((16385, 24, 192, 16, "u8", True), "fused_mfma"), ((16384, 24, 192, 16, "u8", True), "scan_kernel"),
+    ((16384, 24, 256, 16, "u8", True), "fused_mfma"),
     ((8192, 50, 192, 32, "f32", True), "scan_kernel"), ((8193, 50, 192, 32, "bf16", True), "fused_mfma"),
     ((300, 50, 584, 16, "f32", True), "scan_kernel"), ((256, 50, 584, 16, "f32", True), "fused_mfma"),
     ((4096, 50, 96, 64, "u8", True), "fused_mfma"),
