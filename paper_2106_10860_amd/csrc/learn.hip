@@ -20,19 +20,20 @@
 //   order_rows_kernel    the rows of every bucket listed in row order, the bucket sizes
 //   bucket_loss_kernel   L(j, B) (Section 4.2) for every column j of every bucket, two passes
 //                        over the bucket's own rows
-//   select_kernel        heuristic_select_idxs: the four columns with the largest summed loss
-//   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column (bitonic sort of
+//   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column, heuristic_select_idxs' four
+//                        with the largest summed loss (bitonic sort of
 //                        (value, row) keys: equal values stay in row order, as a stable sort
 //                        of a bucket's rows leaves them)
 //   split_chains_kernel (split_chains_small_kernel), split_losses_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
-//                        running sums at every 32nd row in both directions, then the loss of
-//                        every split, a wavefront per 256 rows
+//                        running sums at every 32nd row in both directions (tile_sums_kernel, scan_groups_kernel
+//                        where any order will do), then the loss of every split, a wavefront per 256 rows
 //   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
 //                        candidates
 //   apply_kernel         apply_split: the next level's buckets
 // Prototypes: cooccurrence_kernel (G^T G), count_codes_kernel, list_codes_kernel and gta_kernel (G^T A~),
 // cholesky_panel_kernel, transpose_factor_kernel (the factor by rows), substitution_kernel; or means_kernel.
 #include "common.h"
+#include "device_common.h"
 
 namespace maddness {
 namespace {
@@ -58,6 +59,9 @@ struct LearnArgs {
     int64_t *bucket_count;  // [C][8]
     int32_t *bucket_start;  // [C][8] where the bucket's rows begin in rows_by_bucket[c]
     int32_t *chunk_count;   // [4][C][kMaxChunks][8] rows of every bucket in every chunk of rows, by level
+    int32_t *range_part;  // [C][kRangeParts][2] what a part of the codebook's values span, see any_order()
+    int32_t *range;       // [C][2] and what all of them do
+    int32_t row_bits;     // N <= 2^row_bits, or more than 53 where any_order() is not to be asked
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
@@ -65,6 +69,8 @@ struct LearnArgs {
     int64_t tile_slots;   // tiles of kSplitRows sorted rows of all buckets of a level, at most
     double *sums;         // [C][4][2][tile_slots][2][dmax] Algorithm 4's running sums before every tile, up and down
     int64_t group_slots;  // groups of kGroupTiles tiles of all buckets of a level, at most
+    double *group_sums;   // [C][4][2][group_slots][2][dmax] the sums before every group, up and down, where any order will do:
+                          // then `sums` has those from the group's first row (up), less those to the tile's last (down)
     double *group_loss;   // [C][4][group_slots] loss of the group's best split
     int32_t *group_at;    // [C][4][group_slots][2] the bucket's row it comes after (-1: none); the group's first split
                           // if its loss is not a number (else -1)
@@ -86,6 +92,28 @@ __global__ void clear_kernel(int32_t *p, int64_t n)
     if (i < n) p[i] = 0;
 }
 
+// Sums whose bits allow any order.  Where all values of a codebook are multiples of one power of two, 2^l, and below another,
+// 2^t, their sums and the sums of their squares over all rows are exact in fp64 as long as 2 (t - l) + log2(N) <= 53, in
+// whatever order they are taken: images, counts, quantised features.  (One bit more of t - l is asked for, so that the same
+// holds of differences of two values.)  range[c]: the largest t as an exponent over that of the smallest fp32 number, and
+// kLeast - l; both 0 where all values are zeros.
+constexpr int kLeast = 512, kNoNumber = 1 << 20, kRangeParts = 256;
+__device__ __forceinline__ bool any_order(const LearnArgs &a, int c)
+{
+    const int top = a.range[2 * c], width = top + a.range[2 * c + 1] - kLeast;
+    return a.row_bits <= 53 && (top == 0 || 2 * (width + 1) + a.row_bits <= 53);
+}
+
+__device__ __forceinline__ void span_of(float x, int &top, int &least)
+{
+    const uint32_t bits = __float_as_uint(x) & 0x7fffffffu, field = bits >> 23;
+    if (bits == 0) return;
+    const int e = field ? (int)field : 1;
+    const uint32_t m = (bits & 0x7fffffu) | (field ? 0x800000u : 0u);
+    top = max(top, field == 255 ? kNoNumber : e + 24);
+    least = max(least, kLeast - (e + __ffs((int)m) - 1));
+}
+
 // The columns of every codebook side by side, each row on a 32-byte (or 64-byte) boundary.  The levels read the rows of a
 // bucket in many orders, a codebook's columns at a time: from here they take whole 16-byte pieces, and the rows of a
 // codebook fit in an XCD's L2 where A does not.  A 16-byte piece to a thread and turn.
@@ -93,7 +121,7 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
 {
     const int c = blockIdx.y, pieces = a.pitch / 4, lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
     float4 *X = reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch);
-    // (a grid of as many threads as pieces would have more than 2^32 from 2^34 values on)
+    int top = 0, least = 0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (a.N + 1) * pieces; i += (int64_t)gridDim.x * 256) {
         const int64_t row = i / pieces;
         const int col = 4 * (int)(i - row * pieces);
@@ -101,7 +129,24 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = row < a.N && col + e < d ? a.A[row * a.lda + lo + col + e] : 0.0f;
         X[i] = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) span_of(v[e], top, least);
     }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        top = max(top, __shfl_xor(top, off));
+        least = max(least, __shfl_xor(least, off));
+    }
+    // (one maximum for all, by atomics, took up to 320 us)
+    __shared__ int32_t part[4][2];
+    if ((threadIdx.x & 63) == 0) {
+        part[threadIdx.x >> 6][0] = top;
+        part[threadIdx.x >> 6][1] = least;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        a.range_part[((size_t)c * kRangeParts + blockIdx.x) * 2 + threadIdx.x] =
+            max(max(part[0][threadIdx.x], part[1][threadIdx.x]), max(part[2][threadIdx.x], part[3][threadIdx.x]));
 }
 
 // The rows of every bucket, in row order (a stable counting sort of the rows by bucket): rows_by_bucket[c]
@@ -126,6 +171,14 @@ __global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int 
     const uint8_t *node = a.node + (size_t)c * N;
     int32_t *out = a.rows_by_bucket + (size_t)c * N;
     if (tid < kSplitBuckets) total[tid] = before[tid] = 0;
+    if (level == 0 && chunk == 0 && tid < 128) {
+        // (gather_columns_kernel's parts: 64 lanes of a wavefront for either half of a range)
+        int most = 0;
+        for (int i = lane; i < kRangeParts; i += 64) most = max(most, a.range_part[((size_t)c * kRangeParts + i) * 2 + wave]);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off));
+        if (lane == 0) a.range[2 * c + wave] = most;
+    }
     __syncthreads();
     if (tid < n_chunks)
         for (int k = 0; k < n_buckets; ++k) {
@@ -483,38 +536,58 @@ __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(con
     if (wave < cols && lane == 0) out[wave] = loss;
 }
 
-// heuristic_select_idxs, and L(B_i) = sum over the columns of L(j, B_i).
-__global__ __launch_bounds__(64) void select_kernel(const LearnArgs a, int n_buckets)
+// heuristic_select_idxs, by one wavefront: candidate q of codebook c, the q-th largest of the columns' losses summed over the
+// buckets (equal losses: the lower column; a loss that is not a number is taken where it is the first column left, as a
+// comparison with it is false).  Every workgroup that sorts a candidate's rows finds out for itself, at the cost of a
+// few reads (a launch of its own: 13 us for 32 codebooks of 16 columns); the first one of a codebook leaves it to the
+// others, with L(B_i) = the sum over the columns of L(j, B_i).
+__device__ __forceinline__ int select_candidate(const LearnArgs &a, int c, int d, int n_buckets, int q)
 {
-    extern __shared__ double total[];   // [dmax]
-    const int c = blockIdx.x;
-    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    const int lane = threadIdx.x & 63;
     const double *cl = a.col_loss + (size_t)c * kSplitBuckets * a.dmax;
-    for (int jj = threadIdx.x; jj < d; jj += 64) {
-        double t = 0.0;
-        for (int b = 0; b < n_buckets; ++b) t += cl[(size_t)b * a.dmax + jj];
-        total[jj] = t;
+    double total[kMaxWidth / 64];
+    bool taken[kMaxWidth / 64];
+#pragma unroll
+    for (int i = 0; i < kMaxWidth / 64; ++i) {
+        const int col = min(lane + 64 * i, d - 1);
+        total[i] = 0.0;
+        for (int b = 0; b < n_buckets; ++b) total[i] += cl[(size_t)b * a.dmax + col];
+        taken[i] = lane + 64 * i >= d;
     }
-    if ((int)threadIdx.x < n_buckets) {
-        double l = 0.0;
-        for (int jj = 0; jj < d; ++jj) l += cl[(size_t)threadIdx.x * a.dmax + jj];
-        a.bucket_loss[c * kSplitBuckets + threadIdx.x] = l;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    const int n_cand = d < kCand ? d : kCand;
-    int pick[kCand];
-    for (int q = 0; q < n_cand; ++q) {
-        int best = -1;
-        for (int jj = 0; jj < d; ++jj) {
-            bool taken = false;
-            for (int p = 0; p < q; ++p) taken |= pick[p] == jj;
-            if (!taken && (best < 0 || total[jj] > total[best])) best = jj;   // equal losses: the lower column
+    int best = 0;
+    for (int k = 0; k <= q; ++k) {
+        int first = kMaxWidth;
+#pragma unroll
+        for (int i = kMaxWidth / 64 - 1; i >= 0; --i) {
+            const unsigned long long open = __ballot(!taken[i]);
+            if (open) first = 64 * i + __ffsll(open) - 1;
         }
-        pick[q] = best;
-        a.cand[c * kCand + q] = best;
+        double most = __shfl(first < 64 ? total[0] : total[1], first & 63);
+        best = first;
+        if (most == most) {
+            int at = kMaxWidth;
+            double mine = 0.0;
+#pragma unroll
+            for (int i = 0; i < kMaxWidth / 64; ++i)
+                if (!taken[i] && total[i] == total[i] && (at == kMaxWidth || total[i] > mine)) {
+                    mine = total[i];
+                    at = lane + 64 * i;
+                }
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const double other = __shfl_xor(mine, off);
+                const int at2 = __shfl_xor(at, off);
+                if (at2 < kMaxWidth && (at == kMaxWidth || other > mine || (other == mine && at2 < at))) {
+                    mine = other;
+                    at = at2;
+                }
+            }
+            best = at;
+        }
+#pragma unroll
+        for (int i = 0; i < kMaxWidth / 64; ++i) taken[i] |= lane + 64 * i == best;
     }
-    a.n_cand[c] = n_cand;
+    return best;
 }
 
 // (bucket, value, row) keys, 3 + 32 + 29 bits: unsigned order = by bucket, then by value, equal values (-0 counts
@@ -564,18 +637,35 @@ constexpr int kSortThreads = kSortChunk / 8;
 __device__ __forceinline__ int sort_place(int i) { return i + (i >> 3); }      // (eight keys side by side meet in no LDS bank)
 constexpr size_t sort_lds_bytes(int64_t chunk) { return sizeof(uint64_t) * (size_t)(chunk + chunk / 8 + 1); }
 
-__global__ __launch_bounds__(kSortThreads) void sort_chunks_kernel(const LearnArgs a, int64_t k_first, int64_t j_first)
+__global__ __launch_bounds__(kSortThreads) void sort_chunks_kernel(const LearnArgs a, int64_t k_first, int64_t j_first, int n_buckets)
 {
     extern __shared__ uint64_t chunk[];
     const int c = blockIdx.z, q = blockIdx.y;
-    if (q >= a.n_cand[c]) return;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (q >= min(kCand, d)) return;
     uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
     const int64_t n = a.Npad;
     const int m = (int)(n < kSortChunk ? n : kSortChunk);   // chunk length
     const int64_t base = (int64_t)blockIdx.x * m;
     const int tid = threadIdx.x;
     if (j_first == 0) {
-        const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch + a.cand[c * kCand + q];
+        int32_t &selected = *reinterpret_cast<int32_t *>(chunk + m + m / 8);       // (past the last key's place)
+        if (tid < 64) {
+            const int best = select_candidate(a, c, d, n_buckets, q);
+            if (tid == 0) {
+                selected = best;
+                if (blockIdx.x == 0) a.cand[c * kCand + q] = best;
+                if (blockIdx.x == 0 && q == 0) a.n_cand[c] = min(kCand, d);
+            }
+        } else if (blockIdx.x == 0 && q == 0 && tid < 64 + n_buckets) {
+            const double *cl = a.col_loss + ((size_t)c * kSplitBuckets + tid - 64) * a.dmax;
+            double l = 0.0;
+#pragma unroll 8
+            for (int jj = 0; jj < d; ++jj) l += cl[jj];
+            a.bucket_loss[c * kSplitBuckets + tid - 64] = l;
+        }
+        __syncthreads();
+        const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch + selected;
         const uint8_t *node = a.node + (size_t)c * a.N;
         for (int i = tid; i < m; i += kSortThreads) {
             const int64_t p = base + i;
@@ -685,7 +775,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows;
-    if (count <= (small_too ? kChainRows : 1)) return;
+    if (count <= (small_too ? kChainRows : 1) || any_order(a, c)) return;
     constexpr int kTiles = kChainRows / kSplitRows;
     const int n_steps = (n_tiles + kTiles - 1) / kTiles;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
@@ -737,7 +827,7 @@ __global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const Learn
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
-    if (count < 2 || count > kChainRows) return;
+    if (count < 2 || count > kChainRows || any_order(a, c)) return;
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows, n_rows = n_tiles * kSplitRows, tid = threadIdx.x;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
@@ -774,6 +864,144 @@ __global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const Learn
                 add_16_in_order(sum[dir], v, one);
                 add_16_in_order(squares[dir], v * v, one);
             }
+    }
+}
+
+// The same sums where any order gives the same bits (any_order): no chain.  tile_sums_kernel adds up every tile by itself, a
+// lane per tile and four columns, and a group's tiles with those before them; scan_groups_kernel does the same for the groups of
+// a bucket.  What comes after a row is what there is less what has come.  Bound by the fetch of rows of 32 bytes in sorted order, most of them from beyond L2.
+// (260100 x 27 whole values, 4 codebooks, the four levels: 0.29 + 0.03 ms, the chains 2.36.  Data that do not qualify pay
+// two launches a level, 5 us each.)
+template <int NC>
+__global__ __launch_bounds__(256) void tile_sums_kernel(const LearnArgs a, int n_buckets)
+{
+    constexpr int kPieces = NC / 4, kAhead = 16, kWaveTiles = 64 / kPieces, kWaveGroups = kWaveTiles / kGroupTiles;
+    __shared__ uint32_t listed[4][kWaveTiles][kSplitRows + 1];
+    const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (q >= a.n_cand[c] || !any_order(a, c)) return;
+    const int piece = lane % kPieces, my_tile = lane / kPieces, tile = my_tile % kGroupTiles;
+    const int64_t group = ((int64_t)(blockIdx.x / a.C) * 4 + wave) * kWaveGroups + my_tile / kGroupTiles;
+    int start = 0, count = 0, at = 0;
+    int64_t slot = 0;
+    for (int k = 0; k < n_buckets; ++k) {
+        const int s = a.bucket_start[c * kSplitBuckets + k], n = (int)a.bucket_count[c * kSplitBuckets + k];
+        const int64_t first = first_group(s, k);
+        if (group >= first && group < first + (n + kGroupRows - 1) / kGroupRows) {
+            start = s;
+            count = n;
+            at = (int)(group - first) * kGroupRows + tile * kSplitRows;
+            slot = first_slot(s, k) + (at / kSplitRows);
+        }
+    }
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], rows = max(0, min(kSplitRows, count - at));
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
+    // two tiles' keys to a load
+#pragma unroll
+    for (int i = 0; i < kWaveTiles; i += 2) {
+        const int from = (i + lane / kSplitRows) * kPieces, r = lane % kSplitRows;
+        const int first = __shfl(start + at, from), n = __shfl(rows, from);
+        const uint32_t row = static_cast<uint32_t>(keys[r < n ? first + r : 0]) & ((1u << kKeyRowBits) - 1u);
+        listed[wave][i + lane / kSplitRows][r] = r < n ? row : (uint32_t)a.N;
+    }
+    wave_lds_fence();
+    const uint32_t *row = listed[wave][my_tile];
+    const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + 4 * piece;
+    const size_t pitch = 2 * (size_t)a.dmax;
+    double *up = a.sums + (((size_t)c * kCand + q) * 2 * a.tile_slots + slot) * pitch + 4 * piece, *down = up + a.tile_slots * pitch;
+    double *all = a.group_sums + (((size_t)c * kCand + q) * 2 * a.group_slots + group) * pitch + 4 * piece;
+    for (int col0 = 0; col0 < d; col0 += NC) {
+        double sum[2][4] = {};
+#pragma unroll
+        for (int i0 = 0; i0 < kSplitRows; i0 += kAhead) {
+            float4 v[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) v[i] = *reinterpret_cast<const float4 *>(X + col0 + (uint64_t)row[i0 + i] * (uint32_t)a.pitch);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const double x[4] = {(double)v[i].x, (double)v[i].y, (double)v[i].z, (double)v[i].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sum[0][e] += x[e];
+                    sum[1][e] = __builtin_fma(x[e], x[e], sum[1][e]);
+                }
+            }
+        }
+#pragma unroll
+        for (int which = 0; which < 2; ++which)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double through = sum[which][e];                    // of the group's tiles up to this one
+#pragma unroll
+                for (int off = 1; off < kGroupTiles; off <<= 1) {
+                    const double other = __shfl_up(through, off * kPieces);
+                    through += tile >= off ? other : 0.0;
+                }
+                if (count == 0 || col0 + 4 * piece + e >= d) continue;
+                const int o = which * a.dmax + col0 + e;
+                if (rows > 0) {
+                    up[o] = through - sum[which][e];
+                    down[o] = -through;
+                }
+                if (tile == kGroupTiles - 1) all[o] = through;
+            }
+    }
+}
+
+// A workgroup per (candidate, bucket) and 16 sums; a thread takes up to kScanGroups groups in a row at a time.
+constexpr int kScanThreads = 64, kScanGroups = 16;
+__global__ __launch_bounds__(16 * kScanThreads) void scan_groups_kernel(const LearnArgs a)
+{
+    __shared__ double part[kScanThreads + 1][16];
+    const int c = blockIdx.x % a.C, q = blockIdx.x / a.C, b = blockIdx.y;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    const int side = threadIdx.x & 15, t = threadIdx.x >> 4, chain = min(16 * (int)blockIdx.z + side, 2 * d - 1);
+    if (q >= a.n_cand[c] || 16 * (int)blockIdx.z >= 2 * d || !any_order(a, c)) return;
+    const bool stored = 16 * (int)blockIdx.z + side < 2 * d;
+    const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
+    const int n_groups = (count + kGroupRows - 1) / kGroupRows;
+    const size_t pitch = 2 * (size_t)a.dmax;
+    double *up = a.group_sums + (((size_t)c * kCand + q) * 2 * a.group_slots + first_group(start, b)) * pitch + chain / d * a.dmax + chain % d;
+    double *down = up + a.group_slots * pitch;
+    double before = 0.0, v[kScanGroups];
+    for (int pass = n_groups > kScanThreads * kScanGroups ? 0 : 1; pass < 2; ++pass) {         // (0: for the sum of all)
+        double total = before;
+        before = 0.0;
+        for (int first = 0; first < n_groups; first += kScanThreads * kScanGroups) {
+            const int here = min(n_groups - first, kScanThreads * kScanGroups), per = (here + kScanThreads - 1) / kScanThreads;
+            const int lo = first + t * per, left = min(first + here - lo, per);
+            double sum = 0.0;
+#pragma unroll
+            for (int i = 0; i < kScanGroups; ++i) {
+                v[i] = up[(size_t)min(lo + i, n_groups - 1) * pitch];
+                v[i] = i < left ? v[i] : 0.0;
+                sum += v[i];
+            }
+            __syncthreads();
+            part[t][side] = sum;
+            __syncthreads();
+            if (t == 0) {
+                double s = 0.0;
+#pragma unroll 16
+                for (int i = 0; i < kScanThreads; ++i) {
+                    const double x = part[i][side];
+                    part[i][side] = s;
+                    s += x;
+                }
+                part[kScanThreads][side] = s;
+            }
+            __syncthreads();
+            double at = before + part[t][side];
+            before += part[kScanThreads][side];
+            if (n_groups <= kScanThreads * kScanGroups) total = before;
+            if (pass == 1 && stored)
+#pragma unroll
+                for (int i = 0; i < kScanGroups; ++i)
+                    if (i < left) {
+                        up[(size_t)(lo + i) * pitch] = at;
+                        down[(size_t)(lo + i) * pitch] = total - at;
+                        at += v[i];
+                    }
+        }
     }
 }
 
@@ -823,6 +1051,9 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
     const int chain_dir = (lane / (2 * NC)) & 1, which = (lane / NC) & 1, chain_col = lane % NC;
     const double *ends = a.sums + ((((size_t)c * kCand + q) * 2 + chain_dir) * a.tile_slots + first_slot(start, b) + tile0) * (2 * a.dmax) +
                          (size_t)which * a.dmax;
+    const bool grouped = any_order(a, c);
+    const double *group_ends = a.group_sums + ((((size_t)c * kCand + q) * 2 + chain_dir) * a.group_slots + group) * (2 * a.dmax) +
+                               (size_t)which * a.dmax;
     // as the terms are taken: going up the sums with row k, going down those of the rows after it (what the split after
     // row k leaves above)
     const int k = lane & (T - 1), dir = lane / T, entry = dir ? T - 1 - k : k + 1;
@@ -841,6 +1072,7 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
         for (int u = 0; u < kPer; ++u)
             v[u] = *reinterpret_cast<const float4 *>(X + col0 + (int64_t)__shfl(my_row, lane / kPieces + u * kRows) * a.pitch);
         end = ends[(size_t)t * (2 * a.dmax) + min(col0 + chain_col, d - 1)];
+        if (grouped) end += group_ends[min(col0 + chain_col, d - 1)];
     };
     uint64_t key = key_of(0), next_key = key_of(1);
     int32_t my_row = row_of(0, key);
@@ -1563,7 +1795,9 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.pitch = a.dmax <= 8 ? 8 : (a.dmax + 15) / 16 * 16;
     a.X = w.take<float>(C * (a.N + 1) * a.pitch);
     a.chunk_count = w.take<int32_t>(4 * C * kMaxChunks * kSplitBuckets);
-    a.node = w.take<uint8_t>(C * a.N);      // (right behind chunk_count: both are cleared together)
+    a.range_part = w.take<int32_t>(2 * C * kRangeParts);
+    a.node = w.take<uint8_t>(C * a.N);      // (right behind chunk_count and range_part: all three are cleared together)
+    a.range = w.take<int32_t>(2 * C);
     a.col_loss = w.take<double>(C * kSplitBuckets * a.dmax);
     a.bucket_loss = w.take<double>(C * kSplitBuckets);
     a.bucket_count = w.take<int64_t>(C * kSplitBuckets);
@@ -1575,6 +1809,7 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.tile_slots = a.N / kSplitRows + kSplitBuckets + 1;
     a.sums = w.take<double>(C * kCand * 2 * a.tile_slots * 2 * a.dmax);
     a.group_slots = a.N / kGroupRows + kSplitBuckets + 1;
+    a.group_sums = w.take<double>(C * kCand * 2 * a.group_slots * 2 * a.dmax);
     a.group_loss = w.take<double>(C * kCand * a.group_slots);
     a.group_at = w.take<int32_t>(C * kCand * a.group_slots * 2);
     a.chosen = w.take<int32_t>(C);
@@ -1659,6 +1894,8 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     const int32_t C = a.C, dmax = a.dmax;
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
+    // (a chain of fewer rows takes no longer than the two launches)
+    a.row_bits = N >= 4096 ? 64 - __builtin_clzll((unsigned long long)(N - 1)) : 64;
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
     hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds);
@@ -1668,7 +1905,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     LAUNCH_OK("launch clear_kernel");
 
     const int64_t pieces = (N + 1) * (a.pitch / 4);
-    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, 1 << 16), C), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, kRangeParts), C), dim3(256), 0, stream, a);
     LAUNCH_OK("launch gather_columns_kernel");
 
     const bool narrow = dmax <= 8;
@@ -1679,11 +1916,9 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
         LAUNCH_OK("launch order_rows_kernel");
         hipLaunchKernelGGL(bucket_loss_kernel, dim3(C, n_buckets, a.pitch / 4), dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a);
         LAUNCH_OK("launch bucket_loss_kernel");
-        hipLaunchKernelGGL(select_kernel, dim3(C), dim3(64), sizeof(double) * dmax, stream, a, n_buckets);
-        LAUNCH_OK("launch select_kernel");
         const int64_t chunk_len = a.Npad < kSortChunk ? a.Npad : kSortChunk;
         const dim3 chunks((unsigned)(a.Npad / chunk_len), kCand, C);
-        hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, (int64_t)2, (int64_t)0);
+        hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, (int64_t)2, (int64_t)0, n_buckets);
         LAUNCH_OK("launch sort_chunks_kernel");
         for (int64_t k = 2 * chunk_len; k <= a.Npad; k <<= 1) {
             for (int64_t j = k >> 1; j >= chunk_len;) {
@@ -1696,7 +1931,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
                 LAUNCH_OK("launch sort_exchange_kernel");
                 j >>= count;
             }
-            hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, k, chunk_len >> 1);
+            hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, k, chunk_len >> 1, n_buckets);
             LAUNCH_OK("launch sort_chunks_kernel");
         }
         // (columns eight or sixteen at a time)
@@ -1716,6 +1951,15 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
             else hipLaunchKernelGGL(split_chains_kernel<16>, chain_groups, dim3(32 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a, small_too);
             LAUNCH_OK("launch split_chains_kernel");
         }
+        if (a.row_bits <= 53) {
+            const int at_once = narrow ? 16 : 8;              // groups to a workgroup
+            const dim3 grid_tiles((unsigned)((a.group_slots + at_once - 1) / at_once * C), kCand);
+            if (narrow) hipLaunchKernelGGL(tile_sums_kernel<8>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
+            else hipLaunchKernelGGL(tile_sums_kernel<16>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch tile_sums_kernel");
+            hipLaunchKernelGGL(scan_groups_kernel, dim3(C * kCand, n_buckets, (2 * dmax + 15) / 16), dim3(16 * kScanThreads), 0, stream, a);
+            LAUNCH_OK("launch scan_groups_kernel");
+        }
         if (narrow) hipLaunchKernelGGL(split_losses_kernel<8>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         else hipLaunchKernelGGL(split_losses_kernel<16>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         LAUNCH_OK("launch split_losses_kernel");
@@ -1730,7 +1974,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
 int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const int32_t *bounds_host, int32_t *split_dims,
                        float *thresholds, uint8_t *codes, void *workspace, hipStream_t stream)
 {
-    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + select_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
+    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_small_kernel + split_chains_kernel + tile_sums_kernel + scan_groups_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
     if (int rc = allow_full_lds<sort_chunks_kernel>(); rc != MADDNESS_OK) return rc;
     for (int32_t c = 0; c < C;) {
         LearnArgs a{};

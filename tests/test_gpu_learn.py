@@ -199,3 +199,30 @@ def test_learner_rejects_bad_arguments(mad):
     assert L.maddness_learn_prototypes(None, A.data_ptr(), 100, 300, 300, 1, b, 1, 1.0, P.data_ptr(), ws.data_ptr(),
                                        ws.numel(), None) == mad.MADDNESS_E_INVAL
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("N, widths, scale, kinds", [
+    (4096, (7, 20), 1.0, "ii"),              # the fewest rows whose sums are taken in any order where that is exact
+    (4097, (3, 4, 5), 0.25, "iri"),          # quarters; a codebook beside them whose sums have to be chains
+    (9000, (40, 17), 1.0, "sw"),             # both signs; values of 17 bits: 2 x 18 + 14 bits, next to the limit
+    (8500, (5, 2), 1.0, "Ww"),               # 20 bits: past it
+    (270000, (2, 3), 1.0, "ci"),             # more groups of 256 rows than a workgroup scans at once; equal rows
+])
+def test_learner_sums_of_whole_values(mad, N, widths, scale, kinds):
+    """Sums that are exact in any order, codebook by codebook, against the oracle's in row order: equal to the bit."""
+    rng = np.random.default_rng(N)
+    draw = {"i": lambda n: rng.integers(0, 256, n), "s": lambda n: rng.integers(-300, 300, n), "w": lambda n: rng.integers(0, 1 << 17, n),
+            "W": lambda n: rng.integers(0, 1 << 20, n), "r": lambda n: np.maximum(rng.standard_normal(n), 0),
+            "c": lambda n: np.where(rng.random(n) < 0.999, 7, 8)}
+    print("case whole values", N, widths, flush=True)
+    A = np.concatenate([draw[k]((N, w)) * scale for w, k in zip(widths, kinds)], 1).astype(np.float32)
+    ends = np.cumsum(widths)
+    subspaces = [(int(e - w), int(e)) for e, w in zip(ends, widths)]
+    sd, th, codes = mad.maddness_learn_trees(dev(A), subspaces)
+    P = mad.maddness_learn_prototypes(codes, dev(A), subspaces)
+    want_sd, want_th, want_codes, _ = oracle.learn_trees(A, subspaces)
+    assert (sd.cpu().numpy() == want_sd).all() and (th.cpu().numpy() == want_th).all()
+    assert (codes.cpu().numpy() == want_codes).all()
+    want = oracle.ridge_prototypes(want_codes, A, 1.0)
+    # the same fp64 operations: the fp32 rounding of either is the other's
+    assert (P.cpu().numpy() == want.astype(np.float32)).all()
