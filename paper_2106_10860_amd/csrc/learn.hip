@@ -3,12 +3,14 @@
 // regression, Section 4.3).  Set-up work, run once per problem; what matters here is that
 // it takes milliseconds instead of seconds and that its decisions can be checked.
 //
-// Every quantity a decision depends on (bucket losses, cumulative SSEs, level losses) is
-// computed in fp64 with the operations in the order Algorithms 2-4 state them - sums over the
-// rows of a bucket run sequentially in sorted (or row) order, sums over the columns of the
-// subspace in column order - so that the trees are reproducible to the bit and do not depend
-// on the launch shape.  The parallelism is ACROSS the independent pieces: codebooks, candidate
-// columns, buckets and columns.  This file is compiled without floating-point contraction.
+// Every decision is the one that fp64 sums with the operations in the order Algorithms 2-4 state
+// them lead to - sums over the rows of a bucket sequentially in sorted (or row) order, sums over the
+// columns of the subspace in column order - so that the trees are reproducible to the bit and
+// do not depend on the launch shape.  Most decisions are made by estimates, sums in any order by all
+// threads with a bound of what both can be off; those that are closer than that, and all where
+// rows are few, by the sums themselves.  There the parallelism is ACROSS the independent pieces:
+// codebooks, candidate columns, buckets and columns.  This file is compiled without floating-point
+// contraction.
 //
 // The serial parts are sums in a given order: chains of additions at the adder's latency over
 // operands that other wavefronts have laid side by side in LDS (or no chain, where a sum's bits
@@ -18,17 +20,17 @@
 // gather_columns_kernel  the columns of every codebook side by side, rows aligned
 // Per level t = 1..4 of all C trees at once:
 //   order_rows_kernel    the rows of every bucket listed in row order, the bucket sizes
+//   loss_parts_kernel, select_kernel  heuristic_select_idxs by estimates: the four columns with the largest summed loss
 //   bucket_loss_kernel   L(j, B) (Section 4.2) for every column j of every bucket, two passes
-//                        over the bucket's own rows
-//   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column, heuristic_select_idxs' four
-//                        with the largest summed loss (bitonic sort of
+//                        over the bucket's own rows (the exact losses, where the estimates are unsure)
+//   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column (bitonic sort of
 //                        (value, row) keys: equal values stay in row order, as a stable sort
 //                        of a bucket's rows leaves them)
-//   split_chains_kernel (split_chains_small_kernel), split_losses_kernel  Algorithm 3 for every bucket of the level: Algorithm 4's
-//                        running sums at every 32nd row in both directions (tile_sums_kernel, scan_groups_kernel
-//                        where any order will do), then the loss of every split, a wavefront per 256 rows
-//   choose_kernel        the best threshold and loss per bucket, Algorithm 2's choice among the
-//                        candidates
+//   tile_sums_kernel, scan_groups_kernel, split_gains_kernel, choose_by_gain_kernel  Algorithm 3 for every bucket and
+//                        Algorithm 2's choice among the candidates by estimates
+//   split_chains_kernel (split_chains_small_kernel), split_losses_kernel, choose_kernel  the same where those are unsure:
+//                        Algorithm 4's running sums at every 32nd row in both directions, the loss of every split, a
+//                        wavefront per 256 rows, the best threshold and loss per bucket
 //   apply_kernel         apply_split: the next level's buckets
 // Prototypes: cooccurrence_kernel (G^T G), count_codes_kernel, list_codes_kernel and gta_kernel (G^T A~),
 // cholesky_panel_kernel, transpose_factor_kernel (the factor by rows), substitution_kernel; or means_kernel.
@@ -55,13 +57,12 @@ struct LearnArgs {
     float *X;             // [C][N + 1][pitch] the codebook's columns of A, then zeros; row N is zeros
     uint8_t *node;        // [C][N] bucket (0-based) of every row in the current level
     double *col_loss;     // [C][8][dmax] L(j, B_i)
-    double *bucket_loss;  // [C][8] L(B_i)
     int64_t *bucket_count;  // [C][8]
     int32_t *bucket_start;  // [C][8] where the bucket's rows begin in rows_by_bucket[c]
     int32_t *chunk_count;   // [4][C][kMaxChunks][8] rows of every bucket in every chunk of rows, by level
     int32_t *range_part;  // [C][kRangeParts][2] what a part of the codebook's values span, see any_order()
     int32_t *range;       // [C][2] and what all of them do
-    int32_t row_bits;     // N <= 2^row_bits, or more than 53 where any_order() is not to be asked
+    int32_t row_bits;     // N <= 2^row_bits
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
@@ -69,8 +70,16 @@ struct LearnArgs {
     int64_t tile_slots;   // tiles of kSplitRows sorted rows of all buckets of a level, at most
     double *sums;         // [C][4][2][tile_slots][2][dmax] Algorithm 4's running sums before every tile, up and down
     int64_t group_slots;  // groups of kGroupTiles tiles of all buckets of a level, at most
-    double *group_sums;   // [C][4][2][group_slots][2][dmax] the sums before every group, up and down, where any order will do:
-                          // then `sums` has those from the group's first row (up), less those to the tile's last (down)
+    // what the estimates leave (the tiles' sums lie in `sums`, [C][4][2 tile_slots][2 dmax] or less of it, as [slot][dmax])
+    int64_t part_slots;   // parts of kPartRows rows of all buckets of a level, at most
+    double *parts;        // [C][part_slots][5][dmax] of a part's values x, the pivot taken off (y): sum y, sum y^2, sum x^2,
+                          // the least and the largest x
+    double *energy;       // [C][8] the sum of the squares of a bucket's values, or a little more
+    int32_t *unsure;      // [C][2] whether the candidates, and the split, take exact sums to tell
+    double *group_sums;   // [C][4][group_slots][dmax] the sums of the rows of a bucket before every group
+    double *totals;       // [C][4][8][dmax] and of all its rows
+    double *group_gain;   // [C][4][group_slots][2] the largest gain of a split in the group (-1: no split), the second largest
+    int32_t *group_first; // [C][4][group_slots] the bucket's row that the best one comes after
     double *group_loss;   // [C][4][group_slots] loss of the group's best split
     int32_t *group_at;    // [C][4][group_slots][2] the bucket's row it comes after (-1: none); the group's first split
                           // if its loss is not a number (else -1)
@@ -81,9 +90,13 @@ struct LearnArgs {
     int32_t codes_pitch;
 };
 
-__global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst)
+// (unsure: the flags of LearnArgs, set where no estimates will be made, or null)
+__global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst, int32_t *unsure)
 {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = b.v[i];
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        dst[i] = b.v[i];
+        if (unsure) unsure[i] = 1;
+    }
 }
 
 __global__ void clear_kernel(int32_t *p, int64_t n)
@@ -101,7 +114,7 @@ constexpr int kLeast = 512, kNoNumber = 1 << 20, kRangeParts = 256;
 __device__ __forceinline__ bool any_order(const LearnArgs &a, int c)
 {
     const int top = a.range[2 * c], width = top + a.range[2 * c + 1] - kLeast;
-    return a.row_bits <= 53 && (top == 0 || 2 * (width + 1) + a.row_bits <= 53);
+    return top == 0 || 2 * (width + 1) + a.row_bits <= 53;
 }
 
 __device__ __forceinline__ void span_of(float x, int &top, int &least)
@@ -495,10 +508,12 @@ __device__ __forceinline__ void add_chained(double &s, const double (&t)[4])
 // column, four columns of a bucket to a workgroup.  (Measured, the four levels of 260100 x 27 with 4 codebooks, whole
 // values: 1.65 ms; 3.3 ms with four chains to a wavefront and 14.6 ms with a lane per chain that read and converted its
 // values itself.  20000 x 512 with 32, of both signs, whose first sum takes the chain: 0.31, 0.39 and 1.75 ms.)
-__global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(const LearnArgs a)
+// For the candidates (which: 0) or the losses of buckets that cannot be split (1), where the estimates are not enough.
+__global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(const LearnArgs a, int which)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int c = blockIdx.x, b = blockIdx.y, col0 = blockIdx.z * 4;
+    if (!a.unsure[2 * c + which]) return;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b];
@@ -536,15 +551,251 @@ __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(con
     if (wave < cols && lane == 0) out[wave] = loss;
 }
 
-// heuristic_select_idxs, by one wavefront: candidate q of codebook c, the q-th largest of the columns' losses summed over the
-// buckets (equal losses: the lower column; a loss that is not a number is taken where it is the first column left, as a
-// comparison with it is false).  Every workgroup that sorts a candidate's rows finds out for itself, at the cost of a
-// few reads (a launch of its own: 13 us for 32 codebooks of 16 columns); the first one of a codebook leaves it to the
-// others, with L(B_i) = the sum over the columns of L(j, B_i).
-__device__ __forceinline__ int select_candidate(const LearnArgs &a, int c, int d, int n_buckets, int q)
+// Estimates, and when they are enough.  What comes out of a level is a column and its thresholds, whole choices: the largest of
+// some losses, the least of others.  Sums in any order, of which there is no chain, name the same one as the sums in Algorithms
+// 3 and 4's order wherever the next best is further away than both can be off; where it is not (ties, infinities), the
+// codebook is marked unsure and goes the way of the exact sums.  With u = 2^-53, n rows and S the sum of the squares of a
+// bucket's values, over all columns where several are summed, a chain of n additions is off by n u of the sum of
+// its terms' sizes at most, one of h by h u, and sums over rows are at most sqrt(n S) (Cauchy-Schwarz).
+//
+// L(j, B).  As the exact kernel computes it: the mean is off by (n + 2) u sum|x| / n, which adds n times its square to the
+// loss, and the sum of squares by (n + 3) u of itself.  As sum y^2 - (sum y)^2 / n with y = x - p for a p among the values:
+// (3 n + 12) u sum y^2.  Together less than (4 n + 16) u Sy + (n + 2)^2 2^-104 (Sy + n p^2), the sum over the
+// buckets 16 u Sy more; loss_error is twice that.  (0 for a column of zeros, whose loss is 0 either way.)
+__device__ __forceinline__ double loss_error(double n, double sy, double p)
+{
+    return (8.0 * n + 64.0) * 0x1p-53 * sy + (n + 2.0) * (n + 2.0) * 0x1p-103 * (sy + n * p * p);
+}
+
+// The split's loss.  In Algorithm 4's order a column's two halves are off by (3 n + 4) u of their squares' sum, their sum over d
+// columns by d + 2 of it more.  Here it is a constant less the gain  sum_j w_j^2 n / (n1 n2),  w_j = s_j - n1 T_j / n, from
+// sums s_j, T_j that are off by h u sum|x| with h <= 256 + N / 2^18 (32 rows, 8 tiles, the scan of the groups): |w_j| n / (n1 n2) is
+// at most 2 sqrt(S_j), so the gain is off by 8 h sqrt(n) u S, and some 100 u S for its products and sums.  Sums that are
+// exact in any order (any_order) leave d + 8 and 16 sqrt(n).  energy: S.
+__device__ __forceinline__ double split_error(const LearnArgs &a, double n, double energy, int d, bool exact_sums)
+{
+    const double root = sqrt(n);
+    const double units = exact_sums ? 64.0 * root : 8.0 * n + 8.0 * (256.0 + (double)a.N * 0x1p-18) * root;
+    return (units + 16.0 * d + 1024.0) * 0x1p-53 * energy;
+}
+
+// A workgroup per kPartRows rows of a bucket, in row order: what the estimates of L(j, B) take, column by column.  (With
+// select_kernel, the four levels of 260100 x 27: 0.11 ms against 1.60 for bucket_loss_kernel; 20000 x 512: 0.10 and 0.31.)
+constexpr int kPartRows = 1024, kPartValues = 5;
+__device__ __forceinline__ int64_t first_part(int32_t start, int bucket) { return start / kPartRows + bucket; }
+
+template <int NC>
+__global__ __launch_bounds__(256) void loss_parts_kernel(const LearnArgs a, int n_buckets)
+{
+    constexpr int kPieces = NC / 4, kRows = 256 / kPieces, kPer = kPartRows / kRows, kAhead = 8;
+    __shared__ double from_wave[4][kPieces][4][kPartValues];
+    const int c = blockIdx.x % a.C, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t part = blockIdx.x / a.C;
+    int start = 0, count = 0, at = 0;
+    for (int k = 0; k < n_buckets; ++k) {
+        const int s = a.bucket_start[c * kSplitBuckets + k], n = (int)a.bucket_count[c * kSplitBuckets + k];
+        const int64_t first = first_part(s, k);
+        if (part >= first && part < first + (n + kPartRows - 1) / kPartRows) {
+            start = s;
+            count = n;
+            at = (int)(part - first) * kPartRows;
+        }
+    }
+    if (count == 0) return;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], piece = tid % kPieces;
+    const int32_t *list = a.rows_by_bucket + (size_t)c * a.N + start;
+    const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + 4 * piece;
+    double *out = a.parts + ((size_t)c * a.part_slots + part) * kPartValues * a.dmax;
+    const uint32_t pivot = list[count / 2];
+    uint32_t row[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) row[i] = list[min(at + i * kRows + tid / kPieces, count - 1)];
+    for (int col0 = 0; col0 < d; col0 += NC) {
+        const float4 p4 = *reinterpret_cast<const float4 *>(X + col0 + (uint64_t)pivot * (uint32_t)a.pitch);
+        const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+        double y1[4] = {}, y2[4] = {}, x2[4] = {};
+        float least[4], most[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) least[e] = most[e] = p[e];
+#pragma unroll
+        for (int i0 = 0; i0 < kPer; i0 += kAhead) {
+            float4 v[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) v[i] = *reinterpret_cast<const float4 *>(X + col0 + (uint64_t)row[i0 + i] * (uint32_t)a.pitch);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const bool here = at + (i0 + i) * kRows + tid / kPieces < count;
+                const float x4[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double x = here ? (double)x4[e] : 0.0, y = here ? (double)x4[e] - (double)p[e] : 0.0;
+                    y1[e] += y;
+                    y2[e] = __builtin_fma(y, y, y2[e]);
+                    x2[e] = __builtin_fma(x, x, x2[e]);
+                    least[e] = fminf(least[e], here ? x4[e] : p[e]);
+                    most[e] = fmaxf(most[e], here ? x4[e] : p[e]);
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int off = kPieces; off < 64; off <<= 1) {
+                y1[e] += __shfl_xor(y1[e], off);
+                y2[e] += __shfl_xor(y2[e], off);
+                x2[e] += __shfl_xor(x2[e], off);
+                least[e] = fminf(least[e], __shfl_xor(least[e], off));
+                most[e] = fmaxf(most[e], __shfl_xor(most[e], off));
+            }
+            if (lane < kPieces) {
+                double *to = from_wave[wave][lane][e];
+                to[0] = y1[e];
+                to[1] = y2[e];
+                to[2] = x2[e];
+                to[3] = (double)least[e];
+                to[4] = (double)most[e];
+            }
+        }
+        __syncthreads();
+        if (tid < NC * kPartValues) {
+            const int value = tid / NC, col = tid % NC;
+            double v[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v[w] = from_wave[w][col / 4][col % 4][value];
+            const double r = value < 3 ? (v[0] + v[1]) + (v[2] + v[3])
+                                       : value == 3 ? fmin(fmin(v[0], v[1]), fmin(v[2], v[3])) : fmax(fmax(v[0], v[1]), fmax(v[2], v[3]));
+            if (col0 + col < d) out[value * a.dmax + col0 + col] = r;
+        }
+        __syncthreads();
+    }
+}
+
+// The candidate that is `rank` largest losses down, by one wavefront: total[col] is the loss of column lane + 64 i, taken[i]
+// whether a candidate of lower rank has the column (or there is none).  Equal losses: the lower column; a loss that is not a
+// number is taken where it is the first column left, as a comparison with it is false.
+__device__ __forceinline__ int largest_left(const double (&total)[kMaxWidth / 64], bool (&taken)[kMaxWidth / 64])
 {
     const int lane = threadIdx.x & 63;
+    int first = kMaxWidth;
+#pragma unroll
+    for (int i = kMaxWidth / 64 - 1; i >= 0; --i) {
+        const unsigned long long open = __ballot(!taken[i]);
+        if (open) first = 64 * i + __ffsll(open) - 1;
+    }
+    const double of_first = first < 64 ? __shfl(total[0], first & 63) : __shfl(total[1], first & 63);
+    int best = first;
+    if (of_first == of_first) {
+        int at = kMaxWidth;
+        double mine = 0.0;
+#pragma unroll
+        for (int i = 0; i < kMaxWidth / 64; ++i)
+            if (!taken[i] && total[i] == total[i] && (at == kMaxWidth || total[i] > mine)) {
+                mine = total[i];
+                at = lane + 64 * i;
+            }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double other = __shfl_xor(mine, off);
+            const int at2 = __shfl_xor(at, off);
+            if (at2 < kMaxWidth && (at == kMaxWidth || other > mine || (other == mine && at2 < at))) {
+                mine = other;
+                at = at2;
+            }
+        }
+        best = at;
+    }
+#pragma unroll
+    for (int i = 0; i < kMaxWidth / 64; ++i) taken[i] |= lane + 64 * i == best;
+    return best;
+}
+
+// heuristic_select_idxs from the estimates: the four columns with the largest losses summed over the buckets, largest first,
+// and whether the estimates can tell.  A workgroup per codebook, its 8 wavefronts shared out among the buckets.
+__global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_buckets)
+{
+    __shared__ double from_wave[8][16][kPartValues], loss[kMaxWidth], error[kMaxWidth], energy[kSplitBuckets];
+    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], b = wave % n_buckets, share = wave / n_buckets, shares = 8 / n_buckets;
+    const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
+    const int n_parts = (count + kPartRows - 1) / kPartRows, col = lane & 15;
+    if (tid < kMaxWidth) loss[tid] = error[tid] = 0.0;
+    if (tid < kSplitBuckets) energy[tid] = 0.0;
+    for (int col0 = 0; col0 < d; col0 += 16) {
+        const double *in = a.parts + ((size_t)c * a.part_slots + first_part(start, b)) * kPartValues * a.dmax + min(col0 + col, d - 1);
+        double sum[3] = {0.0, 0.0, 0.0};
+        for (int i = 4 * share + lane / 16; i < n_parts; i += 4 * shares)
+#pragma unroll
+            for (int v = 0; v < 3; ++v) sum[v] += in[((size_t)i * kPartValues + v) * a.dmax];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            sum[v] += __shfl_xor(sum[v], 16);
+            sum[v] += __shfl_xor(sum[v], 32);
+            if (lane < 16) from_wave[wave][lane][v] = sum[v];
+        }
+        __syncthreads();
+        // (a thread per column: the buckets one after the other)
+        if (tid < 16 && col0 + tid < d)
+            for (int k = 0; k < n_buckets; ++k) {
+                const int n = (int)a.bucket_count[c * kSplitBuckets + k];
+                if (n == 0) continue;
+                double y1 = 0.0, y2 = 0.0, x2 = 0.0;
+                for (int w = k; w < 8; w += n_buckets) {
+                    y1 += from_wave[w][tid][0];
+                    y2 += from_wave[w][tid][1];
+                    x2 += from_wave[w][tid][2];
+                }
+                const int32_t pivot = a.rows_by_bucket[(size_t)c * a.N + a.bucket_start[c * kSplitBuckets + k] + n / 2];
+                const double p = (double)a.X[((size_t)c * (a.N + 1) + pivot) * a.pitch + col0 + tid];
+                if (n > 1) {                                  // (a row alone: no loss)
+                    loss[col0 + tid] += fmax(y2 - y1 * y1 / (double)n, 0.0);
+                    error[col0 + tid] += loss_error((double)n, y2, p);
+                    from_wave[k][tid][2] = x2;
+                } else {
+                    from_wave[k][tid][2] = x2;
+                }
+            }
+        __syncthreads();
+        if (tid < n_buckets && a.bucket_count[c * kSplitBuckets + tid] > 0)
+            for (int k = 0; k < min(16, d - col0); ++k) energy[tid] += from_wave[tid][k][2];
+        __syncthreads();
+    }
+    if (tid < n_buckets) a.energy[c * kSplitBuckets + tid] = energy[tid] * 1.0001;
+    if (wave != 0) return;
+    double total[kMaxWidth / 64], off_by[kMaxWidth / 64];
+    bool taken[kMaxWidth / 64];
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < kMaxWidth / 64; ++i) {
+        taken[i] = lane + 64 * i >= d;
+        total[i] = loss[lane + 64 * i];
+        off_by[i] = error[lane + 64 * i];
+        finite &= total[i] < __builtin_inf() && off_by[i] < __builtin_inf();
+    }
+    for (int k = 0; k < n_buckets; ++k) finite &= energy[k] < __builtin_inf();
+    bool sure = !__ballot(!finite);
+    const int n_cand = min(kCand, d);
+    for (int k = 0; k < n_cand; ++k) {
+        const int best = largest_left(total, taken);
+        const double least = loss[best & (kMaxWidth - 1)] - error[best & (kMaxWidth - 1)];
+        // (columns of zeros alone have no error: their losses are equal, in column order)
+        bool less = true;
+#pragma unroll
+        for (int i = 0; i < kMaxWidth / 64; ++i)
+            less &= taken[i] || total[i] + off_by[i] < least || (off_by[i] == 0.0 && error[best & (kMaxWidth - 1)] == 0.0);
+        if (__ballot(!less)) sure = false;
+        if (lane == 0) a.cand[c * kCand + k] = best;
+    }
+    if (lane == 0) {
+        a.n_cand[c] = n_cand;
+        a.unsure[2 * c] = sure ? 0 : 1;
+    }
+}
+
+// The same from the exact losses: candidate q.  Every workgroup that sorts a candidate's rows finds out for itself.
+__device__ __forceinline__ int select_candidate(const LearnArgs &a, int c, int d, int n_buckets, int q)
+{
     const double *cl = a.col_loss + (size_t)c * kSplitBuckets * a.dmax;
+    const int lane = threadIdx.x & 63;
     double total[kMaxWidth / 64];
     bool taken[kMaxWidth / 64];
 #pragma unroll
@@ -555,38 +806,7 @@ __device__ __forceinline__ int select_candidate(const LearnArgs &a, int c, int d
         taken[i] = lane + 64 * i >= d;
     }
     int best = 0;
-    for (int k = 0; k <= q; ++k) {
-        int first = kMaxWidth;
-#pragma unroll
-        for (int i = kMaxWidth / 64 - 1; i >= 0; --i) {
-            const unsigned long long open = __ballot(!taken[i]);
-            if (open) first = 64 * i + __ffsll(open) - 1;
-        }
-        double most = __shfl(first < 64 ? total[0] : total[1], first & 63);
-        best = first;
-        if (most == most) {
-            int at = kMaxWidth;
-            double mine = 0.0;
-#pragma unroll
-            for (int i = 0; i < kMaxWidth / 64; ++i)
-                if (!taken[i] && total[i] == total[i] && (at == kMaxWidth || total[i] > mine)) {
-                    mine = total[i];
-                    at = lane + 64 * i;
-                }
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const double other = __shfl_xor(mine, off);
-                const int at2 = __shfl_xor(at, off);
-                if (at2 < kMaxWidth && (at == kMaxWidth || other > mine || (other == mine && at2 < at))) {
-                    mine = other;
-                    at = at2;
-                }
-            }
-            best = at;
-        }
-#pragma unroll
-        for (int i = 0; i < kMaxWidth / 64; ++i) taken[i] |= lane + 64 * i == best;
-    }
+    for (int k = 0; k <= q; ++k) best = largest_left(total, taken);
     return best;
 }
 
@@ -649,22 +869,23 @@ __global__ __launch_bounds__(kSortThreads) void sort_chunks_kernel(const LearnAr
     const int64_t base = (int64_t)blockIdx.x * m;
     const int tid = threadIdx.x;
     if (j_first == 0) {
-        int32_t &selected = *reinterpret_cast<int32_t *>(chunk + m + m / 8);       // (past the last key's place)
-        if (tid < 64) {
-            const int best = select_candidate(a, c, d, n_buckets, q);
-            if (tid == 0) {
-                selected = best;
-                if (blockIdx.x == 0) a.cand[c * kCand + q] = best;
-                if (blockIdx.x == 0 && q == 0) a.n_cand[c] = min(kCand, d);
+        int selected;
+        if (a.unsure[2 * c]) {
+            // (what the estimates left in cand is not read)
+            int32_t &shared = *reinterpret_cast<int32_t *>(chunk + m + m / 8);       // (past the last key's place)
+            if (tid < 64) {
+                const int best = select_candidate(a, c, d, n_buckets, q);
+                if (tid == 0) shared = best;
+                if (tid == 0 && blockIdx.x == 0) {
+                    a.cand[c * kCand + q] = best;
+                    a.n_cand[c] = min(kCand, d);
+                }
             }
-        } else if (blockIdx.x == 0 && q == 0 && tid < 64 + n_buckets) {
-            const double *cl = a.col_loss + ((size_t)c * kSplitBuckets + tid - 64) * a.dmax;
-            double l = 0.0;
-#pragma unroll 8
-            for (int jj = 0; jj < d; ++jj) l += cl[jj];
-            a.bucket_loss[c * kSplitBuckets + tid - 64] = l;
+            __syncthreads();
+            selected = shared;
+        } else {
+            selected = a.cand[c * kCand + q];
         }
-        __syncthreads();
         const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch + selected;
         const uint8_t *node = a.node + (size_t)c * a.N;
         for (int i = tid; i < m; i += kSortThreads) {
@@ -775,7 +996,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows;
-    if (count <= (small_too ? kChainRows : 1) || any_order(a, c)) return;
+    if (count <= (small_too ? kChainRows : 1) || !a.unsure[2 * c + 1]) return;
     constexpr int kTiles = kChainRows / kSplitRows;
     const int n_steps = (n_tiles + kTiles - 1) / kTiles;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
@@ -827,7 +1048,7 @@ __global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const Learn
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
-    if (count < 2 || count > kChainRows || any_order(a, c)) return;
+    if (count < 2 || count > kChainRows || !a.unsure[2 * c + 1]) return;
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows, n_rows = n_tiles * kSplitRows, tid = threadIdx.x;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
@@ -867,50 +1088,74 @@ __global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const Learn
     }
 }
 
-// The same sums where any order gives the same bits (any_order): no chain.  tile_sums_kernel adds up every tile by itself, a
-// lane per tile and four columns, and a group's tiles with those before them; scan_groups_kernel does the same for the groups of
-// a bucket.  What comes after a row is what there is less what has come.  Bound by the fetch of rows of 32 bytes in sorted order, most of them from beyond L2.
-// (260100 x 27 whole values, 4 codebooks, the four levels: 0.29 + 0.03 ms, the chains 2.36.  Data that do not qualify pay
-// two launches a level, 5 us each.)
+// The estimates' sums, in three steps: tile_sums_kernel adds up every tile by itself, a lane per tile and four columns, and a
+// group's tiles with those before them; scan_groups_kernel does the same for the groups of a bucket; split_gains_kernel walks
+// every tile from there.  Bound by the fetch of rows in sorted order (32 bytes each for up to 8 columns, mostly from beyond L2
+// where a codebook's columns take more than 4 MiB).  The four levels, these three kernels, against the two of exact sums:
+// 20000 x 512 with 32 codebooks 0.12 + 0.04 + 0.18 ms, 0.62 + 0.44; 260100 x 27 with 4 0.20 + 0.03 + 0.26, 2.36 + 0.42.
+// where the rows of the wavefront's groups come from: the rows of its tiles, listed in LDS, and where the lane's own lie
 template <int NC>
-__global__ __launch_bounds__(256) void tile_sums_kernel(const LearnArgs a, int n_buckets)
+struct GroupRows {
+    static constexpr int kPieces = NC / 4, kTiles = 64 / kPieces, kGroups = kTiles / kGroupTiles;
+    int b, start, count, at, rows;           // the bucket, its first row and its rows (0: no such group), the tile's first, its rows
+    int64_t group;
+    uint32_t splits;                         // bit i: a split between row i of the tile and the next is one
+};
+
+template <int NC>
+__device__ __forceinline__ GroupRows<NC> list_group_rows(const LearnArgs &a, int c, int q, int n_buckets, uint32_t (*listed)[kSplitRows + 1])
 {
-    constexpr int kPieces = NC / 4, kAhead = 16, kWaveTiles = 64 / kPieces, kWaveGroups = kWaveTiles / kGroupTiles;
-    __shared__ uint32_t listed[4][kWaveTiles][kSplitRows + 1];
-    const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (q >= a.n_cand[c] || !any_order(a, c)) return;
-    const int piece = lane % kPieces, my_tile = lane / kPieces, tile = my_tile % kGroupTiles;
-    const int64_t group = ((int64_t)(blockIdx.x / a.C) * 4 + wave) * kWaveGroups + my_tile / kGroupTiles;
-    int start = 0, count = 0, at = 0;
-    int64_t slot = 0;
+    using G = GroupRows<NC>;
+    G g;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, my_tile = lane / G::kPieces, tile = my_tile % kGroupTiles;
+    g.group = ((int64_t)(blockIdx.x / a.C) * 4 + wave) * G::kGroups + my_tile / kGroupTiles;
+    g.b = g.start = g.count = g.at = 0;
     for (int k = 0; k < n_buckets; ++k) {
         const int s = a.bucket_start[c * kSplitBuckets + k], n = (int)a.bucket_count[c * kSplitBuckets + k];
         const int64_t first = first_group(s, k);
-        if (group >= first && group < first + (n + kGroupRows - 1) / kGroupRows) {
-            start = s;
-            count = n;
-            at = (int)(group - first) * kGroupRows + tile * kSplitRows;
-            slot = first_slot(s, k) + (at / kSplitRows);
+        if (g.group >= first && g.group < first + (n + kGroupRows - 1) / kGroupRows) {
+            g.b = k;
+            g.start = s;
+            g.count = n;
+            g.at = (int)(g.group - first) * kGroupRows + tile * kSplitRows;
         }
     }
-    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], rows = max(0, min(kSplitRows, count - at));
+    g.rows = max(0, min(kSplitRows, g.count - g.at));
+    g.splits = 0;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
     // two tiles' keys to a load
 #pragma unroll
-    for (int i = 0; i < kWaveTiles; i += 2) {
-        const int from = (i + lane / kSplitRows) * kPieces, r = lane % kSplitRows;
-        const int first = __shfl(start + at, from), n = __shfl(rows, from);
-        const uint32_t row = static_cast<uint32_t>(keys[r < n ? first + r : 0]) & ((1u << kKeyRowBits) - 1u);
-        listed[wave][i + lane / kSplitRows][r] = r < n ? row : (uint32_t)a.N;
+    for (int i = 0; i < G::kTiles; i += 2) {
+        const int from = (i + lane / kSplitRows) * G::kPieces, r = lane % kSplitRows;
+        const int first = __shfl(g.start + g.at, from), left = __shfl(g.count - g.at, from);
+        const uint64_t key = keys[r < left ? first + r : 0], next = keys[r + 1 < left ? first + r + 1 : 0];
+        listed[i + lane / kSplitRows][r] = r < left ? static_cast<uint32_t>(key) & ((1u << kKeyRowBits) - 1u) : (uint32_t)a.N;
+        const unsigned long long here = __ballot(r + 1 < left && key_value(key) < key_value(next));
+        if (my_tile == i) g.splits = (uint32_t)here;
+        if (my_tile == i + 1) g.splits = (uint32_t)(here >> 32);
     }
     wave_lds_fence();
-    const uint32_t *row = listed[wave][my_tile];
+    return g;
+}
+
+template <int NC>
+__global__ __launch_bounds__(256) void tile_sums_kernel(const LearnArgs a, int n_buckets)
+{
+    using G = GroupRows<NC>;
+    constexpr int kAhead = 16;
+    __shared__ uint32_t listed[4][G::kTiles][kSplitRows + 1];
+    const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (q >= a.n_cand[c]) return;
+    const int piece = lane % G::kPieces, tile = lane / G::kPieces % kGroupTiles;
+    const G g = list_group_rows<NC>(a, c, q, n_buckets, listed[wave]);
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    const uint32_t *row = listed[wave][lane / G::kPieces];
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + 4 * piece;
-    const size_t pitch = 2 * (size_t)a.dmax;
-    double *up = a.sums + (((size_t)c * kCand + q) * 2 * a.tile_slots + slot) * pitch + 4 * piece, *down = up + a.tile_slots * pitch;
-    double *all = a.group_sums + (((size_t)c * kCand + q) * 2 * a.group_slots + group) * pitch + 4 * piece;
+    double *before = a.sums + ((size_t)c * kCand + q) * 4 * a.tile_slots * a.dmax +
+                     (size_t)(first_slot(g.start, g.b) + g.at / kSplitRows) * a.dmax + 4 * piece;
+    double *all = a.group_sums + (((size_t)c * kCand + q) * a.group_slots + g.group) * a.dmax + 4 * piece;
     for (int col0 = 0; col0 < d; col0 += NC) {
-        double sum[2][4] = {};
+        double sum[4] = {};
 #pragma unroll
         for (int i0 = 0; i0 < kSplitRows; i0 += kAhead) {
             float4 v[kAhead];
@@ -918,91 +1163,268 @@ __global__ __launch_bounds__(256) void tile_sums_kernel(const LearnArgs a, int n
             for (int i = 0; i < kAhead; ++i) v[i] = *reinterpret_cast<const float4 *>(X + col0 + (uint64_t)row[i0 + i] * (uint32_t)a.pitch);
 #pragma unroll
             for (int i = 0; i < kAhead; ++i) {
-                const double x[4] = {(double)v[i].x, (double)v[i].y, (double)v[i].z, (double)v[i].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    sum[0][e] += x[e];
-                    sum[1][e] = __builtin_fma(x[e], x[e], sum[1][e]);
-                }
+                sum[0] += (double)v[i].x;
+                sum[1] += (double)v[i].y;
+                sum[2] += (double)v[i].z;
+                sum[3] += (double)v[i].w;
             }
         }
 #pragma unroll
-        for (int which = 0; which < 2; ++which)
+        for (int e = 0; e < 4; ++e) {
+            double through = sum[e];                               // of the group's tiles up to this one
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                double through = sum[which][e];                    // of the group's tiles up to this one
-#pragma unroll
-                for (int off = 1; off < kGroupTiles; off <<= 1) {
-                    const double other = __shfl_up(through, off * kPieces);
-                    through += tile >= off ? other : 0.0;
-                }
-                if (count == 0 || col0 + 4 * piece + e >= d) continue;
-                const int o = which * a.dmax + col0 + e;
-                if (rows > 0) {
-                    up[o] = through - sum[which][e];
-                    down[o] = -through;
-                }
-                if (tile == kGroupTiles - 1) all[o] = through;
+            for (int off = 1; off < kGroupTiles; off <<= 1) {
+                const double other = __shfl_up(through, off * G::kPieces);
+                through += tile >= off ? other : 0.0;
             }
+            if (g.count == 0 || col0 + 4 * piece + e >= d) continue;
+            if (g.rows > 0) before[col0 + e] = through - sum[e];
+            if (tile == kGroupTiles - 1) all[col0 + e] = through;
+        }
     }
 }
 
-// A workgroup per (candidate, bucket) and 16 sums; a thread takes up to kScanGroups groups in a row at a time.
+// A workgroup per (candidate, bucket) and 16 columns; a thread takes up to kScanGroups groups in a row at a time.
 constexpr int kScanThreads = 64, kScanGroups = 16;
 __global__ __launch_bounds__(16 * kScanThreads) void scan_groups_kernel(const LearnArgs a)
 {
     __shared__ double part[kScanThreads + 1][16];
-    const int c = blockIdx.x % a.C, q = blockIdx.x / a.C, b = blockIdx.y;
+    const int c = blockIdx.x % a.C, q = blockIdx.x / a.C, b = blockIdx.y, col0 = 16 * blockIdx.z;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
-    const int side = threadIdx.x & 15, t = threadIdx.x >> 4, chain = min(16 * (int)blockIdx.z + side, 2 * d - 1);
-    if (q >= a.n_cand[c] || 16 * (int)blockIdx.z >= 2 * d || !any_order(a, c)) return;
-    const bool stored = 16 * (int)blockIdx.z + side < 2 * d;
+    const int side = threadIdx.x & 15, t = threadIdx.x >> 4, col = min(col0 + side, d - 1);
+    if (q >= a.n_cand[c] || col0 >= d) return;
+    const bool stored = col0 + side < d;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     const int n_groups = (count + kGroupRows - 1) / kGroupRows;
-    const size_t pitch = 2 * (size_t)a.dmax;
-    double *up = a.group_sums + (((size_t)c * kCand + q) * 2 * a.group_slots + first_group(start, b)) * pitch + chain / d * a.dmax + chain % d;
-    double *down = up + a.group_slots * pitch;
-    double before = 0.0, v[kScanGroups];
-    for (int pass = n_groups > kScanThreads * kScanGroups ? 0 : 1; pass < 2; ++pass) {         // (0: for the sum of all)
-        double total = before;
-        before = 0.0;
-        for (int first = 0; first < n_groups; first += kScanThreads * kScanGroups) {
-            const int here = min(n_groups - first, kScanThreads * kScanGroups), per = (here + kScanThreads - 1) / kScanThreads;
-            const int lo = first + t * per, left = min(first + here - lo, per);
-            double sum = 0.0;
+    double *sums = a.group_sums + (((size_t)c * kCand + q) * a.group_slots + first_group(start, b)) * a.dmax + col;
+    double before = 0.0;
+    for (int first = 0; first < n_groups; first += kScanThreads * kScanGroups) {
+        const int here = min(n_groups - first, kScanThreads * kScanGroups), per = (here + kScanThreads - 1) / kScanThreads;
+        const int lo = first + t * per, left = min(first + here - lo, per);
+        double v[kScanGroups], sum = 0.0;
 #pragma unroll
-            for (int i = 0; i < kScanGroups; ++i) {
-                v[i] = up[(size_t)min(lo + i, n_groups - 1) * pitch];
-                v[i] = i < left ? v[i] : 0.0;
-                sum += v[i];
-            }
-            __syncthreads();
-            part[t][side] = sum;
-            __syncthreads();
-            if (t == 0) {
-                double s = 0.0;
+        for (int i = 0; i < kScanGroups; ++i) {
+            v[i] = sums[(size_t)min(lo + i, n_groups - 1) * a.dmax];
+            v[i] = i < left ? v[i] : 0.0;
+            sum += v[i];
+        }
+        __syncthreads();
+        part[t][side] = sum;
+        __syncthreads();
+        if (t == 0) {
+            double s = 0.0;
 #pragma unroll 16
-                for (int i = 0; i < kScanThreads; ++i) {
-                    const double x = part[i][side];
-                    part[i][side] = s;
-                    s += x;
-                }
-                part[kScanThreads][side] = s;
+            for (int i = 0; i < kScanThreads; ++i) {
+                const double x = part[i][side];
+                part[i][side] = s;
+                s += x;
             }
-            __syncthreads();
-            double at = before + part[t][side];
-            before += part[kScanThreads][side];
-            if (n_groups <= kScanThreads * kScanGroups) total = before;
-            if (pass == 1 && stored)
+            part[kScanThreads][side] = s;
+        }
+        __syncthreads();
+        double at = before + part[t][side];
+        before += part[kScanThreads][side];
+        if (stored)
 #pragma unroll
-                for (int i = 0; i < kScanGroups; ++i)
-                    if (i < left) {
-                        up[(size_t)(lo + i) * pitch] = at;
-                        down[(size_t)(lo + i) * pitch] = total - at;
-                        at += v[i];
+            for (int i = 0; i < kScanGroups; ++i)
+                if (i < left) {
+                    sums[(size_t)(lo + i) * a.dmax] = at;
+                    at += v[i];
+                }
+    }
+    if (t == 0 && stored) a.totals[(((size_t)c * kCand + q) * kSplitBuckets + b) * a.dmax + col] = before;
+}
+
+// x of the lane whose number differs in bit kBit (of the lowest two)
+template <int kBit>
+__device__ __forceinline__ double across(double x)
+{
+    const int64_t bits = __builtin_bit_cast(int64_t, x);
+    constexpr int kPerm = kBit == 1 ? 0xb1 : 0x4e;           // lanes 1 0 3 2, or 2 3 0 1
+    const int low = __builtin_amdgcn_update_dpp(0, (int)bits, kPerm, 0xf, 0xf, true);
+    const int high = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), kPerm, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (int64_t)high << 32 | (uint32_t)low);
+}
+
+// The gain of every split (split_error tells what that is): the lanes of a tile walk its rows together, four columns each, and
+// add up what their columns give; lane p of them keeps rows p, p + kPieces, ...
+struct Gain {
+    double best, second;
+    int at;
+    __device__ __forceinline__ void add(double g, double g2, int where)
+    {
+        second = fmax(fmax(second, g2), fmin(best, g));
+        at = g > best ? where : at;
+        best = fmax(best, g);
+    }
+};
+
+template <int NC>
+__global__ __launch_bounds__(256) void split_gains_kernel(const LearnArgs a, int n_buckets)
+{
+    using G = GroupRows<NC>;
+    constexpr int kPieces = G::kPieces, kAhead = 8, kOwn = kSplitRows / kPieces;
+    __shared__ uint32_t listed[4][G::kTiles][kSplitRows + 1];
+    const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (q >= a.n_cand[c]) return;
+    const int piece = lane % kPieces;
+    const G g = list_group_rows<NC>(a, c, q, n_buckets, listed[wave]);
+    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    const uint32_t *row = listed[wave][lane / kPieces];
+    const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + 4 * piece;
+    const double *before = a.sums + ((size_t)c * kCand + q) * 4 * a.tile_slots * a.dmax +
+                           (size_t)(first_slot(g.start, g.b) + g.at / kSplitRows) * a.dmax;
+    const double *all = a.group_sums + (((size_t)c * kCand + q) * a.group_slots + g.group) * a.dmax;
+    const double *totals = a.totals + (((size_t)c * kCand + q) * kSplitBuckets + g.b) * a.dmax;
+    const double n = (double)max(g.count, 1);
+    double squares[kOwn] = {};
+    for (int col0 = 0; col0 < d; col0 += NC) {
+        double sum[4], mean[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int col = min(col0 + 4 * piece + e, d - 1);
+            const bool here = g.rows > 0 && col0 + 4 * piece + e < d;
+            sum[e] = here ? all[col] + before[col] : 0.0;
+            mean[e] = here ? totals[col] / n : 0.0;
+        }
+#pragma unroll
+        for (int i0 = 0; i0 < kSplitRows; i0 += kAhead) {
+            float4 v[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) v[i] = *reinterpret_cast<const float4 *>(X + col0 + (uint64_t)row[i0 + i] * (uint32_t)a.pitch);
+#pragma unroll
+            for (int i1 = 0; i1 < kAhead; i1 += kPieces) {
+                double of[kPieces];
+#pragma unroll
+                for (int i = 0; i < kPieces; ++i) {
+                    const float x[4] = {v[i1 + i].x, v[i1 + i].y, v[i1 + i].z, v[i1 + i].w};
+                    const double minus_n1 = -(double)(g.at + i0 + i1 + i + 1);
+                    of[i] = 0.0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        sum[e] += (double)x[e];
+                        const double w = __builtin_fma(minus_n1, mean[e], sum[e]);
+                        of[i] = __builtin_fma(w, w, of[i]);
                     }
+                }
+                // lane p's row: of[p] of all lanes
+                if constexpr (kPieces == 4) {
+                    const bool odd = piece & 1, high = piece & 2;
+                    const double a0 = (odd ? of[1] : of[0]) + across<1>(odd ? of[0] : of[1]);
+                    const double a1 = (odd ? of[3] : of[2]) + across<1>(odd ? of[2] : of[3]);
+                    squares[(i0 + i1) / kPieces] += (high ? a1 : a0) + across<2>(high ? a0 : a1);
+                } else {
+                    const bool odd = piece & 1;
+                    squares[(i0 + i1) / kPieces] += (odd ? of[1] : of[0]) + across<1>(odd ? of[0] : of[1]);
+                }
+            }
         }
     }
+    Gain best{-1.0, -1.0, -1};
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int r = kPieces * i + piece;
+        const double n1 = (double)(g.at + r + 1), product = n1 * fmax(n - n1, 1.0);
+        double y = __builtin_amdgcn_rcp(product);
+        y = __builtin_fma(__builtin_fma(-product, y, 1.0), y, y);
+        y = __builtin_fma(__builtin_fma(-product, y, 1.0), y, y);
+        const bool splits = g.splits >> r & 1;
+        best.add(splits ? squares[i] * n * y : -1.0, -1.0, splits ? g.at + r : -1);
+    }
+#pragma unroll
+    for (int off = 1; off < kPieces * kGroupTiles; off <<= 1) {
+        const double b2 = __shfl_xor(best.best, off), s2 = __shfl_xor(best.second, off);
+        const int at2 = __shfl_xor(best.at, off);
+        best.add(b2, s2, at2);
+    }
+    if (lane % (kPieces * kGroupTiles) == 0 && g.count > 0) {
+        const size_t o = ((size_t)c * kCand + q) * a.group_slots + g.group;
+        a.group_gain[2 * o] = best.best;
+        a.group_gain[2 * o + 1] = best.second;
+        a.group_first[o] = best.at;
+    }
+}
+
+// (v > l fails where the midpoint rounds to the lower value)
+__device__ __forceinline__ float split_value(uint64_t low, uint64_t high)
+{
+    const float l = key_value(low), h = key_value(high);
+    const float v = (float)(((double)l + (double)h) / 2.0);
+    return v > l ? v : h;
+}
+
+// The best split of every (candidate, bucket) and the best candidate from the gains, where they can tell.  (A candidate that
+// cannot split a bucket gains nothing there: L(B) is the constant that the gains are taken off.)
+__global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a, int level, int n_buckets)
+{
+    __shared__ Gain found[kCand][kSplitBuckets];
+    __shared__ int32_t chosen;
+    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_cand = a.n_cand[c], d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    for (int pair = wave; pair < n_cand * n_buckets; pair += 16) {
+        const int q = pair / n_buckets, b = pair - q * n_buckets;
+        const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
+        const int n_groups = (count + kGroupRows - 1) / kGroupRows;
+        const size_t o = ((size_t)c * kCand + q) * a.group_slots + first_group(start, b);
+        Gain best{-1.0, -1.0, -1};
+#pragma unroll 4
+        for (int i = lane; i < n_groups; i += 64)
+            best.add(a.group_gain[2 * (o + i)], a.group_gain[2 * (o + i) + 1], a.group_first[o + i]);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double b2 = __shfl_xor(best.best, off), s2 = __shfl_xor(best.second, off);
+            const int at2 = __shfl_xor(best.at, off);
+            best.add(b2, s2, at2);
+        }
+        if (lane == 0) found[q][b] = best;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const bool exact_sums = any_order(a, c);
+        double error[kSplitBuckets], of_all = 0.0, most = 0.0;
+        bool any = false, sure = true;
+        int best_q = 0;
+        for (int b = 0; b < n_buckets; ++b) {
+            const int n = (int)a.bucket_count[c * kSplitBuckets + b];
+            const double energy = a.energy[c * kSplitBuckets + b];
+            sure &= energy < __builtin_inf();
+            error[b] = n > 1 ? split_error(a, (double)n, energy, d, exact_sums) : 0.0;
+            of_all += error[b];
+        }
+        double gain[kCand];
+        for (int q = 0; q < n_cand; ++q) {
+            gain[q] = 0.0;
+            for (int b = 0; b < n_buckets; ++b) {
+                any |= found[q][b].at >= 0;
+                gain[q] += fmax(found[q][b].best, 0.0);
+            }
+            if (q == 0 || gain[q] > most) {
+                most = gain[q];
+                best_q = q;
+            }
+        }
+        // (none that splits anything, or no value but 0: all losses are equal, and the first candidate is taken)
+        if (any && of_all > 0.0)
+            for (int q = 0; q < n_cand; ++q) sure &= q == best_q || most - gain[q] > 2.0 * of_all;
+        for (int b = 0; b < n_buckets; ++b) sure &= found[best_q][b].second < 0.0 || found[best_q][b].best - found[best_q][b].second > 2.0 * error[b];
+        a.unsure[2 * c + 1] = sure ? 0 : 1;
+        chosen = sure ? best_q : -1;
+        if (sure) {
+            const int jj = a.cand[c * kCand + best_q];
+            a.chosen[c] = jj;
+            a.split_dims[4 * c + level] = a.bounds[2 * c] + jj;
+            if (level == 3) a.thresholds[16 * c + 15] = 0.0f;
+        }
+    }
+    __syncthreads();
+    const int q = chosen;
+    if (q < 0 || tid >= n_buckets) return;
+    const int at = found[q][tid].at, count = (int)a.bucket_count[c * kSplitBuckets + tid];
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + a.bucket_start[c * kSplitBuckets + tid];
+    float v = 0.0f;
+    if (at >= 0) v = split_value(keys[at], keys[at + 1]);
+    else if (count > 0) v = a.X[((size_t)c * (a.N + 1) + key_row(keys[0])) * a.pitch + a.cand[c * kCand + q]];
+    a.thresholds[16 * c + n_buckets - 1 + tid] = v;
 }
 
 // A wavefront per kGroupTiles tiles of kSplitRows sorted rows of a bucket, one tile after the other with the next one's
@@ -1029,7 +1451,7 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
     __shared__ __align__(16) double sums[kChains][kSumPitch];
     __shared__ __align__(16) float xs[2][NC][kPitch];       // the tile's values, first to last and last to first
     const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x;
-    if (q >= a.n_cand[c]) return;
+    if (q >= a.n_cand[c] || !a.unsure[2 * c + 1]) return;
     const int64_t group = blockIdx.x / a.C;
     int b = -1, start = 0, count = 0;
     for (int k = 0; k < n_buckets; ++k) {
@@ -1051,9 +1473,6 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
     const int chain_dir = (lane / (2 * NC)) & 1, which = (lane / NC) & 1, chain_col = lane % NC;
     const double *ends = a.sums + ((((size_t)c * kCand + q) * 2 + chain_dir) * a.tile_slots + first_slot(start, b) + tile0) * (2 * a.dmax) +
                          (size_t)which * a.dmax;
-    const bool grouped = any_order(a, c);
-    const double *group_ends = a.group_sums + ((((size_t)c * kCand + q) * 2 + chain_dir) * a.group_slots + group) * (2 * a.dmax) +
-                               (size_t)which * a.dmax;
     // as the terms are taken: going up the sums with row k, going down those of the rows after it (what the split after
     // row k leaves above)
     const int k = lane & (T - 1), dir = lane / T, entry = dir ? T - 1 - k : k + 1;
@@ -1072,7 +1491,6 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
         for (int u = 0; u < kPer; ++u)
             v[u] = *reinterpret_cast<const float4 *>(X + col0 + (int64_t)__shfl(my_row, lane / kPieces + u * kRows) * a.pitch);
         end = ends[(size_t)t * (2 * a.dmax) + min(col0 + chain_col, d - 1)];
-        if (grouped) end += group_ends[min(col0 + chain_col, d - 1)];
     };
     uint64_t key = key_of(0), next_key = key_of(1);
     int32_t my_row = row_of(0, key);
@@ -1173,7 +1591,8 @@ __global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int leve
     __shared__ double res_loss[kCand][kSplitBuckets];
     __shared__ float res_v[kCand][kSplitBuckets];
     const int c = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n_cand = a.n_cand[c];
+    const int n_cand = a.n_cand[c], d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (!a.unsure[2 * c + 1]) return;
     for (int pair = wave; pair < n_cand * n_buckets; pair += 8) {
         const int q = pair / n_buckets, b = pair - q * n_buckets;
         const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
@@ -1210,13 +1629,13 @@ __global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int leve
             const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
             float v = 0.0f;
             if (at >= 0) {
-                const float l = key_value(keys[at]), h = key_value(keys[at + 1]);
-                v = (float)(((double)l + (double)h) / 2.0);
-                if (!(v > l)) v = h;
+                v = split_value(keys[at], keys[at + 1]);
             } else if (count > 0) {
                 // cannot be split: the value of the bucket's first row in sorted order, the loss L(B)
                 v = a.X[((size_t)c * (a.N + 1) + key_row(keys[0])) * a.pitch + a.cand[c * kCand + q]];
-                loss = a.bucket_loss[c * kSplitBuckets + b];
+                const double *cl = a.col_loss + ((size_t)c * kSplitBuckets + b) * a.dmax;
+                loss = 0.0;
+                for (int jj = 0; jj < d; ++jj) loss += cl[jj];
             }
             res_v[q][b] = v;
             res_loss[q][b] = loss;
@@ -1799,7 +2218,6 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.node = w.take<uint8_t>(C * a.N);      // (right behind chunk_count and range_part: all three are cleared together)
     a.range = w.take<int32_t>(2 * C);
     a.col_loss = w.take<double>(C * kSplitBuckets * a.dmax);
-    a.bucket_loss = w.take<double>(C * kSplitBuckets);
     a.bucket_count = w.take<int64_t>(C * kSplitBuckets);
     a.bucket_start = w.take<int32_t>(C * kSplitBuckets);
     a.rows_by_bucket = w.take<int32_t>(C * a.N);
@@ -1809,7 +2227,14 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.tile_slots = a.N / kSplitRows + kSplitBuckets + 1;
     a.sums = w.take<double>(C * kCand * 2 * a.tile_slots * 2 * a.dmax);
     a.group_slots = a.N / kGroupRows + kSplitBuckets + 1;
-    a.group_sums = w.take<double>(C * kCand * 2 * a.group_slots * 2 * a.dmax);
+    a.part_slots = a.N / kPartRows + kSplitBuckets + 1;
+    a.parts = w.take<double>(C * a.part_slots * kPartValues * a.dmax);
+    a.energy = w.take<double>(C * kSplitBuckets);
+    a.unsure = w.take<int32_t>(2 * C);
+    a.group_sums = w.take<double>(C * kCand * a.group_slots * a.dmax);
+    a.totals = w.take<double>(C * kCand * kSplitBuckets * a.dmax);
+    a.group_gain = w.take<double>(C * kCand * a.group_slots * 2);
+    a.group_first = w.take<int32_t>(C * kCand * a.group_slots);
     a.group_loss = w.take<double>(C * kCand * a.group_slots);
     a.group_at = w.take<int32_t>(C * kCand * a.group_slots * 2);
     a.chosen = w.take<int32_t>(C);
@@ -1894,11 +2319,13 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     const int32_t C = a.C, dmax = a.dmax;
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
-    // (a chain of fewer rows takes no longer than the two launches)
-    a.row_bits = N >= 4096 ? 64 - __builtin_clzll((unsigned long long)(N - 1)) : 64;
+    a.row_bits = N > 1 ? 64 - __builtin_clzll((unsigned long long)(N - 1)) : 0;
+    // (few rows: their chains take no longer than the estimates' seven launches a level.  1000 rows of 20 columns, 4 codebooks:
+    // 450 us with estimates, 392 without; 3000 of 100, 15: 840 and 849; 5000 of 512, 16: 1044 and 1320)
+    const bool estimated = N >= 2048;
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
-    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds);
+    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds, estimated ? nullptr : a.unsure);
     LAUNCH_OK("launch upload_bounds_kernel");
     const int64_t clear_words = (a.node + (size_t)C * N - reinterpret_cast<uint8_t *>(a.chunk_count) + 3) / 4;
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, stream, a.chunk_count, clear_words);
@@ -1914,7 +2341,15 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
         hipLaunchKernelGGL(order_rows_kernel, dim3((unsigned)((N + order_chunk_rows(N) - 1) / order_chunk_rows(N)), C), dim3(256), 0,
                            stream, a, level, n_buckets);
         LAUNCH_OK("launch order_rows_kernel");
-        hipLaunchKernelGGL(bucket_loss_kernel, dim3(C, n_buckets, a.pitch / 4), dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a);
+        const dim3 grid_parts((unsigned)(a.part_slots * C)), grid_bucket_loss(C, n_buckets, a.pitch / 4);
+        if (estimated) {
+            if (narrow) hipLaunchKernelGGL(loss_parts_kernel<8>, grid_parts, dim3(256), 0, stream, a, n_buckets);
+            else hipLaunchKernelGGL(loss_parts_kernel<16>, grid_parts, dim3(256), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch loss_parts_kernel");
+            hipLaunchKernelGGL(select_kernel, dim3(C), dim3(512), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch select_kernel");
+        }
+        hipLaunchKernelGGL(bucket_loss_kernel, grid_bucket_loss, dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a, 0);
         LAUNCH_OK("launch bucket_loss_kernel");
         const int64_t chunk_len = a.Npad < kSortChunk ? a.Npad : kSortChunk;
         const dim3 chunks((unsigned)(a.Npad / chunk_len), kCand, C);
@@ -1936,6 +2371,23 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
         }
         // (columns eight or sixteen at a time)
         const int groups = narrow ? 1 : a.pitch / 16;
+        if (estimated) {
+            const int at_once = narrow ? 16 : 8;              // groups to a workgroup
+            const dim3 grid_tiles((unsigned)((a.group_slots + at_once - 1) / at_once * C), kCand);
+            if (narrow) hipLaunchKernelGGL(tile_sums_kernel<8>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
+            else hipLaunchKernelGGL(tile_sums_kernel<16>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch tile_sums_kernel");
+            hipLaunchKernelGGL(scan_groups_kernel, dim3(C * kCand, n_buckets, groups), dim3(16 * kScanThreads), 0, stream, a);
+            LAUNCH_OK("launch scan_groups_kernel");
+            if (narrow) hipLaunchKernelGGL(split_gains_kernel<8>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
+            else hipLaunchKernelGGL(split_gains_kernel<16>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch split_gains_kernel");
+            hipLaunchKernelGGL(choose_by_gain_kernel, dim3(C), dim3(1024), 0, stream, a, level, n_buckets);
+            LAUNCH_OK("launch choose_by_gain_kernel");
+            // the codebooks that are unsure
+            hipLaunchKernelGGL(bucket_loss_kernel, grid_bucket_loss, dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a, 1);
+            LAUNCH_OK("launch bucket_loss_kernel");
+        }
         const dim3 chain_groups(C, 8 * groups, n_buckets);
         const dim3 grid_losses((unsigned)(a.group_slots * C), kCand);
         // (where buckets of one tile can be the rule: even shares of the rows are)
@@ -1951,15 +2403,6 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
             else hipLaunchKernelGGL(split_chains_kernel<16>, chain_groups, dim3(32 * 16 + kChainHelpers), stream_lds_bytes<16>(), stream, a, small_too);
             LAUNCH_OK("launch split_chains_kernel");
         }
-        if (a.row_bits <= 53) {
-            const int at_once = narrow ? 16 : 8;              // groups to a workgroup
-            const dim3 grid_tiles((unsigned)((a.group_slots + at_once - 1) / at_once * C), kCand);
-            if (narrow) hipLaunchKernelGGL(tile_sums_kernel<8>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
-            else hipLaunchKernelGGL(tile_sums_kernel<16>, grid_tiles, dim3(256), 0, stream, a, n_buckets);
-            LAUNCH_OK("launch tile_sums_kernel");
-            hipLaunchKernelGGL(scan_groups_kernel, dim3(C * kCand, n_buckets, (2 * dmax + 15) / 16), dim3(16 * kScanThreads), 0, stream, a);
-            LAUNCH_OK("launch scan_groups_kernel");
-        }
         if (narrow) hipLaunchKernelGGL(split_losses_kernel<8>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         else hipLaunchKernelGGL(split_losses_kernel<16>, grid_losses, dim3(64), 0, stream, a, n_buckets);
         LAUNCH_OK("launch split_losses_kernel");
@@ -1974,7 +2417,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
 int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const int32_t *bounds_host, int32_t *split_dims,
                        float *thresholds, uint8_t *codes, void *workspace, hipStream_t stream)
 {
-    note_kernel("gather_columns_kernel + order_rows_kernel + bucket_loss_kernel + sort_chunks_kernel + sort_exchange_kernel + split_chains_small_kernel + split_chains_kernel + tile_sums_kernel + scan_groups_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
+    note_kernel("gather_columns_kernel + order_rows_kernel + loss_parts_kernel + select_kernel + bucket_loss_kernel + sort_chunks_kernel + sort_exchange_kernel + tile_sums_kernel + scan_groups_kernel + split_gains_kernel + choose_by_gain_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
     if (int rc = allow_full_lds<sort_chunks_kernel>(); rc != MADDNESS_OK) return rc;
     for (int32_t c = 0; c < C;) {
         LearnArgs a{};
@@ -1998,7 +2441,7 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
     carve_prototypes(w, a);
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
-    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds);
+    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds, static_cast<int32_t *>(nullptr));
     LAUNCH_OK("launch upload_bounds_kernel");
     if (!ridge) {
         note_kernel("means_kernel", nullptr);

@@ -202,19 +202,23 @@ def test_learner_rejects_bad_arguments(mad):
 
 
 @pytest.mark.parametrize("N, widths, scale, kinds", [
-    (4096, (7, 20), 1.0, "ii"),              # the fewest rows whose sums are taken in any order where that is exact
-    (4097, (3, 4, 5), 0.25, "iri"),          # quarters; a codebook beside them whose sums have to be chains
-    (9000, (40, 17), 1.0, "sw"),             # both signs; values of 17 bits: 2 x 18 + 14 bits, next to the limit
+    (4097, (3, 4, 5), 0.25, "iri"),          # quarters; a codebook beside them whose sums depend on their order
+    (9000, (40, 17), 1.0, "sw"),             # both signs; values of 17 bits: 2 x 18 + 14 bits, next to the limit of exact sums
     (8500, (5, 2), 1.0, "Ww"),               # 20 bits: past it
     (270000, (2, 3), 1.0, "ci"),             # more groups of 256 rows than a workgroup scans at once; equal rows
+    (3000, (6, 5), 1.0, "dr"),               # columns that are copies: only the exact sums tell which comes first
+    (700, (4, 3, 2), 1.0, "bz1"),            # buckets that cannot be split, columns of zeros, columns of one value
+    (2050, (18, 33), 1.0, "dr"),             # the same copies in subspaces of more than 16 columns
 ])
-def test_learner_sums_of_whole_values(mad, N, widths, scale, kinds):
-    """Sums that are exact in any order, codebook by codebook, against the oracle's in row order: equal to the bit."""
+def test_learner_estimates_and_exact_sums(mad, N, widths, scale, kinds):
+    """Data whose choices the estimates settle and data that take the exact sums, codebook by codebook: all equal to the oracle's."""
     rng = np.random.default_rng(N)
+    relu = lambda n: np.maximum(rng.standard_normal(n), 0)
     draw = {"i": lambda n: rng.integers(0, 256, n), "s": lambda n: rng.integers(-300, 300, n), "w": lambda n: rng.integers(0, 1 << 17, n),
-            "W": lambda n: rng.integers(0, 1 << 20, n), "r": lambda n: np.maximum(rng.standard_normal(n), 0),
-            "c": lambda n: np.where(rng.random(n) < 0.999, 7, 8)}
-    print("case whole values", N, widths, flush=True)
+            "W": lambda n: rng.integers(0, 1 << 20, n), "r": relu, "c": lambda n: np.where(rng.random(n) < 0.999, 7, 8),
+            "d": lambda n: np.tile(relu((n[0], (n[1] + 1) // 2)), 2)[:, :n[1]], "b": lambda n: rng.integers(0, 2, n),
+            "z": np.zeros, "1": lambda n: np.full(n, 0.1)}
+    print("case estimates", N, widths, flush=True)
     A = np.concatenate([draw[k]((N, w)) * scale for w, k in zip(widths, kinds)], 1).astype(np.float32)
     ends = np.cumsum(widths)
     subspaces = [(int(e - w), int(e)) for e, w in zip(ends, widths)]
@@ -224,5 +228,5 @@ def test_learner_sums_of_whole_values(mad, N, widths, scale, kinds):
     assert (sd.cpu().numpy() == want_sd).all() and (th.cpu().numpy() == want_th).all()
     assert (codes.cpu().numpy() == want_codes).all()
     want = oracle.ridge_prototypes(want_codes, A, 1.0)
-    # the same fp64 operations: the fp32 rounding of either is the other's
+    # the same fp64 operations: both round to the same fp32
     assert (P.cpu().numpy() == want.astype(np.float32)).all()
