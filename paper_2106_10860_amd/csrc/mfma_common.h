@@ -99,11 +99,11 @@ inline int64_t matrix_cores_min_rows(int C, int M, bool in_lds)
 // time: D = 1024, M = 512, C = 64, N = 65536 took 223 us that way, 82 so (bfloat16 rows: 202 and 65), the scan alone 109
 // and 38; D = 512, M = 256, C = 32, N = 2^18 145 and 139.
 // Entries of (PAD) codebooks >= `codebooks` are zeros, which add nothing to a sum together with the code 0; those of columns
-// >= M are anything (their sums are never stored); entries need no alignment.  Every wavefront takes part (barriers); the
+// >= M are anything (their sums are never stored), or (WRAP) those of column 0, 1, ... again; entries need no alignment.  Every wavefront takes part (barriers); the
 // stage is free again after one more.
 constexpr int kTableStage = 4096;
 
-template <int KG, int NT, int THREADS, bool PAD>
+template <int KG, int NT, int THREADS, bool PAD, bool WRAP = false>
 __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *luts, int M, int col0, int cols, int first, int g,
                                             int j, unsigned char *stage, int tid, int codebooks)
 {
@@ -111,14 +111,16 @@ __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *lut
     constexpr int CHUNKS = 4 * KG / CHUNK, AHEAD = CHUNKS < 4 ? CHUNKS : 4;
     static_assert(CHUNK * P * 16 == kTableStage * (THREADS / 64) && CHUNK % 4 == 0 && (4 * KG) % CHUNK == 0, "stage of the tables");
     v4i *entries = reinterpret_cast<v4i *>(stage);          // [CHUNK][P], a block's columns ordered by (t, j)
-    const int quad = tid % QUADS, cb = tid / QUADS, col = col0 + 4 * quad;
+    const int quad = tid % QUADS, cb = tid / QUADS, from0 = col0 + 4 * quad, col = WRAP && from0 >= M ? from0 - M : from0;
     // the columns' last four bytes where fewer than four are left: moved down when they are used.  In tables of less than
     // four columns the four bytes run on into the next code's, which stand for columns that do not exist; the last
     // codebook of such tables (without PAD, all of them) is read byte by byte
     const bool mine = 4 * quad < cols && col < M;
-    const int back = M >= 4 && col + 4 > M ? col + 4 - M : 0;
+    const int back = !WRAP && M >= 4 && col + 4 > M ? col + 4 - M : 0;
     const int whole_end = M >= 4 ? codebooks : codebooks - 1;
-    auto is_whole = [&](int n) INLINE_LAMBDA { return mine && (PAD ? CHUNK * n + cb < whole_end : M >= 4); };
+    auto is_whole = [&](int n) INLINE_LAMBDA {
+        return mine && (PAD ? CHUNK * n + cb < whole_end : M >= 4) && (!WRAP || col + 4 <= M);
+    };
     uint32_t raw[AHEAD][16];
     auto fetch = [&](int n, uint32_t(&w)[16]) INLINE_LAMBDA {
         const bool read = is_whole(n);
@@ -145,9 +147,9 @@ __device__ __forceinline__ void load_tables(v4i (&B)[NT][KG], const uint8_t *lut
             for (int b = 0; b < 16; ++b) w[b] = 0;
             if (mine && (!PAD || CHUNK * n + cb < codebooks)) {
                 const uint8_t *src = luts + (size_t)(16 * (CHUNK * n + cb)) * M + col;
-                for (int t = 0; t < M - col; ++t)
+                for (int t = 0; t < (WRAP ? 4 : M - col); ++t)
 #pragma unroll
-                    for (int b = 0; b < 16; ++b) w[b] |= (uint32_t)src[(size_t)b * M + t] << (8 * t);
+                    for (int b = 0; b < 16; ++b) w[b] |= (uint32_t)src[(size_t)b * M + t - (WRAP && col + t >= M ? M : 0)] << (8 * t);
             }
         }
         v4i column[4];

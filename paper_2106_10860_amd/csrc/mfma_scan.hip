@@ -3,6 +3,8 @@
 // streams over the rows.  See mfma_common.h for the formulation.
 #include "mfma_common.h"
 
+#include <algorithm>
+
 namespace maddness {
 namespace {
 
@@ -18,6 +20,51 @@ struct MfmaScanArgs {
     int codebooks;          // the any-shape form: the real number of codebooks (<= the kernel's C); rows of codes
                             // are (codebooks + 1) / 2 bytes
 };
+
+// The packed codes of one row as they come from memory (zeros for a row that does not exist), and as the scan takes them:
+// rows of any number of bytes are read in (unaligned) words, the last one up to the row's end and moved down afterwards.
+// (Put together from bytes where they are loaded, the row has to be waited for there, behind the stores before it:
+// M = 250, C = 30, N = 300000 113 us that way, 84 so.)
+template <int CW, bool ODD>
+__device__ __forceinline__ auto load_row_codes(const MfmaScanArgs &a, int64_t row)
+{
+    typedef unsigned cvec __attribute__((ext_vector_type(CW)));
+    cvec v = {};
+    if (row >= a.N) return v;
+    if constexpr (ODD) {
+        const int bytes = (a.codebooks + 1) / 2;
+        const uint8_t *src = a.codes + row * bytes;
+        if (bytes < 4) {
+            for (int t = 0; t < bytes; ++t) v[0] |= (unsigned)src[t] << (8 * t);
+            return v;
+        }
+#pragma unroll
+        for (int q = 0; q < CW; ++q)
+            if (4 * q < bytes) {
+                uint32_t w;
+                __builtin_memcpy(&w, src + min(4 * q, bytes - 4), 4);
+                v[q] = w;
+            }
+    } else {
+        // (rows are C / 2 bytes apart and only the base is known to be 16-byte aligned: copied as
+        // words, so that no wider alignment than a word's is assumed of a row)
+        __builtin_memcpy(&v, reinterpret_cast<const uint32_t *>(a.codes + row * (4 * CW)), sizeof(uint32_t) * CW);
+    }
+    return v;
+}
+
+template <int CW, bool ODD, typename Codes>
+__device__ __forceinline__ Codes whole_codes(const MfmaScanArgs &a, Codes v)
+{
+    if constexpr (ODD) {
+        const int bytes = (a.codebooks + 1) / 2;
+        if (bytes > 4)
+#pragma unroll
+            for (int q = 1; q < CW; ++q)
+                if (4 * q < bytes && 4 * q + 4 > bytes) v[q] >>= 8 * (4 * q + 4 - bytes);
+    }
+    return v;
+}
 
 // The dequantised results of one step of a workgroup (16 rows, or 32 with NT = 2, times its
 // 4 blocks of columns) collected in LDS and written out row by row: a store instruction then
@@ -36,7 +83,6 @@ __device__ __forceinline__ void scan_gathered(const MfmaScanArgs &a, const v4i *
     constexpr int SPAN = 16 * NT;
     constexpr int GPS = NT == 2 ? 2 : 1;            // groups of 16 rows per step
     constexpr int TILE_LD = 4 * SPAN + 4;           // floats per tile row (4 of padding)
-    typedef unsigned cvec __attribute__((ext_vector_type(CW)));
     typedef float piece __attribute__((ext_vector_type(NT)));
     const int j = lane & 15, g = lane >> 4;
     const int col0 = blockIdx.y * 4 * SPAN;          // first column of the workgroup
@@ -61,34 +107,7 @@ __device__ __forceinline__ void scan_gathered(const MfmaScanArgs &a, const v4i *
     // rows without padding between them, all columns in this workgroup: the rows of a step are one range of floats
     const bool dense = ODD && a.o.out && a.o.ldo == a.o.M && gridDim.y == 1;
     const float inv_M = 1.0f / (float)a.o.M;
-    auto load_codes = [&](int64_t rg) INLINE_LAMBDA {
-        const int64_t row = rg * 16 + j;
-        cvec v = {};
-        if constexpr (ODD) {
-            const int bytes = (a.codebooks + 1) / 2;
-            if (row < a.N) {
-                // whole words of the row as (unaligned) 32-bit loads, the last one to three bytes one by one
-                const uint8_t *src = a.codes + row * bytes;
-#pragma unroll
-                for (int q = 0; q < CW; ++q) {
-                    if (4 * q + 4 <= bytes) {
-                        uint32_t w;
-                        __builtin_memcpy(&w, src + 4 * q, 4);
-                        v[q] = w;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 3; ++t)
-                            if (4 * q + t < bytes) v[q] |= (unsigned)src[4 * q + t] << (8 * t);
-                    }
-                }
-            }
-        } else {
-            // (rows are C / 2 bytes apart and only the base is known to be 16-byte aligned: copied as
-            // words, so that no wider alignment than a word's is assumed of a row)
-            if (row < a.N) __builtin_memcpy(&v, reinterpret_cast<const uint32_t *>(a.codes + row * (C / 2)), sizeof(uint32_t) * CW);
-        }
-        return v;
-    };
+    auto load_codes = [&](int64_t rg) INLINE_LAMBDA { return whole_codes<CW, ODD>(a, load_row_codes<CW, ODD>(a, rg * 16 + j)); };
     // step s of this workgroup: groups GPS (blockIdx.x + s gridDim.x) + 0 .. GPS - 1, i.e. 16 GPS
     // consecutive rows
     for (int64_t rg = (int64_t)GPS * blockIdx.x; rg < n_groups; rg += (int64_t)GPS * gridDim.x) {
@@ -197,14 +216,7 @@ __global__ __launch_bounds__(256, 2) void mfma_scan_kernel(const MfmaScanArgs a)
     // rows, 16 at a time; the codes of the next group are fetched ahead
     typedef unsigned cvec __attribute__((ext_vector_type(CW)));
     const int64_t n_groups = (a.N + 15) >> 4;
-    auto load_codes = [&](int64_t rg) INLINE_LAMBDA {
-        const int64_t row = rg * 16 + j;
-        // (rows are C / 2 bytes apart and only the base is known to be 16-byte aligned: copied as
-        // words, so that no wider alignment than a word's is assumed of a row)
-        cvec v = {};
-        if (row < a.N) __builtin_memcpy(&v, reinterpret_cast<const uint32_t *>(a.codes + row * (C / 2)), sizeof(uint32_t) * CW);
-        return v;
-    };
+    auto load_codes = [&](int64_t rg) INLINE_LAMBDA { return load_row_codes<CW, false>(a, rg * 16 + j); };
     int64_t rg = (int64_t)blockIdx.x * share + wave / blocks_here;
     const int64_t stride = (int64_t)gridDim.x * share;
     if constexpr (NT == 2) {
@@ -242,6 +254,122 @@ __global__ __launch_bounds__(256, 2) void mfma_scan_kernel(const MfmaScanArgs a)
     }
 }
 
+// Rows without padding between them that do not begin on 128-byte lines, whole lines written: a line that two wavefronts
+// write a part of each, at different times, costs as much as several whole ones.  Rows whose first floats lie at the same
+// place of a line (row mod `classes`) go to the same workgroups, whose blocks of columns begin where the first line
+// that begins in such a row does.  The row's last line is filled up with the first columns of the row after it: workgroups
+// of their own take it (32 columns to a wavefront, all four the same ones), whose tables go on with column 0 and who scan
+// the next rows' codes as well.  Only lines are stored, each by one wavefront, straight from registers.  (Stores alone of
+// 512 MB, by rows of 1000, 500, 300 and 250 floats: 5.2, 5.2, 5.1 and 5.5 TB/s; rows from their first float to their last
+// 4.4, 3.8, 3.5 and 2.7.  The kernel against the one that gathers rows in LDS: M = 1000, C = 32, N = 131072 148 -> 100 us,
+// 5.2 TB/s; M = 999, C = 64 442 -> 307; M = 513, C = 16, N = 262144 237 -> 112; M = 100, C = 32, N = 2^20 184 -> 105.)
+constexpr int kLine = 32;
+
+// one group of 16 rows after the other: cls + classes i for 16 values of i
+template <int KG, int NT, bool ODD, bool LAST>
+__device__ __forceinline__ void scan_lines(const MfmaScanArgs &a, int classes, int cls, int col0, int first, int end, int blocks_here,
+                                           int64_t rg, int64_t stride, const v4i *one_hot, unsigned char *stage)
+{
+    constexpr int C = 4 * KG, CW = C / 8, SPAN = 16 * NT;
+    typedef float piece __attribute__((ext_vector_type(NT)));
+    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4, M = a.o.M;
+    const int col = col0 + first + NT * j;
+    v4i B[NT][KG];
+    load_tables<KG, NT, 256, ODD, LAST>(B, a.luts, M, col0, blocks_here * SPAN, first, g, j, stage, threadIdx.x, a.codebooks);
+    if (col0 + first >= end) return;                // no barriers below
+    float sc[NT], of[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int real = min(LAST && col + t >= M ? col + t - M : col + t, M - 1);
+        sc[t] = a.scale[real];
+        of[t] = a.offset[real];
+    }
+    const int64_t n_rows = (a.N - cls + classes - 1) / classes, n_groups = (n_rows + 15) >> 4, pitch = (int64_t)classes * M;
+    auto load_codes = [&](int64_t group, int after) INLINE_LAMBDA {
+        return load_row_codes<CW, ODD>(a, group < n_groups ? cls + (group * 16 + j) * classes + after : a.N);
+    };
+    auto store = [&](const v4i (&acc)[NT], int64_t group) INLINE_LAMBDA {
+        if (col >= end) return;
+        const int64_t row0 = cls + (group * 16 + 4 * g) * classes;
+        float *dst = a.o.out + row0 * M + col;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            piece v;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) v[t] = fmaf((float)acc[t][r], sc[t], of[t]);
+            const int64_t row = row0 + (int64_t)r * classes;
+            if (row + (LAST ? 1 : 0) < a.N) __builtin_nontemporal_store(v, reinterpret_cast<piece *>(dst));
+            else if (LAST && row < a.N)                           // (the last row ends inside its last line)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if (col + t < M) dst[t] = v[t];
+            dst += pitch;
+        }
+    };
+    auto next0 = load_codes(rg, 0);
+    if constexpr (LAST) {
+        auto next1 = load_codes(rg, 1);
+        for (; rg < n_groups; rg += stride) {
+            const auto cw0 = whole_codes<CW, ODD>(a, next0), cw1 = whole_codes<CW, ODD>(a, next1);
+            next0 = load_codes(rg + stride, 0);
+            next1 = load_codes(rg + stride, 1);
+            v4i acc[NT], of_next[NT];
+            scan16x2<KG, NT>(cw0, cw1, B, g, one_hot, acc, of_next);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[t][r] = col + t < M ? acc[t][r] : of_next[t][r];
+            store(acc, rg);
+        }
+    } else if constexpr (NT == 2) {
+        // two groups per step: four independent accumulation chains for the matrix pipe
+        auto next1 = load_codes(rg + stride, 0);
+        for (; rg < n_groups; rg += 2 * stride) {
+            const auto cw0 = whole_codes<CW, ODD>(a, next0), cw1 = whole_codes<CW, ODD>(a, next1);
+            next0 = load_codes(rg + 2 * stride, 0);
+            next1 = load_codes(rg + 3 * stride, 0);
+            v4i acc0[NT], acc1[NT];
+            scan16x2<KG, NT>(cw0, cw1, B, g, one_hot, acc0, acc1);
+            store(acc0, rg);
+            if (rg + stride < n_groups) store(acc1, rg + stride);
+        }
+    } else {
+        for (; rg < n_groups; rg += stride) {
+            const auto cw = whole_codes<CW, ODD>(a, next0);
+            next0 = load_codes(rg + stride, 0);
+            v4i acc[NT];
+            scan16<KG, NT>(cw, B, g, one_hot, acc);
+            store(acc, rg);
+        }
+    }
+}
+
+// A class has gridDim.x / classes workgroups (a multiple of 8): `last` of them share out its rows for their last lines, the others
+// are `shares` of the rows times `quarters` of the columns before (blocks for four wavefronts).  The workgroups of all
+// classes that take the same share lie 8 apart, on one XCD: 128 bytes of codes are rows of up to 8 classes and
+// more.
+template <int KG, int NT, bool ODD>
+__global__ __launch_bounds__(256, 2) void mfma_scan_lines_kernel(const MfmaScanArgs a, int classes, int last, int shares, int share, int quarters)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), M = a.o.M;
+    __shared__ v4i one_hot[16];
+    __shared__ __align__(16) unsigned char stage[4 * kTableStage];
+    fill_one_hot_table(one_hot, threadIdx.x);
+    __syncthreads();
+    const int cls = (int)blockIdx.x / 8 % classes, unit = (int)blockIdx.x / (8 * classes) * 8 + (int)blockIdx.x % 8;
+    const int first_float = (int)(((int64_t)cls * M) % kLine);
+    // columns lo .. end - 1 of these rows are whole lines, those from M on of the next row
+    const int lo = (kLine - first_float) % kLine, end = M + (kLine - (first_float + M) % kLine) % kLine;
+    if (unit < last) {
+        scan_lines<KG, 2, ODD, true>(a, classes, cls, end - kLine, 0, end, 1, (int64_t)unit * 4 + wave, (int64_t)last * 4, one_hot, stage);
+        return;
+    }
+    const int blocks_here = 4 / share, y = (unit - last) / shares;
+    if (y >= quarters) return;
+    scan_lines<KG, NT, ODD, false>(a, classes, cls, lo + y * blocks_here * 16 * NT, wave % blocks_here * 16 * NT, end - kLine, blocks_here,
+                                   (int64_t)((unit - last) % shares) * share + wave / blocks_here, (int64_t)shares * share, one_hot, stage);
+}
+
 template <int KG, int NT, bool ODD = false>
 int launch_mfma(const MfmaScanArgs &a, hipStream_t stream)
 {
@@ -249,6 +377,45 @@ int launch_mfma(const MfmaScanArgs &a, hipStream_t stream)
     const int span = 16 * NT * 4;                       // columns per workgroup of 4 wavefronts
     const int gy = (a.o.M + span - 1) / span;
     const int col_blocks = (a.o.M + 16 * NT - 1) / (16 * NT);
+    int classes = 1;
+    while (classes * (int64_t)a.o.M % 32 != 0) classes *= 2;
+    // (less than 48 MB of results, and rows that one workgroup's four blocks take whole: the other forms are as fast or faster,
+    // as caches put the parts of a line together or one workgroup writes them.  C = 32, M = 1000: N = 16384 23 us there, 19 here, C = 64,
+    // M = 250, N = 16384 16 and 31; N = 300000, C = 32, M = 248 58 and 67, M = 250 76 and 86, but M = 252, C = 30 83
+    // and 62; N = 200000, C = 64, M = 66, where the last of three lines takes half of the work, 37 and 46)
+    const bool one_workgroup = col_blocks == 4 && !(ODD && classes <= 8);
+    if (classes > 1 && a.o.out && !a.o.acc && a.o.ldo == a.o.M && a.o.M >= (NT == 4 ? 64 : 96) && aligned_to(a.o.out, 128) && !one_workgroup &&
+        a.N >= 16384 && a.N * a.o.M >= 12 << 20) {
+        // (a row has up to (M + 31) / 32 first floats of a line, its last line's among them)
+        const int blocks = (((a.o.M + 31) / 32 - 1) * 32 + 16 * NT - 1) / (16 * NT);
+        const int share = blocks >= 3 ? 1 : blocks == 2 ? 2 : 4, quarters = (blocks * share + 3) / 4;
+        // one to four turns of the chip (two workgroups per compute unit), whichever leaves the least undone: the last lines take
+        // as long as 64 (32) columns
+        const double group_us = (KG * NT * 34 + 1000) / 2400.0, table_us = 4.0;
+        const int64_t groups = (a.N / classes + 15) / 16;
+        int units = 0, shares = 1, last = 1;
+        double least = 1e30;
+        for (int turns = 1; turns <= 4; ++turns) {
+            const int u = std::max(8, 2 * dev.cus * turns / classes / 8 * 8);
+            const double of_last = NT == 4 ? 0.3 * share : 0.55 * share;
+            for (int n = std::max(1, (int)(u / (quarters + of_last))), k = 0; k < 2; ++n, ++k) {
+                const int l = u - n * quarters;
+                if (l < 1) break;
+                const double us = turns * (std::max((double)((groups + (int64_t)n * share - 1) / ((int64_t)n * share)),
+                                                    (double)groups * (NT == 4 ? 0.3 : 0.55) / l) * group_us + table_us);
+                if (us < least) {
+                    least = us;
+                    units = u;
+                    shares = n;
+                    last = l;
+                }
+            }
+        }
+        note_kernel("mfma_scan_kernel, whole lines", __PRETTY_FUNCTION__);
+        hipLaunchKernelGGL((mfma_scan_lines_kernel<KG, NT, ODD>), dim3((unsigned)(classes * units)), dim3(256), 0, stream, a,
+                           classes, last, shares, share, quarters);
+        return check_hip(hipGetLastError(), "launch mfma_scan_lines_kernel");
+    }
     if constexpr (ODD) {
         const int64_t n_steps = ((a.N + 15) / 16 + (NT == 2 ? 1 : 0)) / (NT == 2 ? 2 : 1);
         int64_t gx = (int64_t)dev.cus * 2 / gy;

@@ -1,0 +1,54 @@
+"""Outputs whose rows begin inside 128-byte lines and take several wavefronts' columns: every result where it belongs,
+equal to the oracle's to the bit, and nothing written beside the rows."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_tables_and_few_rows import dev, problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mad():
+    import torch
+    import paper_2106_10860_amd as m
+    assert torch.cuda.is_available()
+    m.lib()
+    return m
+
+
+# (N, M, C, floats between rows, floats the output starts after a line): rows of a class that make a whole number of groups
+# of 16 and that do not, 2 to 32 classes, one to many blocks of columns, blocks that end with the row and that go on with the next
+# one's columns (on a multiple of four and not), the last row's last line, padding codebooks; padding and other alignments
+# (other kernels)
+CUT = [
+    (16384, 1000, 32, 0, 0), (16390, 1000, 32, 0, 0), (49001, 257, 32, 0, 0), (28100, 449, 30, 0, 0), (53007, 252, 30, 0, 0),
+    (28001, 450, 16, 0, 0), (18700, 676, 8, 0, 0), (18697, 673, 31, 0, 0), (65201, 193, 64, 0, 0), (43400, 290, 40, 0, 0),
+    (89900, 141, 50, 0, 0), (96800, 130, 33, 0, 0), (193600, 65, 32, 0, 0), (93000, 136, 64, 0, 0), (99079, 127, 5, 0, 0), (16386, 1022, 64, 0, 0),
+    (16385, 452, 24, 4, 0), (16384, 1000, 32, 1, 0), (16390, 1000, 32, 0, 4), (33, 514, 64, 0, 0), (16384, 449, 30, 0, 1), (52000, 250, 30, 0, 0),
+]
+
+
+@pytest.mark.parametrize("shape", CUT, ids=lambda s: "N%d_M%d_C%d_pad%d_at%d" % s)
+def test_scan_writes_whole_lines(mad, shape):
+    import torch
+    N, M, C, pad, at = shape
+    print("case", shape, flush=True)
+    _, _, _, luts, scale, offset = problem(N + M, 8, 4 * C, M, C)
+    rng = np.random.default_rng(M)
+    codes = rng.integers(0, 256, size=(N, (C + 1) // 2)).astype(np.uint8)
+    if C % 2:
+        codes[:, -1] &= 15
+    want_out, _, _ = oracle.scan(codes, C, luts, scale, offset)
+    ldo = M + pad
+    raw = torch.full((at + N * ldo + 64,), -7.0, dtype=torch.float32, device="cuda")
+    out = raw[at:at + N * ldo].reshape(N, ldo)[:, :M]
+    mad.maddness_scan(C, dev(codes), dev(luts), dev(scale), dev(offset), out=out)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("mfma_scan_kernel, whole lines" if N * M >= 12 << 20 and not pad and not at and M != 250 else "mfma_scan_kernel"), kernel
+    assert (out.cpu().numpy() == want_out).all()
+    got = raw.cpu().numpy()
+    assert (got[:at] == -7).all() and (got[at + (N - 1) * ldo + M:] == -7).all()
+    assert (got[at:at + N * ldo].reshape(N, ldo)[:, M:][:-1] == -7).all()
