@@ -24,90 +24,107 @@ static __device__ __align__(256) unsigned char scratch[MADDNESS_STATIC_WORKSPACE
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // T and, per codebook and column, the least entry and the range.  A workgroup of eight wavefronts takes RT codebooks
-// (16 RT rows of T) and 32 columns.  64 steps of the inner dimension at a time go to LDS, the next 64 on their way
-// meanwhile; four wavefronts take each half of the columns, the w-th of them contracts d = 4 (w + 4 i) + 0..3 for its
-// RT tiles of 16 x 16, and the partial tiles are added in that order through LDS.
+// (16 RT rows of T) and 32 columns; the w-th wavefront contracts d = 16 (w + 8 n) + 0..15 for all 2 RT tiles of 16 x 16, and the
+// partial tiles are added in that order through LDS.
 // Operand layout of v_mfma_f64_16x16x4_f64: lane l supplies A[i = l % 16][k = l / 16]
 // and B[k = l / 16][j = l % 16]; it receives D[i = 4 r + l / 16][j = l % 16] in
-// accumulator element r = 0..3.
-// 2 * 16 C D M flops; 1024 x 512 with 64 codebooks: 15 us at the 73 TFLOP/s that a large product reaches; takes 29 us
-// there: two wavefronts to a SIMD, each waiting for its operands from LDS, leave the matrix cores busy 38 % of the time (LDS
-// 16 %, by the counters; 30 % of that conflicts, of writes).  One codebook and 16 columns to a workgroup, operands straight from memory, took
-// 77 us: two loads of 16 rows or 4 rows each per matrix instruction, where staged tiles need 5 reads of LDS for 4 of them.
-constexpr int KSPLIT = 4;
-constexpr int GEMM_COLS = 32, GEMM_DEPTH = 64, GEMM_THREADS = 128 * KSPLIT;
-constexpr int A_PITCH = GEMM_DEPTH + 4, B_PITCH = GEMM_COLS + 16;      // (the reads of an operand's 64 values meet in no LDS bank)
+// accumulator element r = 0..3.  Which d stand for k = 0..3 is free: here d = 16 (w + 8 n) + 4 k + t in instruction t, so
+// that a lane's operands of four instructions lie side by side in a row of P.  Every operand has one reader, so it comes
+// straight from memory, the next step's while the matrix cores have this one's, with no barrier before the last step.
+// VEC: rows of P are whole 16-byte pieces on 16-byte boundaries.
+// 2 * 16 C D M flops; 1024 x 512 with 64 codebooks: 15 us at the 73 TFLOP/s that a large product reaches, 20 here
+// (table build 27; 29 and 38 with tiles of both staged in LDS for all wavefronts, whose barriers left the matrix cores idle between
+// the steps; staged with 16-byte reads 34).  Two steps ahead: 31, the registers of a second set cost more than they give.
+constexpr int KSPLIT = 8;
+constexpr int GEMM_COLS = 32, GEMM_DEPTH = 16 * KSPLIT, GEMM_THREADS = 64 * KSPLIT;
 
-template <int RT>
+template <int RT, bool VEC>
 __global__ __launch_bounds__(GEMM_THREADS) void lut_gemm_kernel(const float *__restrict__ P,
                                                                const float *__restrict__ B, int C, int D, int M,
                                                                int64_t ldb, double *__restrict__ T,
                                                                double *__restrict__ delta, double *__restrict__ range)
 {
-    constexpr int ROWS = 16 * RT, TILES = 2 * RT;
-    constexpr int STAGE = ROWS * A_PITCH + GEMM_DEPTH * B_PITCH;           // floats of one of the two stages
-    constexpr size_t PART = sizeof(double) * KSPLIT * TILES * 4 * 64;
-    constexpr size_t LDS = sizeof(float) * 2 * STAGE > PART ? sizeof(float) * 2 * STAGE : PART;
-    __shared__ __align__(16) unsigned char lds[LDS];
-    float *stage = reinterpret_cast<float *>(lds);
-    double(*part)[TILES][4][64] = reinterpret_cast<double(*)[TILES][4][64]>(lds);   // once the stages are done with
+    constexpr int TILES = 2 * RT;
+    __shared__ double part[KSPLIT][TILES][4][64];
     const int c0 = blockIdx.x * RT, m0 = blockIdx.y * GEMM_COLS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, w = wave % KSPLIT, half = wave / KSPLIT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, kk = lane >> 4;
 
-    constexpr int PER_A = ROWS * GEMM_DEPTH / GEMM_THREADS, PER_B = GEMM_DEPTH * GEMM_COLS / GEMM_THREADS;
-    constexpr int A_STEP = GEMM_THREADS / GEMM_DEPTH, B_STEP = GEMM_THREADS / GEMM_COLS;
-    // where this thread's first pieces lie; rows and columns that do not exist read the last one and become zeros
-    // on their way to LDS (decided at the load, the compiler makes every load a branch of its own, each waited for)
-    const int m_own = m0 + tid % GEMM_COLS;
-    const float *b_src = B + min(m_own, M - 1);
-    float a_next[PER_A], b_next[PER_B];
-    auto fetch = [&](int d0) __attribute__((always_inline)) {
-        const int d_a = d0 + lane;
-        const float *a_src = P + min(d_a, D - 1);
+    struct Operands {
+        float a[RT][4], b[2][4];
+    };
+    // (rows, columns and depths that do not exist read others; those depths become zeros where they are used)
+    const float *a_row[RT], *b_col[2];
 #pragma unroll
-        for (int u = 0; u < PER_A; ++u) {
-            const int row = 16 * c0 + wave + A_STEP * u;
-            a_next[u] = a_src[(size_t)min(row, 16 * C - 1) * D];
+    for (int r = 0; r < RT; ++r) a_row[r] = P + (size_t)min(16 * (c0 + r) + i, 16 * C - 1) * D;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) b_col[h] = B + min(m0 + 16 * h + i, M - 1);
+    auto fetch = [&](Operands &o, int d0) __attribute__((always_inline)) {
+        const int d = d0 + 4 * kk;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            if constexpr (VEC) {
+                const float4 v = *reinterpret_cast<const float4 *>(a_row[r] + min(d, D - 4));
+                o.a[r][0] = v.x;
+                o.a[r][1] = v.y;
+                o.a[r][2] = v.z;
+                o.a[r][3] = v.w;
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o.a[r][t] = a_row[r][min(d + t, D - 1)];
+            }
         }
 #pragma unroll
-        for (int u = 0; u < PER_B; ++u) {
-            const int d = d0 + tid / GEMM_COLS + B_STEP * u;
-            b_next[u] = b_src[(size_t)min(d, D - 1) * ldb];
+        for (int t = 0; t < 4; ++t) {
+            const int64_t row = (int64_t)min(d + t, D - 1) * ldb;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) o.b[h][t] = b_col[h][row];
         }
     };
-    double4_t acc[RT];
+    double4_t acc[RT][2];
 #pragma unroll
-    for (int r = 0; r < RT; ++r) acc[r] = double4_t{0.0, 0.0, 0.0, 0.0};
-    fetch(0);
-    int parity = 0;
-    for (int d0 = 0; d0 < D; d0 += GEMM_DEPTH, parity ^= 1) {
-        float *As = stage + parity * STAGE, *Bs = As + ROWS * A_PITCH;
+    for (int r = 0; r < RT; ++r) acc[r][0] = acc[r][1] = double4_t{0.0, 0.0, 0.0, 0.0};
+    auto contract = [&](Operands &o, int d0) __attribute__((always_inline)) {
+        if (d0 + 16 > D) {
 #pragma unroll
-        for (int u = 0; u < PER_A; ++u)
-            As[(wave + A_STEP * u) * A_PITCH + lane] = 16 * c0 + wave + A_STEP * u < 16 * C && d0 + lane < D ? a_next[u] : 0.0f;
+            for (int t = 0; t < 4; ++t) {
+                const bool here = d0 + 4 * kk + t < D;
 #pragma unroll
-        for (int u = 0; u < PER_B; ++u)
-            Bs[(tid / GEMM_COLS + B_STEP * u) * B_PITCH + tid % GEMM_COLS] =
-                d0 + tid / GEMM_COLS + B_STEP * u < D && m_own < M ? b_next[u] : 0.0f;
-        __syncthreads();
-        if (d0 + GEMM_DEPTH < D) fetch(d0 + GEMM_DEPTH);
+                for (int r = 0; r < RT; ++r) o.a[r][t] = here ? o.a[r][t] : 0.0f;
 #pragma unroll
-        for (int s = 0; s < GEMM_DEPTH / 16; ++s) {
-            const int k = 16 * s + 4 * w + kk;
-            const double bv = (double)Bs[k * B_PITCH + 16 * half + i];
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)As[(16 * r + i) * A_PITCH + k], bv, acc[r], 0, 0, 0);
+                for (int h = 0; h < 2; ++h) o.b[h][t] = here ? o.b[h][t] : 0.0f;
+            }
         }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const double b0 = (double)o.b[0][t], b1 = (double)o.b[1][t];
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                const double av = (double)o.a[r][t];
+                acc[r][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b0, acc[r][0], 0, 0, 0);
+                acc[r][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b1, acc[r][1], 0, 0, 0);
+            }
+        }
+    };
+    Operands o;
+    int d0 = 16 * wave;
+    if (d0 < D) fetch(o, d0);
+    // (the last step by itself: with the fetch under a condition the compiler waits for all of it at once, 33 us; fetched
+    // past the end, the last values are waited for at the barrier)
+    for (; d0 + GEMM_DEPTH < D; d0 += GEMM_DEPTH) {
+        contract(o, d0);
+        fetch(o, d0 + GEMM_DEPTH);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
+    if (d0 < D) contract(o, d0);
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) part[w][2 * r + half][e][lane] = acc[r][e];
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wave][2 * r + h][e][lane] = acc[r][h][e];
     __syncthreads();
-    for (int tile = wave; tile < TILES; tile += 2 * KSPLIT) {
+    for (int tile = wave; tile < TILES; tile += KSPLIT) {
         const int c = c0 + tile / 2, m = m0 + 16 * (tile % 2) + i;
         // (an entry that is not a number counts neither way, unless it is the table's first: then minimum and range are
         // none either, as a walk over the sixteen that begins with the first has it)
@@ -162,6 +179,13 @@ __global__ __launch_bounds__(256) void lut_quantize_kernel(const double *__restr
     const int tx = threadIdx.x % QUANT_COLS, ty = threadIdx.x / QUANT_COLS;
     const int m = blockIdx.x * QUANT_COLS + tx, c0 = blockIdx.y * QUANT_CODEBOOKS;
     double r = 0.0;
+    // (the entries first: they are on their way while the scale is worked out; 30 -> 27 us for the table build above)
+    constexpr int PER = 4 * QUANT_CODEBOOKS;          // entry 4 u + ty of the workgroup's
+    double entry[PER], least[QUANT_CODEBOOKS];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) entry[u] = T[(size_t)min(16 * c0 + 4 * u + ty, 16 * C - 1) * M + min(m, M - 1)];
+#pragma unroll
+    for (int k = 0; k < QUANT_CODEBOOKS; ++k) least[k] = delta[(size_t)min(c0 + k, C - 1) * M + min(m, M - 1)];
     if (m < M)
         for (int c = ty; c < C; c += 4 * QUANT_BATCH) {
             double e[QUANT_BATCH];
@@ -188,14 +212,13 @@ __global__ __launch_bounds__(256) void lut_quantize_kernel(const double *__restr
         scale[m] = ldexpf(1.0f, -l);
         offset[m] = (float)beta;
     }
-    for (int row = ty; row < 16 * QUANT_CODEBOOKS; row += 4) {
-        const int c = c0 + row / 16;
-        if (c >= C) break;
-        const size_t at = ((size_t)c * 16 + row % 16) * M + m;
-        double q = rint(ldexp(T[at] - delta[(size_t)c * M + m], l));
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (c0 + u / 4 >= C) break;
+        double q = rint(ldexp(entry[u] - least[u / 4], l));
         q = (q >= 0.0) ? q : 0.0;  // NaN -> 0
         q = q > 255.0 ? 255.0 : q;
-        luts[at] = (uint8_t)q;
+        luts[(size_t)(16 * c0 + 4 * u + ty) * M + m] = (uint8_t)q;
     }
 }
 
@@ -310,15 +333,16 @@ int launch_build_luts(const maddness_params &p, const float *B, int32_t M, int64
     // as many codebooks to a workgroup as still leave one per compute unit
     const int col_tiles = (M + GEMM_COLS - 1) / GEMM_COLS, cus = device_info().cus;
     auto groups = [&](int rt) { return (C + rt - 1) / rt; };
-    if (groups(4) * col_tiles >= cus)
-        hipLaunchKernelGGL(lut_gemm_kernel<4>, dim3(groups(4), col_tiles), dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M,
-                           ldb, T, delta, range);
-    else if (groups(2) * col_tiles >= cus)
-        hipLaunchKernelGGL(lut_gemm_kernel<2>, dim3(groups(2), col_tiles), dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M,
-                           ldb, T, delta, range);
-    else
-        hipLaunchKernelGGL(lut_gemm_kernel<1>, dim3(groups(1), col_tiles), dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M,
-                           ldb, T, delta, range);
+    const bool vec = p.D % 4 == 0 && reinterpret_cast<uintptr_t>(p.prototypes) % 16 == 0;
+    auto launch = [&](auto rt) {
+        constexpr int RT = decltype(rt)::value;
+        const dim3 grid(groups(RT), col_tiles);
+        if (vec) hipLaunchKernelGGL((lut_gemm_kernel<RT, true>), grid, dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M, ldb, T, delta, range);
+        else hipLaunchKernelGGL((lut_gemm_kernel<RT, false>), grid, dim3(GEMM_THREADS), 0, stream, p.prototypes, B, C, p.D, M, ldb, T, delta, range);
+    };
+    if (groups(4) * col_tiles >= cus) launch(std::integral_constant<int, 4>{});
+    else if (groups(2) * col_tiles >= cus) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 1>{});
     int rc = check_hip(hipGetLastError(), "launch lut_gemm_kernel");
     if (rc != MADDNESS_OK) return rc;
     if (!pooled) {
