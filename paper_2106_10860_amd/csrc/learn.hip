@@ -1697,6 +1697,9 @@ struct ProtoArgs {
     int32_t D, C, Q;        // Q = 16 C
     int32_t *bounds;
     int32_t *counts;        // [Q][Q] G^T G
+    int32_t *range_part;    // [D / 64 and more][kProtoParts][2] what a part of 64 columns' values span
+    int32_t row_bits;       // N <= 2^row_bits
+    int32_t shares;         // wavefronts that share a code's rows where any order will do
     double *M;              // [Q][Q]: G^T G + lambda I, then M[k][i] = L[i][k]
     double *Lr;             // [Q][Q]: L by rows
     double *R;              // [Q][D]: G^T A~
@@ -1706,6 +1709,49 @@ struct ProtoArgs {
     int32_t *list_start;    // [C][17] where those of a code begin
     float *P;               // out [C][16][D]
 };
+
+// G^T A~ where its sums' bits allow any order (as any_order for the trees, 64 columns at a time): workgroups of parts of the
+// rows note what those span, and leave it at that as soon as it is too much, for most data after the first rows.  The
+// other workgroups clear the counters and the sums that are added to.
+constexpr int kProtoParts = 256, kProtoClear = 256;
+__global__ __launch_bounds__(256) void prepare_kernel(const ProtoArgs a)
+{
+    const int64_t QQ = (int64_t)a.Q * a.Q, QD = (int64_t)a.Q * a.D;
+    if (blockIdx.x < kProtoClear) {
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < QQ; i += 256 * kProtoClear) a.counts[i] = 0;
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < QD; i += 256 * kProtoClear) a.R[i] = 0.0;
+        return;
+    }
+    const int block = (blockIdx.x - kProtoClear) / kProtoParts, part = (blockIdx.x - kProtoClear) % kProtoParts;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = min(64 * block + lane, a.D - 1);
+    __shared__ int32_t widest[4][2];
+    const int64_t first = a.N * part / kProtoParts, end = a.N * (part + 1) / kProtoParts;
+    int top = 0, least = 0;
+    for (int64_t n0 = first; n0 < end; n0 += 64) {
+        float x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = a.A[min(n0 + 4 * u + wave, end - 1) * a.lda + col];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) span_of(x[u], top, least);
+        if (__ballot(top != 0 && top + least - kLeast + a.row_bits > 53)) {
+            top = kNoNumber;
+            break;
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        top = max(top, __shfl_xor(top, off));
+        least = max(least, __shfl_xor(least, off));
+    }
+    if (lane == 0) {
+        widest[wave][0] = top;
+        widest[wave][1] = least;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        a.range_part[((size_t)block * kProtoParts + part) * 2 + threadIdx.x] =
+            max(max(widest[0][threadIdx.x], widest[1][threadIdx.x]), max(widest[2][threadIdx.x], widest[3][threadIdx.x]));
+}
 
 // G^T G: entry (q, q') counts the training rows whose one-hot row has ones at q and q'.  A workgroup takes
 // codebook c against kCoGroup codebooks c2 and a stretch of the rows, counts in LDS (16 x 16 counters a pair), and adds
@@ -1753,7 +1799,9 @@ __global__ __launch_bounds__(256) void ridge_matrix_kernel(const ProtoArgs a, do
 // meet in its L2.  Bound by the instructions per row (its address, a load, a conversion, an addition):
 // 0.20 + 0.02 ms for 20000 x 512 and 32 codebooks, 0.77 + 0.08 ms for 260100 x 27 and 4 (1.0 and 7.5 ms with every thread
 // reading all rows; four columns to a lane, for a third of the instructions, gave 0.27 ms: fewer wavefronts, and rows
-// four times as long to keep in L2).
+// four times as long to keep in L2).  Where the sums are exact in any order and these wavefronts leave the chip empty, several share
+// a code's rows and add to the result: 260100 x 27 with 4 0.04 ms instead of 0.75,
+// 0.02 for finding out (5 us for data that are not, in a launch that clears the sums as well).
 constexpr int kListRows = 65536;       // rows of a stretch, at most (their distances in bytes from its first fit 32 bits)
 constexpr int kGtaAhead = 32;
 constexpr int kListSpare = 4 * kGtaAhead;     // entries read past the last (and not used)
@@ -1842,11 +1890,33 @@ __global__ __launch_bounds__(256) void list_codes_kernel(const ProtoArgs a, int6
 __global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t first_row)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int k = blockIdx.y * 4 + wave, c = blockIdx.z;
+    const int k = blockIdx.y * 4 + wave, c = blockIdx.z % a.C, share = blockIdx.z / a.C;
     const int col = blockIdx.x * 64 + lane;
-    const int start = a.list_start[c * 17 + k], count = a.list_start[c * 17 + k + 1] - start;
+    int start = a.list_start[c * 17 + k], count = a.list_start[c * 17 + k + 1] - start;
     double *out = a.R + ((size_t)16 * c + k) * a.D + col;
-    double sum = first_row > 0 && col < a.D ? *out : 0.0;
+    bool shared = false;
+    if (a.shares > 1) {
+        const int32_t *range = a.range_part + (size_t)blockIdx.x * kProtoParts * 2;
+        int top = 0, least = 0;
+#pragma unroll
+        for (int i = 0; i < kProtoParts; i += 64) {
+            top = max(top, range[2 * (i + lane)]);
+            least = max(least, range[2 * (i + lane) + 1]);
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            top = max(top, __shfl_xor(top, off));
+            least = max(least, __shfl_xor(least, off));
+        }
+        shared = __builtin_amdgcn_readfirstlane(top == 0 || top + least - kLeast + a.row_bits <= 53);
+        if (share > 0 && !shared) return;
+    }
+    if (shared) {
+        const int per = (count + a.shares - 1) / a.shares;
+        start += share * per;
+        count = max(0, min(per, count - share * per));
+    }
+    double sum = !shared && first_row > 0 && col < a.D ? *out : 0.0;
     if (count > 0) {
         // (the same for a whole wavefront, and written by a kernel before this one: scalar loads)
         const auto *list = (const __attribute__((address_space(4))) uint32_t *)(a.list + (size_t)c * (kListRows + kListSpare) + start);
@@ -1888,7 +1958,9 @@ __global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t fir
             add(x1, at + kGtaAhead);
         }
     }
-    if (col < a.D) *out = sum;
+    if (col >= a.D) return;
+    if (!shared) *out = sum;
+    else if (count > 0) unsafeAtomicAdd(out, sum);      // (exact, in whatever order)
 }
 
 // Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
@@ -2245,6 +2317,7 @@ void carve_prototypes(Carver &w, ProtoArgs &a)
     const size_t Q = a.Q;
     a.bounds = w.take<int32_t>(2 * (size_t)a.C);
     a.counts = w.take<int32_t>(Q * Q);
+    a.range_part = w.take<int32_t>((size_t)(a.D + 63) / 64 * kProtoParts * 2);
     a.M = w.take<double>(Q * Q);
     a.Lr = w.take<double>(Q * Q);
     a.R = w.take<double>(Q * a.D);
@@ -2449,10 +2522,14 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
         LAUNCH_OK("launch means_kernel");
         return MADDNESS_OK;
     }
-    note_kernel("cooccurrence_kernel + count_codes_kernel + list_codes_kernel + gta_kernel + cholesky_panel_kernel + substitution_kernel", nullptr);
+    note_kernel("prepare_kernel + cooccurrence_kernel + count_codes_kernel + list_codes_kernel + gta_kernel + cholesky_panel_kernel + substitution_kernel", nullptr);
     const int64_t QQ = (int64_t)a.Q * a.Q;
-    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((QQ + 255) / 256)), dim3(256), 0, stream, a.counts, QQ);
-    LAUNCH_OK("launch clear_kernel");
+    a.row_bits = N > 1 ? 64 - __builtin_clzll((unsigned long long)(N - 1)) : 0;
+    // (four wavefronts to a SIMD in all, each with 64 rows or more)
+    const int64_t waves = (int64_t)(D + 63) / 64 * 16 * C;
+    a.shares = (int)std::max<int64_t>(1, std::min<int64_t>(16 * device_info().cus / waves, std::min<int64_t>(N, kListRows) / 16 / 64));
+    hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(kProtoClear + (a.shares > 1 ? (D + 63) / 64 * kProtoParts : 0))), dim3(256), 0, stream, a);
+    LAUNCH_OK("launch prepare_kernel");
     // (stretches of at least 2048 rows, and about four workgroups per compute unit)
     const int co_groups = (C + kCoGroup - 1) / kCoGroup;
     const int64_t stretches = std::max<int64_t>(1, std::min<int64_t>(N / 2048, 4 * device_info().cus / (C * co_groups)));
@@ -2468,7 +2545,7 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
         LAUNCH_OK("launch count_codes_kernel");
         hipLaunchKernelGGL(list_codes_kernel, chunks, dim3(256), 0, stream, a, first);
         LAUNCH_OK("launch list_codes_kernel");
-        hipLaunchKernelGGL(gta_kernel, dim3((D + 63) / 64, 4, C), dim3(256), 0, stream, a, first);
+        hipLaunchKernelGGL(gta_kernel, dim3((D + 63) / 64, 4, C * a.shares), dim3(256), 0, stream, a, first);
         LAUNCH_OK("launch gta_kernel");
     }
     for (int J0 = 0; J0 < a.Q; J0 += kCholPanel) {
