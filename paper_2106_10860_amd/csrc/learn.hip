@@ -23,9 +23,8 @@
 //   loss_parts_kernel, select_kernel  heuristic_select_idxs by estimates: the four columns with the largest summed loss
 //   bucket_loss_kernel   L(j, B) (Section 4.2) for every column j of every bucket, two passes
 //                        over the bucket's own rows (the exact losses, where the estimates are unsure)
-//   sort_chunks_kernel, sort_exchange_kernel  the rows ordered by each candidate column (bitonic sort of
-//                        (value, row) keys: equal values stay in row order, as a stable sort
-//                        of a bucket's rows leaves them)
+//   sort_round_kernel, or sort_count_kernel and sort_scatter_kernel  the rows ordered by each candidate column (radix
+//                        sort of (value, row) keys: equal values stay in row order)
 //   tile_sums_kernel, scan_groups_kernel, split_gains_kernel, choose_by_gain_kernel  Algorithm 3 for every bucket and
 //                        Algorithm 2's choice among the candidates by estimates
 //   split_chains_kernel (split_chains_small_kernel), split_losses_kernel, choose_kernel  the same where those are unsure:
@@ -42,7 +41,6 @@ namespace {
 
 constexpr int kSplitBuckets = 8;   // buckets of the deepest level that is split (level 4 splits 8)
 constexpr int kCand = 4;           // candidate columns per level (Section 4.2: n = 4)
-constexpr int kSortChunk = 8192;   // keys sorted in LDS at a time (64 KiB)
 
 struct Bounds {
     int32_t v[2 * MADDNESS_MAX_C];
@@ -50,7 +48,7 @@ struct Bounds {
 
 struct LearnArgs {
     const float *A;
-    int64_t lda, N, Npad;
+    int64_t lda, N;
     int32_t C, dmax;
     int32_t *bounds;      // [C][2] first and one-past-last column of every codebook
     int32_t pitch;        // values of a row of X: dmax rounded up to whole groups of columns
@@ -66,7 +64,9 @@ struct LearnArgs {
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
-    uint64_t *keys;       // [C][4][Npad] sorted (value, row) keys
+    uint64_t *keys;       // [C][4][N] sorted (value, row) keys
+    uint64_t *keys2;      // [C][4][N] the same between digits
+    uint32_t *digit_counts;  // [C][4][kMaxSortChunks][kSortBins] keys of every digit in every chunk
     int64_t tile_slots;   // tiles of kSplitRows sorted rows of all buckets of a level, at most
     double *sums;         // [C][4][2][tile_slots][2][dmax] Algorithm 4's running sums before every tile, up and down
     int64_t group_slots;  // groups of kGroupTiles tiles of all buckets of a level, at most
@@ -826,146 +826,247 @@ __device__ __forceinline__ float key_value(uint64_t key)
 }
 __device__ __forceinline__ int32_t key_row(uint64_t key) { return (int32_t)(key & ((1u << kKeyRowBits) - 1u)); }
 
-// Bitonic sort of Npad keys (a power of two) per (codebook, candidate).  The exchanges at distances below
-// kSortChunk run on chunks of kSortChunk keys in LDS, a workgroup per chunk (sort_chunks_kernel: from the rows
-// themselves, all stages, when k_first is 2; else the distances j_first .. 1 of stage k_first); the exchanges
-// at larger distances go through memory (sort_exchange_kernel).  Both take three distances at a time, eight keys to a
-// thread: bound by LDS, 33 passes over a chunk instead of 91 (20000 rows, 32 codebooks: a level's sort 0.15 ms against
-// 0.23 with a pass per distance).
-__device__ __forceinline__ void exchange(uint64_t &x, uint64_t &y, bool ascending)
+// The rows of every (codebook, candidate) sorted by their keys, least significant digit first, four digits of nine bits of
+// value and bucket (rows that are equal there stay in row order).  A workgroup takes up to 4096 keys at a time (8192 by sort_round_kernel),
+// an eighth of them in a row to a wavefront: a key's place among its wavefront's of the same digit comes from nine ballots and a counter in LDS, the
+// place of the wavefronts' from those counters, and the keys go through LDS in the digit's order, so that what is written
+// are runs.  Up to kSortRound rows are sorted by one launch (sort_round_kernel); more take two a digit: sort_count_kernel counts the
+// digits of every chunk of them, sort_scatter_kernel finds where the chunk's begin and moves its keys.  Bound by the
+// chain of steps of a round, some 60 instructions a key and digit the longest.  (A level's sort, us: 20000 rows, 32 codebooks 117, 150
+// by a bitonic network, 33 passes of 64-bit exchanges over 8192 keys in LDS and the larger distances through memory; 260100,
+// 4 codebooks 165 and 262.  Rounds of 8192 keys: 177 and 164; the first digit's keys made from the rows twice, without regard to
+// XCDs: 156 and 168.)
+constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64, kSortBits = 9, kSortBins = 1 << kSortBits, kSortDigits = 4;
+constexpr int kSortPer = 16, kSortRound = kSortThreads * kSortPer;            // keys of sort_round_kernel
+constexpr int kChunkPer = 8, kChunkRound = kSortThreads * kChunkPer, kMaxSortChunks = 64;      // of a chunk's round
+static_assert(kSortBins == kSortThreads, "a thread per digit");
+static_assert(kSortDigits * kSortBits >= 32 + 3, "value and bucket");
+__device__ __forceinline__ int key_digit(uint64_t key, int digit)
 {
-    const bool swap = (x > y) == ascending;
-    const uint64_t low = swap ? y : x, high = swap ? x : y;
-    x = low;
-    y = high;
+    return (int)(key >> (kKeyRowBits + kSortBits * digit)) & (kSortBins - 1);
+}
+// rows of a chunk: even shares of whole rounds, few enough chunks that every workgroup can add up all of their counts
+__host__ __device__ constexpr int64_t sort_chunk_rows(int64_t N)
+{
+    const int64_t rounds = (N + kChunkRound - 1) / kChunkRound, per = (rounds + kMaxSortChunks - 1) / kMaxSortChunks;
+    const int64_t chunks = (rounds + per - 1) / per;
+    return ((N + chunks - 1) / chunks + kSortThreads - 1) / kSortThreads * kSortThreads;
 }
 
-// the exchanges at distances 4h, 2h and h (the first kCount of them) among the keys i + e h, e = 0..7
-template <int kCount>
-__device__ __forceinline__ void exchange_eight(uint64_t (&v)[8], int64_t i, int64_t h, int64_t k)
+template <int kPer>
+struct SortLds {
+    uint64_t keys[kSortThreads * kPer];
+    uint16_t counts[kSortWaves][kSortBins];        // (two workgroups to a compute unit)
+    int32_t to[kSortBins];
+    uint32_t of_wave[kSortWaves];
+};
+
+// the sum over the workgroup's threads before this one
+__device__ __forceinline__ uint32_t sum_before(uint32_t x, uint32_t *of_wave)
 {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t sum = x;
 #pragma unroll
-    for (int step = 0; step < kCount; ++step) {
-        const int apart = 4 >> step;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if ((e & apart) == 0) exchange(v[e], v[e + apart], ((i + e * h) & k) == 0);
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t other = __shfl_up(sum, off);
+        sum += lane >= off ? other : 0u;
     }
+    if (lane == 63) of_wave[wave] = sum;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) before += w < wave ? of_wave[w] : 0u;
+    return before + sum - x;
 }
 
-constexpr int kSortThreads = kSortChunk / 8;
-__device__ __forceinline__ int sort_place(int i) { return i + (i >> 3); }      // (eight keys side by side meet in no LDS bank)
-constexpr size_t sort_lds_bytes(int64_t chunk) { return sizeof(uint64_t) * (size_t)(chunk + chunk / 8 + 1); }
-
-__global__ __launch_bounds__(kSortThreads) void sort_chunks_kernel(const LearnArgs a, int64_t k_first, int64_t j_first, int n_buckets)
+// One round: the thread's keys (64 i + lane of its wavefront's 64 per_wave; those that do not exist have the last digit and
+// come last) go to s.keys in the digit's order.  Returns how many have digit threadIdx.x; *place is where those begin.
+template <int kPer>
+__device__ __forceinline__ uint32_t sort_round(SortLds<kPer> &s, const uint64_t (&key)[kPer], const int (&digit)[kPer], int per_wave, uint32_t *place)
 {
-    extern __shared__ uint64_t chunk[];
-    const int c = blockIdx.z, q = blockIdx.y;
-    const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
-    if (q >= min(kCand, d)) return;
-    uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
-    const int64_t n = a.Npad;
-    const int m = (int)(n < kSortChunk ? n : kSortChunk);   // chunk length
-    const int64_t base = (int64_t)blockIdx.x * m;
-    const int tid = threadIdx.x;
-    if (j_first == 0) {
-        int selected;
-        if (a.unsure[2 * c]) {
-            // (what the estimates left in cand is not read)
-            int32_t &shared = *reinterpret_cast<int32_t *>(chunk + m + m / 8);       // (past the last key's place)
-            if (tid < 64) {
-                const int best = select_candidate(a, c, d, n_buckets, q);
-                if (tid == 0) shared = best;
-                if (tid == 0 && blockIdx.x == 0) {
-                    a.cand[c * kCand + q] = best;
-                    a.n_cand[c] = min(kCand, d);
-                }
+    const int tid = threadIdx.x, wave = tid >> 6;
+    uint32_t rank[kPer];
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) s.counts[w][tid] = 0;
+    __syncthreads();
+    volatile uint16_t *counts = s.counts[wave];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        if (i < per_wave) {
+            const int mine = digit[i];
+            uint32_t low = ~0u, high = ~0u;                       // the lanes with the same digit
+    #pragma unroll
+            for (int b = 0; b < kSortBits; ++b) {
+                const int32_t bit = mine << (31 - b) >> 31;
+                const unsigned long long m = __ballot(bit != 0);
+                low &= ~((uint32_t)m ^ (uint32_t)bit);
+                high &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
             }
-            __syncthreads();
-            selected = shared;
-        } else {
-            selected = a.cand[c * kCand + q];
+            const uint32_t before = __builtin_amdgcn_mbcnt_hi(high, __builtin_amdgcn_mbcnt_lo(low, 0));
+            const uint32_t seen = counts[mine], all = (uint32_t)(__popc(low) + __popc(high));
+            if (before + 1 == all) counts[mine] = (uint16_t)(seen + all);
+            rank[i] = seen + before;
+            wave_lds_fence();
         }
-        const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch + selected;
-        const uint8_t *node = a.node + (size_t)c * a.N;
-        for (int i = tid; i < m; i += kSortThreads) {
-            const int64_t p = base + i;
-            chunk[sort_place(i)] = p < a.N ? make_key(node[p], x[p * a.pitch], (uint32_t)p) : ~0ull;
-        }
-    } else {
-        for (int i = tid; i < m; i += kSortThreads) chunk[sort_place(i)] = keys[base + i];
     }
     __syncthreads();
-    if (m < 8) {        // (fewer rows than a thread takes)
-        if (tid == 0)
-            for (int i = 1; i < m; ++i)
-                for (int j = i; j > 0 && chunk[sort_place(j - 1)] > chunk[sort_place(j)]; --j) {
-                    const uint64_t t = chunk[sort_place(j)];
-                    chunk[sort_place(j)] = chunk[sort_place(j - 1)];
-                    chunk[sort_place(j - 1)] = t;
-                }
-        __syncthreads();
-    } else {
-        // one pass: distances 4h, 2h, h of stage k (the first kCount of them)
-        auto pass = [&](auto count, int h, int64_t k) __attribute__((always_inline)) {
-            if (8 * tid < m) {
-                const int i = ((tid & ~(h - 1)) << 3) | (tid & (h - 1));
-                uint64_t v[8];
+    uint32_t all = 0;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = chunk[sort_place(i + e * h)];
-                if constexpr (decltype(count)::value == 0) {         // (the first three stages)
-                    exchange(v[0], v[1], true), exchange(v[2], v[3], false), exchange(v[4], v[5], true), exchange(v[6], v[7], false);
-                    exchange(v[0], v[2], true), exchange(v[1], v[3], true), exchange(v[4], v[6], false), exchange(v[5], v[7], false);
-                    exchange(v[0], v[1], true), exchange(v[2], v[3], true), exchange(v[4], v[5], false), exchange(v[6], v[7], false);
-                    exchange_eight<3>(v, base + i, 1, k);
-                } else {
-                    exchange_eight<decltype(count)::value>(v, base + i, h, k);
-                }
+    for (int w = 0; w < kSortWaves; ++w) all += s.counts[w][tid];
+    uint32_t at = sum_before(all, s.of_wave);
+    *place = at;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) chunk[sort_place(i + e * h)] = v[e];
-            }
-            __syncthreads();
-        };
-        using std::integral_constant;
-        if (j_first == 0) pass(integral_constant<int, 0>{}, 1, 8);
-        for (int64_t k = j_first ? k_first : 16; k <= (j_first ? k_first : (int64_t)m); k <<= 1) {
-            int j = j_first ? (int)j_first : (int)(k >> 1);          // (j >= 8: 2^distances)
-            const int distances = 32 - __clz(j);
-            if (distances % 3 == 1) {
-                pass(integral_constant<int, 1>{}, j >> 2, k);
-                j >>= 1;
-            } else if (distances % 3 == 2) {
-                pass(integral_constant<int, 2>{}, j >> 2, k);
-                j >>= 2;
-            }
-            for (; j > 0; j >>= 3) pass(integral_constant<int, 3>{}, j >> 2, k);
-        }
+    for (int w = 0; w < kSortWaves; ++w) {
+        const uint32_t here = s.counts[w][tid];
+        s.counts[w][tid] = (uint16_t)at;
+        at += here;
     }
-    for (int i = tid; i < m; i += kSortThreads) keys[base + i] = chunk[sort_place(i)];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        if (i < per_wave) s.keys[s.counts[wave][digit[i]] + rank[i]] = key[i];
+    __syncthreads();
+    return all;
 }
 
-// the distances h 2^(kCount - 1) .. h of stage k, 2^kCount keys to a thread
-template <int kCount>
-__global__ __launch_bounds__(256) void sort_exchange_kernel(const LearnArgs a, int64_t k, int64_t h)
+// The column of candidate q, which the workgroup finds out from the exact losses where the estimates were unsure (`shared`: a
+// word of LDS); `first` leaves it to the launches that follow.
+__device__ __forceinline__ int sort_column(const LearnArgs &a, int c, int q, int d, int n_buckets, bool first, int32_t *shared)
 {
-    constexpr int kKeys = 1 << kCount;
-    const int c = blockIdx.z, q = blockIdx.y;
+    if (!a.unsure[2 * c]) return a.cand[c * kCand + q];
+    // (what the estimates left in cand is not read)
+    if (threadIdx.x < 64) {
+        const int best = select_candidate(a, c, d, n_buckets, q);
+        if (threadIdx.x == 0) *shared = best;
+        if (threadIdx.x == 0 && first) {
+            a.cand[c * kCand + q] = best;
+            a.n_cand[c] = min(kCand, d);
+        }
+    }
+    __syncthreads();
+    return *shared;
+}
+
+__global__ __launch_bounds__(kSortThreads, 4) void sort_round_kernel(const LearnArgs a, int n_buckets)
+{
+    __shared__ SortLds<kSortPer> s;
+    const int c = blockIdx.z, q = blockIdx.y, d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (q >= min(kCand, d)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = (int)a.N, per_wave = (N + kSortThreads - 1) / kSortThreads;
+    const int col = sort_column(a, c, q, d, n_buckets, true, s.to);
+    const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch + col;
+    const uint8_t *node = a.node + (size_t)c * a.N;
+    uint64_t *out = a.keys + ((size_t)c * kCand + q) * a.N;
+    uint64_t key[kSortPer];
+    int digit[kSortPer];
+#pragma unroll
+    for (int i = 0; i < kSortPer; ++i) {
+        const int p = min(64 * (wave * per_wave + i) + lane, N - 1);
+        key[i] = make_key(node[p], x[(int64_t)p * a.pitch], (uint32_t)p);
+    }
+    for (int k = 0; k < kSortDigits; ++k) {
+#pragma unroll
+        for (int i = 0; i < kSortPer; ++i) digit[i] = 64 * (wave * per_wave + i) + lane < N ? key_digit(key[i], k) : kSortBins - 1;
+        uint32_t place;
+        sort_round(s, key, digit, per_wave, &place);
+        if (k + 1 < kSortDigits)
+#pragma unroll
+            for (int i = 0; i < kSortPer; ++i)
+                if (i < per_wave) key[i] = s.keys[64 * (wave * per_wave + i) + lane];
+    }
+    for (int i = tid; i < N; i += kSortThreads) out[i] = s.keys[i];
+}
+
+// the keys as digit k finds them
+__device__ __forceinline__ const uint64_t *sort_source(const LearnArgs &a, int c, int q, int k)
+{
+    return (k % 2 ? a.keys2 : a.keys) + ((size_t)c * kCand + q) * a.N;
+}
+
+__global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const LearnArgs a, int k, int n_buckets)
+{
+    __shared__ uint32_t counts[kSortBins];
+    __shared__ int32_t shared;
+    // (the codebook changes fastest from workgroup to workgroup: those of one codebook meet on few XCDs, whose L2 holds its columns)
+    const int c = blockIdx.x % a.C, chunk = blockIdx.x / a.C, q = blockIdx.y, d = a.bounds[2 * c + 1] - a.bounds[2 * c], tid = threadIdx.x;
+    if (q >= min(kCand, d)) return;
+    counts[tid] = 0;
+    const int64_t chunk_rows = sort_chunk_rows(a.N), first = chunk * chunk_rows, end = min(a.N, first + chunk_rows);
+    uint64_t *keys = const_cast<uint64_t *>(sort_source(a, c, q, k));
+    const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch;
+    const uint8_t *node = a.node + (size_t)c * a.N;
+    if (k == 0) x += sort_column(a, c, q, d, n_buckets, chunk == 0, &shared);
+    __syncthreads();
+    for (int64_t p0 = first; p0 < end; p0 += kChunkRound) {
+        int digit[kChunkPer];
+#pragma unroll
+        for (int i = 0; i < kChunkPer; ++i) {
+            const int64_t p = min(p0 + i * kSortThreads + tid, end - 1);
+            // (the first digit's keys are made here)
+            const uint64_t key = k == 0 ? make_key(node[p], x[p * a.pitch], (uint32_t)p) : keys[p];
+            if (k == 0) keys[p] = key;
+            digit[i] = key_digit(key, k);
+        }
+#pragma unroll
+        for (int i = 0; i < kChunkPer; ++i) {
+            // (a value that many rows have, as a ReLU's zeros, would be many additions to one word: the digits of the first two lanes
+            // that are left are counted by ballots)
+            bool left = p0 + i * kSortThreads + tid < end;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const unsigned long long lanes = __ballot(left);
+                if (!lanes) break;
+                const int one = __builtin_amdgcn_readlane(digit[i], __ffsll(lanes) - 1);
+                const unsigned long long same = __ballot(left && digit[i] == one);
+                if ((tid & 63) == __ffsll(lanes) - 1) atomicAdd(&counts[one], (uint32_t)__popcll(same));
+                left &= digit[i] != one;
+            }
+            if (left) atomicAdd(&counts[digit[i]], 1u);
+        }
+    }
+    __syncthreads();
+    a.digit_counts[(((size_t)c * kCand + q) * kMaxSortChunks + chunk) * kSortBins + tid] = counts[tid];
+}
+
+__global__ __launch_bounds__(kSortThreads, 4) void sort_scatter_kernel(const LearnArgs a, int k)
+{
+    __shared__ SortLds<kChunkPer> s;
+    const int c = blockIdx.x % a.C, chunk = blockIdx.x / a.C, n_chunks = gridDim.x / a.C, q = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (q >= a.n_cand[c]) return;
-    uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= a.Npad / kKeys) return;
-    const int64_t i = ((t & ~(h - 1)) << kCount) | (t & (h - 1));
-    uint64_t v[kKeys];
+    const int64_t chunk_rows = sort_chunk_rows(a.N), first = chunk * chunk_rows, end = min(a.N, first + chunk_rows);
+    const uint64_t *keys = sort_source(a, c, q, k);
+    uint64_t *out = const_cast<uint64_t *>(sort_source(a, c, q, k + 1));
+    // where the digit threadIdx.x of this chunk goes
+    const uint32_t *counts = a.digit_counts + ((size_t)c * kCand + q) * kMaxSortChunks * kSortBins + tid;
+    uint32_t all = 0, before = 0;
+#pragma unroll 8
+    for (int i = 0; i < n_chunks; ++i) {
+        const uint32_t here = counts[(size_t)i * kSortBins];
+        before += i < chunk ? here : 0u;
+        all += here;
+    }
+    uint32_t at = sum_before(all, s.of_wave) + before;
+    const int per_wave = (int)min((int64_t)kChunkPer, chunk_rows / kSortThreads);
+    for (int64_t p0 = first; p0 < end; p0 += kSortThreads * per_wave) {
+        uint64_t key[kChunkPer];
+        int digit[kChunkPer];
 #pragma unroll
-    for (int e = 0; e < kKeys; ++e) v[e] = keys[i + e * h];
-    const bool ascending = (i & k) == 0;             // (k is twice the largest distance or more: the same for all keys)
+        for (int i = 0; i < kChunkPer; ++i) key[i] = keys[min(p0 + 64 * (wave * per_wave + i) + lane, end - 1)];
 #pragma unroll
-    for (int apart = kKeys / 2; apart > 0; apart >>= 1)
-#pragma unroll
-        for (int e = 0; e < kKeys; ++e)
-            if ((e & apart) == 0) exchange(v[e], v[e + apart], ascending);
-#pragma unroll
-    for (int e = 0; e < kKeys; ++e) keys[i + e * h] = v[e];
+        for (int i = 0; i < kChunkPer; ++i) digit[i] = p0 + 64 * (wave * per_wave + i) + lane < end ? key_digit(key[i], k) : kSortBins - 1;
+        uint32_t place;
+        const uint32_t here = sort_round(s, key, digit, per_wave, &place);
+        s.to[tid] = (int32_t)(at - place);
+        at += here;
+        __syncthreads();
+        const int n = (int)min((int64_t)kSortThreads * per_wave, end - p0);
+        for (int i = tid; i < n; i += kSortThreads) {
+            const uint64_t v = s.keys[i];
+            out[s.to[key_digit(v, k)] + i] = v;
+        }
+        __syncthreads();
+    }
 }
 
 // Algorithm 3 in two parts.  Algorithm 4's running sums are the one serial thing in it, and a serial sum costs a
@@ -999,7 +1100,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     if (count <= (small_too ? kChainRows : 1) || !a.unsure[2 * c + 1]) return;
     constexpr int kTiles = kChainRows / kSplitRows;
     const int n_steps = (n_tiles + kTiles - 1) / kTiles;
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + start;
     const int tid = threadIdx.x, cols = min(NC, d - col0);
     const int chain = (tid / 16) % (2 * NC), l = tid & 15;
     const bool squares = chain >= NC;
@@ -1050,7 +1151,7 @@ __global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const Learn
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     if (count < 2 || count > kChainRows || !a.unsure[2 * c + 1]) return;
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows, n_rows = n_tiles * kSplitRows, tid = threadIdx.x;
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + start;
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
     for (int i = tid; i < n_rows; i += 16 * NC) rows[i] = i < count ? key_row(keys[i]) : (int32_t)a.N;
     __syncthreads();
@@ -1122,7 +1223,7 @@ __device__ __forceinline__ GroupRows<NC> list_group_rows(const LearnArgs &a, int
     }
     g.rows = max(0, min(kSplitRows, g.count - g.at));
     g.splits = 0;
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad;
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N;
     // two tiles' keys to a load
 #pragma unroll
     for (int i = 0; i < G::kTiles; i += 2) {
@@ -1420,7 +1521,7 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
     const int q = chosen;
     if (q < 0 || tid >= n_buckets) return;
     const int at = found[q][tid].at, count = (int)a.bucket_count[c * kSplitBuckets + tid];
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + a.bucket_start[c * kSplitBuckets + tid];
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + a.bucket_start[c * kSplitBuckets + tid];
     float v = 0.0f;
     if (at >= 0) v = split_value(keys[at], keys[at + 1]);
     else if (count > 0) v = a.X[((size_t)c * (a.N + 1) + key_row(keys[0])) * a.pitch + a.cand[c * kCand + q]];
@@ -1467,7 +1568,7 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
     const int tile0 = (int)(group - first_group(start, b)) * kGroupTiles;                   // of the bucket's tiles
     const int n_tiles = min(kGroupTiles, (count + T - 1) / T - tile0);
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
-    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+    const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + start;
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + 4 * (lane % kPieces);
     // as the sums are taken: a lane per chain
     const int chain_dir = (lane / (2 * NC)) & 1, which = (lane / NC) & 1, chain_col = lane % NC;
@@ -1626,7 +1727,7 @@ __global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int leve
                     loss = __builtin_nan("");
                 }
             }
-            const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.Npad + start;
+            const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + start;
             float v = 0.0f;
             if (at >= 0) {
                 v = split_value(keys[at], keys[at + 1]);
@@ -2259,13 +2360,6 @@ __global__ __launch_bounds__(64) void means_kernel(const ProtoArgs a)
 
 size_t align_up(size_t v, size_t al) { return (v + al - 1) / al * al; }
 
-int64_t pow2_at_least(int64_t n)
-{
-    int64_t p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
-
 // carves `bytes` (rounded up to 256) off the workspace
 struct Carver {
     unsigned char *at;
@@ -2295,7 +2389,11 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.rows_by_bucket = w.take<int32_t>(C * a.N);
     a.cand = w.take<int32_t>(C * kCand);
     a.n_cand = w.take<int32_t>(C);
-    a.keys = w.take<uint64_t>(C * kCand * a.Npad);
+    a.keys = w.take<uint64_t>(C * kCand * a.N);
+    if (a.N > kSortRound) {
+        a.keys2 = w.take<uint64_t>(C * kCand * a.N);
+        a.digit_counts = w.take<uint32_t>(C * kCand * kMaxSortChunks * kSortBins);
+    }
     a.tile_slots = a.N / kSplitRows + kSplitBuckets + 1;
     a.sums = w.take<double>(C * kCand * 2 * a.tile_slots * 2 * a.dmax);
     a.group_slots = a.N / kGroupRows + kSplitBuckets + 1;
@@ -2333,7 +2431,7 @@ namespace {
 size_t batch_bytes(int64_t N, int32_t C, int32_t dmax)
 {
     LearnArgs a{};
-    a.N = N; a.Npad = pow2_at_least(N); a.C = C; a.dmax = dmax;
+    a.N = N; a.C = C; a.dmax = dmax;
     Carver w{nullptr};
     carve_trees(w, a);
     return w.used;
@@ -2346,8 +2444,7 @@ size_t batch_bytes(int64_t N, int32_t C, int32_t dmax)
 // widest subspace in *dmax.
 int32_t batch_end(int64_t N, int32_t C, const int32_t *bounds, int32_t first, int32_t *dmax)
 {
-    const size_t rows = (size_t)N, padded = (size_t)pow2_at_least(N);
-    const size_t limit = std::max<size_t>((size_t)4 << 30, 2 * (size_t)C * (37 * rows + 32 * padded));
+    const size_t limit = std::max<size_t>((size_t)4 << 30, 2 * (size_t)C * 69 * (size_t)N);
     *dmax = 0;
     int32_t end = first;
     for (; end < C; ++end) {
@@ -2424,23 +2521,17 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
         }
         hipLaunchKernelGGL(bucket_loss_kernel, grid_bucket_loss, dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a, 0);
         LAUNCH_OK("launch bucket_loss_kernel");
-        const int64_t chunk_len = a.Npad < kSortChunk ? a.Npad : kSortChunk;
-        const dim3 chunks((unsigned)(a.Npad / chunk_len), kCand, C);
-        hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, (int64_t)2, (int64_t)0, n_buckets);
-        LAUNCH_OK("launch sort_chunks_kernel");
-        for (int64_t k = 2 * chunk_len; k <= a.Npad; k <<= 1) {
-            for (int64_t j = k >> 1; j >= chunk_len;) {
-                const int count = j >= 4 * chunk_len ? 3 : j >= 2 * chunk_len ? 2 : 1;
-                const dim3 threads((unsigned)(((a.Npad >> count) + 255) / 256), kCand, C);
-                const int64_t h = j >> (count - 1);
-                if (count == 3) hipLaunchKernelGGL(sort_exchange_kernel<3>, threads, dim3(256), 0, stream, a, k, h);
-                else if (count == 2) hipLaunchKernelGGL(sort_exchange_kernel<2>, threads, dim3(256), 0, stream, a, k, h);
-                else hipLaunchKernelGGL(sort_exchange_kernel<1>, threads, dim3(256), 0, stream, a, k, h);
-                LAUNCH_OK("launch sort_exchange_kernel");
-                j >>= count;
+        if (N <= kSortRound) {
+            hipLaunchKernelGGL(sort_round_kernel, dim3(1, kCand, C), dim3(kSortThreads), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch sort_round_kernel");
+        } else {
+            const dim3 chunks((unsigned)((N + sort_chunk_rows(N) - 1) / sort_chunk_rows(N) * C), kCand);
+            for (int k = 0; k < kSortDigits; ++k) {
+                hipLaunchKernelGGL(sort_count_kernel, chunks, dim3(kSortThreads), 0, stream, a, k, n_buckets);
+                LAUNCH_OK("launch sort_count_kernel");
+                hipLaunchKernelGGL(sort_scatter_kernel, chunks, dim3(kSortThreads), 0, stream, a, k);
+                LAUNCH_OK("launch sort_scatter_kernel");
             }
-            hipLaunchKernelGGL(sort_chunks_kernel, chunks, dim3(kSortThreads), sort_lds_bytes(chunk_len), stream, a, k, chunk_len >> 1, n_buckets);
-            LAUNCH_OK("launch sort_chunks_kernel");
         }
         // (columns eight or sixteen at a time)
         const int groups = narrow ? 1 : a.pitch / 16;
@@ -2490,12 +2581,11 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
 int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const int32_t *bounds_host, int32_t *split_dims,
                        float *thresholds, uint8_t *codes, void *workspace, hipStream_t stream)
 {
-    note_kernel("gather_columns_kernel + order_rows_kernel + loss_parts_kernel + select_kernel + bucket_loss_kernel + sort_chunks_kernel + sort_exchange_kernel + tile_sums_kernel + scan_groups_kernel + split_gains_kernel + choose_by_gain_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
-    if (int rc = allow_full_lds<sort_chunks_kernel>(); rc != MADDNESS_OK) return rc;
+    note_kernel("gather_columns_kernel + order_rows_kernel + loss_parts_kernel + select_kernel + bucket_loss_kernel + sort_round_kernel + sort_count_kernel + sort_scatter_kernel + tile_sums_kernel + scan_groups_kernel + split_gains_kernel + choose_by_gain_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
     for (int32_t c = 0; c < C;) {
         LearnArgs a{};
         const int32_t end = batch_end(N, C, bounds_host, c, &a.dmax);
-        a.A = A; a.lda = lda; a.N = N; a.Npad = pow2_at_least(N); a.C = end - c;
+        a.A = A; a.lda = lda; a.N = N; a.C = end - c;
         a.split_dims = split_dims + 4 * c; a.thresholds = thresholds + 16 * c;
         a.codes = codes ? codes + c : nullptr; a.codes_pitch = C;
         if (int rc = launch_learn_batch(a, bounds_host + 2 * c, workspace, stream); rc != MADDNESS_OK) return rc;
