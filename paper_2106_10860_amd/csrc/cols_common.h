@@ -31,9 +31,16 @@ __device__ __forceinline__ constant_ptr<T> as_constant(const T *p)
     return (constant_ptr<T>)(uintptr_t)p;
 }
 
+template <bool NT, typename T>
+__device__ __forceinline__ T load_once(const T *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // RPL consecutive elements of a column, widened to fp32.  idx and the column
-// stride are multiples of RPL, so the vector load is aligned.
-template <int DT, int RPL>
+// stride are multiples of RPL, so the vector load is aligned.  NT: past the caches.
+template <int DT, int RPL, bool NT>
 __device__ __forceinline__ void load_run(const void *A, int64_t idx, float (&x)[RPL])
 {
     static_assert(RPL == 1 || RPL == 2 || RPL == 4, "rows per lane");
@@ -41,12 +48,12 @@ __device__ __forceinline__ void load_run(const void *A, int64_t idx, float (&x)[
         x[0] = widen_at<DT>(A, idx);
     } else if constexpr (DT == kF32) {
         typedef float fv __attribute__((ext_vector_type(RPL)));
-        const fv v = *reinterpret_cast<const fv *>(static_cast<const float *>(A) + idx);
+        const fv v = load_once<NT>(reinterpret_cast<const fv *>(static_cast<const float *>(A) + idx));
 #pragma unroll
         for (int r = 0; r < RPL; ++r) x[r] = v[r];
     } else if constexpr (DT == kF16) {
         typedef _Float16 hv __attribute__((ext_vector_type(RPL)));
-        const hv v = *reinterpret_cast<const hv *>(static_cast<const _Float16 *>(A) + idx);
+        const hv v = load_once<NT>(reinterpret_cast<const hv *>(static_cast<const _Float16 *>(A) + idx));
 #pragma unroll
         for (int r = 0; r < RPL; ++r) x[r] = (float)v[r];
     } else if constexpr (DT == kBF16) {
@@ -55,7 +62,7 @@ __device__ __forceinline__ void load_run(const void *A, int64_t idx, float (&x)[
         if constexpr (RPL == 2) {
             w[0] = p[0];
         } else {
-            const u2 v = *reinterpret_cast<const u2 *>(p);
+            const u2 v = load_once<NT>(reinterpret_cast<const u2 *>(p));
             w[0] = v.x; w[1] = v.y;
         }
 #pragma unroll
@@ -79,7 +86,7 @@ __device__ __forceinline__ void load_run(const void *A, int64_t idx, float (&x)[
 // word of eight codes being filled and the words finished.  The number of rows N is a
 // multiple of RPL (the launchers hand the last N % 4 rows to the general kernels); a
 // lane past the end reads the last run of the matrix instead, and its codes are not used.
-template <int C, int DT, int CHUNK, int RPL>
+template <int C, int DT, int CHUNK, int RPL, bool NT = false>
 struct ColsEncoder {
     static_assert(C % 8 == 0 && 8 % CHUNK == 0, "a chunk of codebooks lies within one word of codes");
     static constexpr int CW = C / 8;
@@ -106,7 +113,7 @@ struct ColsEncoder {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int j = min(max(split_dims[4 * c + t], 0), a.D - 1);
-                load_run<DT, RPL>(a.A, (int64_t)j * a.lda + nq, x_nxt[u][t]);
+                load_run<DT, RPL, NT>(a.A, (int64_t)j * a.lda + nq, x_nxt[u][t]);
             }
 #pragma unroll
             for (int i = 0; i < 15; ++i) tr_nxt[u].t[i] = thresholds[16 * c + i];

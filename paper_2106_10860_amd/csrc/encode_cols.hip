@@ -25,8 +25,8 @@ using namespace rows;
 using namespace cols;
 
 // CHUNK: codebooks whose loads are issued together (4 loads each); RPL: rows per lane;
-// PIPE (fused mode, M = 256, fp32 output only): encode the next group while scanning.
-template <int MODE, int C, int WAVES, bool AVG, int DT, int CHUNK, int RPL, bool PIPE>
+// PIPE (fused mode, M = 256, fp32 output only): encode the next group while scanning; NT: columns that no cache would hold.
+template <int MODE, int C, int WAVES, bool AVG, int DT, int CHUNK, int RPL, bool PIPE, bool NT>
 __global__ __launch_bounds__(WAVES * 64) void cols_kernel(const RowsArgs a)
 {
     static_assert(MODE == kFused || MODE == kEncode, "modes");
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(WAVES * 64) void cols_kernel(const RowsArgs a)
 
     const int64_t n_groups = (a.N + GROUP - 1) / GROUP;
     const int64_t gstride = (int64_t)gridDim.x * WAVES;
-    ColsEncoder<C, DT, CHUNK, RPL> enc(a);
+    ColsEncoder<C, DT, CHUNK, RPL, NT> enc(a);
 
     int64_t g = (int64_t)blockIdx.x * WAVES + wave;
     if constexpr (MODE == kEncode) {
@@ -175,20 +175,20 @@ __global__ __launch_bounds__(WAVES * 64) void cols_kernel(const RowsArgs a)
 #define MADDNESS_COLS_FUSED_GROUPS_PER_WAVE 1
 #endif
 
-template <int MODE, int C, int WAVES, bool AVG, int DT, int RPL, bool PIPE>
+template <int MODE, int C, int WAVES, bool AVG, int DT, int RPL, bool PIPE, bool NT = false>
 int launch_cols_variant(const RowsArgs &a, int blocks_per_cu, hipStream_t stream)
 {
     constexpr int CHUNK = MODE == kFused ? MADDNESS_COLS_CHUNK_FUSED : MADDNESS_COLS_CHUNK_ENCODE;
     const size_t lds = MODE == kFused ? (size_t)C * 16 * 256 : 0;
     const DeviceInfo &dev = device_info();
     if (lds > (size_t)dev.lds_per_block) return 1;
-    if (int rc = allow_full_lds<cols_kernel<MODE, C, WAVES, AVG, DT, CHUNK, RPL, PIPE>>(); rc != MADDNESS_OK) return rc;
+    if (int rc = allow_full_lds<cols_kernel<MODE, C, WAVES, AVG, DT, CHUNK, RPL, PIPE, NT>>(); rc != MADDNESS_OK) return rc;
     const int64_t n_groups = (a.N + 64 * RPL - 1) / (64 * RPL);
     const int64_t blocks_needed = (n_groups + WAVES - 1) / WAVES;
     const int64_t max_grid = (int64_t)dev.cus * blocks_per_cu;
     const int grid = (int)(blocks_needed < max_grid ? blocks_needed : max_grid);
     note_kernel("cols_kernel", __PRETTY_FUNCTION__);
-    hipLaunchKernelGGL((cols_kernel<MODE, C, WAVES, AVG, DT, CHUNK, RPL, PIPE>), dim3(grid), dim3(WAVES * 64), lds, stream,
+    hipLaunchKernelGGL((cols_kernel<MODE, C, WAVES, AVG, DT, CHUNK, RPL, PIPE, NT>), dim3(grid), dim3(WAVES * 64), lds, stream,
                        a);
     return check_hip(hipGetLastError(), "launch cols_kernel");
 }
@@ -200,6 +200,13 @@ int launch_cols(const RowsArgs &a, int blocks_per_cu, hipStream_t stream)
         // all 64 lanes store fp32 and nothing else: the pipelined variant applies
         if (a.M == 256 && a.out && !a.acc)
             return launch_cols_variant<MODE, C, WAVES, AVG, DT, RPL, true>(a, blocks_per_cu, stream);
+    }
+    // Split columns of more than the last-level cache holds are read past it: nothing of them would be there for another
+    // call.  (N = 2^20, C = 32: fp32 113 -> 105 us, binary16, 268 MB, 60 -> 55.5; where they may be, binary16 with N = 200000 and C = 64,
+    // 102 MB, 47 us as it is, 50 past it.  Bytes are bound by the walk: no difference.)
+    if constexpr (MODE == kEncode && DT != kU8) {
+        if (a.N * 4 * C * elem_size(DT) >= (int64_t)256 << 20)
+            return launch_cols_variant<MODE, C, WAVES, AVG, DT, RPL, false, true>(a, blocks_per_cu, stream);
     }
     return launch_cols_variant<MODE, C, WAVES, AVG, DT, RPL, false>(a, blocks_per_cu, stream);
 }

@@ -1,5 +1,6 @@
 """Outputs whose rows begin inside 128-byte lines and take several wavefronts' columns: every result where it belongs,
-equal to the oracle's to the bit, and nothing written beside the rows."""
+equal to the oracle's to the bit, and nothing written beside the rows.  Split columns larger than the last-level cache, which are
+read past it: the codes of the general kernel."""
 import numpy as np
 import pytest
 
@@ -52,3 +53,28 @@ def test_scan_writes_whole_lines(mad, shape):
     got = raw.cpu().numpy()
     assert (got[:at] == -7).all() and (got[at + (N - 1) * ldo + M:] == -7).all()
     assert (got[at:at + N * ldo].reshape(N, ldo)[:, M:][:-1] == -7).all()
+
+
+@pytest.mark.parametrize("dtype, N, C", [("float32", (1 << 20) + 3, 16), ("float16", (1 << 19) + 6, 64), ("bfloat16", (1 << 20) + 5, 32)])
+def test_encode_columns_larger_than_the_caches(mad, dtype, N, C):
+    import torch
+    print("case columns", dtype, N, C, flush=True)
+    D = 4 * C
+    g = torch.Generator(device="cuda").manual_seed(C)
+    pitch = (N + 3) // 4 * 4
+    A = torch.randn((D, pitch), generator=g, device="cuda").clamp_(min=0).to(getattr(torch, dtype))[:, :N]
+    rng = np.random.default_rng(C)
+    sd = np.stack([rng.permutation(4) + 4 * c for c in range(C)]).astype(np.int32)       # every column, once
+    th = np.abs(rng.standard_normal((C, 16))).astype(np.float32)
+    params = mad.Params(dev(sd), dev(th))
+    got = mad.maddness_encode_typed(params, A, col_major=True)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("cols_kernel") and "NT = true" in kernel, kernel
+    # a walk of the same trees on the same values
+    node = torch.zeros((N, C), dtype=torch.int64, device="cuda")
+    at, thd, sdd = torch.arange(C, device="cuda"), dev(th), dev(sd).long()
+    for t in range(4):
+        node = 2 * node + (A[sdd[:, t]].t().float() >= thd[at, (1 << t) - 1 + node]).long()
+    want = (node[:, 0::2] | (node[:, 1::2] << 4)).to(torch.uint8)
+    assert torch.equal(got, want)
