@@ -75,7 +75,7 @@ struct LearnArgs {
     double *parts;        // [C][part_slots][5][dmax] of a part's values x, the pivot taken off (y): sum y, sum y^2, sum x^2,
                           // the least and the largest x
     double *energy;       // [C][8] the sum of the squares of a bucket's values, or a little more
-    int32_t *unsure;      // [C][2] whether the candidates, and the split, take exact sums to tell
+    int32_t *unsure;      // [C][2] whether the candidates take exact sums to tell; bit q: whether candidate q's split does
     double *group_sums;   // [C][4][group_slots][dmax] the sums of the rows of a bucket before every group
     double *totals;       // [C][4][8][dmax] and of all its rows
     double *group_gain;   // [C][4][group_slots][2] the largest gain of a split in the group (-1: no split), the second largest
@@ -95,7 +95,7 @@ __global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst, in
 {
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         dst[i] = b.v[i];
-        if (unsure) unsure[i] = 1;
+        if (unsure) unsure[i] = (1 << kCand) - 1;
     }
 }
 
@@ -513,7 +513,8 @@ __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(con
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int c = blockIdx.x, b = blockIdx.y, col0 = blockIdx.z * 4;
-    if (!a.unsure[2 * c + which]) return;
+    const int unsure = a.unsure[2 * c + which];
+    if (!unsure || (which && __popc(unsure) < 2)) return;         // (one candidate alone is compared with none)
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b];
@@ -1097,7 +1098,7 @@ __global__ __launch_bounds__(32 * NC + kChainHelpers) void split_chains_kernel(c
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows;
-    if (count <= (small_too ? kChainRows : 1) || !a.unsure[2 * c + 1]) return;
+    if (count <= (small_too ? kChainRows : 1) || !(a.unsure[2 * c + 1] >> q & 1)) return;
     constexpr int kTiles = kChainRows / kSplitRows;
     const int n_steps = (n_tiles + kTiles - 1) / kTiles;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + start;
@@ -1149,7 +1150,7 @@ __global__ __launch_bounds__(16 * NC) void split_chains_small_kernel(const Learn
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (q >= a.n_cand[c] || col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
-    if (count < 2 || count > kChainRows || !a.unsure[2 * c + 1]) return;
+    if (count < 2 || count > kChainRows || !(a.unsure[2 * c + 1] >> q & 1)) return;
     const int n_tiles = (count + kSplitRows - 1) / kSplitRows, n_rows = n_tiles * kSplitRows, tid = threadIdx.x;
     const uint64_t *keys = a.keys + ((size_t)c * kCand + q) * a.N + start;
     const float *X = a.X + (size_t)c * (a.N + 1) * a.pitch + col0;
@@ -1504,11 +1505,15 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
                 best_q = q;
             }
         }
-        // (none that splits anything, or no value but 0: all losses are equal, and the first candidate is taken)
+        // the candidates that may be the best: bits.  (None that splits anything, or no value but 0: all losses are equal, and the
+        // first candidate is taken.)
+        int open = 1 << best_q;
         if (any && of_all > 0.0)
-            for (int q = 0; q < n_cand; ++q) sure &= q == best_q || most - gain[q] > 2.0 * of_all;
+            for (int q = 0; q < n_cand; ++q) open |= most - gain[q] > 2.0 * of_all ? 0 : 1 << q;
+        if (!sure) open = (1 << n_cand) - 1;
+        sure &= open == 1 << best_q;
         for (int b = 0; b < n_buckets; ++b) sure &= found[best_q][b].second < 0.0 || found[best_q][b].best - found[best_q][b].second > 2.0 * error[b];
-        a.unsure[2 * c + 1] = sure ? 0 : 1;
+        a.unsure[2 * c + 1] = sure ? 0 : open;
         chosen = sure ? best_q : -1;
         if (sure) {
             const int jj = a.cand[c * kCand + best_q];
@@ -1552,7 +1557,7 @@ __global__ __launch_bounds__(64) void split_losses_kernel(const LearnArgs a, int
     __shared__ __align__(16) double sums[kChains][kSumPitch];
     __shared__ __align__(16) float xs[2][NC][kPitch];       // the tile's values, first to last and last to first
     const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x;
-    if (q >= a.n_cand[c] || !a.unsure[2 * c + 1]) return;
+    if (q >= a.n_cand[c] || !(a.unsure[2 * c + 1] >> q & 1)) return;
     const int64_t group = blockIdx.x / a.C;
     int b = -1, start = 0, count = 0;
     for (int k = 0; k < n_buckets; ++k) {
@@ -1693,9 +1698,11 @@ __global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int leve
     __shared__ float res_v[kCand][kSplitBuckets];
     const int c = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n_cand = a.n_cand[c], d = a.bounds[2 * c + 1] - a.bounds[2 * c];
-    if (!a.unsure[2 * c + 1]) return;
+    const int unsure = a.unsure[2 * c + 1];
+    if (!unsure) return;
     for (int pair = wave; pair < n_cand * n_buckets; pair += 8) {
         const int q = pair / n_buckets, b = pair - q * n_buckets;
+        if (!(unsure >> q & 1)) continue;
         const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
         const int n_groups = (count + kGroupRows - 1) / kGroupRows;
         const size_t o = ((size_t)c * kCand + q) * a.group_slots + first_group(start, b);
@@ -1744,12 +1751,13 @@ __global__ __launch_bounds__(512) void choose_kernel(const LearnArgs a, int leve
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    int best_q = 0;
+    int best_q = -1;
     double l_min = 0.0;
     for (int q = 0; q < n_cand; ++q) {
+        if (!(unsure >> q & 1)) continue;                  // (the estimates tell that it is not the best)
         double l = 0.0;
         for (int b = 0; b < n_buckets; ++b) l += res_loss[q][b];
-        if (q == 0 || l < l_min) {
+        if (best_q < 0 || l < l_min) {
             l_min = l;
             best_q = q;
         }
