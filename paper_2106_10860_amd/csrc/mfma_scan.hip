@@ -389,13 +389,13 @@ int launch_mfma(const MfmaScanArgs &a, hipStream_t stream)
         // (a row has up to (M + 31) / 32 first floats of a line, its last line's among them)
         const int blocks = (((a.o.M + 31) / 32 - 1) * 32 + 16 * NT - 1) / (16 * NT);
         const int share = blocks >= 3 ? 1 : blocks == 2 ? 2 : 4, quarters = (blocks * share + 3) / 4;
-        // one to four turns of the chip (two workgroups per compute unit), whichever leaves the least undone: the last lines take
+        // one to four turns of the chip (two workgroups per compute unit; very wide rows: more), whichever leaves the least undone: the last lines take
         // as long as 64 (32) columns
         const double group_us = (KG * NT * 34 + 1000) / 2400.0, table_us = 4.0;
         const int64_t groups = (a.N / classes + 15) / 16;
         int units = 0, shares = 1, last = 1;
         double least = 1e30;
-        for (int turns = 1; turns <= 4; ++turns) {
+        for (int turns = 1; turns <= 4 || units == 0; ++turns) {       // (units stays 0 until a class has more workgroups than blocks of columns)
             const int u = std::max(8, 2 * dev.cus * turns / classes / 8 * 8);
             const double of_last = NT == 4 ? 0.3 * share : 0.55 * share;
             for (int n = std::max(1, (int)(u / (quarters + of_last))), k = 0; k < 2; ++n, ++k) {

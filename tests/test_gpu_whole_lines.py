@@ -55,6 +55,29 @@ def test_scan_writes_whole_lines(mad, shape):
     assert (got[at:at + N * ldo].reshape(N, ldo)[:, M:][:-1] == -7).all()
 
 
+@pytest.mark.parametrize("M, C", [(20001, 8), (9002, 33)], ids=str)
+def test_scan_whole_lines_of_very_wide_rows(mad, M, C):
+    """Rows with more blocks of columns than a class of them has workgroups in a turn of the chip, against the general kernel."""
+    import torch
+    N = 16390
+    print("case wide", N, M, C, flush=True)
+    _, _, _, luts, scale, offset = problem(M, 8, 4 * C, M, C)
+    codes = torch.randint(0, 256, (N, (C + 1) // 2), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda", dtype=torch.int32).to(torch.uint8)
+    if C % 2:
+        codes[:, -1] &= 15
+    args = (C, codes, dev(luts), dev(scale), dev(offset))
+    got, _ = mad.maddness_scan(*args)
+    assert mad.maddness_last_kernel().startswith("mfma_scan_kernel, whole lines"), mad.maddness_last_kernel()
+    try:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+        want, _ = mad.maddness_scan(*args)
+        assert mad.maddness_last_kernel().startswith("scan_kernel"), mad.maddness_last_kernel()
+    finally:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("dtype, N, C", [("float32", (1 << 20) + 3, 16), ("float16", (1 << 19) + 6, 64), ("bfloat16", (1 << 20) + 5, 32)])
 def test_encode_columns_larger_than_the_caches(mad, dtype, N, C):
     import torch
