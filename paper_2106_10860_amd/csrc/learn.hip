@@ -35,6 +35,7 @@
 // cholesky_panel_kernel, transpose_factor_kernel (the factor by rows), substitution_kernel; or means_kernel.
 #include "common.h"
 #include "device_common.h"
+#include "learn_bounds.h"
 
 namespace maddness {
 namespace {
@@ -552,33 +553,7 @@ __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(con
     if (wave < cols && lane == 0) out[wave] = loss;
 }
 
-// Estimates, and when they are enough.  What comes out of a level is a column and its thresholds, whole choices: the largest of
-// some losses, the least of others.  Sums in any order, of which there is no chain, name the same one as the sums in Algorithms
-// 3 and 4's order wherever the next best is further away than both can be off; where it is not (ties, infinities), the
-// codebook is marked unsure and goes the way of the exact sums.  With u = 2^-53, n rows and S the sum of the squares of a
-// bucket's values, over all columns where several are summed, a chain of n additions is off by n u of the sum of
-// its terms' sizes at most, one of h by h u, and sums over rows are at most sqrt(n S) (Cauchy-Schwarz).
-//
-// L(j, B).  As the exact kernel computes it: the mean is off by (n + 2) u sum|x| / n, which adds n times its square to the
-// loss, and the sum of squares by (n + 3) u of itself.  As sum y^2 - (sum y)^2 / n with y = x - p for a p among the values:
-// (3 n + 12) u sum y^2.  Together less than (4 n + 16) u Sy + (n + 2)^2 2^-104 (Sy + n p^2), the sum over the
-// buckets 16 u Sy more; loss_error is twice that.  (0 for a column of zeros, whose loss is 0 either way.)
-__device__ __forceinline__ double loss_error(double n, double sy, double p)
-{
-    return (8.0 * n + 64.0) * 0x1p-53 * sy + (n + 2.0) * (n + 2.0) * 0x1p-103 * (sy + n * p * p);
-}
-
-// The split's loss.  In Algorithm 4's order a column's two halves are off by (3 n + 4) u of their squares' sum, their sum over d
-// columns by d + 2 of it more.  Here it is a constant less the gain  sum_j w_j^2 n / (n1 n2),  w_j = s_j - n1 T_j / n, from
-// sums s_j, T_j that are off by h u sum|x| with h <= 256 + N / 2^18 (32 rows, 8 tiles, the scan of the groups): |w_j| n / (n1 n2) is
-// at most 2 sqrt(S_j), so the gain is off by 8 h sqrt(n) u S, and some 100 u S for its products and sums.  Sums that are
-// exact in any order (any_order) leave d + 8 and 16 sqrt(n).  energy: S.
-__device__ __forceinline__ double split_error(const LearnArgs &a, double n, double energy, int d, bool exact_sums)
-{
-    const double root = sqrt(n);
-    const double units = exact_sums ? 64.0 * root : 8.0 * n + 8.0 * (256.0 + (double)a.N * 0x1p-18) * root;
-    return (units + 16.0 * d + 1024.0) * 0x1p-53 * energy;
-}
+// Estimates, and when they are enough: learn_bounds.h.
 
 // A workgroup per kPartRows rows of a bucket, in row order: what the estimates of L(j, B) take, column by column.  (With
 // select_kernel, the four levels of 260100 x 27: 0.11 ms against 1.60 for bucket_loss_kernel; 20000 x 512: 0.10 and 0.31.)
@@ -1348,7 +1323,7 @@ __device__ __forceinline__ double across(double x)
     return __builtin_bit_cast(double, (int64_t)high << 32 | (uint32_t)low);
 }
 
-// The gain of every split (split_error tells what that is): the lanes of a tile walk its rows together, four columns each, and
+// The gain of every split (split_error in learn_bounds.h tells what that is): the lanes of a tile walk its rows together, four columns each, and
 // add up what their columns give; lane p of them keeps rows p, p + kPieces, ...
 struct Gain {
     double best, second;
@@ -1490,7 +1465,9 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
             const int n = (int)a.bucket_count[c * kSplitBuckets + b];
             const double energy = a.energy[c * kSplitBuckets + b];
             sure &= energy < __builtin_inf();
-            error[b] = n > 1 ? split_error(a, (double)n, energy, d, exact_sums) : 0.0;
+            bool every_splits = true;
+            for (int q = 0; q < n_cand; ++q) every_splits &= found[q][b].at >= 0;
+            error[b] = n > 1 ? split_error((double)n, sqrt((double)n), (double)a.N, energy, d, exact_sums, every_splits) : 0.0;
             of_all += error[b];
         }
         double gain[kCand];
