@@ -282,7 +282,7 @@ int maddness_encode_scan_typed(const maddness_params *params, const void *A, int
  *                ridge step, the variant Section 5.1 calls MADDNESS-PQ.
  * prototypes       out [C][16][D] fp32, as maddness_params takes them.
  * workspace        at least maddness_learn_prototypes_workspace(D, C) bytes, 256-byte aligned
- *                  (about 20 Q^2 + 8 Q D + 264000 C bytes, Q = 16 C).
+ *                  (about 20 Q^2 + 8 Q D + 264000 C + 32 D bytes, Q = 16 C, and up to 2 MiB).
  *
  * Both calls are enqueued on `stream` and return without synchronising; errors as everywhere.
  */

@@ -1784,8 +1784,10 @@ struct ProtoArgs {
     int32_t *bounds;
     int32_t *counts;        // [Q][Q] G^T G
     int32_t *range_part;    // [D / 64 and more][kProtoParts][2] what a part of 64 columns' values span
+    int32_t *any_order;     // [D / 64 and more] whether their sums may be taken in any order
     int32_t row_bits;       // N <= 2^row_bits
     int32_t shares;         // wavefronts that share a code's rows where any order will do
+    double *R_shares;       // [shares - 1][Q][D] what the others than the first add to R
     double *M;              // [Q][Q]: G^T G + lambda I, then M[k][i] = L[i][k]
     double *Lr;             // [Q][Q]: L by rows
     double *R;              // [Q][D]: G^T A~
@@ -1798,14 +1800,13 @@ struct ProtoArgs {
 
 // G^T A~ where its sums' bits allow any order (as any_order for the trees, 64 columns at a time): workgroups of parts of the
 // rows note what those span, and leave it at that as soon as it is too much, for most data after the first rows.  The
-// other workgroups clear the counters and the sums that are added to.
+// other workgroups clear the counters.
 constexpr int kProtoParts = 256, kProtoClear = 256;
 __global__ __launch_bounds__(256) void prepare_kernel(const ProtoArgs a)
 {
-    const int64_t QQ = (int64_t)a.Q * a.Q, QD = (int64_t)a.Q * a.D;
     if (blockIdx.x < kProtoClear) {
+        const int64_t QQ = (int64_t)a.Q * a.Q;
         for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < QQ; i += 256 * kProtoClear) a.counts[i] = 0;
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < QD; i += 256 * kProtoClear) a.R[i] = 0.0;
         return;
     }
     const int block = (blockIdx.x - kProtoClear) / kProtoParts, part = (blockIdx.x - kProtoClear) % kProtoParts;
@@ -1813,12 +1814,13 @@ __global__ __launch_bounds__(256) void prepare_kernel(const ProtoArgs a)
     __shared__ int32_t widest[4][2];
     const int64_t first = a.N * part / kProtoParts, end = a.N * (part + 1) / kProtoParts;
     int top = 0, least = 0;
-    for (int64_t n0 = first; n0 < end; n0 += 64) {
-        float x[16];
+    constexpr int kAhead = 32;
+    for (int64_t n0 = first; n0 < end; n0 += 4 * kAhead) {
+        float x[kAhead];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) x[u] = a.A[min(n0 + 4 * u + wave, end - 1) * a.lda + col];
+        for (int u = 0; u < kAhead; ++u) x[u] = a.A[min(n0 + 4 * u + wave, end - 1) * a.lda + col];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) span_of(x[u], top, least);
+        for (int u = 0; u < kAhead; ++u) span_of(x[u], top, least);
         if (__ballot(top != 0 && top + least - kLeast + a.row_bits > 53)) {
             top = kNoNumber;
             break;
@@ -1886,8 +1888,9 @@ __global__ __launch_bounds__(256) void ridge_matrix_kernel(const ProtoArgs a, do
 // 0.20 + 0.02 ms for 20000 x 512 and 32 codebooks, 0.77 + 0.08 ms for 260100 x 27 and 4 (1.0 and 7.5 ms with every thread
 // reading all rows; four columns to a lane, for a third of the instructions, gave 0.27 ms: fewer wavefronts, and rows
 // four times as long to keep in L2).  Where the sums are exact in any order and these wavefronts leave the chip empty, several share
-// a code's rows and add to the result: 260100 x 27 with 4 0.04 ms instead of 0.75,
-// 0.02 for finding out (5 us for data that are not, in a launch that clears the sums as well).
+// a code's rows: 260100 x 27 with 4 0.04 ms instead of 0.75,
+// 0.02 for finding out, in a launch that clears the counters as well (data that are not: 5 to 15 us, 131072 x 64, 8 codebooks 447
+// without and 459 with it; whole values 1300 and 322).
 constexpr int kListRows = 65536;       // rows of a stretch, at most (their distances in bytes from its first fit 32 bits)
 constexpr int kGtaAhead = 32;
 constexpr int kListSpare = 4 * kGtaAhead;     // entries read past the last (and not used)
@@ -1901,6 +1904,22 @@ __global__ __launch_bounds__(256) void count_codes_kernel(const ProtoArgs a, int
     const int rows = (int)(left < kListChunk ? left : kListChunk);
     const uint8_t *code = a.codes + first * a.C + c;
     if (tid < 16) total[tid] = 0;
+    if (a.shares > 1 && first_row == 0)
+        for (int block = 4 * (c + a.C * chunk) + (tid >> 6); block < (a.D + 63) / 64; block += 4 * a.C * (int)gridDim.y) {
+            const int32_t *range = a.range_part + (size_t)block * kProtoParts * 2;
+            int top = 0, least = 0;
+#pragma unroll
+            for (int i = 0; i < kProtoParts; i += 64) {
+                top = max(top, range[2 * (i + lane)]);
+                least = max(least, range[2 * (i + lane) + 1]);
+            }
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                top = max(top, __shfl_xor(top, off));
+                least = max(least, __shfl_xor(least, off));
+            }
+            if (lane == 0) a.any_order[block] = top == 0 || top + least - kLeast + a.row_bits <= 53;
+        }
     __syncthreads();
     int mine = 0;
 #pragma unroll
@@ -1979,30 +1998,17 @@ __global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t fir
     const int k = blockIdx.y * 4 + wave, c = blockIdx.z % a.C, share = blockIdx.z / a.C;
     const int col = blockIdx.x * 64 + lane;
     int start = a.list_start[c * 17 + k], count = a.list_start[c * 17 + k + 1] - start;
-    double *out = a.R + ((size_t)16 * c + k) * a.D + col;
-    bool shared = false;
-    if (a.shares > 1) {
-        const int32_t *range = a.range_part + (size_t)blockIdx.x * kProtoParts * 2;
-        int top = 0, least = 0;
-#pragma unroll
-        for (int i = 0; i < kProtoParts; i += 64) {
-            top = max(top, range[2 * (i + lane)]);
-            least = max(least, range[2 * (i + lane) + 1]);
-        }
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            top = max(top, __shfl_xor(top, off));
-            least = max(least, __shfl_xor(least, off));
-        }
-        shared = __builtin_amdgcn_readfirstlane(top == 0 || top + least - kLeast + a.row_bits <= 53);
-        if (share > 0 && !shared) return;
-    }
+    const bool shared = a.shares > 1 && a.any_order[blockIdx.x];
+    if (share > 0 && !shared) return;
     if (shared) {
         const int per = (count + a.shares - 1) / a.shares;
         start += share * per;
         count = max(0, min(per, count - share * per));
     }
-    double sum = !shared && first_row > 0 && col < a.D ? *out : 0.0;
+    // (every share has sums of its own, which transpose_factor_kernel adds up: additions to one by several wavefronts would ask
+    // for memory that takes atomics of doubles)
+    double *out = (share == 0 ? a.R : a.R_shares + (size_t)(share - 1) * a.Q * a.D) + ((size_t)16 * c + k) * a.D + col;
+    double sum = first_row > 0 && col < a.D ? *out : 0.0;
     if (count > 0) {
         // (the same for a whole wavefront, and written by a kernel before this one: scalar loads)
         const auto *list = (const __attribute__((address_space(4))) uint32_t *)(a.list + (size_t)c * (kListRows + kListSpare) + start);
@@ -2044,9 +2050,7 @@ __global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t fir
             add(x1, at + kGtaAhead);
         }
     }
-    if (col >= a.D) return;
-    if (!shared) *out = sum;
-    else if (count > 0) unsafeAtomicAdd(out, sum);      // (exact, in whatever order)
+    if (col < a.D) *out = sum;
 }
 
 // Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
@@ -2125,10 +2129,22 @@ __global__ __launch_bounds__(256) void cholesky_panel_kernel(const ProtoArgs a, 
         }
 }
 
+// The factor by rows; the workgroups after those add the shares of G^T A~ to the first (exact, in whatever order).
 __global__ __launch_bounds__(256) void transpose_factor_kernel(const ProtoArgs a)
 {
+    const int64_t QQ = (int64_t)a.Q * a.Q;
+    const unsigned factor = (unsigned)((QQ + 255) / 256);
+    if (blockIdx.x >= factor) {
+        const int64_t i = (int64_t)(blockIdx.x - factor) * 256 + threadIdx.x, QD = (int64_t)a.Q * a.D;
+        if (i >= QD || !a.any_order[(i % a.D) / 64]) return;
+        double sum = a.R[i];
+#pragma unroll 16
+        for (int share = 1; share < a.shares; ++share) sum += a.R_shares[(share - 1) * QD + i];
+        a.R[i] = sum;
+        return;
+    }
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)a.Q * a.Q) return;
+    if (i >= QQ) return;
     const int k = (int)(i / a.Q), r = (int)(i - (int64_t)k * a.Q);
     if (k <= r) a.M[i] = a.Lr[(size_t)r * a.Q + k];
 }
@@ -2395,12 +2411,17 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.chosen = w.take<int32_t>(C);
 }
 
+// four wavefronts to a SIMD of 256 compute units in all; at most 2 MiB of their sums
+int64_t most_shares(int32_t D, int32_t C) { return std::max<int64_t>(1, 4096 / (((int64_t)D + 63) / 64 * 16 * C)); }
+
 void carve_prototypes(Carver &w, ProtoArgs &a)
 {
     const size_t Q = a.Q;
     a.bounds = w.take<int32_t>(2 * (size_t)a.C);
     a.counts = w.take<int32_t>(Q * Q);
     a.range_part = w.take<int32_t>((size_t)(a.D + 63) / 64 * kProtoParts * 2);
+    a.any_order = w.take<int32_t>((size_t)(a.D + 63) / 64);
+    a.R_shares = w.take<double>((size_t)(most_shares(a.D, a.C) - 1) * Q * a.D);
     a.M = w.take<double>(Q * Q);
     a.Lr = w.take<double>(Q * Q);
     a.R = w.take<double>(Q * a.D);
@@ -2600,9 +2621,8 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
     note_kernel("prepare_kernel + cooccurrence_kernel + count_codes_kernel + list_codes_kernel + gta_kernel + cholesky_panel_kernel + substitution_kernel", nullptr);
     const int64_t QQ = (int64_t)a.Q * a.Q;
     a.row_bits = N > 1 ? 64 - __builtin_clzll((unsigned long long)(N - 1)) : 0;
-    // (four wavefronts to a SIMD in all, each with 64 rows or more)
-    const int64_t waves = (int64_t)(D + 63) / 64 * 16 * C;
-    a.shares = (int)std::max<int64_t>(1, std::min<int64_t>(16 * device_info().cus / waves, std::min<int64_t>(N, kListRows) / 16 / 64));
+    // (each with 64 rows or more)
+    a.shares = (int)std::max<int64_t>(1, std::min<int64_t>(most_shares(D, C), std::min<int64_t>(N, kListRows) / 16 / 64));
     hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(kProtoClear + (a.shares > 1 ? (D + 63) / 64 * kProtoParts : 0))), dim3(256), 0, stream, a);
     LAUNCH_OK("launch prepare_kernel");
     // (stretches of at least 2048 rows, and about four workgroups per compute unit)
@@ -2628,7 +2648,8 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
         hipLaunchKernelGGL(cholesky_panel_kernel, dim3(tiles, tiles), dim3(256), 0, stream, a, J0);
         LAUNCH_OK("launch cholesky_panel_kernel");
     }
-    hipLaunchKernelGGL(transpose_factor_kernel, dim3((unsigned)((QQ + 255) / 256)), dim3(256), 0, stream, a);
+    const int64_t share_blocks = a.shares > 1 ? ((int64_t)a.Q * D + 255) / 256 : 0;
+    hipLaunchKernelGGL(transpose_factor_kernel, dim3((unsigned)((QQ + 255) / 256 + share_blocks)), dim3(256), 0, stream, a);
     LAUNCH_OK("launch transpose_factor_kernel");
     const size_t lds_limit = (size_t)device_info().lds_per_block;
     if (substitution_lds_bytes(a.Q, 1) > lds_limit)

@@ -237,3 +237,20 @@ def test_learner_estimates_and_exact_sums(mad, N, widths, scale, kinds):
     want = oracle.ridge_prototypes(want_codes, A, 1.0)
     # the same fp64 operations: both round to the same fp32
     assert (P.cpu().numpy() == want.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("C, widths", [(1, (70,)), (3, (9, 64, 3))], ids=str)
+def test_prototypes_of_shared_rows(mad, C, widths):
+    """G^T A~ by several wavefronts to a code, over more rows than are listed at a time: codes that only some of the lists hold
+    or none, 64 columns of whole values beside columns whose sums depend on their order."""
+    N, D = 70001, 130
+    rng = np.random.default_rng(C)
+    print("case shared rows", C, flush=True)
+    A = rng.integers(-100, 100, (N, D)).astype(np.float32)
+    A[:, 64:128] = rng.standard_normal((N, 64))
+    codes = rng.integers(0, 16, (N, C)).astype(np.uint8)
+    codes[:, 0] = np.sort(codes[:, 0])
+    codes[codes == 5] = 6
+    P = mad.maddness_learn_prototypes(dev(codes), dev(A), [(0, w) for w in widths])
+    want = oracle.ridge_prototypes(codes, A, 1.0)
+    assert (P.cpu().numpy() == want.astype(np.float32)).all()
