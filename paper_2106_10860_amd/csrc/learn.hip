@@ -73,8 +73,7 @@ struct LearnArgs {
     int64_t group_slots;  // groups of kGroupTiles tiles of all buckets of a level, at most
     // what the estimates leave (the tiles' sums lie in `sums`, [C][4][2 tile_slots][2 dmax] or less of it, as [slot][dmax])
     int64_t part_slots;   // parts of kPartRows rows of all buckets of a level, at most
-    double *parts;        // [C][part_slots][5][dmax] of a part's values x, the pivot taken off (y): sum y, sum y^2, sum x^2,
-                          // the least and the largest x
+    double *parts;        // [C][part_slots][3][dmax] of a part's values x, the pivot taken off (y): sum y, sum y^2, sum x^2
     double *energy;       // [C][8] the sum of the squares of a bucket's values, or a little more
     int32_t *unsure;      // [C][2] whether the candidates take exact sums to tell; bit q: whether candidate q's split does
     double *group_sums;   // [C][4][group_slots][dmax] the sums of the rows of a bucket before every group
@@ -557,7 +556,7 @@ __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(con
 
 // A workgroup per kPartRows rows of a bucket, in row order: what the estimates of L(j, B) take, column by column.  (With
 // select_kernel, the four levels of 260100 x 27: 0.11 ms against 1.60 for bucket_loss_kernel; 20000 x 512: 0.10 and 0.31.)
-constexpr int kPartRows = 1024, kPartValues = 5;
+constexpr int kPartRows = 1024, kPartValues = 3;
 __device__ __forceinline__ int64_t first_part(int32_t start, int bucket) { return start / kPartRows + bucket; }
 
 template <int NC>
@@ -590,9 +589,6 @@ __global__ __launch_bounds__(256) void loss_parts_kernel(const LearnArgs a, int 
         const float4 p4 = *reinterpret_cast<const float4 *>(X + col0 + (uint64_t)pivot * (uint32_t)a.pitch);
         const float p[4] = {p4.x, p4.y, p4.z, p4.w};
         double y1[4] = {}, y2[4] = {}, x2[4] = {};
-        float least[4], most[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) least[e] = most[e] = p[e];
 #pragma unroll
         for (int i0 = 0; i0 < kPer; i0 += kAhead) {
             float4 v[kAhead];
@@ -608,8 +604,6 @@ __global__ __launch_bounds__(256) void loss_parts_kernel(const LearnArgs a, int 
                     y1[e] += y;
                     y2[e] = __builtin_fma(y, y, y2[e]);
                     x2[e] = __builtin_fma(x, x, x2[e]);
-                    least[e] = fminf(least[e], here ? x4[e] : p[e]);
-                    most[e] = fmaxf(most[e], here ? x4[e] : p[e]);
                 }
             }
         }
@@ -620,16 +614,12 @@ __global__ __launch_bounds__(256) void loss_parts_kernel(const LearnArgs a, int 
                 y1[e] += __shfl_xor(y1[e], off);
                 y2[e] += __shfl_xor(y2[e], off);
                 x2[e] += __shfl_xor(x2[e], off);
-                least[e] = fminf(least[e], __shfl_xor(least[e], off));
-                most[e] = fmaxf(most[e], __shfl_xor(most[e], off));
             }
             if (lane < kPieces) {
                 double *to = from_wave[wave][lane][e];
                 to[0] = y1[e];
                 to[1] = y2[e];
                 to[2] = x2[e];
-                to[3] = (double)least[e];
-                to[4] = (double)most[e];
             }
         }
         __syncthreads();
@@ -638,9 +628,7 @@ __global__ __launch_bounds__(256) void loss_parts_kernel(const LearnArgs a, int 
             double v[4];
 #pragma unroll
             for (int w = 0; w < 4; ++w) v[w] = from_wave[w][col / 4][col % 4][value];
-            const double r = value < 3 ? (v[0] + v[1]) + (v[2] + v[3])
-                                       : value == 3 ? fmin(fmin(v[0], v[1]), fmin(v[2], v[3])) : fmax(fmax(v[0], v[1]), fmax(v[2], v[3]));
-            if (col0 + col < d) out[value * a.dmax + col0 + col] = r;
+            if (col0 + col < d) out[value * a.dmax + col0 + col] = (v[0] + v[1]) + (v[2] + v[3]);
         }
         __syncthreads();
     }
@@ -698,12 +686,12 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_bu
     if (tid < kSplitBuckets) energy[tid] = 0.0;
     for (int col0 = 0; col0 < d; col0 += 16) {
         const double *in = a.parts + ((size_t)c * a.part_slots + first_part(start, b)) * kPartValues * a.dmax + min(col0 + col, d - 1);
-        double sum[3] = {0.0, 0.0, 0.0};
+        double sum[kPartValues] = {};
         for (int i = 4 * share + lane / 16; i < n_parts; i += 4 * shares)
 #pragma unroll
-            for (int v = 0; v < 3; ++v) sum[v] += in[((size_t)i * kPartValues + v) * a.dmax];
+            for (int v = 0; v < kPartValues; ++v) sum[v] += in[((size_t)i * kPartValues + v) * a.dmax];
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {
+        for (int v = 0; v < kPartValues; ++v) {
             sum[v] += __shfl_xor(sum[v], 16);
             sum[v] += __shfl_xor(sum[v], 32);
             if (lane < 16) from_wave[wave][lane][v] = sum[v];
@@ -725,10 +713,8 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_bu
                 if (n > 1) {                                  // (a row alone: no loss)
                     loss[col0 + tid] += fmax(y2 - y1 * y1 / (double)n, 0.0);
                     error[col0 + tid] += loss_error((double)n, y2, p);
-                    from_wave[k][tid][2] = x2;
-                } else {
-                    from_wave[k][tid][2] = x2;
                 }
+                from_wave[k][tid][2] = x2;
             }
         __syncthreads();
         if (tid < n_buckets && a.bucket_count[c * kSplitBuckets + tid] > 0)
