@@ -272,7 +272,11 @@ int maddness_encode_scan_typed(const maddness_params *params, const void *A, int
  *                  bytes (w rounded up to 8 or a multiple of 16, N' = N rounded up to a
  *                  power of two); trees are learned as many at a time as stay within the
  *                  larger of 4 GiB and 2 C (37 N + 32 N'), one at least, and the result does
- *                  not depend on how many.
+ *                  not depend on how many.  Most choices are made by estimates of those sums with
+ *                  bounds of their error, which name the same column and splits, and the sums are
+ *                  only taken where the estimates cannot tell: after the call the workspace begins
+ *                  with two int32 per codebook (of the last ones taken at a time), on how many of
+ *                  the four levels sums chose the candidates, and the splits.
  *
  * maddness_learn_prototypes computes the prototype matrix P from the training codes:
  *   ridge != 0   P = (G^T G + lambda I)^-1 G^T A_train (Section 4.3), G the one-hot matrix of

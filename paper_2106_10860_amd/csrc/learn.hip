@@ -75,7 +75,8 @@ struct LearnArgs {
     int64_t part_slots;   // parts of kPartRows rows of all buckets of a level, at most
     double *parts;        // [C][part_slots][3][dmax] of a part's values x, the pivot taken off (y): sum y, sum y^2, sum x^2
     double *energy;       // [C][8] the sum of the squares of a bucket's values, or a little more
-    int32_t *unsure;      // [C][2] whether the candidates take exact sums to tell; bit q: whether candidate q's split does
+    int32_t *exact_levels;   // [C][2] on how many levels exact sums chose the candidates, and the split among theirs
+    int32_t *unsure;      // [C][2] whether the candidates take exact sums to tell; bit q: whether candidate q's split does, and flags
     double *group_sums;   // [C][4][group_slots][dmax] the sums of the rows of a bucket before every group
     double *totals;       // [C][4][8][dmax] and of all its rows
     double *group_gain;   // [C][4][group_slots][2] the largest gain of a split in the group (-1: no split), the second largest
@@ -90,12 +91,21 @@ struct LearnArgs {
     int32_t codes_pitch;
 };
 
-// (unsure: the flags of LearnArgs, set where no estimates will be made, or null)
-__global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst, int32_t *unsure)
+// What a.unsure[2 c + 1] holds beside a bit per candidate: the comparison of those takes the bucket's exact losses, which have
+// not been summed for the choice of columns; the level's splits have no estimates.
+constexpr int kAllCand = (1 << kCand) - 1, kWantsLosses = 1 << kCand, kNoEstimates = 2 << kCand;
+
+__global__ void upload_bounds_kernel(const Bounds b, int32_t n, int32_t *dst)
 {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        dst[i] = b.v[i];
-        if (unsure) unsure[i] = (1 << kCand) - 1;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = b.v[i];
+}
+
+__global__ void begin_trees_kernel(const Bounds b, const LearnArgs a, bool estimated)
+{
+    for (int i = threadIdx.x; i < 2 * a.C; i += blockDim.x) {
+        a.bounds[i] = b.v[i];
+        a.exact_levels[i] = estimated ? 0 : 4;
+        if (!estimated) a.unsure[i] = kAllCand;
     }
 }
 
@@ -508,13 +518,13 @@ __device__ __forceinline__ void add_chained(double &s, const double (&t)[4])
 // column, four columns of a bucket to a workgroup.  (Measured, the four levels of 260100 x 27 with 4 codebooks, whole
 // values: 1.65 ms; 3.3 ms with four chains to a wavefront and 14.6 ms with a lane per chain that read and converted its
 // values itself.  20000 x 512 with 32, of both signs, whose first sum takes the chain: 0.31, 0.39 and 1.75 ms.)
-// For the candidates (which: 0) or the losses of buckets that cannot be split (1), where the estimates are not enough.
+// For the candidates (which: 0), where the estimates are not enough, or where those were and the splits' are not (1): for the
+// losses of buckets that some candidate cannot split.
 __global__ __launch_bounds__(4 * 64 + kChainHelpers) void bucket_loss_kernel(const LearnArgs a, int which)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int c = blockIdx.x, b = blockIdx.y, col0 = blockIdx.z * 4;
-    const int unsure = a.unsure[2 * c + which];
-    if (!unsure || (which && __popc(unsure) < 2)) return;         // (one candidate alone is compared with none)
+    if (which ? !(a.unsure[2 * c + 1] & kWantsLosses) : !a.unsure[2 * c]) return;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (col0 >= d) return;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b];
@@ -677,13 +687,13 @@ __device__ __forceinline__ int largest_left(const double (&total)[kMaxWidth / 64
 // and whether the estimates can tell.  A workgroup per codebook, its 8 wavefronts shared out among the buckets.
 __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_buckets)
 {
-    __shared__ double from_wave[8][16][kPartValues], loss[kMaxWidth], error[kMaxWidth], energy[kSplitBuckets];
+    __shared__ double from_wave[8][16][kPartValues], loss[kMaxWidth], error[kMaxWidth], energy[kSplitBuckets], spread[kSplitBuckets];
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], b = wave % n_buckets, share = wave / n_buckets, shares = 8 / n_buckets;
     const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
     const int n_parts = (count + kPartRows - 1) / kPartRows, col = lane & 15;
     if (tid < kMaxWidth) loss[tid] = error[tid] = 0.0;
-    if (tid < kSplitBuckets) energy[tid] = 0.0;
+    if (tid < kSplitBuckets) energy[tid] = spread[tid] = 0.0;
     for (int col0 = 0; col0 < d; col0 += 16) {
         const double *in = a.parts + ((size_t)c * a.part_slots + first_part(start, b)) * kPartValues * a.dmax + min(col0 + col, d - 1);
         double sum[kPartValues] = {};
@@ -710,19 +720,29 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_bu
                 }
                 const int32_t pivot = a.rows_by_bucket[(size_t)c * a.N + a.bucket_start[c * kSplitBuckets + k] + n / 2];
                 const double p = (double)a.X[((size_t)c * (a.N + 1) + pivot) * a.pitch + col0 + tid];
-                if (n > 1) {                                  // (a row alone: no loss)
-                    loss[col0 + tid] += fmax(y2 - y1 * y1 / (double)n, 0.0);
-                    error[col0 + tid] += loss_error((double)n, y2, p);
-                }
+                const double here = n > 1 ? fmax(y2 - y1 * y1 / (double)n, 0.0) : 0.0;      // (a row alone: no loss)
+                loss[col0 + tid] += here;
+                if (n > 1) error[col0 + tid] += loss_error((double)n, y2, p);
+                from_wave[k][tid][0] = here;
                 from_wave[k][tid][2] = x2;
             }
         __syncthreads();
         if (tid < n_buckets && a.bucket_count[c * kSplitBuckets + tid] > 0)
-            for (int k = 0; k < min(16, d - col0); ++k) energy[tid] += from_wave[tid][k][2];
+            for (int k = 0; k < min(16, d - col0); ++k) {
+                spread[tid] += from_wave[tid][k][0];
+                energy[tid] += from_wave[tid][k][2];
+            }
         __syncthreads();
     }
     if (tid < n_buckets) a.energy[c * kSplitBuckets + tid] = energy[tid] * 1.0001;
     if (wave != 0) return;
+    // A bucket whose whole loss is less than what two splits of it have to differ by (little spread far from 0): there will be
+    // no telling.  (20000 x 512 of 1000 and a thousandth either way, 32 codebooks: 2976 us with all estimates, 2659 with none.)
+    bool hopeless = false;
+    if (lane < n_buckets && spread[lane] > 0.0) {
+        const double n = (double)a.bucket_count[c * kSplitBuckets + lane];
+        hopeless = spread[lane] < 2.0 * split_error(n, sqrt(n), (double)a.N, energy[lane], d, any_order(a, c), true);
+    }
     double total[kMaxWidth / 64], off_by[kMaxWidth / 64];
     bool taken[kMaxWidth / 64];
     bool finite = true;
@@ -747,9 +767,13 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_bu
         if (__ballot(!less)) sure = false;
         if (lane == 0) a.cand[c * kCand + k] = best;
     }
+    const bool none = __ballot(hopeless || !finite);
     if (lane == 0) {
         a.n_cand[c] = n_cand;
         a.unsure[2 * c] = sure ? 0 : 1;
+        a.unsure[2 * c + 1] = none ? kAllCand | kNoEstimates | (sure ? kWantsLosses : 0) : 0;
+        a.exact_levels[2 * c] += sure ? 0 : 1;
+        a.exact_levels[2 * c + 1] += none ? 1 : 0;
     }
 }
 
@@ -1208,7 +1232,7 @@ __global__ __launch_bounds__(256) void tile_sums_kernel(const LearnArgs a, int n
     constexpr int kAhead = 16;
     __shared__ uint32_t listed[4][G::kTiles][kSplitRows + 1];
     const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (q >= a.n_cand[c]) return;
+    if (q >= a.n_cand[c] || a.unsure[2 * c + 1]) return;
     const int piece = lane % G::kPieces, tile = lane / G::kPieces % kGroupTiles;
     const G g = list_group_rows<NC>(a, c, q, n_buckets, listed[wave]);
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
@@ -1255,7 +1279,7 @@ __global__ __launch_bounds__(16 * kScanThreads) void scan_groups_kernel(const Le
     const int c = blockIdx.x % a.C, q = blockIdx.x / a.C, b = blockIdx.y, col0 = 16 * blockIdx.z;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     const int side = threadIdx.x & 15, t = threadIdx.x >> 4, col = min(col0 + side, d - 1);
-    if (q >= a.n_cand[c] || col0 >= d) return;
+    if (q >= a.n_cand[c] || col0 >= d || a.unsure[2 * c + 1]) return;
     const bool stored = col0 + side < d;
     const int count = (int)a.bucket_count[c * kSplitBuckets + b], start = a.bucket_start[c * kSplitBuckets + b];
     const int n_groups = (count + kGroupRows - 1) / kGroupRows;
@@ -1329,7 +1353,7 @@ __global__ __launch_bounds__(256) void split_gains_kernel(const LearnArgs a, int
     constexpr int kPieces = G::kPieces, kAhead = 8, kOwn = kSplitRows / kPieces;
     __shared__ uint32_t listed[4][G::kTiles][kSplitRows + 1];
     const int c = blockIdx.x % a.C, q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (q >= a.n_cand[c]) return;
+    if (q >= a.n_cand[c] || a.unsure[2 * c + 1]) return;
     const int piece = lane % kPieces;
     const G g = list_group_rows<NC>(a, c, q, n_buckets, listed[wave]);
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c];
@@ -1424,6 +1448,7 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
     __shared__ int32_t chosen;
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_cand = a.n_cand[c], d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (a.unsure[2 * c + 1]) return;
     for (int pair = wave; pair < n_cand * n_buckets; pair += 16) {
         const int q = pair / n_buckets, b = pair - q * n_buckets;
         const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
@@ -1442,47 +1467,55 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
         if (lane == 0) found[q][b] = best;
     }
     __syncthreads();
-    if (tid == 0) {
-        const bool exact_sums = any_order(a, c);
-        double error[kSplitBuckets], of_all = 0.0, most = 0.0;
-        bool any = false, sure = true;
-        int best_q = 0;
-        for (int b = 0; b < n_buckets; ++b) {
-            const int n = (int)a.bucket_count[c * kSplitBuckets + b];
-            const double energy = a.energy[c * kSplitBuckets + b];
-            sure &= energy < __builtin_inf();
-            bool every_splits = true;
-            for (int q = 0; q < n_cand; ++q) every_splits &= found[q][b].at >= 0;
-            error[b] = n > 1 ? split_error((double)n, sqrt((double)n), (double)a.N, energy, d, exact_sums, every_splits) : 0.0;
-            of_all += error[b];
-        }
-        double gain[kCand];
-        for (int q = 0; q < n_cand; ++q) {
-            gain[q] = 0.0;
-            for (int b = 0; b < n_buckets; ++b) {
-                any |= found[q][b].at >= 0;
-                gain[q] += fmax(found[q][b].best, 0.0);
-            }
-            if (q == 0 || gain[q] > most) {
-                most = gain[q];
-                best_q = q;
-            }
+    if (wave == 0) {
+        // a lane per (candidate, bucket)
+        const int q = lane / kSplitBuckets, b = lane % kSplitBuckets;
+        const bool here = q < n_cand && b < n_buckets;
+        const Gain mine = here ? found[q][b] : Gain{-1.0, -1.0, -1};
+        const int n = b < n_buckets ? (int)a.bucket_count[c * kSplitBuckets + b] : 0;
+        const double energy = b < n_buckets ? a.energy[c * kSplitBuckets + b] : 0.0;
+        // (of the lanes of a bucket: whether each of the candidates splits it)
+        const unsigned long long cannot = __ballot(here && mine.at < 0);
+        const bool every_splits = !(cannot & (0x01010101ull << b));
+        const double error = n > 1 ? split_error((double)n, sqrt((double)n), (double)a.N, energy, d, any_order(a, c), every_splits) : 0.0;
+        double of_all = error, gain = fmax(mine.best, 0.0);
+#pragma unroll
+        for (int off = 1; off < kSplitBuckets; off <<= 1) {
+            of_all += __shfl_xor(of_all, off);
+            gain += __shfl_xor(gain, off);
         }
         // the candidates that may be the best: bits.  (None that splits anything, or no value but 0: all losses are equal, and the
         // first candidate is taken.)
+        double most = 0.0;
+        int best_q = 0;
+#pragma unroll
+        for (int i = 0; i < kCand; ++i) {
+            const double g = __shfl(gain, i * kSplitBuckets);
+            if (i == 0 || (i < n_cand && g > most)) {
+                most = g;
+                best_q = i;
+            }
+        }
+        const bool any = __ballot(mine.at >= 0), sure_of_sums = !__ballot(!(energy < __builtin_inf()));
         int open = 1 << best_q;
-        if (any && of_all > 0.0)
-            for (int q = 0; q < n_cand; ++q) open |= most - gain[q] > 2.0 * of_all ? 0 : 1 << q;
-        if (!sure) open = (1 << n_cand) - 1;
-        sure &= open == 1 << best_q;
-        for (int b = 0; b < n_buckets; ++b) sure &= found[best_q][b].second < 0.0 || found[best_q][b].best - found[best_q][b].second > 2.0 * error[b];
-        a.unsure[2 * c + 1] = sure ? 0 : open;
-        chosen = sure ? best_q : -1;
-        if (sure) {
-            const int jj = a.cand[c * kCand + best_q];
-            a.chosen[c] = jj;
-            a.split_dims[4 * c + level] = a.bounds[2 * c] + jj;
-            if (level == 3) a.thresholds[16 * c + 15] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kCand; ++i)
+            if (i < n_cand && any && of_all > 0.0 && !(most - __shfl(gain, i * kSplitBuckets) > 2.0 * of_all)) open |= 1 << i;
+        if (!sure_of_sums) open = (1 << n_cand) - 1;
+        const bool close = q == best_q && !(mine.second < 0.0 || mine.best - mine.second > 2.0 * error);
+        const bool sure = sure_of_sums && open == 1 << best_q && !__ballot(close);
+        // (one candidate alone is compared with none, and where all candidates split all buckets no L(B) takes part)
+        const bool wants = (open & (open - 1)) && !a.unsure[2 * c] && (!sure_of_sums || __ballot(here && (open >> q & 1) && mine.at < 0 && n > 0));
+        if (lane == 0) {
+            a.unsure[2 * c + 1] = sure ? 0 : open | (wants ? kWantsLosses : 0);
+            a.exact_levels[2 * c + 1] += sure ? 0 : 1;
+            chosen = sure ? best_q : -1;
+            if (sure) {
+                const int jj = a.cand[c * kCand + best_q];
+                a.chosen[c] = jj;
+                a.split_dims[4 * c + level] = a.bounds[2 * c] + jj;
+                if (level == 3) a.thresholds[16 * c + 15] = 0.0f;
+            }
         }
     }
     __syncthreads();
@@ -2363,6 +2396,7 @@ struct Carver {
 void carve_trees(Carver &w, LearnArgs &a)
 {
     const size_t C = a.C;
+    a.exact_levels = w.take<int32_t>(2 * C);      // (the workspace begins with it: maddness.h)
     a.bounds = w.take<int32_t>(2 * C);
     a.pitch = a.dmax <= 8 ? 8 : (a.dmax + 15) / 16 * 16;
     a.X = w.take<float>(C * (a.N + 1) * a.pitch);
@@ -2487,8 +2521,8 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     const bool estimated = N >= 2048;
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
-    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds, estimated ? nullptr : a.unsure);
-    LAUNCH_OK("launch upload_bounds_kernel");
+    hipLaunchKernelGGL(begin_trees_kernel, dim3(1), dim3(256), 0, stream, b, a, estimated);
+    LAUNCH_OK("launch begin_trees_kernel");
     const int64_t clear_words = (a.node + (size_t)C * N - reinterpret_cast<uint8_t *>(a.chunk_count) + 3) / 4;
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, stream, a.chunk_count, clear_words);
     LAUNCH_OK("launch clear_kernel");
@@ -2540,7 +2574,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
             LAUNCH_OK("launch split_gains_kernel");
             hipLaunchKernelGGL(choose_by_gain_kernel, dim3(C), dim3(1024), 0, stream, a, level, n_buckets);
             LAUNCH_OK("launch choose_by_gain_kernel");
-            // the codebooks that are unsure
+            // the codebooks whose splits are unsure and whose exact losses are asked for
             hipLaunchKernelGGL(bucket_loss_kernel, grid_bucket_loss, dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a, 1);
             LAUNCH_OK("launch bucket_loss_kernel");
         }
@@ -2596,7 +2630,7 @@ int launch_learn_prototypes(const uint8_t *codes, const float *A, int64_t N, int
     carve_prototypes(w, a);
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
-    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds, static_cast<int32_t *>(nullptr));
+    hipLaunchKernelGGL(upload_bounds_kernel, dim3(1), dim3(256), 0, stream, b, 2 * C, a.bounds);
     LAUNCH_OK("launch upload_bounds_kernel");
     if (!ridge) {
         note_kernel("means_kernel", nullptr);

@@ -201,19 +201,7 @@ def test_learner_rejects_bad_arguments(mad):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("N, widths, scale, kinds", [
-    (4097, (3, 4, 5), 0.25, "iri"),          # quarters; a codebook beside them whose sums depend on their order
-    (9000, (40, 17), 1.0, "sw"),             # both signs; values of 17 bits: 2 x 18 + 14 bits, next to the limit of exact sums
-    (8500, (5, 2), 1.0, "Ww"),               # 20 bits: past it
-    (270000, (2, 3), 1.0, "ci"),             # more groups of 256 rows than a workgroup scans at once; equal rows
-    (3000, (6, 5), 1.0, "dr"),               # columns that are copies: only the exact sums tell which comes first
-    (700, (4, 3, 2), 1.0, "bz1"),            # buckets that cannot be split, columns of zeros, columns of one value
-    (2050, (18, 33), 1.0, "dr"),             # the same copies in subspaces of more than 16 columns
-    (2600, (5, 6, 7), 1.0, "oht"),           # little spread far from 0; large values; subnormal ones
-    (2048, (4, 9), 1.0, "xr"),               # infinities: comparisons with what is not a number
-])
-def test_learner_estimates_and_exact_sums(mad, N, widths, scale, kinds):
-    """Data whose choices the estimates settle and data that take the exact sums, codebook by codebook: all equal to the oracle's."""
+def estimate_matrix(N, widths, scale, kinds):
     rng = np.random.default_rng(N)
     relu = lambda n: np.maximum(rng.standard_normal(n), 0)
     draw = {"i": lambda n: rng.integers(0, 256, n), "s": lambda n: rng.integers(-300, 300, n), "w": lambda n: rng.integers(0, 1 << 17, n),
@@ -222,11 +210,39 @@ def test_learner_estimates_and_exact_sums(mad, N, widths, scale, kinds):
             "z": np.zeros, "1": lambda n: np.full(n, 0.1), "o": lambda n: 1000 + 1e-3 * rng.standard_normal(n),
             "h": lambda n: 1e30 * rng.standard_normal(n), "t": lambda n: 1e-41 * rng.standard_normal(n),
             "x": lambda n: np.where(rng.random(n) < 3 / n[0], np.inf, rng.standard_normal(n))}
+    return np.concatenate([draw[k]((N, w)) * scale for w, k in zip(widths, kinds)], 1).astype(np.float32)
+
+
+# settled: per codebook, whether estimates settle all levels' columns and splits (e) or exact sums some (x); both numbers of levels
+# where they are known
+@pytest.mark.parametrize("N, widths, scale, kinds, settled", [
+    (4097, (3, 4, 5), 0.25, "iri", "eee"),       # quarters; a codebook beside them whose sums depend on their order
+    (9000, (40, 17), 1.0, "sw", "ee"),           # both signs; values of 17 bits: 2 x 18 + 14 bits, next to the limit of exact sums
+    (8500, (5, 2), 1.0, "Ww", "ee"),             # 20 bits: past it
+    (270000, (2, 3), 1.0, "ci", "xe"),           # more groups of 256 rows than a workgroup scans at once; equal rows
+    (3000, (6, 5), 1.0, "dr", "xe"),             # columns that are copies
+    (700, (4, 3, 2), 1.0, "bz1", "xxx"),         # (few rows) buckets that cannot be split, columns of zeros, columns of one value
+    (2600, (4, 3, 2), 1.0, "bz1", "?ex"),        # the same with estimates
+    (2050, (18, 33), 1.0, "dr", "xe"),           # copies in subspaces of more than 16 columns
+    (2600, (5, 6, 7), 1.0, "oht", "xee"),        # little spread far from 0; large values; subnormal ones
+    (2048, (4, 9), 1.0, "xr", "xe"),             # infinities: comparisons with what is not a number
+])
+def test_learner_estimates_and_exact_sums(mad, N, widths, scale, kinds, settled):
+    """Data whose choices the estimates settle and data that take the exact sums, codebook by codebook: all equal to the oracle's."""
+    import torch
     print("case estimates", N, widths, flush=True)
-    A = np.concatenate([draw[k]((N, w)) * scale for w, k in zip(widths, kinds)], 1).astype(np.float32)
+    A = estimate_matrix(N, widths, scale, kinds)
     ends = np.cumsum(widths)
     subspaces = [(int(e - w), int(e)) for e, w in zip(ends, widths)]
-    sd, th, codes = mad.maddness_learn_trees(dev(A), subspaces)
+    workspace = torch.zeros(mad.lib().maddness_learn_trees_workspace(N, A.shape[1], len(widths), mad._bounds(subspaces)[0]),
+                            dtype=torch.uint8, device="cuda")
+    sd, th, codes = mad.maddness_learn_trees(dev(A), subspaces, workspace=workspace)
+    by_exact = workspace[:8 * len(widths)].view(torch.int32).cpu().numpy().reshape(-1, 2)
+    print("levels by exact sums", by_exact.tolist(), flush=True)
+    for kind, levels in zip(settled, by_exact):
+        assert kind == "?" or (levels.sum() > 0) == (kind == "x") and (levels <= 4).all(), by_exact
+    if N < 2048:
+        assert (by_exact == 4).all()
     P = mad.maddness_learn_prototypes(codes, dev(A), subspaces)
     want_sd, want_th, want_codes, _ = oracle.learn_trees(A, subspaces)
     assert (sd.cpu().numpy() == want_sd).all()
