@@ -74,6 +74,8 @@ struct LearnArgs {
     // what the estimates leave (the tiles' sums lie in `sums`, [C][4][2 tile_slots][2 dmax] or less of it, as [slot][dmax])
     int64_t part_slots;   // parts of kPartRows rows of all buckets of a level, at most
     double *parts;        // [C][part_slots][3][dmax] of a part's values x, the pivot taken off (y): sum y, sum y^2, sum x^2
+    int32_t *original;    // [C][dmax] the column that a column is a copy of in all rows, as far as that has been found out; itself
+    int64_t *may_compare; // [C] rows that columns may still be compared in (2.5 ns each, less where a row is few columns; a level's exact sums 13)
     double *energy;       // [C][8] the sum of the squares of a bucket's values, or a little more
     int32_t *exact_levels;   // [C][2] on how many levels exact sums chose the candidates, and the split among theirs
     int32_t *unsure;      // [C][2] whether the candidates take exact sums to tell; bit q: whether candidate q's split does, and flags
@@ -685,13 +687,25 @@ __device__ __forceinline__ int largest_left(const double (&total)[kMaxWidth / 64
 
 // heuristic_select_idxs from the estimates: the four columns with the largest losses summed over the buckets, largest first,
 // and whether the estimates can tell.  A workgroup per codebook, its 8 wavefronts shared out among the buckets.
-__global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_buckets)
+// Columns next to the one that is chosen may be copies of it: then all their sums are the same, and the first is taken.
+// The workgroup compares them row by row (mostly the first rows tell that they are not) and keeps what it finds for
+// choose_by_gain_kernel and the levels that follow.  (131072 x 64, 8 codebooks of which every column has a copy: the four
+// levels' trees 1964 us, 4268 with exact sums for all of them.)
+__global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int level, int n_buckets)
 {
+    __shared__ int32_t original[kMaxWidth], asked;        // (the column to compare with, or -1)
+    __shared__ unsigned long long close[kMaxWidth / 64];  // the columns to compare; those that differ
+    __shared__ uint32_t differ[kMaxWidth / 32];
     __shared__ double from_wave[8][16][kPartValues], loss[kMaxWidth], error[kMaxWidth], energy[kSplitBuckets], spread[kSplitBuckets];
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], b = wave % n_buckets, share = wave / n_buckets, shares = 8 / n_buckets;
     const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
     const int n_parts = (count + kPartRows - 1) / kPartRows, col = lane & 15;
+    // (used at the end, asked for here)
+    const int first_like = tid < d && level > 0 ? a.original[(size_t)c * a.dmax + tid] : tid;
+    const double rows_of_lane = lane < n_buckets ? (double)a.bucket_count[c * kSplitBuckets + lane] : 0.0;
+    const bool exact_sums = any_order(a, c);
+    int64_t left = level == 0 ? (a.pitch <= 32 ? 16 : 8) * a.N : a.may_compare[c];
     if (tid < kMaxWidth) loss[tid] = error[tid] = 0.0;
     if (tid < kSplitBuckets) energy[tid] = spread[tid] = 0.0;
     for (int col0 = 0; col0 < d; col0 += 16) {
@@ -735,38 +749,106 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int n_bu
         __syncthreads();
     }
     if (tid < n_buckets) a.energy[c * kSplitBuckets + tid] = energy[tid] * 1.0001;
-    if (wave != 0) return;
-    // A bucket whose whole loss is less than what two splits of it have to differ by (little spread far from 0): there will be
-    // no telling.  (20000 x 512 of 1000 and a thousandth either way, 32 codebooks: 2976 us with all estimates, 2659 with none.)
-    bool hopeless = false;
-    if (lane < n_buckets && spread[lane] > 0.0) {
-        const double n = (double)a.bucket_count[c * kSplitBuckets + lane];
-        hopeless = spread[lane] < 2.0 * split_error(n, sqrt(n), (double)a.N, energy[lane], d, any_order(a, c), true);
-    }
-    double total[kMaxWidth / 64], off_by[kMaxWidth / 64];
-    bool taken[kMaxWidth / 64];
-    bool finite = true;
-#pragma unroll
-    for (int i = 0; i < kMaxWidth / 64; ++i) {
-        taken[i] = lane + 64 * i >= d;
-        total[i] = loss[lane + 64 * i];
-        off_by[i] = error[lane + 64 * i];
-        finite &= total[i] < __builtin_inf() && off_by[i] < __builtin_inf();
-    }
-    for (int k = 0; k < n_buckets; ++k) finite &= energy[k] < __builtin_inf();
-    bool sure = !__ballot(!finite);
+    if (tid < d) original[tid] = first_like;
+    __syncthreads();
     const int n_cand = min(kCand, d);
-    for (int k = 0; k < n_cand; ++k) {
-        const int best = largest_left(total, taken);
-        const double least = loss[best & (kMaxWidth - 1)] - error[best & (kMaxWidth - 1)];
-        // (columns of zeros alone have no error: their losses are equal, in column order)
-        bool less = true;
+    bool finite = true, sure = true;
+    unsigned long long compared[kMaxWidth / 64] = {};     // (columns that others have been compared with)
+    for (;;) {
+        if (wave == 0) {
+            double total[kMaxWidth / 64], off_by[kMaxWidth / 64];
+            bool taken[kMaxWidth / 64];
+            finite = true;
 #pragma unroll
-        for (int i = 0; i < kMaxWidth / 64; ++i)
-            less &= taken[i] || total[i] + off_by[i] < least || (off_by[i] == 0.0 && error[best & (kMaxWidth - 1)] == 0.0);
-        if (__ballot(!less)) sure = false;
-        if (lane == 0) a.cand[c * kCand + k] = best;
+            for (int i = 0; i < kMaxWidth / 64; ++i) {
+                taken[i] = lane + 64 * i >= d;
+                total[i] = loss[lane + 64 * i];
+                off_by[i] = error[lane + 64 * i];
+                finite &= total[i] < __builtin_inf() && off_by[i] < __builtin_inf();
+            }
+            for (int k = 0; k < n_buckets; ++k) finite &= energy[k] < __builtin_inf();
+            finite = !__ballot(!finite);
+            sure = finite;
+            int ask = -1;
+            for (int k = 0; k < n_cand; ++k) {
+                const int best = largest_left(total, taken) & (kMaxWidth - 1);
+                const double least = loss[best] - error[best];
+                bool any_close = false, alike = true;             // (the estimates of a copy are the same to the bit)
+                unsigned long long those[kMaxWidth / 64];
+#pragma unroll
+                for (int i = 0; i < kMaxWidth / 64; ++i) {
+                    const int col = lane + 64 * i;
+                    // (columns of zeros alone have no error: their losses are equal, in column order)
+                    const bool less = taken[i] || total[i] + off_by[i] < least || (off_by[i] == 0.0 && error[best] == 0.0) ||
+                                      (col > best && original[col] == original[best]);
+                    those[i] = __ballot(!less);
+                    any_close |= those[i] != 0;
+                    alike &= less || (total[i] == loss[best] && off_by[i] == error[best]);
+                }
+                if (lane == 0) a.cand[c * kCand + k] = best;
+                if (!any_close || !sure) continue;
+                int pieces = 0;
+#pragma unroll
+                for (int i = 0; i < kMaxWidth / 64; ++i)
+                    pieces += __popcll((those[i] | those[i] >> 1 | those[i] >> 2 | those[i] >> 3) & 0x1111111111111111ull);
+                if (__ballot(!alike) || (compared[best / 64] >> (best % 64) & 1) || pieces * a.N > left) {
+                    sure = false;
+                    continue;
+                }
+                compared[best / 64] |= 1ull << (best % 64);
+                ask = best;
+                if (lane == 0) {
+#pragma unroll
+                    for (int i = 0; i < kMaxWidth / 64; ++i) close[i] = those[i];
+                }
+                break;
+            }
+            if (lane == 0) asked = ask;
+            if (lane < kMaxWidth / 32) differ[lane] = 0;
+        }
+        __syncthreads();
+        const int best = asked;
+        if (best < 0) break;
+        // a piece of four columns with close ones after the other, its rows until all of them differ
+        constexpr int kAhead = 8;
+        const uint32_t *X = reinterpret_cast<const uint32_t *>(a.X + (size_t)c * (a.N + 1) * a.pitch);
+        for (int piece = 0; 4 * piece < d; ++piece) {
+            const uint32_t wanted = (uint32_t)(close[piece / 16] >> (4 * piece % 64)) & 15u;
+            if (!wanted) continue;
+            for (int64_t row0 = 0; row0 < a.N; row0 += 512 * kAhead) {
+                left -= min(a.N - row0, (int64_t)512 * kAhead);
+                uint4 v[kAhead];
+                uint32_t of_best[kAhead], other = 0;
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) {
+                    const int64_t row = min(row0 + 512 * i + tid, a.N - 1);
+                    v[i] = *reinterpret_cast<const uint4 *>(X + row * a.pitch + 4 * piece);
+                    of_best[i] = X[row * a.pitch + best];
+                }
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i)
+                    other |= (v[i].x != of_best[i] ? 1u : 0u) | (v[i].y != of_best[i] ? 2u : 0u) | (v[i].z != of_best[i] ? 4u : 0u) |
+                             (v[i].w != of_best[i] ? 8u : 0u);
+                other &= wanted;
+                if (other) atomicOr(&differ[piece / 8], other << (4 * piece % 32));
+                __syncthreads();
+                const bool all = ((differ[piece / 8] >> (4 * piece % 32)) & wanted) == wanted;
+                __syncthreads();                          // (all have read it before the next rows' are added)
+                if (all) break;
+            }
+        }
+        __syncthreads();
+        if (tid < d && (close[tid / 64] >> (tid % 64) & 1) && !(differ[tid / 32] >> (tid % 32) & 1)) original[tid] = original[best];
+        __syncthreads();
     }
+    if (tid < d) a.original[(size_t)c * a.dmax + tid] = original[tid];
+    if (wave != 0) return;
+    if (lane == 0) a.may_compare[c] = left;
+    // A bucket whose whole loss is less than what two splits of it have to differ by (little spread far from 0): there will be
+    // no telling.  (20000 x 512 of 1000 and a thousandth either way, 32 codebooks: 2976 us with all estimates, 2625 with none.)
+    bool hopeless = false;
+    if (lane < n_buckets && spread[lane] > 0.0)
+        hopeless = spread[lane] < 2.0 * split_error(rows_of_lane, sqrt(rows_of_lane), (double)a.N, energy[lane], d, exact_sums, true);
     const bool none = __ballot(hopeless || !finite);
     if (lane == 0) {
         a.n_cand[c] = n_cand;
@@ -1449,6 +1531,11 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_cand = a.n_cand[c], d = a.bounds[2 * c + 1] - a.bounds[2 * c];
     if (a.unsure[2 * c + 1]) return;
+    // (used by the first wavefront after the loop: a lane per (candidate, bucket), the copies a lane per candidate)
+    const int n = lane % kSplitBuckets < n_buckets ? (int)a.bucket_count[c * kSplitBuckets + lane % kSplitBuckets] : 0;
+    const double energy = lane % kSplitBuckets < n_buckets ? a.energy[c * kSplitBuckets + lane % kSplitBuckets] : 0.0;
+    const bool exact_sums = any_order(a, c), have_losses = a.unsure[2 * c];
+    const int first_like = lane < n_cand ? a.original[(size_t)c * a.dmax + a.cand[c * kCand + lane]] : -1 - lane;
     for (int pair = wave; pair < n_cand * n_buckets; pair += 16) {
         const int q = pair / n_buckets, b = pair - q * n_buckets;
         const int start = a.bucket_start[c * kSplitBuckets + b], count = (int)a.bucket_count[c * kSplitBuckets + b];
@@ -1468,16 +1555,13 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
     }
     __syncthreads();
     if (wave == 0) {
-        // a lane per (candidate, bucket)
         const int q = lane / kSplitBuckets, b = lane % kSplitBuckets;
         const bool here = q < n_cand && b < n_buckets;
         const Gain mine = here ? found[q][b] : Gain{-1.0, -1.0, -1};
-        const int n = b < n_buckets ? (int)a.bucket_count[c * kSplitBuckets + b] : 0;
-        const double energy = b < n_buckets ? a.energy[c * kSplitBuckets + b] : 0.0;
         // (of the lanes of a bucket: whether each of the candidates splits it)
         const unsigned long long cannot = __ballot(here && mine.at < 0);
         const bool every_splits = !(cannot & (0x01010101ull << b));
-        const double error = n > 1 ? split_error((double)n, sqrt((double)n), (double)a.N, energy, d, any_order(a, c), every_splits) : 0.0;
+        const double error = n > 1 ? split_error((double)n, sqrt((double)n), (double)a.N, energy, d, exact_sums, every_splits) : 0.0;
         double of_all = error, gain = fmax(mine.best, 0.0);
 #pragma unroll
         for (int off = 1; off < kSplitBuckets; off <<= 1) {
@@ -1502,10 +1586,16 @@ __global__ __launch_bounds__(1024) void choose_by_gain_kernel(const LearnArgs a,
         for (int i = 0; i < kCand; ++i)
             if (i < n_cand && any && of_all > 0.0 && !(most - __shfl(gain, i * kSplitBuckets) > 2.0 * of_all)) open |= 1 << i;
         if (!sure_of_sums) open = (1 << n_cand) - 1;
+        // (a copy of an earlier candidate has the same losses, and the first of equal ones is taken)
+#pragma unroll
+        for (int i = 1; i < kCand; ++i)
+#pragma unroll
+            for (int j = 0; j < i; ++j)
+                if (__shfl(first_like, i) == __shfl(first_like, j)) open &= ~(1 << i);
         const bool close = q == best_q && !(mine.second < 0.0 || mine.best - mine.second > 2.0 * error);
         const bool sure = sure_of_sums && open == 1 << best_q && !__ballot(close);
         // (one candidate alone is compared with none, and where all candidates split all buckets no L(B) takes part)
-        const bool wants = (open & (open - 1)) && !a.unsure[2 * c] && (!sure_of_sums || __ballot(here && (open >> q & 1) && mine.at < 0 && n > 0));
+        const bool wants = (open & (open - 1)) && !have_losses && (!sure_of_sums || __ballot(here && (open >> q & 1) && mine.at < 0 && n > 0));
         if (lane == 0) {
             a.unsure[2 * c + 1] = sure ? 0 : open | (wants ? kWantsLosses : 0);
             a.exact_levels[2 * c + 1] += sure ? 0 : 1;
@@ -2420,6 +2510,8 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.group_slots = a.N / kGroupRows + kSplitBuckets + 1;
     a.part_slots = a.N / kPartRows + kSplitBuckets + 1;
     a.parts = w.take<double>(C * a.part_slots * kPartValues * a.dmax);
+    a.original = w.take<int32_t>(C * a.dmax);
+    a.may_compare = w.take<int64_t>(C);
     a.energy = w.take<double>(C * kSplitBuckets);
     a.unsure = w.take<int32_t>(2 * C);
     a.group_sums = w.take<double>(C * kCand * a.group_slots * a.dmax);
@@ -2516,9 +2608,11 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     Carver w{static_cast<unsigned char *>(workspace)};
     carve_trees(w, a);
     a.row_bits = N > 1 ? 64 - __builtin_clzll((unsigned long long)(N - 1)) : 0;
-    // (few rows: their chains take no longer than the estimates' seven launches a level.  1000 rows of 20 columns, 4 codebooks:
-    // 450 us with estimates, 392 without; 3000 of 100, 15: 840 and 849; 5000 of 512, 16: 1044 and 1320)
-    const bool estimated = N >= 2048;
+    const bool narrow = dmax <= 8;
+    // (few rows: their chains take no longer than the estimates' seven launches a level, the sooner so the fewer chains there are.
+    // The trees of 2048 rows of 64 columns, 8 codebooks: 350 us with estimates, 320 to 333 without; 3000: 366 and 367 to 389; 2100, 4
+    // codebooks: 347 and 384 to 402; 2048 of 512, 32 codebooks: 390 and 460)
+    const bool estimated = N >= (narrow ? 3072 : 2048);
     Bounds b{};
     for (int i = 0; i < 2 * C; ++i) b.v[i] = bounds_host[i];
     hipLaunchKernelGGL(begin_trees_kernel, dim3(1), dim3(256), 0, stream, b, a, estimated);
@@ -2531,7 +2625,6 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, kRangeParts), C), dim3(256), 0, stream, a);
     LAUNCH_OK("launch gather_columns_kernel");
 
-    const bool narrow = dmax <= 8;
     for (int level = 0; level < 4; ++level) {
         const int n_buckets = 1 << level;
         hipLaunchKernelGGL(order_rows_kernel, dim3((unsigned)((N + order_chunk_rows(N) - 1) / order_chunk_rows(N)), C), dim3(256), 0,
@@ -2542,7 +2635,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
             if (narrow) hipLaunchKernelGGL(loss_parts_kernel<8>, grid_parts, dim3(256), 0, stream, a, n_buckets);
             else hipLaunchKernelGGL(loss_parts_kernel<16>, grid_parts, dim3(256), 0, stream, a, n_buckets);
             LAUNCH_OK("launch loss_parts_kernel");
-            hipLaunchKernelGGL(select_kernel, dim3(C), dim3(512), 0, stream, a, n_buckets);
+            hipLaunchKernelGGL(select_kernel, dim3(C), dim3(512), 0, stream, a, level, n_buckets);
             LAUNCH_OK("launch select_kernel");
         }
         hipLaunchKernelGGL(bucket_loss_kernel, grid_bucket_loss, dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a, 0);
