@@ -23,7 +23,7 @@
 //   loss_parts_kernel, select_kernel  heuristic_select_idxs by estimates: the four columns with the largest summed loss
 //   bucket_loss_kernel   L(j, B) (Section 4.2) for every column j of every bucket, two passes
 //                        over the bucket's own rows (the exact losses, where the estimates are unsure)
-//   sort_round_kernel, or sort_count_kernel and sort_scatter_kernel  the rows ordered by each candidate column (radix
+//   sort_few_kernel, sort_round_kernel, or sort_count_kernel and sort_scatter_kernel  the rows ordered by each candidate column (radix
 //                        sort of (value, row) keys: equal values stay in row order)
 //   tile_sums_kernel, scan_groups_kernel, split_gains_kernel, choose_by_gain_kernel  Algorithm 3 for every bucket and
 //                        Algorithm 2's choice among the candidates by estimates
@@ -1043,6 +1043,31 @@ __global__ __launch_bounds__(kSortThreads, 4) void sort_round_kernel(const Learn
                 if (i < per_wave) key[i] = s.keys[64 * (wave * per_wave + i) + lane];
     }
     for (int i = tid; i < N; i += kSortThreads) out[i] = s.keys[i];
+}
+
+// The same for up to a thread's key each: a key's place is the number of smaller ones, counted by all threads over the keys in
+// LDS, two to a read.  (A digit's round takes as long for a few keys as for 512.  The trees of 50 rows of 64 columns, 8
+// codebooks: 151 us, 189 by digits; 512 rows 237 and 254.)
+__global__ __launch_bounds__(kSortThreads) void sort_few_kernel(const LearnArgs a, int n_buckets)
+{
+    __shared__ __align__(16) uint64_t keys[kSortThreads];
+    __shared__ int32_t shared;
+    const int c = blockIdx.z, q = blockIdx.y, d = a.bounds[2 * c + 1] - a.bounds[2 * c];
+    if (q >= min(kCand, d)) return;
+    const int tid = threadIdx.x, N = (int)a.N, p = min(tid, N - 1);
+    const int bucket = a.node[(size_t)c * a.N + p];
+    const int col = sort_column(a, c, q, d, n_buckets, true, &shared);
+    const uint64_t mine = make_key(bucket, a.X[((size_t)c * (a.N + 1) + p) * a.pitch + col], (uint32_t)p);
+    keys[tid] = tid < N ? mine : ~0ull;                   // (smaller than none; whole wavefronts, so there is one where N is odd)
+    __syncthreads();
+    int before = 0;
+    const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(keys);
+#pragma unroll 8
+    for (int i = 0; i < (N + 1) / 2; ++i) {
+        const ulonglong2 two = pairs[i];
+        before += (two.x < mine ? 1 : 0) + (two.y < mine ? 1 : 0);
+    }
+    if (tid < N) a.keys[((size_t)c * kCand + q) * a.N + before] = mine;
 }
 
 // the keys as digit k finds them
@@ -2640,7 +2665,10 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
         }
         hipLaunchKernelGGL(bucket_loss_kernel, grid_bucket_loss, dim3(4 * 64 + kChainHelpers), stream_lds_bytes<4>(), stream, a, 0);
         LAUNCH_OK("launch bucket_loss_kernel");
-        if (N <= kSortRound) {
+        if (N <= kSortThreads) {
+            hipLaunchKernelGGL(sort_few_kernel, dim3(1, kCand, C), dim3((unsigned)((N + 63) / 64 * 64)), 0, stream, a, n_buckets);
+            LAUNCH_OK("launch sort_few_kernel");
+        } else if (N <= kSortRound) {
             hipLaunchKernelGGL(sort_round_kernel, dim3(1, kCand, C), dim3(kSortThreads), 0, stream, a, n_buckets);
             LAUNCH_OK("launch sort_round_kernel");
         } else {
@@ -2700,7 +2728,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
 int launch_learn_trees(const float *A, int64_t N, int64_t lda, int32_t C, const int32_t *bounds_host, int32_t *split_dims,
                        float *thresholds, uint8_t *codes, void *workspace, hipStream_t stream)
 {
-    note_kernel("gather_columns_kernel + order_rows_kernel + loss_parts_kernel + select_kernel + bucket_loss_kernel + sort_round_kernel + sort_count_kernel + sort_scatter_kernel + tile_sums_kernel + scan_groups_kernel + split_gains_kernel + choose_by_gain_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
+    note_kernel("gather_columns_kernel + order_rows_kernel + loss_parts_kernel + select_kernel + bucket_loss_kernel + sort_few_kernel + sort_round_kernel + sort_count_kernel + sort_scatter_kernel + tile_sums_kernel + scan_groups_kernel + split_gains_kernel + choose_by_gain_kernel + split_chains_small_kernel + split_chains_kernel + split_losses_kernel + choose_kernel + apply_kernel", nullptr);
     for (int32_t c = 0; c < C;) {
         LearnArgs a{};
         const int32_t end = batch_end(N, C, bounds_host, c, &a.dmax);

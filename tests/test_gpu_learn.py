@@ -282,3 +282,12 @@ def test_prototypes_of_shared_rows(mad, C, widths):
     P = mad.maddness_learn_prototypes(dev(codes), dev(A), [(0, w) for w in widths])
     want = oracle.ridge_prototypes(codes, A, 1.0)
     assert (P.cpu().numpy() == want.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("N", [2, 63, 64, 65, 129, 511, 512, 513])
+def test_learner_sorts_few_rows(mad, N):
+    """Either side of the rows that are sorted by counting: values that repeat, both zeros, both signs."""
+    rng = np.random.default_rng(N)
+    print("case few rows", N, flush=True)
+    A = np.concatenate([rng.standard_normal((N, 5)), rng.integers(-2, 3, (N, 6)) * 0.5, np.where(rng.random((N, 3)) < 0.5, -0.0, 0.0)], 1).astype(np.float32)
+    check_against_oracle(mad, A, [(0, 5), (5, 11), (8, 14), (11, 14)], f"few rows {N}")
