@@ -38,11 +38,12 @@ __device__ __forceinline__ auto load_row_codes(const MfmaScanArgs &a, int64_t ro
             for (int t = 0; t < bytes; ++t) v[0] |= (unsigned)src[t] << (8 * t);
             return v;
         }
+        const int past = bytes % 4 ? 4 - bytes % 4 : 0;
 #pragma unroll
         for (int q = 0; q < CW; ++q)
             if (4 * q < bytes) {
                 uint32_t w;
-                __builtin_memcpy(&w, src + min(4 * q, bytes - 4), 4);
+                __builtin_memcpy(&w, src + 4 * q - (4 * q + 4 > bytes ? past : 0), 4);
                 v[q] = w;
             }
     } else {
@@ -58,7 +59,7 @@ __device__ __forceinline__ Codes whole_codes(const MfmaScanArgs &a, Codes v)
 {
     if constexpr (ODD) {
         const int bytes = (a.codebooks + 1) / 2;
-        if (bytes > 4)
+        if (bytes > 4 && bytes % 4 != 0)
 #pragma unroll
             for (int q = 1; q < CW; ++q)
                 if (4 * q < bytes && 4 * q + 4 > bytes) v[q] >>= 8 * (4 * q + 4 - bytes);
@@ -370,6 +371,42 @@ __global__ __launch_bounds__(256, 2) void mfma_scan_lines_kernel(const MfmaScanA
                                    (int64_t)((unit - last) % shares) * share + wave / blocks_here, (int64_t)shares * share, one_hot, stage);
 }
 
+// Whether rows of M columns that begin in `classes` places of a line are written by whole lines; `results`: all rows' columns.
+// With less than 48 MB of them caches put the parts of a line together for the other forms (C = 32, M = 1000, N = 16384: 23 us
+// there, 19 here, C = 64, M = 250: 16, 31).  What either form measured, this one second (us; Mi: 2^20 results):
+//   - 64 columns or less (96 for NT = 2) are mostly last lines, whose results are scanned twice (N = 200000, C = 64, M = 66: 37, 46)
+//   - rows that one workgroup's four blocks take whole are written by it in one go (C = 32, N = 300000: M = 248 58, 67; M = 250
+//     76, 86; but padded codebooks in up to 8 classes: M = 252, C = 30 83, 62)
+//   - every other row begins on a line (two classes): the other form writes at up to 6.0 TB/s, this one at 5 (130 Mi, C = 16:
+//     M = 400 92, 114; M = 1040 93, 103), but for up to 144 columns (C = 24, M = 144, 80 Mi 81, 66), a few more than a workgroup takes
+//     (C = 16, M = 272, 80 Mi 81, 68) and a few less than a multiple from 1008 on (C = 24, 200 Mi 174, 161), and where results are
+//     few and codebooks many (C = 32, M = 528, 13 Mi 19, 16)
+//   - few codebooks and 145 to 192 columns (C = 8, M = 164, 200 Mi 144, 172; C = 16, M = 188, 40 Mi 34, 37)
+//   - padded codebooks, 16 and 32 classes, 97 to 192 columns (C = 30: M = 170, 13 Mi 27, 35; M = 171, 64 Mi 95, 94; C = 32: M = 183,
+//     30 Mi 46, 54; C = 31: M = 125, 16 Mi 33, 39, 64 Mi 102, 92; C = 24: M = 186, 13 Mi 24, 28, 50 Mi 62, 64)
+//   - NT = 2 and 16 classes, all the more where the blocks do not fill the workgroups (C = 64: M = 310, 13 Mi 28, 42; M = 322, 50 Mi
+//     80, 76; M = 258, 20 Mi 42, 45; M = 162, 64 Mi 116, 134; C = 40: M = 330, 13 Mi 23, 29; M = 258, 50 Mi 77, 51; C = 56, M = 602,
+//     30 Mi 59, 41)
+inline bool lines_pay(int NT, bool odd, int padded, int C, int M, int classes, bool full, int64_t results)
+{
+    const int64_t mi = results >> 20;
+    if (mi < 12 || M < (NT == 4 ? 64 : 96)) return false;
+    if ((M + 16 * NT - 1) / (16 * NT) == 4 && !(odd && classes <= 8)) return false;
+    if (NT == 2) {
+        if (odd || classes < 16) return true;
+        if (M > 160 && M <= 192 && C > 40) return false;
+        return mi >= (full || M >= 576 ? 14 + (C - 40) * 7 / 12 : C - 14);
+    }
+    if (!odd && classes == 2 && !(C > 16 && mi < 24))
+        return M < 160 || (M > 256 && M < (C > 16 || (C > 8 && mi < 64) ? 320 : 288)) || (M > 960 && M % 256 >= 240);
+    if (!odd && C <= 16 && M > (C > 8 ? 152 : 144) && M <= 192) return mi < 24;
+    if (odd && padded == 32 && classes >= 16 && M > 96 && M <= 192) {
+        if (M <= 160) return mi >= (C > 30 ? 32 : C > 24 ? 24 : C > 20 ? 16 : 12);
+        return mi >= (C > 30 ? 128 : C > 20 ? 64 : 32);
+    }
+    return true;
+}
+
 template <int KG, int NT, bool ODD = false>
 int launch_mfma(const MfmaScanArgs &a, hipStream_t stream)
 {
@@ -379,16 +416,11 @@ int launch_mfma(const MfmaScanArgs &a, hipStream_t stream)
     const int col_blocks = (a.o.M + 16 * NT - 1) / (16 * NT);
     int classes = 1;
     while (classes * (int64_t)a.o.M % 32 != 0) classes *= 2;
-    // (less than 48 MB of results, and rows that one workgroup's four blocks take whole: the other forms are as fast or faster,
-    // as caches put the parts of a line together or one workgroup writes them.  C = 32, M = 1000: N = 16384 23 us there, 19 here, C = 64,
-    // M = 250, N = 16384 16 and 31; N = 300000, C = 32, M = 248 58 and 67, M = 250 76 and 86, but M = 252, C = 30 83
-    // and 62; N = 200000, C = 64, M = 66, where the last of three lines takes half of the work, 37 and 46)
-    const bool one_workgroup = col_blocks == 4 && !(ODD && classes <= 8);
-    if (classes > 1 && a.o.out && !a.o.acc && a.o.ldo == a.o.M && a.o.M >= (NT == 4 ? 64 : 96) && aligned_to(a.o.out, 128) && !one_workgroup &&
-        a.N >= 16384 && a.N * a.o.M >= 12 << 20) {
-        // (a row has up to (M + 31) / 32 first floats of a line, its last line's among them)
-        const int blocks = (((a.o.M + 31) / 32 - 1) * 32 + 16 * NT - 1) / (16 * NT);
-        const int share = blocks >= 3 ? 1 : blocks == 2 ? 2 : 4, quarters = (blocks * share + 3) / 4;
+    // (a row has up to (M + 31) / 32 first floats of a line, its last line's among them)
+    const int blocks = (((a.o.M + 31) / 32 - 1) * 32 + 16 * NT - 1) / (16 * NT);
+    const int share = blocks >= 3 ? 1 : blocks == 2 ? 2 : 4, quarters = (blocks * share + 3) / 4;
+    if (classes > 1 && a.o.out && !a.o.acc && a.o.ldo == a.o.M && aligned_to(a.o.out, 128) && a.N >= 16384 &&
+        lines_pay(NT, ODD, 4 * KG, a.codebooks, a.o.M, classes, blocks == 4 / share * quarters, a.N * a.o.M)) {
         // one to four turns of the chip (two workgroups per compute unit; very wide rows: more), whichever leaves the least undone: the last lines take
         // as long as 64 (32) columns
         const double group_us = (KG * NT * 34 + 1000) / 2400.0, table_us = 4.0;
@@ -436,11 +468,11 @@ int launch_mfma(const MfmaScanArgs &a, hipStream_t stream)
         hipLaunchKernelGGL((mfma_scan_kernel<KG, NT, true>), dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, stream, a);
         return check_hip(hipGetLastError(), "launch mfma_scan_kernel");
     }
-    const int share = col_blocks >= 3 ? 1 : (col_blocks == 2 ? 2 : 4);   // as in the kernel
+    const int of_block = col_blocks >= 3 ? 1 : (col_blocks == 2 ? 2 : 4);   // wavefronts with the same block, as in the kernel
     const int64_t n_groups = (a.N + 15) / 16;
     int64_t gx = (int64_t)dev.cus * 2 / gy;             // two workgroups per CU in all
     if (gx < 1) gx = 1;
-    if (gx * share > n_groups) gx = (n_groups + share - 1) / share;
+    if (gx * of_block > n_groups) gx = (n_groups + of_block - 1) / of_block;
     note_kernel("mfma_scan_kernel", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((mfma_scan_kernel<KG, NT>), dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, stream, a);
     return check_hip(hipGetLastError(), "launch mfma_scan_kernel");
