@@ -25,7 +25,8 @@ using namespace rows;
 using namespace cols;
 
 // CHUNK: codebooks whose loads are issued together (4 loads each); RPL: rows per lane;
-// PIPE (fused mode, M = 256, fp32 output only): encode the next group while scanning; NT: columns that no cache would hold.
+// PIPE (fused mode, M = 256, fp32 output only): encode the next group while scanning; NT: columns that no cache would hold
+// are read past the caches, unless some are split twice.
 template <int MODE, int C, int WAVES, bool AVG, int DT, int CHUNK, int RPL, bool PIPE, bool NT>
 __global__ __launch_bounds__(WAVES * 64) void cols_kernel(const RowsArgs a)
 {
@@ -60,9 +61,26 @@ __global__ __launch_bounds__(WAVES * 64) void cols_kernel(const RowsArgs a)
 
     const int64_t n_groups = (a.N + GROUP - 1) / GROUP;
     const int64_t gstride = (int64_t)gridDim.x * WAVES;
-    ColsEncoder<C, DT, CHUNK, RPL, NT> enc(a);
-
     int64_t g = (int64_t)blockIdx.x * WAVES + wave;
+    if constexpr (NT) {
+        static_assert(MODE == kEncode && WAVES * 64 >= 4 * C, "a thread per split");
+        // (a bit per column, 2^15 of them: columns that far apart count as one)
+        __shared__ uint32_t seen[1024];
+        const bool splits = (int)threadIdx.x < 4 * C;
+        const uint32_t mine = splits ? (uint32_t)a.split_dims[threadIdx.x] & 0x7fffu : 0u;
+        if (splits) seen[mine / 32] = 0;
+        __syncthreads();
+        const bool twice = splits && (atomicOr(&seen[mine / 32], 1u << (mine % 32)) >> (mine % 32) & 1u);
+        if (!__syncthreads_or(twice)) {
+            ColsEncoder<C, DT, CHUNK, RPL, true> enc(a);
+            for (; g < n_groups; g += gstride) {
+                enc.encode_group(g * GROUP, lane);
+                enc.store_codes(a.codes_out);
+            }
+            return;
+        }
+    }
+    ColsEncoder<C, DT, CHUNK, RPL> enc(a);
     if constexpr (MODE == kEncode) {
         for (; g < n_groups; g += gstride) {
             enc.encode_group(g * GROUP, lane);
@@ -182,7 +200,9 @@ int launch_cols_variant(const RowsArgs &a, int blocks_per_cu, hipStream_t stream
     const size_t lds = MODE == kFused ? (size_t)C * 16 * 256 : 0;
     const DeviceInfo &dev = device_info();
     if (lds > (size_t)dev.lds_per_block) return 1;
-    if (int rc = allow_full_lds<cols_kernel<MODE, C, WAVES, AVG, DT, CHUNK, RPL, PIPE, NT>>(); rc != MADDNESS_OK) return rc;
+    if constexpr (MODE == kFused) {
+        if (int rc = allow_full_lds<cols_kernel<MODE, C, WAVES, AVG, DT, CHUNK, RPL, PIPE, NT>>(); rc != MADDNESS_OK) return rc;
+    }
     const int64_t n_groups = (a.N + 64 * RPL - 1) / (64 * RPL);
     const int64_t blocks_needed = (n_groups + WAVES - 1) / WAVES;
     const int64_t max_grid = (int64_t)dev.cus * blocks_per_cu;
@@ -202,10 +222,13 @@ int launch_cols(const RowsArgs &a, int blocks_per_cu, hipStream_t stream)
             return launch_cols_variant<MODE, C, WAVES, AVG, DT, RPL, true>(a, blocks_per_cu, stream);
     }
     // Split columns of more than the last-level cache holds are read past it: nothing of them would be there for another
-    // call.  (N = 2^20, C = 32: fp32 113 -> 105 us, binary16, 268 MB, 60 -> 55.5; where they may be, binary16 with N = 200000 and C = 64,
-    // 102 MB, 47 us as it is, 50 past it.  Bytes are bound by the walk: no difference.)
+    // call.  N = 2^20, C = 32: fp32 113 -> 104 us, binary16, 256 MiB, 59 -> 58 and on other columns each time (the same again: 55 -> 57, some
+    // are still there).  Where they may be, binary16 with N = 200000 and C = 64, 102 MB, 47 us as it is, 50 past it.  A column that
+    // is split twice is in the cache the second time: C = 16, N = 4 2^20, fp32, two columns a codebook 111 us as it is, 120 past it; 64 columns
+    // in all 149 and 183.  Fewer columns than splits are told here, others by the kernel.  Bytes are bound by the walk: no
+    // difference.
     if constexpr (MODE == kEncode && DT != kU8) {
-        if (a.N * 4 * C * elem_size(DT) >= (int64_t)256 << 20)
+        if (a.D >= 4 * C && a.N * 4 * C * elem_size(DT) >= (int64_t)256 << 20)
             return launch_cols_variant<MODE, C, WAVES, AVG, DT, RPL, false, true>(a, blocks_per_cu, stream);
     }
     return launch_cols_variant<MODE, C, WAVES, AVG, DT, RPL, false>(a, blocks_per_cu, stream);

@@ -83,22 +83,29 @@ def test_scan_whole_lines_of_very_wide_rows(mad, M, C):
     assert torch.equal(got, want)
 
 
-@pytest.mark.parametrize("dtype, N, C", [("float32", (1 << 20) + 3, 16), ("float16", (1 << 19) + 6, 64), ("bfloat16", (1 << 20) + 5, 32)])
-def test_encode_columns_larger_than_the_caches(mad, dtype, N, C):
+# once: every column is split once; twice: one is split again on another level of its codebook or in another codebook; few: fewer
+# columns than splits
+@pytest.mark.parametrize("dtype, N, C, splits", [("float32", (1 << 20) + 3, 16, "once"), ("float16", (1 << 19) + 6, 64, "once"),
+                                                 ("bfloat16", (1 << 20) + 5, 32, "once"), ("float16", (1 << 19) + 6, 64, "twice"),
+                                                 ("float32", (1 << 20) + 3, 16, "twice"), ("bfloat16", (1 << 20) + 5, 32, "few")])
+def test_encode_columns_larger_than_the_caches(mad, dtype, N, C, splits):
     import torch
-    print("case columns", dtype, N, C, flush=True)
-    D = 4 * C
+    print("case columns", dtype, N, C, splits, flush=True)
+    D = 4 * C - (splits == "few")
     g = torch.Generator(device="cuda").manual_seed(C)
     pitch = (N + 3) // 4 * 4
     A = torch.randn((D, pitch), generator=g, device="cuda").clamp_(min=0).to(getattr(torch, dtype))[:, :N]
     rng = np.random.default_rng(C)
-    sd = np.stack([rng.permutation(4) + 4 * c for c in range(C)]).astype(np.int32)       # every column, once
+    sd = np.stack([rng.permutation(4) + 4 * c for c in range(C)]).astype(np.int32)
+    if splits == "twice":
+        sd[-1, 3] = sd[-1, 0] if C == 16 else sd[0, 1]
+    sd = np.minimum(sd, D - 1)
     th = np.abs(rng.standard_normal((C, 16))).astype(np.float32)
     params = mad.Params(dev(sd), dev(th))
     got = mad.maddness_encode_typed(params, A, col_major=True)
     kernel = mad.maddness_last_kernel()
     torch.cuda.synchronize()
-    assert kernel.startswith("cols_kernel") and "NT = true" in kernel, kernel
+    assert kernel.startswith("cols_kernel") and ("NT = true" in kernel) == (splits != "few"), kernel
     # a walk of the same trees on the same values
     node = torch.zeros((N, C), dtype=torch.int64, device="cuda")
     at, thd, sdd = torch.arange(C, device="cuda"), dev(th), dev(sd).long()
