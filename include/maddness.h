@@ -268,11 +268,10 @@ int maddness_encode_scan_typed(const maddness_params *params, const void *A, int
  *                  training row in every tree; may be NULL.
  * workspace        device scratch of at least maddness_learn_trees_workspace(...) bytes,
  *                  256-byte aligned (maddness_learn_trees_workspace returns 0 for arguments
- *                  it cannot size).  A codebook of w columns takes about N (8 w + 5) + 32 N'
- *                  bytes (w rounded up to 8 or a multiple of 16, N' = N rounded up to a
- *                  power of two); trees are learned as many at a time as stay within the
- *                  larger of 4 GiB and 2 C (37 N + 32 N'), one at least, and the result does
- *                  not depend on how many.  Most choices are made by estimates of those sums with
+ *                  it cannot size).  A codebook of w columns takes about N (8 w + 70 + w / 7) bytes
+ *                  (w rounded up to 8 or a multiple of 16) and up to a megabyte; trees are learned
+ *                  as many at a time as stay within the larger of 4 GiB and 138 C N bytes, one at
+ *                  least, and the result does not depend on how many.  Most choices are made by estimates of those sums with
  *                  bounds of their error, which name the same column and splits, and the sums are
  *                  only taken where the estimates cannot tell: after the call the workspace begins
  *                  with two int32 per codebook (of the last ones taken at a time), on how many of

@@ -2582,9 +2582,10 @@ size_t batch_bytes(int64_t N, int32_t C, int32_t dmax)
 
 // Trees do not depend on each other, so the codebooks are taken in batches, one after the other in the same workspace: as
 // many as stay within `limit`, one at least.  The codebooks' columns (X) and running sums (sums) take 8 bytes per row and
-// column, everything else 69 per row and codebook or less; without a limit 2^20 rows of 16 subspaces of 128 columns take 16.6
-// GiB, and one wide subspace makes all others of its batch as wide.  Returns one past the batch's last codebook, its
-// widest subspace in *dmax.
+// column, keys and lists of rows 69 per row and codebook, twice which for all codebooks is the limit above 4 GiB; sums of groups and
+// parts of rows a byte for seven columns of a row, the counters up to a megabyte.  Without a limit 2^20 rows of 16 subspaces
+// of 128 columns take 17.4 GiB, and one wide subspace makes all others of its batch as wide.  Returns one past the batch's last
+// codebook, its widest subspace in *dmax.
 int32_t batch_end(int64_t N, int32_t C, const int32_t *bounds, int32_t first, int32_t *dmax)
 {
     const size_t limit = std::max<size_t>((size_t)4 << 30, 2 * (size_t)C * 69 * (size_t)N);
