@@ -688,7 +688,7 @@ __device__ __forceinline__ int largest_left(const double (&total)[kMaxWidth / 64
 // heuristic_select_idxs from the estimates: the four columns with the largest losses summed over the buckets, largest first,
 // and whether the estimates can tell.  A workgroup per codebook, its 8 wavefronts shared out among the buckets.
 // Columns next to the one that is chosen may be copies of it: then all their sums are the same, and the first is taken.
-// The workgroup compares them row by row (mostly the first rows tell that they are not) and keeps what it finds for
+// The workgroup compares them row by row and keeps what it finds for
 // choose_by_gain_kernel and the levels that follow.  (131072 x 64, 8 codebooks of which every column has a copy: the four
 // levels' trees 1964 us, 4268 with exact sums for all of them.)
 __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int level, int n_buckets)
@@ -796,6 +796,14 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int leve
                     continue;
                 }
                 compared[best / 64] |= 1ull << (best % 64);
+                // (64 rows first, by this wavefront: columns of few values tie without being copies)
+                const uint32_t *row = reinterpret_cast<const uint32_t *>(a.X) + ((size_t)c * (a.N + 1) + a.N * lane / 64) * a.pitch;
+                const uint32_t of_best = row[best];
+#pragma unroll
+                for (int i = 0; i < kMaxWidth / 64; ++i)
+                    for (unsigned long long m = those[i]; m && sure; m &= m - 1)
+                        if (__ballot(row[64 * i + __ffsll(m) - 1] != of_best)) sure = false;
+                if (!sure) continue;
                 ask = best;
                 if (lane == 0) {
 #pragma unroll
