@@ -262,8 +262,8 @@ __global__ __launch_bounds__(256, 2) void mfma_scan_kernel(const MfmaScanArgs a)
 // of their own take it (32 columns to a wavefront, all four the same ones), whose tables go on with column 0 and who scan
 // the next rows' codes as well.  Only lines are stored, each by one wavefront, straight from registers.  (Stores alone of
 // 512 MB, by rows of 1000, 500, 300 and 250 floats: 5.2, 5.2, 5.1 and 5.5 TB/s; rows from their first float to their last
-// 4.4, 3.8, 3.5 and 2.7.  The kernel against the one that gathers rows in LDS: M = 1000, C = 32, N = 131072 148 -> 100 us,
-// 5.2 TB/s; M = 999, C = 64 442 -> 307; M = 513, C = 16, N = 262144 237 -> 112; M = 100, C = 32, N = 2^20 184 -> 105.)
+// 4.4, 3.8, 3.5 and 2.7.  The kernel against the one that gathers rows in LDS: M = 1000, C = 32, N = 131072 148 -> 107 us,
+// 4.9 TB/s; M = 999, C = 64 443 -> 305; M = 513, C = 16, N = 262144 237 -> 112; M = 100, C = 32, N = 2^20 181 -> 103.)
 constexpr int kLine = 32;
 
 // one group of 16 rows after the other: cls + classes i for 16 values of i
