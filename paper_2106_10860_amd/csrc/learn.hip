@@ -147,15 +147,26 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
     const int c = blockIdx.y, pieces = a.pitch / 4, lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
     float4 *X = reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch);
     int top = 0, least = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (a.N + 1) * pieces; i += (int64_t)gridDim.x * 256) {
-        const int64_t row = i / pieces;
-        const int col = 4 * (int)(i - row * pieces);
-        float v[4];
+    // (four turns' loads ahead of their stores: there are no more workgroups than parts of a range.  2^20 x 128, one codebook:
+    // 550 us one by one)
+    constexpr int kAhead = 4;
+    const int64_t n = (a.N + 1) * pieces, stride = (int64_t)gridDim.x * 256;
+    for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += kAhead * stride) {
+        float v[kAhead][4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = row < a.N && col + e < d ? a.A[row * a.lda + lo + col + e] : 0.0f;
-        X[i] = make_float4(v[0], v[1], v[2], v[3]);
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t i = min(i0 + u * stride, n - 1), row = i / pieces;
+            const int col = 4 * (int)(i - row * pieces);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) span_of(v[e], top, least);
+            for (int e = 0; e < 4; ++e) v[u][e] = row < a.N && col + e < d ? a.A[row * a.lda + lo + col + e] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (i0 + u * stride < n) {
+                X[i0 + u * stride] = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) span_of(v[u][e], top, least);
+            }
     }
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -696,6 +707,7 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int leve
     __shared__ int32_t original[kMaxWidth], asked;        // (the column to compare with, or -1)
     __shared__ unsigned long long close[kMaxWidth / 64];  // the columns to compare; those that differ
     __shared__ uint32_t differ[kMaxWidth / 32];
+    __shared__ bool hopeless;
     __shared__ double from_wave[8][16][kPartValues], loss[kMaxWidth], error[kMaxWidth], energy[kSplitBuckets], spread[kSplitBuckets];
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.bounds[2 * c + 1] - a.bounds[2 * c], b = wave % n_buckets, share = wave / n_buckets, shares = 8 / n_buckets;
@@ -711,7 +723,21 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int leve
     for (int col0 = 0; col0 < d; col0 += 16) {
         const double *in = a.parts + ((size_t)c * a.part_slots + first_part(start, b)) * kPartValues * a.dmax + min(col0 + col, d - 1);
         double sum[kPartValues] = {};
-        for (int i = 4 * share + lane / 16; i < n_parts; i += 4 * shares)
+        // (eight parts asked for at a time: 1024 of 128 columns one by one took 460 us)
+        constexpr int kAhead = 8;
+        int i = 4 * share + lane / 16;
+        for (; i + 4 * shares * (kAhead - 1) < n_parts; i += 4 * shares * kAhead) {
+            double x[kAhead][kPartValues];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int v = 0; v < kPartValues; ++v) x[u][v] = in[((size_t)(i + 4 * shares * u) * kPartValues + v) * a.dmax];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int v = 0; v < kPartValues; ++v) sum[v] += x[u][v];
+        }
+        for (; i < n_parts; i += 4 * shares)
 #pragma unroll
             for (int v = 0; v < kPartValues; ++v) sum[v] += in[((size_t)i * kPartValues + v) * a.dmax];
 #pragma unroll
@@ -751,6 +777,14 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int leve
     if (tid < n_buckets) a.energy[c * kSplitBuckets + tid] = energy[tid] * 1.0001;
     if (tid < d) original[tid] = first_like;
     __syncthreads();
+    // A bucket whose whole loss is less than what two splits of it have to differ by (little spread far from 0): there will be
+    // no telling.  (20000 x 512 of 1000 and a thousandth either way, 32 codebooks: 2976 us with all estimates, 2625 with none.)
+    if (wave == 1) {
+        const bool here = lane < n_buckets && spread[lane] > 0.0 &&
+                          spread[lane] < 2.0 * split_error(rows_of_lane, sqrt(rows_of_lane), (double)a.N, energy[lane], d, exact_sums, true);
+        const unsigned long long those = __ballot(here);
+        if (lane == 0) hopeless = those != 0;
+    }
     const int n_cand = min(kCand, d);
     bool finite = true, sure = true;
     unsigned long long compared[kMaxWidth / 64] = {};     // (columns that others have been compared with)
@@ -852,12 +886,7 @@ __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int leve
     if (tid < d) a.original[(size_t)c * a.dmax + tid] = original[tid];
     if (wave != 0) return;
     if (lane == 0) a.may_compare[c] = left;
-    // A bucket whose whole loss is less than what two splits of it have to differ by (little spread far from 0): there will be
-    // no telling.  (20000 x 512 of 1000 and a thousandth either way, 32 codebooks: 2976 us with all estimates, 2625 with none.)
-    bool hopeless = false;
-    if (lane < n_buckets && spread[lane] > 0.0)
-        hopeless = spread[lane] < 2.0 * split_error(rows_of_lane, sqrt(rows_of_lane), (double)a.N, energy[lane], d, exact_sums, true);
-    const bool none = __ballot(hopeless || !finite);
+    const bool none = hopeless || !finite;
     if (lane == 0) {
         a.n_cand[c] = n_cand;
         a.unsure[2 * c] = sure ? 0 : 1;
