@@ -699,14 +699,14 @@ __device__ __forceinline__ int largest_left(const double (&total)[kMaxWidth / 64
 // heuristic_select_idxs from the estimates: the four columns with the largest losses summed over the buckets, largest first,
 // and whether the estimates can tell.  A workgroup per codebook, its 8 wavefronts shared out among the buckets.
 // Columns next to the one that is chosen may be copies of it: then all their sums are the same, and the first is taken.
-// The workgroup compares them row by row and keeps what it finds for
-// choose_by_gain_kernel and the levels that follow.  (131072 x 64, 8 codebooks of which every column has a copy: the four
-// levels' trees 1964 us, 4268 with exact sums for all of them.)
+// The workgroup compares them row by row and keeps what it finds for choose_by_gain_kernel and the levels that follow.
+// (131072 x 64, 8 codebooks of which every column has a copy: the four levels' trees 1964 us, 4268 with exact sums for all
+// of them.)
 __global__ __launch_bounds__(512) void select_kernel(const LearnArgs a, int level, int n_buckets)
 {
     __shared__ int32_t original[kMaxWidth], asked;        // (the column to compare with, or -1)
-    __shared__ unsigned long long close[kMaxWidth / 64];  // the columns to compare; those that differ
-    __shared__ uint32_t differ[kMaxWidth / 32];
+    __shared__ unsigned long long close[kMaxWidth / 64];  // the columns to compare
+    __shared__ uint32_t differ[kMaxWidth / 32];           // those of them that differ
     __shared__ bool hopeless;
     __shared__ double from_wave[8][16][kPartValues], loss[kMaxWidth], error[kMaxWidth], energy[kSplitBuckets], spread[kSplitBuckets];
     const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
