@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libmaddness.so")
 # a copy kernel of known traffic for bandwidth calibration, a library of its own (not part of the method)
 CALIB_LIB = os.path.join(HERE, "libmaddness_calib.so")
 CALIB_SOURCE = os.path.join("calib", "stream_copy.hip")
-SOURCES = ["api.hip", "encode_scan.hip", "fused_rows.hip", "encode_cols.hip", "mfma_scan.hip", "fused_mfma.hip", "build_luts.hip",
+SOURCES = ["api.hip", "encode_scan.hip", "fused_rows.hip", "encode_cols.hip", "mfma_scan.hip", "fused_mfma.hip", "fused_blocks.hip", "build_luts.hip",
            "learn.hip"]
 # the learner's sums must round as written (a * b + c stays two operations): its split decisions are
 # compared bit for bit with a CPU statement of the same algorithms

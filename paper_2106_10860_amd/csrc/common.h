@@ -113,6 +113,12 @@ int launch_fused_mfma(const maddness_params &p, const MatrixA &A, int64_t N, int
                       const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
                       uint8_t *codes, hipStream_t stream);
 
+// Fused encode + exact scan of row-major A by blocks of rows and columns, for few and medium numbers of rows.  only_if_faster:
+// than the other kernels for whole rows, and not just than the general one.  Same return convention as the row kernels.
+int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
+                        const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
+                        uint8_t *codes, bool only_if_faster, hipStream_t stream);
+
 // Encode only with the first phase of that kernel (row-major fp32 A, up to 64 codebooks, many rows).
 int launch_encode_phased(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes,
                          hipStream_t stream);

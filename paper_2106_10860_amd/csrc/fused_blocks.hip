@@ -1,0 +1,536 @@
+// Fused encode + exact scan of row-major A by blocks of rows and columns, for few and medium numbers of rows.
+//
+// A call of a few thousand rows is bound by latencies: a chain of kernel arguments -> trees, tables and rows -> codes ->
+// sums -> stores on a chip that is mostly idle.  So a workgroup (8 wavefronts) takes a block of up to 128 (256) output
+// columns and few rows, as many workgroups as the chip holds, and asks for everything at once:
+//   1. the tables of its columns come in 16-byte pieces as they lie in memory, a piece per thread and load, all of them on
+//      their way together with the first rows and the trees;
+//   2. they pass through LDS in blocks of [16 codes][16 columns], from where ds_read_b64_tr_b8 hands every lane the 16
+//      entries of one codebook and column, the operand that the matrix instruction wants: no byte is turned round by
+//      vector instructions, of which load_tables (mfma_common.h) spends some 90 per 64 bytes;
+//   3. a chunk of rows is copied to LDS as the one range of bytes it is in memory (any pitch, any alignment), lane
+//      (row, codebook) walks its tree there and leaves 16 times its code in a byte;
+//   4. the wavefronts scan the chunk, one or two tiles of 16 columns each, the rows 16 at a time, with the tables as the
+//      first operand: a lane ends up with four consecutive columns of one row and stores them at once.  The next chunk's
+//      rows are on their way meanwhile.
+// Bound by latencies and by the 64 bytes a clock that a compute unit takes in: N = 10000, D = 512, M = 100, C = 32, of 9.1 us
+// (11.5 by rows_kernel) the launch takes 1.8, asking for 133 KiB and having them 3.8, the codes 0.9, the tables' way through LDS
+// 1.2 and the scan 1.2.  16 wavefronts to a workgroup were slower (11.6), as were two workgroups to a compute unit
+// where one chunk is all the work (11.6), and lanes that read neighbouring codes instead of neighbouring columns of the tables (64
+// lines to a load: N = 676, D = 352, M = 737, C = 32 12.4 us, now 6.8).
+#include <algorithm>
+
+#include "mfma_common.h"
+
+namespace maddness {
+namespace {
+
+using mfma::v4i;
+using rows::aligned_to;
+using rows::f4;
+using rows::kMaxRowBytes;
+
+typedef int v2i __attribute__((ext_vector_type(2)));
+
+constexpr int kBlockWaves = 8, kBlockThreads = 64 * kBlockWaves;
+
+// A block of [16 codes][16 columns] of a codebook's table in LDS, 16 bytes apart: threads that write the same code of
+// neighbouring blocks meet in no bank.
+constexpr int kTileBytes = 272;
+
+struct BlockArgs {
+    const uint8_t *luts;
+    const unsigned char *A;   // bytes
+    int64_t pitch;            // bytes between rows
+    int64_t N;
+    const int32_t *split_dims;
+    const float *thresholds;
+    const float *scale, *offset;
+    float *out;
+    int64_t ldo;
+    uint16_t *acc;
+    uint8_t *codes_out;
+    int M, C, D, dtype, row_bytes;
+    int tile_shift;           // log2 of the tiles of 16 columns to a block
+    int col_blocks;
+    int chunk_rows;
+    int chunks;               // of the whole matrix
+    int row_groups;           // workgroups that share out the chunks, a multiple of 8 where there is more than one block of columns
+    unsigned rows_at, tables_at, codes_at;   // in LDS
+    int overlay;              // the tables go where the first rows were
+};
+
+constexpr int lanes_per_row(int C) { return C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 16 : C <= 32 ? 32 : 64; }
+
+// KG: groups of four codebooks; NTW: tiles of 16 columns per wavefront; PF: 16-byte pieces of a chunk of rows per thread.
+template <int KG, int NTW, int PF>
+__global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const BlockArgs a)
+{
+    constexpr int LPR = lanes_per_row(4 * KG), RPW = 64 / LPR;    // lanes to a row, rows per wavefront while encoding
+    constexpr int KGP = LPR / 4;                                   // bytes of codes per row and lane group
+    constexpr int WAVES = kBlockWaves, THREADS = kBlockThreads;
+    constexpr int PIECES = (KG * NTW * 8 + WAVES - 1) / WAVES;     // of the tables, per thread, at most
+    constexpr int BLOCKS = THREADS / 16;                           // [16][16] blocks of the tables at a time
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    v4i *one_hot = reinterpret_cast<v4i *>(smem);
+    unsigned char *tables = smem + a.tables_at, *stage = smem + a.rows_at, *codes_l = smem + a.codes_at;
+    // (all arguments at once: read where they are used, they are a chain of scalar loads before the first vector load)
+    asm volatile("" ::"s"(a.luts), "s"(a.A), "s"(a.pitch), "s"(a.N), "s"(a.split_dims), "s"(a.thresholds), "s"(a.scale),
+                 "s"(a.offset), "s"(a.out), "s"(a.ldo), "s"(a.acc), "s"(a.codes_out), "s"(a.M), "s"(a.C), "s"(a.D), "s"(a.dtype),
+                 "s"(a.row_bytes), "s"(a.tile_shift), "s"(a.col_blocks), "s"(a.chunk_rows), "s"(a.chunks), "s"(a.row_groups),
+                 "s"(a.rows_at), "s"(a.tables_at), "s"(a.codes_at), "s"(a.overlay));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, g = lane >> 4;
+
+    // Workgroups b, b + 8, ... run on the same XCD: the blocks of columns of the same rows follow each other there.
+    int row_group = blockIdx.x, col_block = 0;
+    if (a.col_blocks > 1) {
+        const int b = blockIdx.x >> 3;
+        col_block = b % a.col_blocks;
+        row_group = (b / a.col_blocks) * 8 + (blockIdx.x & 7);
+    }
+    const int tiles = 1 << a.tile_shift;
+    const int col0 = col_block * 16 * tiles;
+    if (row_group >= a.chunks) return;
+
+    // ---- everything the block needs is asked for at once, in the order in which it is used ----
+    const int c = lane & (LPR - 1);
+    const bool real = c < a.C;
+    Tree tr;
+    load_tree(tr, a.split_dims + 4 * (real ? c : 0), a.thresholds + 16 * (real ? c : 0), a.D);
+
+    f4 pre[PF];
+    int shift = 0, next_shift = 0;      // of the first row in the staged range
+    auto fetch_rows = [&](int chunk) INLINE_LAMBDA {
+        const int64_t row0 = (int64_t)chunk * a.chunk_rows;
+        const int64_t left = a.N - row0;
+        const int n_rows = left < a.chunk_rows ? (int)left : a.chunk_rows;
+        const unsigned char *src = a.A + row0 * a.pitch;
+        next_shift = (int)(reinterpret_cast<uintptr_t>(src) & 15u);
+        // the aligned pieces that cover the range: the first and the last may begin or end up to 15 bytes beyond it, inside
+        // the 16 bytes that hold its first or last element
+        const unsigned last = (unsigned)(next_shift + (n_rows - 1) * (int)a.pitch + a.row_bytes - 1) >> 4;
+        const unsigned char *from = src - next_shift;
+#pragma unroll
+        for (int k = 0; k < PF; ++k) {
+            const unsigned p = tid + THREADS * k;
+            pre[k] = *reinterpret_cast<const f4 *>(from + 16 * (p < last ? p : last));
+        }
+    };
+    auto write_rows = [&]() INLINE_LAMBDA {
+        shift = next_shift;
+#pragma unroll
+        for (int k = 0; k < PF; ++k) reinterpret_cast<f4 *>(stage)[tid + THREADS * k] = pre[k];
+    };
+    int chunk = row_group;
+    fetch_rows(chunk);
+
+    // piece n of a thread: tile tid % tiles (neighbours read neighbouring columns), code (tid / tiles) % 16, codebook
+    // tid / (16 tiles) + n BLOCKS / tiles
+    const unsigned table_bytes = 16u * (unsigned)a.C * (unsigned)a.M;      // (below 2^31: the launcher)
+    const int p_tile = tid & (tiles - 1), p_code = (tid >> a.tile_shift) & 15, p_book = tid >> (4 + a.tile_shift);
+    const int book_step = BLOCKS >> a.tile_shift;
+    const int n_pieces = ((4 * KG << a.tile_shift) + BLOCKS - 1) / BLOCKS;
+    const int last_tile = (a.M - 1 - col0) >> 4;
+    const unsigned p_first = (unsigned)(16 * p_book + p_code) * (unsigned)a.M +
+                             (unsigned)(col0 + 16 * (p_tile < last_tile ? p_tile : last_tile));
+    const unsigned p_step = (unsigned)(16 * book_step) * (unsigned)a.M, p_last = table_bytes - 16;
+    uint4 piece[PIECES];
+#pragma unroll
+    for (int n = 0; n < PIECES; ++n) {
+        if (n < n_pieces) {
+            // (tiles and codebooks that do not exist read others' entries; the last pieces end where the tables end)
+            const unsigned at = p_first + (unsigned)n * p_step;
+            __builtin_memcpy(&piece[n], a.luts + (at < p_last ? at : p_last), 16);
+        }
+    }
+
+    // the wavefront's tiles, and its share of the rows where there are fewer tiles than wavefronts
+    constexpr int NTW_SHIFT = NTW == 2 ? 1 : 0;
+    const int wave_tiles = tiles >> NTW_SHIFT, tile0 = NTW * (wave & (wave_tiles - 1));
+    const int share = wave >> (a.tile_shift - NTW_SHIFT), shares = WAVES >> (a.tile_shift - NTW_SHIFT);
+    int col[NTW];
+    float sc[NTW][4], of[NTW][4];
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+        col[t] = col0 + 16 * (tile0 + t) + 4 * g;
+        if (col0 + 16 * tiles <= a.M) {
+            __builtin_memcpy(sc[t], a.scale + col[t], 16);
+            __builtin_memcpy(of[t], a.offset + col[t], 16);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = col[t] + r < a.M ? col[t] + r : a.M - 1;
+                sc[t][r] = a.scale[m];
+                of[t][r] = a.offset[m];
+            }
+        }
+    }
+    mfma::fill_one_hot_table(one_hot, tid);
+
+    // ---- encode: the codes of a chunk, times 16, into LDS ----
+    const int Cb = (a.C + 1) / 2;
+    auto encode = [&](int64_t row0) INLINE_LAMBDA {
+#pragma unroll 1
+        for (int r0 = wave * RPW; r0 < a.chunk_rows; r0 += 2 * WAVES * RPW) {
+            // two groups of rows at once (the second may be beyond the chunk)
+            int r[2];
+            float x[2][4];
+            const unsigned char *rowp[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                r[h] = r0 + h * WAVES * RPW + lane / LPR;
+                rowp[h] = stage + shift + (r[h] < a.chunk_rows ? r[h] : 0) * (int)a.pitch;
+            }
+            auto read = [&](auto dt) INLINE_LAMBDA {
+                constexpr int DT = decltype(dt)::value;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    x[h][0] = widen_at<DT>(rowp[h], tr.j0); x[h][1] = widen_at<DT>(rowp[h], tr.j1);
+                    x[h][2] = widen_at<DT>(rowp[h], tr.j2); x[h][3] = widen_at<DT>(rowp[h], tr.j3);
+                }
+            };
+            switch (a.dtype) {
+            case kF32: read(std::integral_constant<int, kF32>{}); break;
+            case kF16: read(std::integral_constant<int, kF16>{}); break;
+            case kBF16: read(std::integral_constant<int, kBF16>{}); break;
+            default: read(std::integral_constant<int, kU8>{}); break;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && r0 + WAVES * RPW >= a.chunk_rows) break;
+                unsigned code = hash_regs(tr, x[h][0], x[h][1], x[h][2], x[h][3]);
+                code = real ? code : 0u;
+                if (r[h] < a.chunk_rows) codes_l[r[h] * LPR + (c & 3) * KGP + (c >> 2)] = (unsigned char)(code << 4);
+                if (a.codes_out && col_block == 0) {
+                    // eight codes to a register, the first of eight lanes stores them
+                    unsigned q = code | (rows::from_lane_above<1>(code) << 4);
+                    q |= rows::from_lane_above<2>(q) << 8;
+                    if constexpr (LPR > 4) q |= rows::from_lane_above<4>(q) << 16;
+                    constexpr int HELD = LPR > 4 ? 8 : 4;
+                    if (c % HELD == 0 && r[h] < a.chunk_rows && row0 + r[h] < a.N) {
+                        uint8_t *dst = a.codes_out + (row0 + r[h]) * Cb + c / 2;
+                        for (int b = 0; b < HELD / 2; ++b)
+                            if (c / 2 + b < Cb) dst[b] = (uint8_t)(q >> (8 * b));
+                    }
+                }
+            }
+        }
+    };
+
+    v4i T[NTW][KG];
+    const int first_sum = 128 * a.C;
+
+    // ---- scan: H groups of 16 rows at a time, two chains of sums or more ----
+    auto scan = [&](int64_t row0, int r0, auto groups) INLINE_LAMBDA {
+        constexpr int H = decltype(groups)::value, CHAINS = H == 1 && NTW == 1 && KG > 1 ? 2 : 1;
+        unsigned word[H][(KGP + 3) / 4];
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            // (codes of rows that do not exist are any bytes: within the one-hot table)
+            const unsigned char *mine = codes_l + (r0 + 16 * shares * h + i) * LPR + g * KGP;
+            if constexpr (KGP >= 4) {
+#pragma unroll
+                for (int q = 0; q < KGP / 4; ++q) word[h][q] = reinterpret_cast<const unsigned *>(mine)[q];
+            } else if constexpr (KGP == 2) {
+                word[h][0] = *reinterpret_cast<const uint16_t *>(mine);
+            } else {
+                word[h][0] = *mine;
+            }
+        }
+        v4i sum[H][NTW][CHAINS];
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int t = 0; t < NTW; ++t)
+#pragma unroll
+                for (int q = 0; q < CHAINS; ++q) {
+                    const int start = q == 0 ? first_sum : 0;
+                    sum[h][t][q] = v4i{start, start, start, start};
+                }
+#pragma unroll
+        for (int G = 0; G < KG; ++G) {
+            v4i oh[H];
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const unsigned at = (word[h][G >> 2] >> (8 * (G & 3))) & 240u;
+                oh[h] = *reinterpret_cast<const v4i *>(reinterpret_cast<const unsigned char *>(one_hot) + at);
+            }
+#pragma unroll
+            for (int t = 0; t < NTW; ++t)
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    sum[h][t][G % CHAINS] = __builtin_amdgcn_mfma_i32_16x16x64_i8(T[t][G], oh[h], sum[h][t][G % CHAINS], 0, 0, 0);
+        }
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const int r = r0 + 16 * shares * h + i;
+            const int64_t row = row0 + r;
+            if (r < a.chunk_rows && row < a.N) {
+#pragma unroll
+                for (int t = 0; t < NTW; ++t) {
+                    v4i f = sum[h][t][0];
+                    if constexpr (CHAINS == 2) f += sum[h][t][1];
+                    if (a.out) {
+                        float *dst = a.out + row * a.ldo + col[t];
+                        f4 v;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = fmaf((float)f[q], sc[t][q], of[t][q]);
+                        if (col[t] + 3 < a.M) {
+                            __builtin_memcpy(dst, &v, 16);
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < 3; ++q)
+                                if (col[t] + q < a.M) dst[q] = v[q];
+                        }
+                    }
+                    if (a.acc) {
+                        uint16_t *dst = a.acc + row * a.M + col[t];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (col[t] + q < a.M) dst[q] = (uint16_t)f[q];
+                    }
+                }
+            }
+        }
+    };
+
+    write_rows();
+    __syncthreads();
+    encode((int64_t)chunk * a.chunk_rows);
+    // ---- tables: registers -> LDS -> the matrix instruction's operands ----
+    if (a.overlay) __syncthreads();
+    {
+        unsigned char *dst = tables + ((p_book << a.tile_shift) + p_tile) * kTileBytes + p_code * 16;
+#pragma unroll
+        for (int n = 0; n < PIECES; ++n) {
+            if (n < n_pieces) {
+                const int book = p_book + n * book_step;
+                const unsigned at = p_first + (unsigned)n * p_step;
+                if (at > p_last && at < table_bytes) {
+                    // the end of the tables: move the bytes down (what moves in stands for columns that do not exist)
+                    const unsigned over = 8 * (at - p_last);
+                    const uint64_t lo = (uint64_t)piece[n].y << 32 | piece[n].x, hi = (uint64_t)piece[n].w << 32 | piece[n].z;
+                    const uint64_t l = over >= 64 ? hi >> (over - 64) : lo >> over | hi << (64 - over), u = over >= 64 ? 0 : hi >> over;
+                    piece[n] = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)u, (uint32_t)(u >> 32));
+                }
+                // t - 128 as signed bytes, and nothing where there is no codebook
+                const unsigned flip = 0x80808080u, keep = book < a.C ? ~0u : 0u;
+                const uint4 v = make_uint4((piece[n].x ^ flip) & keep, (piece[n].y ^ flip) & keep, (piece[n].z ^ flip) & keep,
+                                           (piece[n].w ^ flip) & keep);
+                if (book < 4 * KG) *reinterpret_cast<uint4 *>(dst + n * BLOCKS * kTileBytes) = v;
+            }
+        }
+    }
+    __syncthreads();
+    {
+        typedef __attribute__((address_space(3))) v2i lds_v2i;
+        const unsigned char *block = tables + ((g << a.tile_shift) + tile0) * kTileBytes + 8 * i;
+        const int step = (4 << a.tile_shift) * kTileBytes;
+#pragma unroll
+        for (int G = 0; G < KG; ++G)
+#pragma unroll
+            for (int t = 0; t < NTW; ++t) {
+                const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(block + G * step + t * kTileBytes));
+                const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(block + G * step + t * kTileBytes + 128));
+                T[t][G] = v4i{lo.x, lo.y, hi.x, hi.y};
+            }
+    }
+    if (a.overlay && chunk + a.row_groups < a.chunks) __syncthreads();
+
+    while (true) {
+        const int64_t row0 = (int64_t)chunk * a.chunk_rows;
+        const int next = chunk + a.row_groups;
+        const bool more = next < a.chunks;
+        if (more) fetch_rows(next);
+#pragma unroll 1
+        for (int r0 = 16 * share; r0 < a.chunk_rows; r0 += 32 * shares) {
+            if (r0 + 16 * shares < a.chunk_rows) scan(row0, r0, std::integral_constant<int, 2>{});
+            else scan(row0, r0, std::integral_constant<int, 1>{});
+        }
+        if (!more) break;
+        chunk = next;
+        write_rows();
+        __syncthreads();
+        encode((int64_t)chunk * a.chunk_rows);
+        __syncthreads();
+    }
+}
+
+template <int KG, int NTW, int PF>
+int launch_blocks(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
+{
+    if (int rc = allow_full_lds<fused_blocks_kernel<KG, NTW, PF>>(); rc != MADDNESS_OK) return rc;
+    note_kernel("fused_mfma_kernel, A by rows, blocks of columns", __PRETTY_FUNCTION__);
+    hipLaunchKernelGGL((fused_blocks_kernel<KG, NTW, PF>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
+    return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
+}
+
+template <int KG, int NTW>
+int launch_tiles(const BlockArgs &a, int kb, int grid, size_t lds, hipStream_t stream)
+{
+    return kb == 32   ? launch_blocks<KG, NTW, 4>(a, grid, lds, stream)
+           : kb == 64 ? launch_blocks<KG, NTW, 8>(a, grid, lds, stream)
+                      : launch_blocks<KG, NTW, 16>(a, grid, lds, stream);
+}
+
+template <int KG>
+int launch_books(const BlockArgs &a, int ntw, int kb, int grid, size_t lds, hipStream_t stream)
+{
+    if constexpr (KG <= 8)
+        if (ntw == 2) return launch_tiles<KG, 2>(a, kb, grid, lds, stream);
+    return launch_tiles<KG, 1>(a, kb, grid, lds, stream);
+}
+
+// How a call is cut up.
+struct Plan {
+    int tile_shift, col_blocks;
+    int turns;                // chunks that a workgroup takes
+    int64_t groups, rows;     // workgroups to a block of columns, rows of a chunk
+    bool shared;              // two workgroups to a compute unit
+};
+
+// Kernel sizes: codebooks.  0: none (no more than one codebook in eight may be padding).
+int kernel_codebooks(int C)
+{
+    for (int s : {4, 8, 16, 24, 32, 48, 64})
+        if (s >= C) return 8 * (s - C) <= s ? s : 0;
+    return 0;
+}
+
+Plan make_plan(int64_t N, int64_t pitch, bool whole, int M, int KC, int tile_shift, bool shared)
+{
+    const DeviceInfo &dev = device_info();
+    const int wgs = shared ? 2 * dev.cus : dev.cus, kb = shared ? 32 : 128, tiles = (M + 15) / 16;
+    Plan q;
+    q.tile_shift = tile_shift; q.shared = shared;
+    q.col_blocks = (tiles + (1 << tile_shift) - 1) >> tile_shift;
+    q.groups = std::max(1, wgs / q.col_blocks);
+    if (q.groups > 8 && q.col_blocks > 1) q.groups = q.groups / 8 * 8;
+    const int64_t lds = dev.lds_per_block / (shared ? 2 : 1) - 256;
+    const int64_t tables = (int64_t)KC * kTileBytes << tile_shift;
+    const int64_t most = std::min((kb * 1024 - (whole ? 0 : 16)) / pitch,
+                                  (lds - std::max<int64_t>(tables, kb * 1024)) / lanes_per_row(KC) - 16 * (kBlockWaves + 1));
+    const int64_t share = std::max<int64_t>(8, (N + q.groups - 1) / q.groups);
+    if (most < 1) { q.rows = 0; q.turns = 1 << 30; return q; }
+    q.turns = (int)std::min<int64_t>(1 << 30, (share + most - 1) / most);
+    q.rows = (share + q.turns - 1) / q.turns;
+    return q;
+}
+
+Plan choose_plan(int64_t N, int64_t pitch, bool whole, int M, int KC)
+{
+    int shift = 0;
+    while (shift < 3 && (16 << shift) < M) ++shift;
+    Plan plan = make_plan(N, pitch, whole, M, KC, shift, false);
+    if (plan.turns == 1) return plan;
+    // More than one chunk to a workgroup.  Twice the columns to a workgroup are half the rows, which every block of columns
+    // reads and encodes again (N = 2941, D = 384, M = 1000, C = 24: 11.9 and 10.2 us); where one block of columns has them all,
+    // two workgroups to a compute unit, one with its rows on their way while the other has its turn (N = 131072, D = 128,
+    // M = 10, C = 8: 27 and 13.7 us with 128-byte chunks of one workgroup; from 32 codebooks on the tables leave no room:
+    // N = 32768, D = 512, M = 5, C = 32 14.5 and 17.6).
+    if (KC <= 32 && shift == 3) {
+        const Plan wide = make_plan(N, pitch, whole, M, KC, 4, false);
+        if (wide.col_blocks < plan.col_blocks && wide.rows > 0) plan = wide;
+    }
+    if (KC <= 24 && plan.tile_shift <= 3) {
+        const Plan shared = make_plan(N, pitch, whole, M, KC, shift, true);
+        if (shared.rows > 0) plan = shared;
+    }
+    return plan;
+}
+
+// Whether this kernel is the faster one.  only_if_faster = false: instead of the general kernel, which no other kernel would
+// take the call from.  Times in us, this kernel's last.
+bool blocks_pay(const BlockArgs &a, int KC, bool whole, const Plan &plan, bool only_if_faster)
+{
+    const int64_t tables = 16 * (int64_t)a.C * a.M;
+    if (tables <= 8 * 1024) {
+        // Next to no entries to add: up to 20000 rows of up to 8 codebooks both take as long as a launch (N = 8192, D = 27, M = 3,
+        // C = 4: 6.6 and 6.6; N = 4242, D = 128, M = 15, C = 8, bfloat16: 6.7 and 6.7); narrow rows that are not whole 16-byte
+        // pieces are left to the general kernel, which reads their split values alone.
+        if (KC <= 8 && a.N <= 20000) return false;
+        if (a.dtype != MADDNESS_F32 && !whole) return false;
+    }
+    if (!only_if_faster) return true;
+    // One chunk of rows to a workgroup: N = 1891, D = 768, M = 785, C = 48, binary16 45.3 and 11.7; N = 10000, D = 512, M = 100,
+    // C = 32 11.5 and 9.1; N = 8192, D = 512, M = 512, C = 32 15.0 and 12.8; N = 4096, D = 512, M = 1005, C = 32 30.6 and 14.5.
+    if (plan.turns == 1) return true;
+    // Several: the other kernels read a row once for all columns and keep more of it on its way, and the wider and longer the
+    // rows the sooner they win.  Up to 8 codebooks they pay for padding: N = 131072, D = 128, M = 5, C = 8 26 and 13;
+    // N = 521729, D = 64, M = 1000, C = 8 887 and 608; N = 434252, D = 64, M = 256, C = 8 137 and 113; bytes and four codebooks
+    // N = 524288, D = 64, M = 1000 611 and 698.
+    if (KC <= 8) return KC == 8 || a.dtype == MADDNESS_F32;
+    // 16 and 24: N = 65536, D = 192, M = 10, C = 24 26 and 13 (2 turns); N = 248254, D = 256, M = 71, C = 16, bfloat16 65 and 46 (4);
+    // N = 524288, D = 120, M = 13, C = 15 82 and 54 (8); N = 1048576, D = 320, M = 10, C = 16 230 and 262 (41);
+    // two blocks of columns N = 87536, D = 120, M = 474, C = 15, bfloat16 53 and 67; N = 73759, D = 256, M = 256, C = 16 29 and 39.
+    if (KC <= 24) return a.M <= 128 ? plan.turns <= 12 : plan.turns <= 2 && plan.tile_shift == 4 && a.C != 16;
+    // 32: N = 51479, D = 224, M = 247, C = 32 37 and 30 (2 turns); N = 7417, D = 480, M = 1000, C = 30 27 and 18 (2);
+    // N = 65536, D = 352, M = 100, C = 32 33 and 35 (3); N = 262144, D = 256, M = 10, C = 32 74 and 65 (8); N = 175867, D = 512, M = 54 78
+    // and 89 (11); N = 75494, D = 256, M = 512 48 and 67 (5).
+    if (KC == 32) return plan.turns <= (a.M <= 32 ? 8 : 2);
+    // 48 and 64: N = 24287, D = 1024, M = 36, C = 64, bfloat16 21 and 17 (2); N = 63790, D = 528, M = 7, C = 48 40 and 33 (5);
+    // N = 126493, D = 384, M = 128, C = 48 70 and 75 (6); N = 31831, D = 704, M = 256, C = 64, binary16 24 and 34 (3).
+    return a.M <= 128 && plan.turns <= (a.M <= 32 ? 5 : 2);
+}
+
+}  // namespace
+
+int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
+                        const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
+                        uint8_t *codes, bool only_if_faster, hipStream_t stream)
+{
+    const int es = A.elem_bytes(), C = p.C;
+    if (A.col_major || C > 64 || (int64_t)p.D * es > kMaxRowBytes || N < 16 || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    // (these options are about the phased kernel: how many regions it takes)
+    if (option(MADDNESS_OPT_PHASED_ROWS) || option(MADDNESS_OPT_MAX_WORKGROUPS)) return 1;
+    BlockArgs a{};
+    a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.row_bytes = p.D * es; a.D = p.D; a.dtype = A.dtype;
+    a.N = N;
+    a.split_dims = p.split_dims; a.thresholds = p.thresholds;
+    a.luts = luts; a.scale = scale; a.offset = offset; a.M = M; a.C = C;
+    a.out = out; a.ldo = ldo; a.acc = acc; a.codes_out = codes;
+    // the range of a chunk is read whole: rows without much between them
+    if (a.pitch > a.row_bytes + a.row_bytes / 8 + 64) return 1;
+    const int KC = kernel_codebooks(C);
+    if (KC == 0) return 1;
+    const bool whole = a.pitch % 16 == 0 && aligned_to(A.data, 16);      // every row begins on a 16-byte boundary
+    if (a.row_bytes > 4096 && !whole) return 1;
+    const Plan plan = choose_plan(N, a.pitch, whole, M, KC);
+    if (plan.rows < 1 || N / plan.rows >= (1 << 30)) return 1;
+    if (!blocks_pay(a, KC, whole, plan, only_if_faster)) return 1;
+
+    a.tile_shift = plan.tile_shift; a.col_blocks = plan.col_blocks;
+    const int tiles = 1 << plan.tile_shift, ntw = plan.tile_shift == 4 ? 2 : 1;
+    a.chunk_rows = (int)plan.rows;
+    a.chunks = (int)((N + plan.rows - 1) / plan.rows);
+    int64_t groups = std::min<int64_t>(plan.groups, a.chunks);
+    if (a.col_blocks > 1) groups = (groups + 7) / 8 * 8;
+    a.row_groups = (int)groups;
+    const int stage_bytes = (int)(plan.rows * a.pitch + (whole ? 0 : 16));
+    const int kb = stage_bytes <= 32 * 1024 ? 32 : stage_bytes <= 64 * 1024 ? 64 : 128;
+    const size_t table_lds = (size_t)KC * tiles * kTileBytes, rows_lds = (size_t)kb * 1024;
+    // (the scan reads the codes of up to a turn of its wavefronts beyond the last row)
+    const size_t code_lds = (size_t)((plan.rows + 15) / 16 * 16 + 16 * (kBlockWaves * ntw / tiles)) * lanes_per_row(KC);
+    const size_t room = device_info().lds_per_block / (plan.shared ? 2 : 1);
+    a.overlay = 256 + table_lds + rows_lds + code_lds > room ? 1 : 0;
+    a.rows_at = 256;
+    a.tables_at = 256 + (a.overlay ? 0 : (unsigned)rows_lds);
+    a.codes_at = (unsigned)(a.overlay ? 256 + std::max(table_lds, rows_lds) : 256 + table_lds + rows_lds);
+    const size_t lds = a.codes_at + code_lds;
+    if (lds > room) return 1;
+    const int grid = a.row_groups * a.col_blocks;
+    switch (KC) {
+    case 4: return launch_books<1>(a, ntw, kb, grid, lds, stream);
+    case 8: return launch_books<2>(a, ntw, kb, grid, lds, stream);
+    case 16: return launch_books<4>(a, ntw, kb, grid, lds, stream);
+    case 24: return launch_books<6>(a, ntw, kb, grid, lds, stream);
+    case 32: return launch_books<8>(a, ntw, kb, grid, lds, stream);
+    case 48: return launch_books<12>(a, ntw, kb, grid, lds, stream);
+    default: return launch_books<16>(a, ntw, kb, grid, lds, stream);
+    }
+}
+
+}  // namespace maddness

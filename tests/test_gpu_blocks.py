@@ -1,0 +1,87 @@
+"""The fused kernel that works by blocks of rows and columns: every kernel size, one to sixteen tiles of columns to a
+block, one chunk of rows to a workgroup and several (one or two workgroups to a compute unit), tables beside the staged
+rows and in their place, tables whose last pieces run over their end, rows on any element.  The reference is the
+oracle's scalar statement for few rows; for many, the library's general kernels, which the other tests hold against it.
+Sums are whole numbers and one rounding follows: everything is equal to the bit."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_tables_and_few_rows import dev, problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mad():
+    import torch
+    import paper_2106_10860_amd as m
+    assert torch.cuda.is_available()
+    m.lib()
+    return m
+
+
+# (N, D, M, C, dtype, elements between rows, elements before the first, bytes before the tables)
+CASES = [
+    # fewest rows; one column; a table of 16 bytes to a codebook, of which the last piece is all there is
+    (16, 64, 1, 32, "f32", 0, 0, 0), (17, 33, 129, 16, "f32", 0, 1, 1), (31, 48, 15, 48, "f32", 0, 0, 3),
+    # kernel sizes with and without codebooks that do not exist
+    (700, 27, 200, 4, "f32", 0, 0, 0), (515, 61, 100, 7, "f32", 3, 0, 2), (333, 250, 255, 15, "f16", 1, 3, 0),
+    (300, 96, 77, 21, "u8", 0, 5, 1), (257, 333, 64, 31, "bf16", 0, 0, 0), (130, 240, 48, 43, "f32", 0, 3, 0),
+    (90, 505, 127, 63, "f32", 7, 0, 5), (64, 1024, 130, 64, "u8", 0, 0, 0),
+    # blocks of one to eight tiles, and more than one block of columns, the last one with a column
+    (1000, 128, 16, 32, "f32", 0, 0, 0), (1000, 128, 32, 32, "f32", 0, 0, 0), (1000, 128, 60, 32, "f32", 0, 0, 0),
+    (400, 512, 257, 32, "f32", 0, 0, 0), (200, 64, 1025, 24, "f32", 0, 0, 4),
+    # rows of 8 KiB; tables in the place of the first rows
+    (40, 2048, 96, 64, "f32", 0, 0, 0), (9000, 512, 512, 32, "bf16", 0, 0, 0), (4100, 1024, 128, 64, "f32", 0, 0, 0),
+    # several chunks to a workgroup: wide blocks; two workgroups to a compute unit; the last chunk with a row
+    (3001, 384, 1000, 24, "f32", 0, 0, 0), (40001, 120, 90, 15, "f32", 0, 0, 0), (131077, 27, 20, 4, "f32", 0, 0, 0),
+    (65537, 64, 300, 8, "f16", 0, 0, 0), (33000, 480, 16, 30, "f32", 0, 2, 0), (50000, 528, 7, 48, "f32", 0, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%d_D%d_M%d_C%d_%s_p%d_o%d_t%d" % c)
+def test_blocks_of_rows_and_columns(mad, case):
+    import torch
+    N, D, M, C, dtype, pad, before, at = case
+    print("case", case, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D + M, min(N, 2048), D, M, C)
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    full = torch.full((before + N * (D + pad),), 1, dtype=kind, device="cuda")
+    A_d = full[before:].view(N, D + pad)[:, :D]
+    values = (dev(A) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind)
+    A_d.copy_(values[torch.arange(N, device="cuda") % len(A)])
+    raw = torch.zeros(luts.size + at, dtype=torch.uint8, device="cuda")
+    raw[at:] = dev(luts).reshape(-1)
+    luts_d = raw[at:].reshape(C, 16, M)
+    params = mad.Params(dev(sd), dev(th))
+
+    def run():
+        acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+        codes = torch.zeros((N, (C + 1) // 2), dtype=torch.uint8, device="cuda")
+        out = mad.maddness_encode_scan_typed(params, A_d, luts_d, dev(scale), dev(offset), acc=acc, codes=codes)
+        return out, acc, codes, mad.maddness_last_kernel()
+
+    out, acc, codes, kernel = run()
+    torch.cuda.synchronize()
+    assert "blocks of columns" in kernel, kernel
+    if N <= 2048:
+        want_out, want_acc, want_codes = oracle.encode_scan(A_d.float().cpu().numpy().copy(), sd, th, luts, scale, offset)
+        assert (codes.cpu().numpy() == want_codes).all()
+        assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+        assert (out.cpu().numpy() == want_out).all()
+    else:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+        try:
+            want_out, want_acc, want_codes, general = run()
+        finally:
+            mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_AUTO)
+        torch.cuda.synchronize()
+        assert general.startswith("scan_kernel"), general
+        assert torch.equal(codes, want_codes) and torch.equal(acc, want_acc) and torch.equal(out, want_out)
+    # results alone, into rows with columns between them that stay as they are
+    wide = torch.full((N, M + 5), -7.0, device="cuda")
+    mad.maddness_encode_scan_typed(params, A_d, luts_d, dev(scale), dev(offset), out=wide[:, :M])
+    assert mad.maddness_last_kernel() == kernel
+    torch.cuda.synchronize()
+    assert torch.equal(wide[:, :M], out) and bool((wide[:, M:] == -7.0).all())
