@@ -16,6 +16,7 @@ from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmaddness.so")
+NATIVE_PATH = os.path.join(_HERE, "maddness_binding.so")      # argument marshalling in native code
 
 MADDNESS_OK = 0
 MADDNESS_E_INVAL = -1
@@ -104,8 +105,49 @@ def _check(status: int) -> None:
         raise MaddnessError(status, lib().maddness_last_error().decode())
 
 
-# A call spends its time on the host in this marshalling (an empty call took 7 us of it, the launch 3), so the checks
-# below look at a tensor once, take the module from a global and the stream from torch without the object around it.
+# A call spends its time on the host in this marshalling, so the calls that are made over and over go to binding.cpp first,
+# which takes plain device tensors of the expected types apart in native code (1000 rows of 320 floats, C = 16, M = 128: 8.0 us
+# a call by the code below, 4.8 by that one). What it does not know it leaves to that code: NotImplemented.
+
+class _NotBuilt:
+    """In the place of the native marshalling where it is not built: every call goes through the code below."""
+
+    @staticmethod
+    def encode_scan(*_):
+        return NotImplemented
+
+    encode = scan = build_luts = encode_scan
+
+
+class _NotLoaded:
+    """In the place of the native marshalling until the first call (it needs torch and libmaddness)."""
+
+    def __getattr__(self, name):
+        global _native
+        if not os.path.exists(NATIVE_PATH):
+            _native = _NotBuilt
+        else:
+            import importlib.machinery
+            import importlib.util
+            _torch_module()
+            lib()
+            loader = importlib.machinery.ExtensionFileLoader("maddness_binding", NATIVE_PATH)
+            spec = importlib.util.spec_from_file_location("maddness_binding", NATIVE_PATH, loader=loader)
+            module = importlib.util.module_from_spec(spec)
+            loader.exec_module(module)
+            _native = module
+        return getattr(_native, name)
+
+
+_native = _NotLoaded()
+
+
+def _done(result):
+    """The native call's result; a status it returned instead is raised."""
+    if result.__class__ is int:
+        _check(result)
+    return result
+
 
 def _torch_module():
     global _torch
@@ -178,6 +220,9 @@ class Params:
 
 def maddness_encode(params: Params, A, codes=None, stream=None):
     """g(A): packed 4-bit codes, uint8 [N][(C+1)/2]."""
+    r = _native.encode(0, False, params, A, codes, stream)
+    if r is not NotImplemented:
+        return _done(r)
     torch = _torch or _torch_module()
     N, D, lda = _rows(A, "A")
     if params.D is not None and params.D != D:
@@ -213,6 +258,9 @@ def _typed(A, col_major: bool):
 def maddness_encode_typed(params: Params, A, col_major=False, codes=None, stream=None):
     """g(A) for A of dtype float32 / float16 / bfloat16 / uint8, stored by rows ([N][D]) or,
     with col_major, by columns ([D][N])."""
+    r = _native.encode(2, col_major, params, A, codes, stream)
+    if r is not NotImplemented:
+        return _done(r)
     torch = _torch or _torch_module()
     ptr, dt, layout, N, D, lda = _typed(A, col_major)
     if params.D is not None and params.D != D:
@@ -228,6 +276,9 @@ def maddness_encode_typed(params: Params, A, col_major=False, codes=None, stream
 def maddness_encode_scan_typed(params: Params, A, luts, scale, offset, col_major=False, out=None, acc=None,
                                codes=None, want_out=True, stream=None):
     """Fused g, f and alpha f + beta for A of any supported type and storage order."""
+    r = _native.encode_scan(2, col_major, params, A, luts, scale, offset, out, acc, codes, want_out, stream)
+    if r is not NotImplemented:
+        return _done(r)
     torch = _torch or _torch_module()
     ptr, dt, layout, N, D, lda = _typed(A, col_major)
     M = luts.shape[2]
@@ -254,6 +305,9 @@ def maddness_build_luts_pooled(params: Params, B, luts=None, scale=None, offset=
 def maddness_build_luts(params: Params, B, luts=None, scale=None, offset=None, workspace=None,
                         stream=None, _pooled=False):
     """h(B): uint8 tables [C][16][M] with per-column scale and offset."""
+    r = _native.build_luts(_pooled, params, B, luts, scale, offset, workspace, stream)
+    if r is not NotImplemented:
+        return _done(r)
     torch = _torch or _torch_module()
     D, M, ldb = _rows(B, "B")
     if params.D != D:
@@ -293,7 +347,11 @@ def maddness_build_luts_static(params: Params, B, luts, scale, offset, stream=No
     return luts, scale, offset
 
 
-def _scan(entry, n_codebooks: int, codes, luts, scale, offset, out, acc, want_out, stream):
+def _scan(averaged, n_codebooks: int, codes, luts, scale, offset, out, acc, want_out, stream):
+    r = _native.scan(averaged, n_codebooks, codes, luts, scale, offset, out, acc, want_out, stream)
+    if r is not NotImplemented:
+        return _done(r), acc
+    entry = lib().maddness_scan_averaged if averaged else lib().maddness_scan
     torch = _torch or _torch_module()
     N = codes.shape[0]
     M = luts.shape[2]
@@ -311,17 +369,18 @@ def _scan(entry, n_codebooks: int, codes, luts, scale, offset, out, acc, want_ou
 def maddness_scan(n_codebooks: int, codes, luts, scale, offset, out=None, acc=None, want_out=True,
                   stream=None):
     """f and alpha f + beta from packed codes.  Returns (out, acc); either may be None."""
-    return _scan(lib().maddness_scan, n_codebooks, codes, luts, scale, offset, out, acc, want_out, stream)
+    return _scan(False, n_codebooks, codes, luts, scale, offset, out, acc, want_out, stream)
 
 
 def maddness_scan_averaged(n_codebooks: int, codes, luts, scale, offset, out=None, acc=None,
                            want_out=True, stream=None):
     """As maddness_scan with the pairwise-average aggregation (blocks of 16 codebooks)."""
-    return _scan(lib().maddness_scan_averaged, n_codebooks, codes, luts, scale, offset, out, acc,
+    return _scan(True, n_codebooks, codes, luts, scale, offset, out, acc,
                  want_out, stream)
 
 
-def _encode_scan(entry, params: Params, A, luts, scale, offset, out, acc, codes, want_out, stream):
+def _encode_scan(averaged, params: Params, A, luts, scale, offset, out, acc, codes, want_out, stream):
+    entry = lib().maddness_encode_scan_averaged if averaged else lib().maddness_encode_scan
     torch = _torch or _torch_module()
     N, D, lda = _rows(A, "A")
     M = luts.shape[2]
@@ -342,14 +401,20 @@ def _encode_scan(entry, params: Params, A, luts, scale, offset, out, acc, codes,
 def maddness_encode_scan(params: Params, A, luts, scale, offset, out=None, acc=None, codes=None,
                          want_out=True, stream=None):
     """Fused g, f and alpha f + beta.  Returns out (or None when want_out is False)."""
-    return _encode_scan(lib().maddness_encode_scan, params, A, luts, scale, offset, out, acc, codes,
+    r = _native.encode_scan(0, False, params, A, luts, scale, offset, out, acc, codes, want_out, stream)
+    if r is not NotImplemented:
+        return _done(r)
+    return _encode_scan(False, params, A, luts, scale, offset, out, acc, codes,
                         want_out, stream)
 
 
 def maddness_encode_scan_averaged(params: Params, A, luts, scale, offset, out=None, acc=None, codes=None,
                                   want_out=True, stream=None):
     """As maddness_encode_scan with the pairwise-average aggregation (blocks of 16 codebooks)."""
-    return _encode_scan(lib().maddness_encode_scan_averaged, params, A, luts, scale, offset, out, acc,
+    r = _native.encode_scan(1, False, params, A, luts, scale, offset, out, acc, codes, want_out, stream)
+    if r is not NotImplemented:
+        return _done(r)
+    return _encode_scan(True, params, A, luts, scale, offset, out, acc,
                         codes, want_out, stream)
 
 

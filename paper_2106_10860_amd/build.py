@@ -16,6 +16,9 @@ CALIB_LIB = os.path.join(HERE, "libmaddness_calib.so")
 CALIB_SOURCE = os.path.join("calib", "stream_copy.hip")
 SOURCES = ["api.hip", "encode_scan.hip", "fused_rows.hip", "encode_cols.hip", "mfma_scan.hip", "fused_mfma.hip", "fused_blocks.hip", "build_luts.hip",
            "learn.hip"]
+# the Python calls' argument marshalling: host code against torch's headers, a library of its own
+BINDING_LIB = os.path.join(HERE, "maddness_binding.so")
+BINDING_SOURCE = "binding.cpp"
 # the learner's sums must round as written (a * b + c stays two operations): its split decisions are
 # compared bit for bit with a CPU statement of the same algorithms
 FILE_FLAGS = {"learn.hip": ["-ffp-contract=off"]}
@@ -30,6 +33,19 @@ FLAGS = [
     "-Wno-inline-asm",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
+
+
+def binding_command():
+    import sysconfig
+
+    import torch
+    at = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(at, "include"),
+            "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, BINDING_SOURCE), "-o", BINDING_LIB, "-L", HERE, "-l:libmaddness.so", "-Wl,-rpath,$ORIGIN",
+            "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
 def build(verbose: bool = False, extra_flags=(), out: str = LIB, jobs: int = 0) -> str:
@@ -56,6 +72,10 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB, jobs: int = 0) 
             if verbose:
                 print(" ".join(calib), flush=True)
             subprocess.check_call(calib)
+            binding = binding_command()
+            if verbose:
+                print(" ".join(binding), flush=True)
+            subprocess.check_call(binding)
     return out
 
 
