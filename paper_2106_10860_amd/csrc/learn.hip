@@ -62,6 +62,9 @@ struct LearnArgs {
     int32_t *range_part;  // [C][kRangeParts][2] what a part of the codebook's values span, see any_order()
     int32_t *range;       // [C][2] and what all of them do
     int32_t row_bits;     // N <= 2^row_bits
+    uint32_t *varying_part;  // [C][kRangeParts][pitch] the bits in which a part of a column's values differ from its first, see varying_bits()
+    uint32_t *varying;    // [C][pitch] and in which any of them do
+    int32_t gather_parts; // parts of both that there are
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
     int32_t *n_cand;      // [C]
@@ -139,6 +142,13 @@ __device__ __forceinline__ void span_of(float x, int &top, int &least)
     least = max(least, kLeast - (e + __ffs((int)m) - 1));
 }
 
+// A value as a whole number that compares as the values do (-0 counts as 0, and what is not a number is beyond the infinities).
+__device__ __forceinline__ uint32_t ordered_bits(float x)
+{
+    const uint32_t bits = __float_as_uint(x + 0.0f);
+    return (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
+}
+
 // The columns of every codebook side by side, each row on a 32-byte (or 64-byte) boundary.  The levels read the rows of a
 // bucket in many orders, a codebook's columns at a time: from here they take whole 16-byte pieces, and the rows of a
 // codebook fit in an XCD's L2 where A does not.  A 16-byte piece to a thread and turn.
@@ -147,6 +157,16 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
     const int c = blockIdx.y, pieces = a.pitch / 4, lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
     float4 *X = reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch);
     int top = 0, least = 0;
+    // In which bits the columns' values differ from those of the first row: where a thread has the same columns in all turns (8,
+    // 16, 32, 64 or 128 of them), else any.
+    uint32_t first[4], varying[4] = {};
+    const bool same_columns = 256 % pieces == 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int col = 4 * (int)(threadIdx.x % pieces) + e;
+        first[e] = ordered_bits(col < d ? a.A[lo + col] : 0.0f);
+        if (!same_columns) varying[e] = ~0u;
+    }
     // (four turns' loads ahead of their stores: there are no more workgroups than parts of a range.  2^20 x 128, one codebook:
     // 550 us one by one)
     constexpr int kAhead = 4;
@@ -165,7 +185,10 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
             if (i0 + u * stride < n) {
                 X[i0 + u * stride] = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) span_of(v[u][e], top, least);
+                for (int e = 0; e < 4; ++e) {
+                    span_of(v[u][e], top, least);
+                    if (i0 + u * stride < a.N * pieces) varying[e] |= ordered_bits(v[u][e]) ^ first[e];
+                }
             }
     }
 #pragma unroll
@@ -175,11 +198,19 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
     }
     // (one maximum for all, by atomics, took up to 320 us)
     __shared__ int32_t part[4][2];
+    __shared__ uint32_t differ[256][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) differ[threadIdx.x][e] = varying[e];
     if ((threadIdx.x & 63) == 0) {
         part[threadIdx.x >> 6][0] = top;
         part[threadIdx.x >> 6][1] = least;
     }
     __syncthreads();
+    if ((int)threadIdx.x < a.pitch) {
+        uint32_t any = 0;
+        for (int t = threadIdx.x / 4; t < 256; t += pieces) any |= differ[t][threadIdx.x & 3];
+        a.varying_part[((size_t)c * kRangeParts + blockIdx.x) * a.pitch + threadIdx.x] = any;
+    }
     if (threadIdx.x < 2)
         a.range_part[((size_t)c * kRangeParts + blockIdx.x) * 2 + threadIdx.x] =
             max(max(part[0][threadIdx.x], part[1][threadIdx.x]), max(part[2][threadIdx.x], part[3][threadIdx.x]));
@@ -214,6 +245,15 @@ __global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int 
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off));
         if (lane == 0) a.range[2 * c + wave] = most;
+    }
+    if (level == 0 && chunk == 0) {
+        for (int col = wave; col < a.pitch; col += 4) {
+            uint32_t any = 0;
+            for (int i = lane; i < a.gather_parts; i += 64) any |= a.varying_part[((size_t)c * kRangeParts + i) * a.pitch + col];
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) any |= __shfl_xor(any, off);
+            if (lane == 0) a.varying[(size_t)c * a.pitch + col] = any;
+        }
     }
     __syncthreads();
     if (tid < n_chunks)
@@ -289,6 +329,22 @@ __device__ __forceinline__ void add_16_in_order(double &acc, double term, double
         : "+v"(acc)
         : "v"(term), "v"(one));
 }
+#undef MADDNESS_ADD_TERM
+
+#define MADDNESS_ADD_TERM(t, k) "v_fmac_f64_dpp %0, " t ", %5 row_newbcast:" #k " row_mask:0xf bank_mask:0xf\n\t"
+#define MADDNESS_ADD_TERMS(t)                                                                                              \
+    MADDNESS_ADD_TERM(t, 0) MADDNESS_ADD_TERM(t, 1) MADDNESS_ADD_TERM(t, 2) MADDNESS_ADD_TERM(t, 3) MADDNESS_ADD_TERM(t, 4)  \
+    MADDNESS_ADD_TERM(t, 5) MADDNESS_ADD_TERM(t, 6) MADDNESS_ADD_TERM(t, 7) MADDNESS_ADD_TERM(t, 8) MADDNESS_ADD_TERM(t, 9)  \
+    MADDNESS_ADD_TERM(t, 10) MADDNESS_ADD_TERM(t, 11) MADDNESS_ADD_TERM(t, 12) MADDNESS_ADD_TERM(t, 13)                     \
+    MADDNESS_ADD_TERM(t, 14) MADDNESS_ADD_TERM(t, 15)
+// The same with four terms to a lane, 64 steps at a stretch.
+__device__ __forceinline__ void add_64_in_order(double &acc, const double (&term)[4], double one)
+{
+    asm("s_nop 1\n\t" MADDNESS_ADD_TERMS("%1") MADDNESS_ADD_TERMS("%2") MADDNESS_ADD_TERMS("%3") MADDNESS_ADD_TERMS("%4")
+        : "+v"(acc)
+        : "v"(term[0]), "v"(term[1]), "v"(term[2]), "v"(term[3]), "v"(one));
+}
+#undef MADDNESS_ADD_TERMS
 #undef MADDNESS_ADD_TERM
 
 // The chains' part of a tile: `at` is the lane's first value (its 16th of the column's), term(x, i) the term of value x in
@@ -920,9 +976,7 @@ __device__ __forceinline__ int select_candidate(const LearnArgs &a, int c, int d
 constexpr int kKeyRowBits = 29;
 __device__ __forceinline__ uint64_t make_key(int bucket, float x, uint32_t row)
 {
-    const uint32_t bits = __float_as_uint(x + 0.0f);
-    const uint32_t u = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
-    return ((uint64_t)bucket << (32 + kKeyRowBits)) | ((uint64_t)u << kKeyRowBits) | row;
+    return ((uint64_t)bucket << (32 + kKeyRowBits)) | ((uint64_t)ordered_bits(x) << kKeyRowBits) | row;
 }
 __device__ __forceinline__ float key_value(uint64_t key)
 {
@@ -931,8 +985,11 @@ __device__ __forceinline__ float key_value(uint64_t key)
 }
 __device__ __forceinline__ int32_t key_row(uint64_t key) { return (int32_t)(key & ((1u << kKeyRowBits) - 1u)); }
 
-// The rows of every (codebook, candidate) sorted by their keys, least significant digit first, four digits of nine bits of
-// value and bucket (rows that are equal there stay in row order).  A workgroup takes up to 4096 keys at a time (8192 by sort_round_kernel),
+// The rows of every (codebook, candidate) sorted by their keys, least significant digit first, up to four digits of nine bits of
+// value and bucket (rows that are equal there stay in row order).  Of the value only the bits from the first to the last one in
+// which the column's values differ are looked at (SortDigits): whole numbers, bfloat16 and quantised values have few, and the
+// launches of the digits that a column does not have end at once (a level of 260100 windows of an image, 4 codebooks: 165 -> 104 us;
+// finding the bits out takes 5 to 11 us once).  A workgroup takes up to 4096 keys at a time (8192 by sort_round_kernel),
 // an eighth of them in a row to a wavefront: a key's place among its wavefront's of the same digit comes from nine ballots and a counter in LDS, the
 // place of the wavefronts' from those counters, and the keys go through LDS in the digit's order, so that what is written
 // are runs.  Up to kSortRound rows are sorted by one launch (sort_round_kernel); more take two a digit: sort_count_kernel counts the
@@ -946,10 +1003,31 @@ constexpr int kSortPer = 16, kSortRound = kSortThreads * kSortPer;            //
 constexpr int kChunkPer = 8, kChunkRound = kSortThreads * kChunkPer, kMaxSortChunks = 64;      // of a chunk's round
 static_assert(kSortBins == kSortThreads, "a thread per digit");
 static_assert(kSortDigits * kSortBits >= 32 + 3, "value and bucket");
-__device__ __forceinline__ int key_digit(uint64_t key, int digit)
-{
-    return (int)(key >> (kKeyRowBits + kSortBits * digit)) & (kSortBins - 1);
-}
+// The digits of a column's keys: the `width` bits of the value from bit `low` on, in which its values differ, then the level's
+// bits of the bucket.  Of digit k the lower bits are the value's, from bit `shift` of the key on, and those above them the bucket's.
+struct SortDigits {
+    int low, width, count;
+    int shift, down;
+    uint32_t value, bucket;
+    __device__ SortDigits(uint32_t varying, int n_buckets)
+    {
+        low = varying ? __ffs((int)varying) - 1 : 0;
+        width = varying ? 32 - __clz((int)varying) - low : 0;
+        count = max(1, (width + 31 - __clz(n_buckets) + kSortBits - 1) / kSortBits);
+    }
+    __device__ void select(int k)
+    {
+        const int left = min(max(width - kSortBits * k, 0), kSortBits);         // of the value's bits in it
+        shift = min(kKeyRowBits + low + kSortBits * k, 63);
+        value = (1u << left) - 1u;
+        down = 2 * kSortBits - min(max(width - kSortBits * k + kSortBits, 0), 2 * kSortBits);
+        bucket = left == kSortBits ? 0u : (uint32_t)kSortBins - 1u;
+    }
+    __device__ __forceinline__ int of(uint64_t key) const
+    {
+        return (int)(((uint32_t)(key >> shift) & value) | ((((uint32_t)(key >> (32 + kKeyRowBits)) << kSortBits) >> down) & bucket));
+    }
+};
 // rows of a chunk: even shares of whole rounds, few enough chunks that every workgroup can add up all of their counts
 __host__ __device__ constexpr int64_t sort_chunk_rows(int64_t N)
 {
@@ -1069,12 +1147,14 @@ __global__ __launch_bounds__(kSortThreads, 4) void sort_round_kernel(const Learn
         const int p = min(64 * (wave * per_wave + i) + lane, N - 1);
         key[i] = make_key(node[p], x[(int64_t)p * a.pitch], (uint32_t)p);
     }
-    for (int k = 0; k < kSortDigits; ++k) {
+    SortDigits digits(a.varying[(size_t)c * a.pitch + col], n_buckets);
+    for (int k = 0; k < digits.count; ++k) {
+        digits.select(k);
 #pragma unroll
-        for (int i = 0; i < kSortPer; ++i) digit[i] = 64 * (wave * per_wave + i) + lane < N ? key_digit(key[i], k) : kSortBins - 1;
+        for (int i = 0; i < kSortPer; ++i) digit[i] = 64 * (wave * per_wave + i) + lane < N ? digits.of(key[i]) : kSortBins - 1;
         uint32_t place;
         sort_round(s, key, digit, per_wave, &place);
-        if (k + 1 < kSortDigits)
+        if (k + 1 < digits.count)
 #pragma unroll
             for (int i = 0; i < kSortPer; ++i)
                 if (i < per_wave) key[i] = s.keys[64 * (wave * per_wave + i) + lane];
@@ -1107,10 +1187,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_few_kernel(const LearnArgs 
     if (tid < N) a.keys[((size_t)c * kCand + q) * a.N + before] = mine;
 }
 
-// the keys as digit k finds them
-__device__ __forceinline__ const uint64_t *sort_source(const LearnArgs &a, int c, int q, int k)
+// the keys as digit k of `count` finds them: after the last one they are in `keys`
+__device__ __forceinline__ const uint64_t *sort_source(const LearnArgs &a, int c, int q, int k, int count)
 {
-    return (k % 2 ? a.keys2 : a.keys) + ((size_t)c * kCand + q) * a.N;
+    return ((count - k) % 2 ? a.keys2 : a.keys) + ((size_t)c * kCand + q) * a.N;
 }
 
 __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const LearnArgs a, int k, int n_buckets)
@@ -1122,10 +1202,13 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const LearnArg
     if (q >= min(kCand, d)) return;
     counts[tid] = 0;
     const int64_t chunk_rows = sort_chunk_rows(a.N), first = chunk * chunk_rows, end = min(a.N, first + chunk_rows);
-    uint64_t *keys = const_cast<uint64_t *>(sort_source(a, c, q, k));
-    const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch;
+    const int col = k == 0 ? sort_column(a, c, q, d, n_buckets, chunk == 0, &shared) : a.cand[c * kCand + q];
+    SortDigits digits(a.varying[(size_t)c * a.pitch + col], n_buckets);
+    if (k >= digits.count) return;
+    digits.select(k);
+    uint64_t *keys = const_cast<uint64_t *>(sort_source(a, c, q, k, digits.count));
+    const float *x = a.X + (size_t)c * (a.N + 1) * a.pitch + col;
     const uint8_t *node = a.node + (size_t)c * a.N;
-    if (k == 0) x += sort_column(a, c, q, d, n_buckets, chunk == 0, &shared);
     __syncthreads();
     for (int64_t p0 = first; p0 < end; p0 += kChunkRound) {
         int digit[kChunkPer];
@@ -1135,7 +1218,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const LearnArg
             // (the first digit's keys are made here)
             const uint64_t key = k == 0 ? make_key(node[p], x[p * a.pitch], (uint32_t)p) : keys[p];
             if (k == 0) keys[p] = key;
-            digit[i] = key_digit(key, k);
+            digit[i] = digits.of(key);
         }
 #pragma unroll
         for (int i = 0; i < kChunkPer; ++i) {
@@ -1158,15 +1241,18 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const LearnArg
     a.digit_counts[(((size_t)c * kCand + q) * kMaxSortChunks + chunk) * kSortBins + tid] = counts[tid];
 }
 
-__global__ __launch_bounds__(kSortThreads, 4) void sort_scatter_kernel(const LearnArgs a, int k)
+__global__ __launch_bounds__(kSortThreads, 4) void sort_scatter_kernel(const LearnArgs a, int k, int n_buckets)
 {
     __shared__ SortLds<kChunkPer> s;
     const int c = blockIdx.x % a.C, chunk = blockIdx.x / a.C, n_chunks = gridDim.x / a.C, q = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (q >= a.n_cand[c]) return;
     const int64_t chunk_rows = sort_chunk_rows(a.N), first = chunk * chunk_rows, end = min(a.N, first + chunk_rows);
-    const uint64_t *keys = sort_source(a, c, q, k);
-    uint64_t *out = const_cast<uint64_t *>(sort_source(a, c, q, k + 1));
+    SortDigits digits(a.varying[(size_t)c * a.pitch + a.cand[c * kCand + q]], n_buckets);
+    if (k >= digits.count) return;
+    digits.select(k);
+    const uint64_t *keys = sort_source(a, c, q, k, digits.count);
+    uint64_t *out = const_cast<uint64_t *>(sort_source(a, c, q, k + 1, digits.count));
     // where the digit threadIdx.x of this chunk goes
     const uint32_t *counts = a.digit_counts + ((size_t)c * kCand + q) * kMaxSortChunks * kSortBins + tid;
     uint32_t all = 0, before = 0;
@@ -1184,7 +1270,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void sort_scatter_kernel(const Lea
 #pragma unroll
         for (int i = 0; i < kChunkPer; ++i) key[i] = keys[min(p0 + 64 * (wave * per_wave + i) + lane, end - 1)];
 #pragma unroll
-        for (int i = 0; i < kChunkPer; ++i) digit[i] = p0 + 64 * (wave * per_wave + i) + lane < end ? key_digit(key[i], k) : kSortBins - 1;
+        for (int i = 0; i < kChunkPer; ++i) digit[i] = p0 + 64 * (wave * per_wave + i) + lane < end ? digits.of(key[i]) : kSortBins - 1;
         uint32_t place;
         const uint32_t here = sort_round(s, key, digit, per_wave, &place);
         s.to[tid] = (int32_t)(at - place);
@@ -1193,7 +1279,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void sort_scatter_kernel(const Lea
         const int n = (int)min((int64_t)kSortThreads * per_wave, end - p0);
         for (int i = tid; i < n; i += kSortThreads) {
             const uint64_t v = s.keys[i];
-            out[s.to[key_digit(v, k)] + i] = v;
+            out[s.to[digits.of(v)] + i] = v;
         }
         __syncthreads();
     }
@@ -2224,29 +2310,62 @@ __global__ __launch_bounds__(256) void gta_kernel(const ProtoArgs a, int64_t fir
     if (col < a.D) *out = sum;
 }
 
+template <int K>
+__device__ __forceinline__ double row_broadcast(double x)
+{
+    const int64_t bits = __builtin_bit_cast(int64_t, x);
+    const int low = __builtin_amdgcn_update_dpp(0, (int)bits, 0x150 + K, 0xf, 0xf, true);
+    const int high = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), 0x150 + K, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (int64_t)high << 32 | (uint32_t)low);
+}
+
 // Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
 // every sum over k ascending.  M is symmetric, and entry (i, j), i >= j, is kept at M[j][i] (a column side by side).
 // One launch per panel of 16 columns J0 .. J0 + 15, which takes the panel's terms off everything to its right: a
-// workgroup per 64 x 64 tile of what is left, which works out the panel's rows of L that it needs for itself (the 16 of
-// the diagonal block, those of its rows and those of its columns) and then subtracts their 16 products from its
-// entries, k ascending as panels and columns go.  The tiles of the first column store L, by rows; what they read stays
-// as it is.  Bound by the chain of 16 roots and divisions per panel, 12 us a launch.  (Subtracting all columns
+// workgroup per 64 x 64 tile of what is left, which works out the panel's rows of L that it needs for itself and then subtracts
+// their 16 products from its entries, k ascending as panels and columns go.  A wavefront does its 64 rows of the tile, or of the
+// tile's columns, beside the 16 of the diagonal block, of which every row of 16 lanes has one to a lane: what a column
+// needs of another row comes by row broadcasts, without barriers.  The tiles of the first column store L; what they read
+// stays as it is.  Bound by the chain of 16 roots and divisions per panel, 10.1 us (12.2 with the panel's rows
+// in LDS and two barriers to a column).  (Subtracting all columns
 // before the panel at once, when the panel's turn comes, takes few workgroups and up to 31 us a launch: 0.65 against
 // 0.38 ms for Q = 512.)
+// f(0), f(1) .. f(15), the numbers known at compile time (a row broadcast's lane is part of the instruction).
+template <typename F>
+__device__ __forceinline__ void for_16(F f)
+{
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+    f(std::integral_constant<int, 4>{});
+    f(std::integral_constant<int, 5>{});
+    f(std::integral_constant<int, 6>{});
+    f(std::integral_constant<int, 7>{});
+    f(std::integral_constant<int, 8>{});
+    f(std::integral_constant<int, 9>{});
+    f(std::integral_constant<int, 10>{});
+    f(std::integral_constant<int, 11>{});
+    f(std::integral_constant<int, 12>{});
+    f(std::integral_constant<int, 13>{});
+    f(std::integral_constant<int, 14>{});
+    f(std::integral_constant<int, 15>{});
+}
+
+// L is kept in tiles of 16 x 16, as the substitution reads them: of two columns at a time the 16 rows side by side.
+__device__ __forceinline__ size_t factor_at(int Q, int r, int k)
+{
+    return ((size_t)(r >> 4) * (Q >> 4) + (k >> 4)) * 256 + ((k >> 1) & 7) * 32 + (r & 15) * 2 + (k & 1);
+}
+
 constexpr int kCholPanel = 16, kCholTile = 64, kCholPitch = kCholPanel + 1;
 __global__ __launch_bounds__(256) void cholesky_panel_kernel(const ProtoArgs a, int J0)
 {
-    __shared__ double T[kCholPanel + 2 * kCholTile][kCholPitch];     // rows of L: the panel's, the tile's rows, its columns
+    __shared__ double T[2 * kCholTile][kCholPitch];                  // the panel's columns of L: the tile's rows, its columns
     if (blockIdx.y > blockIdx.x) return;                             // (the other triangle)
-    const int Q = a.Q, tid = threadIdx.x;
+    const int Q = a.Q, tid = threadIdx.x, l = tid & 15;
     double *M = a.M;
     const int row0 = J0 + kCholPanel + blockIdx.x * kCholTile, col0 = J0 + kCholPanel + blockIdx.y * kCholTile;
-    const int own = tid < kCholPanel + 2 * kCholTile ? tid : 0;
-    const int grow = own < kCholPanel ? J0 + own : own < kCholPanel + kCholTile ? row0 + own - kCholPanel
-                                                                                : col0 + own - kCholPanel - kCholTile;
-    double t[kCholPanel];
-#pragma unroll
-    for (int j = 0; j < kCholPanel; ++j) t[j] = grow < Q && grow >= J0 + j ? M[(size_t)(J0 + j) * Q + grow] : 0.0;
     // a tile's entries: four rows of four columns to a thread
     const int tr = 4 * (tid & 15), tc = 4 * (tid >> 4);
     double s[4][4];
@@ -2257,34 +2376,50 @@ __global__ __launch_bounds__(256) void cholesky_panel_kernel(const ProtoArgs a, 
             const int r = row0 + tr + f, c = col0 + tc + e;
             s[e][f] = r < Q && c <= r ? M[(size_t)c * Q + r] : 0.0;
         }
+    if (tid < 2 * kCholTile) {
+        const int grow = tid < kCholTile ? row0 + tid : col0 + tid - kCholTile;
+        double diagonal[kCholPanel], t[kCholPanel];
 #pragma unroll
-    for (int j = 0; j < kCholPanel; ++j) {
-        if (tid == j) {
-            t[j] = sqrt(t[j]);
-            T[j][j] = t[j];
+        for (int j = 0; j < kCholPanel; ++j) {
+            diagonal[j] = l >= j ? M[(size_t)(J0 + j) * Q + J0 + l] : 0.0;
+            t[j] = grow < Q ? M[(size_t)(J0 + j) * Q + grow] : 0.0;
         }
-        __syncthreads();
-        if (tid != j) t[j] = t[j] / T[j][j];
-        if (tid > j && tid < kCholPanel) T[tid][j] = t[j];
-        __syncthreads();
-#pragma unroll
-        for (int j2 = j + 1; j2 < kCholPanel; ++j2) t[j2] -= t[j] * T[j2][j];
-    }
-    if (tid >= kCholPanel && tid < kCholPanel + 2 * kCholTile)
+        auto column = [&](auto index) __attribute__((always_inline)) {
+            constexpr int j = decltype(index)::value;
+            const double root = sqrt(row_broadcast<j>(diagonal[j]));
+            diagonal[j] = l == j ? root : diagonal[j] / root;
+            t[j] = t[j] / root;
+            auto off = [&](auto index2) __attribute__((always_inline)) {
+                constexpr int j2 = decltype(index2)::value;
+                if constexpr (j2 > j) {
+                    const double other = row_broadcast<j2>(diagonal[j]);
+                    diagonal[j2] -= diagonal[j] * other;
+                    t[j2] -= t[j] * other;
+                }
+            };
+            for_16(off);
+        };
+        for_16(column);
 #pragma unroll
         for (int j = 0; j < kCholPanel; ++j) T[tid][j] = t[j];
-    if (blockIdx.y == 0 && tid < kCholPanel + kCholTile && grow < Q && (tid >= kCholPanel || blockIdx.x == 0))
+        if (blockIdx.y == 0 && tid < kCholTile) {
+            if (grow < Q)
 #pragma unroll
-        for (int j = 0; j < kCholPanel; ++j)
-            if (tid >= kCholPanel || j <= tid) a.Lr[(size_t)grow * Q + J0 + j] = t[j];
+                for (int j = 0; j < kCholPanel; ++j) a.Lr[factor_at(Q, grow, J0 + j)] = t[j];
+            if (blockIdx.x == 0 && tid < kCholPanel)
+#pragma unroll
+                for (int j = 0; j < kCholPanel; ++j)
+                    if (j <= l) a.Lr[factor_at(Q, J0 + l, J0 + j)] = diagonal[j];
+        }
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kCholPanel; ++k) {
         double li[4], lj[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            li[e] = T[kCholPanel + tr + e][k];
-            lj[e] = T[kCholPanel + kCholTile + tc + e][k];
+            li[e] = T[tr + e][k];
+            lj[e] = T[kCholTile + tc + e][k];
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -2317,186 +2452,255 @@ __global__ __launch_bounds__(256) void transpose_factor_kernel(const ProtoArgs a
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= QQ) return;
     const int k = (int)(i / a.Q), r = (int)(i - (int64_t)k * a.Q);
-    if (k <= r) a.M[i] = a.Lr[(size_t)r * a.Q + k];
+    if (k <= r) a.M[i] = a.Lr[factor_at(a.Q, r, k)];
 }
 
 // L y = G^T A~ and L^T P = y, sums over k ascending: y_i = (b_i - sum_{k<i} L_ik y_k) / L_ii, then
-// P_i = (y_i - sum_{k>i} L_ki P_k) / L_ii.  A workgroup takes NC columns of A~ and keeps them in LDS for both.
-// Forward, a sum ends with the value found last, so 16 rows at a time are solved (by every wavefront for itself, a row of
-// 16 lanes per column) and their products taken off all rows below, which the wavefronts share out.  Backward, a sum
-// BEGINS with the value found just before, and a column's subtractions are one chain of Q^2 / 2 steps: one wavefront
-// subtracts the products, 16 at a time in the lanes of a row, by row broadcasts (as in add_16_in_order), while the other
-// three form those of the next row, all but the one with the value that is just being found; the factor's rows come
-// kSubDepth ahead.  Bound by that chain, 5.2 cycles a step: 0.64 ms for
-// 512 columns of A~ and Q = 512 (2.24 ms with a lane per column that read its products from LDS).  Four columns to a workgroup where LDS holds them and two
+// P_i = (y_i - sum_{k>i} L_ki P_k) / L_ii.  A workgroup of 8 wavefronts takes NC columns of A~ and keeps them in LDS for both.
+// Forward, a sum ends with the value found last, so 16 rows at a time are solved (a row of 16 lanes per column) and their
+// products taken off all rows below: the first wavefront takes the 16 off the next 16 rows and solves those, while the others
+// take them off the rows after these.  Backward, a sum BEGINS with the value found just before, and a column's subtractions
+// are one chain of Q^2 / 2 steps: the first wavefront subtracts the products, 16 at a time in the lanes of a row, by row
+// broadcasts (as in add_16_in_order), while the others form those of the next row, all but the two with the values that
+// are just being found; the factor's rows come kSubDepth ahead, and a row's first products are on their way from LDS while
+// the value before it is divided.  Bound by that chain, 5.2 cycles a step.
+// 512 columns of A~ and Q = 512: 0.55 ms, 0.07 of it forward (0.64 and 0.19 with L by rows, of which a lane's 16 bytes lay in a line each,
+// all wavefronts solving and divisions of 15 dependent operations); Q = 1024, 640 columns 1.80 (2.21).  With all seven wavefronts
+// laying out the first one shares its turns: 0.67.  Four columns to a workgroup where LDS holds them and two
 // rows' products (up to 104 codebooks), else one.
-constexpr int kSubDepth = 4, kSubHelpers = 192, kSubSpare = 128;
-constexpr size_t substitution_lds_bytes(int Q, int nc) { return sizeof(double) * (3 * (size_t)nc * (Q + 16) + kSubSpare + 4); }
+constexpr int kSubDepth = 4, kSubWaves = 8, kSubHelpers = 192, kSubSpare = 128;
+constexpr size_t substitution_lds_bytes(int Q, int nc) { return sizeof(double) * (3 * (size_t)nc * (Q + 16) + kSubSpare + 8); }
 
-template <int K>
-__device__ __forceinline__ double row_broadcast(double x)
+// a / d, correctly rounded, from r = divisor_reciprocal(d), in 5 dependent operations instead of some 15.  r is the correctly
+// rounded 1 / d; a r is within 2 ulps of the quotient, the first correction brings it within one (faithful), and the second
+// rounds it correctly (Markstein, "Computation of elementary functions on the IBM RISC System/6000 processor", 1990, theorem on
+// the last step of a division).  The theorem wants no underflow in the remainders: quotients and divisors outside
+// 2^-200 .. 2^200 (r is not a number there), infinities and not-a-numbers are divided; a zero is its own quotient.
+__device__ __forceinline__ double divisor_reciprocal(double d)
 {
-    const int64_t bits = __builtin_bit_cast(int64_t, x);
-    const int low = __builtin_amdgcn_update_dpp(0, (int)bits, 0x150 + K, 0xf, 0xf, true);
-    const int high = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), 0x150 + K, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, (int64_t)high << 32 | (uint32_t)low);
+    return fabs(d) > 0x1p-200 && fabs(d) < 0x1p200 ? 1.0 / d : __builtin_nan("");
+}
+
+__device__ __forceinline__ double divide(double a, double d, double r)
+{
+    const double q0 = a * r;
+    const unsigned exponent = ((unsigned)(__builtin_bit_cast(uint64_t, q0) >> 52) & 0x7ffu) - (1023 - 200);
+    if (__builtin_amdgcn_ballot_w64(exponent >= 400u && q0 != 0.0)) return a / d;
+    const double q1 = __builtin_fma(__builtin_fma(-d, q0, a), r, q0);
+    const double q2 = __builtin_fma(__builtin_fma(-d, q1, a), r, q1);
+    return q0 == 0.0 ? q0 : q2;
 }
 
 template <int NC, int kPer>
-__global__ __launch_bounds__(256) void substitution_kernel(const ProtoArgs a)
+__global__ __launch_bounds__(64 * kSubWaves) void substitution_kernel(const ProtoArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double *X = reinterpret_cast<double *>(lds_raw);      // [NC][Q + 16]
-    const int Q = a.Q, D = a.D, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = lane & 15;
+    const int Q = a.Q, D = a.D, tid = threadIdx.x, lane = tid & 63, l = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blocks = Q / 16;
     const int col0 = blockIdx.x * NC;
-    for (int idx = tid; idx < Q * NC; idx += 256) {
+    for (int idx = tid; idx < Q * NC; idx += 64 * kSubWaves) {
         const int i = idx / NC, cc = idx % NC;
         X[cc * (Q + 16) + i] = col0 + cc < D ? a.R[(size_t)i * D + col0 + cc] : 0.0;
     }
     double *x = X + min(lane >> 4, NC - 1) * (Q + 16);      // (NC = 1: the other rows of lanes do the same)
     __syncthreads();
-    // forward
-    for (int J = 0; J < blocks; ++J) {
-        double y[16];
-        {
-            const double *Li = a.Lr + (size_t)(16 * J + l) * Q + 16 * J;
-            double L[16];
+    // 16 x 16 entries of L: row 16 m + l, columns 16 J .. 16 J + 15
+    auto fetch_block = [&](double (&L)[16], int m, int J) __attribute__((always_inline)) {
+        const double2 *src = reinterpret_cast<const double2 *>(a.Lr) + ((size_t)min(m, blocks - 1) * blocks + min(J, blocks - 1)) * 128 + l;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) L[k] = Li[k];
-            const double diagonal = Li[l];
-            double acc = x[16 * J + l];
+        for (int u = 0; u < 8; ++u) {
+            const double2 v = src[16 * u];
+            L[2 * u] = v.x;
+            L[2 * u + 1] = v.y;
+        }
+    };
+    // forward
+    if (wave == 0) {
+        double y[16], below[16];
+        auto solve = [&](int J, const double (&L)[16], double diagonal, double acc) __attribute__((always_inline)) {
+            const double r = divisor_reciprocal(diagonal);
             auto step = [&](auto index) __attribute__((always_inline)) {
                 constexpr int k = decltype(index)::value;
-                const double quotient = acc / diagonal;
+                const double quotient = divide(acc, diagonal, r);
                 y[k] = row_broadcast<k>(quotient);
                 acc = l > k ? acc - L[k] * y[k] : l == k ? quotient : acc;
             };
-            step(std::integral_constant<int, 0>{});
-            step(std::integral_constant<int, 1>{});
-            step(std::integral_constant<int, 2>{});
-            step(std::integral_constant<int, 3>{});
-            step(std::integral_constant<int, 4>{});
-            step(std::integral_constant<int, 5>{});
-            step(std::integral_constant<int, 6>{});
-            step(std::integral_constant<int, 7>{});
-            step(std::integral_constant<int, 8>{});
-            step(std::integral_constant<int, 9>{});
-            step(std::integral_constant<int, 10>{});
-            step(std::integral_constant<int, 11>{});
-            step(std::integral_constant<int, 12>{});
-            step(std::integral_constant<int, 13>{});
-            step(std::integral_constant<int, 14>{});
-            step(std::integral_constant<int, 15>{});
-            __syncthreads();                          // (every wavefront has read the panel's rows)
-            if (wave == 0) x[16 * J + l] = acc;
-        }
-        double2 L0[8], L1[8];
-        auto fetch = [&](double2 (&L)[8], int m) __attribute__((always_inline)) {
-            const double2 *src = reinterpret_cast<const double2 *>(a.Lr + (size_t)(16 * min(m, blocks - 1) + l) * Q + 16 * J);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) L[u] = src[u];
+            for_16(step);
+            x[16 * J + l] = acc;
         };
-        auto take_off = [&](const double2 (&L)[8], int m) __attribute__((always_inline)) {
-            double v = x[16 * m + l];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                v -= L[u].x * y[2 * u];
-                v -= L[u].y * y[2 * u + 1];
-            }
-            x[16 * m + l] = v;
+        auto diagonal_of = [&](int J) __attribute__((always_inline)) {
+            const int i = 16 * min(J, blocks - 1) + l;
+            return a.Lr[factor_at(Q, i, i)];
         };
-        int m = J + 1 + wave;
-        fetch(L0, m);
-        for (; m < blocks; m += 8) {
-            fetch(L1, m + 4);
-            __builtin_amdgcn_sched_barrier(0);
-            take_off(L0, m);
-            if (m + 4 >= blocks) break;
-            fetch(L0, m + 8);
-            __builtin_amdgcn_sched_barrier(0);
-            take_off(L1, m + 4);
-        }
+        double L0[16], L1[16], d0, d1;
+        fetch_block(L0, 0, 0);
+        d0 = diagonal_of(0);
+        fetch_block(below, 1, 0);
+        fetch_block(L1, 1, 1);
+        d1 = diagonal_of(1);
+        __builtin_amdgcn_sched_barrier(0);
+        solve(0, L0, d0, x[l]);
         __syncthreads();
-    }
-    // backward
-    double *products = X + NC * (Q + 16);                          // [2][NC][Q + 16] of row i in products[i & 1]
-    double *ends = products + 2 * NC * (Q + 16) + kSubSpare;       // [2][2] row i's diagonal entry and the one beside it
-    const int ht = tid - 64;
-    double ring[kSubDepth][kPer];
-    // helpers: entries i + ht + kSubHelpers u of row i of L^T
-    auto fetch_row = [&](int i, double (&L)[kPer]) __attribute__((always_inline)) {
+        // rows 16 J .. 16 J + 15, from those above them
+        auto turn = [&](int J, double (&L)[16], double &d, double (&next)[16], double &next_d) __attribute__((always_inline)) {
+            double acc = x[16 * J + l];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int k = i + ht + kSubHelpers * u;
-            if (i >= 0 && k < Q) L[u] = a.M[(size_t)i * Q + k];
+            for (int k = 0; k < 16; ++k) acc -= below[k] * y[k];
+            fetch_block(below, J + 1, J);
+            fetch_block(next, J + 1, J + 1);
+            next_d = diagonal_of(J + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            solve(J, L, d, acc);
+            __syncthreads();
+        };
+        for (int J = 1; J < blocks; J += 2) {
+            turn(J, L1, d1, L0, d0);
+            if (J + 1 < blocks) turn(J + 1, L0, d0, L1, d1);
         }
-    };
-    auto lay_out = [&](int i, const double (&L)[kPer]) __attribute__((always_inline)) {
-        double *dst = products + (i & 1) * NC * (Q + 16);
+    } else {
+        double L0[16], L1[16];
+        fetch_block(L0, 1 + wave, 0);
+        __syncthreads();
+        for (int J = 0; J + 1 < blocks; ++J) {
+            // the values of rows 16 J .. 16 J + 15 off rows 16 (J + 2) and below
+            double y[16];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int k = i + ht + kSubHelpers * u;
-            if (i < 0 || k >= Q) continue;
-            if (u == 0 && ht < 2) {
-                ends[2 * (i & 1) + ht] = L[u];
-                continue;
-            }
+            for (int u = 0; u < 16; ++u) y[u] = x[16 * J + u];
+            auto take_off = [&](const double (&L)[16], int m) __attribute__((always_inline)) {
+                double v = x[16 * m + l];
 #pragma unroll
-            for (int cc = 0; cc < NC; ++cc) dst[cc * (Q + 16) + k] = L[u] * X[cc * (Q + 16) + k];
-        }
-    };
-    if (ht >= 0) {
-#pragma unroll
-        for (int u = 0; u < kSubDepth; ++u) fetch_row(Q - 1 - u, ring[u]);
-        lay_out(Q - 1, ring[0]);
-        fetch_row(Q - 1 - kSubDepth, ring[0]);
-    }
-    __syncthreads();
-    double value = 0.0, minus_one = -1.0;
-    asm("" : "+v"(minus_one));
-    auto solve_row = [&](int i) __attribute__((always_inline)) {
-        const int first = (i + 1) >> 4, k0 = 16 * first + l;
-        const double *row = products + ((i & 1) * NC + min(lane >> 4, NC - 1)) * (Q + 16) + l;
-        const double diagonal = ends[2 * (i & 1)], beside = ends[2 * (i & 1) + 1];
-        double acc = x[i];
-        if (first < blocks) {
-            double p[4], p2[4];
-            const double t = row[16 * first];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) p[u] = row[16 * (first + 1 + u)];        // (past the last block: read, not used)
-            add_16_in_order(acc, k0 > i + 1 ? t : k0 == i + 1 ? beside * value : 0.0, minus_one);
-            int m = first + 1;
-            for (; m + 4 <= blocks; m += 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) p2[u] = row[16 * (m + 4 + u)];
+                for (int k = 0; k < 16; ++k) v -= L[k] * y[k];
+                x[16 * m + l] = v;
+            };
+            int m = J + 1 + wave;
+            for (; m < blocks; m += 2 * (kSubWaves - 1)) {
+                fetch_block(L1, m + kSubWaves - 1, J);
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) add_16_in_order(acc, p[u], minus_one);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) p[u] = p2[u];
+                take_off(L0, m);
+                if (m + kSubWaves - 1 >= blocks) break;
+                fetch_block(L0, m + 2 * (kSubWaves - 1), J);
+                __builtin_amdgcn_sched_barrier(0);
+                take_off(L1, m + kSubWaves - 1);
             }
-            if (m < blocks) add_16_in_order(acc, p[0], minus_one);
-            if (m + 1 < blocks) add_16_in_order(acc, p[1], minus_one);
-            if (m + 2 < blocks) add_16_in_order(acc, p[2], minus_one);
-        }
-        value = acc / diagonal;
-        if (l == 0) x[i] = value;
-    };
-    for (int i0 = Q - 1; i0 >= 0; i0 -= kSubDepth) {            // (Q is a multiple of kSubDepth)
-#pragma unroll
-        for (int u = 0; u < kSubDepth; ++u) {
-            const int i = i0 - u;
-            if (ht < 0) {
-                solve_row(i);
-            } else {
-                lay_out(i - 1, ring[(u + 1) % kSubDepth]);
-                fetch_row(i - 1 - kSubDepth, ring[(u + 1) % kSubDepth]);
-            }
+            fetch_block(L0, J + 2 + wave, J + 1);
             __syncthreads();
         }
     }
-    for (int idx = tid; idx < Q * NC; idx += 256) {
+    // backward
+    double *products = X + NC * (Q + 16);                          // [2][NC][Q + 16] of row i in products[i & 1]
+    double *ends = products + 2 * NC * (Q + 16) + kSubSpare;       // [2][4] row i's diagonal entry, the two beside it, 1 / the first
+    const int ht = tid - 64;
+    if (ht >= kSubHelpers) {
+        for (int i = Q; i >= 0; --i) __syncthreads();               // (beside the first wavefront they would take its turns)
+    } else if (ht >= 0) {
+        double ring[kSubDepth][kPer];
+        // entries i + ht + kSubHelpers u of row i of L^T
+        auto fetch_row = [&](int i, double (&L)[kPer]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) L[u] = a.M[(size_t)max(i, 0) * Q + min(max(i, 0) + ht + kSubHelpers * u, Q - 1)];
+        };
+        auto lay_out = [&](int i, const double (&L)[kPer]) __attribute__((always_inline)) {
+            double *dst = products + (i & 1) * NC * (Q + 16);
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int k = i + ht + kSubHelpers * u;
+                if (i < 0 || k >= Q) continue;
+                if (u == 0 && ht < 3) {
+                    ends[4 * (i & 1) + ht] = L[u];
+                    if (ht == 0) ends[4 * (i & 1) + 3] = divisor_reciprocal(L[u]);
+                    continue;
+                }
+#pragma unroll
+                for (int cc = 0; cc < NC; ++cc) dst[cc * (Q + 16) + k] = L[u] * X[cc * (Q + 16) + k];
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < kSubDepth; ++u) fetch_row(Q - 1 - u, ring[u]);
+        // (the first two rows have no products but those beside the diagonal)
+        lay_out(Q - 1, ring[0]);
+        fetch_row(Q - 1 - kSubDepth, ring[0]);
+        lay_out(Q - 2, ring[1]);
+        fetch_row(Q - 2 - kSubDepth, ring[1]);
+        __syncthreads();
+        for (int i0 = Q - 1; i0 >= 0; i0 -= kSubDepth) {            // (Q is a multiple of kSubDepth)
+#pragma unroll
+            for (int u = 0; u < kSubDepth; ++u) {
+                const int i = i0 - u;
+                __syncthreads();                                    // (row i's subtractions are done, row i + 1 is found)
+                lay_out(i - 2, ring[(u + 2) % kSubDepth]);
+                fetch_row(i - 2 - kSubDepth, ring[(u + 2) % kSubDepth]);
+            }
+        }
+    } else {
+        double minus_one = -1.0, v1 = 0.0, v2 = 0.0;                // rows i + 1 and i + 2
+        __builtin_amdgcn_s_setprio(3);
+        asm("" : "+v"(minus_one));
+        double start, t, p[4], diagonal, beside1, beside2, reciprocal;
+        auto row_at = [&](int i) __attribute__((always_inline)) {
+            return products + ((i & 1) * NC + min(lane >> 4, NC - 1)) * (Q + 16) + l;
+        };
+        auto ask = [&](int i) __attribute__((always_inline)) {
+            const double *row = row_at(i) + 16 * ((i + 1) >> 4), *end = ends + 4 * (i & 1);
+            start = x[i];
+            diagonal = end[0]; beside1 = end[1]; beside2 = end[2]; reciprocal = end[3];
+            t = row[0];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) p[u] = row[16 * (1 + u)];        // (past the last block: read, not used)
+        };
+        __syncthreads();
+        ask(Q - 1);
+        for (int i = Q - 1; i >= 0; --i) {
+            const int first = (i + 1) >> 4, k0 = 16 * first + l;
+            const double *row = row_at(i);
+            double acc = start;
+            if (first < blocks) {
+                const double product1 = beside1 * v1, product2 = beside2 * v2;
+                t = k0 > i + 2 ? t : k0 == i + 1 ? product1 : k0 == i + 2 ? product2 : 0.0;
+                p[0] = k0 + 16 == i + 2 ? product2 : p[0];
+                add_16_in_order(acc, t, minus_one);
+                // (two sets of products in turn, not moved: a move would cost as much as a step)
+                double q[4];
+                int m = first + 1;
+                auto next = [&](double (&set)[4], int from) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) set[u] = row[16 * (from + u)];
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                auto rest = [&](const double (&set)[4]) __attribute__((always_inline)) {
+                    if (m < blocks) add_16_in_order(acc, set[0], minus_one);
+                    if (m + 1 < blocks) add_16_in_order(acc, set[1], minus_one);
+                    if (m + 2 < blocks) add_16_in_order(acc, set[2], minus_one);
+                };
+                while (true) {
+                    if (m + 4 > blocks) {
+                        rest(p);
+                        break;
+                    }
+                    next(q, m + 4);
+                    add_64_in_order(acc, p, minus_one);
+                    m += 4;
+                    if (m + 4 > blocks) {
+                        rest(q);
+                        break;
+                    }
+                    next(p, m + 4);
+                    add_64_in_order(acc, q, minus_one);
+                    m += 4;
+                }
+            }
+            __syncthreads();                                        // (row i - 1 is laid out)
+            const double d = diagonal, r = reciprocal;
+            if (i > 0) ask(i - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            v2 = v1;
+            v1 = divide(acc, d, r);
+            if (l == 0) x[i] = v1;
+        }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < Q * NC; idx += 64 * kSubWaves) {
         const int i = idx / NC, cc = idx % NC;
         if (col0 + cc < D) a.P[(size_t)i * D + col0 + cc] = (float)X[cc * (Q + 16) + i];
     }
@@ -2506,7 +2710,7 @@ template <int NC, int kPer>
 int launch_substitution(const ProtoArgs &a, hipStream_t stream)
 {
     if (int rc = allow_full_lds<substitution_kernel<NC, kPer>>(); rc != MADDNESS_OK) return rc;
-    hipLaunchKernelGGL((substitution_kernel<NC, kPer>), dim3((a.D + NC - 1) / NC), dim3(256), substitution_lds_bytes(a.Q, NC), stream, a);
+    hipLaunchKernelGGL((substitution_kernel<NC, kPer>), dim3((a.D + NC - 1) / NC), dim3(64 * kSubWaves), substitution_lds_bytes(a.Q, NC), stream, a);
     return MADDNESS_OK;
 }
 
@@ -2556,6 +2760,8 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.range_part = w.take<int32_t>(2 * C * kRangeParts);
     a.node = w.take<uint8_t>(C * a.N);      // (right behind chunk_count and range_part: all three are cleared together)
     a.range = w.take<int32_t>(2 * C);
+    a.varying_part = w.take<uint32_t>(C * kRangeParts * a.pitch);
+    a.varying = w.take<uint32_t>(C * a.pitch);
     a.col_loss = w.take<double>(C * kSplitBuckets * a.dmax);
     a.bucket_count = w.take<int64_t>(C * kSplitBuckets);
     a.bucket_start = w.take<int32_t>(C * kSplitBuckets);
@@ -2685,7 +2891,8 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
     LAUNCH_OK("launch clear_kernel");
 
     const int64_t pieces = (N + 1) * (a.pitch / 4);
-    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, kRangeParts), C), dim3(256), 0, stream, a);
+    a.gather_parts = (int32_t)std::min<int64_t>((pieces + 255) / 256, kRangeParts);
+    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)a.gather_parts, C), dim3(256), 0, stream, a);
     LAUNCH_OK("launch gather_columns_kernel");
 
     for (int level = 0; level < 4; ++level) {
@@ -2714,7 +2921,7 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
             for (int k = 0; k < kSortDigits; ++k) {
                 hipLaunchKernelGGL(sort_count_kernel, chunks, dim3(kSortThreads), 0, stream, a, k, n_buckets);
                 LAUNCH_OK("launch sort_count_kernel");
-                hipLaunchKernelGGL(sort_scatter_kernel, chunks, dim3(kSortThreads), 0, stream, a, k);
+                hipLaunchKernelGGL(sort_scatter_kernel, chunks, dim3(kSortThreads), 0, stream, a, k, n_buckets);
                 LAUNCH_OK("launch sort_scatter_kernel");
             }
         }
