@@ -304,23 +304,33 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     if (a.overlay) __syncthreads();
     {
         unsigned char *dst = tables + ((p_book << a.tile_shift) + p_tile) * kTileBytes + p_code * 16;
+        const unsigned flip = 0x80808080u;                       // t - 128 as signed bytes
+        if (a.C == 4 * KG && col0 + 16 * tiles <= a.M) {
+            // (all there is to them where every column and codebook exists: N = 3490, D = 1024, M = 512, C = 32 10.6 and 9.7 us)
 #pragma unroll
-        for (int n = 0; n < PIECES; ++n) {
-            if (n < n_pieces) {
-                const int book = p_book + n * book_step;
-                const unsigned at = p_first + (unsigned)n * p_step;
-                if (at > p_last && at < table_bytes) {
-                    // the end of the tables: move the bytes down (what moves in stands for columns that do not exist)
-                    const unsigned over = 8 * (at - p_last);
-                    const uint64_t lo = (uint64_t)piece[n].y << 32 | piece[n].x, hi = (uint64_t)piece[n].w << 32 | piece[n].z;
-                    const uint64_t l = over >= 64 ? hi >> (over - 64) : lo >> over | hi << (64 - over), u = over >= 64 ? 0 : hi >> over;
-                    piece[n] = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)u, (uint32_t)(u >> 32));
+            for (int n = 0; n < PIECES; ++n)
+                if (n < n_pieces && p_book + n * book_step < 4 * KG)
+                    *reinterpret_cast<uint4 *>(dst + n * BLOCKS * kTileBytes) =
+                        make_uint4(piece[n].x ^ flip, piece[n].y ^ flip, piece[n].z ^ flip, piece[n].w ^ flip);
+        } else {
+#pragma unroll
+            for (int n = 0; n < PIECES; ++n) {
+                if (n < n_pieces) {
+                    const int book = p_book + n * book_step;
+                    const unsigned at = p_first + (unsigned)n * p_step;
+                    if (at > p_last && at < table_bytes) {
+                        // the end of the tables: move the bytes down (what moves in stands for columns that do not exist)
+                        const unsigned over = 8 * (at - p_last);
+                        const uint64_t lo = (uint64_t)piece[n].y << 32 | piece[n].x, hi = (uint64_t)piece[n].w << 32 | piece[n].z;
+                        const uint64_t l = over >= 64 ? hi >> (over - 64) : lo >> over | hi << (64 - over), u = over >= 64 ? 0 : hi >> over;
+                        piece[n] = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)u, (uint32_t)(u >> 32));
+                    }
+                    // nothing where there is no codebook
+                    const unsigned keep = book < a.C ? ~0u : 0u;
+                    const uint4 v = make_uint4((piece[n].x ^ flip) & keep, (piece[n].y ^ flip) & keep, (piece[n].z ^ flip) & keep,
+                                               (piece[n].w ^ flip) & keep);
+                    if (book < 4 * KG) *reinterpret_cast<uint4 *>(dst + n * BLOCKS * kTileBytes) = v;
                 }
-                // t - 128 as signed bytes, and nothing where there is no codebook
-                const unsigned flip = 0x80808080u, keep = book < a.C ? ~0u : 0u;
-                const uint4 v = make_uint4((piece[n].x ^ flip) & keep, (piece[n].y ^ flip) & keep, (piece[n].z ^ flip) & keep,
-                                           (piece[n].w ^ flip) & keep);
-                if (book < 4 * KG) *reinterpret_cast<uint4 *>(dst + n * BLOCKS * kTileBytes) = v;
             }
         }
     }
@@ -425,7 +435,10 @@ Plan choose_plan(int64_t N, int64_t pitch, bool whole, int M, int KC)
     int shift = 0;
     while (shift < 3 && (16 << shift) < M) ++shift;
     Plan plan = make_plan(N, pitch, whole, M, KC, shift, false);
-    if (plan.turns == 1) return plan;
+    // One chunk, but of so many rows that two workgroups to a compute unit and several smaller chunks, one's on their way while the
+    // other has its turn, are faster beside small tables (N = 260100, D = 27, M = 2, C = 4 9.9 and 8.2 us; N = 26900, D = 64, M = 767, C = 8,
+    // bfloat16 26.3 and 22.9; N = 44635, D = 120, M = 100, C = 15 12.3 and 11.1; N = 15853, D = 272, M = 100, C = 16, 68 KiB, 7.9 and 8.0).
+    if (plan.turns == 1 && !(KC <= 8 && plan.rows * pitch > 32 * 1024) && !(KC == 16 && plan.rows * pitch > 72 * 1024)) return plan;
     // More than one chunk to a workgroup.  Twice the columns to a workgroup are half the rows, which every block of columns
     // reads and encodes again (N = 2941, D = 384, M = 1000, C = 24: 11.9 and 10.2 us); where one block of columns has them all,
     // two workgroups to a compute unit, one with its rows on their way while the other has its turn (N = 131072, D = 128,
