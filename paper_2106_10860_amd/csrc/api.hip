@@ -266,16 +266,17 @@ static int encode_scan_checked(const maddness_params *params, const void *A, int
     if (N == 0) return MADDNESS_OK;
     if (!general_kernels_only()) {
         hipStream_t st = static_cast<hipStream_t>(stream);
-        const bool by_blocks = !desc.col_major && !averaged && !vector_scan_only();
+        const bool by_blocks = !averaged && !vector_scan_only();
         if (by_blocks) {
-            rc = launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, true, st);
+            rc = desc.col_major ? launch_fused_blocks_cols(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, st)
+                                : launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, true, st);
             if (rc != 1) return rc;
         }
         rc = desc.col_major
                  ? launch_fused_cols(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, averaged, st)
                  : launch_fused_rows(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, averaged, st);
         if (rc != 1) return rc;
-        if (by_blocks) {
+        if (by_blocks && !desc.col_major) {
             rc = launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, false, st);
             if (rc != 1) return rc;
         }

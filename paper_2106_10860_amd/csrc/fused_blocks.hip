@@ -41,7 +41,7 @@ constexpr int kTileBytes = 272;
 struct BlockArgs {
     const uint8_t *luts;
     const unsigned char *A;   // bytes
-    int64_t pitch;            // bytes between rows
+    int64_t pitch;            // bytes between rows (A by columns: between columns)
     int64_t N;
     const int32_t *split_dims;
     const float *thresholds;
@@ -63,7 +63,9 @@ struct BlockArgs {
 constexpr int lanes_per_row(int C) { return C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 16 : C <= 32 ? 32 : 64; }
 
 // KG: groups of four codebooks; NTW: tiles of 16 columns per wavefront; PF: 16-byte pieces of a chunk of rows per thread.
-template <int KG, int NTW, int PF>
+// COLS: A stored by columns.  A chunk is 64 rows, a row to a lane; a wavefront takes every eighth codebook, whose tree is the
+// same for all lanes and whose four columns it reads in runs of 64 values.
+template <int KG, int NTW, int PF, bool COLS = false>
 __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const BlockArgs a)
 {
     constexpr int LPR = lanes_per_row(4 * KG), RPW = 64 / LPR;    // lanes to a row, rows per wavefront while encoding
@@ -71,6 +73,7 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     constexpr int WAVES = kBlockWaves, THREADS = kBlockThreads;
     constexpr int PIECES = (KG * NTW * 8 + WAVES - 1) / WAVES;     // of the tables, per thread, at most
     constexpr int BLOCKS = THREADS / 16;                           // [16][16] blocks of the tables at a time
+    constexpr int BOOKS = COLS ? (4 * KG + WAVES - 1) / WAVES : 1; // codebooks of a wavefront
 
     extern __shared__ __align__(16) unsigned char smem[];
     v4i *one_hot = reinterpret_cast<v4i *>(smem);
@@ -99,8 +102,28 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     const int c = lane & (LPR - 1);
     const bool real = c < a.C;
     Tree tr;
-    load_tree(tr, a.split_dims + 4 * (real ? c : 0), a.thresholds + 16 * (real ? c : 0), a.D);
+    if constexpr (!COLS) load_tree(tr, a.split_dims + 4 * (real ? c : 0), a.thresholds + 16 * (real ? c : 0), a.D);
 
+    // (by columns: the raw values)
+    uint32_t raw[BOOKS][4];
+    auto fetch_columns = [&](int chunk) INLINE_LAMBDA {
+        const int64_t row = (int64_t)chunk * 64 + lane, at = row < a.N ? row : a.N - 1;
+        auto read = [&](auto element) INLINE_LAMBDA {
+            typedef decltype(element) Element;
+#pragma unroll
+            for (int u = 0; u < BOOKS; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int book = min(wave + WAVES * u, a.C - 1), dim = min(max(a.split_dims[4 * book + t], 0), a.D - 1);
+                    raw[u][t] = reinterpret_cast<const Element *>(a.A + dim * a.pitch)[at];
+                }
+        };
+        switch (a.dtype) {
+        case kF32: read(uint32_t{}); break;
+        case kU8: read(uint8_t{}); break;
+        default: read(uint16_t{}); break;
+        }
+    };
     f4 pre[PF];
     int shift = 0, next_shift = 0;      // of the first row in the staged range
     auto fetch_rows = [&](int chunk) INLINE_LAMBDA {
@@ -125,7 +148,8 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         for (int k = 0; k < PF; ++k) reinterpret_cast<f4 *>(stage)[tid + THREADS * k] = pre[k];
     };
     int chunk = row_group;
-    fetch_rows(chunk);
+    if constexpr (COLS) fetch_columns(chunk);
+    else fetch_rows(chunk);
 
     // piece n of a thread: tile tid % tiles (neighbours read neighbouring columns), code (tid / tiles) % 16, codebook
     // tid / (16 tiles) + n BLOCKS / tiles
@@ -220,6 +244,40 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         }
     };
 
+    auto encode_columns = [&]() INLINE_LAMBDA {
+#pragma unroll
+        for (int u = 0; u < BOOKS; ++u) {
+            const int book = wave + WAVES * u;
+            if (book >= 4 * KG) break;
+            Tree tree;
+            const float *th = a.thresholds + 16 * min(book, a.C - 1);
+#pragma unroll
+            for (int k = 0; k < 15; ++k) tree.t[k] = th[k];
+            float x[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                switch (a.dtype) {
+                case kF32: x[t] = __uint_as_float(raw[u][t]); break;
+                case kF16: x[t] = (float)__builtin_bit_cast(_Float16, (uint16_t)raw[u][t]); break;
+                case kBF16: x[t] = __uint_as_float(raw[u][t] << 16); break;
+                default: x[t] = (float)raw[u][t]; break;
+                }
+            }
+            const unsigned code = book < a.C ? hash_regs(tree, x[0], x[1], x[2], x[3]) : 0u;
+            codes_l[lane * LPR + (book & 3) * KGP + (book >> 2)] = (unsigned char)(code << 4);
+        }
+    };
+    // (by columns: the packed codes, from where the wavefronts have left them)
+    auto store_codes = [&](int64_t row0) INLINE_LAMBDA {
+        const int rows = a.N - row0 < 64 ? (int)(a.N - row0) : 64;
+        for (int at = tid; at < rows * Cb; at += THREADS) {
+            const int r = at / Cb, b = at - r * Cb, c0 = 2 * b, c1 = c0 + 1;
+            const unsigned char *mine = codes_l + r * LPR;
+            const unsigned low = mine[(c0 & 3) * KGP + (c0 >> 2)] >> 4, high = c1 < a.C ? mine[(c1 & 3) * KGP + (c1 >> 2)] : 0u;
+            a.codes_out[row0 * Cb + at] = (uint8_t)(low | high);
+        }
+    };
+
     v4i T[NTW][KG];
     const int first_sum = 128 * a.C;
 
@@ -297,9 +355,13 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         }
     };
 
-    write_rows();
-    __syncthreads();
-    encode((int64_t)chunk * a.chunk_rows);
+    if constexpr (COLS) {
+        encode_columns();
+    } else {
+        write_rows();
+        __syncthreads();
+        encode((int64_t)chunk * a.chunk_rows);
+    }
     // ---- tables: registers -> LDS -> the matrix instruction's operands ----
     if (a.overlay) __syncthreads();
     {
@@ -354,7 +416,12 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         const int64_t row0 = (int64_t)chunk * a.chunk_rows;
         const int next = chunk + a.row_groups;
         const bool more = next < a.chunks;
-        if (more) fetch_rows(next);
+        if constexpr (COLS) {
+            if (more) fetch_columns(next);
+            if (a.codes_out && col_block == 0) store_codes(row0);
+        } else {
+            if (more) fetch_rows(next);
+        }
 #pragma unroll 1
         for (int r0 = 16 * share; r0 < a.chunk_rows; r0 += 32 * shares) {
             if (r0 + 16 * shares < a.chunk_rows) scan(row0, r0, std::integral_constant<int, 2>{});
@@ -362,9 +429,14 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         }
         if (!more) break;
         chunk = next;
-        write_rows();
-        __syncthreads();
-        encode((int64_t)chunk * a.chunk_rows);
+        if constexpr (COLS) {
+            __syncthreads();                 // (the codes have been read)
+            encode_columns();
+        } else {
+            write_rows();
+            __syncthreads();
+            encode((int64_t)chunk * a.chunk_rows);
+        }
         __syncthreads();
     }
 }
@@ -392,6 +464,15 @@ int launch_books(const BlockArgs &a, int ntw, int kb, int grid, size_t lds, hipS
     if constexpr (KG <= 8)
         if (ntw == 2) return launch_tiles<KG, 2>(a, kb, grid, lds, stream);
     return launch_tiles<KG, 1>(a, kb, grid, lds, stream);
+}
+
+template <int KG>
+int launch_columns(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
+{
+    if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 1, true>>(); rc != MADDNESS_OK) return rc;
+    note_kernel("fused_mfma_kernel, A by columns, few rows, blocks of columns", __PRETTY_FUNCTION__);
+    hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
+    return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
 }
 
 // How a call is cut up.
@@ -489,6 +570,21 @@ bool blocks_pay(const BlockArgs &a, int KC, bool whole, const Plan &plan, bool o
     return a.M <= 128 && plan.turns <= (a.M <= 32 ? 5 : 2);
 }
 
+// A stored by columns, 16, 32 or 64 codebooks: the kernels that take longer runs of a column and whole rows of results win over
+// several turns, the sooner the wider the results and where these fill their blocks of 64 columns.  There and here, us (turns):
+// C = 64 N = 2048, M = 256, bfloat16 18 and 10 (1); N = 9347, M = 256 18 and 22 (2); N = 26903, M = 128 22 and 25 (2); binary16 N = 100000,
+// M = 100 89 and 64 (7), N = 65536, M = 200 69 and 69 (8), N = 262144, M = 128 129 and 152 (16).  C = 32 N = 100000, M = 100 34 and 26 (4); M = 256
+// N = 10023, bfloat16 20 and 11 (1), N = 54065 26 and 28 (4), N = 100000 38 and 56 (7); binary16 N = 262144, M = 128 55 and 74 (8), bytes
+// N = 131076, M = 64 44 and 27 (5), N = 200000, M = 300 159 and 136 (19), N = 524288 352 and 349 (49).  C = 16 N = 433749, M = 128, bfloat16 115
+// and 97; M = 512, bytes, N = 20000 19 and 13, N = 131072 60 and 98 (16); N = 262144, M = 256 72 and 108 (16).
+bool columns_pay(int C, int M, int dtype, int turns)
+{
+    const bool full = M % 64 == 0;
+    if (C == 64) return turns <= (dtype == MADDNESS_F32 ? 1 : 8);
+    if (C == 32) return turns <= (!full ? 16 : M <= 128 ? 5 : 2);
+    return !full || M < 256 || turns <= 2;
+}
+
 }  // namespace
 
 int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
@@ -543,6 +639,66 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
     case 32: return launch_books<8>(a, ntw, kb, grid, lds, stream);
     case 48: return launch_books<12>(a, ntw, kb, grid, lds, stream);
     default: return launch_books<16>(a, ntw, kb, grid, lds, stream);
+    }
+}
+
+// A stored by columns: 64 rows to a chunk, as many blocks of columns as leave a workgroup for every compute unit.  Taken for
+// numbers of codebooks that the phased kernel does not have, whatever the rows: the general kernel reads the split values a lane
+// for itself and walks large tables tile by tile (us, there and here: N = 554, M = 1000, C = 48, binary16 349 and 9; N = 14231, M = 512,
+// C = 48, binary16 214 and 31; N = 9407, M = 122, C = 24 21 and 7.6; N = 524288, M = 4, C = 48, bfloat16 621 and 172); else by turns
+// (columns_pay).
+int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
+                             const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
+                             uint8_t *codes, hipStream_t stream)
+{
+    const int es = A.elem_bytes(), C = p.C;
+    if (!A.col_major || C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (option(MADDNESS_OPT_PHASED_ROWS) || option(MADDNESS_OPT_MAX_WORKGROUPS) || option(MADDNESS_OPT_COLS_RUN)) return 1;
+    const int KC = kernel_codebooks(C);
+    if (KC == 0) return 1;
+    BlockArgs a{};
+    a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.D = p.D; a.dtype = A.dtype;
+    a.N = N;
+    a.split_dims = p.split_dims; a.thresholds = p.thresholds;
+    a.luts = luts; a.scale = scale; a.offset = offset; a.M = M; a.C = C;
+    a.out = out; a.ldo = ldo; a.acc = acc; a.codes_out = codes;
+    a.chunk_rows = 64;
+    a.chunks = (int)((N + 63) / 64);
+    const DeviceInfo &dev = device_info();
+    const int all_tiles = (M + 15) / 16;
+    int shift = 0;
+    while (shift < 3 && (1 << shift) < all_tiles) ++shift;
+    auto blocks = [&](int sh) { return (all_tiles + (1 << sh) - 1) >> sh; };
+    while (shift > 0 && (int64_t)a.chunks * blocks(shift - 1) <= dev.cus) --shift;
+    const int tiles = 1 << shift;
+    a.tile_shift = shift; a.col_blocks = blocks(shift);
+    const int lpr = lanes_per_row(KC);
+    const size_t table_lds = (size_t)KC * tiles * kTileBytes, code_lds = (size_t)(64 + 16 * (kBlockWaves / tiles)) * lpr;
+    a.rows_at = a.tables_at = 256;
+    a.codes_at = (unsigned)(256 + table_lds);
+    const size_t lds = a.codes_at + code_lds;
+    if (lds > (size_t)dev.lds_per_block) return 1;
+    // (three workgroups to a compute unit where they are small, else two: N = 524288, M = 3, C = 16, binary16 37 and 44 us; N = 178739, M = 128,
+    // C = 32, binary16 50 and 43)
+    const int per_cu = (int)std::min<size_t>(KC <= 16 ? 3 : 2, dev.lds_per_block / lds), wgs = dev.cus * per_cu;
+    int64_t groups = std::max(1, wgs / a.col_blocks);
+    if (groups > 8 && a.col_blocks > 1) groups = groups / 8 * 8;
+    groups = std::min<int64_t>(groups, a.chunks);
+    if (a.col_blocks > 1) groups = (groups + 7) / 8 * 8;
+    a.row_groups = (int)groups;
+    const int grid = a.row_groups * a.col_blocks;
+    if (C == 16 || C == 32 || C == 64) {
+        // (with fewer columns than split values the routes stay those that the tests of the dispatch hold)
+        if (p.D < 4 * C || !columns_pay(C, M, A.dtype, (a.chunks + a.row_groups - 1) / a.row_groups)) return 1;
+    }
+    switch (KC) {
+    case 4: return launch_columns<1>(a, grid, lds, stream);
+    case 8: return launch_columns<2>(a, grid, lds, stream);
+    case 16: return launch_columns<4>(a, grid, lds, stream);
+    case 24: return launch_columns<6>(a, grid, lds, stream);
+    case 32: return launch_columns<8>(a, grid, lds, stream);
+    case 48: return launch_columns<12>(a, grid, lds, stream);
+    default: return launch_columns<16>(a, grid, lds, stream);
     }
 }
 

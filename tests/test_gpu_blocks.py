@@ -85,3 +85,50 @@ def test_blocks_of_rows_and_columns(mad, case):
     assert mad.maddness_last_kernel() == kernel
     torch.cuda.synchronize()
     assert torch.equal(wide[:, :M], out) and bool((wide[:, M:] == -7.0).all())
+
+
+# (N, D, M, C, dtype, elements between columns): less than a run of 64 rows, whole runs, a row more, several runs to a workgroup
+# and workgroups without any; kernel sizes with and without codebooks that do not exist; one to eight tiles of columns
+COLUMNS = [
+    (16, 64, 1, 16, "f32", 0), (63, 300, 130, 64, "f16", 1), (64, 27, 64, 4, "u8", 3), (65, 200, 1000, 48, "f32", 0),
+    (577, 61, 35, 7, "bf16", 0), (1025, 128, 255, 15, "f32", 2), (2049, 256, 512, 32, "u8", 0), (4100, 96, 129, 21, "f16", 5),
+    (9001, 240, 100, 31, "f32", 1), (70001, 72, 20, 8, "u8", 0), (70001, 128, 100, 16, "bf16", 7), (40000, 330, 90, 63, "f32", 0),
+]
+
+
+@pytest.mark.parametrize("case", COLUMNS, ids=lambda c: "N%d_D%d_M%d_C%d_%s_p%d" % c)
+def test_blocks_of_a_stored_by_columns(mad, case):
+    import torch
+    N, D, M, C, dtype, pad = case
+    print("case", case, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D + M, min(N, 2049), D, M, C)
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    values = (dev(A) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind)
+    full = torch.zeros((D, N + pad), dtype=kind, device="cuda")
+    full[:, :N] = values[torch.arange(N, device="cuda") % len(A)].t()
+    A_d = full[:, :N]
+    params = mad.Params(dev(sd), dev(th))
+
+    def run():
+        acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+        codes = torch.zeros((N, (C + 1) // 2), dtype=torch.uint8, device="cuda")
+        out = mad.maddness_encode_scan_typed(params, A_d, dev(luts), dev(scale), dev(offset), col_major=True, acc=acc, codes=codes)
+        return out, acc, codes, mad.maddness_last_kernel()
+
+    out, acc, codes, kernel = run()
+    torch.cuda.synchronize()
+    assert "few rows, blocks of columns" in kernel, kernel
+    if N <= 2049:
+        want_out, want_acc, want_codes = oracle.encode_scan(A_d.float().t().cpu().numpy().copy(), sd, th, luts, scale, offset)
+        assert (codes.cpu().numpy() == want_codes).all()
+        assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+        assert (out.cpu().numpy() == want_out).all()
+    else:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+        try:
+            want_out, want_acc, want_codes, general = run()
+        finally:
+            mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_AUTO)
+        torch.cuda.synchronize()
+        assert general.startswith("scan_kernel"), general
+        assert torch.equal(codes, want_codes) and torch.equal(acc, want_acc) and torch.equal(out, want_out)
