@@ -272,6 +272,10 @@ static int encode_scan_checked(const maddness_params *params, const void *A, int
                                 : launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, true, st);
             if (rc != 1) return rc;
         }
+        if (averaged && !desc.col_major) {
+            rc = launch_averaged_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, st);
+            if (rc != 1) return rc;
+        }
         rc = desc.col_major
                  ? launch_fused_cols(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, averaged, st)
                  : launch_fused_rows(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, averaged, st);

@@ -124,6 +124,11 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
                              const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
                              uint8_t *codes, hipStream_t stream);
 
+// fp32 rows with the aggregation by averages.
+int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
+                           const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
+                           uint8_t *codes, hipStream_t stream);
+
 // Encode only with the first phase of that kernel (row-major fp32 A, up to 64 codebooks, many rows).
 int launch_encode_phased(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes,
                          hipStream_t stream);

@@ -65,7 +65,11 @@ constexpr int lanes_per_row(int C) { return C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 
 // KG: groups of four codebooks; NTW: tiles of 16 columns per wavefront; PF: 16-byte pieces of a chunk of rows per thread.
 // COLS: A stored by columns.  A chunk is 64 rows, a row to a lane; a wavefront takes every eighth codebook, whose tree is the
 // same for all lanes and whose four columns it reads in runs of 64 values.
-template <int KG, int NTW, int PF, bool COLS = false>
+// AVG (rows): the aggregation by pairwise averages in blocks of 16 codebooks (Appendix D), which is no sum and stays on the vector
+// ALUs, with TS = log2 of the tiles of a block of columns.  The tables stay in LDS as they lie in memory, a lane takes four
+// columns of one row, and a code is kept as the distance of its entries from the codebook's first, 16 bits, so that a
+// lookup takes one addition, one read and one average of four bytes.
+template <int KG, int NTW, int PF, bool COLS = false, bool AVG = false, int TS = 0>
 __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const BlockArgs a)
 {
     constexpr int LPR = lanes_per_row(4 * KG), RPW = 64 / LPR;    // lanes to a row, rows per wavefront while encoding
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     float sc[NTW][4], of[NTW][4];
 #pragma unroll
     for (int t = 0; t < NTW; ++t) {
-        col[t] = col0 + 16 * (tile0 + t) + 4 * g;
+        col[t] = AVG ? col0 + 4 * (lane & ((4 << TS) - 1)) : col0 + 16 * (tile0 + t) + 4 * g;
         if (col0 + 16 * tiles <= a.M) {
             __builtin_memcpy(sc[t], a.scale + col[t], 16);
             __builtin_memcpy(of[t], a.offset + col[t], 16);
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
             }
         }
     }
-    mfma::fill_one_hot_table(one_hot, tid);
+    if constexpr (!AVG) mfma::fill_one_hot_table(one_hot, tid);
 
     // ---- encode: the codes of a chunk, times 16, into LDS ----
     const int Cb = (a.C + 1) / 2;
@@ -227,7 +231,11 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
                 if (h == 1 && r0 + WAVES * RPW >= a.chunk_rows) break;
                 unsigned code = hash_regs(tr, x[h][0], x[h][1], x[h][2], x[h][3]);
                 code = real ? code : 0u;
-                if (r[h] < a.chunk_rows) codes_l[r[h] * LPR + (c & 3) * KGP + (c >> 2)] = (unsigned char)(code << 4);
+                if constexpr (AVG) {
+                    if (r[h] < a.chunk_rows) reinterpret_cast<uint16_t *>(codes_l)[r[h] * LPR + c] = (uint16_t)(code << (4 + TS));
+                } else {
+                    if (r[h] < a.chunk_rows) codes_l[r[h] * LPR + (c & 3) * KGP + (c >> 2)] = (unsigned char)(code << 4);
+                }
                 if (a.codes_out && col_block == 0) {
                     // eight codes to a register, the first of eight lanes stores them
                     unsigned q = code | (rows::from_lane_above<1>(code) << 4);
@@ -355,6 +363,59 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         }
     };
 
+    // ---- averages: 64 / (4 << TS) rows at a time ----
+    auto average = [&](int64_t row0) INLINE_LAMBDA {
+        constexpr int LANES = 4 << TS, ROWS = 64 / LANES, BOOK = 256 << TS;
+        const unsigned char *mine = tables + 4 * (lane & (LANES - 1));
+#pragma unroll 1
+        for (int r0 = wave * ROWS; r0 < a.chunk_rows; r0 += WAVES * ROWS) {
+            const int r = r0 + lane / LANES, rr = r < a.chunk_rows ? r : 0;
+            const uint4 *codes = reinterpret_cast<const uint4 *>(codes_l + 2 * rr * LPR);
+            uint32_t even = 0, odd = 0;
+#pragma unroll
+            for (int b = 0; b < KG / 4; ++b) {
+                const uint4 q0 = codes[2 * b], q1 = codes[2 * b + 1];
+                const uint32_t q[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+                uint32_t y[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const uint32_t at = u % 2 ? q[u / 2] >> 16 : q[u / 2] & 0xffffu;
+                    y[u] = *reinterpret_cast<const uint32_t *>(mine + (16 * b + u) * BOOK + at);
+                }
+#pragma unroll
+                for (int span = 1; span < 16; span *= 2)
+#pragma unroll
+                    for (int u = 0; u < 16; u += 2 * span) y[u] = __builtin_amdgcn_lerp(y[u], y[u + span], 0x01010101u);
+                even += y[0] & 0x00FF00FFu;
+                odd += __builtin_amdgcn_perm(y[0], y[0], 0x0c030c01u);
+            }
+            const int64_t row = row0 + r;
+            if (r < a.chunk_rows && row < a.N && col[0] < a.M) {
+                // 16 times the sum of the blocks' averages, less the excess to be expected of them (Theorem D.1)
+                const uint32_t f[4] = {16 * (even & 0xFFFFu), 16 * (odd & 0xFFFFu), 16 * (even >> 16), 16 * (odd >> 16)};
+                if (a.out) {
+                    float *dst = a.out + row * a.ldo + col[0];
+                    f4 v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = fmaf((float)((int)f[q] - a.C), sc[0][q], of[0][q]);
+                    if (col[0] + 3 < a.M) {
+                        __builtin_memcpy(dst, &v, 16);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 3; ++q)
+                            if (col[0] + q < a.M) dst[q] = v[q];
+                    }
+                }
+                if (a.acc) {
+                    uint16_t *dst = a.acc + row * a.M + col[0];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (col[0] + q < a.M) dst[q] = (uint16_t)f[q];
+                }
+            }
+        }
+    };
+
     if constexpr (COLS) {
         encode_columns();
     } else {
@@ -365,14 +426,17 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     // ---- tables: registers -> LDS -> the matrix instruction's operands ----
     if (a.overlay) __syncthreads();
     {
-        unsigned char *dst = tables + ((p_book << a.tile_shift) + p_tile) * kTileBytes + p_code * 16;
-        const unsigned flip = 0x80808080u;                       // t - 128 as signed bytes
+        // (averages: as it lies in memory)
+        constexpr int STEP = AVG ? 256 : kTileBytes;
+        unsigned char *dst = AVG ? tables + ((p_book * 16 + p_code) << (4 + a.tile_shift)) + 16 * p_tile
+                                 : tables + ((p_book << a.tile_shift) + p_tile) * STEP + p_code * 16;
+        const unsigned flip = AVG ? 0u : 0x80808080u;            // t - 128 as signed bytes
         if (a.C == 4 * KG && col0 + 16 * tiles <= a.M) {
             // (all there is to them where every column and codebook exists: N = 3490, D = 1024, M = 512, C = 32 10.6 and 9.7 us)
 #pragma unroll
             for (int n = 0; n < PIECES; ++n)
                 if (n < n_pieces && p_book + n * book_step < 4 * KG)
-                    *reinterpret_cast<uint4 *>(dst + n * BLOCKS * kTileBytes) =
+                    *reinterpret_cast<uint4 *>(dst + n * BLOCKS * STEP) =
                         make_uint4(piece[n].x ^ flip, piece[n].y ^ flip, piece[n].z ^ flip, piece[n].w ^ flip);
         } else {
 #pragma unroll
@@ -391,13 +455,13 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
                     const unsigned keep = book < a.C ? ~0u : 0u;
                     const uint4 v = make_uint4((piece[n].x ^ flip) & keep, (piece[n].y ^ flip) & keep, (piece[n].z ^ flip) & keep,
                                                (piece[n].w ^ flip) & keep);
-                    if (book < 4 * KG) *reinterpret_cast<uint4 *>(dst + n * BLOCKS * kTileBytes) = v;
+                    if (book < 4 * KG) *reinterpret_cast<uint4 *>(dst + n * BLOCKS * STEP) = v;
                 }
             }
         }
     }
     __syncthreads();
-    {
+    if constexpr (!AVG) {
         typedef __attribute__((address_space(3))) v2i lds_v2i;
         const unsigned char *block = tables + ((g << a.tile_shift) + tile0) * kTileBytes + 8 * i;
         const int step = (4 << a.tile_shift) * kTileBytes;
@@ -422,10 +486,14 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         } else {
             if (more) fetch_rows(next);
         }
+        if constexpr (AVG) {
+            average(row0);
+        } else {
 #pragma unroll 1
-        for (int r0 = 16 * share; r0 < a.chunk_rows; r0 += 32 * shares) {
-            if (r0 + 16 * shares < a.chunk_rows) scan(row0, r0, std::integral_constant<int, 2>{});
-            else scan(row0, r0, std::integral_constant<int, 1>{});
+            for (int r0 = 16 * share; r0 < a.chunk_rows; r0 += 32 * shares) {
+                if (r0 + 16 * shares < a.chunk_rows) scan(row0, r0, std::integral_constant<int, 2>{});
+                else scan(row0, r0, std::integral_constant<int, 1>{});
+            }
         }
         if (!more) break;
         chunk = next;
@@ -473,6 +541,29 @@ int launch_columns(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
     note_kernel("fused_mfma_kernel, A by columns, few rows, blocks of columns", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
     return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
+}
+
+template <int KG, int TS>
+int launch_averaged(const BlockArgs &a, int kb, int grid, size_t lds, hipStream_t stream)
+{
+    note_kernel("fused_blocks_kernel, averages", __PRETTY_FUNCTION__);
+    if (kb == 32) {
+        if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 4, false, true, TS>>(); rc != MADDNESS_OK) return rc;
+        hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 4, false, true, TS>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
+    } else {
+        if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 8, false, true, TS>>(); rc != MADDNESS_OK) return rc;
+        hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 8, false, true, TS>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
+    }
+    return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
+}
+
+template <int KG>
+int launch_averaged_tiles(const BlockArgs &a, int kb, int grid, size_t lds, hipStream_t stream)
+{
+    if (a.tile_shift == 1) return launch_averaged<KG, 1>(a, kb, grid, lds, stream);
+    if constexpr (KG <= 8)
+        if (a.tile_shift == 3) return launch_averaged<KG, 3>(a, kb, grid, lds, stream);
+    return launch_averaged<KG, 2>(a, kb, grid, lds, stream);
 }
 
 // How a call is cut up.
@@ -699,6 +790,63 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
     case 32: return launch_columns<8>(a, grid, lds, stream);
     case 48: return launch_columns<12>(a, grid, lds, stream);
     default: return launch_columns<16>(a, grid, lds, stream);
+    }
+}
+
+// The aggregation by averages (fp32 rows, 16, 32, 48 or 64 codebooks): blocks of up to 64 KiB of tables, which stay in LDS.  There
+// (the general kernel, and those for tables in LDS or in tiles of it) and here, us (turns): one turn N = 695, D = 512, M = 1000, C = 32 254
+// and 6.8, N = 1824, D = 1024, M = 128, C = 64 80 and 6.3, N = 4096, D = 512, M = 100, C = 32 7.9 and 6.0; one block of columns N = 128647, D = 256,
+// M = 107, C = 16 85 and 48 (8), N = 390133, D = 1024, M = 45, C = 64 454 and 332 (95); several N = 9845, D = 1024, M = 128, C = 64 81 and 17 (5),
+// N = 119634, D = 128, M = 256, C = 16 66 and 57 (8), N = 129570, D = 256, M = 512, C = 16 139 and 152 (32), N = 172750, D = 512, M = 128, C = 64 120 and
+// 171 (43); C = 32 with tables in LDS for rows_kernel N = 8192, D = 512, M = 256 9.3 and 10.2 (2), N = 50246 31 and 54 (13), N = 524288, M = 128 218
+// and 272 (64), and without N = 62595, M = 1000 292 and 237 (62).
+int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
+                           const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
+                           uint8_t *codes, hipStream_t stream)
+{
+    const int C = p.C;
+    if (!A.plain() || C > 64 || C % 16 != 0 || (int64_t)p.D * 4 > kMaxRowBytes || N < 16 || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    BlockArgs a{};
+    a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * 4; a.row_bytes = p.D * 4; a.D = p.D; a.dtype = A.dtype;
+    a.N = N;
+    a.split_dims = p.split_dims; a.thresholds = p.thresholds;
+    a.luts = luts; a.scale = scale; a.offset = offset; a.M = M; a.C = C;
+    a.out = out; a.ldo = ldo; a.acc = acc; a.codes_out = codes;
+    if (a.pitch > a.row_bytes + a.row_bytes / 8 + 64) return 1;
+    const bool whole = a.pitch % 16 == 0 && aligned_to(A.data, 16);
+    const DeviceInfo &dev = device_info();
+    int shift = 1;
+    while (shift < (C <= 32 ? 3 : 2) && (16 << shift) < M) ++shift;
+    a.tile_shift = shift;
+    a.col_blocks = (M + (16 << shift) - 1) >> (4 + shift);
+    const int64_t tables = (int64_t)256 * C << shift, codes_row = 2 * lanes_per_row(C);
+    int64_t groups = std::max(1, dev.cus / a.col_blocks);
+    if (groups > 8 && a.col_blocks > 1) groups = groups / 8 * 8;
+    const int64_t most = std::min<int64_t>((64 * 1024 - (whole ? 0 : 16)) / a.pitch,
+                                           (dev.lds_per_block - 256 - tables - 64 * 1024) / codes_row);
+    if (most < 1) return 1;
+    const int64_t share = std::max<int64_t>(8, (N + groups - 1) / groups), turns = (share + most - 1) / most;
+    const int64_t rows = (share + turns - 1) / turns;
+    if (N / rows >= (1 << 30)) return 1;
+    const bool held = C == 32 && p.D <= 512 && p.D % 4 == 0 && whole && maddness::rows::tables_ok(C, M, luts, scale, offset, out, ldo, acc);
+    if (turns > 1 && (held || (C != 32 && a.col_blocks > 1 && turns > 16))) return 1;
+    a.chunk_rows = (int)rows;
+    a.chunks = (int)((N + rows - 1) / rows);
+    groups = std::min<int64_t>(groups, a.chunks);
+    if (a.col_blocks > 1) groups = (groups + 7) / 8 * 8;
+    a.row_groups = (int)groups;
+    const int kb = rows * a.pitch + (whole ? 0 : 16) <= 32 * 1024 ? 32 : 64;
+    a.rows_at = 256;
+    a.tables_at = 256 + kb * 1024;
+    a.codes_at = (unsigned)(a.tables_at + tables);
+    const size_t lds = a.codes_at + (size_t)(rows * codes_row);
+    if (lds > (size_t)dev.lds_per_block) return 1;
+    const int grid = a.row_groups * a.col_blocks;
+    switch (C) {
+    case 16: return launch_averaged_tiles<4>(a, kb, grid, lds, stream);
+    case 32: return launch_averaged_tiles<8>(a, kb, grid, lds, stream);
+    case 48: return launch_averaged_tiles<12>(a, kb, grid, lds, stream);
+    default: return launch_averaged_tiles<16>(a, kb, grid, lds, stream);
     }
 }
 

@@ -132,3 +132,52 @@ def test_blocks_of_a_stored_by_columns(mad, case):
         torch.cuda.synchronize()
         assert general.startswith("scan_kernel"), general
         assert torch.equal(codes, want_codes) and torch.equal(acc, want_acc) and torch.equal(out, want_out)
+
+
+# (N, D, M, C, elements between rows, before the first, bytes before the tables): two to eight tiles of columns, the end of the
+# tables, rows on any element, one chunk to a workgroup and several
+AVERAGES = [
+    (16, 64, 1, 16, 0, 0, 0), (33, 100, 31, 64, 0, 1, 3), (700, 512, 100, 32, 0, 0, 0), (300, 64, 1000, 48, 4, 0, 1),
+    (1025, 333, 129, 32, 1, 0, 0), (2048, 1024, 130, 64, 0, 0, 0), (4100, 128, 257, 16, 0, 3, 2), (20001, 256, 60, 32, 0, 0, 0),
+    (9845, 1024, 128, 64, 0, 0, 0), (30000, 64, 300, 16, 0, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", AVERAGES, ids=lambda c: "N%d_D%d_M%d_C%d_p%d_o%d_t%d" % c)
+def test_averages_by_blocks(mad, case):
+    import torch
+    N, D, M, C, pad, before, at = case
+    print("case", case, flush=True)
+    A, sd, th, luts, scale, offset = problem(N + D + M, min(N, 2048), D, M, C)
+    full = torch.full((before + N * (D + pad),), 1.0, device="cuda")
+    A_d = full[before:].view(N, D + pad)[:, :D]
+    A_d.copy_(dev(A)[torch.arange(N, device="cuda") % len(A)])
+    raw = torch.zeros(luts.size + at, dtype=torch.uint8, device="cuda")
+    raw[at:] = dev(luts).reshape(-1)
+    luts_d = raw[at:].reshape(C, 16, M)
+    params = mad.Params(dev(sd), dev(th))
+
+    def run():
+        acc = torch.zeros((N, M), dtype=torch.int16, device="cuda")
+        codes = torch.zeros((N, C // 2), dtype=torch.uint8, device="cuda")
+        out = mad.maddness_encode_scan_averaged(params, A_d, luts_d, dev(scale), dev(offset), acc=acc, codes=codes)
+        return out, acc, codes, mad.maddness_last_kernel()
+
+    out, acc, codes, kernel = run()
+    torch.cuda.synchronize()
+    assert kernel.startswith("fused_blocks_kernel, averages"), kernel
+    if N <= 2048:
+        want_codes = oracle.encode_scan(A_d.cpu().numpy().copy(), sd, th, luts, scale, offset)[2]
+        want_out, want_acc = oracle.scan_averaged(want_codes, C, luts, scale, offset)
+        assert (codes.cpu().numpy() == want_codes).all()
+        assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
+        assert (out.cpu().numpy() == want_out).all()
+    else:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+        try:
+            want_out, want_acc, want_codes, general = run()
+        finally:
+            mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_AUTO)
+        torch.cuda.synchronize()
+        assert general.startswith("scan_kernel"), general
+        assert torch.equal(codes, want_codes) and torch.equal(acc, want_acc) and torch.equal(out, want_out)
