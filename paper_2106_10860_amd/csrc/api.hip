@@ -240,6 +240,8 @@ static int scan_checked(int32_t C, int32_t M, const uint8_t *codes, int64_t N, c
     if (!codes) return fail(MADDNESS_E_INVAL, "codes is NULL");
     if (!general_kernels_only()) {
         if (!averaged && !vector_scan_only()) {
+            rc = launch_scan_blocks(C, M, codes, N, luts, scale, offset, out, ldo, acc, static_cast<hipStream_t>(stream));
+            if (rc != 1) return rc;
             rc = launch_scan_mfma(C, M, codes, N, luts, scale, offset, out, ldo, acc, static_cast<hipStream_t>(stream));
             if (rc != 1) return rc;
         }

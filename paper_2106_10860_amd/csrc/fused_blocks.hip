@@ -1,4 +1,4 @@
-// Fused encode + exact scan of row-major A by blocks of rows and columns, for few and medium numbers of rows.
+// Fused encode + exact scan, and the scan alone, by blocks of rows and columns, for few and medium numbers of rows.
 //
 // A call of a few thousand rows is bound by latencies: a chain of kernel arguments -> trees, tables and rows -> codes ->
 // sums -> stores on a chip that is mostly idle.  So a workgroup (8 wavefronts) takes a block of up to 128 (256) output
@@ -58,7 +58,11 @@ struct BlockArgs {
     int row_groups;           // workgroups that share out the chunks, a multiple of 8 where there is more than one block of columns
     unsigned rows_at, tables_at, codes_at;   // in LDS
     int overlay;              // the tables go where the first rows were
+    int unit;                 // (codes) bytes to an access: 8, 4 or 1
 };
+
+// Units of packed codes that a thread takes of a chunk.
+constexpr int kCodeUnits = 4;
 
 constexpr int lanes_per_row(int C) { return C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 16 : C <= 32 ? 32 : 64; }
 
@@ -69,7 +73,8 @@ constexpr int lanes_per_row(int C) { return C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 
 // ALUs, with TS = log2 of the tiles of a block of columns.  The tables stay in LDS as they lie in memory, a lane takes four
 // columns of one row, and a code is kept as the distance of its entries from the codebook's first, 16 bits, so that a
 // lookup takes one addition, one read and one average of four bytes.
-template <int KG, int NTW, int PF, bool COLS = false, bool AVG = false, int TS = 0>
+// CODES: the scan alone.  A holds packed codes, of which a thread takes up to four units of a chunk and deals them out in LDS.
+template <int KG, int NTW, int PF, bool COLS = false, bool AVG = false, int TS = 0, bool CODES = false>
 __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const BlockArgs a)
 {
     constexpr int LPR = lanes_per_row(4 * KG), RPW = 64 / LPR;    // lanes to a row, rows per wavefront while encoding
@@ -86,7 +91,7 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     asm volatile("" ::"s"(a.luts), "s"(a.A), "s"(a.pitch), "s"(a.N), "s"(a.split_dims), "s"(a.thresholds), "s"(a.scale),
                  "s"(a.offset), "s"(a.out), "s"(a.ldo), "s"(a.acc), "s"(a.codes_out), "s"(a.M), "s"(a.C), "s"(a.D), "s"(a.dtype),
                  "s"(a.row_bytes), "s"(a.tile_shift), "s"(a.col_blocks), "s"(a.chunk_rows), "s"(a.chunks), "s"(a.row_groups),
-                 "s"(a.rows_at), "s"(a.tables_at), "s"(a.codes_at), "s"(a.overlay));
+                 "s"(a.rows_at), "s"(a.tables_at), "s"(a.codes_at), "s"(a.overlay), "s"(a.unit));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4;
@@ -106,7 +111,7 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     const int c = lane & (LPR - 1);
     const bool real = c < a.C;
     Tree tr;
-    if constexpr (!COLS) load_tree(tr, a.split_dims + 4 * (real ? c : 0), a.thresholds + 16 * (real ? c : 0), a.D);
+    if constexpr (!COLS && !CODES) load_tree(tr, a.split_dims + 4 * (real ? c : 0), a.thresholds + 16 * (real ? c : 0), a.D);
 
     // (by columns: the raw values)
     uint32_t raw[BOOKS][4];
@@ -151,8 +156,52 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
 #pragma unroll
         for (int k = 0; k < PF; ++k) reinterpret_cast<f4 *>(stage)[tid + THREADS * k] = pre[k];
     };
+    // (codes: the units of a chunk lie one after another, whatever the rows' bytes)
+    const int Cb = (a.C + 1) / 2;
+    uint2 packed[kCodeUnits];
+    auto fetch_codes = [&](int chunk) INLINE_LAMBDA {
+        const int64_t row0 = (int64_t)chunk * a.chunk_rows;
+        const int n_rows = a.N - row0 < a.chunk_rows ? (int)(a.N - row0) : a.chunk_rows;
+        const unsigned last = (unsigned)(n_rows * Cb - a.unit);
+        const unsigned char *from = a.A + row0 * Cb;
+#pragma unroll
+        for (int k = 0; k < kCodeUnits; ++k) {
+            const unsigned at = min((unsigned)((tid + THREADS * k) * a.unit), last);
+            if (a.unit == 8) __builtin_memcpy(&packed[k], from + at, 8);
+            else if (a.unit == 4) __builtin_memcpy(&packed[k].x, from + at, 4);
+            else packed[k].x = from[at];
+        }
+    };
+    auto deal_codes = [&]() INLINE_LAMBDA {
+        const unsigned per_row = (unsigned)Cb / (unsigned)a.unit;
+#pragma unroll
+        for (int k = 0; k < kCodeUnits; ++k) {
+            const unsigned at = tid + THREADS * k, r = at / per_row, q = at - r * per_row;
+            if ((int)r >= a.chunk_rows) break;
+            unsigned char *mine = codes_l + r * LPR;
+            const unsigned x = packed[k].x, y = packed[k].y;
+            if (a.unit == 8) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    // codebooks 16 q + n, + 4, + 8, + 12, 16 times their codes
+                    const unsigned lo = (n ? x >> (4 * n - 4) : x << 4) & 0x00F000F0u, hi = (n ? y >> (4 * n - 4) : y << 4) & 0x00F000F0u;
+                    *reinterpret_cast<unsigned *>(mine + n * KGP + 4 * q) = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+                }
+            } else if (a.unit == 4) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const unsigned lo = (n ? x >> (4 * n - 4) : x << 4) & 0x00F000F0u;
+                    *reinterpret_cast<uint16_t *>(mine + n * KGP + 2 * q) = (uint16_t)(lo | lo >> 8);
+                }
+            } else {
+                mine[(2 * q & 3) * KGP + q / 2] = (unsigned char)(x << 4);
+                mine[(2 * q + 1 & 3) * KGP + q / 2] = (unsigned char)(x & 0xF0u);
+            }
+        }
+    };
     int chunk = row_group;
     if constexpr (COLS) fetch_columns(chunk);
+    else if constexpr (CODES) fetch_codes(chunk);
     else fetch_rows(chunk);
 
     // piece n of a thread: tile tid % tiles (neighbours read neighbouring columns), code (tid / tiles) % 16, codebook
@@ -199,7 +248,6 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     if constexpr (!AVG) mfma::fill_one_hot_table(one_hot, tid);
 
     // ---- encode: the codes of a chunk, times 16, into LDS ----
-    const int Cb = (a.C + 1) / 2;
     auto encode = [&](int64_t row0) INLINE_LAMBDA {
 #pragma unroll 1
         for (int r0 = wave * RPW; r0 < a.chunk_rows; r0 += 2 * WAVES * RPW) {
@@ -418,6 +466,8 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
 
     if constexpr (COLS) {
         encode_columns();
+    } else if constexpr (CODES) {
+        deal_codes();
     } else {
         write_rows();
         __syncthreads();
@@ -483,6 +533,8 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         if constexpr (COLS) {
             if (more) fetch_columns(next);
             if (a.codes_out && col_block == 0) store_codes(row0);
+        } else if constexpr (CODES) {
+            if (more) fetch_codes(next);
         } else {
             if (more) fetch_rows(next);
         }
@@ -500,6 +552,9 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
         if constexpr (COLS) {
             __syncthreads();                 // (the codes have been read)
             encode_columns();
+        } else if constexpr (CODES) {
+            __syncthreads();
+            deal_codes();
         } else {
             write_rows();
             __syncthreads();
@@ -540,6 +595,15 @@ int launch_columns(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
     if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 1, true>>(); rc != MADDNESS_OK) return rc;
     note_kernel("fused_mfma_kernel, A by columns, few rows, blocks of columns", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
+    return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
+}
+
+template <int KG>
+int launch_codes(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
+{
+    if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 1, false, false, 0, true>>(); rc != MADDNESS_OK) return rc;
+    note_kernel("mfma_scan_kernel, blocks of columns", __PRETTY_FUNCTION__);
+    hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, false, false, 0, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
     return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
 }
 
@@ -659,6 +723,41 @@ bool blocks_pay(const BlockArgs &a, int KC, bool whole, const Plan &plan, bool o
     // 48 and 64: N = 24287, D = 1024, M = 36, C = 64, bfloat16 21 and 17 (2); N = 63790, D = 528, M = 7, C = 48 40 and 33 (5);
     // N = 126493, D = 384, M = 128, C = 48 70 and 75 (6); N = 31831, D = 704, M = 256, C = 64, binary16 24 and 34 (3).
     return a.M <= 128 && plan.turns <= (a.M <= 32 ? 5 : 2);
+}
+
+// The scan alone: whether blocks are faster than what else takes the call.  Times in us, the blocks' last.  `regular`: shapes of which the
+// matrix-core kernel without blocks reads and writes 2 to 16 bytes at a time; of others it goes by single bytes and floats.
+bool scan_blocks_pay(const BlockArgs &a, int64_t ldo, int KC, int64_t turns)
+{
+    const int C = a.C, M = a.M, NT = C <= 32 ? 4 : 2;
+    const int64_t results = a.N * M;
+    const bool regular = C % 8 == 0 && aligned_to(a.A, 16) && M % NT == 0 && aligned_to(a.luts, NT) &&
+                         !(a.out && (ldo % NT != 0 || !aligned_to(a.out, 4 * NT))) && !(a.acc && !aligned_to(a.acc, 2 * NT));
+    if (M <= 16) {
+        // The general kernel, which does no padded work, keeps many rows with next to nothing to add (N = 458095, M = 2, C = 5 7.5 and 9.8;
+        // N = 150549, M = 5, C = 5 6.0 and 6.5; with few rows both take as long as a launch), and those that come by single bytes and
+        // long chunks (N = 506401, M = 2, C = 30 19.1 and 19.7; N = 1033459, M = 3, C = 12 17 and 20; N = 277910, M = 2 15.1 and 14.1).
+        if (C <= 8) return M <= 5 ? a.N <= (1 << 15) : M <= 12 || !regular || results < (3 << 20);
+        if (a.unit == 1 && M <= 3) return turns <= 4;
+        // N = 334, M = 10, C = 8 4.8 and 4.1; N = 1515582, M = 3, C = 48 100 and 37; N = 2339262, M = 16, C = 15 116 and 43; N = 760602, M = 16, C = 32
+        // 25 and 17.  40, 56 and 64 codebooks: N = 90821, M = 10, C = 64 13.1 and 7.3 (2 turns), N = 1231121, M = 8 41 and 51 (10).
+        return C <= 32 || C == 48 || !regular || turns <= (C == 56 ? 1 : 3);
+    }
+    if (!regular) {
+        // N = 117, M = 300, C = 32 7.6 and 4.2; N = 3387, M = 785, C = 24 15.9 and 8.2; N = 656328, M = 20, C = 31 212 and 24; N = 376888,
+        // M = 100, C = 31 128 and 44: whatever the size, but for results that may be written by whole lines (M = 785, C = 24, N = 117350 91 and 131).
+        return results < (12 << 20) || M < 64 || M % 32 == 0 || a.acc || !a.out || ldo != M || !aligned_to(a.out, 128) || a.N < 16384;
+    }
+    // C = 8: N = 512, M = 105 11.4 and 4.1; N = 52771, M = 32 5.3 and 5.1 (1.6 Mi results); N = 109905, M = 36 7.4 and 7.9 (3.8).  16 and 24: N = 5397,
+    // M = 512, C = 16 18.0 and 6.3; N = 58963, M = 128 9.5 and 9.2 (7.2), C = 24 10.6 and 10.7 (7.7).  32: N = 88025, M = 64 11.0 and 9.2 (5.4);
+    // N = 145240, M = 512 60 and 68 (71).
+    if (C <= 24) return results < (C == 8 ? 3 << 20 : 7 << 20);
+    if (C <= 32) return results < (12 << 20);
+    // 40 and 56, padded here: N = 1341, M = 256, C = 56 6.0 and 5.6; N = 14178, M = 512, C = 40 10.8 and 14.5.
+    if (C != KC) return results < (1 << 20);
+    // 48 and 64: N = 16, M = 300, C = 64 8.8 and 4.7; N = 28337, M = 200, C = 64 18.2 and 17.0 (1 turn); N = 112329, M = 36, C = 48 14.1 and 12.8 (2);
+    // N = 46504, M = 200, C = 64 22.6 and 23.6 (2), N = 152246, M = 32, C = 64 12.7 and 16.0 (3).
+    return turns == 1 || (turns == 2 && results < (5 << 20));
 }
 
 // A stored by columns, 16, 32 or 64 codebooks: the kernels that take longer runs of a column and whole rows of results win over
@@ -847,6 +946,65 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
     case 32: return launch_averaged_tiles<8>(a, kb, grid, lds, stream);
     case 48: return launch_averaged_tiles<12>(a, kb, grid, lds, stream);
     default: return launch_averaged_tiles<16>(a, kb, grid, lds, stream);
+    }
+}
+
+// The scan alone: 256 rows to a chunk at most, as many blocks of columns as leave a workgroup for every compute unit where rows are few.
+// N = 1205, M = 300, C = 16 3.7 us (the general kernel 13.0), N = 4070 5.2 (13.5).
+int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, const uint8_t *luts, const float *scale,
+                       const float *offset, float *out, int64_t ldo, uint16_t *acc, hipStream_t stream)
+{
+    if (C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    int KC = 0;
+    for (int s : {64, 48, 32, 24, 16, 8, 4})
+        if (s >= C) KC = s;
+    BlockArgs a{};
+    a.A = codes; a.N = N;
+    a.luts = luts; a.scale = scale; a.offset = offset; a.M = M; a.C = C;
+    a.out = out; a.ldo = ldo; a.acc = acc;
+    const int Cb = (C + 1) / 2;
+    a.unit = Cb % 8 == 0 ? 8 : Cb % 4 == 0 ? 4 : 1;
+    const DeviceInfo &dev = device_info();
+    const int all_tiles = (M + 15) / 16, lpr = lanes_per_row(KC);
+    int shift = 0;
+    while (shift < 3 && (1 << shift) < all_tiles) ++shift;
+    auto blocks = [&](int sh) { return (all_tiles + (1 << sh) - 1) >> sh; };
+    while (shift > 0 && (N + 127) / 128 * blocks(shift - 1) <= dev.cus) --shift;
+    const int tiles = 1 << shift;
+    a.tile_shift = shift; a.col_blocks = blocks(shift);
+    const size_t table_lds = (size_t)KC * tiles * kTileBytes;
+    const int64_t most = std::min(256, kCodeUnits * kBlockThreads * a.unit / Cb);
+    const size_t code_lds = (size_t)((most + 15) / 16 * 16 + 16 * (kBlockWaves / tiles)) * lpr;
+    a.tables_at = a.rows_at = 256;
+    a.codes_at = (unsigned)(256 + table_lds);
+    const size_t lds = a.codes_at + code_lds;
+    if (lds > (size_t)dev.lds_per_block) return 1;
+    // (two workgroups to a compute unit where one would take several turns: N = 33000, M = 200, C = 30 13.5 and 15.6 us; beside one
+    // turn they read the tables twice: N = 450, M = 200, C = 64 8.0 and 5.1; 64 codebooks N = 90821, M = 10 9.3 and 7.3)
+    int64_t groups, share, turns;
+    for (int per_cu = 1;; ++per_cu) {
+        groups = std::max(1, dev.cus * per_cu / a.col_blocks);
+        if (groups > 8 && a.col_blocks > 1) groups = groups / 8 * 8;
+        share = std::max<int64_t>(16, (N + groups - 1) / groups);
+        turns = (share + most - 1) / most;
+        if (per_cu == 2 || turns <= (KC == 64 ? 2 : 1) || 2 * lds > (size_t)dev.lds_per_block) break;
+    }
+    if (!scan_blocks_pay(a, ldo, KC, turns)) return 1;
+    const int64_t rows = std::min(most, ((share + turns - 1) / turns + 15) / 16 * 16);
+    a.chunk_rows = (int)rows;
+    a.chunks = (int)((N + rows - 1) / rows);
+    groups = std::min<int64_t>(groups, a.chunks);
+    if (a.col_blocks > 1) groups = (groups + 7) / 8 * 8;
+    a.row_groups = (int)groups;
+    const int grid = a.row_groups * a.col_blocks;
+    switch (KC) {
+    case 4: return launch_codes<1>(a, grid, lds, stream);
+    case 8: return launch_codes<2>(a, grid, lds, stream);
+    case 16: return launch_codes<4>(a, grid, lds, stream);
+    case 24: return launch_codes<6>(a, grid, lds, stream);
+    case 32: return launch_codes<8>(a, grid, lds, stream);
+    case 48: return launch_codes<12>(a, grid, lds, stream);
+    default: return launch_codes<16>(a, grid, lds, stream);
     }
 }
 

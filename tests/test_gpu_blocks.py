@@ -181,3 +181,56 @@ def test_averages_by_blocks(mad, case):
         torch.cuda.synchronize()
         assert general.startswith("scan_kernel"), general
         assert torch.equal(codes, want_codes) and torch.equal(acc, want_acc) and torch.equal(out, want_out)
+
+
+# (N, M, C, floats between rows, bytes before the codes, bytes before the tables): fewest rows, one column, every kernel size with and
+# without codebooks that do not exist, codes by eight, four and single bytes, one block of columns and several, one chunk and several
+SCANS = [
+    (16, 1, 4, 0, 0, 0), (17, 300, 64, 0, 0, 0), (33, 64, 7, 1, 0, 0), (257, 129, 8, 0, 1, 1), (300, 100, 12, 0, 0, 0),
+    (1411, 1000, 15, 0, 0, 3), (700, 16, 16, 0, 3, 0), (4097, 300, 16, 4, 0, 0), (1000, 255, 23, 0, 0, 0), (5001, 512, 24, 0, 0, 0),
+    (4000, 785, 30, 0, 0, 0), (20000, 20, 31, 3, 0, 0), (10007, 128, 32, 0, 0, 0), (70001, 16, 32, 0, 0, 0), (129, 77, 40, 0, 0, 0),
+    (3001, 300, 48, 0, 0, 0), (140000, 3, 48, 0, 0, 0), (2000, 100, 56, 0, 0, 0), (9001, 36, 63, 0, 2, 0), (140001, 10, 64, 0, 0, 0),
+    (300001, 20, 15, 0, 0, 0), (60000, 250, 30, 2, 0, 0), (14000, 1000, 15, 0, 0, 0), (33, 514, 64, 0, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", SCANS, ids=lambda c: "N%d_M%d_C%d_p%d_c%d_t%d" % c)
+def test_scan_by_blocks(mad, case):
+    import torch
+    N, M, C, pad, before, at = case
+    print("case", case, flush=True)
+    rng = np.random.default_rng(N + M + C)
+    codes_h = rng.integers(0, 256, size=(N, (C + 1) // 2)).astype(np.uint8)
+    if C % 2:
+        codes_h[:, -1] &= 15
+    luts_h = rng.integers(0, 256, size=(C, 16, M), dtype=np.uint8)
+    luts_h[:, :, 0] = 255                           # the largest sums
+    raw_codes, raw_luts = (torch.zeros(n, dtype=torch.uint8, device="cuda") for n in (codes_h.size + before, luts_h.size + at))
+    raw_codes[before:] = dev(codes_h).reshape(-1)
+    raw_luts[at:] = dev(luts_h).reshape(-1)
+    codes, luts = raw_codes[before:].reshape(codes_h.shape), raw_luts[at:].reshape(C, 16, M)
+    scale, offset = (dev(rng.standard_normal(M).astype(np.float32)) for _ in range(2))
+
+    def run(want_out=True):
+        acc = torch.zeros((N, M), dtype=torch.int16, device="cuda") if N < 5000 else None
+        full = torch.full((N, M + pad), -3.0, device="cuda")
+        mad.maddness_scan(C, codes, luts, scale, offset, out=full[:, :M] if want_out else None, acc=acc, want_out=want_out)
+        kernel = mad.maddness_last_kernel()
+        torch.cuda.synchronize()
+        return full, acc, kernel
+
+    got, got_acc, kernel = run()
+    assert kernel.startswith("mfma_scan_kernel, blocks of columns"), kernel
+    only = run(False)[1] if got_acc is not None else None
+    try:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+        want, want_acc, kernel = run()
+    finally:
+        mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, 0)
+    assert kernel.startswith("scan_kernel"), kernel
+    assert torch.equal(got, want)
+    if got_acc is not None:
+        assert torch.equal(got_acc, want_acc) and torch.equal(only, want_acc)
+    if N <= 300:
+        out, acc, _ = oracle.scan(codes_h, C, luts_h, scale.cpu().numpy(), offset.cpu().numpy())
+        assert (got[:, :M].cpu().numpy() == out).all() and (got_acc.cpu().numpy().view(np.uint16) == acc).all()
