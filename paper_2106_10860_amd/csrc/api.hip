@@ -146,6 +146,8 @@ static int encode_checked(const maddness_params *params, const void *A, int32_t 
         rc = desc.col_major ? launch_encode_cols(*params, desc, N, codes, static_cast<hipStream_t>(stream))
                             : launch_encode_rows(*params, desc, N, codes, static_cast<hipStream_t>(stream));
         if (rc != 1) return rc;
+        rc = launch_encode_blocks(*params, desc, N, codes, static_cast<hipStream_t>(stream));
+        if (rc != 1) return rc;
     }
     return launch_encode(*params, desc, N, codes, static_cast<hipStream_t>(stream));
 }

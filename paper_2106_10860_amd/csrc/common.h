@@ -133,6 +133,9 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
 int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, const uint8_t *luts, const float *scale,
                        const float *offset, float *out, int64_t ldo, uint16_t *acc, hipStream_t stream);
 
+// The codes alone by such blocks (rows or columns).
+int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes, hipStream_t stream);
+
 // Encode only with the first phase of that kernel (row-major fp32 A, up to 64 codebooks, many rows).
 int launch_encode_phased(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes,
                          hipStream_t stream);

@@ -1,4 +1,4 @@
-// Fused encode + exact scan, and the scan alone, by blocks of rows and columns, for few and medium numbers of rows.
+// Fused encode + exact scan, and either alone, by blocks of rows and columns, for few and medium numbers of rows.
 //
 // A call of a few thousand rows is bound by latencies: a chain of kernel arguments -> trees, tables and rows -> codes ->
 // sums -> stores on a chip that is mostly idle.  So a workgroup (8 wavefronts) takes a block of up to 128 (256) output
@@ -73,8 +73,9 @@ constexpr int lanes_per_row(int C) { return C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 
 // ALUs, with TS = log2 of the tiles of a block of columns.  The tables stay in LDS as they lie in memory, a lane takes four
 // columns of one row, and a code is kept as the distance of its entries from the codebook's first, 16 bits, so that a
 // lookup takes one addition, one read and one average of four bytes.
+// ENC: the codes alone, no tables: a chunk's rows (columns' values) are on their way while the one before is encoded.
 // CODES: the scan alone.  A holds packed codes, of which a thread takes up to four units of a chunk and deals them out in LDS.
-template <int KG, int NTW, int PF, bool COLS = false, bool AVG = false, int TS = 0, bool CODES = false>
+template <int KG, int NTW, int PF, bool COLS = false, bool AVG = false, int TS = 0, bool CODES = false, bool ENC = false>
 __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const BlockArgs a)
 {
     constexpr int LPR = lanes_per_row(4 * KG), RPW = 64 / LPR;    // lanes to a row, rows per wavefront while encoding
@@ -204,49 +205,6 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
     else if constexpr (CODES) fetch_codes(chunk);
     else fetch_rows(chunk);
 
-    // piece n of a thread: tile tid % tiles (neighbours read neighbouring columns), code (tid / tiles) % 16, codebook
-    // tid / (16 tiles) + n BLOCKS / tiles
-    const unsigned table_bytes = 16u * (unsigned)a.C * (unsigned)a.M;      // (below 2^31: the launcher)
-    const int p_tile = tid & (tiles - 1), p_code = (tid >> a.tile_shift) & 15, p_book = tid >> (4 + a.tile_shift);
-    const int book_step = BLOCKS >> a.tile_shift;
-    const int n_pieces = ((4 * KG << a.tile_shift) + BLOCKS - 1) / BLOCKS;
-    const int last_tile = (a.M - 1 - col0) >> 4;
-    const unsigned p_first = (unsigned)(16 * p_book + p_code) * (unsigned)a.M +
-                             (unsigned)(col0 + 16 * (p_tile < last_tile ? p_tile : last_tile));
-    const unsigned p_step = (unsigned)(16 * book_step) * (unsigned)a.M, p_last = table_bytes - 16;
-    uint4 piece[PIECES];
-#pragma unroll
-    for (int n = 0; n < PIECES; ++n) {
-        if (n < n_pieces) {
-            // (tiles and codebooks that do not exist read others' entries; the last pieces end where the tables end)
-            const unsigned at = p_first + (unsigned)n * p_step;
-            __builtin_memcpy(&piece[n], a.luts + (at < p_last ? at : p_last), 16);
-        }
-    }
-
-    // the wavefront's tiles, and its share of the rows where there are fewer tiles than wavefronts
-    constexpr int NTW_SHIFT = NTW == 2 ? 1 : 0;
-    const int wave_tiles = tiles >> NTW_SHIFT, tile0 = NTW * (wave & (wave_tiles - 1));
-    const int share = wave >> (a.tile_shift - NTW_SHIFT), shares = WAVES >> (a.tile_shift - NTW_SHIFT);
-    int col[NTW];
-    float sc[NTW][4], of[NTW][4];
-#pragma unroll
-    for (int t = 0; t < NTW; ++t) {
-        col[t] = AVG ? col0 + 4 * (lane & ((4 << TS) - 1)) : col0 + 16 * (tile0 + t) + 4 * g;
-        if (col0 + 16 * tiles <= a.M) {
-            __builtin_memcpy(sc[t], a.scale + col[t], 16);
-            __builtin_memcpy(of[t], a.offset + col[t], 16);
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = col[t] + r < a.M ? col[t] + r : a.M - 1;
-                sc[t][r] = a.scale[m];
-                of[t][r] = a.offset[m];
-            }
-        }
-    }
-    if constexpr (!AVG) mfma::fill_one_hot_table(one_hot, tid);
-
     // ---- encode: the codes of a chunk, times 16, into LDS ----
     auto encode = [&](int64_t row0) INLINE_LAMBDA {
 #pragma unroll 1
@@ -281,7 +239,7 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
                 code = real ? code : 0u;
                 if constexpr (AVG) {
                     if (r[h] < a.chunk_rows) reinterpret_cast<uint16_t *>(codes_l)[r[h] * LPR + c] = (uint16_t)(code << (4 + TS));
-                } else {
+                } else if constexpr (!ENC) {
                     if (r[h] < a.chunk_rows) codes_l[r[h] * LPR + (c & 3) * KGP + (c >> 2)] = (unsigned char)(code << 4);
                 }
                 if (a.codes_out && col_block == 0) {
@@ -333,6 +291,70 @@ __global__ __launch_bounds__(kBlockThreads) void fused_blocks_kernel(const Block
             a.codes_out[row0 * Cb + at] = (uint8_t)(low | high);
         }
     };
+
+    if constexpr (ENC) {
+        while (true) {
+            const int next = chunk + a.row_groups;
+            const bool more = next < a.chunks;
+            if constexpr (COLS) {
+                encode_columns();
+                __syncthreads();
+                if (more) fetch_columns(next);
+                store_codes((int64_t)chunk * 64);
+            } else {
+                write_rows();
+                __syncthreads();
+                if (more) fetch_rows(next);
+                encode((int64_t)chunk * a.chunk_rows);
+            }
+            if (!more) return;
+            __syncthreads();
+            chunk = next;
+        }
+    }
+
+    // piece n of a thread: tile tid % tiles (neighbours read neighbouring columns), code (tid / tiles) % 16, codebook
+    // tid / (16 tiles) + n BLOCKS / tiles
+    const unsigned table_bytes = 16u * (unsigned)a.C * (unsigned)a.M;      // (below 2^31: the launcher)
+    const int p_tile = tid & (tiles - 1), p_code = (tid >> a.tile_shift) & 15, p_book = tid >> (4 + a.tile_shift);
+    const int book_step = BLOCKS >> a.tile_shift;
+    const int n_pieces = ((4 * KG << a.tile_shift) + BLOCKS - 1) / BLOCKS;
+    const int last_tile = (a.M - 1 - col0) >> 4;
+    const unsigned p_first = (unsigned)(16 * p_book + p_code) * (unsigned)a.M +
+                             (unsigned)(col0 + 16 * (p_tile < last_tile ? p_tile : last_tile));
+    const unsigned p_step = (unsigned)(16 * book_step) * (unsigned)a.M, p_last = table_bytes - 16;
+    uint4 piece[PIECES];
+#pragma unroll
+    for (int n = 0; n < PIECES; ++n) {
+        if (n < n_pieces) {
+            // (tiles and codebooks that do not exist read others' entries; the last pieces end where the tables end)
+            const unsigned at = p_first + (unsigned)n * p_step;
+            __builtin_memcpy(&piece[n], a.luts + (at < p_last ? at : p_last), 16);
+        }
+    }
+
+    // the wavefront's tiles, and its share of the rows where there are fewer tiles than wavefronts
+    constexpr int NTW_SHIFT = NTW == 2 ? 1 : 0;
+    const int wave_tiles = tiles >> NTW_SHIFT, tile0 = NTW * (wave & (wave_tiles - 1));
+    const int share = wave >> (a.tile_shift - NTW_SHIFT), shares = WAVES >> (a.tile_shift - NTW_SHIFT);
+    int col[NTW];
+    float sc[NTW][4], of[NTW][4];
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+        col[t] = AVG ? col0 + 4 * (lane & ((4 << TS) - 1)) : col0 + 16 * (tile0 + t) + 4 * g;
+        if (col0 + 16 * tiles <= a.M) {
+            __builtin_memcpy(sc[t], a.scale + col[t], 16);
+            __builtin_memcpy(of[t], a.offset + col[t], 16);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = col[t] + r < a.M ? col[t] + r : a.M - 1;
+                sc[t][r] = a.scale[m];
+                of[t][r] = a.offset[m];
+            }
+        }
+    }
+    if constexpr (!AVG) mfma::fill_one_hot_table(one_hot, tid);
 
     v4i T[NTW][KG];
     const int first_sum = 128 * a.C;
@@ -604,6 +626,22 @@ int launch_codes(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
     if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 1, false, false, 0, true>>(); rc != MADDNESS_OK) return rc;
     note_kernel("mfma_scan_kernel, blocks of columns", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, false, false, 0, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
+    return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
+}
+
+template <int KG>
+int launch_codes_of_columns(const BlockArgs &a, size_t lds, hipStream_t stream)
+{
+    note_kernel("fused_blocks_kernel, codes of columns", __PRETTY_FUNCTION__);
+    hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, true, false, 0, false, true>), dim3(a.row_groups), dim3(kBlockThreads), lds, stream, a);
+    return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
+}
+
+template <int KG>
+int launch_codes_of_rows(const BlockArgs &a, size_t lds, hipStream_t stream)
+{
+    note_kernel("fused_blocks_kernel, codes of rows", __PRETTY_FUNCTION__);
+    hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 4, false, false, 0, false, true>), dim3(a.row_groups), dim3(kBlockThreads), lds, stream, a);
     return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
 }
 
@@ -1005,6 +1043,70 @@ int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, co
     case 32: return launch_codes<8>(a, grid, lds, stream);
     case 48: return launch_codes<12>(a, grid, lds, stream);
     default: return launch_codes<16>(a, grid, lds, stream);
+    }
+}
+
+// The codes alone, for what would else be the general kernel's, in which a lane asks for the split values of its row and pair of
+// codebooks one by one.  There and here, us: by rows N = 18129 and fewer all take as long as a launch but for wide or many
+// (N = 12485, D = 1728, C = 32, binary16 13.6 and 8.2), N = 762885, D = 96, C = 24, bfloat16 121 and 48, N = 344094, D = 1000, C = 15, binary16 245 and 118;
+// by columns N = 26139, C = 30, bfloat16 14.2 and 6.6, N = 353958, C = 48 179 and 77, N = 1294803, C = 63, bytes 701 and 332.
+int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes, hipStream_t stream)
+{
+    const int es = A.elem_bytes(), C = p.C;
+    if (C > 64 || N < 16 || N >= (1LL << 36)) return 1;
+    int KC = 0;
+    for (int s : {64, 48, 32, 24, 16, 8, 4})
+        if (s >= C) KC = s;
+    BlockArgs a{};
+    a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.row_bytes = p.D * es; a.D = p.D; a.dtype = A.dtype;
+    a.N = N; a.C = C; a.col_blocks = 1;
+    a.split_dims = p.split_dims; a.thresholds = p.thresholds;
+    a.codes_out = codes;
+    a.rows_at = a.codes_at = a.tables_at = 256;
+    const DeviceInfo &dev = device_info();
+    if (A.col_major) {
+        // (next to no codes to a row: N = 1154410, C = 4, bfloat16 33 and 36; N = 481716, C = 8 18.6 and 20.1; bytes N = 101212, C = 8 11.2 and 5.7)
+        // nor few rows, of which a wavefront here takes several codebooks in turn (N = 5527, C = 64, bfloat16 6.4 and 8.1; N = 7254, C = 40 7.1 and 6.1)
+        if (KC == 4 || (KC == 8 && A.dtype == MADDNESS_F32 && N > (1 << 17)) || N < 128 * KC) return 1;
+        // workgroups to a compute unit, with 4 and as here: N = 440208, C = 24, bytes 45.7 and 42.6; N = 353958, C = 48 88 and 77; N = 132534, C = 63 39.3
+        // and 38.0; fewer for C = 15 lose (N = 302525, bytes 19.8 with 4, 22.1 with 3)
+        const int64_t wgs = (int64_t)dev.cus * (KC <= 16 ? 4 : KC < 64 ? 3 : 2);
+        a.chunk_rows = 64;
+        a.chunks = (int)((N + 63) / 64);
+        a.row_groups = (int)std::min<int64_t>(wgs, a.chunks);
+        const size_t lds = 256 + 64 * (size_t)lanes_per_row(KC);
+        switch (KC) {
+        case 4: return launch_codes_of_columns<1>(a, lds, stream);
+        case 8: return launch_codes_of_columns<2>(a, lds, stream);
+        case 16: return launch_codes_of_columns<4>(a, lds, stream);
+        case 24: return launch_codes_of_columns<6>(a, lds, stream);
+        case 32: return launch_codes_of_columns<8>(a, lds, stream);
+        case 48: return launch_codes_of_columns<12>(a, lds, stream);
+        default: return launch_codes_of_columns<16>(a, lds, stream);
+        }
+    }
+    if (a.row_bytes > kMaxRowBytes || a.pitch > a.row_bytes + a.row_bytes / 8 + 64) return 1;
+    const bool whole = a.pitch % 16 == 0 && aligned_to(A.data, 16);
+    // (whole rows are read here, 64 bytes for each split value there: N = 20680, D = 512, C = 4, binary16 5.8 and 6.1)
+    const int64_t most = (32 * 1024 - (whole ? 0 : 16)) / a.pitch;
+    if (most < 1 || a.row_bytes > 192 * C) return 1;
+    // two workgroups to a compute unit where that makes one chunk to each (N = 27487, D = 120, C = 30 4.6 us, 5.7 with four), else four (N = 240545, D = 192,
+    // C = 48 42.8, 46.3 with two, 49.1 with two and chunks of 64 KiB)
+    int64_t wgs = 2 * (int64_t)dev.cus;
+    if ((N + wgs - 1) / wgs > most) wgs *= 2;
+    const int64_t share = std::max<int64_t>(8, (N + wgs - 1) / wgs), turns = (share + most - 1) / most, rows = (share + turns - 1) / turns;
+    if (N / rows >= (1 << 30)) return 1;
+    a.chunk_rows = (int)rows;
+    a.chunks = (int)((N + rows - 1) / rows);
+    a.row_groups = (int)std::min<int64_t>(wgs, a.chunks);
+    const size_t lds = 256 + 32 * 1024;
+    switch (KC) {
+    case 4: return launch_codes_of_rows<1>(a, lds, stream);
+    case 8: return launch_codes_of_rows<2>(a, lds, stream);
+    case 16: return launch_codes_of_rows<4>(a, lds, stream);
+    case 24:
+    case 32: return launch_codes_of_rows<8>(a, lds, stream);
+    default: return launch_codes_of_rows<16>(a, lds, stream);
     }
 }
 

@@ -28,7 +28,7 @@
 // depth; only the by-columns input gained, 0.295 against 0.324 ms at N = 2^20,
 // M = 256).  Used for many rows of any type by up to 64 codebooks, for any number of them
 // where the tables are larger than the other kernels take at once (and for many shapes whose
-// tables these still hold: few_rows_in_lds), for A stored by columns (few_columns_in_lds); and,
+// tables these still hold: few_rows_in_lds), of the few rows those that the kernel by blocks of rows and columns leaves, for A stored by columns (few_columns_in_lds); and,
 // as its E phase alone, to encode fp32 rows.
 #include <algorithm>
 
@@ -601,7 +601,7 @@ int odd_codebooks(int es, int codebooks, int need)
            : codebooks <= 64 && need * per_row <= 8192 ? 64 : 0;
 }
 
-// Few rows: the general kernel has to bring the tables into LDS, 11 to 20 us for what it holds at once (up to some
+// Few rows (those that the kernel by blocks of rows and columns, which is asked first, has left): the general kernel has to bring the tables into LDS, 11 to 20 us for what it holds at once (up to some
 // 148 KiB; 25 to 45 us where it reads single bytes), and this one tables of `kernel_codebooks` codebooks and whole passes
 // of columns into registers, 12 us for one pass and some 8 for each further one.  So it depends on how much of these is
 // padding.  Measured, general and here: words, fp32 rows, 1.5 times the tables 19 and 13 us, 2.5 times 15 and 13, 3.3 times

@@ -32,7 +32,7 @@
 //                        wavefront per 256 rows, the best threshold and loss per bucket
 //   apply_kernel         apply_split: the next level's buckets
 // Prototypes: cooccurrence_kernel (G^T G), count_codes_kernel, list_codes_kernel and gta_kernel (G^T A~),
-// cholesky_panel_kernel, transpose_factor_kernel (the factor by rows), substitution_kernel; or means_kernel.
+// cholesky_panel_kernel, transpose_factor_kernel (the factor by columns), substitution_kernel; or means_kernel.
 #include "common.h"
 #include "device_common.h"
 #include "learn_bounds.h"
@@ -2046,7 +2046,7 @@ struct ProtoArgs {
     int32_t shares;         // wavefronts that share a code's rows where any order will do
     double *R_shares;       // [shares - 1][Q][D] what the others than the first add to R
     double *M;              // [Q][Q]: G^T G + lambda I, then M[k][i] = L[i][k]
-    double *Lr;             // [Q][Q]: L by rows
+    double *Lr;             // [Q][Q]: L in tiles of 16 x 16 (factor_at)
     double *R;              // [Q][D]: G^T A~
     int64_t stretch;        // rows of a stretch
     uint32_t *list;         // [C][kListRows + kListSpare] distances in bytes of the stretch's rows, by code
@@ -2435,7 +2435,7 @@ __global__ __launch_bounds__(256) void cholesky_panel_kernel(const ProtoArgs a, 
         }
 }
 
-// The factor by rows; the workgroups after those add the shares of G^T A~ to the first (exact, in whatever order).
+// The factor by columns from its tiles; the workgroups after those add the shares of G^T A~ to the first (exact, in whatever order).
 __global__ __launch_bounds__(256) void transpose_factor_kernel(const ProtoArgs a)
 {
     const int64_t QQ = (int64_t)a.Q * a.Q;

@@ -75,7 +75,7 @@ struct ScanOut {
     int M;
 };
 
-// From how many rows on the scan runs on the matrix cores.  `in_lds`: 16 or 32 codebooks, up to 128 KiB: kernels that hold
+// From how many rows on the scan runs on the matrix cores, of what the kernel by blocks of rows and columns leaves.  `in_lds`: 16 or 32 codebooks, up to 128 KiB: kernels that hold
 // the tables in LDS are faster for few rows where they take the shape (M = 256, C = 32: 11 us for 4096 rows of bfloat16, 16
 // for 16384 here), and the general kernel, which does the same for any shape (launch_scan), is taken elsewhere.  It is also
 // for tables of up to 64 KiB.  What neither holds at once it and tiled_rows_kernel walk tile by

@@ -234,3 +234,41 @@ def test_scan_by_blocks(mad, case):
     if N <= 300:
         out, acc, _ = oracle.scan(codes_h, C, luts_h, scale.cpu().numpy(), offset.cpu().numpy())
         assert (got[:, :M].cpu().numpy() == out).all() and (got_acc.cpu().numpy().view(np.uint16) == acc).all()
+
+
+# (N, D, C, dtype, by columns, elements between rows or columns, elements before the first): every kernel size with and without codebooks
+# that do not exist, one chunk to a workgroup and several, rows on any element
+CODES = [
+    (16, 27, 5, "f32", False, 0, 0), (700, 27, 3, "f32", False, 0, 1), (4099, 130, 8, "u8", False, 3, 1), (100003, 97, 15, "f16", False, 0, 0),
+    (30001, 250, 24, "bf16", False, 1, 0), (20000, 120, 30, "f32", False, 0, 0), (9001, 512, 47, "u8", False, 0, 3), (50001, 256, 63, "bf16", False, 0, 0),
+    (1025, 33, 8, "f32", True, 0, 0), (1153, 64, 7, "u8", True, 1, 1), (4097, 64, 15, "bf16", True, 0, 1), (200001, 60, 12, "u8", True, 3, 0),
+    (30001, 97, 24, "f32", True, 0, 0), (120001, 120, 30, "f16", True, 1, 0), (10001, 190, 48, "f32", True, 0, 1), (70001, 252, 63, "u8", True, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", CODES, ids=lambda c: "N%d_D%d_C%d_%s_cols%d_p%d_o%d" % c)
+def test_codes_by_blocks(mad, case):
+    import torch
+    N, D, C, dtype, cols, pad, before = case
+    print("case", case, flush=True)
+    A, sd, th, _, _, _ = problem(N + D, min(N, 2048), D, 4, C)
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
+    many, inner = (D, N) if cols else (N, D)
+    raw = torch.full((before + many * (inner + pad),), 1, dtype=kind, device="cuda")
+    A_d = raw[before:].view(many, inner + pad)[:, :inner]
+    values = (dev(A) * (60 if dtype == "u8" else 1)).clamp(max=255).to(kind)[torch.arange(N, device="cuda") % len(A)]
+    A_d.copy_(values.t() if cols else values)
+    params = mad.Params(dev(sd), dev(th))
+    got = mad.maddness_encode_typed(params, A_d, col_major=cols)
+    kernel = mad.maddness_last_kernel()
+    torch.cuda.synchronize()
+    assert kernel.startswith("fused_blocks_kernel, codes of " + ("columns" if cols else "rows")), kernel
+    want = oracle.pack(oracle.encode(values.float().cpu().numpy(), sd, th)) if N <= 5000 else None
+    if want is None:
+        try:
+            mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
+            want = mad.maddness_encode_typed(params, A_d, col_major=cols).cpu().numpy()
+            assert mad.maddness_last_kernel().startswith("encode_kernel"), mad.maddness_last_kernel()
+        finally:
+            mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, 0)
+    assert (got.cpu().numpy() == want).all()
