@@ -786,15 +786,24 @@ bool scan_blocks_pay(const BlockArgs &a, int64_t ldo, int KC, int64_t turns)
         // M = 100, C = 31 128 and 44: whatever the size, but for results that may be written by whole lines (M = 785, C = 24, N = 117350 91 and 131).
         return results < (12 << 20) || M < 64 || M % 32 == 0 || a.acc || !a.out || ldo != M || !aligned_to(a.out, 128) || a.N < 16384;
     }
-    // C = 8: N = 512, M = 105 11.4 and 4.1; N = 52771, M = 32 5.3 and 5.1 (1.6 Mi results); N = 109905, M = 36 7.4 and 7.9 (3.8).  16 and 24: N = 5397,
-    // M = 512, C = 16 18.0 and 6.3; N = 58963, M = 128 9.5 and 9.2 (7.2), C = 24 10.6 and 10.7 (7.7).  32: N = 88025, M = 64 11.0 and 9.2 (5.4);
-    // N = 145240, M = 512 60 and 68 (71).
+    // Rows of results that begin on 128-byte lines: the other kernel's blocks of columns are as good, and what counts is how much of the blocks
+    // here is padding.  C = 8: N = 38200, M = 64 5.6 and 5.8 (2.3 Mi results); 16: N = 153, M = 512 16.6 and 4.2, N = 29654, M = 192 8.3 and 9.8 (5.4, 7.2 with
+    // padding), N = 8922, M = 640 8.0 and 8.5 (5.4), N = 22553, M = 256 8.3 and 8.2 (5.5); 24: N = 45793, M = 128 9.5 and 9.2 (5.6); 32: N = 88025, M = 64
+    // 11.0 and 9.2 (5.4), N = 42606, M = 192 12.1 and 13.4 (7.8, 10.4), N = 165055, M = 64 13.1 and 13.8 (10); 48 and 64: N = 1341, M = 256 6.0 and 5.6, N = 5420,
+    // M = 512 8.6 and 8.6 (2.6), N = 6197, M = 640 11.2 and 12.0 (3.8), N = 97347, M = 32 9.1 and 8.9 (3), N = 152246, M = 32 12.7 and 16.0 (4.6).
+    const int64_t padded = a.N * 16 * ((int64_t)a.col_blocks << a.tile_shift);
+    const bool on_lines = ldo % 32 == 0;
+    if (on_lines) {
+        if (C <= 32) return padded < (C == 8 ? 2 << 20 : C == 16 ? 4 << 20 : C == 24 ? 5 << 20 : 7 << 20);
+        if (C == KC) return M <= 64 ? turns <= 2 && padded < (4 << 20) : turns == 1 && 2 * padded < (5 << 20);
+    }
+    // Others: N = 109905, M = 36, C = 8 7.4 and 7.9 (3.8); N = 18831, M = 300, C = 16 11.0 and 9.7 (5.4), N = 35862, M = 200 11.3 and 10.4 (6.8); N = 319639, M = 36,
+    // C = 32 22.5 and 19.8 (11).  48 and 64: N = 28337, M = 200, C = 64 18.2 and 17.0 (1 turn), N = 112329, M = 36, C = 48 14.1 and 12.8 (2), N = 46504, M = 200, C = 64
+    // 22.6 and 23.6 (2, 9 Mi).
     if (C <= 24) return results < (C == 8 ? 3 << 20 : 7 << 20);
     if (C <= 32) return results < (12 << 20);
     // 40 and 56, padded here: N = 1341, M = 256, C = 56 6.0 and 5.6; N = 14178, M = 512, C = 40 10.8 and 14.5.
     if (C != KC) return results < (1 << 20);
-    // 48 and 64: N = 16, M = 300, C = 64 8.8 and 4.7; N = 28337, M = 200, C = 64 18.2 and 17.0 (1 turn); N = 112329, M = 36, C = 48 14.1 and 12.8 (2);
-    // N = 46504, M = 200, C = 64 22.6 and 23.6 (2), N = 152246, M = 32, C = 64 12.7 and 16.0 (3).
     return turns == 1 || (turns == 2 && results < (5 << 20));
 }
 
@@ -1007,7 +1016,8 @@ int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, co
     int shift = 0;
     while (shift < 3 && (1 << shift) < all_tiles) ++shift;
     auto blocks = [&](int sh) { return (all_tiles + (1 << sh) - 1) >> sh; };
-    while (shift > 0 && (N + 127) / 128 * blocks(shift - 1) <= dev.cus) --shift;
+    // (eight chunks of rows or a multiple, one to a die: with fewer the other dies have nothing to do, N = 454, M = 640, C = 64 8.1 us so, 5.5 with two tiles to a block)
+    while (shift > 0 && ((N + 127) / 128 + 7) / 8 * 8 * blocks(shift - 1) <= dev.cus) --shift;
     const int tiles = 1 << shift;
     a.tile_shift = shift; a.col_blocks = blocks(shift);
     const size_t table_lds = (size_t)KC * tiles * kTileBytes;
@@ -1047,8 +1057,8 @@ int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, co
 }
 
 // The codes alone, for what would else be the general kernel's, in which a lane asks for the split values of its row and pair of
-// codebooks one by one.  There and here, us: by rows N = 18129 and fewer all take as long as a launch but for wide or many
-// (N = 12485, D = 1728, C = 32, binary16 13.6 and 8.2), N = 762885, D = 96, C = 24, bfloat16 121 and 48, N = 344094, D = 1000, C = 15, binary16 245 and 118;
+// codebooks one by one.  There and here, us: by rows N = 13471, D = 240, C = 24 5.9
+// and 4.6, N = 12485, D = 1728, C = 32, binary16 13.6 and 8.2, N = 762885, D = 96, C = 24, bfloat16 121 and 48, N = 344094, D = 1000, C = 15, binary16 245 and 118;
 // by columns N = 26139, C = 30, bfloat16 14.2 and 6.6, N = 353958, C = 48 179 and 77, N = 1294803, C = 63, bytes 701 and 332.
 int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes, hipStream_t stream)
 {
