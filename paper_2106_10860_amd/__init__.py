@@ -110,7 +110,7 @@ def _check(status: int) -> None:
 # a call by the code below, 4.8 by that one). What it does not know it leaves to that code: NotImplemented.
 
 class _NotBuilt:
-    """In the place of the native marshalling where it is not built: every call goes through the code below."""
+    """In the place of the native marshalling where there is none to load: every call goes through the code below."""
 
     @staticmethod
     def encode_scan(*_):
@@ -124,19 +124,26 @@ class _NotLoaded:
 
     def __getattr__(self, name):
         global _native
-        if not os.path.exists(NATIVE_PATH):
-            _native = _NotBuilt
-        else:
-            import importlib.machinery
-            import importlib.util
-            _torch_module()
-            lib()
-            loader = importlib.machinery.ExtensionFileLoader("maddness_binding", NATIVE_PATH)
-            spec = importlib.util.spec_from_file_location("maddness_binding", NATIVE_PATH, loader=loader)
-            module = importlib.util.module_from_spec(spec)
-            loader.exec_module(module)
-            _native = module
+        _native = _load_native()
         return getattr(_native, name)
+
+
+def _load_native():
+    """The native marshalling.  It is built against one version of torch and of Python and loads with no other; where it does not
+    load, or is not there, the calls are as complete without it, and a warning says that they take longer."""
+    import importlib.machinery
+    import importlib.util
+    _torch_module()
+    lib()
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("maddness_binding", NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("maddness_binding", NATIVE_PATH, loader=loader))
+        loader.exec_module(module)
+        return module
+    except (ImportError, OSError) as e:
+        import warnings
+        warnings.warn(f"the native argument marshalling is not used, calls take some 3 us longer: {e}", RuntimeWarning, stacklevel=5)
+        return _NotBuilt
 
 
 _native = _NotLoaded()

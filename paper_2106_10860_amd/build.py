@@ -40,8 +40,12 @@ def binding_command():
 
     import torch
     at = os.path.dirname(torch.__file__)
+    header = os.path.join(at, "include", "torch", "csrc", "autograd", "python_variable.h")
+    if not os.path.exists(header):
+        raise FileNotFoundError(header)
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            f'-DMADDNESS_TORCH_VERSION="{torch.__version__}"',
             "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(at, "include"),
             "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
             os.path.join(CSRC, BINDING_SOURCE), "-o", BINDING_LIB, "-L", HERE, "-l:libmaddness.so", "-Wl,-rpath,$ORIGIN",
@@ -72,11 +76,24 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB, jobs: int = 0) 
             if verbose:
                 print(" ".join(calib), flush=True)
             subprocess.check_call(calib)
-            binding = binding_command()
-            if verbose:
-                print(" ".join(binding), flush=True)
-            subprocess.check_call(binding)
+            build_binding(verbose)
     return out
+
+
+def build_binding(verbose: bool = False) -> bool:
+    """Compiles the native argument marshalling.  The library is complete without it: where torch, its headers or the compiler are
+    not there that is said, an older build of it is removed, and the Python calls go without."""
+    try:
+        command = binding_command()
+        if verbose:
+            print(" ".join(command), flush=True)
+        subprocess.check_call(command)
+        return True
+    except (ImportError, OSError) as e:
+        if os.path.exists(BINDING_LIB):
+            os.remove(BINDING_LIB)
+        print(f"{os.path.basename(BINDING_LIB)} is not built, the Python calls take some 3 us longer: {e}", file=sys.stderr, flush=True)
+        return False
 
 
 if __name__ == "__main__":

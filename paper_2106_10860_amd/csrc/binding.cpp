@@ -11,6 +11,9 @@
 #include <ATen/ops/empty.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cstdio>
+#include <cstring>
+
 #include "maddness.h"
 
 namespace {
@@ -329,6 +332,24 @@ PyObject *build_luts(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
+// Tensors are read by the layout of the torch, and objects by that of the Python, that this was built with: with others it is an
+// ImportError, also where every symbol is found.
+bool built_for_these()
+{
+    PyObject *torch = PyImport_ImportModule("torch");
+    PyObject *version = torch ? PyObject_GetAttrString(torch, "__version__") : nullptr;
+    const char *have = version ? PyUnicode_AsUTF8(version) : nullptr;
+    char python[32];
+    std::snprintf(python, sizeof python, "%d.%d.", PY_MAJOR_VERSION, PY_MINOR_VERSION);
+    const bool same = have && std::strcmp(have, MADDNESS_TORCH_VERSION) == 0 && std::strncmp(Py_GetVersion(), python, std::strlen(python)) == 0;
+    if (!same && !PyErr_Occurred())
+        PyErr_Format(PyExc_ImportError, "built for torch %s and Python %s, this is torch %s and Python %s", MADDNESS_TORCH_VERSION, PY_VERSION,
+                     have, Py_GetVersion());
+    Py_XDECREF(version);
+    Py_XDECREF(torch);
+    return same;
+}
+
 PyMethodDef methods[] = {
     {"encode_scan", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(encode_scan)), METH_FASTCALL, nullptr},
     {"encode", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(encode)), METH_FASTCALL, nullptr},
@@ -349,6 +370,7 @@ PyMODINIT_FUNC PyInit_maddness_binding()
     s_C = PyUnicode_InternFromString("C");
     s_D = PyUnicode_InternFromString("D");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+    if (!built_for_these()) return nullptr;
     PyObject *torch_c = PyImport_ImportModule("torch._C");
     if (!torch_c) return nullptr;
     get_stream = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
