@@ -322,6 +322,9 @@ int maddness_learn_prototypes(const uint8_t *train_codes, const float *A_train, 
  * MADDNESS_OPT_COLS_RUN     1, 2 or 4 rows per lane in the by-columns kernels; 0: automatic.
  * MADDNESS_OPT_MAX_WORKGROUPS  n >= 1: the phased kernels launch at most n workgroups, so
  *                           that each takes several regions in turn; 0: one per compute unit.
+ * Where PHASED_ROWS or MAX_WORKGROUPS is set, the kernel that works by blocks of rows and columns
+ * (fused_blocks_kernel, for few and medium rows) is left out, so that the kernels beside it can be reached
+ * with few rows too.
  *
  * maddness_set_option returns MADDNESS_E_INVAL for an unknown option or a value outside
  * the ranges above; maddness_get_option returns the current value, or -1 for an unknown

@@ -590,7 +590,7 @@ template <int KG, int NTW, int PF>
 int launch_blocks(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
 {
     if (int rc = allow_full_lds<fused_blocks_kernel<KG, NTW, PF>>(); rc != MADDNESS_OK) return rc;
-    note_kernel("fused_mfma_kernel, A by rows, blocks of columns", __PRETTY_FUNCTION__);
+    note_kernel("fused_blocks_kernel, A by rows", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_blocks_kernel<KG, NTW, PF>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
     return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
 }
@@ -615,7 +615,7 @@ template <int KG>
 int launch_columns(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
 {
     if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 1, true>>(); rc != MADDNESS_OK) return rc;
-    note_kernel("fused_mfma_kernel, A by columns, few rows, blocks of columns", __PRETTY_FUNCTION__);
+    note_kernel("fused_blocks_kernel, A by columns", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
     return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
 }
@@ -624,7 +624,7 @@ template <int KG>
 int launch_codes(const BlockArgs &a, int grid, size_t lds, hipStream_t stream)
 {
     if (int rc = allow_full_lds<fused_blocks_kernel<KG, 1, 1, false, false, 0, true>>(); rc != MADDNESS_OK) return rc;
-    note_kernel("mfma_scan_kernel, blocks of columns", __PRETTY_FUNCTION__);
+    note_kernel("fused_blocks_kernel, scan", __PRETTY_FUNCTION__);
     hipLaunchKernelGGL((fused_blocks_kernel<KG, 1, 1, false, false, 0, true>), dim3(grid), dim3(kBlockThreads), lds, stream, a);
     return check_hip(hipGetLastError(), "launch fused_blocks_kernel");
 }
@@ -667,6 +667,10 @@ int launch_averaged_tiles(const BlockArgs &a, int kb, int grid, size_t lds, hipS
         if (a.tile_shift == 3) return launch_averaged<KG, 3>(a, kb, grid, lds, stream);
     return launch_averaged<KG, 2>(a, kb, grid, lds, stream);
 }
+
+// The options that say how many regions and workgroups the phased kernels take leave this one out: what they are set for is to
+// reach those kernels with few rows.
+bool left_out() { return option(MADDNESS_OPT_PHASED_ROWS) || option(MADDNESS_OPT_MAX_WORKGROUPS); }
 
 // How a call is cut up.
 struct Plan {
@@ -830,8 +834,7 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
 {
     const int es = A.elem_bytes(), C = p.C;
     if (A.col_major || C > 64 || (int64_t)p.D * es > kMaxRowBytes || N < 16 || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
-    // (these options are about the phased kernel: how many regions it takes)
-    if (option(MADDNESS_OPT_PHASED_ROWS) || option(MADDNESS_OPT_MAX_WORKGROUPS)) return 1;
+    if (left_out()) return 1;
     BlockArgs a{};
     a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.row_bytes = p.D * es; a.D = p.D; a.dtype = A.dtype;
     a.N = N;
@@ -890,7 +893,7 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
 {
     const int es = A.elem_bytes(), C = p.C;
     if (!A.col_major || C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
-    if (option(MADDNESS_OPT_PHASED_ROWS) || option(MADDNESS_OPT_MAX_WORKGROUPS) || option(MADDNESS_OPT_COLS_RUN)) return 1;
+    if (left_out() || option(MADDNESS_OPT_COLS_RUN)) return 1;
     const int KC = kernel_codebooks(C);
     if (KC == 0) return 1;
     BlockArgs a{};
@@ -952,6 +955,7 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
 {
     const int C = p.C;
     if (!A.plain() || C > 64 || C % 16 != 0 || (int64_t)p.D * 4 > kMaxRowBytes || N < 16 || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (left_out()) return 1;
     BlockArgs a{};
     a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * 4; a.row_bytes = p.D * 4; a.D = p.D; a.dtype = A.dtype;
     a.N = N;
@@ -1002,6 +1006,7 @@ int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, co
                        const float *offset, float *out, int64_t ldo, uint16_t *acc, hipStream_t stream)
 {
     if (C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (left_out()) return 1;
     int KC = 0;
     for (int s : {64, 48, 32, 24, 16, 8, 4})
         if (s >= C) KC = s;
@@ -1064,6 +1069,7 @@ int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, 
 {
     const int es = A.elem_bytes(), C = p.C;
     if (C > 64 || N < 16 || N >= (1LL << 36)) return 1;
+    if (left_out()) return 1;
     int KC = 0;
     for (int s : {64, 48, 32, 24, 16, 8, 4})
         if (s >= C) KC = s;

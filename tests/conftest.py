@@ -27,3 +27,14 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(params=[True, False], ids=["auto", "no_blocks"])
+def blocks(request):
+    """Every shape twice: with the library's own choice of kernels, and without the one that works by blocks of rows and columns, so
+    that the kernels beside it are reached with the shapes that it would take."""
+    import paper_2106_10860_amd as m
+    if not request.param:
+        m.maddness_set_option(m.MADDNESS_OPT_MAX_WORKGROUPS, 1 << 20)       # (more than any of them launches)
+    yield request.param
+    m.maddness_set_option(m.MADDNESS_OPT_MAX_WORKGROUPS, 0)

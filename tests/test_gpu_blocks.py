@@ -64,7 +64,7 @@ def test_blocks_of_rows_and_columns(mad, case):
 
     out, acc, codes, kernel = run()
     torch.cuda.synchronize()
-    assert "blocks of columns" in kernel, kernel
+    assert kernel.startswith("fused_blocks_kernel, A by rows"), kernel
     if N <= 2048:
         want_out, want_acc, want_codes = oracle.encode_scan(A_d.float().cpu().numpy().copy(), sd, th, luts, scale, offset)
         assert (codes.cpu().numpy() == want_codes).all()
@@ -117,7 +117,7 @@ def test_blocks_of_a_stored_by_columns(mad, case):
 
     out, acc, codes, kernel = run()
     torch.cuda.synchronize()
-    assert "few rows, blocks of columns" in kernel, kernel
+    assert kernel.startswith("fused_blocks_kernel, A by columns"), kernel
     if N <= 2049:
         want_out, want_acc, want_codes = oracle.encode_scan(A_d.float().t().cpu().numpy().copy(), sd, th, luts, scale, offset)
         assert (codes.cpu().numpy() == want_codes).all()
@@ -220,7 +220,7 @@ def test_scan_by_blocks(mad, case):
         return full, acc, kernel
 
     got, got_acc, kernel = run()
-    assert kernel.startswith("mfma_scan_kernel, blocks of columns"), kernel
+    assert kernel.startswith("fused_blocks_kernel, scan"), kernel
     only = run(False)[1] if got_acc is not None else None
     try:
         mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)

@@ -189,7 +189,7 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "N%d_D%d_M%d_C%d_p%d_%d" % s)
-def test_parity_random_parameters(mad, shape):
+def test_parity_random_parameters(mad, shape, blocks):
     N, D, M, C, lda_pad, ldo_pad = shape
     print("case", shape, flush=True)
     rng = np.random.default_rng(hash(shape) % (1 << 31))
@@ -368,7 +368,7 @@ def test_empty_input_is_a_no_op(mad):
 
 
 @pytest.mark.parametrize("cfg", [1, 2, 3, 6])
-def test_parity_paper_shaped_workloads(mad, cfg):
+def test_parity_paper_shaped_workloads(mad, cfg, blocks):
     """Workloads 1-3 and 6 in full, with learned trees and ridge prototypes."""
     from paper_2106_10860_amd.learn import learn
     w = wl.get_workload(cfg)
@@ -813,8 +813,9 @@ TYPED_SHAPES = [
 
 # every shape with the library's own choice of kernels (run 0); the run length of the column kernels on the
 # vector ALUs (1, 2, 4 rows per lane) only where it matters: many rows, tables in LDS
-TYPED_CASES = [pytest.param(s, r, id="N%d_D%d_M%d_C%d_p%d-%s" % (*s, "run%d" % r if r else "auto"))
-               for s in TYPED_SHAPES for r in (0, 1, 2, 4) if r == 0 or (s[0] >= 65536 and s[2] > 64)]
+# (-1: without the kernel by blocks of rows and columns)
+TYPED_CASES = [pytest.param(s, r, id="N%d_D%d_M%d_C%d_p%d-%s" % (*s, "run%d" % r if r > 0 else "no_blocks" if r else "auto"))
+               for s in TYPED_SHAPES for r in (0, -1, 1, 2, 4) if r <= 0 or (s[0] >= 65536 and s[2] > 64)]
 
 
 @pytest.mark.parametrize("shape,run", TYPED_CASES)
@@ -825,7 +826,9 @@ def test_parity_typed_and_column_major(mad, shape, dtype, run, options):
     print("case typed", shape, dtype, run, flush=True)
     # "auto": the library's own choice (many rows: the scan on the matrix cores); "runN": the
     # column kernels on the vector ALUs with N rows per lane
-    if run:
+    if run < 0:
+        options(mad.MADDNESS_OPT_MAX_WORKGROUPS, 1 << 20)
+    elif run:
         options(mad.MADDNESS_OPT_COLS_RUN, run)
         options(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_NO_MATRIX_CORES)
     rng = np.random.default_rng(N + D + C)
@@ -971,7 +974,7 @@ MFMA_SHAPES = [
 
 
 @pytest.mark.parametrize("shape", MFMA_SHAPES, ids=lambda s: "N%d_M%d_C%d" % s)
-@pytest.mark.parametrize("vector_only", [False, True], ids=["matrix", "vector"])
+@pytest.mark.parametrize("vector_only", [None, False, True], ids=["matrix", "no_blocks", "vector"])
 def test_scan_on_matrix_cores(mad, shape, vector_only, options):
     """Random codes and full-range table bytes: the int8 matrix-core scan (and, with the
     switch set, the vector-ALU kernels on the same inputs) against the oracle's exact sum."""
@@ -980,6 +983,8 @@ def test_scan_on_matrix_cores(mad, shape, vector_only, options):
     print("case matrix-core scan", shape, vector_only, flush=True)
     if vector_only:
         options(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_NO_MATRIX_CORES)
+    elif vector_only is not None:               # without the kernel by blocks of rows and columns
+        options(mad.MADDNESS_OPT_MAX_WORKGROUPS, 1 << 20)
     rng = np.random.default_rng(N + M + C)
     packed = oracle.pack(rng.integers(0, 16, size=(N, C), dtype=np.uint8))
     luts_h = rng.integers(0, 256, size=(C, 16, M), dtype=np.uint8)
@@ -1000,7 +1005,8 @@ def test_scan_on_matrix_cores(mad, shape, vector_only, options):
     assert (view.cpu().numpy() == want_out).all(), "out not bit-identical"
     assert (full[:, M:] == -3.0).all(), "wrote outside the output columns"
     if not vector_only:
-        assert "mfma_scan_kernel" in mad.maddness_last_kernel()
+        kernel = mad.maddness_last_kernel()
+        assert kernel.startswith("mfma_scan_kernel") or (vector_only is None and kernel.startswith("fused_blocks_kernel, scan")), kernel
     out2, _ = mad.maddness_scan(C, dev(packed), dev(luts_h), dev(scale_h), dev(offset_h))
     torch.cuda.synchronize()
     assert (out2.cpu().numpy() == want_out).all()
@@ -1010,7 +1016,7 @@ def test_scan_on_matrix_cores(mad, shape, vector_only, options):
 
 
 @pytest.mark.parametrize("seed", [11, 12, 13])
-def test_selected_kernels_against_general_kernels_on_random_shapes(mad, seed, options):
+def test_selected_kernels_against_general_kernels_on_random_shapes(mad, seed, options, blocks):
     """Many random valid shapes (sizes around the kernels' switch points, strides, optional outputs,
     element types, storage orders): whatever kernel the library selects gives the bits of its general
     kernels, which the tests above hold against the oracle."""

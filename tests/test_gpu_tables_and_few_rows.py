@@ -47,7 +47,7 @@ FEW = [
 
 
 @pytest.mark.parametrize("shape", FEW, ids=lambda s: "N%d_D%d_M%d_C%d_at%d" % s)
-def test_tables_in_registers(mad, shape):
+def test_tables_in_registers(mad, shape, blocks):
     import torch
     N, D, M, C, at = shape
     print("case", shape, flush=True)
@@ -62,7 +62,7 @@ def test_tables_in_registers(mad, shape):
     out = mad.maddness_encode_scan(params, dev(A), luts_d, dev(scale), dev(offset), acc=acc, codes=codes)
     kernel = mad.maddness_last_kernel()
     torch.cuda.synchronize()
-    assert kernel.startswith("fused_mfma_kernel"), kernel
+    assert kernel.startswith("fused_mfma_kernel, A by rows") or (blocks and kernel.startswith("fused_blocks_kernel, A by rows")), kernel
     assert (codes.cpu().numpy() == want_codes).all()
     assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
     assert (out.cpu().numpy() == want_out).all()
@@ -74,7 +74,7 @@ def test_tables_in_registers(mad, shape):
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "u8"])
 @pytest.mark.parametrize("shape", [(1, 40, 512, 64, 0), (63, 40, 516, 64, 1), (16385, 64, 68, 16, 3), (4099, 48, 256, 32, 0),
                                    (4097, 40, 512, 64, 5), (40000, 32, 64, 32, 2)], ids=lambda s: "N%d_D%d_M%d_C%d_p%d" % s)
-def test_by_columns_few_rows(mad, shape, dtype):
+def test_by_columns_few_rows(mad, shape, dtype, blocks):
     import torch
     N, D, M, C, pad = shape
     print("case", shape, dtype, flush=True)
@@ -91,7 +91,8 @@ def test_by_columns_few_rows(mad, shape, dtype):
     out = mad.maddness_encode_scan_typed(params, A_d, dev(luts), dev(scale), dev(offset), col_major=True, acc=acc, codes=codes)
     kernel = mad.maddness_last_kernel()
     torch.cuda.synchronize()
-    assert kernel.startswith("fused_mfma_kernel, A by columns, few rows"), kernel
+    assert kernel.startswith("fused_mfma_kernel, A by columns, few rows") or (
+        blocks and kernel.startswith("fused_blocks_kernel, A by columns")), kernel
     assert (codes.cpu().numpy() == want_codes).all()
     assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
     assert (out.cpu().numpy() == want_out).all()
@@ -104,7 +105,7 @@ def test_by_columns_few_rows(mad, shape, dtype):
                                    (999, 505, 257, 31, 7, 5), (4097, 768, 250, 48, 0, 0), (32769, 97, 40, 7, 0, 3),
                                    (777, 1009, 193, 57, 0, 7), (70, 1993, 130, 63, 2, 0)],
                          ids=lambda s: "N%d_D%d_M%d_C%d_p%d_o%d" % s)
-def test_narrow_rows_of_any_shape(mad, shape, dtype):
+def test_narrow_rows_of_any_shape(mad, shape, dtype, blocks):
     import torch
     N, D, M, C, pad, before = shape
     print("case", shape, dtype, flush=True)
@@ -121,7 +122,7 @@ def test_narrow_rows_of_any_shape(mad, shape, dtype):
     out = mad.maddness_encode_scan_typed(params, A_d, dev(luts), dev(scale), dev(offset), acc=acc, codes=codes)
     kernel = mad.maddness_last_kernel()
     torch.cuda.synchronize()
-    assert kernel.startswith("fused_mfma_kernel, A by rows"), kernel
+    assert kernel.startswith("fused_mfma_kernel, A by rows") or (blocks and kernel.startswith("fused_blocks_kernel, A by rows")), kernel
     assert (codes.cpu().numpy() == want_codes).all()
     assert (acc.cpu().numpy().view(np.uint16) == want_acc).all()
     assert (out.cpu().numpy() == want_out).all()
@@ -155,18 +156,18 @@ def test_rows_of_more_than_2_gib(mad, dtype, D, C, M):
 FASTER = [
     # tables between 64 KiB and what the general kernel holds at once: padding of codebooks and columns decides, and rows
     ((1, 1500, 656, 12, "f32", False), "scan_kernel"), ((239, 1500, 592, 12, "f32", False), "scan_kernel"),
-    ((5257, 510, 300, 16, "f32", False), "fused_mfma"), ((120, 2001, 340, 16, "f32", False), "scan_kernel"),
-    ((2000, 300, 250, 30, "f32", False), "fused_mfma"), ((6, 333, 96, 50, "f32", False), "scan_kernel"),
+    ((5257, 510, 300, 16, "f32", False), "fused_blocks"), ((120, 2001, 340, 16, "f32", False), "scan_kernel"),
+    ((2000, 300, 250, 30, "f32", False), "fused_blocks"), ((6, 333, 96, 50, "f32", False), "scan_kernel"),
     ((125, 1000, 288, 20, "f32", False), "fused_mfma"), ((430, 1500, 780, 12, "bf16", False), "scan_kernel"),
-    ((378, 333, 224, 30, "bf16", False), "fused_mfma"), ((1, 256, 172, 40, "u8", False), "scan_kernel"),
+    ((378, 333, 224, 30, "bf16", False), "fused_blocks"), ((1, 256, 172, 40, "u8", False), "scan_kernel"),
     ((16384, 1500, 592, 12, "f32", False), "fused_mfma"), ((1787, 512, 112, 40, "f32", False), "scan_kernel"),
-    ((1000, 256, 92, 64, "f32", False), "fused_mfma"), ((1, 256, 72, 64, "f32", False), "scan_kernel"),
+    ((1000, 256, 92, 64, "f32", False), "fused_blocks"), ((1, 256, 72, 64, "f32", False), "scan_kernel"),
     # narrow rows, small tables: the split values alone or whole rows
     ((32767, 250, 33, 15, "f16", False), "scan_kernel"), ((32768, 250, 33, 15, "f16", False), "fused_mfma"),
     ((53325, 85, 20, 16, "u8", False), "scan_kernel"), ((40000, 716, 5, 4, "u8", False), "scan_kernel"),
     ((33000, 1558, 92, 2, "f16", False), "scan_kernel"), ((40001, 174, 8, 22, "bf16", False), "scan_kernel"),
-    ((35000, 426, 42, 53, "u8", False), "fused_mfma"), ((36000, 472, 66, 16, "bf16", False), "fused_mfma"),
-    ((35550, 107, 72, 16, "f16", False), "fused_mfma"), ((34561, 901, 23, 32, "u8", False), "fused_mfma"),
+    ((35000, 426, 42, 53, "u8", False), "fused_mfma"), ((36000, 472, 66, 16, "bf16", False), "fused_blocks"),
+    ((35550, 107, 72, 16, "f16", False), "fused_blocks"), ((34561, 901, 23, 32, "u8", False), "fused_blocks"),
     # A by columns: small tables by the words of their rows, larger ones up to 8192 rows
     ((80000, 40, 8, 16, "f32", True), "scan_kernel"), ((97000, 20, 16, 16, "f16", True), "scan_kernel"),
     ((98304, 20, 16, 16, "f16", True), "fused_mfma"), ((57000, 24, 28, 32, "u8", True), "scan_kernel"),
@@ -400,7 +401,7 @@ def test_by_columns_many_blocks(mad, shape, dtype, options):
 
 
 @pytest.mark.parametrize("seed", range(4))
-def test_selected_kernels_against_general_kernels_at_their_lines(mad, seed, options):
+def test_selected_kernels_against_general_kernels_at_their_lines(mad, seed, options, blocks):
     """Random shapes with rows on either side of every line of the dispatch, odd widths, columns or rows that start on any
     element: whatever kernel the library selects gives the bits of its general kernels."""
     import torch
