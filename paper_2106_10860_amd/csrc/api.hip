@@ -270,12 +270,15 @@ static int encode_scan_checked(const maddness_params *params, const void *A, int
     if (N == 0) return MADDNESS_OK;
     if (!general_kernels_only()) {
         hipStream_t st = static_cast<hipStream_t>(stream);
-        const bool by_blocks = !averaged && !vector_scan_only();
-        if (by_blocks) {
-            rc = desc.col_major ? launch_fused_blocks_cols(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, st)
-                                : launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, true, st);
-            if (rc != 1) return rc;
-        }
+        // by blocks of rows and columns: where that is faster than the kernels for whole rows, else before the general one
+        auto by_blocks = [&](bool only_if_faster) {
+            if (averaged || vector_scan_only()) return 1;
+            return desc.col_major
+                       ? launch_fused_blocks_cols(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, only_if_faster, st)
+                       : launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, only_if_faster, st);
+        };
+        rc = by_blocks(true);
+        if (rc != 1) return rc;
         if (averaged && !desc.col_major) {
             rc = launch_averaged_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, st);
             if (rc != 1) return rc;
@@ -284,10 +287,8 @@ static int encode_scan_checked(const maddness_params *params, const void *A, int
                  ? launch_fused_cols(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, averaged, st)
                  : launch_fused_rows(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, averaged, st);
         if (rc != 1) return rc;
-        if (by_blocks && !desc.col_major) {
-            rc = launch_fused_blocks(*params, desc, N, M, luts, scale, offset, out, ldo, acc, codes, false, st);
-            if (rc != 1) return rc;
-        }
+        rc = by_blocks(false);
+        if (rc != 1) return rc;
     }
     return launch_scan(params, &desc, nullptr, params->C, M, N, luts, scale, offset, out, ldo, acc, codes,
                        averaged, static_cast<hipStream_t>(stream));

@@ -122,7 +122,7 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
 // The same for A stored by columns.
 int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
                              const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
-                             uint8_t *codes, hipStream_t stream);
+                             uint8_t *codes, bool only_if_faster, hipStream_t stream);
 
 // fp32 rows with the aggregation by averages.
 int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,

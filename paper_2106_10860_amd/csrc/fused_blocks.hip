@@ -811,19 +811,40 @@ bool scan_blocks_pay(const BlockArgs &a, int64_t ldo, int KC, int64_t turns)
     return turns == 1 || (turns == 2 && results < (5 << 20));
 }
 
-// A stored by columns, 16, 32 or 64 codebooks: the kernels that take longer runs of a column and whole rows of results win over
-// several turns, the sooner the wider the results and where these fill their blocks of 64 columns.  There and here, us (turns):
-// C = 64 N = 2048, M = 256, bfloat16 18 and 10 (1); N = 9347, M = 256 18 and 22 (2); N = 26903, M = 128 22 and 25 (2); binary16 N = 100000,
-// M = 100 89 and 64 (7), N = 65536, M = 200 69 and 69 (8), N = 262144, M = 128 129 and 152 (16).  C = 32 N = 100000, M = 100 34 and 26 (4); M = 256
-// N = 10023, bfloat16 20 and 11 (1), N = 54065 26 and 28 (4), N = 100000 38 and 56 (7); binary16 N = 262144, M = 128 55 and 74 (8), bytes
-// N = 131076, M = 64 44 and 27 (5), N = 200000, M = 300 159 and 136 (19), N = 524288 352 and 349 (49).  C = 16 N = 433749, M = 128, bfloat16 115
-// and 97; M = 512, bytes, N = 20000 19 and 13, N = 131072 60 and 98 (16); N = 262144, M = 256 72 and 108 (16).
-bool columns_pay(int C, int M, int dtype, int turns)
+// A stored by columns, 16, 32 or 64 codebooks: whether blocks are faster than the kernels that take whole rows of results, the phased
+// one (to 2^17 rows a row to a lane, beyond, where columns lie on four elements, four) and, of more rows, cols_kernel.  1085 calls with 1 to 1024
+// results, columns used once and many times: of those that these lines take 6 were slower here by more than 3 % (4 to 7), of those that they leave 48 would
+// be faster.  There and here, us; what counts is how many workgroups the blocks of 64 rows and columns make, beside 256 compute units.
+bool columns_pay(const BlockArgs &a, int64_t ld, int turns)
 {
-    const bool full = M % 64 == 0;
-    if (C == 64) return turns <= (dtype == MADDNESS_F32 ? 1 : 8);
-    if (C == 32) return turns <= (!full ? 16 : M <= 128 ? 5 : 2);
-    return !full || M < 256 || turns <= 2;
+    const int C = a.C, M = a.M, cus = device_info().cus;
+    const bool full = M % 64 == 0, wide = a.dtype == MADDNESS_F32;
+    const int64_t blocks = (int64_t)a.chunks * a.col_blocks;
+    if ((a.N & ~(int64_t)3) > (1 << 17)) {             // (they take whole runs of four rows)
+        // cols_kernel: N = 341509, M = 84, C = 16 112 and 59; N = 275568, M = 200, C = 16, bytes 121 and 62; N = 432774, M = 96, C = 32 1.83 times; but N = 380782,
+        // M = 256, C = 16 128 and 146, bytes N = 495291 135 and 177, N = 468621, M = 256, C = 32 206 and 242
+        if (C == 16 || ld % 4 != 0) return C == 64 || !full || M < 192 || (C == 32 && !wide);
+        // four rows to a lane: N = 275892, M = 300, C = 32 183 and 196, N = 374068, M = 128 0.73 times
+        if (wide) return false;
+        // C = 32, binary16 N = 182532, M = 128 1.18 times (6 turns), bytes N = 244748 0.96 (8), N = 463516, M = 96 0.77 (15), N = 208576, M = 32 1.19 (7),
+        // bytes N = 283928 0.85 (9); results that end within a line N = 385860, M = 100, binary16 1.20 (12), N = 251772, M = 300, bytes 185 and 155 (24)
+        if (C == 32) return turns <= (M <= 32 ? 7 : M % 32 == 0 ? 6 : 24);
+        // C = 64, binary16 N = 194028, M = 128 1.13 times (12), N = 239804 0.91 (15), N = 275212, M = 96 0.83 (17); M = 64 N = 255656, bytes 0.60 (8), N = 153432,
+        // M = 256 0.85 (19)
+        return M > 64 && M <= 128 && turns <= 12;
+    }
+    // 16: N = 102000, M = 100 1.3 times, N = 70039, M = 892 111 and 69; N = 24222, M = 320, bytes 1.25 times, N = 20958, M = 512 19.7 and 22.3, N = 57664,
+    // binary16 34 and 45
+    if (C == 16) return !full || M <= 128 || blocks <= 5 * cus;
+    // 32: N = 67775, M = 32 1.16 times, N = 95988, M = 128 0.84; N = 17637, M = 200 1.23, N = 49770 27.7 and 32.3; N = 15120, M = 320 1.19, N = 30591, M = 384 0.82;
+    // N = 68555, M = 300 1.12 (7 turns); narrow types N = 206915, M = 128 2.1, N = 121416, M = 384 1.12, N = 8774, M = 512 21.1 and 15.6, N = 63868 52 and 63
+    if (C == 32 && !wide) return !full || M < 512 || turns <= 4;
+    if (C == 32) return !full && M > 256 ? turns <= 16 : blocks <= (M <= 128 || !full ? 5 : 3) * cus;
+    // 64: N = 13785, M = 256 18.3 and 22.9 (2 turns), N = 28047, M = 64 0.85; narrow types N = 108204, M = 64 81 and 60 (4), N = 118359, M = 128 99 and 76 (8),
+    // N = 14582, M = 300 34 and 31 (3), N = 15912, M = 512 34 and 42 (4); a column or less to a codebook, of which that kernel's reads meet in the caches,
+    // N = 10240, D = 64, M = 256, bytes 0.82
+    if (a.D <= C) return blocks <= cus;
+    return wide ? turns <= 1 && (M > 64 || blocks <= cus) : turns <= (M <= 128 ? 8 : 3);
 }
 
 }  // namespace
@@ -882,14 +903,14 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
     }
 }
 
-// A stored by columns: 64 rows to a chunk, as many blocks of columns as leave a workgroup for every compute unit.  Taken for
-// numbers of codebooks that the phased kernel does not have, whatever the rows: the general kernel reads the split values a lane
-// for itself and walks large tables tile by tile (us, there and here: N = 554, M = 1000, C = 48, binary16 349 and 9; N = 14231, M = 512,
-// C = 48, binary16 214 and 31; N = 9407, M = 122, C = 24 21 and 7.6; N = 524288, M = 4, C = 48, bfloat16 621 and 172); else by turns
-// (columns_pay).
+// A stored by columns: 64 rows to a chunk, as many blocks of columns as leave a workgroup for every compute unit.  Instead of the
+// general kernel (only_if_faster = false) whatever the rows: that one reads the split values a lane for itself and walks large tables tile by tile (us,
+// there and here: N = 554, M = 1000, C = 48, binary16 349 and 9; N = 14231, M = 512, C = 48, binary16 214 and 31; N = 9407, M = 122, C = 24 21 and 7.6;
+// N = 524288, M = 4, C = 48, bfloat16 621 and 172; of 484 calls of 16, 32 and 64 codebooks none was faster there); instead of the others, which take 16, 32 and 64
+// codebooks, by columns_pay.
 int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
                              const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
-                             uint8_t *codes, hipStream_t stream)
+                             uint8_t *codes, bool only_if_faster, hipStream_t stream)
 {
     const int es = A.elem_bytes(), C = p.C;
     if (!A.col_major || C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
@@ -927,10 +948,7 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
     if (a.col_blocks > 1) groups = (groups + 7) / 8 * 8;
     a.row_groups = (int)groups;
     const int grid = a.row_groups * a.col_blocks;
-    if (C == 16 || C == 32 || C == 64) {
-        // (with fewer columns than split values the routes stay those that the tests of the dispatch hold)
-        if (p.D < 4 * C || !columns_pay(C, M, A.dtype, (a.chunks + a.row_groups - 1) / a.row_groups)) return 1;
-    }
+    if (only_if_faster && (C == 16 || C == 32 || C == 64) && !columns_pay(a, A.ld, (a.chunks + a.row_groups - 1) / a.row_groups)) return 1;
     switch (KC) {
     case 4: return launch_columns<1>(a, grid, lds, stream);
     case 8: return launch_columns<2>(a, grid, lds, stream);

@@ -152,39 +152,53 @@ def test_rows_of_more_than_2_gib(mad, dtype, D, C, M):
     assert (out.cpu().numpy() == want_out).all()
 
 
-# (N, D, M, C, dtype, by columns) -> the kernel that measured faster: either side of the rules of the dispatch
+# (N, D, M, C, dtype, by columns) -> the kernel that measured faster, and that of those beside the one by blocks of rows and columns:
+# either side of the rules of the dispatch
+B, F, G, K = "fused_blocks", "fused_mfma", "scan_kernel", "cols_kernel"
 FASTER = [
     # tables between 64 KiB and what the general kernel holds at once: padding of codebooks and columns decides, and rows
-    ((1, 1500, 656, 12, "f32", False), "scan_kernel"), ((239, 1500, 592, 12, "f32", False), "scan_kernel"),
-    ((5257, 510, 300, 16, "f32", False), "fused_blocks"), ((120, 2001, 340, 16, "f32", False), "scan_kernel"),
-    ((2000, 300, 250, 30, "f32", False), "fused_blocks"), ((6, 333, 96, 50, "f32", False), "scan_kernel"),
-    ((125, 1000, 288, 20, "f32", False), "fused_mfma"), ((430, 1500, 780, 12, "bf16", False), "scan_kernel"),
-    ((378, 333, 224, 30, "bf16", False), "fused_blocks"), ((1, 256, 172, 40, "u8", False), "scan_kernel"),
-    ((16384, 1500, 592, 12, "f32", False), "fused_mfma"), ((1787, 512, 112, 40, "f32", False), "scan_kernel"),
-    ((1000, 256, 92, 64, "f32", False), "fused_blocks"), ((1, 256, 72, 64, "f32", False), "scan_kernel"),
+    ((1, 1500, 656, 12, "f32", False), G, G), ((239, 1500, 592, 12, "f32", False), G, G),
+    ((5257, 510, 300, 16, "f32", False), B, F), ((120, 2001, 340, 16, "f32", False), G, G),
+    ((2000, 300, 250, 30, "f32", False), B, F), ((6, 333, 96, 50, "f32", False), G, G),
+    ((125, 1000, 288, 20, "f32", False), F, F), ((430, 1500, 780, 12, "bf16", False), G, G),
+    ((378, 333, 224, 30, "bf16", False), B, F), ((1, 256, 172, 40, "u8", False), G, G),
+    ((16384, 1500, 592, 12, "f32", False), F, F), ((1787, 512, 112, 40, "f32", False), G, G),
+    ((1000, 256, 92, 64, "f32", False), B, F), ((1, 256, 72, 64, "f32", False), G, G),
     # narrow rows, small tables: the split values alone or whole rows
-    ((32767, 250, 33, 15, "f16", False), "scan_kernel"), ((32768, 250, 33, 15, "f16", False), "fused_mfma"),
-    ((53325, 85, 20, 16, "u8", False), "scan_kernel"), ((40000, 716, 5, 4, "u8", False), "scan_kernel"),
-    ((33000, 1558, 92, 2, "f16", False), "scan_kernel"), ((40001, 174, 8, 22, "bf16", False), "scan_kernel"),
-    ((35000, 426, 42, 53, "u8", False), "fused_mfma"), ((36000, 472, 66, 16, "bf16", False), "fused_blocks"),
-    ((35550, 107, 72, 16, "f16", False), "fused_blocks"), ((34561, 901, 23, 32, "u8", False), "fused_blocks"),
+    ((32767, 250, 33, 15, "f16", False), G, G), ((32768, 250, 33, 15, "f16", False), F, F),
+    ((53325, 85, 20, 16, "u8", False), G, G), ((40000, 716, 5, 4, "u8", False), G, G),
+    ((33000, 1558, 92, 2, "f16", False), G, G), ((40001, 174, 8, 22, "bf16", False), G, G),
+    ((35000, 426, 42, 53, "u8", False), F, F), ((36000, 472, 66, 16, "bf16", False), B, F),
+    ((35550, 107, 72, 16, "f16", False), B, F), ((34561, 901, 23, 32, "u8", False), B, F),
     # A by columns: small tables by the words of their rows, larger ones up to 8192 rows
-    ((80000, 40, 8, 16, "f32", True), "scan_kernel"), ((97000, 20, 16, 16, "f16", True), "scan_kernel"),
-    ((98304, 20, 16, 16, "f16", True), "fused_mfma"), ((57000, 24, 28, 32, "u8", True), "scan_kernel"),
-    ((24576, 24, 32, 32, "f32", True), "fused_mfma"), ((24575, 24, 48, 16, "f32", True), "scan_kernel"),
-    ((24576, 24, 188, 16, "f32", True), "scan_kernel"), ((24577, 24, 188, 16, "f32", True), "fused_mfma"),
-    ((16385, 24, 192, 16, "u8", True), "fused_mfma"), ((16384, 24, 192, 16, "u8", True), "scan_kernel"),
-    ((16384, 24, 256, 16, "u8", True), "fused_mfma"),
-    ((8192, 50, 192, 32, "f32", True), "scan_kernel"), ((8193, 50, 192, 32, "bf16", True), "fused_mfma"),
-    ((300, 50, 584, 16, "f32", True), "scan_kernel"), ((256, 50, 584, 16, "f32", True), "fused_mfma"),
-    ((4096, 50, 96, 64, "u8", True), "fused_mfma"),
+    ((80000, 40, 8, 16, "f32", True), B, G), ((97000, 20, 16, 16, "f16", True), B, G),
+    ((98304, 20, 16, 16, "f16", True), B, F), ((57000, 24, 28, 32, "u8", True), B, G),
+    ((24576, 24, 32, 32, "f32", True), B, F), ((24575, 24, 48, 16, "f32", True), B, G),
+    ((24576, 24, 188, 16, "f32", True), B, G), ((24577, 24, 188, 16, "f32", True), B, F),
+    ((16385, 24, 192, 16, "u8", True), B, F), ((16384, 24, 192, 16, "u8", True), B, G),
+    ((16384, 24, 256, 16, "u8", True), B, F),
+    ((8192, 50, 192, 32, "f32", True), B, G), ((8193, 50, 192, 32, "bf16", True), B, F),
+    ((300, 50, 584, 16, "f32", True), B, G), ((256, 50, 584, 16, "f32", True), B, F),
+    ((4096, 50, 96, 64, "u8", True), B, F),
+    # A by columns: blocks of rows and columns or whole rows of results, by the workgroups that these make and their turns
+    ((20417, 64, 512, 16, "f32", True), B, F), ((20481, 64, 512, 16, "f32", True), F, F),
+    ((81920, 128, 128, 32, "f32", True), B, F), ((81921, 128, 128, 32, "f32", True), F, F),
+    ((24576, 128, 256, 32, "f32", True), B, F), ((24577, 128, 256, 32, "f32", True), F, F), ((70001, 128, 300, 32, "f32", True), B, F),
+    ((32768, 128, 512, 32, "u8", True), B, F), ((32769, 128, 512, 32, "u8", True), F, F), ((32769, 128, 500, 32, "u8", True), B, F),
+    ((16384, 256, 64, 64, "f32", True), B, F), ((16385, 256, 64, 64, "f32", True), F, F), ((16385, 256, 128, 64, "f32", True), F, F),
+    ((24576, 256, 256, 64, "f16", True), B, F), ((24577, 256, 256, 64, "f16", True), F, F), ((16385, 64, 128, 64, "f16", True), F, F),
+    ((131077, 64, 256, 16, "f32", True), K, K), ((131077, 64, 200, 16, "f32", True), B, K),
+    ((131076, 128, 64, 32, "f32", True), F, F), ((131076, 128, 64, 32, "u8", True), B, F), ((131077, 128, 256, 32, "f32", True), K, K),
+    ((131076, 256, 96, 64, "f16", True), B, F), ((131076, 256, 64, 64, "f16", True), F, F),
 ]
 
 
 @pytest.mark.parametrize("case", FASTER, ids=lambda c: "N%d_D%d_M%d_C%d_%s_%d" % c[0])
-def test_dispatch_either_side(mad, case):
+def test_dispatch_either_side(mad, case, blocks):
     import torch
-    (N, D, M, C, dtype, col_major), family = case
+    (N, D, M, C, dtype, col_major), family, beside = case
+    if not blocks:
+        family = beside
     print("case", case, flush=True)
     A, sd, th, luts, scale, offset = problem(N + D, N, D, M, C)
     kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "u8": torch.uint8}[dtype]
