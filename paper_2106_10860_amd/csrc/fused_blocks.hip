@@ -812,9 +812,9 @@ bool scan_blocks_pay(const BlockArgs &a, int64_t ldo, int KC, int64_t turns)
 }
 
 // A stored by columns, 16, 32 or 64 codebooks: whether blocks are faster than the kernels that take whole rows of results, the phased
-// one (to 2^17 rows a row to a lane, beyond, where columns lie on four elements, four) and, of more rows, cols_kernel.  1085 calls with 1 to 1024
-// results, columns used once and many times: of those that these lines take 6 were slower here by more than 3 % (4 to 7), of those that they leave 48 would
-// be faster.  There and here, us; what counts is how many workgroups the blocks of 64 rows and columns make, beside 256 compute units.
+// one (to 2^17 rows a row to a lane, beyond, where columns lie on four elements, four) and, of more rows, cols_kernel.  Lines drawn through 1085 calls with 1
+// to 1024 results, columns used once and many times; of 612 others, each after one of its own kind, 10 that they take are slower here by more than 3 % (4 to 17),
+// 21 that they leave would be faster.  There and here, us; what counts is how many workgroups the blocks of 64 rows and columns make, beside 256 compute units.
 bool columns_pay(const BlockArgs &a, int64_t ld, int turns)
 {
     const int C = a.C, M = a.M, cus = device_info().cus;
@@ -822,28 +822,28 @@ bool columns_pay(const BlockArgs &a, int64_t ld, int turns)
     const int64_t blocks = (int64_t)a.chunks * a.col_blocks;
     if ((a.N & ~(int64_t)3) > (1 << 17)) {             // (they take whole runs of four rows)
         // cols_kernel: N = 341509, M = 84, C = 16 112 and 59; N = 275568, M = 200, C = 16, bytes 121 and 62; N = 432774, M = 96, C = 32 1.83 times; but N = 380782,
-        // M = 256, C = 16 128 and 146, bytes N = 495291 135 and 177, N = 468621, M = 256, C = 32 206 and 242
-        if (C == 16 || ld % 4 != 0) return C == 64 || !full || M < 192 || (C == 32 && !wide);
-        // four rows to a lane: N = 275892, M = 300, C = 32 183 and 196, N = 374068, M = 128 0.73 times
-        if (wide) return false;
-        // C = 32, binary16 N = 182532, M = 128 1.18 times (6 turns), bytes N = 244748 0.96 (8), N = 463516, M = 96 0.77 (15), N = 208576, M = 32 1.19 (7),
-        // bytes N = 283928 0.85 (9); results that end within a line N = 385860, M = 100, binary16 1.20 (12), N = 251772, M = 300, bytes 185 and 155 (24)
-        if (C == 32) return turns <= (M <= 32 ? 7 : M % 32 == 0 ? 6 : 24);
-        // C = 64, binary16 N = 194028, M = 128 1.13 times (12), N = 239804 0.91 (15), N = 275212, M = 96 0.83 (17); M = 64 N = 255656, bytes 0.60 (8), N = 153432,
-        // M = 256 0.85 (19)
-        return M > 64 && M <= 128 && turns <= 12;
+        // M = 256, C = 16 128 and 146, bytes N = 495291 135 and 177, N = 468621, M = 256, C = 32 206 and 242; M = 192, C = 16, binary16 1.2 to 1.6 times, where columns
+        // lie on four elements 0.93
+        if (C == 16 || ld % 4 != 0) return C == 64 || !full || M < (ld % 4 != 0 ? 256 : 192) || (C == 32 && !wide);
+        // Four rows to a lane, which pays from some 200000 rows on.  C = 32: N = 149808, M = 32 43 and 35, N = 159528, M = 192 1.38 times, N = 191260, M = 256 0.97, N = 275892, M = 300
+        // 0.94; narrow types N = 172236, M = 64 1.16, N = 199600, M = 256 1.20, N = 255872, M = 64 0.80, N = 285633, M = 192 0.76, N = 172216, M = 512 0.79; results that end
+        // within a line N = 431384, M = 100, bytes 1.23 (14 turns), N = 251772, M = 300 185 and 155 (24).
+        if (C == 32) return M < 512 && (a.N <= (wide ? 170000 : 200000) || (!wide && M > 32 && M % 32 != 0 && turns <= 24));
+        // C = 64: N = 152220, M = 128 1.22 times, N = 267568 0.78, narrow types N = 176504 1.23, N = 228484 0.96; N = 138328, M = 64 0.98, N = 186772, M = 256 0.68
+        return M > 64 && M <= 128 && a.N <= 190000;
     }
     // 16: N = 102000, M = 100 1.3 times, N = 70039, M = 892 111 and 69; N = 24222, M = 320, bytes 1.25 times, N = 20958, M = 512 19.7 and 22.3, N = 57664,
-    // binary16 34 and 45
-    if (C == 16) return !full || M <= 128 || blocks <= 5 * cus;
+    // binary16 34 and 45; N = 104887, M = 100 1.3 times, N = 123476, M = 128 27 and 31
+    if (C == 16) return !full || blocks <= 5 * cus || (M <= 128 && (!wide || 2 * blocks <= 13 * cus));
     // 32: N = 67775, M = 32 1.16 times, N = 95988, M = 128 0.84; N = 17637, M = 200 1.23, N = 49770 27.7 and 32.3; N = 15120, M = 320 1.19, N = 30591, M = 384 0.82;
-    // N = 68555, M = 300 1.12 (7 turns); narrow types N = 206915, M = 128 2.1, N = 121416, M = 384 1.12, N = 8774, M = 512 21.1 and 15.6, N = 63868 52 and 63
-    if (C == 32 && !wide) return !full || M < 512 || turns <= 4;
+    // N = 68555, M = 300 1.12 (7 turns); narrow types N = 206915, M = 128 2.1, N = 121416, M = 384 1.12, N = 8774, M = 512 21.1 and 15.6, N = 63868 52 and 63; a column or
+    // less to a codebook, of which that kernel's reads meet in the caches, N = 17656, M = 192 1.23, N = 78969, M = 320 0.75
+    if (C == 32 && !wide) return !full || M <= 128 || (M < 512 ? a.D > C || blocks <= 4 * cus : turns <= 4);
     if (C == 32) return !full && M > 256 ? turns <= 16 : blocks <= (M <= 128 || !full ? 5 : 3) * cus;
     // 64: N = 13785, M = 256 18.3 and 22.9 (2 turns), N = 28047, M = 64 0.85; narrow types N = 108204, M = 64 81 and 60 (4), N = 118359, M = 128 99 and 76 (8),
-    // N = 14582, M = 300 34 and 31 (3), N = 15912, M = 512 34 and 42 (4); a column or less to a codebook, of which that kernel's reads meet in the caches,
-    // N = 10240, D = 64, M = 256, bytes 0.82
-    if (a.D <= C) return blocks <= cus;
+    // N = 14582, M = 300 34 and 31 (3), N = 15912, M = 512 34 and 42 (4); a column or less to a codebook N = 24988, M = 192, bytes 0.69, N = 88229, D = 64, M = 64, binary16 1.13,
+    // N = 40555, D = 50, M = 64, bytes 0.82
+    if (a.D <= C) return blocks <= (wide || M > 128 || a.D < C ? 1 : 6) * cus;
     return wide ? turns <= 1 && (M > 64 || blocks <= cus) : turns <= (M <= 128 ? 8 : 3);
 }
 

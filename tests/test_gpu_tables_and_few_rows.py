@@ -186,9 +186,11 @@ FASTER = [
     ((24576, 128, 256, 32, "f32", True), B, F), ((24577, 128, 256, 32, "f32", True), F, F), ((70001, 128, 300, 32, "f32", True), B, F),
     ((32768, 128, 512, 32, "u8", True), B, F), ((32769, 128, 512, 32, "u8", True), F, F), ((32769, 128, 500, 32, "u8", True), B, F),
     ((16384, 256, 64, 64, "f32", True), B, F), ((16385, 256, 64, 64, "f32", True), F, F), ((16385, 256, 128, 64, "f32", True), F, F),
-    ((24576, 256, 256, 64, "f16", True), B, F), ((24577, 256, 256, 64, "f16", True), F, F), ((16385, 64, 128, 64, "f16", True), F, F),
-    ((131077, 64, 256, 16, "f32", True), K, K), ((131077, 64, 200, 16, "f32", True), B, K),
-    ((131076, 128, 64, 32, "f32", True), F, F), ((131076, 128, 64, 32, "u8", True), B, F), ((131077, 128, 256, 32, "f32", True), K, K),
+    ((24576, 256, 256, 64, "f16", True), B, F), ((24577, 256, 256, 64, "f16", True), F, F), ((16385, 64, 200, 64, "f16", True), F, F),
+    ((98304, 64, 128, 64, "f16", True), B, F), ((98305, 64, 128, 64, "f16", True), F, F),
+    ((131077, 64, 256, 16, "f32", True), K, K), ((131077, 64, 192, 16, "f32", True), B, K), ((131076, 64, 192, 16, "f32", True), K, K),
+    ((170000, 128, 64, 32, "f32", True), B, F), ((170004, 128, 64, 32, "f32", True), F, F), ((200000, 128, 64, 32, "u8", True), B, F),
+    ((200004, 128, 64, 32, "u8", True), F, F), ((200004, 128, 36, 32, "u8", True), B, F), ((131077, 128, 256, 32, "f32", True), K, K),
     ((131076, 256, 96, 64, "f16", True), B, F), ((131076, 256, 64, 64, "f16", True), F, F),
 ]
 
