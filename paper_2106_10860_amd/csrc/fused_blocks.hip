@@ -733,6 +733,34 @@ Plan choose_plan(int64_t N, int64_t pitch, bool whole, int M, int KC)
     return plan;
 }
 
+// Up to 8 codebooks the phased kernel pays for padding: N = 131072, D = 128, M = 5, C = 8 26 and 13 us (there and here); N = 382808, D = 119, M = 155, C = 7
+// 200 and 115; bytes N = 726104, M = 32 126 and 40.  But it reads a row once for all results, and these blocks once for every 256 of them, of which they
+// write parts of lines.  459 calls that either takes, each after one of its own kind: 15 of those that these lines take are slower here by more than 3 %
+// (4 to 12), of those that they leave 9 would be faster.
+bool few_codebooks_pay(const BlockArgs &a, const Plan &plan)
+{
+    // a block of columns of at most 128: whatever the rows, to 40 turns (N = 932130, D = 176, M = 53 193 and 152); N = 895395, D = 626, M = 65, C = 2 421 and 470 (135)
+    if (plan.tile_shift < 4) return plan.turns <= 64;
+    const int M = a.M;
+    const int64_t results = a.N * M;
+    if (a.dtype == MADDNESS_F32 && a.C == 8 && M % 4 == 0) {
+        // There whole registers of four results.  Whole lines: N = 85003, D = 128, M = 608 63 and 54 (5 turns), N = 580419, D = 240, M = 928 523 and 800 (67), N = 127840, D = 168,
+        // M = 672 93 and 123 (9), N = 99563, D = 128, M = 320 43 and 52 (4); short rows N = 525885, D = 40, M = 736 385 and 328 (9), N = 583765, D = 88, M = 512 318 and 272.  Others: N = 539796, D = 168, M = 524 637 and 430 (35), N = 309841, D = 32, M = 200 121 and 58;
+        // one block of columns, written by 64 bytes there or mostly padding here: N = 210517, D = 244, M = 240 79 and 98 (7), N = 73405, D = 232, M = 156 27 and 32 (3),
+        // N = 487872, D = 212, M = 232 1.14 times (13).
+        if (M % 32 == 0 && a.ldo % 32 == 0) return plan.turns <= (M <= 320 ? 2 : 4) || a.row_bytes < (M <= 512 ? 384 : 320);
+        return plan.turns <= 2 || a.row_bytes < 640 || M > 256 || (M > 160 && M % 16 != 0);
+    }
+    // There results by lines through LDS, 512 columns to a pass: N = 121293, D = 200, M = 286 63 and 56, N = 340947, D = 224, M = 367 181 and 212 (19 turns), N = 286483, D = 128, M = 463 155 and 178 (9), N = 124696, D = 96, M = 415,
+    // binary16 70 and 50; N = 449389, D = 104, M = 617 509 and 353; C = 7 N = 263590, D = 21, M = 984 268 and 310 (259 Mi results).
+    if (a.dtype == MADDNESS_F32) return M > 320 && M <= 512 ? plan.turns <= 4 || a.row_bytes < 512 : M <= 900 || results < (200 << 20);
+    // Narrow types, from where the results leave the last-level cache: bytes N = 613877, D = 24, M = 485 333 and 513, N = 92976, D = 24, M = 418 61 and 46 (37 Mi); N = 154844, D = 84,
+    // M = 886 179 and 211; M = 527, D = 154, binary16 1.52 times, M = 739, D = 184 1.25, M = 612, D = 16 0.89 (508 Mi); bytes M = 308 1.07 (210 Mi), M = 326 0.83 (267 Mi);
+    // whole lines N = 577387, D = 44, M = 800 463 and 370.
+    if (M % 32 == 0 || results < (100 << 20)) return true;
+    return M <= 352 ? results < (250 << 20) : M > 512 && M <= 768 && (a.row_bytes >= 64 || results < (200 << 20));
+}
+
 // Whether this kernel is the faster one.  only_if_faster = false: instead of the general kernel, which no other kernel would
 // take the call from.  Times in us, this kernel's last.
 bool blocks_pay(const BlockArgs &a, int KC, bool whole, const Plan &plan, bool only_if_faster)
@@ -746,14 +774,12 @@ bool blocks_pay(const BlockArgs &a, int KC, bool whole, const Plan &plan, bool o
         if (a.dtype != MADDNESS_F32 && !whole) return false;
     }
     if (!only_if_faster) return true;
+    if (KC <= 8) return few_codebooks_pay(a, plan);
     // One chunk of rows to a workgroup: N = 1891, D = 768, M = 785, C = 48, binary16 45.3 and 11.7; N = 10000, D = 512, M = 100,
     // C = 32 11.5 and 9.1; N = 8192, D = 512, M = 512, C = 32 15.0 and 12.8; N = 4096, D = 512, M = 1005, C = 32 30.6 and 14.5.
     if (plan.turns == 1) return true;
     // Several: the other kernels read a row once for all columns and keep more of it on its way, and the wider and longer the
-    // rows the sooner they win.  Up to 8 codebooks they pay for padding: N = 131072, D = 128, M = 5, C = 8 26 and 13;
-    // N = 521729, D = 64, M = 1000, C = 8 887 and 608; N = 434252, D = 64, M = 256, C = 8 137 and 113; bytes and four codebooks
-    // N = 524288, D = 64, M = 1000 611 and 698.
-    if (KC <= 8) return KC == 8 || a.dtype == MADDNESS_F32;
+    // rows the sooner they win.
     // 16 and 24: N = 65536, D = 192, M = 10, C = 24 26 and 13 (2 turns); N = 248254, D = 256, M = 71, C = 16, bfloat16 65 and 46 (4);
     // N = 524288, D = 120, M = 13, C = 15 82 and 54 (8); N = 1048576, D = 320, M = 10, C = 16 230 and 262 (41);
     // two blocks of columns N = 87536, D = 120, M = 474, C = 15, bfloat16 53 and 67; N = 73759, D = 256, M = 256, C = 16 29 and 39.

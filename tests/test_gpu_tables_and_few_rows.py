@@ -170,6 +170,11 @@ FASTER = [
     ((33000, 1558, 92, 2, "f16", False), G, G), ((40001, 174, 8, 22, "bf16", False), G, G),
     ((35000, 426, 42, 53, "u8", False), F, F), ((36000, 472, 66, 16, "bf16", False), B, F),
     ((35550, 107, 72, 16, "f16", False), B, F), ((34561, 901, 23, 32, "u8", False), B, F),
+    # up to 8 codebooks, several blocks of columns or turns: blocks of rows and columns or whole rows
+    ((76800, 136, 768, 8, "f32", False), B, F), ((76801, 136, 768, 8, "f32", False), F, F), ((76801, 79, 768, 8, "f32", False), B, F),
+    ((95232, 176, 132, 8, "f32", False), B, F), ((95233, 176, 132, 8, "f32", False), F, F), ((95233, 176, 164, 8, "f32", False), B, F),
+    ((131072, 128, 463, 8, "f32", False), B, F), ((131073, 128, 463, 8, "f32", False), F, F),
+    ((209715, 24, 500, 8, "u8", False), B, F), ((209716, 24, 500, 8, "u8", False), F, F),
     # A by columns: small tables by the words of their rows, larger ones up to 8192 rows
     ((80000, 40, 8, 16, "f32", True), B, G), ((97000, 20, 16, 16, "f16", True), B, G),
     ((98304, 20, 16, 16, "f16", True), B, F), ((57000, 24, 28, 32, "u8", True), B, G),
