@@ -763,16 +763,15 @@ bool few_codebooks_pay(const BlockArgs &a, const Plan &plan)
 
 // Whether this kernel is the faster one.  only_if_faster = false: instead of the general kernel, which no other kernel would
 // take the call from.  Times in us, this kernel's last.
-bool blocks_pay(const BlockArgs &a, int KC, bool whole, const Plan &plan, bool only_if_faster)
+bool blocks_pay(const BlockArgs &a, int KC, const Plan &plan, bool only_if_faster)
 {
-    const int64_t tables = 16 * (int64_t)a.C * a.M;
-    if (tables <= 8 * 1024) {
-        // Next to no entries to add: up to 20000 rows of up to 8 codebooks both take as long as a launch (N = 8192, D = 27, M = 3,
-        // C = 4: 6.6 and 6.6; N = 4242, D = 128, M = 15, C = 8, bfloat16: 6.7 and 6.7); narrow rows that are not whole 16-byte
-        // pieces are left to the general kernel, which reads their split values alone.
-        if (KC <= 8 && a.N <= 20000) return false;
-        if (a.dtype != MADDNESS_F32 && !whole) return false;
-    }
+    // Rows of many bytes to a codebook are read whole here; the general kernel asks for 64 bytes of them to a split value, which pays where there are
+    // many of both: N = 13387, D = 1619, M = 17, C = 1, binary16 6.2 and 10.7, N = 12435, D = 1226, M = 81, C = 2 8.7 and 16.0; N = 12233, D = 1090, M = 79, C = 1, bytes 8.0 and 5.9 (13 MiB),
+    // N = 13129, D = 1415, M = 84, C = 5, binary16 11.6 and 11.1 (566 bytes to a codebook).
+    // Few entries to add need no line of their own: N = 8192, D = 27, M = 3, C = 4 both take as long as a launch where calls are made one by one, 4.8 and 3.6 in a graph;
+    // N = 97583, D = 36, M = 3, C = 9, binary16 14.5 and 7.6, N = 5693, D = 44, M = 3, C = 11, binary16 14.4 and 4.0; none of 455 calls with tables of at most 8 KiB was faster there
+    // but for such rows.
+    if (a.row_bytes > 600 * a.C && a.N * a.row_bytes > (16 << 20)) return false;
     if (!only_if_faster) return true;
     if (KC <= 8) return few_codebooks_pay(a, plan);
     // One chunk of rows to a workgroup: N = 1891, D = 768, M = 785, C = 48, binary16 45.3 and 11.7; N = 10000, D = 512, M = 100,
@@ -896,7 +895,7 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
     if (a.row_bytes > 4096 && !whole) return 1;
     const Plan plan = choose_plan(N, a.pitch, whole, M, KC);
     if (plan.rows < 1 || N / plan.rows >= (1 << 30)) return 1;
-    if (!blocks_pay(a, KC, whole, plan, only_if_faster)) return 1;
+    if (!blocks_pay(a, KC, plan, only_if_faster)) return 1;
 
     a.tile_shift = plan.tile_shift; a.col_blocks = plan.col_blocks;
     const int tiles = 1 << plan.tile_shift, ntw = plan.tile_shift == 4 ? 2 : 1;

@@ -165,11 +165,13 @@ FASTER = [
     ((16384, 1500, 592, 12, "f32", False), F, F), ((1787, 512, 112, 40, "f32", False), G, G),
     ((1000, 256, 92, 64, "f32", False), B, F), ((1, 256, 72, 64, "f32", False), G, G),
     # narrow rows, small tables: the split values alone or whole rows
-    ((32767, 250, 33, 15, "f16", False), G, G), ((32768, 250, 33, 15, "f16", False), F, F),
-    ((53325, 85, 20, 16, "u8", False), G, G), ((40000, 716, 5, 4, "u8", False), G, G),
-    ((33000, 1558, 92, 2, "f16", False), G, G), ((40001, 174, 8, 22, "bf16", False), G, G),
+    ((32767, 250, 33, 15, "f16", False), B, G), ((32768, 250, 33, 15, "f16", False), B, F),
+    ((53325, 85, 20, 16, "u8", False), B, G), ((40000, 716, 5, 4, "u8", False), B, G),
+    ((33000, 1558, 92, 2, "f16", False), G, G), ((40001, 174, 8, 22, "bf16", False), B, G),
     ((35000, 426, 42, 53, "u8", False), F, F), ((36000, 472, 66, 16, "bf16", False), B, F),
     ((35550, 107, 72, 16, "f16", False), B, F), ((34561, 901, 23, 32, "u8", False), B, F),
+    # rows of many bytes to a codebook
+    ((6978, 601, 5, 4, "f32", False), B, G), ((6979, 601, 5, 4, "f32", False), G, G), ((6979, 600, 5, 4, "f32", False), B, G),
     # up to 8 codebooks, several blocks of columns or turns: blocks of rows and columns or whole rows
     ((76800, 136, 768, 8, "f32", False), B, F), ((76801, 136, 768, 8, "f32", False), F, F), ((76801, 79, 768, 8, "f32", False), B, F),
     ((95232, 176, 132, 8, "f32", False), B, F), ((95233, 176, 132, 8, "f32", False), F, F), ((95233, 176, 164, 8, "f32", False), B, F),
