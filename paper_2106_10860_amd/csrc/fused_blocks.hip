@@ -680,12 +680,14 @@ struct Plan {
     bool shared;              // two workgroups to a compute unit
 };
 
-// Kernel sizes: codebooks.  0: none (no more than one codebook in eight may be padding).
+// Kernel sizes: codebooks (at most 64).  Padding, up to half of a size, costs less than what else takes such numbers: by rows N = 2361, D = 57, M = 117, C = 3 7.5 us on the
+// general kernel and 3.8, N = 1470, D = 864, M = 3, C = 54, bytes 64 and 5.2, N = 942, D = 720, M = 497, C = 40 26 on the phased kernel and 8.1, N = 395657, D = 198, M = 719, C = 9, bytes
+// 428 and 381; by columns (blocks_pay and launch_fused_blocks_cols say where not) 140 calls 3.6 and, of many rows, 2.3 times as fast.
 int kernel_codebooks(int C)
 {
-    for (int s : {4, 8, 16, 24, 32, 48, 64})
-        if (s >= C) return 8 * (s - C) <= s ? s : 0;
-    return 0;
+    for (int s : {4, 8, 16, 24, 32, 48})
+        if (s >= C) return s;
+    return 64;
 }
 
 Plan make_plan(int64_t N, int64_t pitch, bool whole, int M, int KC, int tile_shift, bool shared)
@@ -768,7 +770,7 @@ bool blocks_pay(const BlockArgs &a, int KC, const Plan &plan, bool only_if_faste
     // Rows of many bytes to a codebook are read whole here; the general kernel asks for 64 bytes of them to a split value, which pays where there are
     // many of both: N = 13387, D = 1619, M = 17, C = 1, binary16 6.2 and 10.7, N = 12435, D = 1226, M = 81, C = 2 8.7 and 16.0; N = 12233, D = 1090, M = 79, C = 1, bytes 8.0 and 5.9 (13 MiB),
     // N = 13129, D = 1415, M = 84, C = 5, binary16 11.6 and 11.1 (566 bytes to a codebook).
-    // Few entries to add need no line of their own: N = 8192, D = 27, M = 3, C = 4 both take as long as a launch where calls are made one by one, 4.8 and 3.6 in a graph;
+    // Few entries to add need no line of their own: N = 8192, D = 27, M = 3, C = 4 both take as long as a launch where calls are made one by one, 4.9 and 3.6 in a graph;
     // N = 97583, D = 36, M = 3, C = 9, binary16 14.5 and 7.6, N = 5693, D = 44, M = 3, C = 11, binary16 14.4 and 4.0; none of 455 calls with tables of at most 8 KiB was faster there
     // but for such rows.
     if (a.row_bytes > 600 * a.C && a.N * a.row_bytes > (16 << 20)) return false;
@@ -890,7 +892,6 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
     // the range of a chunk is read whole: rows without much between them
     if (a.pitch > a.row_bytes + a.row_bytes / 8 + 64) return 1;
     const int KC = kernel_codebooks(C);
-    if (KC == 0) return 1;
     const bool whole = a.pitch % 16 == 0 && aligned_to(A.data, 16);      // every row begins on a 16-byte boundary
     if (a.row_bytes > 4096 && !whole) return 1;
     const Plan plan = choose_plan(N, a.pitch, whole, M, KC);
@@ -941,7 +942,6 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
     if (!A.col_major || C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
     if (left_out() || option(MADDNESS_OPT_COLS_RUN)) return 1;
     const int KC = kernel_codebooks(C);
-    if (KC == 0) return 1;
     BlockArgs a{};
     a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.D = p.D; a.dtype = A.dtype;
     a.N = N;
@@ -973,7 +973,12 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
     if (a.col_blocks > 1) groups = (groups + 7) / 8 * 8;
     a.row_groups = (int)groups;
     const int grid = a.row_groups * a.col_blocks;
-    if (only_if_faster && (C == 16 || C == 32 || C == 64) && !columns_pay(a, A.ld, (a.chunks + a.row_groups - 1) / a.row_groups)) return 1;
+    const int turns = (a.chunks + a.row_groups - 1) / a.row_groups;
+    if (only_if_faster && (C == 16 || C == 32 || C == 64) && !columns_pay(a, A.ld, turns)) return 1;
+    // Next to nothing to read and to add for many rows, half of it padding: the general kernel (N = 774266, M = 2, C = 2 16 and 34, N = 88197, M = 3, C = 1, binary16 5.0 and 6.0;
+    // N = 150580, M = 6, C = 3 7.7 and 9.0, N = 625847, M = 7, C = 4 28 and 35, N = 675992, M = 1, C = 6 27 and 34; one turn N = 26413, M = 3, C = 2 5.5 and 3.7; N = 137365, M = 9, C = 2 14.1 and 8.7; N = 529582, M = 4, C = 6, bytes
+    // 31 and 27).
+    if (M <= 8 && (C <= 2 ? turns > 1 : turns > 3 && (C == 3 || (C <= 6 && A.dtype == MADDNESS_F32)))) return 1;
     switch (KC) {
     case 4: return launch_columns<1>(a, grid, lds, stream);
     case 8: return launch_columns<2>(a, grid, lds, stream);
@@ -1050,9 +1055,7 @@ int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, co
 {
     if (C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
     if (left_out()) return 1;
-    int KC = 0;
-    for (int s : {64, 48, 32, 24, 16, 8, 4})
-        if (s >= C) KC = s;
+    const int KC = kernel_codebooks(C);
     BlockArgs a{};
     a.A = codes; a.N = N;
     a.luts = luts; a.scale = scale; a.offset = offset; a.M = M; a.C = C;
@@ -1113,9 +1116,7 @@ int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, 
     const int es = A.elem_bytes(), C = p.C;
     if (C > 64 || N < 16 || N >= (1LL << 36)) return 1;
     if (left_out()) return 1;
-    int KC = 0;
-    for (int s : {64, 48, 32, 24, 16, 8, 4})
-        if (s >= C) KC = s;
+    const int KC = kernel_codebooks(C);
     BlockArgs a{};
     a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.row_bytes = p.D * es; a.D = p.D; a.dtype = A.dtype;
     a.N = N; a.C = C; a.col_blocks = 1;

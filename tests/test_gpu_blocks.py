@@ -29,6 +29,9 @@ CASES = [
     (700, 27, 200, 4, "f32", 0, 0, 0), (515, 61, 100, 7, "f32", 3, 0, 2), (333, 250, 255, 15, "f16", 1, 3, 0),
     (300, 96, 77, 21, "u8", 0, 5, 1), (257, 333, 64, 31, "bf16", 0, 0, 0), (130, 240, 48, 43, "f32", 0, 3, 0),
     (90, 505, 127, 63, "f32", 7, 0, 5), (64, 1024, 130, 64, "u8", 0, 0, 0),
+    # kernel sizes of which up to half is padding
+    (300, 27, 40, 1, "f32", 0, 0, 0), (333, 45, 130, 5, "f16", 1, 0, 1), (257, 99, 17, 9, "u8", 0, 3, 0), (130, 170, 255, 17, "f32", 0, 1, 3),
+    (90, 250, 31, 25, "bf16", 3, 0, 0), (70, 333, 100, 33, "f32", 0, 0, 5), (65, 505, 129, 49, "u8", 0, 5, 2), (40001, 99, 90, 11, "f16", 0, 0, 0),
     # blocks of one to eight tiles, and more than one block of columns, the last one with a column
     (1000, 128, 16, 32, "f32", 0, 0, 0), (1000, 128, 32, 32, "f32", 0, 0, 0), (1000, 128, 60, 32, "f32", 0, 0, 0),
     (400, 512, 257, 32, "f32", 0, 0, 0), (200, 64, 1025, 24, "f32", 0, 0, 4),
@@ -92,6 +95,8 @@ def test_blocks_of_rows_and_columns(mad, case):
 COLUMNS = [
     (16, 64, 1, 16, "f32", 0), (63, 300, 130, 64, "f16", 1), (64, 27, 64, 4, "u8", 3), (65, 200, 1000, 48, "f32", 0),
     (577, 61, 35, 7, "bf16", 0), (1025, 128, 255, 15, "f32", 2), (2049, 256, 512, 32, "u8", 0), (4100, 96, 129, 21, "f16", 5),
+    (700, 27, 40, 1, "f32", 0), (333, 45, 130, 5, "f16", 1), (1025, 99, 17, 9, "u8", 0), (130, 170, 255, 17, "f32", 3), (2000, 250, 31, 25, "bf16", 0),
+    (90, 333, 100, 33, "f32", 0), (577, 505, 129, 49, "u8", 1),
     (9001, 240, 100, 31, "f32", 1), (70001, 72, 20, 8, "u8", 0), (70001, 128, 100, 16, "bf16", 7), (40000, 330, 90, 63, "f32", 0),
 ]
 

@@ -386,7 +386,7 @@ ROUTES = [
     ((20000, 1024, 512, 64, 512, 0), "fused_mfma_kernel, A by rows"),       # tables larger than LDS
     ((20000, 1024, 512, 64, 512, 1), "tiled_rows_kernel"),
     ((1 << 18, 510, 250, 30, 250, 0), "fused_mfma_kernel, A by rows [C = 32, DV = 2, NT = 4, DT = 0, SCAN = true, GATHER = true, PAD = true, ODD = true]"),
-    ((20000, 131, 7, 5, 7, 0), "fused_mfma_kernel, A by rows [C = 16, DV = 1"),
+    ((20000, 131, 7, 5, 7, 0), "fused_blocks_kernel, A by rows [KG = 2"),
     ((20000, 27, 2, 4, 2, 0), "fused_blocks_kernel, A by rows"),            # the image workload's shape: rows too short for the others
     ((5000, 64, 40, 8, 40, 0), "fused_blocks_kernel, A by rows"),           # few rows of such a shape
     ((20000, 27, 2, 4, 2, 2), "scan_kernel<true>"), ((5000, 64, 40, 8, 40, 2), "scan_kernel<true>"),

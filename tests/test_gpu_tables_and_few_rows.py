@@ -157,18 +157,18 @@ def test_rows_of_more_than_2_gib(mad, dtype, D, C, M):
 B, F, G, K = "fused_blocks", "fused_mfma", "scan_kernel", "cols_kernel"
 FASTER = [
     # tables between 64 KiB and what the general kernel holds at once: padding of codebooks and columns decides, and rows
-    ((1, 1500, 656, 12, "f32", False), G, G), ((239, 1500, 592, 12, "f32", False), G, G),
+    ((1, 1500, 656, 12, "f32", False), G, G), ((239, 1500, 592, 12, "f32", False), B, G),
     ((5257, 510, 300, 16, "f32", False), B, F), ((120, 2001, 340, 16, "f32", False), G, G),
     ((2000, 300, 250, 30, "f32", False), B, F), ((6, 333, 96, 50, "f32", False), G, G),
-    ((125, 1000, 288, 20, "f32", False), F, F), ((430, 1500, 780, 12, "bf16", False), G, G),
+    ((125, 1000, 288, 20, "f32", False), B, F), ((430, 1500, 780, 12, "bf16", False), B, G),
     ((378, 333, 224, 30, "bf16", False), B, F), ((1, 256, 172, 40, "u8", False), G, G),
-    ((16384, 1500, 592, 12, "f32", False), F, F), ((1787, 512, 112, 40, "f32", False), G, G),
+    ((16384, 1500, 592, 12, "f32", False), F, F), ((1787, 512, 112, 40, "f32", False), B, G),
     ((1000, 256, 92, 64, "f32", False), B, F), ((1, 256, 72, 64, "f32", False), G, G),
     # narrow rows, small tables: the split values alone or whole rows
     ((32767, 250, 33, 15, "f16", False), B, G), ((32768, 250, 33, 15, "f16", False), B, F),
     ((53325, 85, 20, 16, "u8", False), B, G), ((40000, 716, 5, 4, "u8", False), B, G),
     ((33000, 1558, 92, 2, "f16", False), G, G), ((40001, 174, 8, 22, "bf16", False), B, G),
-    ((35000, 426, 42, 53, "u8", False), F, F), ((36000, 472, 66, 16, "bf16", False), B, F),
+    ((35000, 426, 42, 53, "u8", False), B, F), ((36000, 472, 66, 16, "bf16", False), B, F),
     ((35550, 107, 72, 16, "f16", False), B, F), ((34561, 901, 23, 32, "u8", False), B, F),
     # rows of many bytes to a codebook
     ((6978, 601, 5, 4, "f32", False), B, G), ((6979, 601, 5, 4, "f32", False), G, G), ((6979, 600, 5, 4, "f32", False), B, G),
@@ -199,6 +199,10 @@ FASTER = [
     ((170000, 128, 64, 32, "f32", True), B, F), ((170004, 128, 64, 32, "f32", True), F, F), ((200000, 128, 64, 32, "u8", True), B, F),
     ((200004, 128, 64, 32, "u8", True), F, F), ((200004, 128, 36, 32, "u8", True), B, F), ((131077, 128, 256, 32, "f32", True), K, K),
     ((131076, 256, 96, 64, "f16", True), B, F), ((131076, 256, 64, 64, "f16", True), F, F),
+    # numbers of codebooks that only the general kernel has besides, and where that is the faster one
+    ((554, 200, 100, 40, "f16", True), B, G), ((49152, 16, 4, 2, "f16", True), B, G), ((49153, 16, 4, 2, "f16", True), G, G),
+    ((49153, 16, 9, 2, "f16", True), B, G), ((147456, 24, 8, 6, "f32", True), B, G), ((147457, 24, 8, 6, "f32", True), G, G),
+    ((147457, 24, 8, 6, "u8", True), B, G),
 ]
 
 
