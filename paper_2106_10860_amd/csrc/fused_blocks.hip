@@ -1125,9 +1125,12 @@ int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, 
     a.rows_at = a.codes_at = a.tables_at = 256;
     const DeviceInfo &dev = device_info();
     if (A.col_major) {
-        // (next to no codes to a row: N = 1154410, C = 4, bfloat16 33 and 36; N = 481716, C = 8 18.6 and 20.1; bytes N = 101212, C = 8 11.2 and 5.7)
-        // nor few rows, of which a wavefront here takes several codebooks in turn (N = 5527, C = 64, bfloat16 6.4 and 8.1; N = 7254, C = 40 7.1 and 6.1)
-        if (KC == 4 || (KC == 8 && A.dtype == MADDNESS_F32 && N > (1 << 17)) || N < 128 * KC) return 1;
+        // Next to no codes to a row (N = 1154410, C = 4, bfloat16 33 and 36; N = 481716, C = 8 18.6 and 20.1, N = 816156, C = 9 44 and 52; bytes N = 101212, C = 8 11.2 and 5.7),
+        // nor few rows, of which a wavefront here takes several codebooks in turn (N = 5527, C = 64, bfloat16 6.4 and 8.1, N = 3980, C = 23, bytes 3.9 and 4.3; fp32 N = 6119, C = 9 2.7 and 3.2,
+        // N = 8793, C = 15 4.1 and 3.7, N = 7801, C = 26 4.3 and 5.2, N = 11712, C = 24 6.1 and 4.7, N = 5491, C = 8 2.9 and 2.7, N = 6227, C = 48 7.2 and 6.8).
+        const bool wide = A.dtype == MADDNESS_F32;
+        if (KC == 4 || (wide && ((KC == 8 && N > (1 << 17)) || (C <= 12 && N > (1 << 18))))) return 1;
+        if (N < (wide && C != 8 && KC <= 32 ? (KC <= 16 ? 8192 : 9216) : (KC == 24 ? 192 : 128) * KC)) return 1;
         // workgroups to a compute unit, with 4 and as here: N = 440208, C = 24, bytes 45.7 and 42.6; N = 353958, C = 48 88 and 77; N = 132534, C = 63 39.3
         // and 38.0; fewer for C = 15 lose (N = 302525, bytes 19.8 with 4, 22.1 with 3)
         const int64_t wgs = (int64_t)dev.cus * (KC <= 16 ? 4 : KC < 64 ? 3 : 2);
@@ -1145,8 +1148,14 @@ int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, 
         default: return launch_codes_of_columns<16>(a, lds, stream);
         }
     }
-    if (a.row_bytes > kMaxRowBytes || a.pitch > a.row_bytes + a.row_bytes / 8 + 64) return 1;
+    if ((int64_t)p.D * es > kMaxRowBytes || a.pitch > a.row_bytes + a.row_bytes / 8 + 64) return 1;
     const bool whole = a.pitch % 16 == 0 && aligned_to(A.data, 16);
+    // Few codes: the launch here is the longer one, by a tenth (fp32 N = 70, C = 1 1.9 and 2.6, N = 2650, C = 14 2.7 and 3.5, N = 4279, C = 28 3.8 and 3.9, N = 7829, C = 28 4.1 and 4.1,
+    // N = 14754, C = 24 6.4 and 4.6; the other types, which take longer there, from where the rows here make two workgroups to a compute unit: bytes N = 1887, C = 20 3.5 and 2.9,
+    // N = 4702, C = 3 3.2 and 3.7, N = 14523, C = 6 3.5 and 3.7, N = 7210, C = 19 4.1 and 3.7), but for powers of two, where there every lane has a pair of codebooks and workgroups are
+    // fewest (N = 240, D = 64, C = 8 3.3 and 2.6, N = 72, C = 32 3.0 and 2.7; from there on N = 4796, C = 8 2.8 and 3.6, binary16 N = 2173, C = 16 3.7 and 3.4).
+    const bool few = N <= 8 * dev.cus, power = C >= 8 && (C & (C - 1)) == 0;
+    if (A.dtype == MADDNESS_F32 ? N * C < (192 << 10) && !(few && power) : N * C < (88 << 10) && !few && !power) return 1;
     // (whole rows are read here, 64 bytes for each split value there: N = 20680, D = 512, C = 4, binary16 5.8 and 6.1)
     const int64_t most = (32 * 1024 - (whole ? 0 : 16)) / a.pitch;
     if (most < 1 || a.row_bytes > 192 * C) return 1;

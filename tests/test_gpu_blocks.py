@@ -244,14 +244,21 @@ def test_scan_by_blocks(mad, case):
 # (N, D, C, dtype, by columns, elements between rows or columns, elements before the first): every kernel size with and without codebooks
 # that do not exist, one chunk to a workgroup and several, rows on any element
 CODES = [
-    (16, 27, 5, "f32", False, 0, 0), (700, 27, 3, "f32", False, 0, 1), (4099, 130, 8, "u8", False, 3, 1), (100003, 97, 15, "f16", False, 0, 0),
+    (16, 27, 5, "f16", False, 0, 0), (700, 27, 3, "u8", False, 0, 1), (4099, 130, 8, "u8", False, 3, 1), (100003, 97, 15, "f16", False, 0, 0),
     (30001, 250, 24, "bf16", False, 1, 0), (20000, 120, 30, "f32", False, 0, 0), (9001, 512, 47, "u8", False, 0, 3), (50001, 256, 63, "bf16", False, 0, 0),
-    (1025, 33, 8, "f32", True, 0, 0), (1153, 64, 7, "u8", True, 1, 1), (4097, 64, 15, "bf16", True, 0, 1), (200001, 60, 12, "u8", True, 3, 0),
+    (1025, 33, 8, "f16", True, 0, 0), (1153, 64, 7, "u8", True, 1, 1), (4097, 64, 15, "bf16", True, 0, 1), (200001, 60, 12, "u8", True, 3, 0),
     (30001, 97, 24, "f32", True, 0, 0), (120001, 120, 30, "f16", True, 1, 0), (10001, 190, 48, "f32", True, 0, 1), (70001, 252, 63, "u8", True, 0, 0),
+    (70, 40, 8, "f32", False, 0, 0), (13108, 60, 15, "f32", False, 0, 0), (2048, 90, 20, "u8", False, 0, 0), (4506, 90, 20, "u8", False, 0, 0),
+    (100001, 27, 3, "f32", False, 0, 1), (8192, 60, 15, "f32", True, 0, 0), (9216, 100, 25, "f32", True, 0, 0), (2048, 64, 8, "f32", False, 0, 0), (4608, 100, 23, "u8", True, 0, 0),
+]
+# as many codes and fewer, for which the general kernel is the faster one
+FEW_CODES = [
+    (16, 27, 5, "f32", False, 0, 0), (13107, 60, 15, "f32", False, 0, 0), (2049, 90, 20, "u8", False, 0, 0), (4505, 90, 20, "u8", False, 0, 0),
+    (8191, 60, 15, "f32", True, 0, 0), (9215, 100, 25, "f32", True, 0, 0), (2049, 64, 8, "f32", False, 0, 0), (4607, 100, 23, "u8", True, 0, 0), (262145, 40, 12, "f32", True, 0, 0),
 ]
 
 
-@pytest.mark.parametrize("case", CODES, ids=lambda c: "N%d_D%d_C%d_%s_cols%d_p%d_o%d" % c)
+@pytest.mark.parametrize("case", CODES + FEW_CODES, ids=lambda c: "N%d_D%d_C%d_%s_cols%d_p%d_o%d" % c)
 def test_codes_by_blocks(mad, case):
     import torch
     N, D, C, dtype, cols, pad, before = case
@@ -267,7 +274,7 @@ def test_codes_by_blocks(mad, case):
     got = mad.maddness_encode_typed(params, A_d, col_major=cols)
     kernel = mad.maddness_last_kernel()
     torch.cuda.synchronize()
-    assert kernel.startswith("fused_blocks_kernel, codes of " + ("columns" if cols else "rows")), kernel
+    assert kernel.startswith("fused_blocks_kernel, codes of " + ("columns" if cols else "rows")) == (case not in FEW_CODES), kernel
     want = oracle.pack(oracle.encode(values.float().cpu().numpy(), sd, th)) if N <= 5000 else None
     if want is None:
         try:
