@@ -1139,7 +1139,6 @@ int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, 
         a.row_groups = (int)std::min<int64_t>(wgs, a.chunks);
         const size_t lds = 256 + 64 * (size_t)lanes_per_row(KC);
         switch (KC) {
-        case 4: return launch_codes_of_columns<1>(a, lds, stream);
         case 8: return launch_codes_of_columns<2>(a, lds, stream);
         case 16: return launch_codes_of_columns<4>(a, lds, stream);
         case 24: return launch_codes_of_columns<6>(a, lds, stream);
