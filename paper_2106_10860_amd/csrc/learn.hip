@@ -62,7 +62,7 @@ struct LearnArgs {
     int32_t *range_part;  // [C][kRangeParts][2] what a part of the codebook's values span, see any_order()
     int32_t *range;       // [C][2] and what all of them do
     int32_t row_bits;     // N <= 2^row_bits
-    uint32_t *varying_part;  // [C][kRangeParts][pitch] the bits in which a part of a column's values differ from its first, see varying_bits()
+    uint32_t *varying_part;  // [C][kRangeParts][pitch] the bits in which a part of a column's values differ from its first row's, see gather_columns_kernel and SortDigits
     uint32_t *varying;    // [C][pitch] and in which any of them do
     int32_t gather_parts; // parts of both that there are
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
@@ -2319,17 +2319,6 @@ __device__ __forceinline__ double row_broadcast(double x)
     return __builtin_bit_cast(double, (int64_t)high << 32 | (uint32_t)low);
 }
 
-// Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
-// every sum over k ascending.  M is symmetric, and entry (i, j), i >= j, is kept at M[j][i] (a column side by side).
-// One launch per panel of 16 columns J0 .. J0 + 15, which takes the panel's terms off everything to its right: a
-// workgroup per 64 x 64 tile of what is left, which works out the panel's rows of L that it needs for itself and then subtracts
-// their 16 products from its entries, k ascending as panels and columns go.  A wavefront does its 64 rows of the tile, or of the
-// tile's columns, beside the 16 of the diagonal block, of which every row of 16 lanes has one to a lane: what a column
-// needs of another row comes by row broadcasts, without barriers.  The tiles of the first column store L; what they read
-// stays as it is.  Bound by the chain of 16 roots and divisions per panel, 10.1 us (12.2 with the panel's rows
-// in LDS and two barriers to a column).  (Subtracting all columns
-// before the panel at once, when the panel's turn comes, takes few workgroups and up to 31 us a launch: 0.65 against
-// 0.38 ms for Q = 512.)
 // f(0), f(1) .. f(15), the numbers known at compile time (a row broadcast's lane is part of the instruction).
 template <typename F>
 __device__ __forceinline__ void for_16(F f)
@@ -2358,6 +2347,17 @@ __device__ __forceinline__ size_t factor_at(int Q, int r, int k)
     return ((size_t)(r >> 4) * (Q >> 4) + (k >> 4)) * 256 + ((k >> 1) & 7) * 32 + (r & 15) * 2 + (k & 1);
 }
 
+// Cholesky factorisation M = L L^T: L_jj = sqrt(M_jj - sum_k L_jk^2), L_ij = (M_ij - sum_k L_ik L_jk) / L_jj,
+// every sum over k ascending.  M is symmetric, and entry (i, j), i >= j, is kept at M[j][i] (a column side by side).
+// One launch per panel of 16 columns J0 .. J0 + 15, which takes the panel's terms off everything to its right: a
+// workgroup per 64 x 64 tile of what is left, which works out the panel's rows of L that it needs for itself and then subtracts
+// their 16 products from its entries, k ascending as panels and columns go.  A wavefront does its 64 rows of the tile, or of the
+// tile's columns, beside the 16 of the diagonal block, of which every row of 16 lanes has one to a lane: what a column
+// needs of another row comes by row broadcasts, without barriers.  The tiles of the first column store L; what they read
+// stays as it is.  Bound by the chain of 16 roots and divisions per panel, 10.1 us (12.2 with the panel's rows
+// in LDS and two barriers to a column).  (Subtracting all columns
+// before the panel at once, when the panel's turn comes, takes few workgroups and up to 31 us a launch: 0.65 against
+// 0.38 ms for Q = 512.)
 constexpr int kCholPanel = 16, kCholTile = 64, kCholPitch = kCholPanel + 1;
 __global__ __launch_bounds__(256) void cholesky_panel_kernel(const ProtoArgs a, int J0)
 {
