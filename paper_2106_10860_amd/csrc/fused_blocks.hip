@@ -1,6 +1,6 @@
 // Fused encode + exact scan, and either alone, by blocks of rows and columns, for few and medium numbers of rows.
 //
-// A call of a few thousand rows is bound by latencies: a chain of kernel arguments -> trees, tables and rows -> codes ->
+// A call of up to a few thousand rows is bound by latencies: a chain of kernel arguments -> trees, tables and rows -> codes ->
 // sums -> stores on a chip that is mostly idle.  So a workgroup (8 wavefronts) takes a block of up to 128 (256) output
 // columns and few rows, as many workgroups as the chip holds, and asks for everything at once:
 //   1. the tables of its columns come in 16-byte pieces as they lie in memory, a piece per thread and load, all of them on
@@ -18,6 +18,9 @@
 // 1.2 and the scan 1.2.  16 wavefronts to a workgroup were slower (11.6), as were two workgroups to a compute unit
 // where one chunk is all the work (11.6), and lanes that read neighbouring codes instead of neighbouring columns of the tables (64
 // lines to a load: N = 676, D = 352, M = 737, C = 32 12.4 us, now 6.8).
+// From the first row on: a single request takes what a launch and this chain take, there and here, us: N = 2, D = 240, M = 60, C = 48 7.2 and 4.7, N = 7, D = 75, M = 577, C = 15
+// 15.3 and 4.4, N = 10, D = 28, M = 4, C = 4 3.7 and 3.3; by columns N = 10, D = 704, M = 30, C = 64, bytes 26 and 9.1; the scan alone N = 7, M = 788, C = 50 9.4 and 5.2;
+// averages N = 4, D = 240, M = 242, C = 16 18 and 4.5; of 306 calls of up to 15 rows none was slower.
 #include <algorithm>
 
 #include "mfma_common.h"
@@ -881,7 +884,7 @@ int launch_fused_blocks(const maddness_params &p, const MatrixA &A, int64_t N, i
                         uint8_t *codes, bool only_if_faster, hipStream_t stream)
 {
     const int es = A.elem_bytes(), C = p.C;
-    if (A.col_major || C > 64 || (int64_t)p.D * es > kMaxRowBytes || N < 16 || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (A.col_major || C > 64 || (int64_t)p.D * es > kMaxRowBytes || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
     if (left_out()) return 1;
     BlockArgs a{};
     a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * es; a.row_bytes = p.D * es; a.D = p.D; a.dtype = A.dtype;
@@ -939,7 +942,7 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
                              uint8_t *codes, bool only_if_faster, hipStream_t stream)
 {
     const int es = A.elem_bytes(), C = p.C;
-    if (!A.col_major || C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (!A.col_major || C > 64 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
     if (left_out() || option(MADDNESS_OPT_COLS_RUN)) return 1;
     const int KC = kernel_codebooks(C);
     BlockArgs a{};
@@ -1002,7 +1005,7 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
                            uint8_t *codes, hipStream_t stream)
 {
     const int C = p.C;
-    if (!A.plain() || C > 64 || C % 16 != 0 || (int64_t)p.D * 4 > kMaxRowBytes || N < 16 || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (!A.plain() || C > 64 || C % 16 != 0 || (int64_t)p.D * 4 > kMaxRowBytes || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
     if (left_out()) return 1;
     BlockArgs a{};
     a.A = static_cast<const unsigned char *>(A.data); a.pitch = A.ld * 4; a.row_bytes = p.D * 4; a.D = p.D; a.dtype = A.dtype;
@@ -1053,7 +1056,7 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
 int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, const uint8_t *luts, const float *scale,
                        const float *offset, float *out, int64_t ldo, uint16_t *acc, hipStream_t stream)
 {
-    if (C > 64 || N < 16 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
+    if (C > 64 || N >= (1LL << 36) || 16 * (int64_t)C * M >= (1LL << 31)) return 1;
     if (left_out()) return 1;
     const int KC = kernel_codebooks(C);
     BlockArgs a{};
@@ -1114,7 +1117,7 @@ int launch_scan_blocks(int32_t C, int32_t M, const uint8_t *codes, int64_t N, co
 int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, uint8_t *codes, hipStream_t stream)
 {
     const int es = A.elem_bytes(), C = p.C;
-    if (C > 64 || N < 16 || N >= (1LL << 36)) return 1;
+    if (C > 64 || N >= (1LL << 36)) return 1;
     if (left_out()) return 1;
     const int KC = kernel_codebooks(C);
     BlockArgs a{};

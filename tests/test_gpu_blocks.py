@@ -23,6 +23,8 @@ def mad():
 
 # (N, D, M, C, dtype, elements between rows, elements before the first, bytes before the tables)
 CASES = [
+    # one row, and fewer than a group of 16
+    (1, 64, 128, 16, "f32", 0, 0, 0), (1, 27, 1, 4, "u8", 0, 1, 0), (2, 1024, 512, 64, "f16", 0, 0, 0), (7, 333, 300, 30, "bf16", 1, 0, 3), (15, 61, 33, 7, "f32", 0, 1, 0),
     # fewest rows; one column; a table of 16 bytes to a codebook, of which the last piece is all there is
     (16, 64, 1, 32, "f32", 0, 0, 0), (17, 33, 129, 16, "f32", 0, 1, 1), (31, 48, 15, 48, "f32", 0, 0, 3),
     # kernel sizes with and without codebooks that do not exist
@@ -93,6 +95,7 @@ def test_blocks_of_rows_and_columns(mad, case):
 # (N, D, M, C, dtype, elements between columns): less than a run of 64 rows, whole runs, a row more, several runs to a workgroup
 # and workgroups without any; kernel sizes with and without codebooks that do not exist; one to eight tiles of columns
 COLUMNS = [
+    (1, 64, 128, 16, "f32", 0), (2, 300, 130, 64, "f16", 1), (7, 30, 33, 9, "u8", 0), (15, 200, 1000, 48, "bf16", 3),
     (16, 64, 1, 16, "f32", 0), (63, 300, 130, 64, "f16", 1), (64, 27, 64, 4, "u8", 3), (65, 200, 1000, 48, "f32", 0),
     (577, 61, 35, 7, "bf16", 0), (1025, 128, 255, 15, "f32", 2), (2049, 256, 512, 32, "u8", 0), (4100, 96, 129, 21, "f16", 5),
     (700, 27, 40, 1, "f32", 0), (333, 45, 130, 5, "f16", 1), (1025, 99, 17, 9, "u8", 0), (130, 170, 255, 17, "f32", 3), (2000, 250, 31, 25, "bf16", 0),
@@ -142,6 +145,7 @@ def test_blocks_of_a_stored_by_columns(mad, case):
 # (N, D, M, C, elements between rows, before the first, bytes before the tables): two to eight tiles of columns, the end of the
 # tables, rows on any element, one chunk to a workgroup and several
 AVERAGES = [
+    (1, 64, 128, 16, 0, 0, 0), (2, 512, 31, 64, 0, 1, 0), (15, 100, 300, 32, 1, 0, 1),
     (16, 64, 1, 16, 0, 0, 0), (33, 100, 31, 64, 0, 1, 3), (700, 512, 100, 32, 0, 0, 0), (300, 64, 1000, 48, 4, 0, 1),
     (1025, 333, 129, 32, 1, 0, 0), (2048, 1024, 130, 64, 0, 0, 0), (4100, 128, 257, 16, 0, 3, 2), (20001, 256, 60, 32, 0, 0, 0),
     (9845, 1024, 128, 64, 0, 0, 0), (30000, 64, 300, 16, 0, 0, 0),
@@ -191,6 +195,7 @@ def test_averages_by_blocks(mad, case):
 # (N, M, C, floats between rows, bytes before the codes, bytes before the tables): fewest rows, one column, every kernel size with and
 # without codebooks that do not exist, codes by eight, four and single bytes, one block of columns and several, one chunk and several
 SCANS = [
+    (1, 1, 4, 0, 0, 0), (1, 300, 64, 0, 0, 0), (2, 129, 7, 1, 1, 0), (15, 100, 32, 0, 0, 3),
     (16, 1, 4, 0, 0, 0), (17, 300, 64, 0, 0, 0), (33, 64, 7, 1, 0, 0), (257, 129, 8, 0, 1, 1), (300, 100, 12, 0, 0, 0),
     (1411, 1000, 15, 0, 0, 3), (700, 16, 16, 0, 3, 0), (4097, 300, 16, 4, 0, 0), (1000, 255, 23, 0, 0, 0), (5001, 512, 24, 0, 0, 0),
     (4000, 785, 30, 0, 0, 0), (20000, 20, 31, 3, 0, 0), (10007, 128, 32, 0, 0, 0), (70001, 16, 32, 0, 0, 0), (129, 77, 40, 0, 0, 0),
@@ -244,6 +249,7 @@ def test_scan_by_blocks(mad, case):
 # (N, D, C, dtype, by columns, elements between rows or columns, elements before the first): every kernel size with and without codebooks
 # that do not exist, one chunk to a workgroup and several, rows on any element
 CODES = [
+    (1, 27, 5, "f16", False, 0, 0), (1, 64, 8, "f32", False, 0, 1), (7, 512, 47, "u8", False, 3, 0), (15, 130, 63, "bf16", False, 0, 1),
     (16, 27, 5, "f16", False, 0, 0), (700, 27, 3, "u8", False, 0, 1), (4099, 130, 8, "u8", False, 3, 1), (100003, 97, 15, "f16", False, 0, 0),
     (30001, 250, 24, "bf16", False, 1, 0), (20000, 120, 30, "f32", False, 0, 0), (9001, 512, 47, "u8", False, 0, 3), (50001, 256, 63, "bf16", False, 0, 0),
     (1025, 33, 8, "f16", True, 0, 0), (1153, 64, 7, "u8", True, 1, 1), (4097, 64, 15, "bf16", True, 0, 1), (200001, 60, 12, "u8", True, 3, 0),
