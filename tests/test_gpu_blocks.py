@@ -37,7 +37,8 @@ CASES = [
     # blocks of one to eight tiles, and more than one block of columns, the last one with a column
     (1000, 128, 16, 32, "f32", 0, 0, 0), (1000, 128, 32, 32, "f32", 0, 0, 0), (1000, 128, 60, 32, "f32", 0, 0, 0),
     (400, 512, 257, 32, "f32", 0, 0, 0), (200, 64, 1025, 24, "f32", 0, 0, 4),
-    # rows of 8 KiB; tables in the place of the first rows
+    # rows of 4 to 8 KiB on any element; rows of 8 KiB; tables in the place of the first rows
+    (300, 1025, 40, 64, "f32", 0, 1, 0), (40, 2047, 130, 48, "f32", 1, 3, 1), (4000, 1501, 17, 16, "f32", 2, 1, 0),
     (40, 2048, 96, 64, "f32", 0, 0, 0), (9000, 512, 512, 32, "bf16", 0, 0, 0), (4100, 1024, 128, 64, "f32", 0, 0, 0),
     # several chunks to a workgroup: wide blocks; two workgroups to a compute unit; the last chunk with a row
     (3001, 384, 1000, 24, "f32", 0, 0, 0), (40001, 120, 90, 15, "f32", 0, 0, 0), (131077, 27, 20, 4, "f32", 0, 0, 0),

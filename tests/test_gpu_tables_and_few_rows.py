@@ -158,7 +158,7 @@ B, F, G, K = "fused_blocks", "fused_mfma", "scan_kernel", "cols_kernel"
 FASTER = [
     # tables between 64 KiB and what the general kernel holds at once: padding of codebooks and columns decides, and rows
     ((1, 1500, 656, 12, "f32", False), B, G), ((239, 1500, 592, 12, "f32", False), B, G),
-    ((5257, 510, 300, 16, "f32", False), B, F), ((120, 2001, 340, 16, "f32", False), G, G),
+    ((5257, 510, 300, 16, "f32", False), B, F), ((120, 2001, 340, 16, "f32", False), B, G),
     ((2000, 300, 250, 30, "f32", False), B, F), ((6, 333, 96, 50, "f32", False), B, G),
     ((125, 1000, 288, 20, "f32", False), B, F), ((430, 1500, 780, 12, "bf16", False), B, G),
     ((378, 333, 224, 30, "bf16", False), B, F), ((1, 256, 172, 40, "u8", False), B, G),
