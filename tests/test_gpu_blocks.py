@@ -201,11 +201,15 @@ SCANS = [
     (1411, 1000, 15, 0, 0, 3), (700, 16, 16, 0, 3, 0), (4097, 300, 16, 4, 0, 0), (1000, 255, 23, 0, 0, 0), (5001, 512, 24, 0, 0, 0),
     (4000, 785, 30, 0, 0, 0), (20000, 20, 31, 3, 0, 0), (10007, 128, 32, 0, 0, 0), (70001, 16, 32, 0, 0, 0), (129, 77, 40, 0, 0, 0),
     (3001, 300, 48, 0, 0, 0), (140000, 3, 48, 0, 0, 0), (2000, 100, 56, 0, 0, 0), (9001, 36, 63, 0, 2, 0), (140001, 10, 64, 0, 0, 0),
-    (300001, 20, 15, 0, 0, 0), (60000, 250, 30, 2, 0, 0), (14000, 1000, 15, 0, 0, 0), (33, 514, 64, 0, 0, 0),
+    (67584, 12, 61, 0, 0, 0), (300001, 20, 15, 0, 0, 0), (60000, 250, 30, 2, 0, 0), (14000, 1000, 15, 0, 0, 0), (33, 514, 64, 0, 0, 0),
 ]
 
 
-@pytest.mark.parametrize("case", SCANS, ids=lambda c: "N%d_M%d_C%d_p%d_c%d_t%d" % c)
+# those that other kernels take faster
+SCANS_LEFT = [(67585, 12, 61, 0, 0, 0), (600000, 2, 30, 0, 0, 0), (600000, 10, 40, 0, 0, 0)]
+
+
+@pytest.mark.parametrize("case", SCANS + SCANS_LEFT, ids=lambda c: "N%d_M%d_C%d_p%d_c%d_t%d" % c)
 def test_scan_by_blocks(mad, case):
     import torch
     N, M, C, pad, before, at = case
@@ -231,7 +235,7 @@ def test_scan_by_blocks(mad, case):
         return full, acc, kernel
 
     got, got_acc, kernel = run()
-    assert kernel.startswith("fused_blocks_kernel, scan"), kernel
+    assert kernel.startswith("fused_blocks_kernel, scan") == (case not in SCANS_LEFT), kernel
     only = run(False)[1] if got_acc is not None else None
     try:
         mad.maddness_set_option(mad.MADDNESS_OPT_KERNELS, mad.MADDNESS_KERNELS_GENERAL)
