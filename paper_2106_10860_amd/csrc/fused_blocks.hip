@@ -1003,7 +1003,9 @@ int launch_fused_blocks_cols(const maddness_params &p, const MatrixA &A, int64_t
 // M = 107, C = 16 85 and 48 (8), N = 390133, D = 1024, M = 45, C = 64 454 and 332 (95); several N = 9845, D = 1024, M = 128, C = 64 81 and 17 (5),
 // N = 119634, D = 128, M = 256, C = 16 66 and 57 (8), N = 129570, D = 256, M = 512, C = 16 139 and 152 (32), N = 172750, D = 512, M = 128, C = 64 120 and
 // 171 (43); C = 32 with tables in LDS for rows_kernel N = 8192, D = 512, M = 256 9.3 and 10.2 (2), N = 50246 31 and 54 (13), N = 524288, M = 128 218
-// and 272 (64), and without N = 62595, M = 1000 292 and 237 (62).
+// and 272 (64), and without, where the general kernel walks the tables tile by tile and blocks read every row once for each, N = 58664, D = 256, M = 791 297 and 135 (29),
+// N = 262070, M = 303 344 and 283 (52), N = 161770, M = 772 286 and 423 (79), N = 126359, D = 512, M = 656 281 and 370 (99), N = 534525, M = 984 1155 and 1958 (522); rows of 512
+// bytes N = 403599, D = 128, M = 646 902 and 668 (79), N = 683104, M = 915 1674 and 1409 (167).
 int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N, int32_t M, const uint8_t *luts,
                            const float *scale, const float *offset, float *out, int64_t ldo, uint16_t *acc,
                            uint8_t *codes, hipStream_t stream)
@@ -1034,7 +1036,7 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
     const int64_t rows = (share + turns - 1) / turns;
     if (N / rows >= (1 << 30)) return 1;
     const bool held = C == 32 && p.D <= 512 && p.D % 4 == 0 && whole && maddness::rows::tables_ok(C, M, luts, scale, offset, out, ldo, acc);
-    if (turns > 1 && (held || (C != 32 && a.col_blocks > 1 && turns > 16))) return 1;
+    if (turns > 1 && (held || (a.col_blocks > 1 && (C != 32 ? turns > 16 : turns > 64 && a.row_bytes >= 1024)))) return 1;
     a.chunk_rows = (int)rows;
     a.chunks = (int)((N + rows - 1) / rows);
     groups = std::min<int64_t>(groups, a.chunks);
