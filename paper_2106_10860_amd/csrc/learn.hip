@@ -64,6 +64,8 @@ struct LearnArgs {
     int32_t row_bits;     // N <= 2^row_bits
     uint32_t *varying_part;  // [C][kRangeParts][pitch] the bits in which a part of a column's values differ from its first row's, see gather_columns_kernel and SortDigits
     uint32_t *varying;    // [C][pitch] and in which any of them do
+    uint32_t *cand_varying;  // [C][4] those of the candidates
+    int32_t look;         // whether the sort goes by them; else by all bits
     int32_t gather_parts; // parts of both that there are
     int32_t *rows_by_bucket;  // [C][N] the rows of bucket 0 in row order, then those of bucket 1, ...
     int32_t *cand;        // [C][4] candidate columns (within the subspace), best first
@@ -152,20 +154,20 @@ __device__ __forceinline__ uint32_t ordered_bits(float x)
 // The columns of every codebook side by side, each row on a 32-byte (or 64-byte) boundary.  The levels read the rows of a
 // bucket in many orders, a codebook's columns at a time: from here they take whole 16-byte pieces, and the rows of a
 // codebook fit in an XCD's L2 where A does not.  A 16-byte piece to a thread and turn.
+// LOOK: and in which bits a column's values differ, for a sort by digits.  (Fewer rows are sorted by comparing: the trees of 50 rows of 64 columns, 8 codebooks, 164 us,
+// 169 with; a thread has the same columns in all turns where there are 8, 16, 32, 64 or 128 of them.)
+template <bool LOOK>
 __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
 {
     const int c = blockIdx.y, pieces = a.pitch / 4, lo = a.bounds[2 * c], d = a.bounds[2 * c + 1] - lo;
     float4 *X = reinterpret_cast<float4 *>(a.X + (size_t)c * (a.N + 1) * a.pitch);
     int top = 0, least = 0;
-    // In which bits the columns' values differ from those of the first row: where a thread has the same columns in all turns (8,
-    // 16, 32, 64 or 128 of them), else any.
+    // in which bits the columns' values differ from those of the first row
     uint32_t first[4], varying[4] = {};
-    const bool same_columns = 256 % pieces == 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int col = 4 * (int)(threadIdx.x % pieces) + e;
-        first[e] = ordered_bits(col < d ? a.A[lo + col] : 0.0f);
-        if (!same_columns) varying[e] = ~0u;
+        first[e] = LOOK ? ordered_bits(col < d ? a.A[lo + col] : 0.0f) : 0u;
     }
     // (four turns' loads ahead of their stores: there are no more workgroups than parts of a range.  2^20 x 128, one codebook:
     // 550 us one by one)
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     span_of(v[u][e], top, least);
-                    if (i0 + u * stride < a.N * pieces) varying[e] |= ordered_bits(v[u][e]) ^ first[e];
+                    if (LOOK && i0 + u * stride < a.N * pieces) varying[e] |= ordered_bits(v[u][e]) ^ first[e];
                 }
             }
     }
@@ -198,15 +200,17 @@ __global__ __launch_bounds__(256) void gather_columns_kernel(const LearnArgs a)
     }
     // (one maximum for all, by atomics, took up to 320 us)
     __shared__ int32_t part[4][2];
-    __shared__ uint32_t differ[256][4];
+    __shared__ uint32_t differ[LOOK ? 256 : 1][4];
+    if constexpr (LOOK) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) differ[threadIdx.x][e] = varying[e];
+        for (int e = 0; e < 4; ++e) differ[threadIdx.x][e] = varying[e];
+    }
     if ((threadIdx.x & 63) == 0) {
         part[threadIdx.x >> 6][0] = top;
         part[threadIdx.x >> 6][1] = least;
     }
     __syncthreads();
-    if ((int)threadIdx.x < a.pitch) {
+    if (LOOK && (int)threadIdx.x < a.pitch) {
         uint32_t any = 0;
         for (int t = threadIdx.x / 4; t < 256; t += pieces) any |= differ[t][threadIdx.x & 3];
         a.varying_part[((size_t)c * kRangeParts + blockIdx.x) * a.pitch + threadIdx.x] = any;
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(256) void order_rows_kernel(const LearnArgs a, int 
         for (int off = 1; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off));
         if (lane == 0) a.range[2 * c + wave] = most;
     }
-    if (level == 0 && chunk == 0) {
+    if (a.look && level == 0 && chunk == 0) {
         for (int col = wave; col < a.pitch; col += 4) {
             uint32_t any = 0;
             for (int i = lane; i < a.gather_parts; i += 64) any |= a.varying_part[((size_t)c * kRangeParts + i) * a.pitch + col];
@@ -989,7 +993,8 @@ __device__ __forceinline__ int32_t key_row(uint64_t key) { return (int32_t)(key 
 // value and bucket (rows that are equal there stay in row order).  Of the value only the bits from the first to the last one in
 // which the column's values differ are looked at (SortDigits): whole numbers, bfloat16 and quantised values have few, and the
 // launches of the digits that a column does not have end at once (a level of 260100 windows of an image, 4 codebooks: 165 -> 104 us;
-// finding the bits out takes 5 to 11 us once).  A workgroup takes up to 4096 keys at a time (8192 by sort_round_kernel),
+// finding the bits out and going by them costs data that uses all bits 2 to 4 per cent below 100000 rows: 20000 rows of 28 columns, 4 codebooks, 548 and 570,
+// whole numbers 541 and 487).  A workgroup takes up to 4096 keys at a time (8192 by sort_round_kernel),
 // an eighth of them in a row to a wavefront: a key's place among its wavefront's of the same digit comes from nine ballots and a counter in LDS, the
 // place of the wavefronts' from those counters, and the keys go through LDS in the digit's order, so that what is written
 // are runs.  Up to kSortRound rows are sorted by one launch (sort_round_kernel); more take two a digit: sort_count_kernel counts the
@@ -1147,7 +1152,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void sort_round_kernel(const Learn
         const int p = min(64 * (wave * per_wave + i) + lane, N - 1);
         key[i] = make_key(node[p], x[(int64_t)p * a.pitch], (uint32_t)p);
     }
-    SortDigits digits(a.varying[(size_t)c * a.pitch + col], n_buckets);
+    SortDigits digits(a.look ? a.varying[(size_t)c * a.pitch + col] : ~0u, n_buckets);
     for (int k = 0; k < digits.count; ++k) {
         digits.select(k);
 #pragma unroll
@@ -1202,8 +1207,12 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const LearnArg
     if (q >= min(kCand, d)) return;
     counts[tid] = 0;
     const int64_t chunk_rows = sort_chunk_rows(a.N), first = chunk * chunk_rows, end = min(a.N, first + chunk_rows);
-    const int col = k == 0 ? sort_column(a, c, q, d, n_buckets, chunk == 0, &shared) : a.cand[c * kCand + q];
-    SortDigits digits(a.varying[(size_t)c * a.pitch + col], n_buckets);
+    // (the bits of the column are left beside it, where the launches after the first find them without the column's number)
+    const int col = k == 0 ? sort_column(a, c, q, d, n_buckets, chunk == 0, &shared) : 0;
+    uint32_t varying = ~0u;
+    if (a.look) varying = k == 0 ? a.varying[(size_t)c * a.pitch + col] : a.cand_varying[c * kCand + q];
+    if (k == 0 && chunk == 0 && tid == 0) a.cand_varying[c * kCand + q] = varying;
+    SortDigits digits(varying, n_buckets);
     if (k >= digits.count) return;
     digits.select(k);
     uint64_t *keys = const_cast<uint64_t *>(sort_source(a, c, q, k, digits.count));
@@ -1248,7 +1257,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void sort_scatter_kernel(const Lea
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (q >= a.n_cand[c]) return;
     const int64_t chunk_rows = sort_chunk_rows(a.N), first = chunk * chunk_rows, end = min(a.N, first + chunk_rows);
-    SortDigits digits(a.varying[(size_t)c * a.pitch + a.cand[c * kCand + q]], n_buckets);
+    SortDigits digits(a.look ? a.cand_varying[c * kCand + q] : ~0u, n_buckets);
     if (k >= digits.count) return;
     digits.select(k);
     const uint64_t *keys = sort_source(a, c, q, k, digits.count);
@@ -2762,6 +2771,7 @@ void carve_trees(Carver &w, LearnArgs &a)
     a.range = w.take<int32_t>(2 * C);
     a.varying_part = w.take<uint32_t>(C * kRangeParts * a.pitch);
     a.varying = w.take<uint32_t>(C * a.pitch);
+    a.cand_varying = w.take<uint32_t>(C * kCand);
     a.col_loss = w.take<double>(C * kSplitBuckets * a.dmax);
     a.bucket_count = w.take<int64_t>(C * kSplitBuckets);
     a.bucket_start = w.take<int32_t>(C * kSplitBuckets);
@@ -2892,7 +2902,9 @@ static int launch_learn_batch(LearnArgs a, const int32_t *bounds_host, void *wor
 
     const int64_t pieces = (N + 1) * (a.pitch / 4);
     a.gather_parts = (int32_t)std::min<int64_t>((pieces + 255) / 256, kRangeParts);
-    hipLaunchKernelGGL(gather_columns_kernel, dim3((unsigned)a.gather_parts, C), dim3(256), 0, stream, a);
+    a.look = N > kSortThreads && 256 % (a.pitch / 4) == 0 ? 1 : 0;
+    if (a.look) hipLaunchKernelGGL(gather_columns_kernel<true>, dim3((unsigned)a.gather_parts, C), dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(gather_columns_kernel<false>, dim3((unsigned)a.gather_parts, C), dim3(256), 0, stream, a);
     LAUNCH_OK("launch gather_columns_kernel");
 
     for (int level = 0; level < 4; ++level) {

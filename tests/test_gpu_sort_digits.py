@@ -9,7 +9,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,widths", [(700, [7, 8, 3]), (8192, [16, 5]), (8193, [6, 8]), (9001, [48]), (12000, [20, 4])], ids=str)
+@pytest.mark.parametrize("N,widths", [(512, [8, 3]), (513, [8, 16]), (700, [7, 8, 3]), (8192, [16, 5]), (8193, [6, 8]), (9001, [48]), (12000, [20, 4])], ids=str)
 def test_trees_of_columns_with_few_bits(N, widths):
     import torch
     import paper_2106_10860_amd as mad
