@@ -40,6 +40,11 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+def scans_on_matrix_cores(kernel_name: str) -> bool:
+    """Whether the exact scan of the kernel that maddness_last_kernel() names runs on the matrix cores."""
+    return kernel_name.startswith(("fused_mfma_kernel", "mfma_scan_kernel", "fused_blocks_kernel, A by", "fused_blocks_kernel, scan"))
+
+
 def committed_traffic(workload_name: str):
     """HBM bytes per launch of the fused kernel as measured with rocprofv3 --pmc (FETCH_SIZE /
     WRITE_SIZE runs, scaled by a copy kernel of known size) and where that figure comes from:
@@ -191,7 +196,7 @@ def run_workload(args, workload: int, steps: int, warmup: int, rows: int, with_c
     algo_bytes = bytes_per_row * N
     achieved = algo_bytes / (kernel_avg_ms * 1e-3) / 1e9
     traffic, traffic_source = committed_traffic(w.name) if N == w.N else (None, None)
-    on_matrix_cores = "mfma" in kernel_name
+    on_matrix_cores = scans_on_matrix_cores(kernel_name)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "traffic_source": traffic_source,
                 "kernel": kernel_name + " (fused encode+scan, the only kernel of a step; name as reported by "

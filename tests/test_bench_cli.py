@@ -1,5 +1,6 @@
 """Host-side behaviour of bench.py and the entry module that needs no GPU."""
 import os
+import re
 import subprocess
 import sys
 
@@ -20,6 +21,19 @@ def test_bench_line_fields_are_declared():
                 "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline", "bound", "achieved", "peak", "frac",
                 "traffic", "cores", "kind", "sample"):
         assert f'"{key}"' in text, key
+
+
+def test_route_of_a_kernel():
+    sys.path.insert(0, ROOT)
+    from bench import scans_on_matrix_cores
+    csrc = os.path.join(ROOT, "paper_2106_10860_amd", "csrc")
+    names = {m for f in os.listdir(csrc) if f.endswith(".hip")
+             for m in re.findall(r'note_kernel\("([^"]+)"', open(os.path.join(csrc, f)).read())}
+    on = {n for n in names if scans_on_matrix_cores(n)}
+    assert {n for n in names if "blocks" in n} - on == {"fused_blocks_kernel, averages", "fused_blocks_kernel, codes of rows",
+                                                        "fused_blocks_kernel, codes of columns"}
+    assert {n for n in names if "mfma" in n} <= on
+    assert not any(n.startswith(("rows_kernel", "cols_kernel", "scan_kernel", "encode_kernel", "tiled_rows_kernel")) for n in on)
 
 
 def test_nothing_committed_reads_the_working_folder_or_the_paper_copy():
