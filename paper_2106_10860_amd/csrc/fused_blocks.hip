@@ -14,8 +14,8 @@
 //      first operand: a lane ends up with four consecutive columns of one row and stores them at once.  The next chunk's
 //      rows are on their way meanwhile.
 // Bound by latencies and by the 64 bytes a clock that a compute unit takes in: N = 10000, D = 512, M = 100, C = 32, of 9.1 us
-// (11.5 by rows_kernel) the launch takes 1.8, asking for 133 KiB and having them 3.8, the codes 0.9, the tables' way through LDS
-// 1.2 and the scan 1.2.  16 wavefronts to a workgroup were slower (11.6), as were two workgroups to a compute unit
+// (11.5 by rows_kernel) the launch takes 1.7, asking for 133 KiB and having them 3.9, the codes 0.9, the tables' way through LDS
+// 1.2 and the scan 1.4 (the 100 MHz clock in the first wavefront of every workgroup; vector ALUs busy 23 %, LDS 19 %, matrix cores 4 %).  16 wavefronts to a workgroup were slower (11.6), as were two workgroups to a compute unit
 // where one chunk is all the work (11.6), and lanes that read neighbouring codes instead of neighbouring columns of the tables (64
 // lines to a load: N = 676, D = 352, M = 737, C = 32 12.4 us, now 6.8).
 // From the first row on: a single request takes what a launch and this chain take, there and here, us: N = 2, D = 240, M = 60, C = 48 7.2 and 4.7, N = 7, D = 75, M = 577, C = 15
