@@ -812,8 +812,9 @@ bool scan_blocks_pay(const BlockArgs &a, int64_t ldo, int KC, int64_t turns)
         if (C <= 8) return M <= 5 ? a.N <= (1 << 15) : M <= 12 || !regular || results < (3 << 20);
         if (a.unit == 1 && M <= 3) return turns <= 4;
         // (and of more than 48 codebooks, whose chunks are 64 rows: N = 133462, M = 12, C = 61 18.9 and 25.2, N = 1519685, M = 7, C = 60 0.53 times, N = 41505, M = 8, C = 54 0.78, N = 31202,
-        // M = 16, C = 53 1.30)
-        if (a.unit == 1 && C > 48) return turns <= 2;
+        // M = 16, C = 53 1.30; results that the general kernel does not add four to a word keep them to where both take as long: N = 134422, M = 10, C = 50 27.8 and 19.1, N = 127361, M = 9,
+        // C = 51 28.1 and 19.4; 300000 to 500000 rows 0.99, more 0.77)
+        if (a.unit == 1 && C > 48) return turns <= 2 || (M > 8 && M != 12 && a.N <= 300000);
         // N = 334, M = 10, C = 8 4.8 and 4.1; N = 1515582, M = 3, C = 48 100 and 37; N = 2339262, M = 16, C = 15 116 and 43; N = 760602, M = 16, C = 32
         // 25 and 17.  40, 56 and 64 codebooks: N = 90821, M = 10, C = 64 13.1 and 7.3 (2 turns), N = 1231121, M = 8 41 and 51 (10).
         return C <= 32 || C == 48 || !regular || turns <= (C == 56 ? 1 : 3);

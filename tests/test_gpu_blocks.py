@@ -204,11 +204,12 @@ SCANS = [
     (4000, 785, 30, 0, 0, 0), (20000, 20, 31, 3, 0, 0), (10007, 128, 32, 0, 0, 0), (70001, 16, 32, 0, 0, 0), (129, 77, 40, 0, 0, 0),
     (3001, 300, 48, 0, 0, 0), (140000, 3, 48, 0, 0, 0), (2000, 100, 56, 0, 0, 0), (9001, 36, 63, 0, 2, 0), (140001, 10, 64, 0, 0, 0),
     (67584, 12, 61, 0, 0, 0), (300001, 20, 15, 0, 0, 0), (60000, 250, 30, 2, 0, 0), (14000, 1000, 15, 0, 0, 0), (33, 514, 64, 0, 0, 0),
+    (300000, 10, 50, 0, 0, 0),
 ]
 
 
 # those that other kernels take faster
-SCANS_LEFT = [(67585, 12, 61, 0, 0, 0), (600000, 2, 30, 0, 0, 0), (600000, 10, 40, 0, 0, 0)]
+SCANS_LEFT = [(67585, 12, 61, 0, 0, 0), (600000, 2, 30, 0, 0, 0), (600000, 10, 40, 0, 0, 0), (300001, 10, 50, 0, 0, 0)]
 
 
 @pytest.mark.parametrize("case", SCANS + SCANS_LEFT, ids=lambda c: "N%d_M%d_C%d_p%d_c%d_t%d" % c)
