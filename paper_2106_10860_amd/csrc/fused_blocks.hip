@@ -1037,7 +1037,10 @@ int launch_averaged_blocks(const maddness_params &p, const MatrixA &A, int64_t N
     const int64_t rows = (share + turns - 1) / turns;
     if (N / rows >= (1 << 30)) return 1;
     const bool held = C == 32 && p.D <= 512 && p.D % 4 == 0 && whole && maddness::rows::tables_ok(C, M, luts, scale, offset, out, ldo, acc);
-    if (turns > 1 && (held || (a.col_blocks > 1 && (C != 32 ? turns > 16 : turns > 64 && a.row_bytes >= 1024)))) return 1;
+    // (to 100 turns for up to 90000 rows by four blocks of columns or more, beside which the general kernel walks most tables: N = 46431, D = 863, M = 1000 329 and 252 (81),
+    // N = 34478, D = 1361, M = 793 374 and 262 (90), N = 19214, D = 1834, M = 847 365 and 141 (76), N = 82756, D = 1024, M = 531 327 and 334 (108); N = 124436, D = 512, M = 556 232 and 301 (82))
+    const int64_t most_turns = a.col_blocks >= 4 && N < 90000 ? 100 : 64;
+    if (turns > 1 && (held || (a.col_blocks > 1 && (C != 32 ? turns > 16 : turns > most_turns && a.row_bytes >= 1024)))) return 1;
     a.chunk_rows = (int)rows;
     a.chunks = (int)((N + rows - 1) / rows);
     groups = std::min<int64_t>(groups, a.chunks);

@@ -149,10 +149,10 @@ AVERAGES = [
     (1, 64, 128, 16, 0, 0, 0), (2, 512, 31, 64, 0, 1, 0), (15, 100, 300, 32, 1, 0, 1),
     (16, 64, 1, 16, 0, 0, 0), (33, 100, 31, 64, 0, 1, 3), (700, 512, 100, 32, 0, 0, 0), (300, 64, 1000, 48, 4, 0, 1),
     (1025, 333, 129, 32, 1, 0, 0), (2048, 1024, 130, 64, 0, 0, 0), (4100, 128, 257, 16, 0, 3, 2), (20001, 256, 60, 32, 0, 0, 0),
-    (9845, 1024, 128, 64, 0, 0, 0), (30000, 64, 300, 16, 0, 0, 0), (65536, 2048, 130, 32, 0, 0, 0),
+    (9845, 1024, 128, 64, 0, 0, 0), (30000, 64, 300, 16, 0, 0, 0), (65536, 2048, 130, 32, 0, 0, 0), (20000, 2040, 900, 32, 0, 0, 0),
 ]
-# a turn more of long rows, which the general kernel takes faster
-AVERAGES_LEFT = [(65537, 2048, 130, 32, 0, 0, 0)]
+# more turns of long rows, which the general kernel takes faster
+AVERAGES_LEFT = [(65537, 2048, 130, 32, 0, 0, 0), (27000, 2040, 900, 32, 0, 0, 0)]
 
 
 @pytest.mark.parametrize("case", AVERAGES + AVERAGES_LEFT, ids=lambda c: "N%d_D%d_M%d_C%d_p%d_o%d_t%d" % c)
