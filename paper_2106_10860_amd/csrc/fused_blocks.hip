@@ -1166,8 +1166,9 @@ int launch_encode_blocks(const maddness_params &p, const MatrixA &A, int64_t N, 
     // N = 14754, C = 24 6.4 and 4.6; the other types, which take longer there, from where the rows here make two workgroups to a compute unit: bytes N = 1887, C = 20 3.5 and 2.9,
     // N = 4702, C = 3 3.2 and 3.7, N = 14523, C = 6 3.5 and 3.7, N = 7210, C = 19 4.1 and 3.7), but for powers of two, where there every lane has a pair of codebooks and workgroups are
     // fewest (N = 240, D = 64, C = 8 3.3 and 2.6, N = 72, C = 32 3.0 and 2.7; from there on N = 4796, C = 8 2.8 and 3.6, binary16 N = 2173, C = 16 3.7 and 3.4).
+    // (fp32 N = 16500 to 24500, C = 8 5.3 and 4.0, C = 16, 32 and 64 1.06 times, below 128 Ki codes 0.83)
     const bool few = N <= 8 * dev.cus, power = C >= 8 && (C & (C - 1)) == 0;
-    if (A.dtype == MADDNESS_F32 ? N * C < (192 << 10) && !(few && power) : N * C < (88 << 10) && !few && !power) return 1;
+    if (A.dtype == MADDNESS_F32 ? N * C < ((power ? 128 : 192) << 10) && !(few && power) : N * C < (88 << 10) && !few && !power) return 1;
     // (whole rows are read here, 64 bytes for each split value there: N = 20680, D = 512, C = 4, binary16 5.8 and 6.1)
     const int64_t most = (32 * 1024 - (whole ? 0 : 16)) / a.pitch;
     if (most < 1 || a.row_bytes > 192 * C) return 1;

@@ -264,11 +264,13 @@ CODES = [
     (30001, 97, 24, "f32", True, 0, 0), (120001, 120, 30, "f16", True, 1, 0), (10001, 190, 48, "f32", True, 0, 1), (70001, 252, 63, "u8", True, 0, 0),
     (70, 40, 8, "f32", False, 0, 0), (13108, 60, 15, "f32", False, 0, 0), (2048, 90, 20, "u8", False, 0, 0), (4506, 90, 20, "u8", False, 0, 0),
     (100001, 27, 3, "f32", False, 0, 1), (8192, 60, 15, "f32", True, 0, 0), (9216, 100, 25, "f32", True, 0, 0), (2048, 64, 8, "f32", False, 0, 0), (4608, 100, 23, "u8", True, 0, 0),
+    (16384, 64, 8, "f32", False, 0, 0),
 ]
 # as many codes and fewer, for which the general kernel is the faster one
 FEW_CODES = [
     (16, 27, 5, "f32", False, 0, 0), (13107, 60, 15, "f32", False, 0, 0), (2049, 90, 20, "u8", False, 0, 0), (4505, 90, 20, "u8", False, 0, 0),
     (8191, 60, 15, "f32", True, 0, 0), (9215, 100, 25, "f32", True, 0, 0), (2049, 64, 8, "f32", False, 0, 0), (4607, 100, 23, "u8", True, 0, 0), (262145, 40, 12, "f32", True, 0, 0),
+    (16383, 64, 8, "f32", False, 0, 0),
 ]
 
 
